@@ -325,6 +325,7 @@ int32_t fc_focused_conv2d(const fc_conv_desc *desc, const void *x, const uint8_t
         partials = (float *)((uint8_t *)workspace + l.partials);
     }
     bool counters_cleared = false;
+    const bool f32 = desc->in_dtype == FC_F32 && conv_f32_supported(g);
 
     if (mask_in && !idx) {
         // derive mask_out, the index list and its length here, in the workspace
@@ -337,7 +338,8 @@ int32_t fc_focused_conv2d(const fc_conv_desc *desc, const void *x, const uint8_t
         // kernel (16 positions per thread, labels from the centre tap): no compaction launch.
         // Labels the caller brings (mask_out without a list) are compacted as they are, so that
         // the rows computed and the rows cleared follow the same labels.
-        const bool rank_in_kernel = mfma && g.m <= kInlineRankPositions && !mask_out;
+        // fp32 layers label and compact their rows inside the convolution kernel whatever their size.
+        const bool rank_in_kernel = f32 || (mfma && g.m <= kInlineRankPositions && !mask_out);
         if (!rank_in_kernel) {
             CompactExtras ex;
             if (tile_counters) {
@@ -386,12 +388,14 @@ int32_t fc_focused_conv2d(const fc_conv_desc *desc, const void *x, const uint8_t
                              partials, tile_counters, s);
         if (e != hipSuccess) return FC_ERR_HIP;
     } else {
-        if (conv_stem_supported(g, desc->in_dtype, desc->out_dtype))
+        if (f32)
+            e = launch_conv_f32(g, x, mask_in, mask_out, w, bias, idx, count, out, s);
+        else if (conv_stem_supported(g, desc->in_dtype, desc->out_dtype))
             e = launch_conv_stem(g, desc->in_dtype, desc->out_dtype, x, mask_in, w, bias, idx, count, out, s);
         else
             e = launch_conv_direct(g, desc->in_dtype, desc->out_dtype, x, mask_in, w, bias, idx, count, out, s);
         if (e != hipSuccess) return FC_ERR_HIP;
-        if (mask_in && !(g.flags & FC_SKIP_ZERO_FILL)) {
+        if (mask_in && !(f32 && !idx) && !(g.flags & FC_SKIP_ZERO_FILL)) {
             e = launch_zero_fill(g, mask_in, mask_out, out, desc->out_dtype, s);
             if (e != hipSuccess) return FC_ERR_HIP;
         }
@@ -422,10 +426,15 @@ int32_t fc_focused_gconv2d(const fc_conv_desc *desc, int32_t groups, const void 
     if (!aligned16(x) || !aligned16(w) || !aligned16(out) || !aligned16(idx) || !aligned16(bias)) return FC_ERR_ALIGN;
     if (conv_tensors_overlap(g, desc, x, out)) return FC_ERR_NULL;
     hipStream_t s = (hipStream_t)stream;
+    const bool matrix = conv_grouped_supported(g, groups, desc->in_dtype, desc->out_dtype);
+    const bool own_rows = matrix && mask_in && !idx; // the kernel labels, compacts and clears by itself
     if (mask_in && !idx) {
         const ConvWorkspace l = conv_ws_layout(g);
         if (!workspace || workspace_bytes < l.total) return FC_ERR_WORKSPACE;
         if (!aligned16(workspace)) return FC_ERR_ALIGN;
+    }
+    if (mask_in && !idx && !own_rows) {
+        const ConvWorkspace l = conv_ws_layout(g);
         uint8_t *ws = (uint8_t *)workspace;
         const MaskGeom mg = mask_geom(g.n, g.h, g.w, g.kh, g.kw, g.sh, g.sw, g.ph, g.pw, g.dh, g.dw, g.ho, g.wo);
         hipError_t ec;
@@ -451,10 +460,12 @@ int32_t fc_focused_gconv2d(const fc_conv_desc *desc, int32_t groups, const void 
     Geom one = g; // the geometry of one group
     one.c_in = g.c_in / groups;
     one.c_out = g.c_out / groups;
-    hipError_t e = launch_conv_direct(one, desc->in_dtype, desc->out_dtype, x, mask_in, w, bias, idx, count, out, s,
-                                      groups);
+    hipError_t e = matrix ? launch_conv_grouped(g, groups, desc->in_dtype, desc->out_dtype, x, mask_in, mask_out, w, bias,
+                                                idx, count, out, s)
+                          : launch_conv_direct(one, desc->in_dtype, desc->out_dtype, x, mask_in, w, bias, idx, count, out,
+                                               s, groups);
     if (e != hipSuccess) return FC_ERR_HIP;
-    if (mask_in && !(g.flags & FC_SKIP_ZERO_FILL)) {
+    if (mask_in && !own_rows && !(g.flags & FC_SKIP_ZERO_FILL)) {
         e = launch_zero_fill(g, mask_in, mask_out, out, desc->out_dtype, s);
         if (e != hipSuccess) return FC_ERR_HIP;
     }

@@ -167,6 +167,21 @@ __device__ __forceinline__ uint32_t kept_flags16(const MaskGeom &g, const uint8_
     return flags;
 }
 
+// label of output position p: its mask_out entry, or the input mask under its centre tap
+__device__ __forceinline__ bool position_kept(const Geom &g, const uint8_t *__restrict__ mask_in,
+                                              const uint8_t *__restrict__ mask_out, int64_t p)
+{
+    const bool packed = (g.flags & FC_PACKED_MASKS) != 0;
+    if (mask_out) return mask_at(mask_out, p, packed);
+    const uint32_t t = (uint32_t)p / (uint32_t)g.wo; // (position counts fit 31 bits)
+    const int ow = (int)((uint32_t)p - t * (uint32_t)g.wo);
+    const int b = (int)(t / (uint32_t)g.ho);
+    const int oh = (int)(t - (uint32_t)b * (uint32_t)g.ho);
+    int ih = min(max(oh * g.sh - g.ph + g.dh * ((g.kh - 1) / 2), 0), g.h - 1);
+    int iw = min(max(ow * g.sw - g.pw + g.dw * ((g.kw - 1) / 2), 0), g.w - 1);
+    return mask_at(mask_in, (int64_t)(b * g.h + ih) * g.w + iw, packed);
+}
+
 // inclusive prefix sum over the 64 lanes of a wave, on the cross-lane data path of the
 // vector ALU (no LDS traffic): shifts by 1, 2, 4, 8 inside each row of 16 lanes, then the last
 // lane of row 0 / row 2 is broadcast into row 1 / row 3, then lane 31 into rows 2 and 3.
@@ -243,6 +258,17 @@ hipError_t launch_maxpool(const void *x, int n, int h, int w, int c, int dtype, 
 hipError_t launch_conv_direct(const Geom &g, int in_dtype, int out_dtype, const void *x,
                               const uint8_t *mask_in, const void *w, const float *bias,
                               const int32_t *idx, const int32_t *count, void *out, hipStream_t s, int groups = 1);
+
+// fp32 storage and grouped layers of 16-bit storage on the matrix cores (see fc_conv_reg.hip).  With a
+// mask and no list the kernels label positions themselves (from mask_out, or the centre tap of mask_in)
+// and clear the irrelevant rows; with a list the caller clears them.
+bool conv_f32_supported(const Geom &g);
+hipError_t launch_conv_f32(const Geom &g, const void *x, const uint8_t *mask_in, const uint8_t *mask_out, const void *w,
+                           const float *bias, const int32_t *idx, const int32_t *count, void *out, hipStream_t s);
+bool conv_grouped_supported(const Geom &g, int groups, int in_dtype, int out_dtype);
+hipError_t launch_conv_grouped(const Geom &g, int groups, int in_dtype, int out_dtype, const void *x, const uint8_t *mask_in,
+                               const uint8_t *mask_out, const void *w, const float *bias, const int32_t *idx,
+                               const int32_t *count, void *out, hipStream_t s);
 
 // Depthwise layer (one filter per channel); labels positions from mask_in itself and clears
 // the irrelevant rows.

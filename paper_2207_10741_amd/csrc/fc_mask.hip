@@ -559,20 +559,6 @@ hipError_t launch_mask_pack(const uint8_t *mask, int64_t m, uint64_t *bits, hipS
 // ---------------------------------------------------------------------------
 // Zero-fill of the irrelevant output rows: a lane owns 16 bytes of one row.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ bool position_kept(const Geom &g, const uint8_t *__restrict__ mask_in,
-                                              const uint8_t *__restrict__ mask_out, int64_t p)
-{
-    const bool packed = (g.flags & FC_PACKED_MASKS) != 0;
-    if (mask_out) return mask_at(mask_out, p, packed);
-    const uint32_t t = (uint32_t)p / (uint32_t)g.wo; // (position counts fit 31 bits)
-    const int ow = (int)((uint32_t)p - t * (uint32_t)g.wo);
-    const int b = (int)(t / (uint32_t)g.ho);
-    const int oh = (int)(t - (uint32_t)b * (uint32_t)g.ho);
-    int ih = min(max(oh * g.sh - g.ph + g.dh * ((g.kh - 1) / 2), 0), g.h - 1);
-    int iw = min(max(ow * g.sw - g.pw + g.dw * ((g.kw - 1) / 2), 0), g.w - 1);
-    return mask_at(mask_in, (int64_t)(b * g.h + ih) * g.w + iw, packed);
-}
-
 // Rows of whole 16-byte pieces: a wave looks at 64 positions at a time (one label each), lists
 // the irrelevant ones in LDS in order, and then all its lanes store 16-byte pieces of those
 // rows, so the stores are dense and none of them waits for a label.  The labels of the next 64

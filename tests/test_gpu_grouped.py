@@ -121,3 +121,18 @@ def test_expanded_group_weights_run_the_grouped_layer_on_the_full_layer_path(lay
                              bias=bias, mask_in=mask, dtype=dtype)
     keep = O.mask_downsample(mask, k, k, (s_, s_), (p, p)) != 0
     assert G.rel_err(G.to_f64(out), want, keep) <= (5e-4 if dtype == synth.FP8 else TOL_F32_OUT)
+
+
+@pytest.mark.parametrize("layer", [
+    # channels per group in and out, around the 16-channel blocks of the matrix-core form: 4 -> 4 (four groups a
+    # block), 8 -> 8, 4 -> 8, 16 -> 16, 32 -> 32, 64 -> 64 (the longest reduction it takes), 8 -> 48 (three blocks
+    # a group), a block count that does not fill the last workgroup, 5x5, and shapes it leaves to the direct kernel
+    (1, 9, 15, 16, 16, 3, 1, 1, 4), (2, 13, 11, 64, 64, 3, 2, 1, 8), (1, 17, 8, 32, 64, 3, 1, 1, 8),
+    (1, 16, 8, 80, 80, 3, 1, 1, 5), (1, 12, 13, 96, 96, 3, 1, 1, 3), (1, 10, 9, 128, 128, 3, 1, 1, 2),
+    (1, 11, 12, 32, 192, 1, 1, 0, 4), (1, 14, 10, 48, 48, 5, 1, 2, 12), (1, 9, 9, 128, 128, 5, 1, 2, 2),
+    (1, 8, 8, 24, 24, 3, 1, 1, 4)])
+@pytest.mark.parametrize("mask_kind,precomputed", [("objects", False), ("bernoulli", True), (None, False)])
+def test_grouped_layer_channel_blocks(layer, mask_kind, precomputed):
+    out, want, keep = _run(layer, synth.BF16, B.F32, mask_kind=mask_kind, irr=0.4, precomputed=precomputed)
+    assert G.rel_err(G.to_f64(out), want, keep) <= TOL_F32_OUT
+    assert not out.cpu().numpy()[~keep].view(np.uint32).any()

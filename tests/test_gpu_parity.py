@@ -646,3 +646,21 @@ def test_issue_probe_runs_and_counts_cycles():
     with pytest.raises(B.FcError):
         B.calibrate_issue(0, 3, 10, 1, src)
 
+
+
+@pytest.mark.parametrize("layer", [
+    # n, h, w, ci, co, k, s, p, d: channel counts around the 16-channel steps and the 32-channel blocks,
+    # positions around the 32- and 128-position spans, tap counts up to 64, and a layer with enough rows
+    # that a wave takes a whole reduction
+    (1, 5, 7, 1, 1, 3, 1, 1, 1), (2, 9, 13, 3, 5, 3, 1, 1, 1), (1, 8, 4, 15, 31, 1, 1, 0, 1), (1, 11, 3, 16, 33, 3, 2, 1, 1),
+    (3, 17, 15, 17, 64, 3, 1, 2, 2), (1, 30, 17, 24, 65, 5, 1, 2, 1), (2, 13, 9, 9, 12, 7, 1, 3, 1), (1, 16, 16, 4, 8, 8, 1, 3, 1),
+    (4, 96, 97, 12, 40, 3, 1, 1, 1), (3, 90, 91, 21, 96, 1, 1, 0, 1), (3, 120, 130, 8, 64, 3, 1, 1, 1)])
+@pytest.mark.parametrize("mask_kind,precomputed", [("objects", False), ("bernoulli", True), ("bernoulli", False), (None, False)])
+def test_fp32_storage_on_the_matrix_cores(layer, mask_kind, precomputed):
+    out, want, keep = _run_layer(*layer, synth.F32, irr=0.4, mask_kind=mask_kind, precomputed=precomputed, seed=231)
+    assert G.rel_err(G.to_f64(out), want, keep) <= 1e-5
+    assert not out.cpu().numpy()[~keep].view(np.uint32).any()
+    left, _, _ = _run_layer(*layer, synth.F32, irr=0.4, mask_kind=mask_kind, precomputed=precomputed, seed=231,
+                            flags_extra=B.SKIP_ZERO_FILL)
+    got = left.cpu().numpy()
+    assert (got[~keep] == 7.0).all() and np.array_equal(got[keep], out.cpu().numpy()[keep])
