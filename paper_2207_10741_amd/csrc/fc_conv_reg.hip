@@ -1,5 +1,5 @@
-// Focused convolution whose matrix operands go straight from global memory into registers:
-// fp32 storage (any channel counts) and grouped layers of 16-bit storage.
+// Focused convolution of fp32 storage (any channel counts from four on) and of grouped layers of 16-bit
+// storage, on the matrix cores.
 //
 // Sec. III-A as everywhere: rows = kept positions, columns = output channels, reduction = taps
 // x input channels, gated taps read as zero.  What these two layer types have in common is
@@ -26,6 +26,7 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
 
 constexpr int kRegThreads = 256;
 constexpr int kMaxSpan = 128;
+constexpr int kGroupedSpan = 64;
 
 // The rows of one workgroup's span, in LDS.
 struct SpanRows {
@@ -94,13 +95,27 @@ __device__ __forceinline__ void span_rows(const Geom &g, const uint8_t *__restri
     __syncthreads();
     // one thread per (row, tap): inside the image and relevant?
     const int taps = g.kh * g.kw;
-    for (int i = tid; i < n * taps; i += kRegThreads) {
-        const int r = (int)((uint32_t)i / (uint32_t)taps), t = i - r * taps;
-        const int kh = (int)((uint32_t)t / (uint32_t)g.kw), kw = t - kh * g.kw;
-        const int ih = (int)(int16_t)(s.hw[r] & 0xffff) + kh * g.dh, iw = (s.hw[r] >> 16) + kw * g.dw;
-        bool ok = ih >= 0 && ih < g.h && iw >= 0 && iw < g.w;
-        if (ok && mask_in) ok = mask_at(mask_in, (int64_t)(s.img[r] * g.h + ih) * g.w + iw, packed);
-        if (ok) atomicOr(&s.bits[t >> 5][r], 1u << (t & 31));
+    constexpr int U = 3; // look-ups of a thread in flight together
+    for (int i0 = tid; i0 < n * taps; i0 += U * kRegThreads) {
+        int row[U], tp[U], pix[U];
+        uint8_t rel[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = i0 + u * kRegThreads;
+            const bool some = i < n * taps;
+            const int r = some ? (int)((uint32_t)i / (uint32_t)taps) : 0, t = some ? i - r * taps : 0;
+            const int kh = (int)((uint32_t)t / (uint32_t)g.kw), kw = t - kh * g.kw;
+            const int ih = (int)(int16_t)(s.hw[r] & 0xffff) + kh * g.dh, iw = (s.hw[r] >> 16) + kw * g.dw;
+            const bool ok = some && ih >= 0 && ih < g.h && iw >= 0 && iw < g.w;
+            row[u] = r;
+            tp[u] = t;
+            pix[u] = ok ? (s.img[r] * g.h + ih) * g.w + iw : -1;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) rel[u] = mask_in ? (uint8_t)mask_at(mask_in, max(pix[u], 0), packed) : (uint8_t)1;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (pix[u] >= 0 && rel[u]) atomicOr(&s.bits[tp[u] >> 5][row[u]], 1u << (tp[u] & 31));
     }
     __syncthreads();
     *nrows = n;
@@ -132,20 +147,25 @@ __device__ __forceinline__ void clear_dropped(const SpanRows &s, int ndrop, TO *
 // fp32 storage.  Bound: the fp32 matrix rate (157 TFLOP/s) on large layers, the set-up's chain of
 // dependent loads on small ones.
 //
-// A wave owns 32 rows x NB * 32 output channels.  One step = 16 input channels of one tap: lane
-// (row, half) holds channels 4 * half .. + 3 of each 8-channel piece of its row as one 16-byte load,
-// and the four elements feed four matrix instructions whose reduction pair is (element e of the
-// lower half, element e of the upper half); both operands are loaded the same way, so the
-// pairing of channels is the same.  Three register sets: the loads of step s + 2 are issued before
-// step s is multiplied.
+// One stage = 32 input channels (128 bytes) of one tap for the TM rows of the tile and its TN output
+// channels, gathered straight into a ring of NB LDS buffers (swizzled as everywhere, see
+// fc_dma_util.hpp).  Lane (row, half) of a wave reads the 16-byte piece 2 * kk + half of its row, and the
+// four elements feed four v_mfma_f32_32x32x2_f32 whose reduction pair is (element e of the lower half,
+// element e of the upper half); both operands are read the same way, so the pairing of
+// channels is the same.  (Operands loaded from global memory straight into registers need no
+// barrier but put every lane of a load on another line: 64 cycles of address work each, and the large
+// layers stop at 77 TFLOP/s.)
 //
-// KSPLIT: the four waves of a workgroup take the same 32 rows and a quarter of the reduction
-// each and add up in LDS, in wave order: a layer of a few hundred row blocks is then spread over
-// four times as many SIMDs (64 -> 64 on 2 x 60 x 80 positions, 48 % irrelevant: 66 us on
-// the vector ALUs with 5 us each of compaction and zero-fill).  Otherwise the waves take 32 rows
-// each of a 128-position span.
+// WK = 4: the four waves take the same 32 rows and every fourth kk of each stage, two stages
+// between barriers, and add up through LDS in wave order: a layer of a few hundred row blocks is spread
+// over four times as many SIMDs.  WK = 1: 32 rows of a 128-position span each.
+// TAIL: the input channels are not whole 32-channel stages.
+//
+// Measured (mask given, call included): 64 -> 64 on 2 x 60 x 80, half kept: 75.5 us on the vector ALUs
+// with a compaction and a zero-fill launch, 15.6 us; 128 -> 128 on 8 x 120 x 120 without a mask: 320 us =
+// 106 TFLOP/s.
 // ---------------------------------------------------------------------------------------------
-template <int NB, bool KSPLIT>
+template <int TN, int WK, int NB, bool TAIL>
 __global__ __launch_bounds__(kRegThreads, 2) void k_conv_f32(Geom g, const float *__restrict__ x,
                                                              const uint8_t *__restrict__ mask_in,
                                                              const uint8_t *__restrict__ mask_out,
@@ -154,85 +174,85 @@ __global__ __launch_bounds__(kRegThreads, 2) void k_conv_f32(Geom g, const float
                                                              const int32_t *__restrict__ idx,
                                                              const int32_t *__restrict__ count, float *__restrict__ out)
 {
-    constexpr int S = KSPLIT ? 32 : 128;
-    constexpr int NQ = NB * 4; // accumulator quads (4 channels of one position) per lane
+    constexpr int TM = WK == 4 ? 32 : 128;
+    constexpr int CB = TN / 32;              // 32-channel blocks of a wave
+    constexpr int XR = TM / 32, WR = TN / 32;// loads per thread and stage
+    constexpr int L = XR + WR;
+    constexpr int R = WK == 4 ? 2 : 1;       // stages between two barriers
+    constexpr uint32_t STAGE = (uint32_t)(TM + TN) * 128u;
+    static_assert(NB % R == 0 && NB >= 2 * R && NB * L <= 63, "vmcnt is a 6-bit counter");
+    static_assert(WK == 1 || NB * STAGE >= 4u * CB * 4u * 64u * 16u, "the partial sums fit the stage buffers");
+    __shared__ __align__(16) unsigned char stage[NB * STAGE];
     __shared__ SpanRows rows_s;
-    __shared__ float4 part[KSPLIT ? 4 * NQ * 64 : 1];
     const int rows = idx ? *count : g.m;
-    const int first = blockIdx.x * S;
+    const int first = blockIdx.x * TM;
     if (first >= rows) return;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5, l32 = lane & 31;
-    const int co0 = blockIdx.y * (NB * 32);
+    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int co0 = blockIdx.y * TN;
     int n, nd;
-    span_rows<S>(g, mask_in, mask_out, idx, rows, first, rows_s, &n, &nd);
-    if (nd && !(g.flags & FC_SKIP_ZERO_FILL))
-        clear_dropped<float>(rows_s, nd, out, g.c_out, co0, min(NB * 32, g.c_out - co0));
-    const int r0 = KSPLIT ? 0 : wave * 32;
-    if (r0 >= n) return; // (KSPLIT: the whole workgroup; otherwise nothing below waits for this wave)
+    span_rows<TM>(g, mask_in, mask_out, idx, rows, first, rows_s, &n, &nd);
+    if (nd && !(g.flags & FC_SKIP_ZERO_FILL)) clear_dropped<float>(rows_s, nd, out, g.c_out, co0, min(TN, g.c_out - co0));
+    if (n == 0) return;
 
     const int taps = g.kh * g.kw;
-    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<float *>(x), 0, (uint32_t)g.n * g.h * g.w * g.c_in * 4u, 0x00020000);
-    const __amdgpu_buffer_rsrc_t rw =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(w), 0, (uint32_t)g.c_out * taps * g.c_in * 4u, 0x00020000);
-    const int r = r0 + l32;
-    const bool live = r < n;
-    const uint32_t xbase = live ? (uint32_t)(rows_s.base[r] * g.c_in + half * 4) * 4u : 0u;
-    const uint64_t bits = live ? (rows_s.bits[0][r] | ((uint64_t)rows_s.bits[1][r] << 32)) : 0ull;
-    uint32_t wbase[NB];
-    bool wlive[NB];
+    // a row's offset is that of its first tap, which may lie in front of the tensor: x is read through a
+    // descriptor that starts a padding's worth earlier (those taps are switched off, nothing in front
+    // of the tensor is read), so that the per-lane part of an offset is never negative
+    const uint32_t xbias = (uint32_t)(g.ph * g.w + g.pw) * (uint32_t)g.c_in * 4u;
+    const u32x4_t rsrc_x = make_rsrc_words(reinterpret_cast<const unsigned char *>(x) - xbias,
+                                           (uint32_t)g.n * g.h * g.w * g.c_in * 4u + xbias);
+    const u32x4_t rsrc_w = make_rsrc_words(w, (uint32_t)g.c_out * taps * g.c_in * 4u);
+    // A row whose length is no multiple of four ends in a piece of its last four channels, of which the
+    // first `again` were already in the piece before it: they are cleared in both operands.  `edge` = first
+    // channel of that piece.
+    const int again = TAIL ? (4 - (g.c_in & 3)) & 3 : 0, edge = again ? g.c_in - 4 + again : -1;
+    const int cch = (g.c_in + 31) >> 5, stages = taps * cch;
+    const int last_steps = (g.c_in - (cch - 1) * 32 + 7) >> 3; // 8-channel steps of a tap's last stage
+    const int slot = tid & 7, prow = tid >> 3;
+    const int piece = slot ^ FC_SWZ(prow); // (the rows of a thread's loads differ by multiples of 32)
+    uint32_t xoff[XR], woff[WR];
+    uint32_t xbits[2][XR];
 #pragma unroll
-    for (int b = 0; b < NB; ++b) {
-        const int co = co0 + b * 32 + l32;
-        wlive[b] = co < g.c_out;
-        wbase[b] = (uint32_t)(co * taps * g.c_in + half * 4) * 4u;
+    for (int j = 0; j < XR; ++j) {
+        const int r = prow + j * 32;
+        const bool live = r < n;
+        xoff[j] = live ? (uint32_t)(rows_s.base[r] * g.c_in + piece * 4) * 4u + xbias : 0u;
+        xbits[0][j] = live ? rows_s.bits[0][r] : 0u;
+        xbits[1][j] = live ? rows_s.bits[1][r] : 0u;
     }
+#pragma unroll
+    for (int j = 0; j < WR; ++j) {
+        const int co = co0 + prow + j * 32;
+        woff[j] = co < g.c_out ? (uint32_t)(co * taps * g.c_in + piece * 4) * 4u : kOutOfRange;
+    }
+    const uint32_t lds0 =
+        __builtin_amdgcn_readfirstlane((uint32_t)reinterpret_cast<uintptr_t>(stage) + (uint32_t)wave * 1024u);
 
-    const int cch = (g.c_in + 15) >> 4, steps = taps * cch;
-    const int s0 = KSPLIT ? wave * steps / 4 : 0, s1 = KSPLIT ? (wave + 1) * steps / 4 : steps;
-    const bool by4 = (g.c_in & 3) == 0;
-    const int tail = g.c_in - (cch - 1) * 16; // channels of a tap's last step (1 .. 16)
-    // cursor of the next step to load
-    int tap = s0 / cch, cc = s0 - tap * cch, kh = tap / g.kw, kw = tap - kh * g.kw;
-
-    f32x16_t acc[NB];
+    // cursor of the next stage to load (stages past the end load zeros)
+    int tap = 0, cc = 0, kh = 0, kw = 0, ibuf = 0;
+    auto issue = [&]() __attribute__((always_inline)) {
+        const bool in_k = tap < taps;
+        uint32_t sx = in_k ? (uint32_t)((kh * g.dh * g.w + kw * g.dw) * g.c_in + cc * 32) * 4u : 0u;
+        uint32_t sw = in_k ? (uint32_t)(tap * g.c_in + cc * 32) * 4u : 0u;
+        sx = __builtin_amdgcn_readfirstlane(sx);
+        sw = __builtin_amdgcn_readfirstlane(sw);
+        __asm__("" : "+s"(sx), "+s"(sw)); // (registers, not constants: the load takes no literal there)
+        const uint32_t sel = in_k ? 1u << (tap & 31) : 0u;
+        const int ch = cc * 32 + piece * 4;
+        const bool in = !TAIL || ch < g.c_in;
+        const uint32_t back = TAIL && ch == edge ? (uint32_t)again * 4u : 0u;
+        const uint32_t to = lds0 + (uint32_t)ibuf * STAGE;
 #pragma unroll
-    for (int b = 0; b < NB; ++b)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[b][i] = 0.f;
-
-    u32x4_t xv[3][2], wv[3][NB][2];
-    auto load = [&](auto set_c) __attribute__((always_inline)) {
-        constexpr int st = decltype(set_c)::value;
-        const uint32_t sx = (uint32_t)((kh * g.dh * g.w + kw * g.dw) * g.c_in + cc * 16) * 4u;
-        const uint32_t sw = (uint32_t)(tap * g.c_in + cc * 16) * 4u;
-        const bool tap_ok = (bits >> tap) & 1u;
-        const int left = g.c_in - cc * 16 - half * 4; // channels from this lane's first one to the end
-        if (by4 || cc + 1 < cch) {
-#pragma unroll
-            for (int p = 0; p < 2; ++p) {
-                const bool in = p * 8 < left;
-                xv[st][p] = __builtin_amdgcn_raw_buffer_load_b128(rx, tap_ok && in ? xbase + sx + p * 32u : kOutOfRange, 0, 0);
-#pragma unroll
-                for (int b = 0; b < NB; ++b)
-                    wv[st][b][p] = __builtin_amdgcn_raw_buffer_load_b128(
-                        rw, wlive[b] && in ? wbase[b] + sw + p * 32u : kOutOfRange, 0, 0);
-            }
-        } else {
-            // the last channels of a row whose length is no multiple of four: one by one
-#pragma unroll
-            for (int p = 0; p < 2; ++p)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const bool in = p * 8 + e < left;
-                    const uint32_t o = p * 32u + e * 4u;
-                    xv[st][p][e] = __builtin_amdgcn_raw_buffer_load_b32(rx, tap_ok && in ? xbase + sx + o : kOutOfRange, 0, 0);
-#pragma unroll
-                    for (int b = 0; b < NB; ++b)
-                        wv[st][b][p][e] =
-                            __builtin_amdgcn_raw_buffer_load_b32(rw, wlive[b] && in ? wbase[b] + sw + o : kOutOfRange, 0, 0);
-                }
+        for (int j = 0; j < XR; ++j) {
+            const bool ok = ((tap < 32 ? xbits[0][j] : xbits[1][j]) & sel) && in;
+            dma_load16_s(rsrc_x, ok ? xoff[j] - back : kOutOfRange, sx, to + (uint32_t)j * 4096u);
         }
+#pragma unroll
+        for (int j = 0; j < WR; ++j)
+            dma_load16_s(rsrc_w, in_k && in && woff[j] != kOutOfRange ? woff[j] - back : kOutOfRange, sw,
+                         to + (uint32_t)(XR + j) * 4096u);
+        ibuf = ibuf + 1 == NB ? 0 : ibuf + 1;
         if (++cc == cch) {
             cc = 0;
             ++tap;
@@ -242,40 +262,68 @@ __global__ __launch_bounds__(kRegThreads, 2) void k_conv_f32(Geom g, const float
             }
         }
     };
-    int mcc = cc; // channel step of the next step to multiply
-    auto multiply = [&](auto set_c) __attribute__((always_inline)) {
-        constexpr int st = decltype(set_c)::value;
-        __builtin_amdgcn_sched_barrier(0);
-        const bool whole = mcc + 1 < cch || tail > 8; // (otherwise the upper eight channels do not exist)
-        mcc = mcc + 1 == cch ? 0 : mcc + 1;
+
+    f32x16_t acc[CB];
 #pragma unroll
-        for (int p = 0; p < 2; ++p)
-            if (p == 0 || whole)
+    for (int b = 0; b < CB; ++b)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[b][i] = 0.f;
+#pragma unroll
+    for (int d = 0; d < NB - R; ++d) issue();
+
+    const uint32_t frag = (uint32_t)l32 * 128u;
+    const int wm = WK == 4 ? 0 : wave;
+    int mcc = 0, cbuf = 0; // channel chunk and buffer of the stage to multiply
+    // (an odd number of stages: the last round's second stage is one past the end, all zeros)
+    for (int s = 0; s < stages; s += R) {
+        wait_vmcnt<(NB - 2 * R) * L>(); // this thread's loads of the round's stages have landed
+        __syncthreads();                // ... and everyone else's; the buffers of the round before are free
+#pragma unroll
+        for (int d = 0; d < R; ++d) issue();
+#pragma unroll
+        for (int d = 0; d < R; ++d) {
+            const unsigned char *xs = stage + (uint32_t)cbuf * STAGE + (uint32_t)wm * 4096u + frag;
+            const unsigned char *ws = stage + (uint32_t)cbuf * STAGE + (uint32_t)TM * 128u + frag;
+            const bool last = mcc + 1 == cch;
+            const int steps = TAIL && last ? last_steps : 4;
+#pragma unroll
+            for (int kq = 0; kq < 4 / WK; ++kq) {
+                const int kk = WK == 4 ? wave : kq;
+                if (TAIL && kk >= steps) break;
+                const uint32_t o = (uint32_t)((2 * kk + half) ^ FC_SWZ(l32)) * 16u;
+                float4 xv = *reinterpret_cast<const float4 *>(xs + o), wv[CB];
+#pragma unroll
+                for (int b = 0; b < CB; ++b) wv[b] = *reinterpret_cast<const float4 *>(ws + b * 4096 + o);
+                if (TAIL && last && again && kk == steps - 1) {
+                    const int drop = mcc * 32 + (2 * kk + half) * 4 == edge ? again : 0;
+                    xv.x = drop > 0 ? 0.f : xv.x;
+                    xv.y = drop > 1 ? 0.f : xv.y;
+                    xv.z = drop > 2 ? 0.f : xv.z;
+#pragma unroll
+                    for (int b = 0; b < CB; ++b) {
+                        wv[b].x = drop > 0 ? 0.f : wv[b].x;
+                        wv[b].y = drop > 1 ? 0.f : wv[b].y;
+                        wv[b].z = drop > 2 ? 0.f : wv[b].z;
+                    }
+                }
+                const float xe[4] = {xv.x, xv.y, xv.z, xv.w};
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
 #pragma unroll
-                    for (int b = 0; b < NB; ++b)
-                        acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(wv[st][b][p][e]),
-                                                                      __uint_as_float(xv[st][p][e]), acc[b], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    using C0 = std::integral_constant<int, 0>;
-    using C1 = std::integral_constant<int, 1>;
-    using C2 = std::integral_constant<int, 2>;
-    if (s0 < s1) load(C0{});
-    if (s0 + 1 < s1) load(C1{});
-    for (int s = s0; s < s1; s += 3) {
-        if (s + 2 < s1) load(C2{});
-        multiply(C0{});
-        if (s + 1 >= s1) break;
-        if (s + 3 < s1) load(C0{});
-        multiply(C1{});
-        if (s + 2 >= s1) break;
-        if (s + 4 < s1) load(C1{});
-        multiply(C2{});
+                    for (int b = 0; b < CB; ++b) {
+                        const float we = e == 0 ? wv[b].x : e == 1 ? wv[b].y : e == 2 ? wv[b].z : wv[b].w;
+                        acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(we, xe[e], acc[b], 0, 0, 0);
+                    }
+            }
+            mcc = last ? 0 : mcc + 1;
+            cbuf = cbuf + 1 == NB ? 0 : cbuf + 1;
+        }
     }
+    wait_vmcnt<0>();
 
-    // a lane's quad (b, q) = channels co0 + 32 b + 8 q + 4 half .. + 3 of position p
+    // a lane's quad (b, q) = channels co0 + 32 b + 8 q + 4 half .. + 3 of the position of row r
+    const int r = wm * 32 + l32;
+    const int64_t at = r < n ? (int64_t)rows_s.p[r] * g.c_out : -1;
     auto finish = [&](int b, int q, float4 v) __attribute__((always_inline)) {
         const int co = co0 + b * 32 + q * 8 + half * 4;
         float e[4] = {v.x, v.y, v.z, v.w};
@@ -284,78 +332,82 @@ __global__ __launch_bounds__(kRegThreads, 2) void k_conv_f32(Geom g, const float
             if (bias && co + i < g.c_out) e[i] += bias[co + i];
             if (g.flags & FC_RELU) e[i] = !(e[i] > 0.f) ? (e[i] != e[i] ? e[i] : 0.f) : e[i];
         }
-        if (!live) return;
-        float *o = out + (int64_t)rows_s.p[r] * g.c_out + co;
+        if (at < 0) return;
         if ((g.c_out & 3) == 0) {
-            if (co < g.c_out) *reinterpret_cast<float4 *>(o) = make_float4(e[0], e[1], e[2], e[3]);
+            if (co < g.c_out) *reinterpret_cast<float4 *>(out + at + co) = make_float4(e[0], e[1], e[2], e[3]);
         } else {
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                if (co + i < g.c_out) o[i] = e[i];
+                if (co + i < g.c_out) out[at + co + i] = e[i];
         }
     };
-    if constexpr (KSPLIT) {
+    if constexpr (WK == 4) {
+        __syncthreads(); // every wave is done with the stage buffers
+        float4 *part = reinterpret_cast<float4 *>(stage);
 #pragma unroll
-        for (int b = 0; b < NB; ++b)
+        for (int b = 0; b < CB; ++b)
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                part[(wave * NQ + b * 4 + q) * 64 + lane] =
+                part[((wave * CB + b) * 4 + q) * 64 + lane] =
                     make_float4(acc[b][q * 4], acc[b][q * 4 + 1], acc[b][q * 4 + 2], acc[b][q * 4 + 3]);
         __syncthreads();
         // wave v finishes quad v of every 32-channel block
 #pragma unroll
-        for (int b = 0; b < NB; ++b) {
+        for (int b = 0; b < CB; ++b) {
             float4 v = part[(b * 4 + wave) * 64 + lane];
 #pragma unroll
             for (int k = 1; k < 4; ++k) {
-                const float4 t = part[(k * NQ + b * 4 + wave) * 64 + lane];
+                const float4 t = part[((k * CB + b) * 4 + wave) * 64 + lane];
                 v.x += t.x; v.y += t.y; v.z += t.z; v.w += t.w;
             }
             finish(b, wave, v);
         }
     } else {
 #pragma unroll
-        for (int b = 0; b < NB; ++b)
+        for (int b = 0; b < CB; ++b)
 #pragma unroll
             for (int q = 0; q < 4; ++q)
                 finish(b, q, make_float4(acc[b][q * 4], acc[b][q * 4 + 1], acc[b][q * 4 + 2], acc[b][q * 4 + 3]));
     }
 }
 
-// 64 taps: the tap-valid bits of a row; 32-bit byte offsets into x and w; row origins in 16 bits
+// four channels: one piece; 64 taps: the tap-valid bits of a row; 32-bit byte offsets into x and w; row
+// origins in 16 bits
 bool conv_f32_supported(const Geom &g)
 {
-    return g.kh * g.kw <= 64 && g.h <= 16384 && g.w <= 16384 && g.ph <= 8192 && g.pw <= 8192 &&
-           (uint64_t)g.n * g.h * g.w * g.c_in * 4u < kBufferLimit &&
+    return g.c_in >= 4 && g.kh * g.kw <= 64 && g.h <= 16384 && g.w <= 16384 && g.ph <= 8192 && g.pw <= 8192 &&
+           ((uint64_t)g.n * g.h * g.w + (uint64_t)g.ph * g.w + g.pw) * g.c_in * 4u < kBufferLimit &&
            (uint64_t)g.c_out * g.kh * g.kw * g.c_in * 4u < kBufferLimit;
 }
 
-template <int NB, bool KSPLIT>
+template <int TN, int WK, int NB, bool TAIL>
 static hipError_t launch_f32(const Geom &g, const void *x, const uint8_t *mask_in, const uint8_t *mask_out, const void *w,
                              const float *bias, const int32_t *idx, const int32_t *count, void *out, hipStream_t s)
 {
-    constexpr int S = KSPLIT ? 32 : 128;
-    hipLaunchKernelGGL((k_conv_f32<NB, KSPLIT>), dim3((g.m + S - 1) / S, (g.c_out + NB * 32 - 1) / (NB * 32)),
-                       dim3(kRegThreads), 0, s, g, (const float *)x, mask_in, mask_out, (const float *)w, bias, idx, count,
-                       (float *)out);
+    constexpr int TM = WK == 4 ? 32 : 128;
+    hipLaunchKernelGGL((k_conv_f32<TN, WK, NB, TAIL>), dim3((g.m + TM - 1) / TM, (g.c_out + TN - 1) / TN), dim3(kRegThreads), 0,
+                       s, g, (const float *)x, mask_in, mask_out, (const float *)w, bias, idx, count, (float *)out);
     return hipGetLastError();
 }
 
 hipError_t launch_conv_f32(const Geom &g, const void *x, const uint8_t *mask_in, const uint8_t *mask_out, const void *w,
                            const float *bias, const int32_t *idx, const int32_t *count, void *out, hipStream_t s)
 {
-    // 64 output channels per wave halve the reading of x; an odd number of 32-channel blocks would
-    // leave half of the last pair idle
+    // 64 output channels per tile halve the gathering of x; an odd number of 32-channel blocks would
+    // leave half of the last tile idle
     const int blocks32 = (g.c_out + 31) / 32;
     const bool wide = blocks32 % 2 == 0;
-    // one wave per 32 rows would give fewer than one wave per SIMD: split the reduction
+#define FC_F32(TN, WK, NB)                                                                                     \
+    (g.c_in % 32 ? launch_f32<TN, WK, NB, true>(g, x, mask_in, mask_out, w, bias, idx, count, out, s)          \
+                 : launch_f32<TN, WK, NB, false>(g, x, mask_in, mask_out, w, bias, idx, count, out, s))
+    // Split the reduction when a wave per 32 rows would give fewer than one wave per SIMD, or, with a mask,
+    // four: spans without a kept row leave their CUs to the others, which the smaller spans even out
+    // (95 -> 116 on 4 x 67 x 90, half of it kept: 73 -> 67 us; without a mask 33 -> 65 on 4 x 90 x 90 loses,
+    // 47 -> 53 us).  32 output channels then: 64 halve the workgroups (64 -> 64 on 2 x 60 x 80: 15.6 and 17.5 us).
     const int64_t waves = (int64_t)((g.m + 31) / 32) * (wide ? blocks32 / 2 : blocks32);
-    const bool ksplit = waves < 1024;
-    if (wide)
-        return ksplit ? launch_f32<2, true>(g, x, mask_in, mask_out, w, bias, idx, count, out, s)
-                      : launch_f32<2, false>(g, x, mask_in, mask_out, w, bias, idx, count, out, s);
-    return ksplit ? launch_f32<1, true>(g, x, mask_in, mask_out, w, bias, idx, count, out, s)
-                  : launch_f32<1, false>(g, x, mask_in, mask_out, w, bias, idx, count, out, s);
+    if (waves < (mask_in ? 4096 : 1024)) return FC_F32(32, 4, 6);
+    return wide ? FC_F32(64, 1, 2) : FC_F32(32, 1, 3);
+#undef FC_F32
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -391,7 +443,7 @@ __global__ __launch_bounds__(kRegThreads, KS > 9 ? 1 : 2) void k_conv_grouped(
     const uint8_t *__restrict__ mask_out, const uint16_t *__restrict__ w, const float *__restrict__ bias,
     const int32_t *__restrict__ idx, const int32_t *__restrict__ count, TO *__restrict__ out)
 {
-    constexpr int S = kMaxSpan;
+    constexpr int S = kGroupedSpan;
     __shared__ SpanRows rows_s;
     const int rows = idx ? *count : g.m;
     const int first = blockIdx.x * S;
@@ -444,7 +496,7 @@ __global__ __launch_bounds__(kRegThreads, KS > 9 ? 1 : 2) void k_conv_grouped(
     u32x4_t xv[2][KS];
     auto load = [&](auto set_c, int r) __attribute__((always_inline)) {
         constexpr int st = decltype(set_c)::value;
-        const bool live = r < n;
+        const bool live = r < n; // (n <= kMaxSpan; r may point past it)
         const int base = live ? rows_s.base[r] * g.c_in * 2 : 0;
         const uint32_t bits = live ? rows_s.bits[0][r] : 0u;
 #pragma unroll
@@ -455,6 +507,7 @@ __global__ __launch_bounds__(kRegThreads, KS > 9 ? 1 : 2) void k_conv_grouped(
     auto multiply = [&](auto set_c, int r) __attribute__((always_inline)) {
         constexpr int st = decltype(set_c)::value;
         f32x4_t acc = {bq.x, bq.y, bq.z, bq.w};
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int s = 0; s < KS; ++s) acc = mfma16<DT>(wf[s], xv[st][s], acc);
         if (g.flags & FC_RELU)
@@ -465,12 +518,13 @@ __global__ __launch_bounds__(kRegThreads, KS > 9 ? 1 : 2) void k_conv_grouped(
     };
     using C0 = std::integral_constant<int, 0>;
     using C1 = std::integral_constant<int, 1>;
-    if (n > 0) load(C0{}, col);
+    // (tiles past the end load nothing but are issued all the same, see k_conv_f32)
+    load(C0{}, col);
     for (int r = col; r - col < n; r += 32) {
-        if (r - col + 16 < n) load(C1{}, r + 16);
+        load(C1{}, r + 16);
         multiply(C0{}, r);
         if (r - col + 16 >= n) break;
-        if (r - col + 32 < n) load(C0{}, r + 32);
+        load(C0{}, r + 32);
         multiply(C1{}, r + 16);
     }
 }
@@ -502,7 +556,7 @@ static hipError_t launch_grouped(const Geom &g, int groups, const void *x, const
                                  hipStream_t s)
 {
     const int cig = g.c_in / groups, cog = g.c_out / groups;
-    const dim3 grid((g.m + kMaxSpan - 1) / kMaxSpan, (g.c_out + 63) / 64);
+    const dim3 grid((g.m + kGroupedSpan - 1) / kGroupedSpan, (g.c_out + 63) / 64);
     const int steps = grouped_steps(g, cig, cog);
     auto kern = steps <= 5 ? k_conv_grouped<DT, TO, 5> : (steps <= 9 ? k_conv_grouped<DT, TO, 9> : k_conv_grouped<DT, TO, 18>);
     hipLaunchKernelGGL(kern, grid, dim3(kRegThreads), 0, s, g, cig, cog, (const uint16_t *)x, mask_in, mask_out,
