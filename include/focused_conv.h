@@ -383,6 +383,23 @@ int32_t fc_maxpool2d_masked(const void *x, int32_t n, int32_t h, int32_t w, int3
                             int32_t k, int32_t stride, int32_t pad, const uint8_t *keep, void *out,
                             void *stream);
 
+/* A fixed sequence of layers enqueued by one call (a network whose layers take a few microseconds
+ * each is otherwise bound by the language that calls them one by one).  Exactly the calls named below,
+ * in order, with pointers taken from a table: a call's fields are slots of `slots`, negative = NULL.
+ *   FC_CALL_CONV     fc_focused_conv2d(&desc, x, mask_in, w, bias, mask_out, idx, count, out, workspace, ...)
+ *   FC_CALL_DWCONV   fc_focused_dwconv2d(&desc, x, mask_in, w, bias, out, ...)
+ *   FC_CALL_MAXPOOL  fc_maxpool2d_masked(x, n, h, w, c_in, in_dtype, kh, stride_h, pad_h of desc, mask_out as
+ *                    `keep`, out, ...)
+ * Slots and kinds are checked before anything is enqueued (FC_ERR_RANGE, FC_ERR_DTYPE); a layer whose
+ * own checks fail ends the sequence with its status, the layers before it stay enqueued. */
+enum { FC_CALL_CONV = 0, FC_CALL_DWCONV = 1, FC_CALL_MAXPOOL = 2 };
+typedef struct fc_call {
+    fc_conv_desc desc;
+    int32_t kind, x, mask_in, w, bias, mask_out, idx, count, out;
+} fc_call;
+int32_t fc_run_calls(const fc_call *calls, int32_t n_calls, void *const *slots, int32_t n_slots, void *workspace,
+                     size_t workspace_bytes, void *stream);
+
 #ifdef __cplusplus
 }
 #endif

@@ -28,7 +28,7 @@ FUNCTIONS = ("fc_status_string", "fc_out_dims", "fc_workspace_bytes", "fc_compac
              "fc_mask_pyramid_packed",
              "fc_expand_group_weights",
              "fc_focused_dwconv2d",
-             "fc_maxpool2d", "fc_maxpool2d_masked")
+             "fc_maxpool2d", "fc_maxpool2d_masked", "fc_run_calls")
 MAX_PYRAMID_LEVELS = 8
 
 
@@ -43,6 +43,15 @@ class ConvDesc(ctypes.Structure):
     _fields_ = [(k, ctypes.c_int32) for k in (
         "n", "h", "w", "c_in", "c_out", "kh", "kw", "stride_h", "stride_w",
         "pad_h", "pad_w", "dil_h", "dil_w", "in_dtype", "out_dtype")] + [("flags", ctypes.c_uint32)]
+
+
+class Call(ctypes.Structure):
+    """Mirror of fc_call: one layer of a fc_run_calls sequence, its pointers as slots of a table."""
+    _fields_ = [("desc", ConvDesc)] + [(k, ctypes.c_int32) for k in (
+        "kind", "x", "mask_in", "w", "bias", "mask_out", "idx", "count", "out")]
+
+
+CALL_CONV, CALL_DWCONV, CALL_MAXPOOL = 0, 1, 2
 
 
 class MaskStep(ctypes.Structure):
@@ -133,6 +142,8 @@ def lib():
         L.fc_maxpool2d.argtypes = [vp] + [i32] * 8 + [vp, vp]
         L.fc_maxpool2d_masked.restype = i32
         L.fc_maxpool2d_masked.argtypes = [vp] + [i32] * 8 + [vp, vp, vp]
+        L.fc_run_calls.restype = i32
+        L.fc_run_calls.argtypes = [ctypes.POINTER(Call), i32, ctypes.POINTER(vp), i32, vp, ctypes.c_size_t, vp]
         _lib = L
     return _lib
 
@@ -172,18 +183,45 @@ def _torch():
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()      # (the argument types convert plain integers)
+
+
+# A call of a small layer costs a few microseconds on the device, so the host side of one is kept as
+# short: the stream's handle comes from torch's C function (torch.cuda.current_stream() builds a Python
+# object around it, 2.8 us against 0.1 us), sizes that only depend on the descriptor are looked up.
+
+def _current_raw_stream():
+    c = _torch()._C
+    return c._cuda_getCurrentRawStream(c._cuda_getDevice())
 
 
 def _stream(stream):
-    if stream is None:
-        stream = _torch().cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    return _current_raw_stream() if stream is None else stream.cuda_stream
+
+
+_torch_dtypes = None
 
 
 def torch_dtype(code: int):
-    torch = _torch()
-    return {F32: torch.float32, BF16: torch.bfloat16, F16: torch.float16, FP8: torch.float8_e4m3fn}[code]
+    global _torch_dtypes
+    if _torch_dtypes is None:
+        torch = _torch()
+        _torch_dtypes = {F32: torch.float32, BF16: torch.bfloat16, F16: torch.float16, FP8: torch.float8_e4m3fn}
+    return _torch_dtypes[code]
+
+
+_sizes = {}     # bytes of a descriptor -> (output shape, output dtype, workspace bytes)
+
+
+def _conv_sizes(desc: ConvDesc):
+    key = bytes(desc)
+    got = _sizes.get(key)
+    if got is None:
+        if len(_sizes) >= 4096:
+            _sizes.clear()
+        ho, wo = out_dims(desc)
+        got = _sizes[key] = ((desc.n, ho, wo, desc.c_out), torch_dtype(desc.out_dtype), workspace_bytes(desc))
+    return got
 
 
 def _require_cuda(*tensors):
@@ -320,11 +358,9 @@ class PreparedPyramid:
             self._args = (_ptr(mask_in), n, h, w, nl, self._steps, *self._ptrs, _ptr(self._ws), self._ws.numel())
             self._fn = lib().fc_mask_pyramid
         self.mask_in = mask_in   # (kept alive: the call reads it)
-        self._current_stream = torch.cuda.current_stream
 
     def __call__(self, stream=None):
-        hnd = (self._current_stream() if stream is None else stream).cuda_stream
-        rc = self._fn(*self._args, ctypes.c_void_p(hnd))
+        rc = self._fn(*self._args, _stream(stream))
         if rc != 0:
             raise FcError(rc, "fc_mask_pyramid")
         return self.levels
@@ -371,11 +407,11 @@ def focused_conv2d(desc: ConvDesc, x, w, bias=None, mask_in=None, mask_out=None,
     """fc_focused_conv2d.  x NHWC, w [C_out,KH,KW,C_in]; returns out NHWC."""
     torch = _torch()
     _require_cuda(x, w, bias, mask_in, mask_out, idx, count, out, workspace)
-    ho, wo = out_dims(desc)
+    shape, dtype, need = _conv_sizes(desc)
     if out is None:
-        out = torch.empty((desc.n, ho, wo, desc.c_out), dtype=torch_dtype(desc.out_dtype), device=x.device)
+        out = torch.empty(shape, dtype=dtype, device=x.device)
     if workspace is None and mask_in is not None and idx is None:
-        workspace = torch.empty((workspace_bytes(desc),), dtype=torch.uint8, device=x.device)
+        workspace = torch.empty((need,), dtype=torch.uint8, device=x.device)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     _check(lib().fc_focused_conv2d(ctypes.byref(desc), _ptr(x), _ptr(mask_in), _ptr(w), _ptr(bias),
                                    _ptr(mask_out), _ptr(idx), _ptr(count), _ptr(out), _ptr(workspace),
@@ -418,11 +454,9 @@ class PreparedConv:
         self._args = (ctypes.byref(desc), _ptr(x), _ptr(mask_in), _ptr(w), _ptr(bias), _ptr(mask_out), _ptr(idx),
                       _ptr(count), _ptr(out), _ptr(workspace), ws_bytes)
         self._fn = lib().fc_focused_conv2d
-        self._current_stream = torch.cuda.current_stream
 
     def __call__(self, stream=None):
-        h = (self._current_stream() if stream is None else stream).cuda_stream
-        rc = self._fn(*self._args, ctypes.c_void_p(h))
+        rc = self._fn(*self._args, _stream(stream))
         if rc != 0:
             raise FcError(rc, "fc_focused_conv2d")
         return self.out
@@ -433,11 +467,11 @@ def focused_gconv2d(desc: ConvDesc, groups: int, x, w, bias=None, mask_in=None, 
     """fc_focused_gconv2d.  x NHWC, w [C_out,KH,KW,C_in/groups]; returns out NHWC."""
     torch = _torch()
     _require_cuda(x, w, bias, mask_in, mask_out, idx, count, out, workspace)
-    ho, wo = out_dims(desc)
+    shape, dtype, need = _conv_sizes(desc)
     if out is None:
-        out = torch.empty((desc.n, ho, wo, desc.c_out), dtype=torch_dtype(desc.out_dtype), device=x.device)
+        out = torch.empty(shape, dtype=dtype, device=x.device)
     if workspace is None and mask_in is not None and idx is None:
-        workspace = torch.empty((workspace_bytes(desc),), dtype=torch.uint8, device=x.device)
+        workspace = torch.empty((need,), dtype=torch.uint8, device=x.device)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     _check(lib().fc_focused_gconv2d(ctypes.byref(desc), groups, _ptr(x), _ptr(mask_in), _ptr(w), _ptr(bias),
                                     _ptr(mask_out), _ptr(idx), _ptr(count), _ptr(out), _ptr(workspace),
@@ -460,9 +494,9 @@ def focused_dwconv2d(desc: ConvDesc, x, w, bias=None, mask_in=None, out=None, st
     """fc_focused_dwconv2d.  x NHWC, w [C,KH,KW] (one filter per channel); returns out NHWC."""
     torch = _torch()
     _require_cuda(x, w, bias, mask_in, out)
-    ho, wo = out_dims(desc)
+    shape, dtype, _ = _conv_sizes(desc)
     if out is None:
-        out = torch.empty((desc.n, ho, wo, desc.c_out), dtype=torch_dtype(desc.out_dtype), device=x.device)
+        out = torch.empty(shape, dtype=dtype, device=x.device)
     _check(lib().fc_focused_dwconv2d(ctypes.byref(desc), _ptr(x), _ptr(mask_in), _ptr(w), _ptr(bias), _ptr(out),
                                      _stream(stream)), "fc_focused_dwconv2d")
     return out
@@ -481,11 +515,9 @@ class PreparedDwConv:
         self._keep = (desc, x, w, bias, mask_in, out)
         self._args = (ctypes.byref(desc), _ptr(x), _ptr(mask_in), _ptr(w), _ptr(bias), _ptr(out))
         self._fn = lib().fc_focused_dwconv2d
-        self._current_stream = torch.cuda.current_stream
 
     def __call__(self, stream=None):
-        h = (self._current_stream() if stream is None else stream).cuda_stream
-        rc = self._fn(*self._args, ctypes.c_void_p(h))
+        rc = self._fn(*self._args, _stream(stream))
         if rc != 0:
             raise FcError(rc, "fc_focused_dwconv2d")
         return self.out
@@ -546,3 +578,11 @@ def maxpool2d(x, k: int, stride: int, pad: int, dtype: int, out=None, stream=Non
         _check(lib().fc_maxpool2d_masked(_ptr(x), n, h, w, c, dtype, k, stride, pad, _ptr(keep), _ptr(out),
                                          _stream(stream)), "fc_maxpool2d_masked")
     return out
+
+
+def run_calls(calls, slots, workspace, stream=None):
+    """fc_run_calls: `calls` a ctypes array of Call, `slots` a ctypes array of device addresses (c_void_p).
+    The caller keeps the tensors behind the addresses alive."""
+    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    _check(lib().fc_run_calls(calls, len(calls), slots, len(slots), _ptr(workspace), ws_bytes, _stream(stream)),
+           "fc_run_calls")

@@ -324,7 +324,8 @@ int32_t fc_focused_conv2d(const fc_conv_desc *desc, const void *x, const uint8_t
         tile_counters = (int32_t *)((uint8_t *)workspace + l.counters);
         partials = (float *)((uint8_t *)workspace + l.partials);
     }
-    bool counters_cleared = false;
+    // (a layer whose reduction is too short to split leaves the counters alone)
+    bool counters_cleared = !split_k_reachable(g, desc->in_dtype);
     const bool f32 = desc->in_dtype == FC_F32 && conv_f32_supported(g);
 
     if (mask_in && !idx) {
@@ -342,7 +343,7 @@ int32_t fc_focused_conv2d(const fc_conv_desc *desc, const void *x, const uint8_t
         const bool rank_in_kernel = f32 || (mfma && g.m <= kInlineRankPositions && !mask_out);
         if (!rank_in_kernel) {
             CompactExtras ex;
-            if (tile_counters) {
+            if (tile_counters && !counters_cleared) {
                 ex.zero = tile_counters;
                 ex.zero_n = kSplitGrid;
                 counters_cleared = true;
@@ -743,6 +744,38 @@ int32_t fc_calibrate_issue(int32_t mode, int32_t waves_per_simd, int32_t steps, 
                                   (hipStream_t)stream) == hipSuccess
                ? FC_OK
                : FC_ERR_HIP;
+}
+
+int32_t fc_run_calls(const fc_call *calls, int32_t n_calls, void *const *slots, int32_t n_slots, void *workspace,
+                     size_t workspace_bytes, void *stream)
+{
+    if (!calls || !slots) return FC_ERR_NULL;
+    if (n_calls < 0 || n_slots < 0) return FC_ERR_SHAPE;
+    for (int32_t i = 0; i < n_calls; ++i) {
+        const fc_call &c = calls[i];
+        const int32_t used[] = {c.x, c.mask_in, c.w, c.bias, c.mask_out, c.idx, c.count, c.out};
+        for (int32_t u : used)
+            if (u >= n_slots) return FC_ERR_RANGE;
+        if (c.kind != FC_CALL_CONV && c.kind != FC_CALL_DWCONV && c.kind != FC_CALL_MAXPOOL) return FC_ERR_DTYPE;
+    }
+    auto at = [&](int32_t slot) { return slot < 0 ? nullptr : slots[slot]; };
+    for (int32_t i = 0; i < n_calls; ++i) {
+        const fc_call &c = calls[i];
+        const fc_conv_desc &d = c.desc;
+        int32_t rc;
+        if (c.kind == FC_CALL_CONV)
+            rc = fc_focused_conv2d(&d, at(c.x), (const uint8_t *)at(c.mask_in), at(c.w), (const float *)at(c.bias),
+                                   (const uint8_t *)at(c.mask_out), (const int32_t *)at(c.idx),
+                                   (const int32_t *)at(c.count), at(c.out), workspace, workspace_bytes, stream);
+        else if (c.kind == FC_CALL_DWCONV)
+            rc = fc_focused_dwconv2d(&d, at(c.x), (const uint8_t *)at(c.mask_in), at(c.w), (const float *)at(c.bias),
+                                     at(c.out), stream);
+        else
+            rc = fc_maxpool2d_masked(at(c.x), d.n, d.h, d.w, d.c_in, d.in_dtype, d.kh, d.stride_h, d.pad_h,
+                                     (const uint8_t *)at(c.mask_out), at(c.out), stream);
+        if (rc != FC_OK) return rc;
+    }
+    return FC_OK;
 }
 
 int32_t fc_maxpool2d(const void *x, int32_t n, int32_t h, int32_t w, int32_t c, int32_t dtype, int32_t k,

@@ -293,6 +293,14 @@ static inline bool split_k_possible(const Geom &g)
     const int64_t tiles64 = (int64_t)((g.m + 127) / 128) * ((g.c_out + 63) / 64);
     return tiles64 < kSplitGrid; // fewer tiles than workgroups even for the dense row count
 }
+// Fewest stages (128-byte pieces of one tap's channels) a K-split is left with: a layer with fewer than
+// two splits' worth is never split, and its calls need no cleared counters.
+constexpr int kMinSplitStages = 8;
+static inline bool split_k_reachable(const Geom &g, int in_dtype)
+{
+    const int64_t row = (int64_t)g.c_in * (in_dtype == FC_FP8 ? 1 : 2);
+    return split_k_possible(g) && (int64_t)g.kh * g.kw * ((row + 127) / 128) >= 2 * kMinSplitStages;
+}
 static inline size_t split_k_counter_bytes(const Geom &g) { return split_k_possible(g) ? align_up(kSplitGrid * sizeof(int32_t), 256) : 0; }
 static inline size_t split_k_partial_bytes(const Geom &g)
 {

@@ -5,18 +5,98 @@ rescaled per layer) - by one fc_mask_pyramid call per pass when the mask levels 
 a chain, as they do in a feed-forward network; each conv is one fc_focused_conv2d
 call, each depthwise conv one fc_focused_dwconv2d call.
 
-Plumbing only: the order of library calls and which tensor feeds which.  Max-pools
+Plumbing only: the order of library calls and which tensor feeds which.  The calls of a pass are
+laid out once per way of running the stack and enqueued by one fc_run_calls.  Max-pools
 (not part of the paper's method) go through the library's helper, which with a mask
 computes only the pooled positions the mask keeps.
 """
 from __future__ import annotations
 
+import ctypes
 from typing import Dict, List, Optional
 
 import numpy as np
 
 from . import binding as B
 from . import synth
+
+
+MAX_PYRAMIDS = 16
+
+
+class _Plan:
+    """The fc_run_calls sequence of one way of running a stack.
+
+    Slots: 0 the input, 1 its mask, then mask / list / count of every pyramid level, weights and bias of
+    every layer, the outputs.  Outputs that the caller does not get live in one arena, at offsets such that
+    tensors in use at the same time do not overlap."""
+
+    def __init__(self, stack: "ConvStack", masked: bool, keep_outputs: bool, chain: bool, compact: bool):
+        ops, n = stack.ops, len(stack.ops)
+        readers = stack._readers()
+        table: List[Optional[int]] = [None, None]
+        if masked:
+            table += [None] * (3 * len(stack.pyramid_steps))
+
+        def slot(address=None):
+            table.append(address)
+            return len(table) - 1
+
+        out_slot = {-1: 0}
+        compacted = set()
+        calls = []
+        self.levels = [(i, stack._level_of[i] if masked else -1) for i in range(n)]
+        self.returned, arena_ops = [], []
+        for i, op in enumerate(ops):
+            ho, wo = stack.sizes[i]
+            shape, dtype = (stack.n, ho, wo, op.c_out), B.torch_dtype(stack.dtype)
+            m_in = m_out = idx = count = -1
+            if masked:
+                src_level, level = stack._level_of[op.src], stack._level_of[i]
+                m_in = 1 if src_level < 0 else 2 + 3 * src_level
+                m_out, idx, count = (2 + 3 * level + k for k in range(3))
+            src = out_slot[op.src]
+            out_slot[i] = slot()
+            if op.kind == "maxpool":
+                hi, wi = stack.sizes[op.src]
+                d = B.conv_desc(stack.n, hi, wi, op.c_in, op.c_in, (op.k, op.k), (op.stride, op.stride), (op.pad, op.pad),
+                                (1, 1), stack.dtype)
+                calls.append(B.Call(d, B.CALL_MAXPOOL, src, -1, -1, -1, m_out, -1, -1, out_slot[i]))
+            else:
+                skip = chain and masked and stack._gated_readers_only(i, readers)
+                extra = B.SKIP_ZERO_FILL if skip else 0
+                if op.src in compacted:
+                    extra |= B.COMPACT_IN
+                if compact and stack._compact_out(i, skip, readers):
+                    extra |= B.COMPACT_OUT
+                    compacted.add(i)
+                    shape = (stack.n * ho * wo, op.c_out)
+                w, b = slot(stack.weights[i].data_ptr()), slot(stack.biases[i].data_ptr())
+                if op.kind == "dwconv":
+                    # labels come from the input mask inside the call: no list, no workspace
+                    calls.append(B.Call(stack.desc(i, flags_extra=extra), B.CALL_DWCONV, src, m_in, w, b, -1, -1, -1,
+                                        out_slot[i]))
+                else:
+                    calls.append(B.Call(stack.desc(i, flags_extra=extra | B.WORKSPACE_READY), B.CALL_CONV, src, m_in, w, b,
+                                        m_out, idx, count, out_slot[i]))
+            if keep_outputs or i == n - 1:
+                self.returned.append((i, out_slot[i], shape, dtype))
+            else:
+                arena_ops.append((i, max(readers.get(i, [i])), int(np.prod(shape)) * dtype.itemsize))
+        self.calls = (B.Call * n)(*calls)
+        self.slots = (ctypes.c_void_p * len(table))(*table)
+        # first fit, in the order the ops run: live from an op's own call to its last reader's
+        placed, self.in_arena, self.arena_bytes = [], [], 0
+        for i, last, size in arena_ops:
+            size = -(-size // 256) * 256
+            at = 0
+            for p_at, p_size in sorted((a, sz) for a, sz, p_last in placed if p_last >= i):
+                if at + size <= p_at:
+                    break
+                at = max(at, p_at + p_size)
+            placed.append((at, size, last))
+            self.in_arena.append((out_slot[i], at))
+            self.arena_bytes = max(self.arena_bytes, at + size)
 
 
 class ConvStack:
@@ -61,6 +141,7 @@ class ConvStack:
         # then one fc_mask_pyramid call per pass builds all of them
         self.pyramid_steps = self._pyramid_steps()
         self._pyramids: Dict[int, object] = {}
+        self._plans: Dict[tuple, _Plan] = {}
 
     def _same_view(self, i: int) -> bool:
         op = self.ops[i]
@@ -86,6 +167,7 @@ class ConvStack:
                 steps.append(((op.k, op.k), (op.stride, op.stride), (op.pad, op.pad), (1, 1)))
                 level = plans[key] = len(steps) - 1
             level_of[i] = level
+        self._level_of = level_of
         return steps if 0 < len(steps) <= B.MAX_PYRAMID_LEVELS else None
 
     def _to_dev(self, storage: np.ndarray):
@@ -117,6 +199,67 @@ class ConvStack:
         return (op.kind == "conv" and self.dtype in (B.BF16, B.F16) and op.c_in % 8 == 0 and op.c_out % 8 == 0
                 and op.k * op.k <= 32)
 
+    def _pyramid(self, mask):
+        """The prepared pyramid call of a mask tensor; the last few masks' are kept."""
+        pyr = self._pyramids.get(mask.data_ptr())
+        if pyr is None or pyr.mask_in is not mask:
+            self._pyramids.pop(mask.data_ptr(), None)
+            if len(self._pyramids) >= MAX_PYRAMIDS:
+                del self._pyramids[next(iter(self._pyramids))]
+            pyr = self._pyramids[mask.data_ptr()] = B.PreparedPyramid(mask, self.pyramid_steps)
+        return pyr
+
+    def _readers(self):
+        readers: Dict[int, List[int]] = {}
+        for j, op in enumerate(self.ops):
+            readers.setdefault(op.src, []).append(j)
+        return readers
+
+    def _gated_readers_only(self, i: int, readers) -> bool:
+        return bool(readers.get(i)) and all(self.ops[j].kind in ("conv", "dwconv") for j in readers[i])
+
+    def _compact_out(self, i: int, skip: bool, readers) -> bool:
+        """May op i hand its output on as a list of kept rows?"""
+        return (skip and self.ops[i].kind == "conv" and self._matrix_core_shape(i)
+                and all(self._pointwise(j) and self._matrix_core_shape(j) for j in readers[i]))
+
+    def _run_planned(self, x, mask, keep_outputs: bool, chain: bool, compact: bool):
+        key = (mask is not None, keep_outputs, chain, compact)
+        plan = self._plans.get(key)
+        if plan is None:
+            plan = self._plans[key] = _Plan(self, *key)
+        B._require_cuda(x, mask)
+        torch = self.torch
+        slots = type(plan.slots).from_buffer_copy(plan.slots)
+        slots[0] = x.data_ptr()
+        masks: Dict[int, object] = {-1: mask}
+        if mask is not None:
+            pyr = self._pyramid(mask)
+            levels = pyr()
+            slots[1] = mask.data_ptr()
+            at = 2
+            for level in levels:
+                for t in level:
+                    slots[at] = t.data_ptr()
+                    at += 1
+            for i, level in plan.levels:
+                masks[i] = levels[level][0]
+        else:
+            for i, _ in plan.levels:
+                masks[i] = None
+        outs: Dict[int, object] = {-1: x}
+        dev = x.device
+        if plan.arena_bytes:
+            arena = torch.empty((plan.arena_bytes,), dtype=torch.uint8, device=dev)
+            base = arena.data_ptr()
+            for slot, offset in plan.in_arena:
+                slots[slot] = base + offset
+        for i, slot, shape, dtype in plan.returned:
+            out = outs[i] = torch.empty(shape, dtype=dtype, device=dev)
+            slots[slot] = out.data_ptr()
+        B.run_calls(plan.calls, slots, self.workspace)
+        return outs, masks
+
     def run(self, x, mask=None, keep_outputs: bool = True, chain: bool = False, canary=None, compact: bool = False):
         """x: device NHWC tensor; mask: device uint8 [N,H,W] or None (dense).
         Returns (outputs, masks): per-op output tensors and per-op output masks
@@ -131,11 +274,9 @@ class ConvStack:
         compacted, in list order (FC_COMPACT_OUT), and those readers read them that way
         (FC_COMPACT_IN): they see the same mask through the same geometry, hence the same list.
         canary: value every conv output buffer is pre-filled with (tests)."""
-        readers: Dict[int, List[str]] = {}
-        reader_ops: Dict[int, List[int]] = {}
-        for j, op in enumerate(self.ops):
-            readers.setdefault(op.src, []).append(op.kind)
-            reader_ops.setdefault(op.src, []).append(j)
+        if canary is None and (mask is None or self.pyramid_steps is not None):
+            return self._run_planned(x, mask, keep_outputs, chain, compact)
+        readers = self._readers()
         compacted: Dict[int, bool] = {}   # op -> its output is stored compacted
         outs: Dict[int, object] = {-1: x}
         masks: Dict[int, object] = {-1: mask}
@@ -143,10 +284,7 @@ class ConvStack:
         produced: Dict[int, tuple] = {}   # 0/1 masks this run wrote, with their kept lists
         levels = None                     # all mask levels from one call, taken in order
         if mask is not None and self.pyramid_steps is not None:
-            pyr = self._pyramids.get(mask.data_ptr())
-            if pyr is None or pyr.mask_in is not mask:
-                pyr = self._pyramids[mask.data_ptr()] = B.PreparedPyramid(mask, self.pyramid_steps)
-            levels = list(pyr())
+            levels = list(self._pyramid(mask)())
         last_use = {}
         for i, op in enumerate(self.ops):
             last_use[op.src] = i
@@ -174,15 +312,13 @@ class ConvStack:
                     idx, count = B.active_index_compact(m_out)
                     plan = plans[key] = produced[id(m_out)] = (m_out, idx, count)
             if op.kind in ("conv", "dwconv"):
-                gated_readers_only = bool(readers.get(i)) and all(k in ("conv", "dwconv") for k in readers[i])
-                skip = chain and plan is not None and gated_readers_only
+                skip = chain and plan is not None and self._gated_readers_only(i, readers)
                 extra = B.WORKSPACE_READY | (B.SKIP_ZERO_FILL if skip else 0)
                 out = None
                 ho, wo = self.sizes[i]
                 if compacted.get(op.src, False):
                     extra |= B.COMPACT_IN
-                if (compact and skip and op.kind == "conv" and self._matrix_core_shape(i)
-                        and all(self._pointwise(j) and self._matrix_core_shape(j) for j in reader_ops[i])):
+                if compact and self._compact_out(i, skip, readers):
                     extra |= B.COMPACT_OUT
                     compacted[i] = True
                     out = (self.torch.empty if canary is None else
