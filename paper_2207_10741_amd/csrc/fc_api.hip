@@ -505,6 +505,8 @@ int32_t fc_focused_dwconv2d(const fc_conv_desc *desc, const void *x, const uint8
     return e == hipSuccess ? FC_OK : FC_ERR_HIP;
 }
 
+using PyramidArgs = ListArgs<kMaxPyramidLevels>;
+
 // Fills the geometry part of the pyramid arguments; returns an fc_status.
 static int32_t pyramid_geometry(int32_t n, int32_t h, int32_t w, int32_t levels, const fc_mask_step *steps,
                                 PyramidArgs *a)
@@ -512,35 +514,39 @@ static int32_t pyramid_geometry(int32_t n, int32_t h, int32_t w, int32_t levels,
     if (!steps) return FC_ERR_NULL;
     if (n <= 0 || h <= 0 || w <= 0 || levels <= 0 || levels > kMaxPyramidLevels) return FC_ERR_SHAPE;
     if ((int64_t)n * h * w >= INT32_MAX) return FC_ERR_RANGE;
-    a->levels = levels;
-    a->n = n;
-    a->h[0] = h;
-    a->w[0] = w;
+    a->lists = levels;
+    AxisMap row = {1, 0, 0, h - 1}, col = {1, 0, 0, w - 1}; // level l - 1 -> input mask
+    int32_t hi = h, wi = w;                                 // size of level l - 1
     int64_t blocks = 0;
     for (int l = 0; l < levels; ++l) {
         const fc_mask_step &t = steps[l];
         if (t.kh <= 0 || t.kw <= 0 || t.stride_h <= 0 || t.stride_w <= 0 || t.pad_h < 0 || t.pad_w < 0 ||
             t.dil_h <= 0 || t.dil_w <= 0)
             return FC_ERR_SHAPE;
-        const int32_t ho = out_dim(a->h[l], t.kh, t.stride_h, t.pad_h, t.dil_h);
-        const int32_t wo = out_dim(a->w[l], t.kw, t.stride_w, t.pad_w, t.dil_w);
+        const int32_t ho = out_dim(hi, t.kh, t.stride_h, t.pad_h, t.dil_h);
+        const int32_t wo = out_dim(wi, t.kw, t.stride_w, t.pad_w, t.dil_w);
         if (ho <= 0 || wo <= 0) return FC_ERR_SHAPE;
-        a->h[l + 1] = ho;
-        a->w[l + 1] = wo;
-        a->sh[l] = t.stride_h;
-        a->sw[l] = t.stride_w;
-        a->ch0[l] = -t.pad_h + t.dil_h * ((t.kh - 1) / 2);
-        a->cw0[l] = -t.pad_w + t.dil_w * ((t.kw - 1) / 2);
-        a->m[l] = (int64_t)n * ho * wo;
-        a->div_w[l] = make_fastdiv((uint32_t)wo);
-        a->div_h[l] = make_fastdiv((uint32_t)ho);
-        if (a->m[l] >= INT32_MAX) return FC_ERR_RANGE;
-        a->block0[l] = (int32_t)blocks;
-        blocks += compact_blocks(a->m[l]);
+        const int64_t m = (int64_t)n * ho * wo;
+        if (m >= INT32_MAX) return FC_ERR_RANGE;
+        LabelMap &L = a->at[l];
+        const int32_t ch0 = -t.pad_h + t.dil_h * ((t.kh - 1) / 2), cw0 = -t.pad_w + t.dil_w * ((t.kw - 1) / 2);
+        row = compose_axis(t.stride_h, ch0, hi, row);
+        col = compose_axis(t.stride_w, cw0, wi, col);
+        L.row = row;
+        L.col = col;
+        L.identity = l == 0 && t.stride_h == 1 && t.stride_w == 1 && ch0 == 0 && cw0 == 0 && ho == h && wo == w;
+        L.m = (int32_t)m;
+        L.hl = hi = ho;
+        L.wl = wi = wo;
+        L.h0 = h;
+        L.w0 = w;
+        L.div_w = make_fastdiv((uint32_t)wo);
+        L.div_h = make_fastdiv((uint32_t)ho);
+        L.block0 = (int32_t)blocks;
+        blocks += compact_blocks(m);
     }
     if (blocks >= INT32_MAX) return FC_ERR_RANGE;
-    a->block0[levels] = (int32_t)blocks;
-    a->identity0 = (a->sh[0] == 1 && a->sw[0] == 1 && a->ch0[0] == 0 && a->cw0[0] == 0 && a->h[1] == h && a->w[1] == w) ? 1 : 0;
+    a->blocks = (int32_t)blocks;
     return FC_OK;
 }
 
@@ -552,8 +558,8 @@ int32_t fc_mask_pyramid_dims(int32_t h, int32_t w, int32_t levels, const fc_mask
     const int32_t rc = pyramid_geometry(1, h, w, levels, steps, &a);
     if (rc != FC_OK) return rc;
     for (int l = 0; l < levels; ++l) {
-        hs[l] = a.h[l + 1];
-        ws[l] = a.w[l + 1];
+        hs[l] = a.at[l].hl;
+        ws[l] = a.at[l].wl;
     }
     return FC_OK;
 }
@@ -565,7 +571,7 @@ int32_t fc_mask_pyramid_workspace_bytes(int32_t n, int32_t h, int32_t w, int32_t
     PyramidArgs a;
     const int32_t rc = pyramid_geometry(n, h, w, levels, steps, &a);
     if (rc != FC_OK) return rc;
-    *bytes = align_up((size_t)a.block0[levels] * sizeof(int32_t), 256);
+    *bytes = align_up((size_t)a.blocks * sizeof(int32_t), 256);
     return FC_OK;
 }
 
@@ -578,21 +584,23 @@ static int32_t mask_pyramid_any(const uint8_t *mask_in, int32_t packed_in, int32
     PyramidArgs a;
     const int32_t rc = pyramid_geometry(n, h, w, levels, steps, &a);
     if (rc != FC_OK) return rc;
-    a.packed_in = packed_in ? 1 : 0;
-    a.packed_out = packed_out ? 1 : 0;
-    if (a.packed_in && !aligned16(mask_in)) return FC_ERR_ALIGN;
+    if (packed_in && !aligned16(mask_in)) return FC_ERR_ALIGN;
     for (int l = 0; l < levels; ++l) {
         if (!mask_out[l] || !idx[l] || !count[l]) return FC_ERR_NULL;
         if (!aligned16(mask_out[l]) || !aligned16(idx[l])) return FC_ERR_ALIGN;
-        a.mask_out[l] = mask_out[l];
-        a.idx[l] = idx[l];
-        a.count[l] = count[l];
+        LabelMap &L = a.at[l];
+        L.packed_in = packed_in ? 1 : 0;
+        L.packed_out = packed_out ? 1 : 0;
+        L.mask_out = mask_out[l];
+        L.idx = idx[l];
+        L.count = count[l];
     }
-    if (!aligned16(mask_in)) a.identity0 = 0;
-    const size_t need = align_up((size_t)a.block0[levels] * sizeof(int32_t), 256);
+    a.vec_in = aligned16(mask_in);
+    a.ex = CompactExtras();
+    const size_t need = align_up((size_t)a.blocks * sizeof(int32_t), 256);
     if (!workspace || workspace_bytes < need) return FC_ERR_WORKSPACE;
     if (!aligned16(workspace)) return FC_ERR_ALIGN;
-    const hipError_t e = launch_mask_pyramid(a, mask_in, (int32_t *)workspace, (hipStream_t)stream);
+    const hipError_t e = launch_lists(a, mask_in, (int32_t *)workspace, (hipStream_t)stream);
     return e == hipSuccess ? FC_OK : FC_ERR_HIP;
 }
 

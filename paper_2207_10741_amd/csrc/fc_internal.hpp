@@ -72,10 +72,7 @@ __device__ __forceinline__ uint32_t fast_div(uint32_t n, FastDiv f)
 static inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 constexpr int kCompactBlockThreads = 256;
-constexpr int kCompactBytesPerThread = 16;
-constexpr int kCompactBlockElems = kCompactBlockThreads * kCompactBytesPerThread; // 4096
-
-constexpr int kCompactSingleLaunchBlocks = 16; // up to this many blocks the compaction is one launch
+constexpr int kCompactBlockElems = 4096; // positions per workgroup of the list kernels
 
 static inline int64_t compact_blocks(int64_t m) { return (m + kCompactBlockElems - 1) / kCompactBlockElems; }
 
@@ -216,22 +213,38 @@ struct CompactExtras {
 // may be NULL), the ascending index list and its length.
 hipError_t launch_compact(const MaskGeom &g, const uint8_t *mask_in, uint8_t *mask_out, int32_t *idx,
                           int32_t *count, int32_t *block_counts, const CompactExtras &extras, hipStream_t s);
-// Mask pyramid: level l (1-based here; index 0 of h/w is the input mask) is the centre-tap
-// rescaling of level l - 1 with vertical/horizontal step sh/sw and first-tap offset ch0/cw0.
+// Mask pyramid: level l is the centre-tap rescaling of level l - 1, level 0 that of the input mask.
 constexpr int kMaxPyramidLevels = 8;
-struct PyramidArgs {
-    int32_t levels, n;
-    int32_t packed_in, packed_out; // the input mask / the levels' masks are one bit per pixel
-    int32_t identity0; // level 0 has the input's resolution, centred window, and the input is 16-byte aligned
-    int32_t h[kMaxPyramidLevels + 1], w[kMaxPyramidLevels + 1]; // [0] = input mask, [l + 1] = level l
-    int32_t sh[kMaxPyramidLevels], sw[kMaxPyramidLevels], ch0[kMaxPyramidLevels], cw0[kMaxPyramidLevels];
-    int64_t m[kMaxPyramidLevels];          // positions of level l
-    FastDiv div_w[kMaxPyramidLevels], div_h[kMaxPyramidLevels]; // by the level's width and height
-    int32_t block0[kMaxPyramidLevels + 1]; // first block of level l; [levels] = total
-    uint8_t *mask_out[kMaxPyramidLevels];
-    int32_t *idx[kMaxPyramidLevels];
-    int32_t *count[kMaxPyramidLevels];
+
+// A level's coordinate -> the input mask's, along one axis: clamp(v * mul + add, lo, hi).  Rescaling steps
+// are such maps, and so is a composition of them (a clamped value's image is its image, clamped to the
+// images of the bounds), so a level reads the input mask with one multiply-add whatever its depth.
+struct AxisMap {
+    int32_t mul, add, lo, hi;
 };
+// step v -> clamp(v * stride + first, 0, inner_size - 1), followed by `inner`
+AxisMap compose_axis(int32_t stride, int32_t first, int32_t inner_size, const AxisMap &inner);
+
+// One list to build: positions 0 .. m - 1 (flat [n][hl][wl] order), their labels in a mask of h0 x w0 images.
+struct LabelMap {
+    int32_t m, hl, wl, h0, w0;
+    int32_t identity;              // position p reads mask pixel p
+    int32_t packed_in, packed_out; // one bit per pixel (see mask_at)
+    int32_t block0;                // first workgroup of this list
+    AxisMap row, col;
+    FastDiv div_w, div_h;
+    uint8_t *mask_out;             // the labels, or NULL
+    int32_t *idx, *count;
+};
+template <int NL> struct ListArgs {
+    int32_t lists, blocks;
+    int32_t vec_in; // the input mask's address allows 16-byte loads
+    LabelMap at[NL];
+    CompactExtras ex;
+};
+// block_counts: one int per 4096 positions of every list (not used when the lists are short)
+hipError_t launch_lists(const ListArgs<1> &a, const uint8_t *mask_in, int32_t *block_counts, hipStream_t s);
+hipError_t launch_lists(const ListArgs<kMaxPyramidLevels> &a, const uint8_t *mask_in, int32_t *block_counts, hipStream_t s);
 // kept positions of a [n][ho][wo] mask in tile order; block_counts: one int per 256 tile rows
 hipError_t launch_compact_tiled(const uint8_t *mask, int n, int ho, int wo, int tile_h, int tile_w, int32_t *idx,
                                 int32_t *count, int32_t *block_counts, hipStream_t s);
@@ -240,7 +253,6 @@ static inline int64_t tiled_rows(int n, int ho, int wo, int tile_h, int tile_w)
 {
     return (int64_t)n * ((ho + tile_h - 1) / tile_h) * ((wo + tile_w - 1) / tile_w) * tile_h;
 }
-hipError_t launch_mask_pyramid(const PyramidArgs &a, const uint8_t *mask_in, int32_t *block_counts, hipStream_t s);
 // bytes -> bits (nonzero byte = 1; the bits of the last word past m are zero), and the
 // centre-tap rescaling of a mask in either form into either form
 hipError_t launch_mask_pack(const uint8_t *mask, int64_t m, uint64_t *bits, hipStream_t s);

@@ -91,145 +91,306 @@ hipError_t launch_mask_window(const uint8_t *mask_in, int n, int h, int w, int k
 }
 
 // ---------------------------------------------------------------------------
-// Ordered compaction, fused with the mask propagation.  A block owns 4096
-// consecutive output positions, a lane 16 of them.  The output-resolution mask is
-// never needed as an input: every kernel recomputes a position's flag from the
-// input mask (centre tap), which for a stride-1 "same" layer is one 128-bit load
-// per lane.  Ranks inside a block come from a wave prefix sum (shuffles inside a
-// wave, LDS across the four waves); the indices are staged in LDS in order and
-// copied out coalesced.  No block ever waits on another block, so every grid drains:
-//   - small inputs (up to 16 blocks): ONE launch; a block counts the kept
-//     positions of all blocks before it by itself (at most 60 KB of mask re-read
-//     per block, out of L2, all loads in flight together);
-//   - larger inputs: two launches, per-block counts first, then prefix + scatter.
+// Ordered kept lists (Sec. III-A: which patches become columns) fused with the mask
+// propagation (Sec. III-B), for one mask or for all levels of a pyramid.  A workgroup of 1024
+// threads owns 4096 consecutive positions of one list, a lane four of them: it labels them in the
+// input mask (one 32-bit load for a list at the mask's own resolution, four byte loads in flight
+// otherwise), ranks them by a prefix sum (vector ALU inside a wave, LDS across the sixteen
+// waves) and stores the kept ones.  Bound: launch latency for the masks of one image, HBM for the
+// largest.  No workgroup ever waits on another, so every grid drains:
+//   - short lists: ONE launch; a workgroup counts the kept positions before its own by itself (16 bytes per
+//     lane and load at the mask's resolution, sixteen labels per lane in flight otherwise);
+//   - longer lists: two launches, labels and per-workgroup counts first, then offsets and lists.
+// (Four levels of one 224 x 224 mask: 7.1 + 4.2 us in two launches with sixteen positions per lane and the
+// levels' maps applied one after another; the labels of 5 814 positions through a stride: 8.9 us.)
 // ---------------------------------------------------------------------------
+constexpr int kListThreads = 1024;
+constexpr int kListWaves = kListThreads / 64;
+// Most workgroups of a list in the one-launch form.  At the mask's resolution the last workgroup reads
+// 16 KB per 16 lanes-wide load, so 64 of them (256 KB) cost what one round trip and a half costs; through a
+// stride every four workgroups before it are one round trip.
+constexpr int kOnceBlocksIdentity = 64, kOnceBlocks = 16;
 
-// sum of v over the block (all threads get it); scratch holds one int per wave
+// sum of v over the workgroup (all threads get it)
+template <int WAVES>
 __device__ __forceinline__ int block_sum(int v, int *scratch)
 {
-    // wave total through ballots of the value's bits would need its width; use the scan
     const int incl = wave_inclusive_scan(v);
     __syncthreads();
     if ((threadIdx.x & 63) == 63) scratch[threadIdx.x >> 6] = incl;
     __syncthreads();
     int s = 0;
 #pragma unroll
-    for (int i = 0; i < kCompactBlockThreads / 64; ++i) s += scratch[i];
+    for (int i = 0; i < WAVES; ++i) s += scratch[i];
     return s;
 }
 
-__global__ __launch_bounds__(kCompactBlockThreads) void k_compact_count(MaskGeom g,
-                                                                         const uint8_t *__restrict__ mask_in,
-                                                                         int32_t *__restrict__ block_counts)
+// 0x80 in every nonzero byte
+__device__ __forceinline__ uint32_t nonzero_bytes(uint32_t v) { return (((v & 0x7f7f7f7fu) + 0x7f7f7f7fu) | v) & 0x80808080u; }
+
+// bit j = position p0 + j of the list is kept (p0 a multiple of four; positions past the end read as 0)
+__device__ __forceinline__ uint32_t label4(const LabelMap &L, const uint8_t *__restrict__ mask_in, int p0, bool vec)
 {
-    __shared__ int wave_sum[kCompactBlockThreads / 64];
-    const int64_t p0 = (int64_t)blockIdx.x * kCompactBlockElems + (int64_t)threadIdx.x * kCompactBytesPerThread;
-    const int c = __popc(kept_flags16(g, mask_in, p0));
-    // wave total through ballots of the count's bits (counts are 0..16: 5 bits)
-    int total = 0;
-#pragma unroll
-    for (int b = 0; b < 5; ++b) total += __popcll(__ballot((c >> b) & 1)) << b;
-    if ((threadIdx.x & 63) == 0) wave_sum[threadIdx.x >> 6] = total;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int s = 0;
-#pragma unroll
-        for (int i = 0; i < kCompactBlockThreads / 64; ++i) s += wave_sum[i];
-        block_counts[blockIdx.x] = s;
+    if (p0 >= L.m) return 0;
+    const int left = L.m - p0;
+    if (L.identity && L.packed_in) {
+        const uint32_t f = (reinterpret_cast<const uint32_t *>(mask_in)[p0 >> 5] >> (p0 & 31)) & 15u;
+        return left < 4 ? f & ((1u << left) - 1u) : f;
     }
-}
-
-// SELF = true: the block counts everything before it by itself (single launch);
-// otherwise it sums the per-block counts of the first launch.
-template <bool SELF>
-__global__ __launch_bounds__(kCompactBlockThreads) void k_compact_scatter(MaskGeom g,
-                                                                           const uint8_t *__restrict__ mask_in,
-                                                                           const int32_t *__restrict__ block_counts,
-                                                                           uint8_t *__restrict__ mask_out,
-                                                                           int32_t *__restrict__ idx,
-                                                                           int32_t *__restrict__ count,
-                                                                           CompactExtras ex)
-{
-    __shared__ int wave_sum[kCompactBlockThreads / 64];
-    __shared__ int scratch[kCompactBlockThreads / 64];
-    __shared__ int32_t stage[kCompactBlockElems];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-
-    // offset of this block = number of kept positions in all blocks before it
-    int part = 0;
-    if (SELF) {
-        // all loads of the (at most kCompactSingleLaunchBlocks - 1) earlier chunks are
-        // independent: unrolled, so that they are in flight together
-#pragma unroll
-        for (int pb = 0; pb < kCompactSingleLaunchBlocks - 1; ++pb)
-            if (pb < (int)blockIdx.x)
-                part += __popc(kept_flags16(g, mask_in, (int64_t)pb * kCompactBlockElems + (int64_t)tid * 16));
-    } else {
-        for (int i = tid; i < (int)blockIdx.x; i += kCompactBlockThreads) part += block_counts[i];
+    if (L.identity && vec && left >= 4) {
+        const uint32_t v = nonzero_bytes(*reinterpret_cast<const uint32_t *>(mask_in + p0));
+        return ((v >> 7) & 1u) | ((v >> 14) & 2u) | ((v >> 21) & 4u) | (v >> 28);
     }
-    const int block_base = block_sum(part, scratch);
-
-    const int64_t p0 = (int64_t)blockIdx.x * kCompactBlockElems + (int64_t)tid * kCompactBytesPerThread;
-    const uint32_t flags = kept_flags16(g, mask_in, p0);
-    if (mask_out && g.packed_out) {
-        // sixteen labels = one 16-bit piece of the packed mask (zeros past the end, up to a whole word)
-        if (p0 < ((g.m + 63) & ~(int64_t)63)) reinterpret_cast<uint16_t *>(mask_out)[p0 >> 4] = (uint16_t)flags;
-    } else if (mask_out) {
-        if (p0 + 16 <= g.m) {
-            uint32_t wds[4];
+    const uint32_t t = fast_div((uint32_t)p0, L.div_w);
+    int ow = p0 - (int)t * L.wl;
+    int b = (int)fast_div(t, L.div_h), oh = (int)t - b * L.hl;
+    auto along = [](const AxisMap &a, int v) { return min(max(v * a.mul + a.add, a.lo), a.hi); };
+    int row_at = (b * L.h0 + along(L.row, oh)) * L.w0;
+    int at[4];
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-                wds[q] = ((flags >> (4 * q)) & 1u) | (((flags >> (4 * q + 1)) & 1u) << 8) |
-                         (((flags >> (4 * q + 2)) & 1u) << 16) | (((flags >> (4 * q + 3)) & 1u) << 24);
-            *reinterpret_cast<uint4 *>(mask_out + p0) = make_uint4(wds[0], wds[1], wds[2], wds[3]);
-        } else {
-            for (int j = 0; j < 16 && p0 + j < g.m; ++j) mask_out[p0 + j] = (flags >> j) & 1u;
+    for (int j = 0; j < 4; ++j) {
+        at[j] = j < left ? row_at + along(L.col, ow) : -1;
+        if (++ow == L.wl) {
+            ow = 0;
+            if (++oh == L.hl) {
+                oh = 0;
+                ++b;
+            }
+            row_at = (b * L.h0 + along(L.row, oh)) * L.w0;
         }
     }
-    const int c = __popc(flags);
-    const int incl = wave_inclusive_scan(c);
-    if (lane == 63) wave_sum[wave] = incl;
-    __syncthreads();
-
-    int before = 0, block_total = 0;
+    uint32_t f = 0;
+    if (L.packed_in) {
+        uint32_t got[4];
 #pragma unroll
-    for (int i = 0; i < kCompactBlockThreads / 64; ++i) {
-        if (i < wave) before += wave_sum[i];
-        block_total += wave_sum[i];
+        for (int j = 0; j < 4; ++j) got[j] = at[j] >= 0 ? reinterpret_cast<const uint32_t *>(mask_in)[at[j] >> 5] : 0u;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) f |= ((got[j] >> (at[j] & 31)) & 1u) << j;
+    } else {
+        uint8_t got[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) got[j] = at[j] >= 0 ? mask_in[at[j]] : (uint8_t)0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) f |= got[j] ? 1u << j : 0u;
     }
-    int pos = before + incl - c;
-    uint32_t f = flags;
-    while (f) {
-        const int j = __ffs(f) - 1;
-        f &= f - 1;
-        stage[pos++] = (int32_t)(p0 + j);
-    }
-    __syncthreads();
-    for (int i = tid; i < block_total; i += kCompactBlockThreads) idx[(int64_t)block_base + i] = stage[i];
-    if (blockIdx.x == gridDim.x - 1 && tid == 0) *count = block_base + block_total;
-
-    // on the side, for the convolution that follows: clear its split-K tile counters
-    if (ex.zero && blockIdx.x == 0)
-        for (int i = tid; i < ex.zero_n; i += kCompactBlockThreads) ex.zero[i] = 0;
+    return f;
 }
 
-hipError_t launch_compact(const MaskGeom &g_in, const uint8_t *mask_in, uint8_t *mask_out, int32_t *idx,
-                          int32_t *count, int32_t *block_counts, const CompactExtras &extras, hipStream_t s)
+// Labels of positions p0 .. p0 + 3 to mask_out (bytes 0 / 1, or bits, zeros up to a whole 64-bit word).
+// All lanes call it.
+__device__ __forceinline__ void store_labels(const LabelMap &L, int p0, uint32_t f)
 {
-    MaskGeom g = g_in;
-    if (!g.packed_in && (reinterpret_cast<uintptr_t>(mask_in) & 15u)) g.identity = 0; // the 128-bit path needs alignment
-    const int nb = (int)compact_blocks(g.m);
-    if (nb <= kCompactSingleLaunchBlocks) {
-        hipLaunchKernelGGL(k_compact_scatter<true>, dim3(nb), dim3(kCompactBlockThreads), 0, s, g, mask_in,
-                           (const int32_t *)nullptr, mask_out, idx, count, extras);
+    if (!L.mask_out) return;
+    if (L.packed_out) {
+        const int lane = threadIdx.x & 63;
+        uint32_t v = f << (4 * (lane & 3));
+        v |= __shfl_xor(v, 1);
+        v |= __shfl_xor(v, 2);
+        if ((lane & 3) == 0 && (int64_t)p0 < (((int64_t)L.m + 63) & ~(int64_t)63)) reinterpret_cast<uint16_t *>(L.mask_out)[p0 >> 4] = (uint16_t)v;
+        return;
+    }
+    if (p0 + 4 <= L.m) {
+        *reinterpret_cast<uint32_t *>(L.mask_out + p0) =
+            (f & 1u) | ((f & 2u) << 7) | ((f & 4u) << 14) | ((f & 8u) << 21);
+    } else {
+        for (int j = 0; j < 4 && p0 + j < L.m; ++j) L.mask_out[p0 + j] = (f >> j) & 1u;
+    }
+}
+
+template <int NL>
+__device__ __forceinline__ int list_of_block(const ListArgs<NL> &a, int block)
+{
+    int l = 0;
+#pragma unroll
+    for (int i = 1; i < NL; ++i)
+        if (i < a.lists && block >= a.at[i].block0) l = i;
+    return l;
+}
+
+// the workgroup's part of the list: kept positions p0 .. p0 + 3 of every lane after `base` earlier ones;
+// returns the number kept by the whole workgroup
+__device__ __forceinline__ int store_list(const LabelMap &L, int p0, uint32_t f, int base, int *wave_sum)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int c = __popc(f), incl = wave_inclusive_scan(c);
+    if (lane == 63) wave_sum[wave] = incl;
+    __syncthreads();
+    int before = 0, total = 0;
+#pragma unroll
+    for (int i = 0; i < kListWaves; ++i) {
+        const int t = wave_sum[i];
+        before += i < wave ? t : 0;
+        total += t;
+    }
+    int32_t *to = L.idx + (base + before + incl - c);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        if ((f >> j) & 1u) *to++ = p0 + j;
+    return total;
+}
+
+// one launch: labels, lists and counts
+template <int NL>
+__global__ __launch_bounds__(kListThreads) void k_lists_once(ListArgs<NL> a, const uint8_t *__restrict__ mask_in)
+{
+    __shared__ int wave_sum[kListWaves], scratch[kListWaves];
+    const int tid = threadIdx.x;
+    const LabelMap &L = a.at[NL == 1 ? 0 : list_of_block(a, blockIdx.x)];
+    const int block = blockIdx.x - L.block0;
+    const int p0 = block * kCompactBlockElems + tid * 4;
+    const bool vec = a.vec_in != 0;
+    const uint32_t f = label4(L, mask_in, p0, vec);
+
+    // kept positions of this list before this workgroup's
+    int part = 0;
+    if (L.identity && vec && !L.packed_in) {
+        const uint4 *m4 = reinterpret_cast<const uint4 *>(mask_in);
+        const int pieces = block * (kCompactBlockElems / 16);
+        for (int i0 = tid; i0 < pieces; i0 += 4 * kListThreads) {
+            uint4 v[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[k] = i0 + k * kListThreads < pieces ? m4[i0 + k * kListThreads] : make_uint4(0, 0, 0, 0);
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                part += __popc(nonzero_bytes(v[k].x)) + __popc(nonzero_bytes(v[k].y)) + __popc(nonzero_bytes(v[k].z)) +
+                        __popc(nonzero_bytes(v[k].w));
+        }
+    } else {
+        for (int b0 = 0; b0 < block; b0 += 4) {
+            uint32_t g[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                g[k] = b0 + k < block ? label4(L, mask_in, (b0 + k) * kCompactBlockElems + tid * 4, vec) : 0u;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) part += __popc(g[k]);
+        }
+    }
+    store_labels(L, p0, f);
+    const int base = block ? block_sum<kListWaves>(part, scratch) : 0;
+    const int total = store_list(L, p0, f, base, wave_sum);
+    if (tid == 0 && (int64_t)(block + 1) * kCompactBlockElems >= L.m) *L.count = base + total;
+
+    // on the side, for the convolution that follows: clear its split-K tile counters
+    if (NL == 1 && a.ex.zero && blockIdx.x == 0)
+        for (int i = tid; i < a.ex.zero_n; i += kListThreads) a.ex.zero[i] = 0;
+}
+
+// two launches: labels and per-workgroup counts ...
+template <int NL>
+__global__ __launch_bounds__(kListThreads) void k_lists_count(ListArgs<NL> a, const uint8_t *__restrict__ mask_in,
+                                                              int32_t *__restrict__ block_counts)
+{
+    __shared__ int scratch[kListWaves];
+    const LabelMap &L = a.at[NL == 1 ? 0 : list_of_block(a, blockIdx.x)];
+    const int p0 = (blockIdx.x - L.block0) * kCompactBlockElems + threadIdx.x * 4;
+    const uint32_t f = label4(L, mask_in, p0, a.vec_in != 0);
+    store_labels(L, p0, f);
+    const int total = block_sum<kListWaves>(__popc(f), scratch);
+    if (threadIdx.x == 0) block_counts[blockIdx.x] = total;
+}
+
+// ... then offsets and lists (labels from mask_out where the first launch left them)
+template <int NL>
+__global__ __launch_bounds__(kListThreads) void k_lists_scatter(ListArgs<NL> a, const uint8_t *__restrict__ mask_in,
+                                                                const int32_t *__restrict__ block_counts)
+{
+    __shared__ int wave_sum[kListWaves], scratch[kListWaves];
+    const int tid = threadIdx.x;
+    const LabelMap &L = a.at[NL == 1 ? 0 : list_of_block(a, blockIdx.x)];
+    const int p0 = (blockIdx.x - L.block0) * kCompactBlockElems + tid * 4;
+    uint32_t f = 0;
+    if (L.mask_out && p0 < L.m) {
+        if (L.packed_out) {
+            f = (reinterpret_cast<const uint32_t *>(L.mask_out)[p0 >> 5] >> (p0 & 31)) & 15u; // (zeros past the end)
+        } else if (p0 + 4 <= L.m) {
+            const uint32_t v = *reinterpret_cast<const uint32_t *>(L.mask_out + p0); // bytes 0 / 1
+            f = (v & 1u) | ((v >> 7) & 2u) | ((v >> 14) & 4u) | ((v >> 21) & 8u);
+        } else {
+            for (int j = 0; p0 + j < L.m; ++j) f |= L.mask_out[p0 + j] ? 1u << j : 0u;
+        }
+    } else if (!L.mask_out) {
+        f = label4(L, mask_in, p0, a.vec_in != 0);
+    }
+    int part = 0;
+    for (int i = L.block0 + tid; i < (int)blockIdx.x; i += kListThreads) part += block_counts[i];
+    const int base = block_sum<kListWaves>(part, scratch);
+    const int total = store_list(L, p0, f, base, wave_sum);
+    if (tid == 0 && (int64_t)((int)blockIdx.x - L.block0 + 1) * kCompactBlockElems >= L.m) *L.count = base + total;
+    if (NL == 1 && a.ex.zero && blockIdx.x == 0)
+        for (int i = tid; i < a.ex.zero_n; i += kListThreads) a.ex.zero[i] = 0;
+}
+
+template <int NL>
+static hipError_t launch_lists_n(const ListArgs<NL> &a, const uint8_t *mask_in, int32_t *block_counts, hipStream_t s)
+{
+    bool once = true;
+    for (int l = 0; l < a.lists; ++l) {
+        const bool fast = a.at[l].identity && a.vec_in && !a.at[l].packed_in;
+        once = once && compact_blocks(a.at[l].m) <= (fast ? kOnceBlocksIdentity : kOnceBlocks);
+    }
+    if (once) {
+        hipLaunchKernelGGL(k_lists_once<NL>, dim3(a.blocks), dim3(kListThreads), 0, s, a, mask_in);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL(k_compact_count, dim3(nb), dim3(kCompactBlockThreads), 0, s, g, mask_in, block_counts);
-    hipError_t e = hipGetLastError();
+    hipLaunchKernelGGL(k_lists_count<NL>, dim3(a.blocks), dim3(kListThreads), 0, s, a, mask_in, block_counts);
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_compact_scatter<false>, dim3(nb), dim3(kCompactBlockThreads), 0, s, g, mask_in,
-                       (const int32_t *)block_counts, mask_out, idx, count, extras);
+    hipLaunchKernelGGL(k_lists_scatter<NL>, dim3(a.blocks), dim3(kListThreads), 0, s, a, mask_in,
+                       (const int32_t *)block_counts);
     return hipGetLastError();
+}
+
+hipError_t launch_lists(const ListArgs<1> &a, const uint8_t *mask_in, int32_t *block_counts, hipStream_t s)
+{
+    return launch_lists_n(a, mask_in, block_counts, s);
+}
+
+hipError_t launch_lists(const ListArgs<kMaxPyramidLevels> &a, const uint8_t *mask_in, int32_t *block_counts, hipStream_t s)
+{
+    return launch_lists_n(a, mask_in, block_counts, s);
+}
+
+static int32_t to_int32(int64_t v)
+{
+    const int64_t most = 1 << 30; // (far outside every image: what matters is the side it is clamped to)
+    return (int32_t)(v > most ? most : (v < -most ? -most : v));
+}
+
+AxisMap compose_axis(int32_t stride, int32_t first, int32_t inner_size, const AxisMap &inner)
+{
+    auto image = [&](int64_t v) {
+        const int64_t t = v * inner.mul + inner.add;
+        return (int32_t)(t < inner.lo ? inner.lo : (t > inner.hi ? inner.hi : t));
+    };
+    AxisMap r;
+    r.mul = to_int32((int64_t)stride * inner.mul);
+    r.add = to_int32((int64_t)first * inner.mul + inner.add);
+    r.lo = image(0);
+    r.hi = image(inner_size - 1);
+    return r;
+}
+
+hipError_t launch_compact(const MaskGeom &g, const uint8_t *mask_in, uint8_t *mask_out, int32_t *idx,
+                          int32_t *count, int32_t *block_counts, const CompactExtras &extras, hipStream_t s)
+{
+    ListArgs<1> a;
+    a.lists = 1;
+    a.blocks = (int)compact_blocks(g.m);
+    a.vec_in = (reinterpret_cast<uintptr_t>(mask_in) & 15u) == 0;
+    a.ex = extras;
+    LabelMap &L = a.at[0];
+    L.m = (int32_t)g.m;
+    L.hl = g.ho; L.wl = g.wo; L.h0 = g.h; L.w0 = g.w;
+    L.identity = g.identity;
+    L.packed_in = g.packed_in; L.packed_out = g.packed_out;
+    L.block0 = 0;
+    const AxisMap rows = {1, 0, 0, g.h - 1}, cols = {1, 0, 0, g.w - 1};
+    L.row = compose_axis(g.sh, g.ch0, g.h, rows);
+    L.col = compose_axis(g.sw, g.cw0, g.w, cols);
+    L.div_w = make_fastdiv((uint32_t)g.wo);
+    L.div_h = make_fastdiv((uint32_t)g.ho);
+    L.mask_out = mask_out; L.idx = idx; L.count = count;
+    return launch_lists(a, mask_in, block_counts, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -284,7 +445,7 @@ __global__ __launch_bounds__(kCompactBlockThreads) void k_tiled_count(TiledGeom 
     __shared__ int scratch[kCompactBlockThreads / 64];
     int first;
     const uint32_t flags = tiled_row_flags(g, mask, (int)(blockIdx.x * kCompactBlockThreads + threadIdx.x), &first);
-    const int total = block_sum(__popc(flags), scratch);
+    const int total = block_sum<kCompactBlockThreads / 64>(__popc(flags), scratch);
     if (threadIdx.x == 0) block_counts[blockIdx.x] = total;
 }
 
@@ -299,7 +460,7 @@ __global__ __launch_bounds__(kCompactBlockThreads) void k_tiled_scatter(TiledGeo
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     int part = 0;
     for (int i = tid; i < (int)blockIdx.x; i += kCompactBlockThreads) part += block_counts[i];
-    const int block_base = block_sum(part, scratch);
+    const int block_base = block_sum<kCompactBlockThreads / 64>(part, scratch);
     int first;
     const uint32_t flags = tiled_row_flags(g, mask, (int)(blockIdx.x * kCompactBlockThreads + tid), &first);
     const int c = __popc(flags);
@@ -338,182 +499,6 @@ hipError_t launch_compact_tiled(const uint8_t *mask, int n, int ho, int wo, int 
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_tiled_scatter, dim3(nb), dim3(kCompactBlockThreads), 0, s, g, mask,
                        (const int32_t *)block_counts, idx, count);
-    return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------
-// Mask pyramid (Sec. III-B: one mask, rescaled to every layer's size): the masks and
-// the kept-position lists of all levels from the input mask, in two launches.
-// Level l is the centre-tap rescaling of level l - 1, so a position of level l reads
-// the input mask through the composition of the levels' index maps; no level waits for
-// another.  Launch 1 writes every level's 0/1 mask and per-block counts, launch 2 turns
-// the counts into offsets and writes the ordered lists.
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ int pyramid_level_of(const PyramidArgs &a, int block)
-{
-    int l = 0;
-#pragma unroll
-    for (int i = 1; i < kMaxPyramidLevels; ++i)
-        if (i < a.levels && block >= a.block0[i]) l = i;
-    return l;
-}
-
-__global__ __launch_bounds__(kCompactBlockThreads) void k_pyramid_masks(PyramidArgs a,
-                                                                         const uint8_t *__restrict__ mask_in,
-                                                                         int32_t *__restrict__ block_counts)
-{
-    __shared__ int scratch[kCompactBlockThreads / 64];
-    const int l = pyramid_level_of(a, blockIdx.x);
-    const int64_t m = a.m[l];
-    const int64_t p0 = (int64_t)(blockIdx.x - a.block0[l]) * kCompactBlockElems +
-                       (int64_t)threadIdx.x * kCompactBytesPerThread;
-    uint32_t flags = 0;
-    if (l == 0 && a.identity0 && a.packed_in) {
-        if (p0 < m) {
-            flags = reinterpret_cast<const uint16_t *>(mask_in)[p0 >> 4];
-            if (p0 + 16 > m) flags &= (1u << (uint32_t)(m - p0)) - 1u;
-        }
-    } else if (l == 0 && a.identity0 && p0 + 16 <= m) {
-        // the first level keeps the resolution of an aligned input mask: one 128-bit load
-        const uint4 v = *reinterpret_cast<const uint4 *>(mask_in + p0);
-        const uint32_t wds[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-#pragma unroll
-            for (int b = 0; b < 4; ++b) flags |= ((wds[q] >> (8 * b)) & 0xffu) ? (1u << (4 * q + b)) : 0u;
-    } else if (p0 < m) {
-        // (positions fit 31 bits; the level's parameters are read with constant indices, so they
-        // sit in scalar registers instead of being fetched again for every position)
-        const int wl = a.w[l + 1], hl = a.h[l + 1];
-        const uint32_t t = fast_div((uint32_t)p0, a.div_w[l]);
-        int ow = (int)((uint32_t)p0 - t * (uint32_t)wl);
-        int b = (int)fast_div(t, a.div_h[l]);
-        int oh = (int)(t - (uint32_t)b * (uint32_t)hl);
-        // a row / column of level l seen through all levels down to the input mask
-        auto row_in = [&](int v) {
-#pragma unroll
-            for (int q = kMaxPyramidLevels - 1; q >= 0; --q)
-                if (q <= l) v = min(max(v * a.sh[q] + a.ch0[q], 0), a.h[q] - 1);
-            return v;
-        };
-        auto col_in = [&](int v) {
-#pragma unroll
-            for (int q = kMaxPyramidLevels - 1; q >= 0; --q)
-                if (q <= l) v = min(max(v * a.sw[q] + a.cw0[q], 0), a.w[q] - 1);
-            return v;
-        };
-        int row_at = (b * a.h[0] + row_in(oh)) * a.w[0];
-        // addresses first, then all sixteen bytes in flight together
-        int at[16];
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            at[j] = p0 + j < m ? row_at + col_in(ow) : -1;
-            if (++ow == wl) {
-                ow = 0;
-                if (++oh == hl) {
-                    oh = 0;
-                    ++b;
-                }
-                row_at = (b * a.h[0] + row_in(oh)) * a.w[0];
-            }
-        }
-        if (a.packed_in) {
-            uint32_t got[16];
-#pragma unroll
-            for (int j = 0; j < 16; ++j)
-                got[j] = at[j] >= 0 ? reinterpret_cast<const uint32_t *>(mask_in)[at[j] >> 5] : 0u;
-#pragma unroll
-            for (int j = 0; j < 16; ++j) flags |= ((got[j] >> (at[j] & 31)) & 1u) << j;
-        } else {
-            uint8_t got[16];
-#pragma unroll
-            for (int j = 0; j < 16; ++j) got[j] = at[j] >= 0 ? mask_in[at[j]] : (uint8_t)0;
-#pragma unroll
-            for (int j = 0; j < 16; ++j) flags |= got[j] ? (1u << j) : 0u;
-        }
-    }
-    if (a.packed_out) {
-        if (p0 < ((m + 63) & ~(int64_t)63)) reinterpret_cast<uint16_t *>(a.mask_out[l])[p0 >> 4] = (uint16_t)flags;
-    } else if (p0 < m) {
-        uint8_t *mo = a.mask_out[l];
-        if (p0 + 16 <= m && (reinterpret_cast<uintptr_t>(mo) & 15u) == 0) {
-            uint32_t wds[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                wds[q] = ((flags >> (4 * q)) & 1u) | (((flags >> (4 * q + 1)) & 1u) << 8) |
-                         (((flags >> (4 * q + 2)) & 1u) << 16) | (((flags >> (4 * q + 3)) & 1u) << 24);
-            *reinterpret_cast<uint4 *>(mo + p0) = make_uint4(wds[0], wds[1], wds[2], wds[3]);
-        } else {
-            for (int j = 0; j < 16 && p0 + j < m; ++j) mo[p0 + j] = (flags >> j) & 1u;
-        }
-    }
-    const int total = block_sum(__popc(flags), scratch);
-    if (threadIdx.x == 0) block_counts[blockIdx.x] = total;
-}
-
-__global__ __launch_bounds__(kCompactBlockThreads) void k_pyramid_lists(PyramidArgs a,
-                                                                         const int32_t *__restrict__ block_counts)
-{
-    __shared__ int wave_sum[kCompactBlockThreads / 64];
-    __shared__ int scratch[kCompactBlockThreads / 64];
-    __shared__ int32_t stage[kCompactBlockElems];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int l = pyramid_level_of(a, blockIdx.x);
-    const int64_t m = a.m[l];
-    const int first = a.block0[l], last = a.block0[l + 1] - 1;
-
-    int part = 0;
-    for (int i = first + tid; i < (int)blockIdx.x; i += kCompactBlockThreads) part += block_counts[i];
-    const int block_base = block_sum(part, scratch);
-
-    // the level's own 0/1 mask, written by the first launch
-    const int64_t p0 = (int64_t)(blockIdx.x - first) * kCompactBlockElems + (int64_t)tid * kCompactBytesPerThread;
-    const uint8_t *mo = a.mask_out[l];
-    uint32_t flags = 0;
-    if (a.packed_out) {
-        if (p0 < m) flags = reinterpret_cast<const uint16_t *>(mo)[p0 >> 4]; // (zeros past the end)
-    } else if (p0 + 16 <= m && (reinterpret_cast<uintptr_t>(mo) & 15u) == 0) {
-        const uint4 v = *reinterpret_cast<const uint4 *>(mo + p0);
-        const uint32_t wds[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-#pragma unroll
-            for (int b = 0; b < 4; ++b) flags |= ((wds[q] >> (8 * b)) & 0xffu) ? (1u << (4 * q + b)) : 0u;
-    } else {
-        for (int j = 0; j < 16 && p0 + j < m; ++j)
-            if (mo[p0 + j]) flags |= 1u << j;
-    }
-    const int c = __popc(flags);
-    const int incl = wave_inclusive_scan(c);
-    if (lane == 63) wave_sum[wave] = incl;
-    __syncthreads();
-    int before = 0, block_total = 0;
-#pragma unroll
-    for (int i = 0; i < kCompactBlockThreads / 64; ++i) {
-        if (i < wave) before += wave_sum[i];
-        block_total += wave_sum[i];
-    }
-    int pos = before + incl - c;
-    uint32_t f = flags;
-    while (f) {
-        const int j = __ffs(f) - 1;
-        f &= f - 1;
-        stage[pos++] = (int32_t)(p0 + j);
-    }
-    __syncthreads();
-    int32_t *idx = a.idx[l];
-    for (int i = tid; i < block_total; i += kCompactBlockThreads) idx[(int64_t)block_base + i] = stage[i];
-    if ((int)blockIdx.x == last && tid == 0) *a.count[l] = block_base + block_total;
-}
-
-hipError_t launch_mask_pyramid(const PyramidArgs &a, const uint8_t *mask_in, int32_t *block_counts, hipStream_t s)
-{
-    const int nb = a.block0[a.levels];
-    hipLaunchKernelGGL(k_pyramid_masks, dim3(nb), dim3(kCompactBlockThreads), 0, s, a, mask_in, block_counts);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_pyramid_lists, dim3(nb), dim3(kCompactBlockThreads), 0, s, a,
-                       (const int32_t *)block_counts);
     return hipGetLastError();
 }
 

@@ -166,3 +166,27 @@ def test_layers_that_read_byte_masks_refuse_packed_ones():
     dw = B.conv_desc(1, 16, 16, 16, 16, in_dtype=B.BF16, out_dtype=B.BF16, flags=B.PACKED_MASKS)
     assert B.lib().fc_focused_dwconv2d(ctypes.byref(dw), t.data_ptr(), t.data_ptr(), t.data_ptr(), None, o.data_ptr(),
                                        None) == -3
+
+
+@pytest.mark.parametrize("n,h,w", [(1, 256, 257), (4, 256, 257), (1, 512, 513), (3, 91, 5), (1, 64, 64)])
+@pytest.mark.parametrize("first", [((3, 3), (1, 1), (1, 1), (1, 1)), ((7, 7), (2, 2), (3, 3), (1, 1)),
+                                   ((5, 3), (1, 3), (9, 0), (2, 1))])
+@pytest.mark.parametrize("packed", [False, True])
+def test_pyramid_lists_around_the_one_launch_limits(n, h, w, first, packed):
+    """Level sizes on both sides of 16 and of 64 workgroups of 4096 positions, a first level with the mask's
+    resolution, a strided one, and one whose window reaches far outside the image (clamped twice)."""
+    mask = synth.mask_bernoulli(n, h, w, 0.5, 260, h, w) * np.uint8(5)
+    steps = [first, ((3, 3), (2, 2), (1, 1), (1, 1)), ((3, 3), (1, 2), (3, 1), (1, 1))]
+    pyr = B.PreparedPyramid(G.mask_dev(mask), steps, packed=packed)
+    m = mask
+    for (m_out, idx, count), (k, s, p, d), dims in zip(pyr(), steps, pyr.dims):
+        m = O.mask_downsample(m, k[0], k[1], s, p, d)
+        assert m.shape == dims
+        got = m_out.cpu().numpy()
+        if packed:
+            got = np.unpackbits(got.view(np.uint8), bitorder="little")[:m.size].reshape(m.shape)
+        np.testing.assert_array_equal(got, m)
+        want_idx, want_cnt = O.active_index_compact(m.reshape(-1))
+        cnt = int(count.cpu().item())
+        assert cnt == want_cnt
+        np.testing.assert_array_equal(idx[:cnt].cpu().numpy(), want_idx)
