@@ -298,13 +298,14 @@ int32_t fc_focused_conv2d(const fc_conv_desc *desc, const void *x, const uint8_t
     hipStream_t s = (hipStream_t)stream;
 
     const bool mfma = conv_mfma_supported(g, desc->in_dtype, desc->out_dtype);
+    const bool stem = !mfma && conv_stem_supported(g, desc->in_dtype, desc->out_dtype);
     const bool packed = (g.flags & FC_PACKED_MASKS) != 0;
     // the kernel for RGB stems reads byte masks image by image
-    if (packed && !mfma && conv_stem_supported(g, desc->in_dtype, desc->out_dtype)) return FC_ERR_DTYPE;
+    if (packed && stem) return FC_ERR_DTYPE;
     // 8-bit layers exist on the matrix cores only (16 | c_in, 8 | c_out, at most 32 taps)
     if (desc->in_dtype == FC_FP8 && !mfma) return FC_ERR_DTYPE;
     // 8-bit outputs: the matrix-core kernels round to them, the direct kernel does not
-    if (desc->out_dtype == FC_FP8 && !mfma && !conv_stem_supported(g, desc->in_dtype, desc->out_dtype))
+    if (desc->out_dtype == FC_FP8 && !mfma && !stem)
         return FC_ERR_DTYPE;
     if (g.flags & (FC_COMPACT_OUT | FC_COMPACT_IN)) {
         // compacted activations: rows in list order, so the list must be given
@@ -391,12 +392,12 @@ int32_t fc_focused_conv2d(const fc_conv_desc *desc, const void *x, const uint8_t
     } else {
         if (f32)
             e = launch_conv_f32(g, x, mask_in, mask_out, w, bias, idx, count, out, s);
-        else if (conv_stem_supported(g, desc->in_dtype, desc->out_dtype))
-            e = launch_conv_stem(g, desc->in_dtype, desc->out_dtype, x, mask_in, w, bias, idx, count, out, s);
+        else if (stem)
+            e = launch_conv_stem(g, desc->in_dtype, desc->out_dtype, x, mask_in, mask_out, w, bias, idx, count, out, s);
         else
             e = launch_conv_direct(g, desc->in_dtype, desc->out_dtype, x, mask_in, w, bias, idx, count, out, s);
         if (e != hipSuccess) return FC_ERR_HIP;
-        if (mask_in && !(f32 && !idx) && !(g.flags & FC_SKIP_ZERO_FILL)) {
+        if (mask_in && !stem && !(f32 && !idx) && !(g.flags & FC_SKIP_ZERO_FILL)) {
             e = launch_zero_fill(g, mask_in, mask_out, out, desc->out_dtype, s);
             if (e != hipSuccess) return FC_ERR_HIP;
         }

@@ -7,11 +7,17 @@
 // the patch of a kept position is gathered element by element straight into the MFMA's
 // B-operand registers: lane l of a wave owns position l % 32 of its 32-row block and the
 // reduction elements (l / 32) * 8 .. + 8 of every 16-wide step; a small table in LDS gives,
-// for each reduction index k = (kh, kw, ci), the tap number and the element offset from the
-// position's first tap.  A tap that falls outside the image or on an irrelevant input pixel
-// contributes zeros and is never loaded.  The weights of 64 output channels sit in LDS as
-// the A operand for the whole kernel; accumulators start from the bias; the epilogue applies
-// ReLU, rounds once, transposes the tile through LDS and stores whole 16-byte row pieces.
+// for each reduction index, the tap number and the element offset from the position's first tap.
+// The pixels of one kernel row lie side by side, so the reduction is laid out kernel row by kernel
+// row, each padded to whole pieces of 8 elements, and a lane fetches a piece with one (unaligned)
+// 16-byte load; elements of taps outside the image or on an irrelevant input pixel, and
+// the padding, are then replaced by zeros.  (7x7 on one 224 x 224 image: eight 2-byte loads a step
+// and a weight loop with one load in flight took 32 us.)  A wave whose pieces would reach
+// past either end of x, a dilated kernel, and kernels whose rows are far from whole pieces load element by element.  The weights of 64 output channels
+// sit in LDS as the A operand for the whole kernel; accumulators start from the bias; the epilogue
+// applies ReLU, rounds once, transposes the tile through LDS and stores whole 16-byte row pieces.
+// With a mask the kernel also clears the irrelevant rows: workgroups without a tile do it when
+// there are enough of them, else all after their tiles.
 #include "fc_mfma_util.hpp"
 
 namespace fc {
@@ -19,7 +25,8 @@ namespace fc {
 constexpr int kStemThreads = 256;   // 4 waves, 32 positions each
 constexpr int kStemRows = 128;      // positions per tile
 constexpr int kStemCo = 64;         // output channels per workgroup
-constexpr int kStemMaxK = 160;      // padded reduction length the tables are sized for (7x7x3 = 147)
+constexpr int kStemMaxK = 160;      // longest reduction (7x7x3 = 147)
+constexpr int kStemMaxPadded = 192; // longest reduction laid out by kernel rows (7 x 24 = 168)
 constexpr int kStemMaxTaps = 64;    // tap-valid bits live in one 64-bit word per position
 
 // bytes per weight row in LDS: the padded reduction plus one 16-byte piece, so that the 32
@@ -41,14 +48,20 @@ bool conv_stem_supported(const Geom &g, int in_dtype, int out_dtype)
     return true;
 }
 
-// divisors of the position decode, prepared on the host
+// divisors and the layout of the reduction, prepared on the host
 struct StemDivs {
-    FastDiv wo, ho;
+    FastDiv wo, ho, row;
+    FastDiv per_co, per_row; // pieces of 8 elements: of the whole padded reduction, of one padded row
+    int32_t row_pieces;
+    int32_t pitch;  // padded elements of a kernel row; 0: reduction elements in plain (kh, kw, ci) order
+    int32_t ksteps; // 16-wide steps of the (padded) reduction
+    int32_t reach;  // elements from a position's first one to the end of its last piece
 };
 
 template <int DT, typename TO>
-__global__ __launch_bounds__(kStemThreads, 5) void k_conv_stem(Geom g, StemDivs dv, const uint16_t *__restrict__ x,
+__global__ __launch_bounds__(kStemThreads, 4) void k_conv_stem(Geom g, StemDivs dv, const uint16_t *__restrict__ x,
                                                             const uint8_t *__restrict__ mask_in,
+                                                            const uint8_t *__restrict__ mask_out,
                                                             const uint16_t *__restrict__ w,
                                                             const float *__restrict__ bias,
                                                             const int32_t *__restrict__ idx,
@@ -60,7 +73,8 @@ __global__ __launch_bounds__(kStemThreads, 5) void k_conv_stem(Geom g, StemDivs 
     const int rows = idx ? *count : g.m;
     const int taps = g.kh * g.kw;
     const int K = taps * g.c_in;
-    const int ksteps = (K + 15) / 16;
+    const int ksteps = dv.ksteps;
+    const int row_len = g.kw * g.c_in; // reduction elements of a kernel row
     // LDS, sized by the launcher for this layer's reduction length (a 3x3x3 stem needs 24 KB,
     // so six workgroups share a CU and hide each other's gather latency)
     const int WPITCH = stem_weight_pitch(ksteps);                   // bytes per weight row
@@ -73,19 +87,52 @@ __global__ __launch_bounds__(kStemThreads, 5) void k_conv_stem(Geom g, StemDivs 
     uint32_t *tap_s = reinterpret_cast<uint32_t *>(bias_s + kStemCo); // [tap] kh*dh | kw*dw << 16
     const int co0 = blockIdx.y * kStemCo;
 
-    // ---- once per workgroup: weights and the reduction-index table ----
-    for (int i = tid; i < kStemCo * ksteps * 16; i += kStemThreads) {
-        const int j = i / (ksteps * 16), k = i - j * (ksteps * 16);
-        const int co = co0 + j;
-        const uint16_t v = (co < g.c_out && k < K) ? w[(int64_t)co * K + k] : (uint16_t)0;
-        *reinterpret_cast<uint16_t *>(w_s + j * WPITCH + k * 2) = v;
+    // ---- once per workgroup: weights, a piece of 8 reduction elements per load, and the
+    // reduction-index table ----
+    {
+        const int per_co = ksteps * 2, w_elems = g.c_out * K;
+        const int wrow = dv.pitch ? row_len : K; // elements of a padded row
+        constexpr int U = 3; // loads in flight
+        for (int i0 = tid; i0 < kStemCo * per_co; i0 += U * kStemThreads) {
+            uint4 wv[U];
+            int left[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int i = i0 + u * kStemThreads;
+                const int j = (int)fast_div((uint32_t)i, dv.per_co), q = i - j * per_co;
+                const int row = (int)fast_div((uint32_t)q, dv.per_row), e0 = (q - row * dv.row_pieces) * 8;
+                // elements of the piece that exist; one that would leave the tensor is loaded further up
+                left[u] = (j < kStemCo && co0 + j < g.c_out && row * wrow < K) ? min(wrow - e0, 8) : 0;
+                const int src = left[u] > 0 ? (co0 + j) * K + row * wrow + e0 : 0, at = min(src, w_elems - 8);
+                left[u] |= (src - at) << 8;
+                __builtin_memcpy(&wv[u], w + at, 16);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int i = i0 + u * kStemThreads;
+                const int n = left[u] & 255;
+                for (int k = left[u] >> 8; k > 0; --k) { // ... and moved back, an element at a time (rare)
+                    wv[u].x = (wv[u].x >> 16) | (wv[u].y << 16);
+                    wv[u].y = (wv[u].y >> 16) | (wv[u].z << 16);
+                    wv[u].z = (wv[u].z >> 16) | (wv[u].w << 16);
+                    wv[u].w >>= 16;
+                }
+                auto keep = [&](int t) { return t + 1 < n ? 0xffffffffu : (t < n ? 0xffffu : 0u); };
+                const uint4 v = make_uint4(wv[u].x & keep(0), wv[u].y & keep(2), wv[u].z & keep(4), wv[u].w & keep(6));
+                const int j = (int)fast_div((uint32_t)i, dv.per_co), q = i - j * per_co;
+                if (j < kStemCo) *reinterpret_cast<uint4 *>(w_s + j * WPITCH + q * 16) = v;
+            }
+        }
     }
     for (int k = tid; k < ksteps * 16; k += kStemThreads) {
-        uint32_t e = 0xff000000u; // padding of the reduction: a tap number no position has
-        if (k < K) {
-            const int tap = k / g.c_in, ci = k - tap * g.c_in;
-            const int kh = tap / g.kw, kw = tap - kh * g.kw;
-            e = ((uint32_t)tap << 24) | (uint32_t)((kh * g.dh * g.w + kw * g.dw) * g.c_in + ci);
+        uint32_t e = 0xff000000u; // padding of the reduction: a tap number no position has (63 modulo 64)
+        const int kh = dv.pitch ? k / dv.pitch : (int)fast_div((uint32_t)k, dv.row);
+        const int r = k - kh * (dv.pitch ? dv.pitch : row_len);
+        if (kh < g.kh) {
+            const int kw = r / g.c_in, ci = r - kw * g.c_in;
+            // (the first element of a piece carries its offset whether or not it is padding)
+            e = (uint32_t)((kh * g.dh * g.w + kw * g.dw) * g.c_in + ci) |
+                (r < row_len ? (uint32_t)(kh * g.kw + kw) << 24 : 0xff000000u);
         }
         lut[k] = e;
     }
@@ -101,68 +148,80 @@ __global__ __launch_bounds__(kStemThreads, 5) void k_conv_stem(Geom g, StemDivs 
     const int ntiles = (rows + kStemRows - 1) / kStemRows;
     // ---- locating a tile's rows, in pieces so that the memory round trips of the NEXT tile
     // (position list, then mask bytes) run under the gathers, MFMAs and stores of the current
-    // one.  Piece 1: the list entry.  Piece 2: decode it and request the first sixteen taps'
-    // mask bytes (eight per half-wave).  Piece 3: tap-valid bits from those bytes, the remaining
-    // taps (kernels with more than sixteen) fetched on the spot, halves merged. ----
+    // one.  Piece 1: the list entry.  Piece 2: decode it and request the mask bytes, the taps of a
+    // kernel row with one (unaligned) 8-byte load, alternate kernel rows per half-wave.  Piece 3: tap-valid
+    // bits from those bytes, halves merged.  (Kernels with more than eight rows or columns, or
+    // dilated: tap by tap in piece 3.) ----
+    const int64_t mask_bytes = (int64_t)g.n * g.h * g.w;
+    const bool by_rows = g.kw <= 8 && g.kh <= 8 && g.dw == 1 && mask_bytes >= 8;
     struct Located {
-        int p, base, ih0, iw0;
-        const uint8_t *mimg;
-        bool lookup;       // bits have to be built tap by tap
-        bool inside[8];
-        uint8_t mb[8];
+        int p, base, ih0, iw0, b;
+        bool lookup;       // bits have to be built
+        uint2 rows[4];
     };
     auto fetch_entry = [&](int tile) -> int {
         const int r = tile * kStemRows + wave * 32 + (lane & 31);
         return r < rows ? (idx ? idx[r] : r) : -1;
     };
-    auto request_taps = [&](const Located &L, int t0, bool (&inside)[8], uint8_t (&mb)[8]) {
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int t = t0 + 2 * u;
-            const uint32_t e = tap_s[t & (kStemMaxTaps - 1)];
-            const int ih = L.ih0 + (int)(e & 0xffffu), iw = L.iw0 + (int)(e >> 16);
-            inside[u] = t < taps && ih >= 0 && ih < g.h && iw >= 0 && iw < g.w;
-            mb[u] = 1;
-            // a tap outside the image reads the image's first pixel instead and is dropped afterwards
-            if (L.mimg) mb[u] = L.mimg[inside[u] ? ih * g.w + iw : 0];
-        }
-    };
     auto decode = [&](int p, Located &L) {
         L.p = p;
         L.base = 0;
-        L.ih0 = L.iw0 = 0;
-        L.mimg = nullptr;
+        L.ih0 = L.iw0 = L.b = 0;
         L.lookup = false;
         if (p >= 0) {
             const int q = (int)fast_div((uint32_t)p, dv.wo);
             const int ow = p - q * g.wo;
-            const int b = (int)fast_div((uint32_t)q, dv.ho);
-            const int oh = q - b * g.ho;
+            L.b = (int)fast_div((uint32_t)q, dv.ho);
+            const int oh = q - L.b * g.ho;
             L.ih0 = oh * g.sh - g.ph;
             L.iw0 = ow * g.sw - g.pw;
-            L.base = ((b * g.h + L.ih0) * g.w + L.iw0) * g.c_in; // may point before the image: only used with a valid tap
-            L.mimg = mask_in ? mask_in + (int64_t)b * g.h * g.w : nullptr;
+            L.base = ((L.b * g.h + L.ih0) * g.w + L.iw0) * g.c_in; // may point before the image: only used with a valid tap
             const bool interior = L.ih0 >= 0 && L.ih0 + reach_h < g.h && L.iw0 >= 0 && L.iw0 + reach_w < g.w;
             L.lookup = mask_in || !interior; // else every tap is inside the image and nothing gates it
-            // the two halves of the wave own the same positions: each looks at half of the taps
-            if (L.lookup) request_taps(L, half, L.inside, L.mb);
+        }
+        if (by_rows) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                L.rows[v] = make_uint2(0x01010101u, 0x01010101u);
+                if (mask_in && 2 * v < g.kh) {
+                    // bytes from the row's first tap on; a load that would leave the mask is moved inside
+                    // it and its bytes moved back (what lies outside the image is dropped below)
+                    const int64_t off = (int64_t)(L.b * g.h + L.ih0 + (half + 2 * v) * g.dh) * g.w + L.iw0;
+                    const int64_t at = off < 0 ? 0 : (off > mask_bytes - 8 ? mask_bytes - 8 : off);
+                    uint64_t m;
+                    __builtin_memcpy(&m, mask_in + at, 8);
+                    const int64_t moved = off - at;
+                    m = moved < 0 ? (moved > -8 ? m << (-8 * moved) : 0ull) : (moved < 8 ? m >> (8 * moved) : 0ull);
+                    L.rows[v] = make_uint2((uint32_t)m, (uint32_t)(m >> 32));
+                }
+            }
         }
     };
     auto finish = [&](const Located &L) -> uint64_t {
+        if (!L.lookup) return L.p >= 0 ? all_taps : 0ull;
         uint64_t bits = 0;
-        if (L.p >= 0) {
-            if (!L.lookup) {
-                bits = all_taps;
-            } else {
+        if (by_rows) {
+            // columns of the kernel inside the image
+            const int c0 = max(-L.iw0, 0), c1 = min(g.w - L.iw0, g.kw); // [c0, c1)
+            const uint32_t cols = c1 > c0 ? ((1u << c1) - 1u) & ~((1u << c0) - 1u) : 0u;
+            auto four = [](uint32_t v) { // one bit per nonzero byte
+                v = (((v & 0x7f7f7f7fu) + 0x7f7f7f7fu) | v) & 0x80808080u;
+                return ((v >> 7) & 1u) | ((v >> 14) & 2u) | ((v >> 21) & 4u) | (v >> 28);
+            };
 #pragma unroll
-                for (int u = 0; u < 8; ++u) bits |= (uint64_t)(L.inside[u] && L.mb[u] != 0) << ((half + 2 * u) & 63);
-                for (int t0 = half + 16; t0 < taps; t0 += 16) {
-                    bool inside[8];
-                    uint8_t mb[8];
-                    request_taps(L, t0, inside, mb);
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) bits |= (uint64_t)(inside[u] && mb[u] != 0) << ((t0 + 2 * u) & 63);
-                }
+            for (int v = 0; v < 4; ++v) {
+                const int kh = half + 2 * v, ih = L.ih0 + kh * g.dh;
+                const bool in = kh < g.kh && (uint32_t)ih < (uint32_t)g.h;
+                const uint32_t r = in ? (four(L.rows[v].x) | (four(L.rows[v].y) << 4)) & cols : 0u;
+                bits |= (uint64_t)r << ((kh * g.kw) & 63);
+            }
+        } else {
+            for (int t = half; t < taps; t += 2) {
+                const uint32_t e = tap_s[t];
+                const int ih = L.ih0 + (int)(e & 0xffffu), iw = L.iw0 + (int)(e >> 16);
+                bool in = ih >= 0 && ih < g.h && iw >= 0 && iw < g.w;
+                if (in && mask_in) in = mask_in[(int64_t)(L.b * g.h + ih) * g.w + iw] != 0;
+                bits |= (uint64_t)in << t;
             }
         }
         // merge the halves' bits
@@ -172,6 +231,7 @@ __global__ __launch_bounds__(kStemThreads, 5) void k_conv_stem(Geom g, StemDivs 
         return (uint64_t)lo2 | ((uint64_t)hi2 << 32);
     };
 
+    const int x_elems = g.n * g.h * g.w * g.c_in;
     Located nxt;
     uint64_t bits_n = 0;
     if ((int)blockIdx.x < ntiles) {
@@ -198,28 +258,58 @@ __global__ __launch_bounds__(kStemThreads, 5) void k_conv_stem(Geom g, StemDivs 
                 acc[cb][q * 4 + 3] = bq.w;
             }
 
-        for (int j = 0; j < ksteps; ++j) {
-            // this lane's 8 reduction elements of step j
-            const uint4 e0 = *reinterpret_cast<const uint4 *>(&lut[j * 16 + half * 8]);
-            const uint4 e1 = *reinterpret_cast<const uint4 *>(&lut[j * 16 + half * 8 + 4]);
-            const uint32_t ent[8] = {e0.x, e0.y, e0.z, e0.w, e1.x, e1.y, e1.z, e1.w};
-            uint32_t val[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const uint32_t tap = ent[e] >> 24;
-                const bool ok = tap < (uint32_t)kStemMaxTaps && ((bits >> tap) & 1ull);
-                val[e] = ok ? (uint32_t)x[base + (int)(ent[e] & 0xffffffu)] : 0u;
-            }
-            uint4 xf;
-            xf.x = val[0] | (val[1] << 16);
-            xf.y = val[2] | (val[3] << 16);
-            xf.z = val[4] | (val[5] << 16);
-            xf.w = val[6] | (val[7] << 16);
+        auto selected = [&](uint32_t ent) { return ((ent >> 24) < (uint32_t)kStemMaxTaps) && ((bits >> ((ent >> 24) & 63u)) & 1ull); };
+        // all ones in the halves whose element is in use (padding: tap 63, which no such layer has)
+        auto pair_mask = [&](uint32_t lo, uint32_t hi) -> uint32_t {
+            const uint32_t t = ((uint32_t)(bits >> ((lo >> 24) & 63u)) & 1u) | (((uint32_t)(bits >> ((hi >> 24) & 63u)) & 1u) << 16);
+            return (t << 16) - t;
+        };
+        auto multiply = [&](int j, const uint4 &xf) {
 #pragma unroll
             for (int cb = 0; cb < 2; ++cb) {
                 const uint4 wf = *reinterpret_cast<const uint4 *>(w_s + (cb * 32 + (lane & 31)) * WPITCH +
                                                                    (j * 16 + half * 8) * 2);
                 acc[cb] = mfma32<DT>(wf, xf, acc[cb]);
+            }
+        };
+        if (dv.pitch && __all(base >= 0 && base <= x_elems - dv.reach)) {
+            constexpr int U = 4; // pieces in flight
+            for (int j0 = 0; j0 < ksteps; j0 += U) {
+                uint4 v[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int j = min(j0 + u, ksteps - 1);
+                    const uint32_t e = lut[j * 16 + half * 8];
+                    __builtin_memcpy(&v[u], x + base + (int)(e & 0xffffffu), 16);
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if (j0 + u >= ksteps) break;
+                    const uint32_t *le = &lut[(j0 + u) * 16 + half * 8];
+                    const uint4 e0 = *reinterpret_cast<const uint4 *>(le), e1 = *reinterpret_cast<const uint4 *>(le + 4);
+                    uint4 xf;
+                    xf.x = v[u].x & pair_mask(e0.x, e0.y);
+                    xf.y = v[u].y & pair_mask(e0.z, e0.w);
+                    xf.z = v[u].z & pair_mask(e1.x, e1.y);
+                    xf.w = v[u].w & pair_mask(e1.z, e1.w);
+                    multiply(j0 + u, xf);
+                }
+            }
+        } else {
+            for (int j = 0; j < ksteps; ++j) {
+                // this lane's 8 reduction elements of step j
+                const uint4 e0 = *reinterpret_cast<const uint4 *>(&lut[j * 16 + half * 8]);
+                const uint4 e1 = *reinterpret_cast<const uint4 *>(&lut[j * 16 + half * 8 + 4]);
+                const uint32_t ent[8] = {e0.x, e0.y, e0.z, e0.w, e1.x, e1.y, e1.z, e1.w};
+                uint32_t val[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) val[e] = selected(ent[e]) ? (uint32_t)x[base + (int)(ent[e] & 0xffffffu)] : 0u;
+                uint4 xf;
+                xf.x = val[0] | (val[1] << 16);
+                xf.y = val[2] | (val[3] << 16);
+                xf.z = val[4] | (val[5] << 16);
+                xf.w = val[6] | (val[7] << 16);
+                multiply(j, xf);
             }
         }
 
@@ -270,10 +360,20 @@ __global__ __launch_bounds__(kStemThreads, 5) void k_conv_stem(Geom g, StemDivs 
         if (more) bits_n = finish(nxt); // piece 3
         __syncthreads(); // everyone is done with row_p and o_s before the next tile rewrites them
     }
+
+    if (mask_in && !(g.flags & FC_SKIP_ZERO_FILL)) {
+        const int idle = (int)gridDim.x - ntiles;
+        const bool idle_only = idle >= (int)gridDim.x / 16 && idle > 0;
+        const int me = idle_only ? (int)blockIdx.x - ntiles : (int)blockIdx.x, of = idle_only ? idle : (int)gridDim.x;
+        if (me >= 0)
+            clear_irrelevant(g, mask_in, mask_out, out, g.c_out * (int)sizeof(TO) / 16,
+                             (me * (int)gridDim.y + (int)blockIdx.y) * (kStemThreads / 64) + wave,
+                             of * (int)gridDim.y * (kStemThreads / 64), reinterpret_cast<int32_t *>(stem_lds) + wave * 64);
+    }
 }
 
 template <int DT, typename TO>
-static hipError_t launch_stem_t(const Geom &g, const void *x, const uint8_t *mask_in, const void *w,
+static hipError_t launch_stem_t(const Geom &g, const void *x, const uint8_t *mask_in, const uint8_t *mask_out, const void *w,
                                 const float *bias, const int32_t *idx, const int32_t *count, void *out,
                                 hipStream_t s)
 {
@@ -282,29 +382,39 @@ static hipError_t launch_stem_t(const Geom &g, const void *x, const uint8_t *mas
     const int64_t tiles = ((int64_t)g.m + kStemRows - 1) / kStemRows;
     const int gx = (int)(tiles > 2048 ? 2048 : tiles);
     const int gy = (g.c_out + kStemCo - 1) / kStemCo;
-    const int ksteps = (g.kh * g.kw * g.c_in + 15) / 16;
-    const size_t lds = (size_t)kStemRows * (kStemCo * sizeof(TO) + 16) + (size_t)kStemCo * stem_weight_pitch(ksteps) +
-                       (size_t)ksteps * 16 * sizeof(uint32_t) + (size_t)kStemRows * sizeof(int32_t) + (size_t)kStemCo * sizeof(float) + (size_t)kStemMaxTaps * sizeof(uint32_t);
     StemDivs dv;
     dv.wo = make_fastdiv((uint32_t)g.wo);
     dv.ho = make_fastdiv((uint32_t)g.ho);
+    dv.row = make_fastdiv((uint32_t)(g.kw * g.c_in));
+    dv.pitch = (g.kw * g.c_in + 7) / 8 * 8;
+    // short kernel rows are mostly padding (3x3x3: three steps for two): those keep the plain order
+    if (g.dw != 1 || g.kh * dv.pitch > kStemMaxPadded || g.kh * g.kw > 63 ||
+        4 * g.kh * dv.pitch > 5 * g.kh * g.kw * g.c_in)
+        dv.pitch = 0;
+    const int ksteps = dv.ksteps = ((dv.pitch ? g.kh * dv.pitch : g.kh * g.kw * g.c_in) + 15) / 16;
+    dv.row_pieces = dv.pitch ? dv.pitch / 8 : ksteps * 2;
+    dv.per_row = make_fastdiv((uint32_t)dv.row_pieces);
+    dv.per_co = make_fastdiv((uint32_t)(ksteps * 2));
+    dv.reach = (g.kh - 1) * g.dh * g.w * g.c_in + dv.pitch;
+    const size_t lds = (size_t)kStemRows * (kStemCo * sizeof(TO) + 16) + (size_t)kStemCo * stem_weight_pitch(ksteps) +
+                       (size_t)ksteps * 16 * sizeof(uint32_t) + (size_t)kStemRows * sizeof(int32_t) + (size_t)kStemCo * sizeof(float) + (size_t)kStemMaxTaps * sizeof(uint32_t);
     hipLaunchKernelGGL((k_conv_stem<DT, TO>), dim3(gx, gy), dim3(kStemThreads), lds, s, g, dv, (const uint16_t *)x,
-                       mask_in, (const uint16_t *)w, bias, idx, count, (TO *)out);
+                       mask_in, mask_out, (const uint16_t *)w, bias, idx, count, (TO *)out);
     return hipGetLastError();
 }
 
 hipError_t launch_conv_stem(const Geom &g, int in_dtype, int out_dtype, const void *x, const uint8_t *mask_in,
-                            const void *w, const float *bias, const int32_t *idx, const int32_t *count,
-                            void *out, hipStream_t s)
+                            const uint8_t *mask_out, const void *w, const float *bias, const int32_t *idx,
+                            const int32_t *count, void *out, hipStream_t s)
 {
     if (in_dtype == FC_BF16) {
-        if (out_dtype == FC_F32) return launch_stem_t<FC_BF16, float>(g, x, mask_in, w, bias, idx, count, out, s);
-        if (out_dtype == FC_FP8) return launch_stem_t<FC_BF16, uint8_t>(g, x, mask_in, w, bias, idx, count, out, s);
-        return launch_stem_t<FC_BF16, uint16_t>(g, x, mask_in, w, bias, idx, count, out, s);
+        if (out_dtype == FC_F32) return launch_stem_t<FC_BF16, float>(g, x, mask_in, mask_out, w, bias, idx, count, out, s);
+        if (out_dtype == FC_FP8) return launch_stem_t<FC_BF16, uint8_t>(g, x, mask_in, mask_out, w, bias, idx, count, out, s);
+        return launch_stem_t<FC_BF16, uint16_t>(g, x, mask_in, mask_out, w, bias, idx, count, out, s);
     }
-    if (out_dtype == FC_F32) return launch_stem_t<FC_F16, float>(g, x, mask_in, w, bias, idx, count, out, s);
-    if (out_dtype == FC_FP8) return launch_stem_t<FC_F16, uint8_t>(g, x, mask_in, w, bias, idx, count, out, s);
-    return launch_stem_t<FC_F16, uint16_t>(g, x, mask_in, w, bias, idx, count, out, s);
+    if (out_dtype == FC_F32) return launch_stem_t<FC_F16, float>(g, x, mask_in, mask_out, w, bias, idx, count, out, s);
+    if (out_dtype == FC_FP8) return launch_stem_t<FC_F16, uint8_t>(g, x, mask_in, mask_out, w, bias, idx, count, out, s);
+    return launch_stem_t<FC_F16, uint16_t>(g, x, mask_in, mask_out, w, bias, idx, count, out, s);
 }
 
 } // namespace fc

@@ -179,6 +179,37 @@ __device__ __forceinline__ bool position_kept(const Geom &g, const uint8_t *__re
     return mask_at(mask_in, (int64_t)(b * g.h + ih) * g.w + iw, packed);
 }
 
+// Zero-fill of the irrelevant output rows (whole 16-byte pieces, `pieces` per row): wave `worker` of
+// `workers` looks at 64 positions at a time (one label each), lists the irrelevant ones in LDS in order
+// (`dropped`: 64 ints of its own), and then all its lanes store 16-byte pieces of those rows, so the stores
+// are dense and none of them waits for a label.  The labels of the next 64 positions are requested before
+// the stores of the current ones.
+__device__ __forceinline__ void clear_irrelevant(const Geom &g, const uint8_t *__restrict__ mask_in,
+                                                 const uint8_t *__restrict__ mask_out, void *__restrict__ out, int pieces,
+                                                 int worker, int workers, int32_t *dropped)
+{
+    const int lane = threadIdx.x & 63;
+    const int64_t step = (int64_t)workers * 64;
+    typedef uint32_t u32x4_nt __attribute__((ext_vector_type(4)));
+    const u32x4_nt zero4 = {0u, 0u, 0u, 0u};
+    u32x4_nt *o4 = reinterpret_cast<u32x4_nt *>(out);
+    int64_t p0 = (int64_t)worker * 64;
+    bool kept = p0 + lane >= g.m || position_kept(g, mask_in, mask_out, p0 + lane);
+    for (; p0 < g.m; p0 += step) {
+        const uint64_t drop = __ballot(!kept);
+        const int nd = __popcll(drop);
+        if (!kept) dropped[__popcll(drop & ((1ull << lane) - 1ull))] = (int32_t)(p0 + lane); // in position order
+        // (same wave wrote and reads the list: program order suffices)
+        const int64_t pn = p0 + step + lane;
+        kept = pn >= g.m || position_kept(g, mask_in, mask_out, pn);
+        const int total = nd * pieces;
+        for (int c = lane; c < total; c += 64) {
+            const int rk = c / pieces, pc = c - rk * pieces;
+            __builtin_nontemporal_store(zero4, o4 + (int64_t)dropped[rk] * pieces + pc);
+        }
+    }
+}
+
 // inclusive prefix sum over the 64 lanes of a wave, on the cross-lane data path of the
 // vector ALU (no LDS traffic): shifts by 1, 2, 4, 8 inside each row of 16 lanes, then the last
 // lane of row 0 / row 2 is broadcast into row 1 / row 3, then lane 31 into rows 2 and 3.
@@ -288,12 +319,11 @@ bool conv_depthwise_supported(const Geom &g, int in_dtype);
 hipError_t launch_conv_depthwise(const Geom &g, int in_dtype, int out_dtype, const void *x, const uint8_t *mask_in,
                                  const void *w, const float *bias, void *out, hipStream_t s);
 
-// Matrix-core path for layers with at most 4 input channels (RGB stems); the caller clears the
-// irrelevant rows with launch_zero_fill.
+// Matrix-core path for layers with at most 4 input channels (RGB stems); clears the irrelevant rows too.
 bool conv_stem_supported(const Geom &g, int in_dtype, int out_dtype);
 hipError_t launch_conv_stem(const Geom &g, int in_dtype, int out_dtype, const void *x, const uint8_t *mask_in,
-                            const void *w, const float *bias, const int32_t *idx, const int32_t *count,
-                            void *out, hipStream_t s);
+                            const uint8_t *mask_out, const void *w, const float *bias, const int32_t *idx,
+                            const int32_t *count, void *out, hipStream_t s);
 
 // Split-K scratch of the matrix-core path (optional): fp32 partial tiles and one counter
 // per tile.  Only layers with few tiles use it; for the others the sizes are zero.

@@ -208,8 +208,10 @@ __device__ __forceinline__ int list_of_block(const ListArgs<NL> &a, int block)
 }
 
 // the workgroup's part of the list: kept positions p0 .. p0 + 3 of every lane after `base` earlier ones;
-// returns the number kept by the whole workgroup
-__device__ __forceinline__ int store_list(const LabelMap &L, int p0, uint32_t f, int base, int *wave_sum)
+// returns the number kept by the whole workgroup.  `staged`: the list is put together in LDS and leaves in
+// whole lines (long lists: 8.3 million entries 38 us straight from the lanes)
+__device__ __forceinline__ int store_list(const LabelMap &L, int p0, uint32_t f, int base, int *wave_sum,
+                                          int32_t *staged = nullptr)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int c = __popc(f), incl = wave_inclusive_scan(c);
@@ -222,10 +224,14 @@ __device__ __forceinline__ int store_list(const LabelMap &L, int p0, uint32_t f,
         before += i < wave ? t : 0;
         total += t;
     }
-    int32_t *to = L.idx + (base + before + incl - c);
+    int32_t *to = (staged ? staged : L.idx + base) + (before + incl - c);
 #pragma unroll
     for (int j = 0; j < 4; ++j)
         if ((f >> j) & 1u) *to++ = p0 + j;
+    if (staged) {
+        __syncthreads();
+        for (int i = threadIdx.x; i < total; i += kListThreads) L.idx[(int64_t)base + i] = staged[i];
+    }
     return total;
 }
 
@@ -295,6 +301,7 @@ __global__ __launch_bounds__(kListThreads) void k_lists_scatter(ListArgs<NL> a, 
                                                                 const int32_t *__restrict__ block_counts)
 {
     __shared__ int wave_sum[kListWaves], scratch[kListWaves];
+    __shared__ int32_t staged[kCompactBlockElems];
     const int tid = threadIdx.x;
     const LabelMap &L = a.at[NL == 1 ? 0 : list_of_block(a, blockIdx.x)];
     const int p0 = (blockIdx.x - L.block0) * kCompactBlockElems + tid * 4;
@@ -314,7 +321,7 @@ __global__ __launch_bounds__(kListThreads) void k_lists_scatter(ListArgs<NL> a, 
     int part = 0;
     for (int i = L.block0 + tid; i < (int)blockIdx.x; i += kListThreads) part += block_counts[i];
     const int base = block_sum<kListWaves>(part, scratch);
-    const int total = store_list(L, p0, f, base, wave_sum);
+    const int total = store_list(L, p0, f, base, wave_sum, staged);
     if (tid == 0 && (int64_t)((int)blockIdx.x - L.block0 + 1) * kCompactBlockElems >= L.m) *L.count = base + total;
     if (NL == 1 && a.ex.zero && blockIdx.x == 0)
         for (int i = tid; i < a.ex.zero_n; i += kListThreads) a.ex.zero[i] = 0;
@@ -544,37 +551,15 @@ hipError_t launch_mask_pack(const uint8_t *mask, int64_t m, uint64_t *bits, hipS
 // ---------------------------------------------------------------------------
 // Zero-fill of the irrelevant output rows: a lane owns 16 bytes of one row.
 // ---------------------------------------------------------------------------
-// Rows of whole 16-byte pieces: a wave looks at 64 positions at a time (one label each), lists
-// the irrelevant ones in LDS in order, and then all its lanes store 16-byte pieces of those
-// rows, so the stores are dense and none of them waits for a label.  The labels of the next 64
-// positions are requested before the stores of the current ones.
+// rows of whole 16-byte pieces
 __global__ __launch_bounds__(256) void k_zero_fill16(Geom g, const uint8_t *__restrict__ mask_in,
                                                      const uint8_t *__restrict__ mask_out,
                                                      uint4 *__restrict__ out, int chunks_per_row)
 {
     __shared__ int32_t dropped_s[4][64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int32_t *dropped = dropped_s[wave];
-    const int64_t nwaves = (int64_t)gridDim.x * 4;
-    const int64_t step = nwaves * 64;
-    typedef uint32_t u32x4_nt __attribute__((ext_vector_type(4)));
-    const u32x4_nt zero4 = {0u, 0u, 0u, 0u};
-    u32x4_nt *o4 = reinterpret_cast<u32x4_nt *>(out);
-    int64_t p0 = ((int64_t)blockIdx.x * 4 + wave) * 64;
-    bool kept = p0 + lane >= g.m || position_kept(g, mask_in, mask_out, p0 + lane);
-    for (; p0 < g.m; p0 += step) {
-        const uint64_t drop = __ballot(!kept);
-        const int nd = __popcll(drop);
-        if (!kept) dropped[__popcll(drop & ((1ull << lane) - 1ull))] = (int32_t)(p0 + lane); // in position order
-        // (same wave wrote and reads the list: program order suffices)
-        const int64_t pn = p0 + step + lane;
-        kept = pn >= g.m || position_kept(g, mask_in, mask_out, pn);
-        const int total = nd * chunks_per_row;
-        for (int c = lane; c < total; c += 64) {
-            const int rk = c / chunks_per_row, pc = c - rk * chunks_per_row;
-            __builtin_nontemporal_store(zero4, o4 + (int64_t)dropped[rk] * chunks_per_row + pc);
-        }
-    }
+    const int wave = threadIdx.x >> 6;
+    clear_irrelevant(g, mask_in, mask_out, out, chunks_per_row, (int)blockIdx.x * 4 + wave, (int)gridDim.x * 4,
+                     dropped_s[wave]);
 }
 
 __global__ __launch_bounds__(256) void k_zero_fill_bytes(Geom g, const uint8_t *__restrict__ mask_in,
@@ -669,8 +654,10 @@ __global__ __launch_bounds__(256) void k_maxpool(const T *__restrict__ x, int n,
 
 // 16-bit types, channel count a multiple of 8: one lane owns 8 consecutive channels of an
 // output position (16-byte loads and one 16-byte store).  IDX: the type the flat index is split
-// in (32 bits whenever the tensor allows: the three divisions are most of the arithmetic).
-template <typename T, typename IDX>
+// in (32 bits whenever the tensor allows: the three divisions are most of the arithmetic).  K: window
+// size known here (2, 3; all loads of a window in flight together: a small pool is a chain of round trips
+// otherwise, 64 channels of one 112 x 112 map 7.2 us), or 0 = k.
+template <typename T, typename IDX, int K>
 __global__ __launch_bounds__(256) void k_maxpool_x8(const T *__restrict__ x, int n, int h, int w, int c, int k,
                                                     int stride, int pad, int ho, int wo,
                                                     const uint8_t *__restrict__ keep, T *__restrict__ out)
@@ -698,25 +685,46 @@ __global__ __launch_bounds__(256) void k_maxpool_x8(const T *__restrict__ x, int
             best[e] = 0.f;
             raw[e] = 0;
         }
-        for (int a = 0; a < k; ++a) {
-            const int ih = oh * stride - pad + a;
-            if (ih < 0 || ih >= h) continue;
-            for (int q = 0; q < k; ++q) {
-                const int iw = ow * stride - pad + q;
-                if (iw < 0 || iw >= w) continue;
-                const uint4 v = *reinterpret_cast<const uint4 *>(x + (((int64_t)b * h + ih) * w + iw) * c + g8 * 8);
-                const uint32_t wd[4] = {v.x, v.y, v.z, v.w};
+        auto take = [&](const uint4 &v) __attribute__((always_inline)) {
+            const uint32_t wd[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    T one;
-                    one.bits = (uint16_t)(wd[e >> 1] >> (16 * (e & 1)));
-                    const float f = to_float(one);
-                    if (!have || f > best[e]) {
-                        best[e] = f;
-                        raw[e] = one.bits;
-                    }
+            for (int e = 0; e < 8; ++e) {
+                T one;
+                one.bits = (uint16_t)(wd[e >> 1] >> (16 * (e & 1)));
+                const float f = to_float(one);
+                if (!have || f > best[e]) {
+                    best[e] = f;
+                    raw[e] = one.bits;
                 }
-                have = true;
+            }
+            have = true;
+        };
+        const T *xb = x + (int64_t)b * h * w * c + g8 * 8;
+        if constexpr (K > 0) {
+            uint4 v[K * K];
+            bool in[K * K];
+#pragma unroll
+            for (int a = 0; a < K; ++a)
+#pragma unroll
+                for (int q = 0; q < K; ++q) {
+                    const int ih = oh * stride - pad + a, iw = ow * stride - pad + q;
+                    in[a * K + q] = ih >= 0 && ih < h && iw >= 0 && iw < w;
+                    // (a tap outside reads the nearest pixel inside and is dropped)
+                    v[a * K + q] = *reinterpret_cast<const uint4 *>(
+                        xb + (int64_t)(min(max(ih, 0), h - 1) * w + min(max(iw, 0), w - 1)) * c);
+                }
+#pragma unroll
+            for (int t = 0; t < K * K; ++t)
+                if (in[t]) take(v[t]);
+        } else {
+            for (int a = 0; a < k; ++a) {
+                const int ih = oh * stride - pad + a;
+                if (ih < 0 || ih >= h) continue;
+                for (int q = 0; q < k; ++q) {
+                    const int iw = ow * stride - pad + q;
+                    if (iw < 0 || iw >= w) continue;
+                    take(*reinterpret_cast<const uint4 *>(xb + (int64_t)(ih * w + iw) * c));
+                }
             }
         }
         uint4 o;
@@ -766,21 +774,21 @@ hipError_t launch_maxpool(const void *x, int n, int h, int w, int c, int dtype, 
         const int64_t total8 = (int64_t)n * ho * wo * (c / 8);
         const int blocks8 = (int)((total8 + 255) / 256 > 65536 ? 65536 : (total8 + 255) / 256);
         const bool small = total8 < (int64_t)INT32_MAX;
+#define FC_POOL(T, IDX, K)                                                                                         \
+    hipLaunchKernelGGL((k_maxpool_x8<T, IDX, K>), dim3(blocks8), dim3(256), 0, s, (const T *)x, n, h, w, c, k, stride, \
+                       pad, ho, wo, keep, (T *)out)
+#define FC_POOL_T(T)                                       \
+    if (!small) FC_POOL(T, int64_t, 0);                    \
+    else if (k == 2) FC_POOL(T, uint32_t, 2);              \
+    else if (k == 3) FC_POOL(T, uint32_t, 3);              \
+    else FC_POOL(T, uint32_t, 0)
         if (dtype == FC_BF16) {
-            if (small)
-                hipLaunchKernelGGL((k_maxpool_x8<bf16_t, uint32_t>), dim3(blocks8), dim3(256), 0, s, (const bf16_t *)x, n,
-                                   h, w, c, k, stride, pad, ho, wo, keep, (bf16_t *)out);
-            else
-                hipLaunchKernelGGL((k_maxpool_x8<bf16_t, int64_t>), dim3(blocks8), dim3(256), 0, s, (const bf16_t *)x, n,
-                                   h, w, c, k, stride, pad, ho, wo, keep, (bf16_t *)out);
+            FC_POOL_T(bf16_t);
         } else {
-            if (small)
-                hipLaunchKernelGGL((k_maxpool_x8<f16_t, uint32_t>), dim3(blocks8), dim3(256), 0, s, (const f16_t *)x, n, h,
-                                   w, c, k, stride, pad, ho, wo, keep, (f16_t *)out);
-            else
-                hipLaunchKernelGGL((k_maxpool_x8<f16_t, int64_t>), dim3(blocks8), dim3(256), 0, s, (const f16_t *)x, n, h,
-                                   w, c, k, stride, pad, ho, wo, keep, (f16_t *)out);
+            FC_POOL_T(f16_t);
         }
+#undef FC_POOL_T
+#undef FC_POOL
         return hipGetLastError();
     }
     const int64_t total = (int64_t)n * ho * wo * c;

@@ -664,3 +664,43 @@ def test_fp32_storage_on_the_matrix_cores(layer, mask_kind, precomputed):
                             flags_extra=B.SKIP_ZERO_FILL)
     got = left.cpu().numpy()
     assert (got[~keep] == 7.0).all() and np.array_equal(got[keep], out.cpu().numpy()[keep])
+
+
+@pytest.mark.parametrize("layer", [
+    # n, h, w, ci, co, k, s, p, d: kernel rows of one to three pieces, one tap, one channel, a dilated kernel (element by
+    # element), nine columns (taps looked up one by one), a mask shorter than one 8-byte look-up, 64 taps, two
+    # channel blocks, positions around the 128-row tile, padding wider than the kernel
+    (2, 33, 29, 3, 64, 7, 2, 3, 1), (1, 17, 9, 1, 8, 1, 1, 0, 1), (3, 16, 8, 4, 72, 3, 1, 1, 1), (1, 19, 23, 2, 136, 5, 1, 2, 1),
+    (2, 21, 18, 3, 16, 3, 1, 2, 2), (1, 24, 40, 1, 24, (3, 9), 1, (1, 4), 1), (1, 2, 3, 3, 16, 3, 1, 1, 1),
+    (1, 20, 20, 2, 16, 8, 1, 3, 1), (4, 65, 63, 3, 32, 3, 2, 1, 1), (1, 12, 12, 3, 8, 3, 1, 5, 1)])
+@pytest.mark.parametrize("mask_kind,precomputed", [("objects", False), ("bernoulli", True), (None, False)])
+def test_stem_kernel_rows(layer, mask_kind, precomputed):
+    n, h, w, ci, co, k, s, p, d = layer
+    kh, kw = k if isinstance(k, tuple) else (k, k)
+    ph, pw = p if isinstance(p, tuple) else (p, p)
+    torch = G.torch_mod()
+    for dtype in (synth.BF16, synth.F16):
+        x = synth.activations((n, h, w, ci), dtype, 233, 1)
+        wt = synth.he_weights(co, kh, kw, ci, dtype, 233, 2)
+        bias = synth.bias(co, 233, 3)
+        mask = None if mask_kind is None else (synth.mask_bernoulli if mask_kind == "bernoulli" else synth.mask_objects)(
+            n, h, w, 0.4, 233, 4)
+        if mask is not None:        # nothing at an irrelevant pixel may reach an output
+            x.reshape(n * h * w, ci)[mask.reshape(-1) == 0] = synth.to_storage(np.array([np.nan], np.float32), dtype)[0]
+        desc = B.conv_desc(n, h, w, ci, co, (kh, kw), (s, s), (ph, pw), (d, d), dtype, B.F32, B.RELU)
+        ho, wo = B.out_dims(desc)
+        out = torch.full((n, ho, wo, co), 7.0, dtype=torch.float32, device=G.dev())
+        md = None if mask is None else G.mask_dev(mask)
+        kwargs = {}
+        if precomputed:
+            m_out = B.mask_downsample(md, (kh, kw), (s, s), (ph, pw), (d, d))
+            idx, count = B.active_index_compact(m_out)
+            kwargs = dict(mask_out=m_out, idx=idx, count=count)
+        B.focused_conv2d(desc, G.to_dev(x, dtype), G.to_dev(wt, dtype), torch.from_numpy(bias).to(G.dev()), mask_in=md, out=out,
+                         **kwargs)
+        want = O.focused_conv2d(O.ConvShape(n, h, w, ci, co, kh, kw, (s, s), (ph, pw), (d, d), relu=True), x, wt, bias=bias,
+                                mask_in=mask, dtype=dtype)
+        keep = (O.mask_downsample(mask, kh, kw, (s, s), (ph, pw), (d, d)) != 0) if mask is not None \
+            else np.ones(want.shape[:3], bool)
+        assert G.rel_err(G.to_f64(out), want, keep) <= TOL_F32_OUT
+        assert not out.cpu().numpy()[~keep].view(np.uint32).any()
