@@ -59,6 +59,8 @@ int32_t make_geom(const fc_conv_desc *d, Geom *g)
     g->kh = d->kh; g->kw = d->kw; g->sh = d->stride_h; g->sw = d->stride_w;
     g->ph = d->pad_h; g->pw = d->pad_w; g->dh = d->dil_h; g->dw = d->dil_w;
     g->ho = ho; g->wo = wo; g->m = (int32_t)m; g->flags = d->flags;
+    g->div_wo = make_fastdiv((uint32_t)wo);
+    g->div_ho = make_fastdiv((uint32_t)ho);
     return FC_OK;
 }
 
@@ -325,8 +327,10 @@ int32_t fc_focused_conv2d(const fc_conv_desc *desc, const void *x, const uint8_t
         tile_counters = (int32_t *)((uint8_t *)workspace + l.counters);
         partials = (float *)((uint8_t *)workspace + l.partials);
     }
-    // (a layer whose reduction is too short to split leaves the counters alone)
-    bool counters_cleared = !split_k_reachable(g, desc->in_dtype);
+    const bool small = mfma && conv_small_wanted(g, desc->in_dtype);
+    const int small_splits = small ? conv_small_splits(g, tile_counters != nullptr) : 1;
+    // (a layer whose reduction is not split leaves the counters alone)
+    bool counters_cleared = small ? small_splits == 1 : !split_k_reachable(g, desc->in_dtype);
     const bool f32 = desc->in_dtype == FC_F32 && conv_f32_supported(g);
 
     if (mask_in && !idx) {
@@ -340,8 +344,8 @@ int32_t fc_focused_conv2d(const fc_conv_desc *desc, const void *x, const uint8_t
         // kernel (16 positions per thread, labels from the centre tap): no compaction launch.
         // Labels the caller brings (mask_out without a list) are compacted as they are, so that
         // the rows computed and the rows cleared follow the same labels.
-        // fp32 layers label and compact their rows inside the convolution kernel whatever their size.
-        const bool rank_in_kernel = f32 || (mfma && g.m <= kInlineRankPositions && !mask_out);
+        // The fp32 kernel and the one for small layers label their rows themselves, whatever the labels' source.
+        const bool rank_in_kernel = f32 || small || (mfma && g.m <= kInlineRankPositions && !mask_out);
         if (!rank_in_kernel) {
             CompactExtras ex;
             if (tile_counters && !counters_cleared) {
@@ -373,7 +377,15 @@ int32_t fc_focused_conv2d(const fc_conv_desc *desc, const void *x, const uint8_t
 
     hipError_t e;
     const bool pw = mfma && (idx || !mask_in) && conv_pw_wanted(g, desc->in_dtype, desc->out_dtype, mask_in != nullptr);
-    if (mfma && idx && !(pw && (g.flags & FC_RESIDENT_WEIGHTS)) &&
+    if (small) {
+        if (small_splits > 1 && !counters_cleared && !(g.flags & FC_WORKSPACE_READY)) {
+            e = launch_zero_i32(tile_counters, kSplitGrid, s);
+            if (e != hipSuccess) return FC_ERR_HIP;
+        }
+        e = launch_conv_small(g, desc->in_dtype, desc->out_dtype, small_splits, x, mask_in, mask_out, w, bias, idx, count, out,
+                              partials, tile_counters, s);
+        if (e != hipSuccess) return FC_ERR_HIP;
+    } else if (mfma && idx && !(pw && (g.flags & FC_RESIDENT_WEIGHTS)) &&
         conv_line_wanted(g, desc->in_dtype, desc->out_dtype, mask_in != nullptr)) {
         e = launch_conv_line(g, desc->in_dtype, desc->out_dtype, x, mask_in, mask_out, w, bias, idx, count, out, s);
         if (e != hipSuccess) return FC_ERR_HIP;

@@ -254,10 +254,8 @@ __global__ __launch_bounds__(WM *WN * 64, MINW) void k_conv_dma(Geom g, const ui
                     if (mask_out) {
                         kept = mask_at(mask_out, pp, packed_masks);
                     } else {
-                        const int ow = pp % g.wo;
-                        const int q = pp / g.wo;
-                        const int oh = q % g.ho;
-                        const int b = q / g.ho;
+                        const int q = (int)fast_div((uint32_t)pp, g.div_wo), ow = pp - q * g.wo;
+                        const int b = (int)fast_div((uint32_t)q, g.div_ho), oh = q - b * g.ho;
                         const int ih = min(max(oh * g.sh + ch0, 0), g.h - 1);
                         const int iw = min(max(ow * g.sw + cw0, 0), g.w - 1);
                         kept = mask_at(mask_in, (int64_t)(b * g.h + ih) * g.w + iw, packed_masks);
@@ -279,7 +277,13 @@ __global__ __launch_bounds__(WM *WN * 64, MINW) void k_conv_dma(Geom g, const ui
         const int unit = xcd * per_xcd + slot_t;
         if (unit >= nunits) break;
         const int tile = unit / S, split = unit - tile * S;
-        const int s_begin = (int)((int64_t)split * stages / S), s_end = (int)((int64_t)(split + 1) * stages / S);
+        // (32-bit divisions only, and positions through multiplies: the 64-bit ones were a third of the
+        // 4 300 cycles a workgroup took to its rows' addresses)
+        int s_begin = 0, s_end = stages;
+        if (S > 1) {
+            s_begin = (int)((uint32_t)(split * stages) / (uint32_t)S);
+            s_end = (int)((uint32_t)((split + 1) * stages) / (uint32_t)S);
+        }
         const int nst = s_end - s_begin; // stages of this unit
         const int nt = tile / n_mt, mt = tile - nt * n_mt;
         const int co0 = nt * TN;
@@ -308,10 +312,9 @@ __global__ __launch_bounds__(WM *WN * 64, MINW) void k_conv_dma(Geom g, const ui
             int p = -1, base = 0, b = 0, hw = 0;
             if (m < rows) {
                 p = inline_rank ? row_p[tid] : (idx ? idx[m] : m);
-                const int ow = p % g.wo;
-                const int q = p / g.wo;
-                const int oh = q % g.ho;
-                b = q / g.ho;
+                const int q = (int)fast_div((uint32_t)p, g.div_wo), ow = p - q * g.wo;
+                b = (int)fast_div((uint32_t)q, g.div_ho);
+                const int oh = q - b * g.ho;
                 const int ih0 = oh * g.sh - g.ph, iw0 = ow * g.sw - g.pw;
                 sa_p = p; sa_ow = ow; sa_ih0 = ih0; sa_iw0 = iw0; sa_b = b;
                 base = (b * g.h + ih0) * g.w + iw0;
@@ -515,7 +518,11 @@ __global__ __launch_bounds__(WM *WN * 64, MINW) void k_conv_dma(Geom g, const ui
                 }
             }
             const int groups = g.kh * cchunks;
-            const int g_begin = (int)((int64_t)split * groups / S), g_end = (int)((int64_t)(split + 1) * groups / S);
+            int g_begin = 0, g_end = groups;
+            if (S > 1) {
+                g_begin = (int)((uint32_t)(split * groups) / (uint32_t)S);
+                g_end = (int)((uint32_t)((split + 1) * groups) / (uint32_t)S);
+            }
             const int ng = g_end - g_begin;
             // cursors: next pixel line to gather, next weight slab to fetch
             int xkh = g_begin / cchunks, xcc = g_begin - xkh * cchunks, xleft = ng;
@@ -810,21 +817,35 @@ __global__ __launch_bounds__(WM *WN * 64, MINW) void k_conv_dma(Geom g, const ui
                 for (int b = 0; b < CB; ++b)
 #pragma unroll
                     for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
-            for (int sp = 0; sp < S; ++sp) {
-                const uint32_t theirs = (uint32_t)(tile * S + sp) * (uint32_t)(TM * TN * 4);
+            // (several partial tiles in flight: one round trip each was most of a split tile's time)
+            constexpr int U = PB * CB <= 1 ? 4 : (PB * CB <= 2 ? 2 : 1);
+            for (int sp = 0; sp < S; sp += U) {
+                u32x4_t v[U][PB][CB][4];
 #pragma unroll
-                for (int a = 0; a < PB; ++a)
+                for (int u = 0; u < U; ++u) {
+                    const uint32_t theirs = sp + u < S ? (uint32_t)(tile * S + sp + u) * (uint32_t)(TM * TN * 4) : kOutOfRange;
 #pragma unroll
-                    for (int b = 0; b < CB; ++b)
+                    for (int a = 0; a < PB; ++a)
 #pragma unroll
-                        for (int h = 0; h < 4; ++h) {
-                            const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(
-                                rp, theirs + (uint32_t)(((a * CB + b) * 4 + h) * NT + tid) * 16u, 0, kDeviceScope);
-                            acc[a][b][4 * h] += __uint_as_float(v.x);
-                            acc[a][b][4 * h + 1] += __uint_as_float(v.y);
-                            acc[a][b][4 * h + 2] += __uint_as_float(v.z);
-                            acc[a][b][4 * h + 3] += __uint_as_float(v.w);
-                        }
+                        for (int b = 0; b < CB; ++b)
+#pragma unroll
+                            for (int h = 0; h < 4; ++h)
+                                v[u][a][b][h] = __builtin_amdgcn_raw_buffer_load_b128(
+                                    rp, theirs + (uint32_t)(((a * CB + b) * 4 + h) * NT + tid) * 16u, 0, kDeviceScope);
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int a = 0; a < PB; ++a)
+#pragma unroll
+                        for (int b = 0; b < CB; ++b)
+#pragma unroll
+                            for (int h = 0; h < 4; ++h) {
+                                acc[a][b][4 * h] += __uint_as_float(v[u][a][b][h].x);
+                                acc[a][b][4 * h + 1] += __uint_as_float(v[u][a][b][h].y);
+                                acc[a][b][4 * h + 2] += __uint_as_float(v[u][a][b][h].z);
+                                acc[a][b][4 * h + 3] += __uint_as_float(v[u][a][b][h].w);
+                            }
             }
         }
         constexpr int OP = TN * (int)sizeof(TO) + 16;

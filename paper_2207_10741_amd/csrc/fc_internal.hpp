@@ -9,6 +9,26 @@
 
 namespace fc {
 
+// n / d for n < 2^31 as a multiply and a shift: s = ceil(log2 d), m = ceil(2^(31+s) / d);
+// m*d = 2^(31+s) + e with e < d <= 2^s, so the estimate is off by less than 1/d.
+struct FastDiv {
+    uint32_t m, s;
+};
+
+static inline FastDiv make_fastdiv(uint32_t d)
+{
+    FastDiv f;
+    f.s = 0;
+    while ((1ull << f.s) < d) ++f.s;
+    f.m = (uint32_t)(((1ull << (31 + f.s)) + d - 1) / d);
+    return f;
+}
+
+__device__ __forceinline__ uint32_t fast_div(uint32_t n, FastDiv f)
+{
+    return (uint32_t)(((uint64_t)n * f.m) >> (31 + f.s));
+}
+
 // Geometry handed to every kernel (plain ints, passed by value).
 struct Geom {
     int32_t n, h, w, c_in, c_out, kh, kw;
@@ -16,6 +36,7 @@ struct Geom {
     int32_t ho, wo;
     int32_t m;        // n*ho*wo
     uint32_t flags;
+    FastDiv div_wo, div_ho;
 };
 
 // 16-bit storage types are carried as raw bit patterns.
@@ -48,26 +69,6 @@ __device__ __forceinline__ uint16_t f16_bits_rne(float f)
 __device__ __forceinline__ void from_float(float f, float *o) { *o = f; }
 __device__ __forceinline__ void from_float(float f, bf16_t *o) { o->bits = bf16_bits_rne(f); }
 __device__ __forceinline__ void from_float(float f, f16_t *o) { o->bits = f16_bits_rne(f); }
-
-// n / d for n < 2^31 as a multiply and a shift: s = ceil(log2 d), m = ceil(2^(31+s) / d);
-// m*d = 2^(31+s) + e with e < d <= 2^s, so the estimate is off by less than 1/d.
-struct FastDiv {
-    uint32_t m, s;
-};
-
-static inline FastDiv make_fastdiv(uint32_t d)
-{
-    FastDiv f;
-    f.s = 0;
-    while ((1ull << f.s) < d) ++f.s;
-    f.m = (uint32_t)(((1ull << (31 + f.s)) + d - 1) / d);
-    return f;
-}
-
-__device__ __forceinline__ uint32_t fast_div(uint32_t n, FastDiv f)
-{
-    return (uint32_t)(((uint64_t)n * f.m) >> (31 + f.s));
-}
 
 static inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
@@ -357,6 +358,15 @@ hipError_t launch_conv_mfma(const Geom &g, int in_dtype, int out_dtype, const vo
                             const uint8_t *mask_in, const uint8_t *mask_out, const void *w,
                             const float *bias, const int32_t *idx, const int32_t *count, void *out,
                             float *partials, int32_t *tile_counters, hipStream_t s);
+
+// Layers of a few hundred 32-row blocks, 16-bit storage, more than one tap (see fc_conv_small.hip; shapes
+// conv_mfma_supported accepts).  Without a list the kernel labels the positions itself, from mask_out or the
+// centre tap of mask_in.  splits > 1 needs partials and cleared tile_counters.
+bool conv_small_wanted(const Geom &g, int in_dtype);
+int conv_small_splits(const Geom &g, bool room);
+hipError_t launch_conv_small(const Geom &g, int in_dtype, int out_dtype, int splits, const void *x, const uint8_t *mask_in,
+                             const uint8_t *mask_out, const void *w, const float *bias, const int32_t *idx,
+                             const int32_t *count, void *out, float *partials, int32_t *tile_counters, hipStream_t s);
 
 // Calibration launches (see fc_calibrate.hip): `blocks` workgroups of four waves each run
 // `iters` rounds of eight matrix instructions; a streaming copy of `bytes` bytes.
