@@ -327,10 +327,10 @@ int32_t fc_focused_conv2d(const fc_conv_desc *desc, const void *x, const uint8_t
         tile_counters = (int32_t *)((uint8_t *)workspace + l.counters);
         partials = (float *)((uint8_t *)workspace + l.partials);
     }
-    const bool small = mfma && conv_small_wanted(g, desc->in_dtype);
-    const int small_splits = small ? conv_small_splits(g, tile_counters != nullptr) : 1;
+    const bool room = tile_counters != nullptr;
+    const bool small = mfma && conv_small_wanted(g, desc->in_dtype, room, mask_in && !idx);
     // (a layer whose reduction is not split leaves the counters alone)
-    bool counters_cleared = small ? small_splits == 1 : !split_k_reachable(g, desc->in_dtype);
+    bool counters_cleared = small ? !conv_small_counts(g, room) : !split_k_reachable(g, desc->in_dtype);
     const bool f32 = desc->in_dtype == FC_F32 && conv_f32_supported(g);
 
     if (mask_in && !idx) {
@@ -378,11 +378,11 @@ int32_t fc_focused_conv2d(const fc_conv_desc *desc, const void *x, const uint8_t
     hipError_t e;
     const bool pw = mfma && (idx || !mask_in) && conv_pw_wanted(g, desc->in_dtype, desc->out_dtype, mask_in != nullptr);
     if (small) {
-        if (small_splits > 1 && !counters_cleared && !(g.flags & FC_WORKSPACE_READY)) {
+        if (!counters_cleared && !(g.flags & FC_WORKSPACE_READY)) {
             e = launch_zero_i32(tile_counters, kSplitGrid, s);
             if (e != hipSuccess) return FC_ERR_HIP;
         }
-        e = launch_conv_small(g, desc->in_dtype, desc->out_dtype, small_splits, x, mask_in, mask_out, w, bias, idx, count, out,
+        e = launch_conv_small(g, desc->in_dtype, desc->out_dtype, room, x, mask_in, mask_out, w, bias, idx, count, out,
                               partials, tile_counters, s);
         if (e != hipSuccess) return FC_ERR_HIP;
     } else if (mfma && idx && !(pw && (g.flags & FC_RESIDENT_WEIGHTS)) &&

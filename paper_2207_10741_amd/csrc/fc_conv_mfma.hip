@@ -45,9 +45,6 @@
 
 namespace fc {
 
-constexpr int kMaxSplits = 16;                 // most K-splits of one tile
-constexpr int kBusySplitStages = 64;          // shortest reduction that is split on a busy chip
-constexpr int kSmallLayerTiles = 64;  // layers with at most this many 128 x 64 tiles use 64 x 64 tiles
 [[maybe_unused]] constexpr int kMaxTaps = 32;                   // tap-valid bits per row live in one 32-bit word
 
 // Bytes of the LDS stage region: NB buffers of (TM + TN) rows for the tap-by-tap loop; with the

@@ -3,11 +3,12 @@
 //
 // Such a layer is a chain of memory round trips: its matrix work takes a tenth of its time.  This
 // kernel is cut for the chain, not for the throughput:
-//   - a tile is 32 rows x TN channels, and its reduction is dealt out over the four waves of a
-//     workgroup (and, for long reductions, over S workgroups), so no wave multiplies for long;
+//   - a wave owns 32 rows x 32 channels and, where the reduction is long, one split of it; the splits of a
+//     tile are the waves of one workgroup (of several, past four) and meet in LDS.  Splits and the order
+//     within them are those of the tiled kernel: the same sums, bit for bit;
 //   - every wave is a pipeline of its own: it stages its own pixels and weights in its own ring of LDS
 //     slots (a slot = 64 channels of one tap for the tile's rows and channels), with no barrier
-//     before the sums of the four waves meet;
+//     before the sums of the waves meet;
 //   - the tile of a workgroup follows from its number alone, so the weights of its first slots are
 //     requested before anything is known about its rows;
 //   - with a list, the count and the entries are read together (entries past the count are dropped);
@@ -23,24 +24,39 @@
 
 namespace fc {
 
-constexpr int kSmallThreads = 256;
-constexpr int kSmallRows = 32;
-constexpr int kSmallSlots = 3;
+constexpr int kSmallRows = 32, kSmallChannels = 32;
+constexpr int kSmallSlots = 4;
+constexpr int kSmallWaves = 4;      // most waves of a workgroup
+constexpr uint32_t kSmallSlotBytes = (kSmallRows + kSmallChannels) * 128u;
+constexpr uint32_t kSmallWaveBytes = kSmallSlots * kSmallSlotBytes;
 
-template <int TN> constexpr uint32_t small_slot_bytes() { return (uint32_t)(kSmallRows + TN) * 128u; }
-template <int TN> constexpr size_t small_lds_bytes() { return (size_t)4 * kSmallSlots * small_slot_bytes<TN>(); }
-
-// How the launch is cut: channel tiles, splits of the reduction, and the division of the workgroup number.
+// How the launch is cut: channel tiles, groups of (up to four) splits, and the divisions of the workgroup number.
 struct SmallCut {
-    int32_t n_nt, splits;
-    FastDiv per_mt; // by n_nt * splits
-    FastDiv by_s;   // by splits
-    FastDiv by_cch; // by the 64-channel chunks of a tap
+    int32_t n_nt, groups, room;
+    FastDiv per_mt;    // by n_nt * groups
+    FastDiv by_groups;
+    FastDiv by_cch;    // by the 64-channel chunks of a tap
     FastDiv by_kw;
 };
 
-template <int DT, typename TO, int TN>
-__global__ __launch_bounds__(kSmallThreads, 1) void k_conv_small(Geom g, SmallCut cut, const uint16_t *__restrict__ x,
+// Splits of every tile's reduction when `rows` rows are kept: for 3x3 kernels the tiled kernel's rule for its
+// 64 x 64 tiles; the others never ran there on such tiles and are cut for the waves of one workgroup.
+__host__ __device__ static inline int small_splits(int rows, int c_out, int stages, int taps, bool room)
+{
+    if (taps != 9) return stages >= 4 * kSmallWaves ? kSmallWaves : 1;
+    const int ntiles = ((rows + 63) / 64) * ((c_out + 63) / 64);
+    if (!room || ntiles <= 0) return 1;
+    int s = kSplitGrid / ntiles;
+    s = s < 1 ? 1 : (s > stages ? stages : s);
+    if (s > kMaxSplits) s = kMaxSplits;
+    const int cap = stages / kMinSplitStages;
+    if (s > cap) s = cap < 1 ? 1 : cap;
+    if (ntiles * 4 > kSplitGrid && stages < kBusySplitStages) s = 1;
+    return s;
+}
+
+template <int DT, typename TO>
+__global__ __launch_bounds__(64 * kSmallWaves, 1) void k_conv_small(Geom g, SmallCut cut, const uint16_t *__restrict__ x,
                                                                  const uint8_t *__restrict__ mask_in,
                                                                  const uint8_t *__restrict__ mask_out,
                                                                  const uint16_t *__restrict__ w,
@@ -51,69 +67,98 @@ __global__ __launch_bounds__(kSmallThreads, 1) void k_conv_small(Geom g, SmallCu
                                                                  int32_t *__restrict__ tile_counters)
 {
     constexpr int NS = kSmallSlots;
-    constexpr int CB = TN / 32;         // 32-channel blocks
-    constexpr int XL = kSmallRows / 8;  // wave loads of a slot: 8 rows of 128 bytes each
-    constexpr int WL = TN / 8;
-    constexpr uint32_t SLOT = small_slot_bytes<TN>();
+    constexpr int XL = kSmallRows / 8, WL = kSmallChannels / 8; // wave loads of a slot: 8 rows of 128 bytes each
+    constexpr uint32_t SLOT = kSmallSlotBytes;
     extern __shared__ __align__(16) unsigned char lds[];
 
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
+    const int waves = blockDim.x >> 6;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int unit = blockIdx.x, nts = cut.n_nt * cut.splits;
+    const int unit = blockIdx.x, nts = cut.n_nt * cut.groups;
     const int mt = (int)fast_div((uint32_t)unit, cut.per_mt), in_mt = unit - mt * nts;
-    const int nt = (int)fast_div((uint32_t)in_mt, cut.by_s), split = in_mt - nt * cut.splits;
-    const int co0 = nt * TN, r0 = mt * kSmallRows;
+    const int nt = (int)fast_div((uint32_t)in_mt, cut.by_groups), group = in_mt - nt * cut.groups;
+    const int co0 = nt * kSmallChannels, r0 = mt * kSmallRows;
     const int taps = g.kh * g.kw, cch = (g.c_in + 63) >> 6, total = taps * cch;
-    // this workgroup's stages [b, e), this wave's [q0, q1)
-    const int b = (int)((uint32_t)(split * total) / (uint32_t)cut.splits);
-    const int e = (int)((uint32_t)((split + 1) * total) / (uint32_t)cut.splits);
-    const int q0 = b + ((wave * (e - b)) >> 2), q1 = b + (((wave + 1) * (e - b)) >> 2), n = q1 - q0;
+    const int split = group * waves + wave;
+    // this wave's stages [q0, q0 + n)
+    int rows = g.m, splits = 1, q0 = 0, n = 0;
+    auto take_split = [&]() {
+        splits = small_splits(rows, g.c_out, total, taps, cut.room != 0);
+        const uint32_t b = splits > 1 ? (uint32_t)(split * total) / (uint32_t)splits : 0u;
+        const uint32_t e = splits > 1 ? (uint32_t)((split + 1) * total) / (uint32_t)splits : (uint32_t)total;
+        q0 = (int)b;
+        n = split < splits ? (int)(e - b) : 0;
+    };
+    // (with a list the splits follow the kept count; when that could change them, the count is waited for)
+    const bool wait_count = idx && small_splits(1, g.c_out, total, taps, cut.room != 0) != small_splits(g.m, g.c_out, total, taps, cut.room != 0);
+    if (wait_count) rows = *count;
+    take_split();
 
-    const uint32_t lds_wave = __builtin_amdgcn_readfirstlane((uint32_t)reinterpret_cast<uintptr_t>(lds) + (uint32_t)wave * (NS * SLOT));
-    const unsigned char *my_lds = lds + (uint32_t)wave * (NS * SLOT);
+    const uint32_t lds_wave = __builtin_amdgcn_readfirstlane((uint32_t)reinterpret_cast<uintptr_t>(lds) + (uint32_t)wave * kSmallWaveBytes);
+    const unsigned char *my_lds = lds + (uint32_t)wave * kSmallWaveBytes;
     const int prow = lane >> 3;
     // (rows of a lane's loads differ by multiples of 8: the swizzle alternates with bit 2 of (row >> 1))
     const int piece0 = (lane & 7) ^ FC_SWZ(prow), piece1 = (lane & 7) ^ FC_SWZ(prow + 8);
 
     // ---- weights of the first slots ----
     const u32x4_t rsrc_w = make_rsrc_words(w, (uint32_t)g.c_out * taps * g.c_in * 2u);
-    auto stage_of = [&](int q, int *tap, int *cc) {
-        *tap = (int)fast_div((uint32_t)q, cut.by_cch);
-        *cc = q - *tap * cch;
+    // (Code that runs once is kept short - loops rolled - since fetching it is what it costs; the loop over
+    // the stages steps its cursors instead of dividing.)
+    struct Cursor {
+        int tap, cc, kh, kw, left; // left: stages to come
     };
-    // (Loops are kept rolled throughout: the kernel runs every instruction once or a few times, so what
-    // an unrolled copy costs is the fetching of its code.)
-    const int ch0 = piece0 * 8, ch1 = piece1 * 8;
-    const uint32_t wrow = (uint32_t)(taps * g.c_in) * 2u;
-    const uint32_t woff = (uint32_t)(co0 + prow) * wrow;
-    auto load_w = [&](int i) __attribute__((always_inline)) { // slot contents of this wave's stage i
-        int tap, cc;
-        stage_of(q0 + i, &tap, &cc);
-        const uint32_t sw = (uint32_t)(tap * g.c_in + cc * 64) * 2u;
-        const int left = i < n ? g.c_in - cc * 64 : 0;
-        const uint32_t o0 = ch0 < left ? woff + sw + (uint32_t)ch0 * 2u : kOutOfRange;
-        const uint32_t o1 = ch1 < left ? woff + sw + (uint32_t)ch1 * 2u : kOutOfRange;
-        uint32_t to = lds_wave + (uint32_t)(i % NS) * SLOT + (uint32_t)kSmallRows * 128u;
-        uint32_t row = 0; // rows of weights past the last channel lie past the tensor's end
-#pragma unroll 1
-        for (int j = 0; j < WL; j += 2) {
-            dma_load16(rsrc_w, o0 == kOutOfRange ? o0 : o0 + row, to);
-            dma_load16(rsrc_w, o1 == kOutOfRange ? o1 : o1 + row + 8u * wrow, to + 1024u);
-            row += 16u * wrow;
-            to = __builtin_amdgcn_readfirstlane(to + 2048u);
+    auto cursor_at = [&](int q, int left) {
+        Cursor c;
+        c.tap = (int)fast_div((uint32_t)q, cut.by_cch);
+        c.cc = q - c.tap * cch;
+        c.kh = (int)fast_div((uint32_t)c.tap, cut.by_kw);
+        c.kw = c.tap - c.kh * g.kw;
+        c.left = left;
+        return c;
+    };
+    auto advance = [&](Cursor &c) {
+        --c.left;
+        if (++c.cc == cch) {
+            c.cc = 0;
+            ++c.tap;
+            if (++c.kw == g.kw) {
+                c.kw = 0;
+                ++c.kh;
+            }
         }
     };
+    const int ch0 = piece0 * 8, ch1 = piece1 * 8;
+    // weight rows past the last channel lie past the tensor's end and read as zeros
+    uint32_t woff[WL];
+#pragma unroll
+    for (int j = 0; j < WL; ++j)
+        woff[j] = (uint32_t)(co0 + prow + 8 * j) * (uint32_t)(taps * g.c_in) * 2u + (uint32_t)(j & 1 ? ch1 : ch0) * 2u;
+    auto load_w = [&](const Cursor &c, int slot) __attribute__((always_inline)) {
+        uint32_t sw = (uint32_t)(c.tap * g.c_in + c.cc * 64) * 2u;
+        sw = __builtin_amdgcn_readfirstlane(c.left > 0 ? sw : 0u);
+        __asm__("" : "+s"(sw));
+        const int room = c.left > 0 ? g.c_in - c.cc * 64 : 0;
+        const uint32_t to = lds_wave + (uint32_t)slot * SLOT + (uint32_t)kSmallRows * 128u;
+#pragma unroll
+        for (int j = 0; j < WL; ++j)
+            dma_load16_s(rsrc_w, (j & 1 ? ch1 : ch0) < room ? woff[j] : kOutOfRange, sw,
+                         __builtin_amdgcn_readfirstlane(to + (uint32_t)j * 1024u));
+    };
+    Cursor wc = cursor_at(q0, n);
 #pragma unroll 1
-    for (int i = 0; i < NS; ++i) load_w(i);
+    for (int i = 0; i < NS - 1; ++i) {
+        load_w(wc, i);
+        advance(wc);
+    }
 
     // ---- the tile's rows: lane l holds row l & 31 ----
     const bool packed = (g.flags & FC_PACKED_MASKS) != 0;
     const bool fill = mask_in && !(g.flags & FC_SKIP_ZERO_FILL);
-    int rows = g.m, p = r0 + l32;
+    int p = r0 + l32;
     bool live = p < g.m, drop = false;
     if (idx) {
         const int entry = idx[min(p, g.m - 1)];
-        rows = *count;
+        if (!wait_count) rows = *count;
         live = p < rows;
         p = live ? entry : 0;
     } else if (mask_in) {
@@ -148,28 +193,30 @@ __global__ __launch_bounds__(kSmallThreads, 1) void k_conv_small(Geom g, SmallCu
             xoff[j] = (uint32_t)__shfl(pix0, r) * (uint32_t)g.c_in * 2u + xbias + (uint32_t)((j & 1 ? piece1 : piece0) * 16);
             xin[j] = (uint32_t)__shfl((int)inside, r);
         }
-        auto load_x = [&](int i) __attribute__((always_inline)) {
-            int tap, cc;
-            stage_of(q0 + i, &tap, &cc);
-            const int kh = (int)fast_div((uint32_t)tap, cut.by_kw), kw = tap - kh * g.kw;
-            const uint32_t sx = __builtin_amdgcn_readfirstlane((uint32_t)((kh * g.dh * g.w + kw * g.dw) * g.c_in + cc * 64) * 2u);
-            const uint32_t to = lds_wave + (uint32_t)(i % NS) * SLOT;
-            const int left = i < n ? g.c_in - cc * 64 : 0;
-            const uint32_t sel0 = ch0 < left ? 1u << (tap & 31) : 0u, sel1 = ch1 < left ? 1u << (tap & 31) : 0u;
+        auto load_x = [&](const Cursor &c, int slot) __attribute__((always_inline)) {
+            uint32_t sx = (uint32_t)((c.kh * g.dh * g.w + c.kw * g.dw) * g.c_in + c.cc * 64) * 2u;
+            sx = __builtin_amdgcn_readfirstlane(c.left > 0 ? sx : 0u);
+            __asm__("" : "+s"(sx));
+            const int room = c.left > 0 ? g.c_in - c.cc * 64 : 0;
+            const uint32_t bit = 1u << (c.tap & 31);
+            const uint32_t sel0 = ch0 < room ? bit : 0u, sel1 = ch1 < room ? bit : 0u;
+            const uint32_t to = lds_wave + (uint32_t)slot * SLOT;
 #pragma unroll
             for (int j = 0; j < XL; ++j)
-                dma_load16(rsrc_x, (xin[j] & (j & 1 ? sel1 : sel0)) ? xoff[j] + sx : kOutOfRange,
-                           __builtin_amdgcn_readfirstlane(to + (uint32_t)j * 1024u));
+                dma_load16_s(rsrc_x, (xin[j] & (j & 1 ? sel1 : sel0)) ? xoff[j] : kOutOfRange, sx,
+                             __builtin_amdgcn_readfirstlane(to + (uint32_t)j * 1024u));
         };
+        Cursor xc = cursor_at(q0, n);
 #pragma unroll 1
-        for (int i = 0; i < NS; ++i) load_x(i);
+        for (int i = 0; i < NS - 1; ++i) {
+            load_x(xc, i);
+            advance(xc);
+        }
 
         // what the mask says about this lane's row under the wave's taps
         uint32_t bits = inside;
         if (mask_in) {
-            int t0, t1, cc;
-            stage_of(q0, &t0, &cc);
-            stage_of(n > 0 ? q1 - 1 : q0, &t1, &cc);
+            const int t0 = cursor_at(q0, 0).tap, t1 = cursor_at(n > 0 ? q0 + n - 1 : q0, 0).tap;
             const int64_t mask_bytes = (int64_t)g.n * g.h * g.w;
             uint32_t rel = 0;
             if (!packed && g.dw == 1 && g.kw <= 4 && mask_bytes >= 4) {
@@ -208,157 +255,165 @@ __global__ __launch_bounds__(kSmallThreads, 1) void k_conv_small(Geom g, SmallCu
             bits &= rel;
         }
 
-        f32x16_t acc[CB];
+        // the sums start from the bias (first split)
+        f32x16_t acc;
 #pragma unroll
-        for (int c = 0; c < CB; ++c)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) acc[c][i] = 0.f;
+        for (int q = 0; q < 4; ++q) {
+            const int co = co0 + q * 8 + half * 4;
+            float4 bq = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (bias && split == 0 && co < g.c_out) bq = *reinterpret_cast<const float4 *>(bias + co);
+            acc[4 * q] = bq.x; acc[4 * q + 1] = bq.y; acc[4 * q + 2] = bq.z; acc[4 * q + 3] = bq.w;
+        }
         const uint32_t frag = (uint32_t)l32 * 128u, swz = FC_SWZ(l32);
-        wait_vmcnt<0>(); // the first NS slots
+        // A step multiplies the operands it finds in registers, after requesting the next stage's from LDS;
+        // the slot they came from is then free and takes the stage NS - 1 further on.
+        struct Operands {
+            Frag<DT> x[4], w[4];
+        };
+        auto fetch = [&](Operands &o, int slot) __attribute__((always_inline)) {
+            const unsigned char *xs = my_lds + (uint32_t)slot * SLOT + frag, *ws = xs + kSmallRows * 128;
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) {
+                const uint32_t at = (uint32_t)((2 * kk + half) ^ swz) * 16u;
+                o.x[kk].load(xs, at);
+                o.w[kk].load(ws, at);
+            }
+        };
+        Cursor mc = cursor_at(q0, n);
+        int slot = 0; // of the stage about to be multiplied
+        auto step = [&](Operands &now, Operands &next) __attribute__((always_inline)) {
+            const int after = slot + 1 == NS ? 0 : slot + 1;
+            wait_vmcnt<(XL + WL) * (NS - 3)>(); // the next stage has landed
+            fetch(next, after);
+            __builtin_amdgcn_sched_barrier(0);
+            const int last = slot == 0 ? NS - 1 : slot - 1; // (free since the step before)
+            load_w(wc, last);
+            load_x(xc, last);
+            advance(wc);
+            advance(xc);
+            const bool on = (bits >> (mc.tap & 31)) & 1u;
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) {
+                now.x[kk].v.x = on ? now.x[kk].v.x : 0u;
+                now.x[kk].v.y = on ? now.x[kk].v.y : 0u;
+                now.x[kk].v.z = on ? now.x[kk].v.z : 0u;
+                now.x[kk].v.w = on ? now.x[kk].v.w : 0u;
+                acc = mfma32<DT>(now.w[kk], now.x[kk], acc);
+            }
+            advance(mc);
+            slot = after;
+            // (operands read before their slot is written again: the loads above go to the slot of the
+            // step before, whose operands have been multiplied)
+        };
+        Operands oa, ob;
+        wait_vmcnt<0>(); // the first NS - 1 slots
+        fetch(oa, 0);
 #pragma unroll 1
-        for (int i = 0; i < n; ++i) {
-            wait_vmcnt<(XL + WL) * (NS - 1)>(); // slot i (later ones are behind it)
-            int tap, cc;
-            stage_of(q0 + i, &tap, &cc);
-            const unsigned char *xs = my_lds + (uint32_t)(i % NS) * SLOT + frag, *ws = xs + kSmallRows * 128;
-            Frag<DT> xf[4], wf[4][CB];
-#pragma unroll
-            for (int kk = 0; kk < 4; ++kk) {
-                const uint32_t o = (uint32_t)((2 * kk + half) ^ swz) * 16u;
-                xf[kk].load(xs, o);
-#pragma unroll
-                for (int c = 0; c < CB; ++c) wf[kk][c].load(ws + c * 4096, o);
-            }
-            __builtin_amdgcn_sched_barrier(0); // all operands of the slot in flight before the first multiply
-            const bool on = (bits >> (tap & 31)) & 1u;
-            const int ks = min(4, (g.c_in - cc * 64 + 15) >> 4); // 16-channel steps that exist
-#pragma unroll
-            for (int kk = 0; kk < 4; ++kk) {
-                if (kk >= ks) break;
-                xf[kk].v.x = on ? xf[kk].v.x : 0u;
-                xf[kk].v.y = on ? xf[kk].v.y : 0u;
-                xf[kk].v.z = on ? xf[kk].v.z : 0u;
-                xf[kk].v.w = on ? xf[kk].v.w : 0u;
-#pragma unroll
-                for (int c = 0; c < CB; ++c) acc[c] = mfma32<DT>(wf[kk][c], xf[kk], acc[c]);
-            }
-            // the slot's next contents (past the end: loads that are switched off, so that the counts of the
-            // waits hold)
-            __asm__ volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            load_w(i + NS);
-            load_x(i + NS);
+        for (int i = 0; i < n; i += 2) {
+            step(oa, ob);
+            if (i + 1 >= n) break;
+            step(ob, oa);
         }
         wait_vmcnt<0>();
 
-        // ---- the waves' sums meet: quad (c, q) of a lane = channels 32 c + 8 q + 4 half .. + 3 of its row ----
-        __syncthreads();
-        float4 *part = reinterpret_cast<float4 *>(lds);
-#pragma unroll
-        for (int c = 0; c < CB; ++c)
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                part[((wave * CB + c) * 4 + q) * 64 + lane] =
-                    make_float4(acc[c][4 * q], acc[c][4 * q + 1], acc[c][4 * q + 2], acc[c][4 * q + 3]);
-        __syncthreads();
-        float4 v[CB]; // wave q finishes quad q of every block
-#pragma unroll
-        for (int c = 0; c < CB; ++c) {
-            v[c] = part[(c * 4 + wave) * 64 + lane];
-#pragma unroll
-            for (int k = 1; k < 4; ++k) {
-                const float4 t = part[((k * CB + c) * 4 + wave) * 64 + lane];
-                v[c].x += t.x; v[c].y += t.y; v[c].z += t.z; v[c].w += t.w;
+        // quad q of a lane = channels 8 q + 4 half .. + 3 of its row; wave v finishes quads v, v + waves, ...
+        auto store = [&](int q, const float4 &t_in) __attribute__((always_inline)) {
+            const int co = co0 + q * 8 + half * 4;
+            if (co >= g.c_out || !(live || (drop && fill))) return;
+            const int64_t orow = (g.flags & FC_COMPACT_OUT) ? (int64_t)r0 + l32 : (int64_t)(drop ? r0 + l32 : p);
+            float4 t = drop ? make_float4(0.f, 0.f, 0.f, 0.f) : t_in;
+            TO *o = out + orow * g.c_out + co;
+            if constexpr (sizeof(TO) == 4) {
+                if (g.flags & FC_RELU) {
+                    t.x = relu_keep_nan(t.x); t.y = relu_keep_nan(t.y);
+                    t.z = relu_keep_nan(t.z); t.w = relu_keep_nan(t.w);
+                }
+                store4<DT, TO>(o, t.x, t.y, t.z, t.w);
+            } else if constexpr (sizeof(TO) == 1) {
+                uint32_t pk;
+                store4<DT, TO>(reinterpret_cast<TO *>(&pk), t.x, t.y, t.z, t.w);
+                if (g.flags & FC_RELU) pk = relu_packed8(pk);
+                *reinterpret_cast<uint32_t *>(o) = pk;
+            } else {
+                uint2 pk;
+                store4<DT, TO>(reinterpret_cast<TO *>(&pk), t.x, t.y, t.z, t.w);
+                if (g.flags & FC_RELU) {
+                    pk.x = relu_packed16(pk.x);
+                    pk.y = relu_packed16(pk.y);
+                }
+                *reinterpret_cast<uint2 *>(o) = pk;
             }
-        }
-        bool mine = true;
-        if (cut.splits > 1) {
+        };
+        const int mates = (splits + waves - 1) / waves; // workgroups that share the tile
+        if (splits == 1) {
+            if (wave == 0 && group == 0)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) store(q, make_float4(acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]));
+        } else if (mates == 1) {
+            if (group == 0) { // uniform
+                __syncthreads(); // every wave is done with its slots
+                float4 *part = reinterpret_cast<float4 *>(lds);
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    part[(wave * 4 + q) * 64 + lane] = make_float4(acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]);
+                __syncthreads();
+                for (int q = wave; q < 4; q += waves) {
+                    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+                    for (int k = 0; k < splits; ++k) {
+                        const float4 t = part[(k * 4 + q) * 64 + lane];
+                        v.x += t.x; v.y += t.y; v.z += t.z; v.w += t.w;
+                    }
+                    store(q, v);
+                }
+            }
+        } else if (group < mates) { // uniform
             // Park the sums (device-scope accesses, as in the tiled kernel), count in; the workgroup that
-            // arrives last adds the S partial tiles in split order.
+            // arrives last adds the partial tiles in split order.
             const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(
                 partials, 0, (uint32_t)((size_t)kSplitGrid * kSplitTileFloats * sizeof(float)), 0x00020000);
-            constexpr uint32_t TILE = (uint32_t)kSmallRows * TN * 4u;
+            constexpr uint32_t TILE = (uint32_t)kSmallRows * kSmallChannels * 4u;
+            const int tile = mt * cut.n_nt + nt;
+            const uint32_t first = (uint32_t)(tile * splits) * TILE;
+            if (split < splits)
 #pragma unroll
-            for (int c = 0; c < CB; ++c) {
-                u32x4_t t;
-                t.x = __float_as_uint(v[c].x); t.y = __float_as_uint(v[c].y);
-                t.z = __float_as_uint(v[c].z); t.w = __float_as_uint(v[c].w);
-                __builtin_amdgcn_raw_buffer_store_b128(t, rp, (uint32_t)unit * TILE + (uint32_t)(c * 256 + tid) * 16u, 0, kDeviceScope);
-            }
+                for (int q = 0; q < 4; ++q) {
+                    u32x4_t t;
+                    t.x = __float_as_uint(acc[4 * q]); t.y = __float_as_uint(acc[4 * q + 1]);
+                    t.z = __float_as_uint(acc[4 * q + 2]); t.w = __float_as_uint(acc[4 * q + 3]);
+                    __builtin_amdgcn_raw_buffer_store_b128(t, rp, first + (uint32_t)split * TILE + (uint32_t)(q * 64 + lane) * 16u,
+                                                           0, kDeviceScope);
+                }
             wait_vmcnt<0>();
             __syncthreads();
-            int *arrived = reinterpret_cast<int *>(lds + 4 * CB * 4 * 64 * 16);
-            const int tile = mt * cut.n_nt + nt;
+            int *arrived = reinterpret_cast<int *>(lds);
             if (tid == 0)
                 *arrived = __hip_atomic_fetch_add(&tile_counters[tile], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __syncthreads();
-            mine = *arrived == cut.splits - 1;
-            if (mine) {
+            if (*arrived == mates - 1) {
                 if (tid == 0) // leave the counters as they were found
                     __hip_atomic_store(&tile_counters[tile], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                const uint32_t first = (uint32_t)(unit - split) * TILE;
+                for (int q = wave; q < 4; q += waves) {
+                    u32x4_t t[kMaxSplits]; // all partial tiles in flight
 #pragma unroll
-                for (int c = 0; c < CB; ++c) v[c] = make_float4(0.f, 0.f, 0.f, 0.f);
-                constexpr int U = 4; // partial tiles in flight
-                for (int s0 = 0; s0 < cut.splits; s0 += U) {
-                    u32x4_t t[U][CB];
+                    for (int k = 0; k < kMaxSplits; ++k)
+                        t[k] = __builtin_amdgcn_raw_buffer_load_b128(
+                            rp, k < splits ? first + (uint32_t)k * TILE + (uint32_t)(q * 64 + lane) * 16u : kOutOfRange, 0, kDeviceScope);
+                    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-                    for (int u = 0; u < U; ++u)
-#pragma unroll
-                        for (int c = 0; c < CB; ++c)
-                            t[u][c] = __builtin_amdgcn_raw_buffer_load_b128(
-                                rp, s0 + u < cut.splits ? first + (uint32_t)(s0 + u) * TILE + (uint32_t)(c * 256 + tid) * 16u : kOutOfRange,
-                                0, kDeviceScope);
-#pragma unroll
-                    for (int u = 0; u < U; ++u)
-#pragma unroll
-                        for (int c = 0; c < CB; ++c) {
-                            v[c].x += __uint_as_float(t[u][c].x); v[c].y += __uint_as_float(t[u][c].y);
-                            v[c].z += __uint_as_float(t[u][c].z); v[c].w += __uint_as_float(t[u][c].w);
-                        }
-                }
-            }
-        }
-        if (mine && (live || (drop && fill))) {
-            const int64_t orow = (g.flags & FC_COMPACT_OUT) ? (int64_t)r0 + l32 : (int64_t)(drop ? r0 + l32 : p);
-#pragma unroll
-            for (int c = 0; c < CB; ++c) {
-                const int co = co0 + c * 32 + wave * 8 + half * 4;
-                if (co >= g.c_out) continue;
-                float4 t = v[c];
-                if (bias) {
-                    const float4 bq = *reinterpret_cast<const float4 *>(bias + co);
-                    t.x += bq.x; t.y += bq.y; t.z += bq.z; t.w += bq.w;
-                }
-                if (drop) t = make_float4(0.f, 0.f, 0.f, 0.f);
-                TO *o = out + orow * g.c_out + co;
-                if constexpr (sizeof(TO) == 4) {
-                    if (g.flags & FC_RELU) {
-                        t.x = relu_keep_nan(t.x); t.y = relu_keep_nan(t.y);
-                        t.z = relu_keep_nan(t.z); t.w = relu_keep_nan(t.w);
+                    for (int k = 0; k < kMaxSplits; ++k) { // (zeros past the last split)
+                        v.x += __uint_as_float(t[k].x); v.y += __uint_as_float(t[k].y);
+                        v.z += __uint_as_float(t[k].z); v.w += __uint_as_float(t[k].w);
                     }
-                    store4<DT, TO>(o, t.x, t.y, t.z, t.w);
-                } else if constexpr (sizeof(TO) == 1) {
-                    uint32_t pk;
-                    store4<DT, TO>(reinterpret_cast<TO *>(&pk), t.x, t.y, t.z, t.w);
-                    if (g.flags & FC_RELU) pk = relu_packed8(pk);
-                    *reinterpret_cast<uint32_t *>(o) = pk;
-                } else {
-                    uint2 pk;
-                    store4<DT, TO>(reinterpret_cast<TO *>(&pk), t.x, t.y, t.z, t.w);
-                    if (g.flags & FC_RELU) {
-                        pk.x = relu_packed16(pk.x);
-                        pk.y = relu_packed16(pk.y);
-                    }
-                    *reinterpret_cast<uint2 *>(o) = pk;
+                    store(q, v);
                 }
             }
         }
     } else {
         wait_vmcnt<0>(); // (weights on their way into LDS)
-        if (fill && drop && split == 0) { // 32 irrelevant positions: wave v clears every fourth 16-byte piece
-            const int pieces = min(TN, g.c_out - co0) * (int)sizeof(TO) / 16;
+        if (fill && drop && group == 0) { // 32 irrelevant positions
+            const int pieces = min(kSmallChannels, g.c_out - co0) * (int)sizeof(TO) / 16;
             const u32x4_t zero = {0u, 0u, 0u, 0u};
-            for (int i = wave * 2 + half; i < pieces; i += 8)
+            for (int i = wave * 2 + half; i < pieces; i += 2 * waves)
                 *reinterpret_cast<u32x4_t *>(out + (int64_t)(r0 + l32) * g.c_out + co0 + i * (16 / (int)sizeof(TO))) = zero;
         }
     }
@@ -370,7 +425,7 @@ __global__ __launch_bounds__(kSmallThreads, 1) void k_conv_small(Geom g, SmallCu
         if (!idle_only || mt >= tiles) {
             if (any) __syncthreads(); // LDS is free again
             clear_irrelevant(g, mask_in, mask_out, out, g.c_out * (int)sizeof(TO) / 16,
-                             (idle_only ? unit - tiles * nts : unit) * 4 + wave, (idle_only ? idle : grid) * 4,
+                             (idle_only ? unit - tiles * nts : unit) * waves + wave, (idle_only ? idle : grid) * waves,
                              reinterpret_cast<int32_t *>(lds) + wave * 64);
         }
     }
@@ -380,36 +435,33 @@ __global__ __launch_bounds__(kSmallThreads, 1) void k_conv_small(Geom g, SmallCu
 
 static int small_total(const Geom &g) { return g.kh * g.kw * ((g.c_in + 63) / 64); }
 
-// Layers whose 32-row x 64-channel tiles come to about one workgroup per CU (its slots fill most of a CU's
-// LDS).  Measured against the tiled kernel on half-kept layers, call without a list / with a list / no mask:
-// 64 -> 64 at 56 x 56 9.0 / 7.5 / 7.0 -> 6.0 / 5.7 / 5.3 us, 512 -> 512 at 7 x 7 14.3 / 11.6 / 11.3 -> 8.7 / 8.3 / 8.0 us;
-// 128 -> 128 on 8 x 28 x 28 (392 tiles) 15.8 / 11.9 / 11.9 -> 18.3 / 11.2 / 15.2 us, so the line lies below that.
-bool conv_small_wanted(const Geom &g, int in_dtype)
+// The layers the tiled kernel would run on 64 x 64 tiles: 32-row x 32-channel tiles come to about one
+// or two per CU.  Without a list the splits must not depend on the kept count.
+bool conv_small_wanted(const Geom &g, int in_dtype, bool room, bool needs_labels)
 {
     if (in_dtype != FC_BF16 && in_dtype != FC_F16) return false;
     if (g.kh * g.kw == 1 || (g.flags & (FC_COMPACT_IN | FC_RESIDENT_WEIGHTS))) return false;
-    return (int64_t)((g.m + 31) / 32) * ((g.c_out + 63) / 64) <= 320;
+    const int taps = g.kh * g.kw, total = small_total(g);
+    const int64_t tiles = (int64_t)((g.m + 31) / 32) * ((g.c_out + 31) / 32);
+    const int splits = small_splits(1, g.c_out, total, taps, room);
+    // 3x3: what the tiled kernel would run on 64 x 64 tiles, while a CU gets no more than about four waves
+    // (512 -> 512 on 8 x 7 x 7, 1 872 waves, is 14.8 us there and 24.6 us here)
+    if (taps == 9 && ((int64_t)((g.m + 127) / 128) * ((g.c_out + 63) / 64) > kSmallLayerTiles || tiles * splits > 1024)) return false;
+    if (taps != 9 && tiles > 1024) return false;
+    return !needs_labels || splits == small_splits(g.m, g.c_out, total, taps, room);
 }
 
-// Splits of the reduction over workgroups: only where it is so long that the weights of a tile, at
-// the 64 bytes a cycle a CU can take in, cost more than the exchange of partial sums (about 4 000 cycles).
-int conv_small_splits(const Geom &g, bool room)
-{
-    const int total = small_total(g);
-    const int tiles = ((g.m + 31) / 32) * ((g.c_out + 63) / 64);
-    if (!room || total < 36) return 1;
-    int s = total / 18;
-    while (s > 1 && tiles * s > 256) --s; // (one workgroup per CU)
-    return s > 8 ? 8 : s;
-}
+// May tiles meet through the workspace (more splits than a workgroup has waves)?
+bool conv_small_counts(const Geom &g, bool room) { return small_splits(1, g.c_out, small_total(g), g.kh * g.kw, room) > kSmallWaves; }
 
-template <int DT, typename TO, int TN>
-static hipError_t launch_small_t(const Geom &g, int splits, const void *x, const uint8_t *mask_in, const uint8_t *mask_out,
+template <int DT, typename TO>
+static hipError_t launch_small_t(const Geom &g, bool room, const void *x, const uint8_t *mask_in, const uint8_t *mask_out,
                                  const void *w, const float *bias, const int32_t *idx, const int32_t *count, void *out,
                                  float *partials, int32_t *tile_counters, hipStream_t s)
 {
-    auto kern = k_conv_small<DT, TO, TN>;
-    constexpr size_t bytes = small_lds_bytes<TN>();
+    auto kern = k_conv_small<DT, TO>;
+    const int splits = small_splits(1, g.c_out, small_total(g), g.kh * g.kw, room); // the most any kept count gives
+    const int waves = splits < kSmallWaves ? splits : kSmallWaves;
     // (more than 64 KB of dynamic LDS: allowed once per function and device)
     static std::atomic<uint64_t> attr_devices{0};
     int dev = 0;
@@ -417,40 +469,30 @@ static hipError_t launch_small_t(const Geom &g, int splits, const void *x, const
     if (e != hipSuccess) return e;
     const uint64_t dev_bit = 1ull << (dev & 63);
     if (!(attr_devices.load(std::memory_order_acquire) & dev_bit)) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)(kSmallWaves * kSmallWaveBytes));
         if (e != hipSuccess) return e;
         attr_devices.fetch_or(dev_bit, std::memory_order_release);
     }
     SmallCut cut;
-    cut.n_nt = (g.c_out + TN - 1) / TN;
-    cut.splits = splits;
-    cut.per_mt = make_fastdiv((uint32_t)(cut.n_nt * splits));
-    cut.by_s = make_fastdiv((uint32_t)splits);
+    cut.n_nt = (g.c_out + kSmallChannels - 1) / kSmallChannels;
+    cut.groups = (splits + waves - 1) / waves;
+    cut.room = room;
+    cut.per_mt = make_fastdiv((uint32_t)(cut.n_nt * cut.groups));
+    cut.by_groups = make_fastdiv((uint32_t)cut.groups);
     cut.by_kw = make_fastdiv((uint32_t)g.kw);
     cut.by_cch = make_fastdiv((uint32_t)((g.c_in + 63) / 64));
-    const int grid = ((g.m + kSmallRows - 1) / kSmallRows) * cut.n_nt * splits;
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(kSmallThreads), bytes, s, g, cut, (const uint16_t *)x, mask_in, mask_out,
-                       (const uint16_t *)w, bias, idx, count, (TO *)out, partials, tile_counters);
+    const int grid = ((g.m + kSmallRows - 1) / kSmallRows) * cut.n_nt * cut.groups;
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * waves), waves * kSmallWaveBytes, s, g, cut, (const uint16_t *)x, mask_in,
+                       mask_out, (const uint16_t *)w, bias, idx, count, (TO *)out, partials, tile_counters);
     return hipGetLastError();
 }
 
-template <int DT, typename TO>
-static hipError_t launch_small_o(const Geom &g, int splits, const void *x, const uint8_t *mask_in, const uint8_t *mask_out,
-                                 const void *w, const float *bias, const int32_t *idx, const int32_t *count, void *out,
-                                 float *partials, int32_t *tile_counters, hipStream_t s)
-{
-    // 32 channels per tile while that is no more than a workgroup per CU: half the work each (64 -> 64 at
-    // 56 x 56 7.2 -> 6.0 us; 256 -> 256 on 8 x 14 x 14, 392 such tiles, 11.2 -> 16.6 us)
-    if (((g.m + 31) / 32) * ((g.c_out + 31) / 32) * splits > 256)
-        return launch_small_t<DT, TO, 64>(g, splits, x, mask_in, mask_out, w, bias, idx, count, out, partials, tile_counters, s);
-    return launch_small_t<DT, TO, 32>(g, splits, x, mask_in, mask_out, w, bias, idx, count, out, partials, tile_counters, s);
-}
-
-hipError_t launch_conv_small(const Geom &g, int in_dtype, int out_dtype, int splits, const void *x, const uint8_t *mask_in,
+hipError_t launch_conv_small(const Geom &g, int in_dtype, int out_dtype, bool room, const void *x, const uint8_t *mask_in,
                              const uint8_t *mask_out, const void *w, const float *bias, const int32_t *idx,
                              const int32_t *count, void *out, float *partials, int32_t *tile_counters, hipStream_t s)
 {
-#define FC_SMALL(DT, TO) launch_small_o<DT, TO>(g, splits, x, mask_in, mask_out, w, bias, idx, count, out, partials, tile_counters, s)
+#define FC_SMALL(DT, TO) launch_small_t<DT, TO>(g, room, x, mask_in, mask_out, w, bias, idx, count, out, partials, tile_counters, s)
     if (in_dtype == FC_BF16)
         return out_dtype == FC_F32 ? FC_SMALL(FC_BF16, float) : (out_dtype == FC_FP8 ? FC_SMALL(FC_BF16, uint8_t) : FC_SMALL(FC_BF16, uint16_t));
     return out_dtype == FC_F32 ? FC_SMALL(FC_F16, float) : (out_dtype == FC_FP8 ? FC_SMALL(FC_F16, uint8_t) : FC_SMALL(FC_F16, uint16_t));

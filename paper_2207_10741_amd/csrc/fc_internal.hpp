@@ -339,6 +339,9 @@ static inline bool split_k_possible(const Geom &g)
 // Fewest stages (128-byte pieces of one tap's channels) a K-split is left with: a layer with fewer than
 // two splits' worth is never split, and its calls need no cleared counters.
 constexpr int kMinSplitStages = 8;
+constexpr int kMaxSplits = 16;         // most K-splits of one tile
+constexpr int kBusySplitStages = 64;   // shortest reduction that is split on a busy chip
+constexpr int kSmallLayerTiles = 64;   // layers with at most this many 128 x 64 tiles use small tiles
 static inline bool split_k_reachable(const Geom &g, int in_dtype)
 {
     const int64_t row = (int64_t)g.c_in * (in_dtype == FC_FP8 ? 1 : 2);
@@ -359,12 +362,13 @@ hipError_t launch_conv_mfma(const Geom &g, int in_dtype, int out_dtype, const vo
                             const float *bias, const int32_t *idx, const int32_t *count, void *out,
                             float *partials, int32_t *tile_counters, hipStream_t s);
 
-// Layers of a few hundred 32-row blocks, 16-bit storage, more than one tap (see fc_conv_small.hip; shapes
+// Layers of a few hundred tiles, 16-bit storage, more than one tap (see fc_conv_small.hip; shapes
 // conv_mfma_supported accepts).  Without a list the kernel labels the positions itself, from mask_out or the
-// centre tap of mask_in.  splits > 1 needs partials and cleared tile_counters.
-bool conv_small_wanted(const Geom &g, int in_dtype);
-int conv_small_splits(const Geom &g, bool room);
-hipError_t launch_conv_small(const Geom &g, int in_dtype, int out_dtype, int splits, const void *x, const uint8_t *mask_in,
+// centre tap of mask_in (needs_labels).  room: partials and tile_counters are there; conv_small_counts: the
+// counters are used and must be clear.
+bool conv_small_wanted(const Geom &g, int in_dtype, bool room, bool needs_labels);
+bool conv_small_counts(const Geom &g, bool room);
+hipError_t launch_conv_small(const Geom &g, int in_dtype, int out_dtype, bool room, const void *x, const uint8_t *mask_in,
                              const uint8_t *mask_out, const void *w, const float *bias, const int32_t *idx,
                              const int32_t *count, void *out, float *partials, int32_t *tile_counters, hipStream_t s);
 
