@@ -169,7 +169,36 @@ __global__ __launch_bounds__(kDwThreads, (WLDS ? 8 : (KS > 3 ? 2 : 4))) void k_d
     // WLDS only: [WROWS + 1][CT]: the filters (fp32 per tap, or packed pairs of taps), then the bias
     extern __shared__ __align__(16) float dw_w[];
     const int CT = a.lanes_per_pos * VEC; // channels of this workgroup
-    if constexpr (WLDS) {
+    if constexpr (WLDS && PAIR) {
+        // one lane per channel chunk: its filters are 9 contiguous 16-byte pieces, all in flight together
+        // (element by element through the workgroup was 13 round trips for 576 channels)
+        if ((int)threadIdx.x < a.lanes_per_pos) {
+            const bool some = chunk < a.chunks;
+            const TI *wp = w + (int64_t)(some ? chunk : 0) * (VEC * TAPS_C);
+            uint32_t raw[VEC * TAPS_C / 2];
+#pragma unroll
+            for (int k = 0; k < VEC * TAPS_C / 8; ++k) {
+                const u32x4 t = reinterpret_cast<const u32x4 *>(wp)[k];
+                raw[4 * k] = t.x; raw[4 * k + 1] = t.y; raw[4 * k + 2] = t.z; raw[4 * k + 3] = t.w;
+            }
+            float bq[VEC];
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) bq[v] = bias && some ? bias[chunk * VEC + v] : 0.f;
+            float *to = dw_w + j * VEC;
+#pragma unroll
+            for (int r = 0; r < kDwPairRows; ++r)
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) {
+                    const int e0 = v * TAPS_C + 2 * r, e1 = e0 + 1;
+                    const uint32_t lo = (raw[e0 >> 1] >> (16 * (e0 & 1))) & 0xffffu;
+                    const uint32_t hi = 2 * r + 1 < TAPS_C ? (raw[e1 >> 1] >> (16 * (e1 & 1))) & 0xffffu : 0u;
+                    to[r * CT + v] = __uint_as_float(lo | (hi << 16));
+                }
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) to[WROWS * CT + v] = bq[v];
+        }
+        __syncthreads();
+    } else if constexpr (WLDS) {
         const int ch_first = blockIdx.z * CT;
         for (int i = threadIdx.x; i < (WROWS + 1) * CT; i += kDwThreads) {
             const int t = i / CT, ch = ch_first + (i - t * CT);
@@ -370,7 +399,7 @@ __global__ __launch_bounds__(kDwThreads, (WLDS ? 8 : (KS > 3 ? 2 : 4))) void k_d
     }
 }
 
-constexpr size_t kDwWldsBytes = 20 * 1024; // filters in LDS only while eight workgroups still fit a CU
+constexpr size_t kDwWldsBytes = 24 * 1024; // filters in LDS only while six workgroups still fit a CU (960 channels: 23 KB)
 
 template <typename TI, typename TO, int VEC, int KS>
 hipError_t launch_k(const Geom &g, const void *x, const uint8_t *mask_in, const void *w, const float *bias,
