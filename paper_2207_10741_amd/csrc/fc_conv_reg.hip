@@ -529,6 +529,157 @@ __global__ __launch_bounds__(kRegThreads, KS > 9 ? 1 : 2) void k_conv_grouped(
     }
 }
 
+// The same layer where output positions are input pixels (unit stride, same size) and there is no list.
+// The kernel above spends most of its time on addresses: a lane's pieces lie in other lines than its
+// neighbours', 64 cycles of the address unit per load, for the weights of a block as for the pixels.
+// Here the pixels under a span of 64 consecutive positions are, for every kernel row, one run of
+// 64 + (kw - 1) dil_w consecutive pixels: they are staged in LDS once (whole 128-byte pieces of 64 output
+// channels' groups), the workgroup's weights likewise, and all operands come from there; a gated tap
+// reads a piece of zeros.  (128 channels in 32 groups on 16 x 56 x 56, half kept: 16.6 us above.)
+constexpr int kWindowSpan = 64;
+struct WindowCut {
+    int32_t line;      // pixels of a kernel row's run
+    int32_t lg_pieces; // log2 of the 16-byte pieces of a pixel's window
+    int32_t x_bytes, w_bytes;
+    FastDiv by_line, by_kw, by_ppt;
+};
+
+template <int DT, typename TO, int KS>
+__global__ __launch_bounds__(kRegThreads, 2) void k_conv_grouped_window(
+    Geom g, WindowCut cut, int cig, int cog, const uint16_t *__restrict__ x, const uint8_t *__restrict__ mask_in,
+    const uint8_t *__restrict__ mask_out, const uint16_t *__restrict__ w, const float *__restrict__ bias,
+    TO *__restrict__ out)
+{
+    // [pixels | weights | 16 bytes of zeros | tap bits | kept positions, then dropped ones from the end]
+    extern __shared__ __align__(16) unsigned char lds[];
+    unsigned char *w_s = lds + cut.x_bytes, *zero_s = w_s + cut.w_bytes;
+    uint32_t *bits_s = reinterpret_cast<uint32_t *>(zero_s + 16);
+    uint8_t *order_s = reinterpret_cast<uint8_t *>(bits_s + kWindowSpan);
+    const uint32_t lds0 = (uint32_t)reinterpret_cast<uintptr_t>(lds);
+    const int tid = threadIdx.x, lane = tid & 63, col = lane & 15, quarter = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int first = blockIdx.x * kWindowSpan, blk0 = blockIdx.y * 64, co0 = blk0 + wave * 16;
+    const int taps = g.kh * g.kw;
+    const int win0 = (blk0 / cog) * cig; // first input channel of the workgroup's groups
+
+    // ---- weights: one contiguous block ----
+    {
+        const u32x4_t rsrc_w = make_rsrc_words(w, (uint32_t)g.c_out * taps * cig * 2u);
+        const uint32_t at = (uint32_t)(blk0 * taps * cig) * 2u;
+        for (uint32_t o = (uint32_t)wave * 1024u; o < (uint32_t)cut.w_bytes; o += 4096u)
+            dma_load16(rsrc_w, at + o + (uint32_t)lane * 16u, __builtin_amdgcn_readfirstlane(lds0 + cut.x_bytes + o));
+    }
+    // ---- labels: lane l of every wave holds position first + l ----
+    const int p = first + lane;
+    const bool inside = p < g.m;
+    const bool kept = inside && (!mask_in || position_kept(g, mask_in, mask_out, p));
+    const uint64_t kept_set = __ballot(kept), drop_set = __ballot(inside && !kept);
+    const int n = __popcll(kept_set), nd = __popcll(drop_set);
+    if (wave == 0) {
+        const uint64_t below = (1ull << lane) - 1ull;
+        if (kept) order_s[__popcll(kept_set & below)] = (uint8_t)lane;
+        if (inside && !kept) order_s[kWindowSpan - 1 - __popcll(drop_set & below)] = (uint8_t)lane;
+        bits_s[lane] = 0u;
+        if (lane < 4) reinterpret_cast<uint32_t *>(zero_s)[lane] = 0u;
+    }
+    if (n > 0) {
+        // ---- pixels: LDS piece c of pixel slot q holds the window's piece c ^ (q >> 1) ----
+        const int pieces = 1 << cut.lg_pieces;
+        const u32x4_t rsrc_x = make_rsrc_words(x, (uint32_t)g.n * g.h * g.w * g.c_in * 2u);
+        const int npix = g.n * g.h * g.w, slots = g.kh * cut.line;
+        for (int o = wave * 64; o < (slots << cut.lg_pieces); o += kRegThreads) {
+            const int i = o + lane, q = i >> cut.lg_pieces, c = (i ^ (q >> 1)) & (pieces - 1);
+            const int k = (int)fast_div((uint32_t)q, cut.by_line), t = q - k * cut.line;
+            const int pix = first + (k * g.dh - g.ph) * g.w - g.pw + t, ch = win0 + c * 8;
+            const bool ok = q < slots && pix >= 0 && pix < npix && ch < g.c_in;
+            dma_load16(rsrc_x, ok ? (uint32_t)(pix * g.c_in + ch) * 2u : kOutOfRange,
+                       __builtin_amdgcn_readfirstlane(lds0 + (uint32_t)o * 16u));
+        }
+        // ---- taps in use: this wave's share of them, for all positions ----
+        const bool packed = (g.flags & FC_PACKED_MASKS) != 0;
+        const int pp = kept ? p : 0;
+        const int r = (int)fast_div((uint32_t)pp, g.div_wo), ow = pp - r * g.wo;
+        const int img = (int)fast_div((uint32_t)r, g.div_ho), oh = r - img * g.ho;
+        __syncthreads(); // bits_s cleared
+        uint32_t mine = 0;
+        constexpr int U = 3; // look-ups in flight
+        for (int t0 = wave; t0 < taps; t0 += 4 * U) {
+            bool in[U];
+            uint8_t m[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int t = t0 + 4 * u, kh = (int)fast_div((uint32_t)t, cut.by_kw), kw = t - kh * g.kw;
+                const int ih = oh - g.ph + kh * g.dh, iw = ow - g.pw + kw * g.dw;
+                in[u] = kept && t < taps && (uint32_t)ih < (uint32_t)g.h && (uint32_t)iw < (uint32_t)g.w;
+                m[u] = mask_in ? (uint8_t)mask_at(mask_in, in[u] ? (img * g.h + ih) * g.w + iw : 0, packed) : (uint8_t)1;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) mine |= in[u] && m[u] ? 1u << (t0 + 4 * u) : 0u;
+        }
+        if (mine) atomicOr(&bits_s[lane], mine);
+    }
+    wait_vmcnt<0>();
+    __syncthreads();
+    if (nd > 0 && !(g.flags & FC_SKIP_ZERO_FILL)) {
+        const int pieces = min(64, g.c_out - blk0) * (int)sizeof(TO) / 16; // (16 divides the channels)
+        const u32x4_t zero = {0u, 0u, 0u, 0u};
+        for (int i = tid; i < nd * pieces; i += kRegThreads) {
+            const int k = (int)((uint32_t)i / (uint32_t)pieces), c = i - k * pieces;
+            const int64_t row = (int64_t)(first + order_s[kWindowSpan - 1 - k]) * g.c_out + blk0;
+            __builtin_nontemporal_store(zero, reinterpret_cast<u32x4_t *>(out + row) + c);
+        }
+    }
+    if (co0 >= g.c_out || n == 0) return;
+
+    // ---- this wave's 16 channels: weights from LDS to registers, and where their pieces lie ----
+    const int ic = cog >= 16 ? cig : (16 / cog) * cig, ppt = ic >> 3;
+    const int bw0 = (co0 / cog) * cig;             // first input channel of the block's groups
+    const int co = co0 + col, wch = (co / cog) * cig;
+    u32x4_t wf[KS];
+    int xq[KS];        // pixel slot of the piece from the position's own slot
+    uint32_t xc[KS], xsel[KS];
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+        const int q = s * 4 + quarter;
+        const int tap = (int)fast_div((uint32_t)q, cut.by_ppt), pc = q - tap * ppt;
+        const int kh = (int)fast_div((uint32_t)tap, cut.by_kw), kw = tap - kh * g.kw;
+        xq[s] = kh * cut.line + kw * g.dw;
+        xc[s] = (uint32_t)((bw0 - win0) >> 3) + (uint32_t)pc;
+        xsel[s] = tap < taps ? 1u << tap : 0u;
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf) {
+            const int local = bw0 + pc * 8 + hf * 4 - wch;
+            const bool ok = tap < taps && local >= 0 && local < cig;
+            const uint2 v = ok ? *reinterpret_cast<const uint2 *>(w_s + (((co - blk0) * taps + tap) * cig + local) * 2) : make_uint2(0, 0);
+            wf[s][2 * hf] = v.x;
+            wf[s][2 * hf + 1] = v.y;
+        }
+    }
+    float4 bq = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (bias) bq = *reinterpret_cast<const float4 *>(bias + co0 + quarter * 4);
+    const uint32_t zero_at = (uint32_t)(cut.x_bytes + cut.w_bytes), pmask = (1u << cut.lg_pieces) - 1u;
+    for (int r0 = 0; r0 < n; r0 += 16) {
+        const bool live = r0 + col < n;
+        const int j = live ? order_s[r0 + col] : 0;
+        const uint32_t bits = live ? bits_s[j] : 0u;
+        u32x4_t xv[KS];
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const uint32_t q = (uint32_t)(j + xq[s]);
+            const uint32_t at = ((q << cut.lg_pieces) + ((xc[s] ^ (q >> 1)) & pmask)) * 16u;
+            xv[s] = *reinterpret_cast<const u32x4_t *>(lds + ((bits & xsel[s]) ? at : zero_at));
+        }
+        f32x4_t acc = {bq.x, bq.y, bq.z, bq.w};
+#pragma unroll
+        for (int s = 0; s < KS; ++s) acc = mfma16<DT>(wf[s], xv[s], acc);
+        if (g.flags & FC_RELU)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[i] = !(acc[i] > 0.f) ? (acc[i] != acc[i] ? acc[i] : 0.f) : acc[i];
+        if (live)
+            store4<DT, TO>(out + (int64_t)(first + j) * g.c_out + co0 + quarter * 4, acc[0], acc[1], acc[2], acc[3]);
+    }
+}
+
 // matrix steps of a 16-channel block's reduction
 static int grouped_steps(const Geom &g, int cig, int cog)
 {
@@ -556,6 +707,27 @@ static hipError_t launch_grouped(const Geom &g, int groups, const void *x, const
                                  hipStream_t s)
 {
     const int cig = g.c_in / groups, cog = g.c_out / groups;
+    // spans of positions as windows of pixels: unit stride, same size, no list, groups that do not straddle a
+    // workgroup's 64 channels and whose channels make a power of two of 16-byte pieces, at most 64 KB of LDS
+    const int wch = cog <= 64 && 64 % cog == 0 ? 64 / cog * cig : 0;
+    if (!idx && g.sh == 1 && g.sw == 1 && g.ho == g.h && g.wo == g.w && wch >= 32 && wch <= 128 && (wch & (wch - 1)) == 0 &&
+        grouped_steps(g, cig, cog) <= 9) {
+        WindowCut cut;
+        cut.line = kWindowSpan + (g.kw - 1) * g.dw;
+        cut.lg_pieces = wch == 32 ? 2 : (wch == 64 ? 3 : 4);
+        cut.x_bytes = (g.kh * cut.line * wch * 2 + 1023) & ~1023;
+        cut.w_bytes = (64 * g.kh * g.kw * cig * 2 + 1023) & ~1023;
+        cut.by_line = make_fastdiv((uint32_t)cut.line);
+        cut.by_kw = make_fastdiv((uint32_t)g.kw);
+        cut.by_ppt = make_fastdiv((uint32_t)((cog >= 16 ? cig : (16 / cog) * cig) / 8));
+        const int bytes = cut.x_bytes + cut.w_bytes + 16 + kWindowSpan * 5;
+        if (bytes <= 64 * 1024) {
+            auto kern = grouped_steps(g, cig, cog) <= 5 ? k_conv_grouped_window<DT, TO, 5> : k_conv_grouped_window<DT, TO, 9>;
+            hipLaunchKernelGGL(kern, dim3((g.m + kWindowSpan - 1) / kWindowSpan, (g.c_out + 63) / 64), dim3(kRegThreads), bytes, s,
+                               g, cut, cig, cog, (const uint16_t *)x, mask_in, mask_out, (const uint16_t *)w, bias, (TO *)out);
+            return hipGetLastError();
+        }
+    }
     const dim3 grid((g.m + kGroupedSpan - 1) / kGroupedSpan, (g.c_out + 63) / 64);
     const int steps = grouped_steps(g, cig, cog);
     auto kern = steps <= 5 ? k_conv_grouped<DT, TO, 5> : (steps <= 9 ? k_conv_grouped<DT, TO, 9> : k_conv_grouped<DT, TO, 18>);
