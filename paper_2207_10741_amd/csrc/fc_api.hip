@@ -345,7 +345,9 @@ int32_t fc_focused_conv2d(const fc_conv_desc *desc, const void *x, const uint8_t
         // Labels the caller brings (mask_out without a list) are compacted as they are, so that
         // the rows computed and the rows cleared follow the same labels.
         // The fp32 kernel and the one for small layers label their rows themselves, whatever the labels' source.
-        const bool rank_in_kernel = f32 || small || (mfma && g.m <= kInlineRankPositions && !mask_out);
+        const bool rank_in_kernel = f32 || small || (mfma && g.m <= kInlineRankPositions && !mask_out) ||
+                                    (mfma && tiles_label_rows(g, desc->in_dtype) &&
+                                     !conv_line_wanted(g, desc->in_dtype, desc->out_dtype, true));
         if (!rank_in_kernel) {
             CompactExtras ex;
             if (tile_counters && !counters_cleared) {

@@ -81,10 +81,13 @@ constexpr size_t dma_lds_bytes()
 // A tile whose line would need more than SL slots (a fragmented mask) runs the tap-by-tap
 // loop instead.  NBW: LDS buffers for the per-tap weight slabs of the shared-halo loop.
 //
+// OWN: the 64 x 64 instance for layers with a mask and no list that label their rows themselves (tiles_label_rows).
+// The rows of a tile are consecutive positions, the irrelevant ones are stored as zeros, and no reduction is split.
+//
 // CMP: the instances that serve compacted activations (FC_COMPACT_IN / FC_COMPACT_OUT: rows
 // stored in list order).  Separate instances, so that the ordinary ones do not change by a
 // register: the 128 x 64 three-buffer instance loses 20 % with a handful more.
-template <int DT, typename TO, int TM, int TN, int WM, int WN, int TAPC, int NB, int MINW, int SL, int NBW, bool CMP>
+template <int DT, typename TO, int TM, int TN, int WM, int WN, int TAPC, int NB, int MINW, int SL, int NBW, bool CMP, bool OWN>
 __global__ __launch_bounds__(WM *WN * 64, MINW) void k_conv_dma(Geom g, const uint16_t *__restrict__ x,
                                                                  const uint8_t *__restrict__ mask_in,
                                                                  const uint8_t *__restrict__ mask_out,
@@ -151,7 +154,7 @@ __global__ __launch_bounds__(WM *WN * 64, MINW) void k_conv_dma(Geom g, const ui
     // tile then has every thread drop its positions of that tile's rank range into row_p.  A
     // small layer so needs no compaction launch before this one.
     const bool packed_masks = (g.flags & FC_PACKED_MASKS) != 0; // masks are one bit per pixel
-    const bool inline_rank = !idx && mask_in;
+    const bool inline_rank = !OWN && !idx && mask_in;
     uint32_t rank_flags = 0;
     int rank_base = 0;
     int rows = g.m;
@@ -174,7 +177,7 @@ __global__ __launch_bounds__(WM *WN * 64, MINW) void k_conv_dma(Geom g, const ui
         rank_base = before + incl - cnt;
         rows = total;
         __syncthreads(); // row_p is free again
-    } else if (idx) {
+    } else if (!OWN && idx) {
         rows = *count;
     }
     const int n_nt = (g.c_out + TN - 1) / TN;
@@ -206,21 +209,7 @@ __global__ __launch_bounds__(WM *WN * 64, MINW) void k_conv_dma(Geom g, const ui
     // Units of one tile are adjacent in the order, so they share an XCD.  S is the same in
     // every workgroup (it depends on the kept count and the grid only).
     int S = 1;
-    if (partials && ntiles > 0) {
-        S = (int)gridDim.x / ntiles;
-        const int work = HALO ? g.kh * cchunks : stages; // (kernel row, chunk) groups or stages
-        S = S < 1 ? 1 : (S > work ? work : S);
-        if (S > kMaxSplits) S = kMaxSplits;
-        // the exchange of partial tiles costs about as much as twenty stages, so a unit keeps at
-        // least kMinSplitStages of them: short reductions are not split at all (a 3x3 layer with
-        // 64 input channels: 8.4 us unsplit against 19.3 us split three ways)
-        const int s_cap = stages / kMinSplitStages;
-        if (S > s_cap) S = s_cap < 1 ? 1 : s_cap;
-        // when the tiles alone already fill more than a quarter of the grid, the exchange also
-        // competes with the other tiles' traffic and only long reductions gain (512 channels at
-        // 16 x 16, batch 16: 72 stages split three ways 31 -> 26 us, 36 stages 20 -> 28 us)
-        if (ntiles * 4 > (int)gridDim.x && stages < kBusySplitStages) S = 1;
-    }
+    if (!OWN && partials && ntiles > 0) S = split_k_splits(ntiles, (int)gridDim.x, HALO ? g.kh * cchunks : stages, stages);
     const int nunits = ntiles * S;
     const int per_xcd = (nunits + 7) >> 3;
     const int xcd = blockIdx.x & 7;
@@ -231,7 +220,7 @@ __global__ __launch_bounds__(WM *WN * 64, MINW) void k_conv_dma(Geom g, const ui
     // irrelevant rows (about one tile's worth of rows each, off the critical path of the
     // tiles); otherwise every workgroup clears its share before its tiles.  A wave looks
     // at 64 positions at a time and stores whole 16-byte pieces with all lanes.
-    if (mask_in && !(g.flags & FC_SKIP_ZERO_FILL)) {
+    if (!OWN && mask_in && !(g.flags & FC_SKIP_ZERO_FILL)) {
         const int slots = gridDim.x >> 3;
         const int idle_slots = slots > per_xcd ? slots - per_xcd : 0;
         const bool idle_only = idle_slots > 0 && idle_slots * 8 >= (int)(gridDim.x >> 4);
@@ -281,7 +270,7 @@ __global__ __launch_bounds__(WM *WN * 64, MINW) void k_conv_dma(Geom g, const ui
             s_begin = (int)((uint32_t)(split * stages) / (uint32_t)S);
             s_end = (int)((uint32_t)((split + 1) * stages) / (uint32_t)S);
         }
-        const int nst = s_end - s_begin; // stages of this unit
+        int nst = s_end - s_begin; // stages of this unit
         const int nt = tile / n_mt, mt = tile - nt * n_mt;
         const int co0 = nt * TN;
 
@@ -303,12 +292,14 @@ __global__ __launch_bounds__(WM *WN * 64, MINW) void k_conv_dma(Geom g, const ui
             }
             __syncthreads();
         }
+        bool dropped_row = false; // OWN: this thread's row is an irrelevant position
         int sa_p = -1, sa_ow = 0, sa_ih0 = 0, sa_iw0 = 0, sa_b = 0; // this thread's row (tid < TM)
         if (tid < TM) {
             const int m = mt * TM + tid;
             int p = -1, base = 0, b = 0, hw = 0;
             if (m < rows) {
-                p = inline_rank ? row_p[tid] : (idx ? idx[m] : m);
+                p = inline_rank ? row_p[tid] : (!OWN && idx ? idx[m] : m);
+                if constexpr (OWN) dropped_row = !position_kept(g, mask_in, mask_out, m);
                 const int q = (int)fast_div((uint32_t)p, g.div_wo), ow = p - q * g.wo;
                 b = (int)fast_div((uint32_t)q, g.div_ho);
                 const int oh = q - b * g.ho;
@@ -449,6 +440,8 @@ __global__ __launch_bounds__(WM *WN * 64, MINW) void k_conv_dma(Geom g, const ui
             for (int i = 0; i < PAIR_CH; ++i)
                 if (pin_[i] && mv[i]) atomicOr(&row_bits[prow_[i]], 1u << ptap_[i]);
         }
+        // (a dropped row is marked after the bytes of all taps were requested: one round trip for both)
+        if (OWN && dropped_row) row_p[tid] = -2 - sa_p;
 
         // per-thread, loop-invariant byte offsets; gp = the global 16-byte piece this lane
         // fetches for its LDS slot (the swizzle)
@@ -673,7 +666,11 @@ __global__ __launch_bounds__(WM *WN * 64, MINW) void k_conv_dma(Geom g, const ui
             const int r = prow + j * RPP;
             xgp[j] = slot ^ FC_SWZ(r);
             xoff[j] = ((uint32_t)row_base[r] * (uint32_t)g.c_in + (uint32_t)xgp[j] * EPP) * ES;
-            xbits[j] = row_bits[r];
+            xbits[j] = OWN && row_p[r] < 0 ? 0u : row_bits[r];
+        }
+        if constexpr (OWN) {
+            static_assert(TM == 64, "one lane per row");
+            if (__ballot(row_p[lane] >= 0) == 0) nst = 0; // 64 rows, all irrelevant or past the end
         }
         // cursor: the next stage to be issued (starts at this unit's first stage)
         int tap = s_begin / cchunks, cc = s_begin - tap * cchunks;
@@ -904,7 +901,11 @@ __global__ __launch_bounds__(WM *WN * 64, MINW) void k_conv_dma(Geom g, const ui
             }
             // streaming stores: the output is not read again by this kernel
 #pragma unroll
-            for (int k = 0; k < NPASS; ++k)
+            for (int k = 0; k < NPASS; ++k) {
+                if (OWN && pp[k] < -1 && !(g.flags & FC_SKIP_ZERO_FILL)) {
+                    pp[k] = -2 - pp[k];
+                    pv[k] = u32x4_t{0u, 0u, 0u, 0u};
+                }
                 if (pp[k] >= 0 && co < g.c_out) {
                     // compacted output: row = place in the list, else the position itself
                     int64_t orow = (int64_t)pp[k];
@@ -913,6 +914,7 @@ __global__ __launch_bounds__(WM *WN * 64, MINW) void k_conv_dma(Geom g, const ui
                     }
                     __builtin_nontemporal_store(pv[k], reinterpret_cast<u32x4_t *>(out + orow * g.c_out + co));
                 }
+            }
         }
     }
 
@@ -921,6 +923,23 @@ __global__ __launch_bounds__(WM *WN * 64, MINW) void k_conv_dma(Geom g, const ui
 // ---------------------------------------------------------------------------
 
 #if !defined(FC_MFMA_PART) || FC_MFMA_PART == 0
+// Does a 3x3 layer with a mask and no list label its rows tile by tile (64 x 64 tiles of consecutive positions,
+// irrelevant ones stored as zeros) instead of compacting them in a launch of its own?  While all tiles of the
+// layer run at once, dropping the irrelevant rows shortens nothing and the compaction is 4.5 us: 72 -> 200 on
+// 3 x 75 x 101, stride 2 (348 tiles of 18 stages) 17.0 -> 12.3 us, 64 -> 64 on 8 x 56 x 56 (392 of 9) 12.2 -> 8.6 us,
+// 128 -> 128 on 8 x 28 x 28 (196 of 18) 14.7 -> 9.5 us, whatever the kept share.  From two rounds of tiles on, or
+// with long reductions, the rows left out are worth it: 64 -> 128 on 8 x 56 x 56 (784 tiles) 14.4 -> 20 us; 392 tiles
+// of 36 stages gain 1.5 us at a kept share of one half and lose as much at one fifth.
+bool tiles_label_rows(const Geom &g, int in_dtype)
+{
+    if (g.kh != 3 || g.kw != 3 || g.m <= kInlineRankPositions || (g.flags & FC_RESIDENT_WEIGHTS)) return false;
+    const int chunks = (g.c_in * (in_dtype == FC_FP8 ? 1 : 2) + 127) / 128;
+    // (with a list these take the shared-halo loop, whose order of stages is another one)
+    if (g.sw == 1 && g.dw == 1 && g.wo >= 32 && chunks > 1) return false;
+    const int64_t tiles = (int64_t)((g.m + 63) / 64) * ((g.c_out + 63) / 64);
+    return tiles <= kSplitGrid && tiles * 9 * chunks <= 20 * kSplitGrid;
+}
+
 bool conv_mfma_supported(const Geom &g, int in_dtype, int out_dtype)
 {
     if (in_dtype != FC_BF16 && in_dtype != FC_F16 && in_dtype != FC_FP8) return false;
@@ -942,12 +961,12 @@ bool conv_mfma_supported(const Geom &g, int in_dtype, int out_dtype)
 }
 #endif
 
-template <int DT, typename TO, bool CMP, int TM, int TN, int WM, int WN, int TAPC, int NB, int MINW, int SL = 0, int NBW = 2>
+template <int DT, typename TO, bool CMP, int TM, int TN, int WM, int WN, int TAPC, int NB, int MINW, int SL = 0, int NBW = 2, bool OWN = false>
 static hipError_t launch_dma(const Geom &g, const void *x, const uint8_t *mask_in, const uint8_t *mask_out,
                              const void *w, const float *bias, const int32_t *idx, const int32_t *count,
                              void *out, float *partials, int32_t *tile_counters, hipStream_t s)
 {
-    auto kern = k_conv_dma<DT, TO, TM, TN, WM, WN, TAPC, NB, MINW, SL, NBW, CMP>;
+    auto kern = k_conv_dma<DT, TO, TM, TN, WM, WN, TAPC, NB, MINW, SL, NBW, CMP, OWN>;
     constexpr size_t lds = dma_lds_bytes<TM, TN, NB, SL, NBW>();
     // more than 64 KB of dynamic LDS has to be allowed once per function and device; two
     // threads that both find the bit clear both set the attribute, which is harmless
@@ -965,7 +984,7 @@ static hipError_t launch_dma(const Geom &g, const void *x, const uint8_t *mask_i
     const int64_t max_tiles = (int64_t)((g.m + TM - 1) / TM) * ((g.c_out + TN - 1) / TN);
     const int64_t cap = 256 * 8;
     int blocks = (int)((max_tiles < cap ? max_tiles : cap) + 7) & ~7; // a multiple of the XCD count
-    if (partials) blocks = kSplitGrid; // few tiles: enough workgroups for the K-split to fill the chip
+    if (partials && !OWN) blocks = kSplitGrid; // few tiles: enough workgroups for the K-split to fill the chip
     hipLaunchKernelGGL(kern, dim3(blocks), dim3(WM * WN * 64), lds, s, g, (const uint16_t *)x, mask_in, mask_out,
                        (const uint16_t *)w, bias, idx, count, (TO *)out, partials, tile_counters);
     return hipGetLastError();
@@ -982,6 +1001,10 @@ static hipError_t launch_tile(const Geom &g, const void *x, const uint8_t *mask_
     // otherwise 128 x 64, which doubles the tile count (the kept count is not known here,
     // so the dense row count decides)
     const int64_t tiles128 = (int64_t)((g.m + 127) / 128) * ((g.c_out + 127) / 128);
+    if constexpr (TAPC == 9 && !CMP) {
+        if (mask_in && !idx && g.m > kInlineRankPositions) // the layers of tiles_label_rows; others have a list
+            return launch_dma<DT, TO, CMP, 64, 64, 2, 2, TAPC, 4, 2, 0, 2, true>(FC_ARGS);
+    }
     // Layers with only a handful of tiles (the late layers of a network at batch 1) are all
     // latency: 64 x 64 tiles put them on more CUs and four stage buffers keep three gathers in
     // flight (a ResNet-18 stack at batch 1: 0.243 -> 0.221 ms dense, 0.266 -> 0.245 ms focused)

@@ -45,14 +45,7 @@ __host__ __device__ static inline int small_splits(int rows, int c_out, int stag
 {
     if (taps != 9) return stages >= 4 * kSmallWaves ? kSmallWaves : 1;
     const int ntiles = ((rows + 63) / 64) * ((c_out + 63) / 64);
-    if (!room || ntiles <= 0) return 1;
-    int s = kSplitGrid / ntiles;
-    s = s < 1 ? 1 : (s > stages ? stages : s);
-    if (s > kMaxSplits) s = kMaxSplits;
-    const int cap = stages / kMinSplitStages;
-    if (s > cap) s = cap < 1 ? 1 : cap;
-    if (ntiles * 4 > kSplitGrid && stages < kBusySplitStages) s = 1;
-    return s;
+    return room && ntiles > 0 ? split_k_splits(ntiles, kSplitGrid, stages, stages) : 1;
 }
 
 template <int DT, typename TO>

@@ -341,6 +341,23 @@ static inline bool split_k_possible(const Geom &g)
 constexpr int kMinSplitStages = 8;
 constexpr int kMaxSplits = 16;         // most K-splits of one tile
 constexpr int kBusySplitStages = 64;   // shortest reduction that is split on a busy chip
+// Splits of a reduction of `stages` stages (dealt out in `work` pieces) of each of ntiles tiles on `grid` workgroups.
+__host__ __device__ static inline int split_k_splits(int ntiles, int grid, int work, int stages)
+{
+    int s = grid / ntiles;
+    s = s < 1 ? 1 : (s > work ? work : s);
+    if (s > kMaxSplits) s = kMaxSplits;
+    // the exchange of partial tiles costs about as much as twenty stages, so a unit keeps at
+    // least kMinSplitStages of them: short reductions are not split at all (a 3x3 layer with
+    // 64 input channels: 8.4 us unsplit against 19.3 us split three ways)
+    const int cap = stages / kMinSplitStages;
+    if (s > cap) s = cap < 1 ? 1 : cap;
+    // when the tiles alone already fill more than a quarter of the grid, the exchange also
+    // competes with the other tiles' traffic and only long reductions gain (512 channels at
+    // 16 x 16, batch 16: 72 stages split three ways 31 -> 26 us, 36 stages 20 -> 28 us)
+    if (ntiles * 4 > grid && stages < kBusySplitStages) s = 1;
+    return s;
+}
 constexpr int kSmallLayerTiles = 64;   // layers with at most this many 128 x 64 tiles use small tiles
 static inline bool split_k_reachable(const Geom &g, int in_dtype)
 {
@@ -356,6 +373,7 @@ hipError_t launch_zero_i32(int32_t *p, int n, hipStream_t s);
 
 // Matrix-core path (only for shapes conv_mfma_supported accepts).  It also clears
 // the irrelevant output rows unless FC_SKIP_ZERO_FILL is set; mask_out may be NULL.
+bool tiles_label_rows(const Geom &g, int in_dtype);
 bool conv_mfma_supported(const Geom &g, int in_dtype, int out_dtype);
 hipError_t launch_conv_mfma(const Geom &g, int in_dtype, int out_dtype, const void *x,
                             const uint8_t *mask_in, const uint8_t *mask_out, const void *w,

@@ -704,3 +704,46 @@ def test_stem_kernel_rows(layer, mask_kind, precomputed):
             else np.ones(want.shape[:3], bool)
         assert G.rel_err(G.to_f64(out), want, keep) <= TOL_F32_OUT
         assert not out.cpu().numpy()[~keep].view(np.uint32).any()
+
+
+@pytest.mark.parametrize("layer", [
+    # n, h, w, ci, co, k, s, p, d: one 32 x 32 tile per wave - rows, channels and input channels off the tile and chunk
+    # sizes, one row, splits that meet in a workgroup and (512 channels) through the workspace, other kernel sizes, all 32
+    # taps a row has bits for; then 64 x 64 tiles that label their rows, one of them without a full tile at the end
+    (1, 11, 13, 72, 40, 3, 1, 1, 1), (1, 1, 1, 64, 32, 3, 1, 1, 1), (2, 7, 7, 512, 104, 3, 1, 1, 1), (1, 14, 14, 264, 64, 3, 2, 1, 1),
+    (1, 33, 31, 16, 24, (5, 2), 1, (2, 0), 1), (1, 20, 20, 64, 32, (4, 8), 1, 3, 1), (1, 18, 21, 136, 48, (1, 7), 2, (0, 3), 1),
+    (1, 65, 67, 8, 72, 3, 1, 1, 1), (3, 75, 101, 72, 200, 3, 2, 1, 1), (2, 66, 63, 128, 64, 3, 1, 2, 2)])
+@pytest.mark.parametrize("mode", ["own", "labels", "list", "packed", "dense"])
+def test_small_layer_tiles(layer, mode):
+    n, h, w, ci, co, k, s, p, d = layer
+    kh, kw = k if isinstance(k, tuple) else (k, k)
+    ph, pw = p if isinstance(p, tuple) else (p, p)
+    torch = G.torch_mod()
+    for dtype in (synth.BF16, synth.F16):
+        x = synth.activations((n, h, w, ci), dtype, 239, 1)
+        wt = synth.he_weights(co, kh, kw, ci, dtype, 239, 2)
+        bias = synth.bias(co, 239, 3)
+        mask = None if mode == "dense" else synth.mask_objects(n, h, w, 0.5, 239, 4)
+        if mask is not None:        # nothing at an irrelevant pixel may reach an output
+            x.reshape(n * h * w, ci)[mask.reshape(-1) == 0] = synth.to_storage(np.array([np.nan], np.float32), dtype)[0]
+        desc = B.conv_desc(n, h, w, ci, co, (kh, kw), (s, s), (ph, pw), (d, d), dtype, B.F32,
+                           B.RELU | (B.PACKED_MASKS if mode == "packed" else 0))
+        ho, wo = B.out_dims(desc)
+        out = torch.full((n, ho, wo, co), 7.0, dtype=torch.float32, device=G.dev())
+        md = None if mask is None else G.mask_dev(mask)
+        kwargs = {}
+        if mode in ("labels", "list"):
+            kwargs = dict(mask_out=B.mask_downsample(md, (kh, kw), (s, s), (ph, pw), (d, d)))
+        if mode == "list":
+            kwargs["idx"], kwargs["count"] = B.active_index_compact(kwargs["mask_out"])
+        if mode == "packed":
+            md = B.mask_pack(md)
+        B.focused_conv2d(desc, G.to_dev(x, dtype), G.to_dev(wt, dtype), torch.from_numpy(bias).to(G.dev()), mask_in=md, out=out,
+                         **kwargs)
+        want = O.focused_conv2d(O.ConvShape(n, h, w, ci, co, kh, kw, (s, s), (ph, pw), (d, d), relu=True), x, wt, bias=bias,
+                                mask_in=mask, dtype=dtype)
+        keep = (O.mask_downsample(mask, kh, kw, (s, s), (ph, pw), (d, d)) != 0) if mask is not None \
+            else np.ones(want.shape[:3], bool)
+        if keep.any():
+            assert G.rel_err(G.to_f64(out), want, keep) <= TOL_F32_OUT
+        assert not out.cpu().numpy()[~keep].view(np.uint32).any()
