@@ -168,12 +168,12 @@ def test_layers_that_read_byte_masks_refuse_packed_ones():
                                        None) == -3
 
 
-@pytest.mark.parametrize("n,h,w", [(1, 256, 257), (4, 256, 257), (1, 512, 513), (3, 91, 5), (1, 64, 64)])
+@pytest.mark.parametrize("n,h,w", [(1, 256, 257), (1, 256, 255), (4, 256, 257), (1, 512, 513), (3, 91, 5), (1, 64, 64)])
 @pytest.mark.parametrize("first", [((3, 3), (1, 1), (1, 1), (1, 1)), ((7, 7), (2, 2), (3, 3), (1, 1)),
                                    ((5, 3), (1, 3), (9, 0), (2, 1))])
 @pytest.mark.parametrize("packed", [False, True])
 def test_pyramid_lists_around_the_one_launch_limits(n, h, w, first, packed):
-    """Level sizes on both sides of 16 and of 64 workgroups of 4096 positions, a first level with the mask's
+    """Level sizes on both sides of 4 and of 64 workgroups of 4096 positions, a first level with the mask's
     resolution, a strided one, and one whose window reaches far outside the image (clamped twice)."""
     mask = synth.mask_bernoulli(n, h, w, 0.5, 260, h, w) * np.uint8(5)
     steps = [first, ((3, 3), (2, 2), (1, 1), (1, 1)), ((3, 3), (1, 2), (3, 1), (1, 1))]
