@@ -34,10 +34,13 @@ namespace {
 constexpr int kDwThreads = 256;
 constexpr uint32_t kDwBufferLimit = 0xF0000000u; // one image (and its mask) stays below this many bytes
 constexpr uint32_t kDwOutOfRange = kDwBufferLimit;
+constexpr int kDwTileLanes = 128;                // most channel chunks of a workgroup (filters of 1024 channels: 24 KB of LDS)
 constexpr int kDwTargetBlocks = 1024;            // four workgroups per CU
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2_native __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x2_native __attribute__((ext_vector_type(2)));
 
 struct DwArgs {
     Geom g;
@@ -102,16 +105,15 @@ __device__ __forceinline__ void store_piece(TO *dst, const float *v)
         }
     } else {
         if constexpr (VEC == 8) {
-            uint32_t wds[4];
+            // two values per conversion instruction (round to nearest even)
+            typedef float f32x2 __attribute__((ext_vector_type(2)));
+            u32x4 p;
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                TO lo, hi;
-                from_float(v[2 * k], &lo);
-                from_float(v[2 * k + 1], &hi);
-                wds[k] = (uint32_t)lo.bits | ((uint32_t)hi.bits << 16);
+                const f32x2 two = {v[2 * k], v[2 * k + 1]};
+                if constexpr (__is_same(TO, bf16_t)) p[k] = __builtin_bit_cast(uint32_t, __builtin_convertvector(two, bf16x2_native));
+                else p[k] = __builtin_bit_cast(uint32_t, __builtin_convertvector(two, f16x2_native));
             }
-            u32x4 p;
-            p.x = wds[0]; p.y = wds[1]; p.z = wds[2]; p.w = wds[3];
             *reinterpret_cast<u32x4 *>(dst) = p;
         } else {
 #pragma unroll
@@ -122,8 +124,6 @@ __device__ __forceinline__ void store_piece(TO *dst, const float *v)
 
 // a.lo * b.lo + a.hi * b.hi + c for two packed 16-bit floats per operand, summed in fp32
 // (v_dot2c_f32_bf16 / v_dot2c_f32_f16)
-typedef __bf16 bf16x2_native __attribute__((ext_vector_type(2)));
-typedef _Float16 f16x2_native __attribute__((ext_vector_type(2)));
 template <typename TI>
 __device__ __forceinline__ float dot2_acc(uint32_t a, uint32_t b, float c)
 {
@@ -392,11 +392,184 @@ __global__ __launch_bounds__(kDwThreads, (WLDS ? 8 : (KS > 3 ? 2 : 4))) void k_d
         }
         if (relu) {
 #pragma unroll
-            for (int v = 0; v < VEC; ++v)
-                if (!(acc[v] > 0.f)) acc[v] = (acc[v] != acc[v]) ? acc[v] : 0.f;
+            for (int v = 0; v < VEC; ++v) acc[v] = __builtin_elementwise_maximum(acc[v], 0.f); // (NaN stays NaN)
         }
         store_piece<TO, VEC>(orow, acc);
     }
+}
+
+// 3 x 3 layers of the 16-bit types with stride 1 or 2, no dilation and padding of at most one: a lane owns PY x PX
+// neighbouring positions of its eight channels, so that the pixels and mask bytes under overlapping windows are
+// loaded once (2 x 2 positions at stride 1: 16 loads for 4 windows instead of 36; 2 x 1 at stride 2: 15 instead of 18)
+// and the filters are read from LDS once for all of them.  What bounds such a layer is vector instructions and, in
+// the small ones, a chain of round trips; one step per workgroup, with three of them instead of five: the mask bytes
+// (the positions' labels among them, under the centre taps) are requested before the filters, the pixels before the
+// barrier that makes the filters visible.  Three waves per SIMD (168 registers) hold a whole window; with four, 2 x 2 spills.
+// Sums as in k_dwconv, bit for bit.  Batch 32, half the pixels kept, k_dwconv -> here: 32 channels at 112 x 112 15.2 ->
+// 11.8 us, 96 at 112 / 2 15.6 -> 13.1, 144 at 56 16.0 -> 13.4, 192 at 28 9.1 -> 7.0, 384 at 14 6.6 -> 5.4, 960 at 7 6.5 ->
+// 4.9 us (of which 0.3 .. 1.7 us are the conversions, in both kernels: two values per instruction and no branch on NaN).
+struct DwTileArgs {
+    Geom g;
+    int32_t lanes;     // channel chunks of one tile handled by one workgroup
+    int32_t per_block; // tiles of a workgroup
+    int32_t chunks;    // channel chunks in all: C / 8
+    int32_t tiles_x, tiles;
+    FastDiv div_lanes, div_tx;
+};
+
+template <typename TI, typename TO, int S, int PY, int PX>
+__global__ __launch_bounds__(kDwThreads, 3) void k_dwconv_tile(DwTileArgs a, const TI *__restrict__ x,
+                                                               const uint8_t *__restrict__ mask_in, const TI *__restrict__ w,
+                                                               const float *__restrict__ bias, TO *__restrict__ out)
+{
+    constexpr int VEC = 8, TAPS = 9, R = (PY - 1) * S + 3, Q = (PX - 1) * S + 3, N = PY * PX;
+    const Geom &g = a.g;
+    const int b = blockIdx.y, C = g.c_in, CT = a.lanes * VEC;
+    const int tt = (int)fast_div(threadIdx.x, a.div_lanes), j = (int)threadIdx.x - tt * a.lanes;
+    const int chunk = blockIdx.z * a.lanes + j, c0 = chunk * VEC;
+    const bool mine = tt < a.per_block && chunk < a.chunks;
+    extern __shared__ __align__(16) float dw_w[]; // [kDwPairRows + 1][CT]: packed pairs of taps, then the bias
+
+    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<TI *>(x + (int64_t)b * g.h * g.w * C), 0, (uint32_t)g.h * g.w * C * 2u, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rm = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint8_t *>(mask_in ? mask_in + (int64_t)b * g.h * g.w : nullptr), 0, mask_in ? (uint32_t)g.h * g.w : 0u,
+        0x00020000);
+
+    // taps inside the image, and what the mask says about them
+    const int tile = blockIdx.x * a.per_block + tt;
+    const bool live = mine && tile < a.tiles;
+    const int tile_y = (int)fast_div((uint32_t)tile, a.div_tx), oh0 = tile_y * PY, ow0 = (tile - tile_y * a.tiles_x) * PX;
+    const int ih0 = oh0 * S - g.ph, iw0 = ow0 * S - g.pw;
+    const uint32_t pix0 = (uint32_t)(ih0 * g.w + iw0);
+    bool row_in[R], col_in[Q];
+#pragma unroll
+    for (int r = 0; r < R; ++r) row_in[r] = live && (uint32_t)(ih0 + r) < (uint32_t)g.h;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) col_in[q] = (uint32_t)(iw0 + q) < (uint32_t)g.w;
+    uint32_t mb[R][Q];
+    if (mask_in) {
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int q = 0; q < Q; ++q)
+                mb[r][q] = __builtin_amdgcn_raw_buffer_load_b8(
+                    rm, row_in[r] && col_in[q] ? pix0 + (uint32_t)(r * g.w + q) : kDwOutOfRange, 0, 0);
+    }
+
+    // the filters: one lane per channel chunk, 9 contiguous 16-byte pieces in flight together
+    if ((int)threadIdx.x < a.lanes) {
+        const bool some = chunk < a.chunks;
+        const TI *wp = w + (int64_t)(some ? chunk : 0) * (VEC * TAPS);
+        uint32_t raw[VEC * TAPS / 2];
+#pragma unroll
+        for (int k = 0; k < VEC * TAPS / 8; ++k) {
+            const u32x4 t = reinterpret_cast<const u32x4 *>(wp)[k];
+            raw[4 * k] = t.x; raw[4 * k + 1] = t.y; raw[4 * k + 2] = t.z; raw[4 * k + 3] = t.w;
+        }
+        float bq[VEC];
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) bq[v] = bias && some ? bias[chunk * VEC + v] : 0.f;
+        float *to = dw_w + j * VEC;
+#pragma unroll
+        for (int r = 0; r < kDwPairRows; ++r)
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) {
+                const int e0 = v * TAPS + 2 * r, e1 = e0 + 1;
+                const uint32_t lo = (raw[e0 >> 1] >> (16 * (e0 & 1))) & 0xffffu;
+                const uint32_t hi = 2 * r + 1 < TAPS ? (raw[e1 >> 1] >> (16 * (e1 & 1))) & 0xffffu : 0u;
+                to[r * CT + v] = __uint_as_float(lo | (hi << 16));
+            }
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) to[kDwPairRows * CT + v] = bq[v];
+    }
+
+    // labels: the mask under the centre taps (inside the image: padding of at most one)
+    uint32_t kept = 0, here = 0;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const int oy = i / PX, ox = i - oy * PX;
+        const bool in = live && oh0 + oy < g.ho && ow0 + ox < g.wo;
+        here |= in ? 1u << i : 0u;
+        kept |= in && (!mask_in || mb[oy * S + 1][ox * S + 1]) ? 1u << i : 0u;
+    }
+    // pixels (out of range, hence zeros, where gated)
+    RawWords<16> xv[R][Q];
+    const uint32_t row_bytes = (uint32_t)g.w * C * 2u, off0 = (pix0 * (uint32_t)C + (uint32_t)c0) * 2u;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const bool on = kept && row_in[r] && col_in[q] && (!mask_in || mb[r][q]);
+            xv[r][q] = buffer_load<16>(rx, on ? off0 + (uint32_t)r * row_bytes + (uint32_t)(q * C * 2) : kDwOutOfRange);
+        }
+    __syncthreads();
+
+    const float *wl = dw_w + j * VEC;
+    const bool relu = (g.flags & FC_RELU) != 0, fill = (g.flags & FC_SKIP_ZERO_FILL) == 0;
+    TO *out_at = out + ((int64_t)b * g.ho * g.wo + (int64_t)oh0 * g.wo + ow0) * C + c0;
+    if (kept) {
+        float acc[N][VEC];
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) {
+            const float bv = wl[kDwPairRows * CT + v];
+#pragma unroll
+            for (int i = 0; i < N; ++i) acc[i][v] = bv;
+        }
+#pragma unroll
+        for (int p = 0; p < kDwPairRows; ++p) {
+            uint32_t wf[VEC];
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) wf[v] = __float_as_uint(wl[p * CT + v]);
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                const int oy = (i / PX) * S, ox = (i % PX) * S, t0 = 2 * p, t1 = 2 * p + 1;
+#pragma unroll
+                for (int q = 0; q < VEC / 2; ++q) {
+                    const uint32_t x0 = xv[oy + t0 / 3][ox + t0 % 3].v[q];
+                    const uint32_t x1 = t1 < TAPS ? xv[oy + (t1 < TAPS ? t1 : 0) / 3][ox + t1 % 3].v[q] : 0u;
+                    const uint32_t even = __builtin_amdgcn_perm(x1, x0, 0x05040100u);
+                    const uint32_t odd = __builtin_amdgcn_perm(x1, x0, 0x07060302u);
+                    acc[i][2 * q] = dot2_acc<TI>(even, wf[2 * q], acc[i][2 * q]);
+                    acc[i][2 * q + 1] = dot2_acc<TI>(odd, wf[2 * q + 1], acc[i][2 * q + 1]);
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+            if ((kept >> i) & 1u) {
+                if (relu)
+#pragma unroll
+                    for (int v = 0; v < VEC; ++v) acc[i][v] = __builtin_elementwise_maximum(acc[i][v], 0.f); // (NaN stays NaN)
+                store_piece<TO, VEC>(out_at + ((int64_t)(i / PX) * g.wo + i % PX) * C, acc[i]);
+            }
+    }
+    if (fill && kept != here) {
+        const float z[VEC] = {};
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+            if (((here & ~kept) >> i) & 1u) store_piece<TO, VEC>(out_at + ((int64_t)(i / PX) * g.wo + i % PX) * C, z);
+    }
+}
+
+template <typename TI, typename TO, int S, int PY, int PX>
+hipError_t launch_tile(const Geom &g, const void *x, const uint8_t *mask_in, const void *w, const float *bias, void *out,
+                       hipStream_t s)
+{
+    DwTileArgs a;
+    a.g = g;
+    a.chunks = g.c_in / 8;
+    const int ctiles = (a.chunks + kDwTileLanes - 1) / kDwTileLanes;
+    a.lanes = (a.chunks + ctiles - 1) / ctiles;
+    a.per_block = kDwThreads / a.lanes;
+    a.tiles_x = (g.wo + PX - 1) / PX;
+    a.tiles = a.tiles_x * ((g.ho + PY - 1) / PY);
+    a.div_lanes = make_fastdiv((uint32_t)a.lanes);
+    a.div_tx = make_fastdiv((uint32_t)a.tiles_x);
+    const size_t lds = (size_t)(kDwPairRows + 1) * a.lanes * 8 * sizeof(float);
+    hipLaunchKernelGGL((k_dwconv_tile<TI, TO, S, PY, PX>), dim3((a.tiles + a.per_block - 1) / a.per_block, g.n, ctiles),
+                       dim3(kDwThreads), lds, s, a, (const TI *)x, mask_in, (const TI *)w, bias, (TO *)out);
+    return hipGetLastError();
 }
 
 constexpr size_t kDwWldsBytes = 24 * 1024; // filters in LDS only while six workgroups still fit a CU (960 channels: 23 KB)
@@ -441,6 +614,13 @@ hipError_t launch_t(const Geom &g, const void *x, const uint8_t *mask_in, const 
 {
     constexpr int VEC = 16 / (int)sizeof(TI);
     const bool square = g.kh == g.kw;
+    // (padding of at most one keeps the centre tap, whose pixel labels the position, inside the image)
+    if constexpr (sizeof(TI) == 2) {
+        const bool tile = g.c_in % VEC == 0 && square && g.kh == 3 && g.sh == g.sw && g.sh <= 2 && g.dh == 1 && g.dw == 1 &&
+                          g.ph <= 1 && g.pw <= 1;
+        if (tile && g.sh == 1) return launch_tile<TI, TO, 1, 2, 2>(g, x, mask_in, w, bias, out, s);
+        if (tile) return launch_tile<TI, TO, 2, 2, 1>(g, x, mask_in, w, bias, out, s);
+    }
     if (g.c_in % VEC == 0) {
         if (square && g.kh == 3) return launch_k<TI, TO, VEC, 3>(g, x, mask_in, w, bias, out, s);
         if (square && g.kh == 5) return launch_k<TI, TO, VEC, 5>(g, x, mask_in, w, bias, out, s);

@@ -164,3 +164,20 @@ def test_depthwise_sampled_positions_at_a_large_size():
     assert torch.equal(out16, out32.to(torch.bfloat16))
     # every irrelevant row of the whole tensor is zero bytes
     assert not out16.view(torch.int16)[torch.from_numpy(mask == 0).to(G.dev())].any()
+
+
+@pytest.mark.parametrize("layer", [
+    # tiles of 2 x 2 positions (stride 1) and 2 x 1 (stride 2): odd and even sides, one position, one row, one column,
+    # no padding, padding on one axis, more channel chunks than a workgroup's lanes, padding and dilation of the other kernel
+    (1, 3, 3, 8, 3, 1, 0, 1), (2, 1, 9, 16, 3, 1, 1, 1), (2, 9, 1, 16, 3, 2, 1, 1), (1, 11, 10, 24, 3, 1, (0, 1), 1),
+    (2, 10, 11, 40, 3, 2, (1, 0), 1), (1, 5, 6, 1032, 3, 1, 1, 1), (1, 6, 5, 2064, 3, 2, 0, 1), (1, 12, 13, 16, 3, 1, 2, 1),
+    (1, 13, 12, 16, 3, 2, 2, 2)])
+@pytest.mark.parametrize("mask_kind", ["objects", "bernoulli", None])
+def test_depthwise_position_tiles(layer, mask_kind):
+    torch = G.torch_mod()
+    for dtype in (synth.BF16, synth.F16):
+        out, want, keep = _run(*layer, dtype, mask_kind=mask_kind, irr=0.5, seed=306)
+        assert G.rel_err(G.to_f64(out), want, keep) <= TOL_F32_OUT
+        assert not out.cpu().numpy()[~keep].view(np.uint32).any()
+        low, _, _ = _run(*layer, dtype, mask_kind=mask_kind, irr=0.5, seed=306, out_dtype=dtype)
+        assert torch.equal(low, out.to(low.dtype))
