@@ -672,7 +672,10 @@ def test_fp32_storage_on_the_matrix_cores(layer, mask_kind, precomputed):
     # channel blocks, positions around the 128-row tile, padding wider than the kernel
     (2, 33, 29, 3, 64, 7, 2, 3, 1), (1, 17, 9, 1, 8, 1, 1, 0, 1), (3, 16, 8, 4, 72, 3, 1, 1, 1), (1, 19, 23, 2, 136, 5, 1, 2, 1),
     (2, 21, 18, 3, 16, 3, 1, 2, 2), (1, 24, 40, 1, 24, (3, 9), 1, (1, 4), 1), (1, 2, 3, 3, 16, 3, 1, 1, 1),
-    (1, 20, 20, 2, 16, 8, 1, 3, 1), (4, 65, 63, 3, 32, 3, 2, 1, 1), (1, 12, 12, 3, 8, 3, 1, 5, 1)])
+    (1, 20, 20, 2, 16, 8, 1, 3, 1), (4, 65, 63, 3, 32, 3, 2, 1, 1), (1, 12, 12, 3, 8, 3, 1, 5, 1),
+    # short kernel rows in plain order: one, two and four of them, three channels and four
+    (1, 9, 11, 3, 8, (1, 3), 1, (0, 1), 1), (2, 15, 14, 3, 8, (2, 3), 2, (1, 2), 1), (1, 17, 19, 3, 72, (4, 3), 1, (1, 0), 1),
+    (1, 31, 8, 4, 16, 3, 1, 1, 1)])
 @pytest.mark.parametrize("mask_kind,precomputed", [("objects", False), ("bernoulli", True), (None, False)])
 def test_stem_kernel_rows(layer, mask_kind, precomputed):
     n, h, w, ci, co, k, s, p, d = layer
