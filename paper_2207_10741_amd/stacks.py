@@ -22,6 +22,7 @@ from . import synth
 
 
 MAX_PYRAMIDS = 16
+ARENA_CACHED = 224 << 20    # bytes of an arena that the last cache level (256 MB) holds beside weights and input
 
 
 class _Plan:
@@ -85,18 +86,31 @@ class _Plan:
                 arena_ops.append((i, max(readers.get(i, [i])), int(np.prod(shape)) * dtype.itemsize))
         self.calls = (B.Call * n)(*calls)
         self.slots = (ctypes.c_void_p * len(table))(*table)
-        # first fit, in the order the ops run: live from an op's own call to its last reader's
-        placed, self.in_arena, self.arena_bytes = [], [], 0
-        for i, last, size in arena_ops:
-            size = -(-size // 256) * 256
-            at = 0
-            for p_at, p_size in sorted((a, sz) for a, sz, p_last in placed if p_last >= i):
-                if at + size <= p_at:
-                    break
-                at = max(at, p_at + p_size)
-            placed.append((at, size, last))
-            self.in_arena.append((out_slot[i], at))
-            self.arena_bytes = max(self.arena_bytes, at + size)
+        # A range is given out again some ops after its tensor's last reader while the arena stays inside the
+        # chip's last cache level: writing over what the ops just before have read or written costs (MobileNetV2,
+        # batch 32: 425 us with ranges reused at once, 401 us six ops later).  A larger arena is packed tightly
+        # (ResNet-50 on 12 frames of 100 x 100: 711 us tight in 153 MB, 735 us in 322 MB).
+        for rest in (12, 8, 6, 4, 2, 0):
+            offsets, self.arena_bytes = _place(arena_ops, rest)
+            if self.arena_bytes <= ARENA_CACHED:
+                break
+        self.in_arena = [(out_slot[i], at) for (i, _, _), at in zip(arena_ops, offsets)]
+
+
+def _place(tensors, rest: int):
+    """Offsets for (op, op of the last reader, bytes), and the bytes in all: first fit, in the order the ops run; a
+    range is taken from its tensor's own op to `rest` ops after the last reader's."""
+    placed, total = [], 0
+    for i, last, size in tensors:
+        size = -(-size // 256) * 256
+        at = 0
+        for p_at, p_size in sorted((a, sz) for a, sz, p_last in placed if p_last >= i - rest):
+            if at + size <= p_at:
+                break
+            at = max(at, p_at + p_size)
+        placed.append((at, size, last))
+        total = max(total, at + size)
+    return [at for at, _, _ in placed], total
 
 
 class ConvStack:
