@@ -414,7 +414,11 @@ __global__ __launch_bounds__(WM *WN * 64, MINW) void k_conv_dma(Geom g, const ui
         // set-up B: one thread per (row, tap) decides "inside the image and relevant" (for a
         // masked layer it fetches the mask byte under the tap; all of a thread's bytes are in
         // flight together)
-        for (int i0 = 0; i0 < ((use_halo || self_tap) ? 0 : PAIR_IT); i0 += PAIR_CH) {
+        // (any kernel size: a loop over as many pairs as there are, kept rolled - unrolled it took the registers
+        // of the whole kernel)
+        const int pair_it = TAPC == 32 ? (TM * taps + NT - 1) / NT : PAIR_IT;
+#pragma unroll(TAPC == 32 ? 1 : PAIR_IT)
+        for (int i0 = 0; i0 < ((use_halo || self_tap) ? 0 : pair_it); i0 += PAIR_CH) {
             int prow_[PAIR_CH], ptap_[PAIR_CH], ppix_[PAIR_CH];
             bool pin_[PAIR_CH];
 #pragma unroll

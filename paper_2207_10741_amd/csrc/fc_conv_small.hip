@@ -40,12 +40,17 @@ struct SmallCut {
 };
 
 // Splits of every tile's reduction when `rows` rows are kept: for 3x3 kernels the tiled kernel's rule for its
-// 64 x 64 tiles; the others never ran there on such tiles and are cut for the waves of one workgroup.
+// 64 x 64 tiles (which splits nothing without a workspace: 384 -> 48 on 4 x 26 x 14, 54 stages in one wave, 22.0 us, in
+// four 9.8 us); the others never ran there on such tiles and are cut for the waves of one workgroup.
 __host__ __device__ static inline int small_splits(int rows, int c_out, int stages, int taps, bool room)
 {
     if (taps != 9) return stages >= 4 * kSmallWaves ? kSmallWaves : 1;
     const int ntiles = ((rows + 63) / 64) * ((c_out + 63) / 64);
-    return room && ntiles > 0 ? split_k_splits(ntiles, kSplitGrid, stages, stages) : 1;
+    if (!room) { // no workspace to meet in: the waves of a workgroup
+        const int cap = stages / kMinSplitStages;
+        return cap < 1 ? 1 : (cap < kSmallWaves ? cap : kSmallWaves);
+    }
+    return ntiles > 0 ? split_k_splits(ntiles, kSplitGrid, stages, stages) : 1;
 }
 
 template <int DT, typename TO>
