@@ -413,17 +413,29 @@ hipError_t launch_conv_f32(const Geom &g, const void *x, const uint8_t *mask_in,
 // ---------------------------------------------------------------------------------------------
 // Grouped layers of 16-bit storage.  Bound: HBM / L2 (x read, out written).
 //
-// A wave owns 16 output channels; the groups they belong to read a window of IC input channels
-// (16 / cog groups of cig channels, or the one group the block lies in).  The reduction of the
-// block is taps x IC, cut into pieces of 8 channels of one tap; four pieces make one
-// v_mfma_f32_16x16x32: lane (column, quarter) holds piece 4 s + quarter, for the weights of output
-// channel `column` (zero outside its own group: the block-diagonal part costs nothing but
-// matrix slots, of which there are plenty) and for the pixel of position `column`.  The weights
-// of the block stay in registers for all rows of the span; a row tile is 16 positions, its loads
-// issued a tile ahead.  The four waves of a workgroup take neighbouring channel blocks, so
-// that together they read whole 128-byte lines.
-// (128 channels in 32 groups, 16 x 56 x 56, 48 % irrelevant: 49 us on the vector ALUs, 9 us
-// of compaction and 5 us of zero-fill around it.)
+// An output channel's products hold its own group's inputs and nothing else: a foreign input times a
+// zero weight would be NaN where that input is infinite or NaN.
+//
+// 16 channels per group and more (k_conv_grouped): a wave owns 16 output channels of one group.  The
+// reduction is taps x input channels of the group, cut into pieces of 8 channels of one tap; four pieces
+// make one v_mfma_f32_16x16x32: lane (column, quarter) holds piece 4 s + quarter, for the weights of output
+// channel `column` and for the pixel of position `column`.  The weights of the block stay in registers for all
+// rows of the span; a row tile is 16 positions, its loads issued a tile ahead.  The four waves of a workgroup
+// take neighbouring channel blocks.
+//
+// 4 or 8 channels per group (k_conv_grouped_quads): v_mfma_f32_4x4x4_16b multiplies sixteen independent 4 x 4
+// blocks.  A block is four output channels of one group at four positions, so a wave covers 64 channels of
+// four positions per instruction and 4 input channels of one tap; lane (block, j) holds output
+// channel 4 block + j of the weights and position j of the pixels, and ends with its block's four channels
+// at position j.  Nothing is multiplied for padding, and the rate (1/4 of the large instructions') is still far
+// from being the bound: 4 -> 4 channels on 16 x 56 x 56, half kept, is 0.4 us of them.  The halves of an
+// 8-channel piece are summed apart and added at the end (as one chain the error of 8 -> 8 f16 channels against 64-bit
+// sums is 7.4e-8 of the result, so 6.1e-8; products of 32 elements had 5.8e-8).  The four waves of a workgroup take the
+// quads of rows in turn.
+// (With a mask / without one / with a list and no zero-fill, us: 128 channels in 32 groups on 16 x 56 x 56 12.6 / 12.8 /
+// 13.1, and at stride 2 9.2 / 8.4 / 8.8; 256 in 32 groups 22.4 / 25.2 / 23.1.  16-channel products with zero weights for the
+// foreign groups, which mixed groups as said above: 12.9 / 13.8 / 15.0, 10.0 / 9.6 / 9.9, 22.8 / 23.8 / 26.2.  On the vector
+// ALUs, with a compaction and a zero-fill launch, the first of these was 61 us.)
 // ---------------------------------------------------------------------------------------------
 template <int DT>
 __device__ __forceinline__ f32x4_t mfma16(const u32x4_t &a, const u32x4_t &b, const f32x4_t &c)
@@ -434,6 +446,25 @@ __device__ __forceinline__ f32x4_t mfma16(const u32x4_t &a, const u32x4_t &b, co
     else
         return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, a), __builtin_bit_cast(f16x8_t, b), c, 0,
                                                       0, 0);
+}
+
+// sixteen independent products of 4 x 4 x 4: lane (block, j) holds row j of `a` and column j of `b`, four elements each
+template <int DT>
+__device__ __forceinline__ f32x4_t mfma4(const uint2 &a, const uint2 &b, const f32x4_t &c)
+{
+    if constexpr (DT == FC_BF16) {
+        typedef short i16x4_t __attribute__((ext_vector_type(4)));
+        return __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(__builtin_bit_cast(i16x4_t, a), __builtin_bit_cast(i16x4_t, b), c, 0, 0, 0);
+    } else {
+        typedef _Float16 f16x4_t __attribute__((ext_vector_type(4)));
+        return __builtin_amdgcn_mfma_f32_4x4x4f16(__builtin_bit_cast(f16x4_t, a), __builtin_bit_cast(f16x4_t, b), c, 0, 0, 0);
+    }
+}
+
+__device__ __forceinline__ void relu4(f32x4_t &v)
+{
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = !(v[i] > 0.f) ? (v[i] != v[i] ? v[i] : 0.f) : v[i];
 }
 
 // g: the whole layer (all groups); cig / cog: channels of one group; KS: matrix steps
@@ -451,9 +482,8 @@ __global__ __launch_bounds__(kRegThreads, KS > 9 ? 1 : 2) void k_conv_grouped(
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, col = lane & 15, quarter = lane >> 4;
     const int co0 = (blockIdx.y * 4 + wave) * 16;
     const int taps = g.kh * g.kw;
-    const int ic = cog >= 16 ? cig : (16 / cog) * cig; // channels of the block's window
-    const int win0 = (co0 / cog) * cig;
-    const int ppt = ic >> 3; // pieces per tap
+    const int win0 = (co0 / cog) * cig; // first input channel of the block's group
+    const int ppt = cig >> 3;           // pieces per tap
 
     // this lane's part of the block's weights, and where its pieces lie in a pixel's neighbourhood
     // (loaded first: they are on their way while the rows are set up)
@@ -464,7 +494,6 @@ __global__ __launch_bounds__(kRegThreads, KS > 9 ? 1 : 2) void k_conv_grouped(
     uint32_t xsel[KS];// its tap's bit
     {
         const int co = co0 + col;
-        const int wch = (co / cog) * cig; // first input channel of this output channel's group
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
             const int q = s * 4 + quarter;
@@ -472,15 +501,8 @@ __global__ __launch_bounds__(kRegThreads, KS > 9 ? 1 : 2) void k_conv_grouped(
             const int kh = (int)((uint32_t)tap / (uint32_t)g.kw), kw = tap - kh * g.kw;
             xo[s] = ((kh * g.dh * g.w + kw * g.dw) * g.c_in + win0 + pc * 8) * 2;
             xsel[s] = tap < taps ? 1u << tap : 0u;
-#pragma unroll
-            for (int hf = 0; hf < 2; ++hf) {
-                const int local = win0 + pc * 8 + hf * 4 - wch;
-                const bool ok = tap < taps && co < g.c_out && local >= 0 && local < cig;
-                const auto v = __builtin_amdgcn_raw_buffer_load_b64(
-                    rw, ok ? (uint32_t)((co * taps + tap) * cig + local) * 2u : kOutOfRange, 0, 0);
-                wf[s][2 * hf] = v[0];
-                wf[s][2 * hf + 1] = v[1];
-            }
+            wf[s] = __builtin_amdgcn_raw_buffer_load_b128(
+                rw, tap < taps && co < g.c_out ? (uint32_t)((co * taps + tap) * cig + pc * 8) * 2u : kOutOfRange, 0, 0);
         }
     }
     int n, nd;
@@ -510,9 +532,7 @@ __global__ __launch_bounds__(kRegThreads, KS > 9 ? 1 : 2) void k_conv_grouped(
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int s = 0; s < KS; ++s) acc = mfma16<DT>(wf[s], xv[st][s], acc);
-        if (g.flags & FC_RELU)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) acc[i] = !(acc[i] > 0.f) ? (acc[i] != acc[i] ? acc[i] : 0.f) : acc[i];
+        if (g.flags & FC_RELU) relu4(acc);
         if (r < n)
             store4<DT, TO>(out + (int64_t)rows_s.p[r] * g.c_out + co0 + quarter * 4, acc[0], acc[1], acc[2], acc[3]);
     };
@@ -529,14 +549,164 @@ __global__ __launch_bounds__(kRegThreads, KS > 9 ? 1 : 2) void k_conv_grouped(
     }
 }
 
-// The same layer where output positions are input pixels (unit stride, same size) and there is no list.
-// The kernel above spends most of its time on addresses: a lane's pieces lie in other lines than its
-// neighbours', 64 cycles of the address unit per load, for the weights of a block as for the pixels.
+// 4 or 8 channels per group.  A lane's weights are one run of taps x cig elements (channel blk0 + lane), staged with the
+// workgroup's other channels as one block through LDS; its pixels are taps x cig elements in loads of V
+// times four channels: NL >= taps * cig / (4 V) loads (NL = 9: cig = 4 V only).
+template <int DT, typename TO, int V, int NL>
+__global__ __launch_bounds__(kRegThreads, V * NL > 36 ? 1 : 2) void k_conv_grouped_quads(
+    Geom g, int cig, int cog, const uint16_t *__restrict__ x, const uint8_t *__restrict__ mask_in,
+    const uint8_t *__restrict__ mask_out, const uint16_t *__restrict__ w, const float *__restrict__ bias,
+    const int32_t *__restrict__ idx, const int32_t *__restrict__ count, TO *__restrict__ out)
+{
+    constexpr int S = kGroupedSpan;
+    constexpr int NB = V * NL > 36 ? 1 : 2; // quads whose pixels are held
+    constexpr bool ONE = NL == 9;           // one load per tap (cig == 4 V)
+    extern __shared__ __align__(16) unsigned char lds[]; // weights
+    __shared__ SpanRows rows_s;
+    const int rows = idx ? *count : g.m;
+    const int first = blockIdx.x * S;
+    if (first >= rows) return;
+    const int tid = threadIdx.x, lane = tid & 63, j = lane & 3, blk0 = blockIdx.y * 64;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int taps = g.kh * g.kw;
+    // byte offsets of the taps, kept in scalar registers where a tap is one load (what a quad costs is the instructions
+    // of its addresses)
+    uint32_t tap_at[ONE ? NL : 1];
+    if constexpr (ONE) {
+        int kw = 0;
+        uint32_t row = 0;
+#pragma unroll
+        for (int s = 0; s < NL; ++s) {
+            tap_at[s] = s < taps ? row + (uint32_t)(kw * g.dw * g.c_in) * 2u : 0u;
+            if (++kw == g.kw) {
+                kw = 0;
+                row += (uint32_t)(g.dh * g.w * g.c_in) * 2u;
+            }
+        }
+    }
+    {
+        const u32x4_t rsrc_w = make_rsrc_words(w, (uint32_t)g.c_out * taps * cig * 2u);
+        const uint32_t at = (uint32_t)(blk0 * taps * cig) * 2u, bytes = (uint32_t)(64 * taps * cig) * 2u;
+        const uint32_t lds0 = (uint32_t)reinterpret_cast<uintptr_t>(lds);
+        for (uint32_t o = (uint32_t)wave * 1024u; o < bytes; o += 4096u) // (the block's size is rounded up to 1 KB)
+            dma_load16(rsrc_w, at + o + (uint32_t)lane * 16u, __builtin_amdgcn_readfirstlane(lds0 + o));
+    }
+    int n, nd;
+    span_rows<S>(g, mask_in, mask_out, idx, rows, first, rows_s, &n, &nd);
+    if (nd && !(g.flags & FC_SKIP_ZERO_FILL))
+        clear_dropped<TO>(rows_s, nd, out, g.c_out, blk0, min(64, g.c_out - blk0));
+    wait_vmcnt<0>();
+    __syncthreads();
+    if (n == 0) return;
+
+    const int co = blk0 + (lane & ~3); // the block's channels co .. co + 3, all of one group
+    uint2 wf[NL][V];
+#pragma unroll
+    for (int s = 0; s < NL; ++s)
+#pragma unroll
+        for (int v = 0; v < V; ++v)
+            wf[s][v] = s * V * 4 < taps * cig ? *reinterpret_cast<const uint2 *>(lds + (lane * taps * cig + (s * V + v) * 4) * 2)
+                                              : make_uint2(0u, 0u);
+    // (x through a descriptor that starts a padding's worth earlier, see k_conv_f32: a tap's offset is then a scalar)
+    const uint32_t xbias = (uint32_t)(g.ph * g.w + g.pw) * (uint32_t)g.c_in * 2u;
+    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint16_t *>(x) - xbias / 2, 0, (uint32_t)g.n * g.h * g.w * g.c_in * 2u + xbias, 0x00020000);
+    float4 bq = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (bias && co < g.c_out) bq = *reinterpret_cast<const float4 *>(bias + co);
+    // Pixels are loaded with neighbouring lanes on neighbouring channels - lane 16 row + block, whole lines of four rows
+    // (lanes 4 block + row, as the products take them, are 64 lines to the address unit: 22.0 us for 4 -> 4 channels on 16 x 56 x 56, half kept, where this takes 13.1)
+    // - and change lanes on their way to the product.
+    const int load_block = lane & 15, load_co = blk0 + load_block * 4;
+    const uint32_t group_off = (uint32_t)(load_co / cog * cig) * 2u;
+    const int from_lane = (j * 16 + (lane >> 2)) * 4;
+    auto to_block = [&](const uint2 &v) __attribute__((always_inline)) {
+        return make_uint2((uint32_t)__builtin_amdgcn_ds_bpermute(from_lane, (int)v.x),
+                          (uint32_t)__builtin_amdgcn_ds_bpermute(from_lane, (int)v.y));
+    };
+    uint2 xv[NB][NL][V];
+    auto load = [&](auto set_c, int quad) __attribute__((always_inline)) {
+        constexpr int st = decltype(set_c)::value;
+        const int r = quad + (lane >> 4);
+        const bool live = r < n && load_co < g.c_out; // (n <= kMaxSpan; r may point past it)
+        const uint32_t base = live ? (uint32_t)rows_s.base[r] * (uint32_t)g.c_in * 2u + xbias + group_off : 0u;
+        const uint32_t bits = live ? rows_s.bits[0][r] : 0u;
+        auto fetch = [&](int s, int tap, uint32_t at) __attribute__((always_inline)) {
+            const uint32_t on = tap < taps ? (uint32_t)__builtin_amdgcn_sbfe((int)bits, (uint32_t)tap, 1) : 0u;
+            const uint32_t off = (base & on) | (kOutOfRange & ~on);
+            if constexpr (V == 1) {
+                const auto t = __builtin_amdgcn_raw_buffer_load_b64(rx, off, at, 0);
+                xv[st][s][0] = make_uint2(t[0], t[1]);
+            } else {
+                const auto t = __builtin_amdgcn_raw_buffer_load_b128(rx, off, at, 0);
+                xv[st][s][0] = make_uint2(t[0], t[1]);
+                xv[st][s][1] = make_uint2(t[2], t[3]);
+            }
+        };
+        if constexpr (ONE) {
+#pragma unroll
+            for (int s = 0; s < NL; ++s) fetch(s, s, tap_at[s]);
+        } else {
+            int tap = 0, kw = 0, sub = 0; // of the load (the same for all lanes)
+            uint32_t row = 0;             // byte offset of the tap's kernel row
+#pragma unroll
+            for (int s = 0; s < NL; ++s) {
+                fetch(s, tap, tap < taps ? row + (uint32_t)(kw * g.dw * g.c_in + sub) * 2u : 0u);
+                sub += 4 * V;
+                if (sub == cig) {
+                    sub = 0;
+                    ++tap;
+                    if (++kw == g.kw) {
+                        kw = 0;
+                        row += (uint32_t)(g.dh * g.w * g.c_in) * 2u;
+                    }
+                }
+            }
+        }
+    };
+    auto multiply = [&](auto set_c, int quad) __attribute__((always_inline)) {
+        constexpr int st = decltype(set_c)::value;
+        const int r = quad + j;
+        f32x4_t sum[2] = {{bq.x, bq.y, bq.z, bq.w}, {0.f, 0.f, 0.f, 0.f}};
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = 0; s < NL; ++s)
+#pragma unroll
+            for (int v = 0; v < V; ++v) sum[v] = mfma4<DT>(wf[s][v], to_block(xv[st][s][v]), sum[v]);
+        f32x4_t acc = V == 1 ? sum[0] : sum[0] + sum[1];
+        if (g.flags & FC_RELU) relu4(acc);
+        if (r < n && co < g.c_out) store4<DT, TO>(out + (int64_t)rows_s.p[r] * g.c_out + co, acc[0], acc[1], acc[2], acc[3]);
+    };
+    using C0 = std::integral_constant<int, 0>;
+    using C1 = std::integral_constant<int, NB - 1>;
+    const int r0 = wave * 4; // wave v: quads v, v + 4, ...
+    if constexpr (NB == 1) {
+        for (int r = r0; r < n; r += 16) {
+            load(C0{}, r);
+            multiply(C0{}, r);
+        }
+    } else {
+        load(C0{}, r0);
+        for (int r = r0; r < n; r += 32) {
+            load(C1{}, r + 16);
+            multiply(C0{}, r);
+            if (r + 16 >= n) break;
+            load(C0{}, r + 32);
+            multiply(C1{}, r + 16);
+        }
+    }
+}
+
+// The same layers where output positions are input pixels (unit stride, same size) and there is no list.
+// The kernels above spend much of their time on addresses and on waiting for gathers one quad or tile ahead.
 // Here the pixels under a span of 64 consecutive positions are, for every kernel row, one run of
 // 64 + (kw - 1) dil_w consecutive pixels: they are staged in LDS once (whole 128-byte pieces of 64 output
 // channels' groups), the workgroup's weights likewise, and all operands come from there; a gated tap
-// reads a piece of zeros.  (128 channels in 32 groups on 16 x 56 x 56, half kept: 16.6 us above.)
+// reads a piece of zeros.  V = 0: blocks of 16 channels, KS matrix steps.  V = 1, 2: quads of rows, 3x3 kernels and 4 V
+// input channels per group, so that a tap is one read; everything about the reads is fixed when the kernel is compiled
+// (a pixel's pieces 1 << LG, its kernel row's line), because what a quad costs is the instructions of its addresses: with
+// the line's length and the taps at run time the kernel took 17.8 us where it now takes 12.5 (4 -> 4 channels on 16 x 56 x 56, half kept).
 constexpr int kWindowSpan = 64;
+constexpr int kQuadLine = kWindowSpan + 4; // pixel slots of a line: one of zeros, 66 pixels, one to make four divide it
 struct WindowCut {
     int32_t line;      // pixels of a kernel row's run
     int32_t lg_pieces; // log2 of the 16-byte pieces of a pixel's window
@@ -544,7 +714,7 @@ struct WindowCut {
     FastDiv by_line, by_kw, by_ppt;
 };
 
-template <int DT, typename TO, int KS>
+template <int DT, typename TO, int V, int KS, int LG>
 __global__ __launch_bounds__(kRegThreads, 2) void k_conv_grouped_window(
     Geom g, WindowCut cut, int cig, int cog, const uint16_t *__restrict__ x, const uint8_t *__restrict__ mask_in,
     const uint8_t *__restrict__ mask_out, const uint16_t *__restrict__ w, const float *__restrict__ bias,
@@ -561,6 +731,10 @@ __global__ __launch_bounds__(kRegThreads, 2) void k_conv_grouped_window(
     const int first = blockIdx.x * kWindowSpan, blk0 = blockIdx.y * 64, co0 = blk0 + wave * 16;
     const int taps = g.kh * g.kw;
     const int win0 = (blk0 / cog) * cig; // first input channel of the workgroup's groups
+    const int lg_pieces = V ? LG : cut.lg_pieces, line = V ? kQuadLine : cut.line;
+    // Sixteen lanes that read one piece of sixteen neighbouring pixels, or a few pieces each of the four pixels of a quad,
+    // meet in different banks (two pixels of 128 bytes, or one of 256, fill all of them).
+    auto swizzle = [&](int q) { return V == 0 ? q >> 1 : (LG == 4 ? q : q >> 1) << 2; };
 
     // ---- weights: one contiguous block ----
     {
@@ -583,15 +757,16 @@ __global__ __launch_bounds__(kRegThreads, 2) void k_conv_grouped_window(
         if (lane < 4) reinterpret_cast<uint32_t *>(zero_s)[lane] = 0u;
     }
     if (n > 0) {
-        // ---- pixels: LDS piece c of pixel slot q holds the window's piece c ^ (q >> 1) ----
-        const int pieces = 1 << cut.lg_pieces;
+        // ---- pixels: LDS piece c of pixel slot q holds the window's piece c ^ swizzle(q) ----
+        const int pieces = 1 << lg_pieces;
         const u32x4_t rsrc_x = make_rsrc_words(x, (uint32_t)g.n * g.h * g.w * g.c_in * 2u);
-        const int npix = g.n * g.h * g.w, slots = g.kh * cut.line;
-        for (int o = wave * 64; o < (slots << cut.lg_pieces); o += kRegThreads) {
-            const int i = o + lane, q = i >> cut.lg_pieces, c = (i ^ (q >> 1)) & (pieces - 1);
-            const int k = (int)fast_div((uint32_t)q, cut.by_line), t = q - k * cut.line;
+        const int npix = g.n * g.h * g.w, slots = g.kh * line;
+        for (int o = wave * 64; o < (slots << lg_pieces); o += kRegThreads) {
+            const int i = o + lane, q = i >> lg_pieces, c = (i ^ swizzle(q)) & (pieces - 1);
+            const int k = V ? (int)((uint32_t)q / (uint32_t)kQuadLine) : (int)fast_div((uint32_t)q, cut.by_line);
+            const int t = q - k * line - (V ? 1 : 0);
             const int pix = first + (k * g.dh - g.ph) * g.w - g.pw + t, ch = win0 + c * 8;
-            const bool ok = q < slots && pix >= 0 && pix < npix && ch < g.c_in;
+            const bool ok = q < slots && t >= 0 && pix >= 0 && pix < npix && ch < g.c_in;
             dma_load16(rsrc_x, ok ? (uint32_t)(pix * g.c_in + ch) * 2u : kOutOfRange,
                        __builtin_amdgcn_readfirstlane(lds0 + (uint32_t)o * 16u));
         }
@@ -629,58 +804,110 @@ __global__ __launch_bounds__(kRegThreads, 2) void k_conv_grouped_window(
             __builtin_nontemporal_store(zero, reinterpret_cast<u32x4_t *>(out + row) + c);
         }
     }
-    if (co0 >= g.c_out || n == 0) return;
-
-    // ---- this wave's 16 channels: weights from LDS to registers, and where their pieces lie ----
-    const int ic = cog >= 16 ? cig : (16 / cog) * cig, ppt = ic >> 3;
-    const int bw0 = (co0 / cog) * cig;             // first input channel of the block's groups
-    const int co = co0 + col, wch = (co / cog) * cig;
-    u32x4_t wf[KS];
-    int xq[KS];        // pixel slot of the piece from the position's own slot
-    uint32_t xc[KS], xsel[KS];
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-        const int q = s * 4 + quarter;
-        const int tap = (int)fast_div((uint32_t)q, cut.by_ppt), pc = q - tap * ppt;
-        const int kh = (int)fast_div((uint32_t)tap, cut.by_kw), kw = tap - kh * g.kw;
-        xq[s] = kh * cut.line + kw * g.dw;
-        xc[s] = (uint32_t)((bw0 - win0) >> 3) + (uint32_t)pc;
-        xsel[s] = tap < taps ? 1u << tap : 0u;
-#pragma unroll
-        for (int hf = 0; hf < 2; ++hf) {
-            const int local = bw0 + pc * 8 + hf * 4 - wch;
-            const bool ok = tap < taps && local >= 0 && local < cig;
-            const uint2 v = ok ? *reinterpret_cast<const uint2 *>(w_s + (((co - blk0) * taps + tap) * cig + local) * 2) : make_uint2(0, 0);
-            wf[s][2 * hf] = v.x;
-            wf[s][2 * hf + 1] = v.y;
-        }
-    }
-    float4 bq = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (bias) bq = *reinterpret_cast<const float4 *>(bias + co0 + quarter * 4);
-    const uint32_t zero_at = (uint32_t)(cut.x_bytes + cut.w_bytes), pmask = (1u << cut.lg_pieces) - 1u;
-    for (int r0 = 0; r0 < n; r0 += 16) {
-        const bool live = r0 + col < n;
-        const int j = live ? order_s[r0 + col] : 0;
-        const uint32_t bits = live ? bits_s[j] : 0u;
-        u32x4_t xv[KS];
+    if (n == 0) return;
+    const uint32_t pmask = (1u << lg_pieces) - 1u;
+    if constexpr (V == 0) {
+        const uint32_t zero_at = (uint32_t)(cut.x_bytes + cut.w_bytes);
+        if (co0 >= g.c_out) return;
+        // ---- this wave's 16 channels: weights from LDS to registers, and where their pieces lie ----
+        const int ppt = cig >> 3;
+        const int bw0 = (co0 / cog) * cig; // first input channel of the block's group
+        const int co = co0 + col;
+        u32x4_t wf[KS];
+        int xq[KS];        // pixel slot of the piece from the position's own slot
+        uint32_t xc[KS], xsel[KS];
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
-            const uint32_t q = (uint32_t)(j + xq[s]);
-            const uint32_t at = ((q << cut.lg_pieces) + ((xc[s] ^ (q >> 1)) & pmask)) * 16u;
-            xv[s] = *reinterpret_cast<const u32x4_t *>(lds + ((bits & xsel[s]) ? at : zero_at));
+            const int q = s * 4 + quarter;
+            const int tap = (int)fast_div((uint32_t)q, cut.by_ppt), pc = q - tap * ppt;
+            const int kh = (int)fast_div((uint32_t)tap, cut.by_kw), kw = tap - kh * g.kw;
+            xq[s] = kh * cut.line + kw * g.dw;
+            xc[s] = (uint32_t)((bw0 - win0) >> 3) + (uint32_t)pc;
+            xsel[s] = tap < taps ? 1u << tap : 0u;
+            const u32x4_t zero = {0u, 0u, 0u, 0u};
+            wf[s] = tap < taps ? *reinterpret_cast<const u32x4_t *>(w_s + (((co - blk0) * taps + tap) * cig + pc * 8) * 2) : zero;
         }
-        f32x4_t acc = {bq.x, bq.y, bq.z, bq.w};
+        float4 bq = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (bias) bq = *reinterpret_cast<const float4 *>(bias + co0 + quarter * 4);
+        for (int r0 = 0; r0 < n; r0 += 16) {
+            const bool live = r0 + col < n;
+            const int j = live ? order_s[r0 + col] : 0;
+            const uint32_t bits = live ? bits_s[j] : 0u;
+            u32x4_t xv[KS];
 #pragma unroll
-        for (int s = 0; s < KS; ++s) acc = mfma16<DT>(wf[s], xv[s], acc);
-        if (g.flags & FC_RELU)
+            for (int s = 0; s < KS; ++s) {
+                const uint32_t q = (uint32_t)(j + xq[s]);
+                const uint32_t at = ((q << cut.lg_pieces) + ((xc[s] ^ (uint32_t)swizzle((int)q)) & pmask)) * 16u;
+                xv[s] = *reinterpret_cast<const u32x4_t *>(lds + ((bits & xsel[s]) ? at : zero_at));
+            }
+            f32x4_t acc = {bq.x, bq.y, bq.z, bq.w};
 #pragma unroll
-            for (int i = 0; i < 4; ++i) acc[i] = !(acc[i] > 0.f) ? (acc[i] != acc[i] ? acc[i] : 0.f) : acc[i];
-        if (live)
-            store4<DT, TO>(out + (int64_t)(first + j) * g.c_out + co0 + quarter * 4, acc[0], acc[1], acc[2], acc[3]);
+            for (int s = 0; s < KS; ++s) acc = mfma16<DT>(wf[s], xv[s], acc);
+            if (g.flags & FC_RELU) relu4(acc);
+            if (live)
+                store4<DT, TO>(out + (int64_t)(first + j) * g.c_out + co0 + quarter * 4, acc[0], acc[1], acc[2], acc[3]);
+        }
+    } else {
+        // ---- lane (block, j): the weights of channel blk0 + lane, and the pixels of row j of a quad ----
+        constexpr uint32_t PIX = 16u << LG, LINE = kQuadLine * PIX; // bytes
+        const int j = lane & 3, co = blk0 + (lane & ~3);
+        uint2 wf[9][V];
+#pragma unroll
+        for (int s = 0; s < 9; ++s)
+#pragma unroll
+            for (int v = 0; v < V; ++v) wf[s][v] = *reinterpret_cast<const uint2 *>(w_s + (lane * 9 + s) * 8 * V + v * 8);
+        float4 bq = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (bias && co < g.c_out) bq = *reinterpret_cast<const float4 *>(bias + co);
+        const uint32_t in_pixel = (uint32_t)((co / cog) * cig - win0) * 2u; // the block's group in a pixel
+        TO *const o = out + (int64_t)first * g.c_out + co;
+        // wave v: quads v, v + 4, ... of the kept rows
+        int row[kWindowSpan / 16];
+        uint32_t bits[kWindowSpan / 16];
+#pragma unroll
+        for (int u = 0; u < kWindowSpan / 16; ++u) row[u] = order_s[wave * 4 + u * 16 + j];
+#pragma unroll
+        for (int u = 0; u < kWindowSpan / 16; ++u) {
+            const bool live = wave * 4 + u * 16 + j < n && co < g.c_out;
+            bits[u] = bits_s[row[u] & (kWindowSpan - 1)];
+            row[u] = live ? row[u] : -1;
+            bits[u] = live ? bits[u] : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < kWindowSpan / 16; ++u) {
+            if (wave * 4 + u * 16 >= n) break;
+            // a tap that is off reads its line's slot of zeros
+            uint2 xv[9][V];
+#pragma unroll
+            for (int kw = 0; kw < 3; ++kw) {
+                const uint32_t q = (uint32_t)(row[u] + 1 + kw);
+                const uint32_t at = q * PIX + (((in_pixel >> 4) ^ (uint32_t)swizzle((int)q)) & pmask) * 16u + (in_pixel & 15u);
+#pragma unroll
+                for (int kh = 0; kh < 3; ++kh) {
+                    const uint32_t on = (uint32_t)__builtin_amdgcn_sbfe((int)bits[u], kh * 3 + kw, 1);
+                    const unsigned char *from = lds + (at & on) + kh * LINE;
+                    if constexpr (V == 1) {
+                        xv[kh * 3 + kw][0] = *reinterpret_cast<const uint2 *>(from);
+                    } else {
+                        const uint4 t = *reinterpret_cast<const uint4 *>(from);
+                        xv[kh * 3 + kw][0] = make_uint2(t.x, t.y);
+                        xv[kh * 3 + kw][1] = make_uint2(t.z, t.w);
+                    }
+                }
+            }
+            f32x4_t sum[2] = {{bq.x, bq.y, bq.z, bq.w}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+            for (int s = 0; s < 9; ++s)
+#pragma unroll
+                for (int v = 0; v < V; ++v) sum[v] = mfma4<DT>(wf[s][v], xv[s][v], sum[v]);
+            f32x4_t acc = V == 1 ? sum[0] : sum[0] + sum[1];
+            if (g.flags & FC_RELU) relu4(acc);
+            if (row[u] >= 0) store4<DT, TO>(o + row[u] * g.c_out, acc[0], acc[1], acc[2], acc[3]);
+        }
     }
 }
 
-// matrix steps of a 16-channel block's reduction
+// The reduction of a 16-channel block, or of as many channels as make one, in 32-element steps: the measure of the weights
+// a lane holds
 static int grouped_steps(const Geom &g, int cig, int cog)
 {
     const int ic = cog >= 16 ? cig : (16 / cog) * cig;
@@ -692,13 +919,16 @@ bool conv_grouped_supported(const Geom &g, int groups, int in_dtype, int out_dty
     if (in_dtype != FC_BF16 && in_dtype != FC_F16) return false;
     if (out_dtype != in_dtype && out_dtype != FC_F32) return false;
     const int cig = g.c_in / groups, cog = g.c_out / groups;
-    // whole 16-channel blocks that do not cut a group boundary; windows of whole 16-byte pieces
+    // quads of channels inside a group with whole 8-byte pieces of its inputs, or 16-channel blocks inside a group with
+    // whole 16-byte pieces (one or two channels per group: a quad would mix groups, the direct kernel keeps them apart)
     if (g.c_out % 16 != 0 || g.c_in % 8 != 0 || cig % 4 != 0) return false;
-    if (cog < 16 ? 16 % cog != 0 : cog % 16 != 0) return false;
-    if ((cog >= 16 ? cig : (16 / cog) * cig) % 8 != 0) return false;
+    if (cog != 4 && cog != 8 && (cog % 16 != 0 || cig % 8 != 0)) return false;
     if (g.kh * g.kw > 32 || grouped_steps(g, cig, cog) > 18) return false; // tap bits; weights in registers
     if (g.h > 16384 || g.w > 16384 || g.ph > 8192 || g.pw > 8192) return false;
-    return (uint64_t)g.n * g.h * g.w * g.c_in * 2u < kBufferLimit && (uint64_t)g.c_out * g.kh * g.kw * cig * 2u < kBufferLimit;
+    // (quads read x through a descriptor that starts ph rows and pw pixels early)
+    const uint64_t early = cog < 16 ? (uint64_t)g.ph * g.w + g.pw : 0;
+    return ((uint64_t)g.n * g.h * g.w + early) * g.c_in * 2u < kBufferLimit &&
+           (uint64_t)g.c_out * g.kh * g.kw * cig * 2u < kBufferLimit;
 }
 
 template <int DT, typename TO>
@@ -706,30 +936,46 @@ static hipError_t launch_grouped(const Geom &g, int groups, const void *x, const
                                  const void *w, const float *bias, const int32_t *idx, const int32_t *count, void *out,
                                  hipStream_t s)
 {
-    const int cig = g.c_in / groups, cog = g.c_out / groups;
+    const int cig = g.c_in / groups, cog = g.c_out / groups, taps = g.kh * g.kw, steps = grouped_steps(g, cig, cog);
+    const bool quads = cog < 16;
+    const int v = cig % 8 == 0 ? 2 : 1; // quads: 4-channel pieces of a load
     // spans of positions as windows of pixels: unit stride, same size, no list, groups that do not straddle a
-    // workgroup's 64 channels and whose channels make a power of two of 16-byte pieces, at most 64 KB of LDS
+    // workgroup's 64 channels and whose channels make a power of two of 16-byte pieces, at most 64 KB of LDS; quads: what
+    // their form is compiled for
     const int wch = cog <= 64 && 64 % cog == 0 ? 64 / cog * cig : 0;
     if (!idx && g.sh == 1 && g.sw == 1 && g.ho == g.h && g.wo == g.w && wch >= 32 && wch <= 128 && (wch & (wch - 1)) == 0 &&
-        grouped_steps(g, cig, cog) <= 9) {
+        (quads ? g.kh == 3 && g.kw == 3 && g.dw == 1 && cig == 4 * v : steps <= 9)) {
         WindowCut cut;
-        cut.line = kWindowSpan + (g.kw - 1) * g.dw;
+        cut.line = quads ? kQuadLine : kWindowSpan + (g.kw - 1) * g.dw;
         cut.lg_pieces = wch == 32 ? 2 : (wch == 64 ? 3 : 4);
         cut.x_bytes = (g.kh * cut.line * wch * 2 + 1023) & ~1023;
-        cut.w_bytes = (64 * g.kh * g.kw * cig * 2 + 1023) & ~1023;
+        cut.w_bytes = (64 * taps * cig * 2 + 1023) & ~1023;
         cut.by_line = make_fastdiv((uint32_t)cut.line);
         cut.by_kw = make_fastdiv((uint32_t)g.kw);
-        cut.by_ppt = make_fastdiv((uint32_t)((cog >= 16 ? cig : (16 / cog) * cig) / 8));
+        cut.by_ppt = make_fastdiv((uint32_t)(cig >= 8 ? cig / 8 : 1));
         const int bytes = cut.x_bytes + cut.w_bytes + 16 + kWindowSpan * 5;
         if (bytes <= 64 * 1024) {
-            auto kern = grouped_steps(g, cig, cog) <= 5 ? k_conv_grouped_window<DT, TO, 5> : k_conv_grouped_window<DT, TO, 9>;
+            // (quads: 4 -> 8, 4 -> 4, 8 -> 8, 8 -> 4 channels per group)
+            auto kern = !quads ? (steps <= 5 ? k_conv_grouped_window<DT, TO, 0, 5, 0> : k_conv_grouped_window<DT, TO, 0, 9, 0>)
+                        : v == 1 ? (cog == 8 ? k_conv_grouped_window<DT, TO, 1, 9, 2> : k_conv_grouped_window<DT, TO, 1, 9, 3>)
+                                 : (cog == 8 ? k_conv_grouped_window<DT, TO, 2, 9, 3> : k_conv_grouped_window<DT, TO, 2, 9, 4>);
             hipLaunchKernelGGL(kern, dim3((g.m + kWindowSpan - 1) / kWindowSpan, (g.c_out + 63) / 64), dim3(kRegThreads), bytes, s,
                                g, cut, cig, cog, (const uint16_t *)x, mask_in, mask_out, (const uint16_t *)w, bias, (TO *)out);
             return hipGetLastError();
         }
     }
     const dim3 grid((g.m + kGroupedSpan - 1) / kGroupedSpan, (g.c_out + 63) / 64);
-    const int steps = grouped_steps(g, cig, cog);
+    if (quads) {
+        const int loads = taps * cig / (4 * v), bytes = (64 * taps * cig * 2 + 1023) & ~1023;
+        const bool one = cig == 4 * v && loads <= 9;
+        auto kern = v == 1 ? (one ? k_conv_grouped_quads<DT, TO, 1, 9>
+                                         : (loads <= 36 ? k_conv_grouped_quads<DT, TO, 1, 36> : k_conv_grouped_quads<DT, TO, 1, 72>))
+                           : (one ? k_conv_grouped_quads<DT, TO, 2, 9>
+                                         : (loads <= 18 ? k_conv_grouped_quads<DT, TO, 2, 18> : k_conv_grouped_quads<DT, TO, 2, 36>));
+        hipLaunchKernelGGL(kern, grid, dim3(kRegThreads), bytes, s, g, cig, cog, (const uint16_t *)x, mask_in, mask_out,
+                           (const uint16_t *)w, bias, idx, count, (TO *)out);
+        return hipGetLastError();
+    }
     auto kern = steps <= 5 ? k_conv_grouped<DT, TO, 5> : (steps <= 9 ? k_conv_grouped<DT, TO, 9> : k_conv_grouped<DT, TO, 18>);
     hipLaunchKernelGGL(kern, grid, dim3(kRegThreads), 0, s, g, cig, cog, (const uint16_t *)x, mask_in, mask_out,
                        (const uint16_t *)w, bias, idx, count, (TO *)out);

@@ -136,3 +136,38 @@ def test_grouped_layer_channel_blocks(layer, mask_kind, precomputed):
     out, want, keep = _run(layer, synth.BF16, B.F32, mask_kind=mask_kind, irr=0.4, precomputed=precomputed)
     assert G.rel_err(G.to_f64(out), want, keep) <= TOL_F32_OUT
     assert not out.cpu().numpy()[~keep].view(np.uint32).any()
+
+
+@pytest.mark.parametrize("cig,cog", [(4, 4), (8, 8), (4, 8), (8, 4), (12, 8), (16, 8), (16, 16), (8, 48), (8, 2), (4, 1)])
+@pytest.mark.parametrize("mask_kind,precomputed,stride", [("objects", False, 1), ("objects", True, 1), (None, False, 1),
+                                                          ("bernoulli", False, 2)])
+@pytest.mark.parametrize("dtype,bad", [(synth.F16, (0x7c00, 0x7e00)), (synth.BF16, (0xff80, 0x7fc0))])
+def test_values_that_are_not_finite_stay_in_their_group(cig, cog, mask_kind, precomputed, stride, dtype, bad):
+    """Inf and NaN in every pixel of one group's input: the outputs of the other groups keep their bits."""
+    torch = G.torch_mod()
+    groups, hit = 16, 5
+    n, h, w, ci, co = 1, 11, 13, groups * cig, groups * cog
+    x = synth.activations((n, h, w, ci), dtype, 402, 1)
+    wt = synth.he_weights(co, 3, 3, cig, dtype, 402, 2)
+    mask = None if mask_kind is None else (synth.mask_bernoulli if mask_kind == "bernoulli" else synth.mask_objects)(
+        n, h, w, 0.4, 402, 4)
+    desc = B.conv_desc(n, h, w, ci, co, (3, 3), (stride, stride), (1, 1), (1, 1), dtype, B.F32)
+    md = None if mask is None else G.mask_dev(mask)
+    kw = {}
+    if precomputed:
+        m_out = B.mask_downsample(md, (3, 3), (stride, stride), (1, 1))
+        idx, count = B.active_index_compact(m_out)
+        kw = dict(mask_out=m_out, idx=idx, count=count)
+    run = lambda a: B.focused_gconv2d(desc, groups, G.to_dev(a, dtype), G.to_dev(wt, dtype), None, mask_in=md, **kw).cpu().numpy()
+    clean = run(x)
+    assert np.isfinite(clean).all()
+    spoilt = x.copy()
+    spoilt[..., hit * cig:(hit + 1) * cig - 1] = bad[0]
+    spoilt[..., (hit + 1) * cig - 1] = bad[1]
+    got = run(spoilt)
+    others = [c for c in range(co) if c // cog != hit]
+    np.testing.assert_array_equal(got[..., others].view(np.uint32), clean[..., others].view(np.uint32))
+    keep = np.ones(clean.shape[:3], bool) if mask is None else O.mask_downsample(mask, 3, 3, (stride, stride), (1, 1)) != 0
+    own = got[keep][:, hit * cog:(hit + 1) * cog]
+    assert np.isnan(own).all()      # (every kept position sees its own, relevant pixel)
+    assert not got[~keep].view(np.uint32).any()
