@@ -490,7 +490,7 @@ __global__ __launch_bounds__(kRegThreads, KS > 9 ? 1 : 2) void k_conv_grouped(
     const __amdgpu_buffer_rsrc_t rw =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(w), 0, (uint32_t)g.c_out * taps * cig * 2u, 0x00020000);
     u32x4_t wf[KS];
-    int xo[KS];       // byte offset of the piece from the row's first tap
+    uint32_t xo[KS];  // byte offset of the piece from the row's first tap (of tensors of up to 0xF0000000 bytes)
     uint32_t xsel[KS];// its tap's bit
     {
         const int co = co0 + col;
@@ -499,7 +499,7 @@ __global__ __launch_bounds__(kRegThreads, KS > 9 ? 1 : 2) void k_conv_grouped(
             const int q = s * 4 + quarter;
             const int tap = (int)((uint32_t)q / (uint32_t)ppt), pc = q - tap * ppt;
             const int kh = (int)((uint32_t)tap / (uint32_t)g.kw), kw = tap - kh * g.kw;
-            xo[s] = ((kh * g.dh * g.w + kw * g.dw) * g.c_in + win0 + pc * 8) * 2;
+            xo[s] = (uint32_t)((kh * g.dh * g.w + kw * g.dw) * g.c_in + win0 + pc * 8) * 2u;
             xsel[s] = tap < taps ? 1u << tap : 0u;
             wf[s] = __builtin_amdgcn_raw_buffer_load_b128(
                 rw, tap < taps && co < g.c_out ? (uint32_t)((co * taps + tap) * cig + pc * 8) * 2u : kOutOfRange, 0, 0);
@@ -519,11 +519,11 @@ __global__ __launch_bounds__(kRegThreads, KS > 9 ? 1 : 2) void k_conv_grouped(
     auto load = [&](auto set_c, int r) __attribute__((always_inline)) {
         constexpr int st = decltype(set_c)::value;
         const bool live = r < n; // (n <= kMaxSpan; r may point past it)
-        const int base = live ? rows_s.base[r] * g.c_in * 2 : 0;
+        const uint32_t base = live ? (uint32_t)rows_s.base[r] * (uint32_t)g.c_in * 2u : 0u; // (modulo 2^32 until xo is added)
         const uint32_t bits = live ? rows_s.bits[0][r] : 0u;
 #pragma unroll
         for (int s = 0; s < KS; ++s)
-            xv[st][s] = __builtin_amdgcn_raw_buffer_load_b128(rx, (bits & xsel[s]) ? (uint32_t)(base + xo[s]) : kOutOfRange,
+            xv[st][s] = __builtin_amdgcn_raw_buffer_load_b128(rx, (bits & xsel[s]) ? base + xo[s] : kOutOfRange,
                                                               0, 0);
     };
     auto multiply = [&](auto set_c, int r) __attribute__((always_inline)) {

@@ -171,3 +171,17 @@ def test_values_that_are_not_finite_stay_in_their_group(cig, cog, mask_kind, pre
     own = got[keep][:, hit * cog:(hit + 1) * cog]
     assert np.isnan(own).all()      # (every kept position sees its own, relevant pixel)
     assert not got[~keep].view(np.uint32).any()
+
+
+@pytest.mark.parametrize("groups", [2, 8])      # 16 channels per group, and 4
+def test_input_of_more_than_two_gigabytes(groups):
+    """The last image of a 2.4 GB input gives the bits it gives alone (byte offsets past 2^31)."""
+    torch = G.torch_mod()
+    n, h, w, c = 36, 1024, 1024, 32
+    x = torch.zeros((n, h, w, c), dtype=torch.float16, device=G.dev())
+    x[-1] = torch.from_numpy(synth.activations((h, w, c), synth.F16, 403, 1).view(np.float16)).to(G.dev())
+    wt = G.to_dev(synth.he_weights(c, 3, 3, c // groups, synth.F16, 403, 2), synth.F16)
+    run = lambda a: B.focused_gconv2d(B.conv_desc(a.shape[0], h, w, c, c, (3, 3), (2, 2), in_dtype=B.F16), groups, a, wt)
+    alone = run(x[-1:].clone())
+    assert alone.count_nonzero() > 0
+    assert torch.equal(run(x)[-1:], alone)
