@@ -11,7 +11,7 @@
 //     before the sums of the waves meet;
 //   - the tile of a workgroup follows from its number alone, so the weights of its first slots are
 //     requested before anything is known about its rows;
-//   - with a list, the count and the entries are read together (entries past the count are dropped);
+//   - with a list, the count travels while the weights are requested, then the entries below it are read;
 //     without one, a tile is 32 consecutive positions, labelled here: no compaction before the
 //     kernel and no zero-fill after it, irrelevant rows come out as zeros;
 //   - pixels are gathered as soon as their addresses are known; what the input mask says about
@@ -89,7 +89,8 @@ __global__ __launch_bounds__(64 * kSmallWaves, 1) void k_conv_small(Geom g, Smal
     };
     // (with a list the splits follow the kept count; when that could change them, the count is waited for)
     const bool wait_count = idx && small_splits(1, g.c_out, total, taps, cut.room != 0) != small_splits(g.m, g.c_out, total, taps, cut.room != 0);
-    if (wait_count) rows = *count;
+    const int listed = idx ? *count : 0;
+    if (wait_count) rows = listed;
     take_split();
 
     const uint32_t lds_wave = __builtin_amdgcn_readfirstlane((uint32_t)reinterpret_cast<uintptr_t>(lds) + (uint32_t)wave * kSmallWaveBytes);
@@ -155,10 +156,10 @@ __global__ __launch_bounds__(64 * kSmallWaves, 1) void k_conv_small(Geom g, Smal
     int p = r0 + l32;
     bool live = p < g.m, drop = false;
     if (idx) {
-        const int entry = idx[min(p, g.m - 1)];
-        if (!wait_count) rows = *count;
+        // (entries past the count are not read: a caller's list may end there)
+        rows = listed;
         live = p < rows;
-        p = live ? entry : 0;
+        p = live ? idx[p] : 0;
     } else if (mask_in) {
         const bool kept = live && position_kept(g, mask_in, mask_out, live ? p : 0);
         drop = live && !kept;

@@ -750,3 +750,29 @@ def test_small_layer_tiles(layer, mode):
         if keep.any():
             assert G.rel_err(G.to_f64(out), want, keep) <= TOL_F32_OUT
         assert not out.cpu().numpy()[~keep].view(np.uint32).any()
+
+
+@pytest.mark.parametrize("layer", [
+    # n, h, w, ci, co, k, s: one wave a tile, splits in a workgroup and through the workspace, the tiled kernel, an RGB stem,
+    # the resident-weights kernel, fp32 on the matrix cores and not
+    (1, 11, 13, 72, 40, 3, 1), (2, 7, 7, 512, 104, 3, 1), (1, 20, 20, 64, 32, 5, 1), (3, 75, 101, 72, 200, 3, 2),
+    (1, 40, 44, 3, 32, 3, 2), (2, 60, 64, 128, 64, 1, 1), (1, 30, 31, 24, 40, 3, 1)])
+@pytest.mark.parametrize("dtype", [synth.BF16, synth.F32])
+def test_list_that_ends_at_its_count(layer, dtype):
+    """A caller's list needs no room past its count: the layer gives the bits it gives with a list of full capacity."""
+    torch = G.torch_mod()
+    n, h, w, ci, co, k, s = layer
+    x = G.to_dev(synth.activations((n, h, w, ci), dtype, 241, 1), dtype)
+    wt = G.to_dev(synth.he_weights(co, k, k, ci, dtype, 241, 2), dtype)
+    md = G.mask_dev(synth.mask_objects(n, h, w, 0.5, 241, 4))
+    desc = B.conv_desc(n, h, w, ci, co, (k, k), (s, s), (k // 2, k // 2), in_dtype=dtype)
+    m_out = B.mask_downsample(md, (k, k), (s, s), (k // 2, k // 2))
+    idx, count = B.active_index_compact(m_out)
+    kept = int(count.item())
+    assert 0 < kept < idx.numel()
+    ws = B.ready_workspace(torch.empty((B.workspace_bytes(desc),), dtype=torch.uint8, device=G.dev()))
+    for workspace in (None, ws):
+        full = B.focused_conv2d(desc, x, wt, mask_in=md, mask_out=m_out, idx=idx, count=count, workspace=workspace)
+        trimmed = B.focused_conv2d(desc, x, wt, mask_in=md, mask_out=m_out, idx=idx[:kept].clone(), count=count,
+                                   workspace=workspace)
+        assert torch.equal(full, trimmed)
