@@ -22,6 +22,7 @@ from . import synth
 
 
 MAX_PYRAMIDS = 16
+HEAD_CALLS = 6
 ARENA_CACHED = 224 << 20    # bytes of an arena that the last cache level (256 MB) holds beside weights and input
 
 
@@ -29,24 +30,24 @@ class _Plan:
     """The fc_run_calls sequence of one way of running a stack.
 
     Slots: 0 the input, 1 its mask, then mask / list / count of every pyramid level, weights and bias of
-    every layer, the outputs.  Outputs that the caller does not get live in one arena, at offsets such that
-    tensors in use at the same time do not overlap."""
+    every layer, the outputs.  All are filled in per run; the plan itself holds no address.  Outputs that the
+    caller does not get live in one arena, at offsets such that tensors in use at the same time do not overlap."""
 
     def __init__(self, stack: "ConvStack", masked: bool, keep_outputs: bool, chain: bool, compact: bool):
         ops, n = stack.ops, len(stack.ops)
         readers = stack._readers()
-        table: List[Optional[int]] = [None, None]
-        if masked:
-            table += [None] * (3 * len(stack.pyramid_steps))
+        n_slots = 2 + (3 * len(stack.pyramid_steps) if masked else 0)
 
-        def slot(address=None):
-            table.append(address)
-            return len(table) - 1
+        def slot():
+            nonlocal n_slots
+            n_slots += 1
+            return n_slots - 1
 
         out_slot = {-1: 0}
         compacted = set()
         calls = []
         self.levels = [(i, stack._level_of[i] if masked else -1) for i in range(n)]
+        params = []         # (op, slot of its weights, slot of its bias)
         self.returned, arena_ops = [], []
         for i, op in enumerate(ops):
             ho, wo = stack.sizes[i]
@@ -72,7 +73,8 @@ class _Plan:
                     extra |= B.COMPACT_OUT
                     compacted.add(i)
                     shape = (stack.n * ho * wo, op.c_out)
-                w, b = slot(stack.weights[i].data_ptr()), slot(stack.biases[i].data_ptr())
+                w, b = slot(), slot()
+                params.append((i, w, b))
                 if op.kind == "dwconv":
                     # labels come from the input mask inside the call: no list, no workspace
                     calls.append(B.Call(stack.desc(i, flags_extra=extra), B.CALL_DWCONV, src, m_in, w, b, -1, -1, -1,
@@ -84,8 +86,12 @@ class _Plan:
                 self.returned.append((i, out_slot[i], shape, dtype))
             else:
                 arena_ops.append((i, max(readers.get(i, [i])), int(np.prod(shape)) * dtype.itemsize))
-        self.calls = (B.Call * n)(*calls)
-        self.slots = (ctypes.c_void_p * len(table))(*table)
+        # the pass is enqueued in two parts: the device runs the first layers while the host fills in the others' slots
+        # (MobileNetV2's 104 tensors take it tens of microseconds)
+        cut = min(HEAD_CALLS, n)
+        self.parts = [([q for q in params if lo <= q[0] < hi], (B.Call * (hi - lo))(*calls[lo:hi]))
+                      for lo, hi in ((0, cut), (cut, n)) if hi > lo]
+        self.slots = ctypes.c_void_p * n_slots
         # A range is given out again some ops after its tensor's last reader while the arena stays inside the
         # chip's last cache level: writing over what the ops just before have read or written costs (MobileNetV2,
         # batch 32: 425 us with ranges reused at once, 401 us six ops later).  A larger arena is packed tightly
@@ -238,13 +244,13 @@ class ConvStack:
                 and all(self._pointwise(j) and self._matrix_core_shape(j) for j in readers[i]))
 
     def _run_planned(self, x, mask, keep_outputs: bool, chain: bool, compact: bool):
-        key = (mask is not None, keep_outputs, chain, compact)
-        plan = self._plans.get(key)
+        way = (mask is not None, keep_outputs, chain, compact)
+        plan = self._plans.get((way, self.relu))
         if plan is None:
-            plan = self._plans[key] = _Plan(self, *key)
+            plan = self._plans[way, self.relu] = _Plan(self, *way)
         B._require_cuda(x, mask)
         torch = self.torch
-        slots = type(plan.slots).from_buffer_copy(plan.slots)
+        slots = plan.slots()
         slots[0] = x.data_ptr()
         masks: Dict[int, object] = {-1: mask}
         if mask is not None:
@@ -271,7 +277,12 @@ class ConvStack:
         for i, slot, shape, dtype in plan.returned:
             out = outs[i] = torch.empty(shape, dtype=dtype, device=dev)
             slots[slot] = out.data_ptr()
-        B.run_calls(plan.calls, slots, self.workspace)
+        for params, calls in plan.parts:
+            for i, w_slot, b_slot in params:        # whatever tensors the dicts hold now
+                w, b = self.weights[i], self.biases[i]
+                B._require_cuda(w, b)
+                slots[w_slot], slots[b_slot] = w.data_ptr(), B._ptr(b)
+            B.run_calls(calls, slots, self.workspace)
         return outs, masks
 
     def run(self, x, mask=None, keep_outputs: bool = True, chain: bool = False, canary=None, compact: bool = False):

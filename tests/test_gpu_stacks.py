@@ -355,3 +355,34 @@ def test_graph_replays_match_eager():
         torch.cuda.synchronize()
         assert torch.equal(call.out, eager), rep
         assert not torch.equal(other, eager)
+
+
+def test_assigned_weights_take_effect_on_the_next_run():
+    """A tensor put into `weights` or `biases` after a run is what the next run reads: the outputs are those of a
+    stack that has held it from the start, and of the call-by-call path."""
+    torch = G.torch_mod()
+    dtype = synth.BF16
+    ops = workloads.resnet18()[:7]
+    n, h, w, c_in = 1, 64, 96, 3
+    x = G.to_dev(synth.activations((n, h, w, c_in), dtype, 380, 1), dtype)
+    md = G.mask_dev(synth.mask_objects(n, h, w, 0.4, 380, 2))
+    stack, fresh = (ConvStack(ops, n, h, w, dtype, seed=381) for _ in range(2))
+    before, _ = stack.run(x, md)
+    convs = [i for i, op in enumerate(ops) if op.kind == "conv"]
+    for s in (stack, fresh):
+        s.weights = {i: (t * 0.5 if i == convs[1] else t) for i, t in s.weights.items()}
+        s.weights[convs[2]] = s.weights[convs[2]] * -1.0
+        s.biases[convs[3]] = torch.full_like(s.biases[convs[3]], 0.25)
+        s.biases[convs[4]] = None
+    torch.cuda.synchronize()
+    keep_busy = [torch.full_like(t, 3.0) for t in stack.weights.values()]     # (the replaced tensors' memory is in use again)
+    got, _ = stack.run(x, md)
+    want, _ = fresh.run(x, md)
+    by_call, _ = stack.run(x, md, canary=0.0)
+    for i in convs:
+        assert torch.equal(got[i], want[i]) and torch.equal(got[i], by_call[i]), ops[i].name
+    assert not torch.equal(got[convs[1]], before[convs[1]])
+    stack.weights[convs[0]] = stack.weights[convs[0]].transpose(1, 2)
+    with pytest.raises(ValueError):
+        stack.run(x, md)
+    assert keep_busy
