@@ -386,3 +386,70 @@ def test_assigned_weights_take_effect_on_the_next_run():
     with pytest.raises(ValueError):
         stack.run(x, md)
     assert keep_busy
+
+
+@pytest.mark.parametrize("net,shape,dtype", [
+    ("resnet18", (1, 64, 96, 3), synth.BF16), ("resnet50_bottlenecks", (2, 48, 64, 64), synth.BF16),
+    ("resnet50_bottlenecks", (2, 40, 56, 64), synth.FP8), ("vgg16", (1, 72, 128, 3), synth.F16),
+    ("mobilenetv2", (3, 64, 96, 3), synth.F16)])
+@pytest.mark.parametrize("chain,compact", [(False, False), (True, False), (True, True)])
+@pytest.mark.parametrize("rest_limit", [None, 0])     # ranges that rest while the arena is small, and packed tightly
+def test_outputs_in_the_arena_give_the_bits_of_kept_ones(net, shape, dtype, chain, compact, rest_limit, monkeypatch):
+    """A run whose intermediate outputs share one arena, over memory that held NaN, ends with the bits of the run
+    whose outputs all have memory of their own; so does the dense one."""
+    torch = G.torch_mod()
+    if rest_limit is not None:
+        from paper_2207_10741_amd import stacks
+        monkeypatch.setattr(stacks, "ARENA_CACHED", rest_limit)
+    n, h, w, c_in = shape
+    ops = getattr(workloads, net)()
+    stack = ConvStack(ops, n, h, w, dtype, seed=390)
+    x = G.to_dev(synth.activations(shape, dtype, 390, 1), dtype)
+    md = G.mask_dev(synth.mask_objects(n, h, w, 0.45, 390, 2))
+    last = len(ops) - 1
+    for mask in (md, None):
+        kept, kept_masks = stack.run(x, mask, chain=chain, compact=compact)
+        for seed in range(2):
+            # the allocator hands the freed block out again
+            torch.full((64 << 20,), 0xFF, dtype=torch.uint8, device=G.dev())
+            got, masks = stack.run(x, mask, keep_outputs=False, chain=chain, compact=compact)
+            assert sorted(got) == [-1, last]
+            assert torch.equal(got[last].view(torch.uint8), kept[last].view(torch.uint8))
+        plan = stack._plans[(mask is not None, False, chain, compact), True]
+        assert len(plan.in_arena) == last and 0 < plan.arena_bytes <= 64 << 20
+        if mask is not None:
+            assert all(torch.equal(masks[i], kept_masks[i]) for i in range(len(ops)))
+
+
+def test_run_calls_enqueues_the_layers_before_a_refused_one():
+    """A sequence gives the bits of the single calls; a layer that is refused ends it with that layer's status, what
+    was in front of it runs, what comes after does not."""
+    import ctypes
+    torch = G.torch_mod()
+    dtype = synth.BF16
+    n, h, w, c = 1, 24, 40, 32
+    x = G.to_dev(synth.activations((n, h, w, c), dtype, 391, 1), dtype)
+    wt = G.to_dev(synth.he_weights(c, 3, 3, c, dtype, 391, 2), dtype)
+    dw = G.to_dev(np.ascontiguousarray(synth.he_weights(c, 3, 3, 1, dtype, 391, 3)[..., 0]), dtype)
+    md = G.mask_dev(synth.mask_objects(n, h, w, 0.4, 391, 4))
+    idx, count = B.active_index_compact(md)
+    m = B.mask_downsample(md, (2, 2), (2, 2), (0, 0))
+    desc, pool = B.conv_desc(n, h, w, c, c), B.conv_desc(n, h, w, c, c, (2, 2), (2, 2), (0, 0))
+    a = B.focused_conv2d(desc, x, wt, mask_in=md, mask_out=md, idx=idx, count=count)
+    b = B.focused_dwconv2d(desc, a, dw, mask_in=md)
+    p = B.maxpool2d(b, 2, 2, 0, dtype, keep=m)
+    outs = [torch.full_like(t, 7.0) for t in (a, b, p)]
+    slots = (ctypes.c_void_p * 10)(*[t.data_ptr() for t in (x, wt, dw, md, idx, count, m, *outs)])
+    calls = [B.Call(desc, B.CALL_CONV, 0, 3, 1, -1, 3, 4, 5, 7), B.Call(desc, B.CALL_DWCONV, 7, 3, 2, -1, -1, -1, -1, 8),
+             B.Call(pool, B.CALL_MAXPOOL, 8, -1, -1, -1, 6, -1, -1, 9)]
+    B.run_calls((B.Call * 3)(*calls), slots, None)
+    torch.cuda.synchronize()
+    assert all(torch.equal(got, want) for got, want in zip(outs, (a, b, p)))
+    for t in outs:
+        t.fill_(7.0)
+    calls[1].w = -1
+    with pytest.raises(B.FcError) as e:
+        B.run_calls((B.Call * 3)(*calls), slots, None)
+    assert e.value.status == -1
+    torch.cuda.synchronize()
+    assert torch.equal(outs[0], a) and (outs[1] == 7.0).all() and (outs[2] == 7.0).all()
