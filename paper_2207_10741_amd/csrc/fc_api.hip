@@ -87,15 +87,18 @@ bool conv_line_wanted(const Geom &g, int in_dtype, int out_dtype, bool focused)
 // tile.  Measured against the tiled kernel at 48 % irrelevant pixels on 50 000 .. 2.5 M
 // positions: without a mask 12 .. 25 % faster up to 0.6 M positions (6 % slower at 2.5 M);
 // chained (no zero-fill) equal at 50 000, 1 .. 17 % faster from 100 000 on; with zero-fill 4 .. 7 %
-// slower up to 0.4 M (the zero-fill comes after a wave's units instead of between tiles), 16 %
-// faster at 0.6 M, 2 % slower at 2.1 M, 4 .. 5 % faster from 4 M on (16.6 M: 1 307 against 1 252 us).  Into 128 channels the tiled kernels win or draw.  128 8-bit
-// channels into 64 follow the same pattern (0.6 M positions: 25 .. 28 % faster in all three modes).
+// slower up to 0.4 M (the zero-fill comes after a wave's units instead of between tiles).  From 0.5 M on, 30 .. 70 %
+// irrelevant, on inputs that are not in the last cache level already, 3 .. 18 % faster at each of 14 sizes up to 16.6 M
+// (0.5 M 55 against 47 us, 1.0 M 105 / 92, 2.1 M 199 / 185, 2.8 M 256 / 242, 4.1 M 366 / 344, 16.6 M 1 354 / 1 307); called again
+// and again on one input, of which up to 256 MB are then in that level, the tiled kernel gets more out of it: 2 .. 7 % faster
+// from 2.1 to 2.8 M, even at 3.7 M.  Into 128 channels the tiled kernels win or draw.  128 8-bit
+// channels into 64 follow the same pattern (2.1 M positions: 198 / 176 us; 0.6 M: 25 .. 28 % faster in all three modes).
 static bool conv_pw_wanted_3x3(const Geom &g, bool masked)
 {
     if (g.c_out > 64) return false;
     if (!masked) return g.m >= 40000 && g.m < 1500000;
     if (g.flags & (FC_SKIP_ZERO_FILL | FC_COMPACT_OUT)) return g.m >= 80000;
-    return g.m >= 500000 && (g.m < 2000000 || g.m >= 3000000);
+    return g.m >= 500000;
 }
 
 // Does the resident-weights kernel serve this layer?  1x1 layers without padding whose rows are whole
