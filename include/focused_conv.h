@@ -217,7 +217,7 @@ int32_t fc_active_index_compact_tiled(const uint8_t *mask, int32_t n, int32_t ho
 
 /* Mask pyramid (Sec. III-B: one mask per image, rescaled to every layer's size).  Builds, for
  * `levels` successive resolution changes, the mask and the kept-position list of every level
- * from the input mask in two launches.  steps[l] is the window (kernel, stride, padding,
+ * from the input mask, in one launch for the masks of one small image, else in two.  steps[l] is the window (kernel, stride, padding,
  * dilation) of the layer that takes level l - 1 (the input mask for l = 0) to level l; level l
  * equals fc_mask_downsample of level l - 1 with that window, and its list equals
  * fc_active_index_compact of it (bit for bit).
@@ -256,7 +256,8 @@ int32_t fc_mask_pyramid_packed(const void *mask_in, int32_t mask_in_packed, int3
  *             idx/count, the call compacts these labels itself (into the
  *             workspace): the rows computed and the rows cleared follow them
  *   idx,count device, as fc_active_index_compact writes them from mask_out; both
- *             NULL = computed here into the workspace
+ *             NULL = computed here into the workspace.  Entries past `count` are
+ *             not read: a list may end there
  *   out       device, NHWC, out_dtype; its bytes must not overlap those of x
  *             (FC_ERR_NULL)
  *   workspace device, >= fc_workspace_bytes(desc) when idx is NULL and mask_in is
@@ -266,7 +267,11 @@ int32_t fc_mask_pyramid_packed(const void *mask_in, int32_t mask_in_packed, int3
  *             partials are always added in the same order).  Its first bytes
  *             hold arrival counters that every call finds and leaves at zero;
  *             a call clears them first unless FC_WORKSPACE_READY is set
- * `count` is read on the device only; the launch grid does not depend on it. */
+ * `count` is read on the device only; the launch grid does not depend on it.
+ * The same call gives the same bits every time.  Calls that differ in what they bring (a list or
+ * none, a workspace or none, other flags) may run on different kernels or split a reduction
+ * differently, so the order of a row's fp32 sum, and with it the last bits, can differ between them
+ * on the same data; each is within the same error of the exact sum. */
 int32_t fc_focused_conv2d(const fc_conv_desc *desc, const void *x, const uint8_t *mask_in,
                           const void *w, const float *bias, const uint8_t *mask_out,
                           const int32_t *idx, const int32_t *count, void *out,
@@ -302,20 +307,27 @@ int32_t fc_focused_conv2d_noalloc(const fc_conv_desc *desc, const void *x, const
  *   desc      c_in and c_out are the totals; both must be multiples of groups (FC_ERR_SHAPE)
  *   w         device, [c_out][kh][kw][c_in / groups]
  *   workspace needed (>= fc_workspace_bytes(desc)) only when mask_in is given without a list
- * Layers with more than one channel per group run on the vector ALUs, not on the matrix
- * cores, and take the 32- and 16-bit storage types only (FC_FP8: FC_ERR_DTYPE). */
+ * Layers with more than one channel per group take the 32- and 16-bit storage types only
+ * (FC_FP8: FC_ERR_DTYPE).  16-bit layers with 4, 8 or a multiple of 16 output channels per group
+ * and a multiple of 4 (4 and 8) or 8 (16 and more) input channels per group, c_out a multiple
+ * of 16 and c_in of 8, run on the matrix cores while a channel's weights fit the
+ * registers (9 * 16 input channels per group for 4 output channels, 9 * 32 for 8, 9 * 64 for 16);
+ * the others run on the vector ALUs.  Groups are kept apart in either: a value that is not finite
+ * reaches the outputs of its own group only. */
 int32_t fc_focused_gconv2d(const fc_conv_desc *desc, int32_t groups, const void *x,
                            const uint8_t *mask_in, const void *w, const float *bias,
                            const uint8_t *mask_out, const int32_t *idx, const int32_t *count,
                            void *out, void *workspace, size_t workspace_bytes, void *stream);
 
 /* A grouped layer is the full layer with block-diagonal weights (the terms outside the blocks
- * are zeros and change no sum).  This writes those weights: w_full[c_out][kh][kw][c_in] from
+ * are zeros and change no sum of finite values).  This writes those weights: w_full[c_out][kh][kw][c_in] from
  * w_grouped[c_out][kh][kw][c_in / groups], any storage type, both device.  With them
- * fc_focused_conv2d runs the grouped layer on the matrix cores, which for the group counts of
- * common networks is several times faster than fc_focused_gconv2d in spite of the `groups`
- * times larger multiply count (and is the only way to run a grouped layer in FC_FP8).  Expand
- * once when the weights are loaded. */
+ * fc_focused_conv2d runs the grouped layer as a full one: the only way to run a grouped layer in
+ * FC_FP8, and a fast one for channel counts per group that fc_focused_gconv2d leaves to the vector
+ * ALUs (for the others, see there, fc_focused_gconv2d is the faster call).  Two things differ
+ * from it: the terms outside the blocks are multiplied, so a value that is not finite reaches the
+ * outputs of every group, and c_in and c_out count as those of a full layer.  Expand once when the
+ * weights are loaded. */
 int32_t fc_expand_group_weights(int32_t c_in, int32_t c_out, int32_t kh, int32_t kw, int32_t groups,
                                 int32_t dtype, const void *w_grouped, void *w_full, void *stream);
 

@@ -7,7 +7,8 @@
 // There is no contraction here (KH*KW multiply-adds per output value, 2 bytes in and 2 bytes
 // out), so the kernel is bound by memory traffic and vector ALU work, not by the matrix cores.
 //
-// Mapping.  A lane owns VEC consecutive channels (16 bytes of a pixel) for the whole launch.
+// Mapping of k_dwconv (k_dwconv_tile, for the 3 x 3 layers of most networks, is described at its place).  A lane owns
+// VEC consecutive channels (16 bytes of a pixel) for the whole launch.
 // The lanes of a workgroup are laid out [position][channel chunk]: consecutive lanes read and
 // write consecutive 16-byte pieces of a pixel, then the next pixel, and the workgroup walks the
 // positions of one image with a grid stride.  Pixels are not staged in LDS; taps shared by

@@ -1,5 +1,6 @@
-// Direct focused convolution for shapes the matrix-core path does not take
-// (odd channel counts such as RGB stems, fp32 storage, very large kernels).
+// Direct focused convolution for shapes the matrix-core kernels do not take (16-bit storage with odd channel
+// counts, fp32 storage of fewer than four input channels, very large kernels, and grouped layers whose
+// channels per group are neither 4, 8 nor whole blocks of 16).
 // Sec. III-A: only the kept patches are evaluated.
 //
 // One lane owns one kept position and CO_T of its output channels, held as fp32

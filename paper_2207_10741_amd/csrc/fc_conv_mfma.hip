@@ -929,11 +929,14 @@ __global__ __launch_bounds__(WM *WN * 64, MINW) void k_conv_dma(Geom g, const ui
 #if !defined(FC_MFMA_PART) || FC_MFMA_PART == 0
 // Does a 3x3 layer with a mask and no list label its rows tile by tile (64 x 64 tiles of consecutive positions,
 // irrelevant ones stored as zeros) instead of compacting them in a launch of its own?  While all tiles of the
-// layer run at once, dropping the irrelevant rows shortens nothing and the compaction is 4.5 us: 72 -> 200 on
-// 3 x 75 x 101, stride 2 (348 tiles of 18 stages) 17.0 -> 12.3 us, 64 -> 64 on 8 x 56 x 56 (392 of 9) 12.2 -> 8.6 us,
-// 128 -> 128 on 8 x 28 x 28 (196 of 18) 14.7 -> 9.5 us, whatever the kept share.  From two rounds of tiles on, or
-// with long reductions, the rows left out are worth it: 64 -> 128 on 8 x 56 x 56 (784 tiles) 14.4 -> 20 us; 392 tiles
-// of 36 stages gain 1.5 us at a kept share of one half and lose as much at one fifth.
+// layer run at once, dropping the irrelevant rows shortens nothing and the compaction is 4.5 us.  Calls one after
+// another, the output tensor included, compacted -> here: 72 -> 200 on 3 x 75 x 101, stride 2 (348 tiles of 18 stages)
+// 18.8 -> 16.4 us, 64 -> 64 on 8 x 56 x 56 (392 of 9) 14.5 -> 10.5 us, 128 -> 128 on 8 x 28 x 28 (196 of 18) 16.6 -> 13.7 us,
+// whatever the kept share.  From two rounds of tiles on, or with long reductions, the rows left out are worth
+// it: 64 -> 128 on 8 x 56 x 56 (784 tiles) 14.4 -> 20 us; 392 tiles of 36 stages gain 1.5 us at a kept share of one half
+// and lose as much at one fifth.
+// (Such a call never splits a tile's reduction; with the list and a workspace the same layer does where few rows are
+// kept, so its last bits can be others there.)
 bool tiles_label_rows(const Geom &g, int in_dtype)
 {
     if (g.kh != 3 || g.kw != 3 || g.m <= kInlineRankPositions || (g.flags & FC_RESIDENT_WEIGHTS)) return false;

@@ -2,15 +2,14 @@
 // storage, on the matrix cores.
 //
 // Sec. III-A as everywhere: rows = kept positions, columns = output channels, reduction = taps
-// x input channels, gated taps read as zero.  What these two layer types have in common is
-// that the matrix cores are not the bottleneck that LDS staging exists for:
-//   - fp32: v_mfma_f32_32x32x2_f32 runs at 1/16 of the 16-bit rate, so a wave needs three
-//     16-byte loads per lane for every 512 cycles of matrix work; the L1 delivers that;
+// x input channels, gated taps read as zero.  The two layer types share how rows are found and cleared; what
+// bounds them differs:
+//   - fp32: v_mfma_f32_32x32x2_f32 runs at 1/16 of the 16-bit rate, so large layers are bound by it; the operands
+//     come through a ring of LDS stages, with a barrier per stage (k_conv_f32);
 //   - grouped: a layer's multiplies are few (a ResNeXt stage: 0.24 GFLOP), its time is the
-//     reading of x and the writing of out, and a 16-channel output block needs only the
-//     channels of its own groups.
-// No tile is staged, no barrier separates the steps of a reduction, and every wave runs ahead
-// on its own loads.
+//     reading of x and the writing of out.  Weights stay in registers; the pixels come straight from global memory, a
+//     tile or quad of rows ahead (k_conv_grouped, k_conv_grouped_quads), or, where positions are pixels, from one window
+//     of pixels in LDS (k_conv_grouped_window).
 //
 // Rows.  A workgroup owns a span of consecutive positions.  Without a list it labels the span
 // itself, compacts the kept positions in LDS and clears the rows of the others, so a masked call
@@ -161,8 +160,8 @@ __device__ __forceinline__ void clear_dropped(const SpanRows &s, int ndrop, TO *
 // over four times as many SIMDs.  WK = 1: 32 rows of a 128-position span each.
 // TAIL: the input channels are not whole 32-channel stages.
 //
-// Measured (mask given, call included): 64 -> 64 on 2 x 60 x 80, half kept: 75.5 us on the vector ALUs
-// with a compaction and a zero-fill launch, 15.6 us; 128 -> 128 on 8 x 120 x 120 without a mask: 320 us =
+// Measured (mask given, call and output tensor included): 64 -> 64 on 2 x 60 x 80, half kept: 75.8 us on the vector
+// ALUs with a compaction and a zero-fill launch, 15.9 us; 128 -> 128 on 8 x 120 x 120 without a mask: 321 us =
 // 106 TFLOP/s.
 // ---------------------------------------------------------------------------------------------
 template <int TN, int WK, int NB, bool TAIL>
