@@ -92,11 +92,12 @@ hipError_t launch_mask_window(const uint8_t *mask_in, int n, int h, int w, int k
 
 // ---------------------------------------------------------------------------
 // Ordered kept lists (Sec. III-A: which patches become columns) fused with the mask
-// propagation (Sec. III-B), for one mask or for all levels of a pyramid.  A workgroup of 1024
-// threads owns 4096 consecutive positions of one list, a lane four of them: it labels them in the
-// input mask (one 32-bit load for a list at the mask's own resolution, four byte loads in flight
-// otherwise), ranks them by a prefix sum (vector ALU inside a wave, LDS across the sixteen
-// waves) and stores the kept ones.  Bound: launch latency for the masks of one image, HBM for the
+// propagation (Sec. III-B), for one mask or for all levels of a pyramid.  A workgroup owns 4096
+// consecutive positions of one list, a lane PER of them: it labels them in the
+// input mask (one load for a list at the mask's own resolution, PER byte loads in flight
+// otherwise), ranks them by a prefix sum (vector ALU inside a wave, LDS across the
+// waves) and stores the kept ones.  PER = 4 (1024 threads) for the latency of short lists, 16 (256 threads) for the
+// throughput of long ones, see launch_lists_n.  Bound: launch latency for the masks of one image, HBM for the
 // largest.  No workgroup ever waits on another, so every grid drains:
 //   - short lists: ONE launch; a workgroup counts the kept positions before its own by itself (16 bytes per
 //     lane and load at the mask's resolution, sixteen labels per lane in flight otherwise);
@@ -104,14 +105,21 @@ hipError_t launch_mask_window(const uint8_t *mask_in, int n, int h, int w, int k
 // (Four levels of one 224 x 224 mask: 7.1 + 4.2 us in two launches with sixteen positions per lane and the
 // levels' maps applied one after another; the labels of 5 814 positions through a stride: 8.9 us.)
 // ---------------------------------------------------------------------------
-constexpr int kListThreads = 1024;
+constexpr int kListThreads = 1024; // of a workgroup whose lanes take four positions
 constexpr int kListWaves = kListThreads / 64;
+template <int PER> constexpr int kThreadsOf = kCompactBlockElems / PER;
 // Most workgroups of a list in the one-launch form.  At the mask's resolution the last workgroup reads
 // 16 KB per 16 lanes-wide load, so 64 of them (256 KB) cost what one round trip and a half costs (one list of
 // 131 072 positions 4.6 us against 5.7 us in two launches, of 262 144 5.9 against 5.8).  Through a stride four workgroups
 // before it are one round trip, and every further four one more: four levels of one 224 x 224 mask 6.2 us against 6.5 us
 // in two launches, of two 8.8 against 6.6 us, of 16 x 128 x 128 17.0 against 7.6 us.
 constexpr int kOnceBlocksIdentity = 64, kOnceBlocks = 4;
+// Workgroups of a list at the mask's resolution from which on a lane takes sixteen positions: there the labels of
+// sixteen are one load as those of four are, and what such a list costs is instructions per lane.  Four -> sixteen, a list
+// alone / a pyramid of four levels: 1.6 M positions 10.1 -> 9.9 / 12.4 -> 12.4 us, 2.1 M 10.1 -> 10.0 / 13.9 -> 12.8, 5.2 M
+// 14.6 -> 11.4 / 23.1 -> 18.3, 16.6 M 34.5 -> 20.9 / 57.2 -> 42.0.  (Below the line, or where the first level has a stride,
+// four stay ahead: 0.8 M 10.2 against 11.4 us, three strided levels of 16.6 M 22.0 against 23.3.)
+constexpr int kLongBlocks = 400;
 
 // sum of v over the workgroup (all threads get it)
 template <int WAVES>
@@ -130,27 +138,36 @@ __device__ __forceinline__ int block_sum(int v, int *scratch)
 // 0x80 in every nonzero byte
 __device__ __forceinline__ uint32_t nonzero_bytes(uint32_t v) { return (((v & 0x7f7f7f7fu) + 0x7f7f7f7fu) | v) & 0x80808080u; }
 
-// bit j = position p0 + j of the list is kept (p0 a multiple of four; positions past the end read as 0)
-__device__ __forceinline__ uint32_t label4(const LabelMap &L, const uint8_t *__restrict__ mask_in, int p0, bool vec)
+// bit j = position p0 + j of the list is kept, j < PER (p0 a multiple of PER; positions past the end read as 0)
+template <int PER>
+__device__ __forceinline__ uint32_t labels(const LabelMap &L, const uint8_t *__restrict__ mask_in, int p0, bool vec)
 {
     if (p0 >= L.m) return 0;
     const int left = L.m - p0;
     if (L.identity && L.packed_in) {
-        const uint32_t f = (reinterpret_cast<const uint32_t *>(mask_in)[p0 >> 5] >> (p0 & 31)) & 15u;
-        return left < 4 ? f & ((1u << left) - 1u) : f;
+        const uint32_t f = (reinterpret_cast<const uint32_t *>(mask_in)[p0 >> 5] >> (p0 & 31)) & ((1u << PER) - 1u);
+        return left < PER ? f & ((1u << left) - 1u) : f;
     }
-    if (L.identity && vec && left >= 4) {
-        const uint32_t v = nonzero_bytes(*reinterpret_cast<const uint32_t *>(mask_in + p0));
-        return ((v >> 7) & 1u) | ((v >> 14) & 2u) | ((v >> 21) & 4u) | (v >> 28);
+    if (L.identity && vec && left >= PER) {
+        auto four = [](uint32_t w) {
+            const uint32_t v = nonzero_bytes(w);
+            return ((v >> 7) & 1u) | ((v >> 14) & 2u) | ((v >> 21) & 4u) | (v >> 28);
+        };
+        if constexpr (PER == 4) {
+            return four(*reinterpret_cast<const uint32_t *>(mask_in + p0));
+        } else {
+            const uint4 v = *reinterpret_cast<const uint4 *>(mask_in + p0);
+            return four(v.x) | (four(v.y) << 4) | (four(v.z) << 8) | (four(v.w) << 12);
+        }
     }
     const uint32_t t = fast_div((uint32_t)p0, L.div_w);
     int ow = p0 - (int)t * L.wl;
     int b = (int)fast_div(t, L.div_h), oh = (int)t - b * L.hl;
     auto along = [](const AxisMap &a, int v) { return min(max(v * a.mul + a.add, a.lo), a.hi); };
     int row_at = (b * L.h0 + along(L.row, oh)) * L.w0;
-    int at[4];
+    int at[PER];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < PER; ++j) {
         at[j] = j < left ? row_at + along(L.col, ow) : -1;
         if (++ow == L.wl) {
             ow = 0;
@@ -163,39 +180,46 @@ __device__ __forceinline__ uint32_t label4(const LabelMap &L, const uint8_t *__r
     }
     uint32_t f = 0;
     if (L.packed_in) {
-        uint32_t got[4];
+        uint32_t got[PER];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) got[j] = at[j] >= 0 ? reinterpret_cast<const uint32_t *>(mask_in)[at[j] >> 5] : 0u;
+        for (int j = 0; j < PER; ++j) got[j] = at[j] >= 0 ? reinterpret_cast<const uint32_t *>(mask_in)[at[j] >> 5] : 0u;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) f |= ((got[j] >> (at[j] & 31)) & 1u) << j;
+        for (int j = 0; j < PER; ++j) f |= ((got[j] >> (at[j] & 31)) & 1u) << j;
     } else {
-        uint8_t got[4];
+        uint8_t got[PER];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) got[j] = at[j] >= 0 ? mask_in[at[j]] : (uint8_t)0;
+        for (int j = 0; j < PER; ++j) got[j] = at[j] >= 0 ? mask_in[at[j]] : (uint8_t)0;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) f |= got[j] ? 1u << j : 0u;
+        for (int j = 0; j < PER; ++j) f |= got[j] ? 1u << j : 0u;
     }
     return f;
 }
 
-// Labels of positions p0 .. p0 + 3 to mask_out (bytes 0 / 1, or bits, zeros up to a whole 64-bit word).
+// Labels of positions p0 .. p0 + PER - 1 to mask_out (bytes 0 / 1, or bits, zeros up to a whole 64-bit word).
 // All lanes call it.
+template <int PER>
 __device__ __forceinline__ void store_labels(const LabelMap &L, int p0, uint32_t f)
 {
     if (!L.mask_out) return;
     if (L.packed_out) {
         const int lane = threadIdx.x & 63;
-        uint32_t v = f << (4 * (lane & 3));
-        v |= __shfl_xor(v, 1);
-        v |= __shfl_xor(v, 2);
-        if ((lane & 3) == 0 && (int64_t)p0 < (((int64_t)L.m + 63) & ~(int64_t)63)) reinterpret_cast<uint16_t *>(L.mask_out)[p0 >> 4] = (uint16_t)v;
+        uint32_t v = f;
+        if constexpr (PER == 4) { // four lanes make a 16-bit piece
+            v <<= 4 * (lane & 3);
+            v |= __shfl_xor(v, 1);
+            v |= __shfl_xor(v, 2);
+        }
+        if ((PER == 16 || (lane & 3) == 0) && (int64_t)p0 < (((int64_t)L.m + 63) & ~(int64_t)63)) reinterpret_cast<uint16_t *>(L.mask_out)[p0 >> 4] = (uint16_t)v;
         return;
     }
-    if (p0 + 4 <= L.m) {
-        *reinterpret_cast<uint32_t *>(L.mask_out + p0) =
-            (f & 1u) | ((f & 2u) << 7) | ((f & 4u) << 14) | ((f & 8u) << 21);
+    if (p0 + PER <= L.m) {
+        auto bytes = [](uint32_t v) { return (v & 1u) | ((v & 2u) << 7) | ((v & 4u) << 14) | ((v & 8u) << 21); };
+        if constexpr (PER == 4)
+            *reinterpret_cast<uint32_t *>(L.mask_out + p0) = bytes(f);
+        else
+            *reinterpret_cast<uint4 *>(L.mask_out + p0) = make_uint4(bytes(f), bytes(f >> 4), bytes(f >> 8), bytes(f >> 12));
     } else {
-        for (int j = 0; j < 4 && p0 + j < L.m; ++j) L.mask_out[p0 + j] = (f >> j) & 1u;
+        for (int j = 0; j < PER && p0 + j < L.m; ++j) L.mask_out[p0 + j] = (f >> j) & 1u;
     }
 }
 
@@ -209,9 +233,10 @@ __device__ __forceinline__ int list_of_block(const ListArgs<NL> &a, int block)
     return l;
 }
 
-// the workgroup's part of the list: kept positions p0 .. p0 + 3 of every lane after `base` earlier ones;
+// the workgroup's part of the list: kept positions p0 .. p0 + PER - 1 of every lane after `base` earlier ones;
 // returns the number kept by the whole workgroup.  `staged`: the list is put together in LDS and leaves in
 // whole lines (long lists: 8.3 million entries 38 us straight from the lanes)
+template <int PER>
 __device__ __forceinline__ int store_list(const LabelMap &L, int p0, uint32_t f, int base, int *wave_sum,
                                           int32_t *staged = nullptr)
 {
@@ -221,18 +246,22 @@ __device__ __forceinline__ int store_list(const LabelMap &L, int p0, uint32_t f,
     __syncthreads();
     int before = 0, total = 0;
 #pragma unroll
-    for (int i = 0; i < kListWaves; ++i) {
+    for (int i = 0; i < kThreadsOf<PER> / 64; ++i) {
         const int t = wave_sum[i];
         before += i < wave ? t : 0;
         total += t;
     }
     int32_t *to = (staged ? staged : L.idx + base) + (before + incl - c);
+    if constexpr (PER == 4) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-        if ((f >> j) & 1u) *to++ = p0 + j;
+        for (int j = 0; j < PER; ++j)
+            if ((f >> j) & 1u) *to++ = p0 + j;
+    } else {
+        for (; f; f &= f - 1) *to++ = p0 + __ffs((int)f) - 1;
+    }
     if (staged) {
         __syncthreads();
-        for (int i = threadIdx.x; i < total; i += kListThreads) L.idx[(int64_t)base + i] = staged[i];
+        for (int i = threadIdx.x; i < total; i += kThreadsOf<PER>) L.idx[(int64_t)base + i] = staged[i];
     }
     return total;
 }
@@ -247,7 +276,7 @@ __global__ __launch_bounds__(kListThreads) void k_lists_once(ListArgs<NL> a, con
     const int block = blockIdx.x - L.block0;
     const int p0 = block * kCompactBlockElems + tid * 4;
     const bool vec = a.vec_in != 0;
-    const uint32_t f = label4(L, mask_in, p0, vec);
+    const uint32_t f = labels<4>(L, mask_in, p0, vec);
 
     // kept positions of this list before this workgroup's
     int part = 0;
@@ -268,14 +297,14 @@ __global__ __launch_bounds__(kListThreads) void k_lists_once(ListArgs<NL> a, con
             uint32_t g[4];
 #pragma unroll
             for (int k = 0; k < 4; ++k)
-                g[k] = b0 + k < block ? label4(L, mask_in, (b0 + k) * kCompactBlockElems + tid * 4, vec) : 0u;
+                g[k] = b0 + k < block ? labels<4>(L, mask_in, (b0 + k) * kCompactBlockElems + tid * 4, vec) : 0u;
 #pragma unroll
             for (int k = 0; k < 4; ++k) part += __popc(g[k]);
         }
     }
-    store_labels(L, p0, f);
+    store_labels<4>(L, p0, f);
     const int base = block ? block_sum<kListWaves>(part, scratch) : 0;
-    const int total = store_list(L, p0, f, base, wave_sum);
+    const int total = store_list<4>(L, p0, f, base, wave_sum);
     if (tid == 0 && (int64_t)(block + 1) * kCompactBlockElems >= L.m) *L.count = base + total;
 
     // on the side, for the convolution that follows: clear its split-K tile counters
@@ -284,68 +313,77 @@ __global__ __launch_bounds__(kListThreads) void k_lists_once(ListArgs<NL> a, con
 }
 
 // two launches: labels and per-workgroup counts ...
-template <int NL>
-__global__ __launch_bounds__(kListThreads) void k_lists_count(ListArgs<NL> a, const uint8_t *__restrict__ mask_in,
-                                                              int32_t *__restrict__ block_counts)
+template <int NL, int PER>
+__global__ __launch_bounds__(kThreadsOf<PER>) void k_lists_count(ListArgs<NL> a, const uint8_t *__restrict__ mask_in,
+                                                                 int32_t *__restrict__ block_counts)
 {
-    __shared__ int scratch[kListWaves];
+    __shared__ int scratch[kThreadsOf<PER> / 64];
     const LabelMap &L = a.at[NL == 1 ? 0 : list_of_block(a, blockIdx.x)];
-    const int p0 = (blockIdx.x - L.block0) * kCompactBlockElems + threadIdx.x * 4;
-    const uint32_t f = label4(L, mask_in, p0, a.vec_in != 0);
-    store_labels(L, p0, f);
-    const int total = block_sum<kListWaves>(__popc(f), scratch);
+    const int p0 = (blockIdx.x - L.block0) * kCompactBlockElems + threadIdx.x * PER;
+    const uint32_t f = labels<PER>(L, mask_in, p0, a.vec_in != 0);
+    store_labels<PER>(L, p0, f);
+    const int total = block_sum<kThreadsOf<PER> / 64>(__popc(f), scratch);
     if (threadIdx.x == 0) block_counts[blockIdx.x] = total;
 }
 
 // ... then offsets and lists (labels from mask_out where the first launch left them)
-template <int NL>
-__global__ __launch_bounds__(kListThreads) void k_lists_scatter(ListArgs<NL> a, const uint8_t *__restrict__ mask_in,
-                                                                const int32_t *__restrict__ block_counts)
+template <int NL, int PER>
+__global__ __launch_bounds__(kThreadsOf<PER>) void k_lists_scatter(ListArgs<NL> a, const uint8_t *__restrict__ mask_in,
+                                                                   const int32_t *__restrict__ block_counts)
 {
-    __shared__ int wave_sum[kListWaves], scratch[kListWaves];
+    constexpr int W = kThreadsOf<PER> / 64;
+    __shared__ int wave_sum[W], scratch[W];
     __shared__ int32_t staged[kCompactBlockElems];
     const int tid = threadIdx.x;
     const LabelMap &L = a.at[NL == 1 ? 0 : list_of_block(a, blockIdx.x)];
-    const int p0 = (blockIdx.x - L.block0) * kCompactBlockElems + tid * 4;
+    const int p0 = (blockIdx.x - L.block0) * kCompactBlockElems + tid * PER;
     uint32_t f = 0;
     if (L.mask_out && p0 < L.m) {
         if (L.packed_out) {
-            f = (reinterpret_cast<const uint32_t *>(L.mask_out)[p0 >> 5] >> (p0 & 31)) & 15u; // (zeros past the end)
-        } else if (p0 + 4 <= L.m) {
-            const uint32_t v = *reinterpret_cast<const uint32_t *>(L.mask_out + p0); // bytes 0 / 1
-            f = (v & 1u) | ((v >> 7) & 2u) | ((v >> 14) & 4u) | ((v >> 21) & 8u);
+            f = (reinterpret_cast<const uint32_t *>(L.mask_out)[p0 >> 5] >> (p0 & 31)) & ((1u << PER) - 1u); // (zeros past the end)
+        } else if (p0 + PER <= L.m) {
+            auto four = [](uint32_t v) { return (v & 1u) | ((v >> 7) & 2u) | ((v >> 14) & 4u) | ((v >> 21) & 8u); }; // bytes 0 / 1
+            if constexpr (PER == 4) {
+                f = four(*reinterpret_cast<const uint32_t *>(L.mask_out + p0));
+            } else {
+                const uint4 v = *reinterpret_cast<const uint4 *>(L.mask_out + p0);
+                f = four(v.x) | (four(v.y) << 4) | (four(v.z) << 8) | (four(v.w) << 12);
+            }
         } else {
             for (int j = 0; p0 + j < L.m; ++j) f |= L.mask_out[p0 + j] ? 1u << j : 0u;
         }
     } else if (!L.mask_out) {
-        f = label4(L, mask_in, p0, a.vec_in != 0);
+        f = labels<PER>(L, mask_in, p0, a.vec_in != 0);
     }
     int part = 0;
-    for (int i = L.block0 + tid; i < (int)blockIdx.x; i += kListThreads) part += block_counts[i];
-    const int base = block_sum<kListWaves>(part, scratch);
-    const int total = store_list(L, p0, f, base, wave_sum, staged);
+    for (int i = L.block0 + tid; i < (int)blockIdx.x; i += kThreadsOf<PER>) part += block_counts[i];
+    const int base = block_sum<kThreadsOf<PER> / 64>(part, scratch);
+    const int total = store_list<PER>(L, p0, f, base, wave_sum, staged);
     if (tid == 0 && (int64_t)((int)blockIdx.x - L.block0 + 1) * kCompactBlockElems >= L.m) *L.count = base + total;
     if (NL == 1 && a.ex.zero && blockIdx.x == 0)
-        for (int i = tid; i < a.ex.zero_n; i += kListThreads) a.ex.zero[i] = 0;
+        for (int i = tid; i < a.ex.zero_n; i += kThreadsOf<PER>) a.ex.zero[i] = 0;
 }
 
 template <int NL>
 static hipError_t launch_lists_n(const ListArgs<NL> &a, const uint8_t *mask_in, int32_t *block_counts, hipStream_t s)
 {
-    bool once = true;
+    bool once = true, longer = false;
     for (int l = 0; l < a.lists; ++l) {
         const bool fast = a.at[l].identity && a.vec_in && !a.at[l].packed_in;
+        longer = longer || ((fast || (a.at[l].identity && a.at[l].packed_in)) && compact_blocks(a.at[l].m) > kLongBlocks);
         once = once && compact_blocks(a.at[l].m) <= (fast ? kOnceBlocksIdentity : kOnceBlocks);
     }
     if (once) {
         hipLaunchKernelGGL(k_lists_once<NL>, dim3(a.blocks), dim3(kListThreads), 0, s, a, mask_in);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL(k_lists_count<NL>, dim3(a.blocks), dim3(kListThreads), 0, s, a, mask_in, block_counts);
+    const int threads = longer ? kThreadsOf<16> : kThreadsOf<4>;
+    hipLaunchKernelGGL((longer ? k_lists_count<NL, 16> : k_lists_count<NL, 4>), dim3(a.blocks), dim3(threads), 0, s, a,
+                       mask_in, block_counts);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_lists_scatter<NL>, dim3(a.blocks), dim3(kListThreads), 0, s, a, mask_in,
-                       (const int32_t *)block_counts);
+    hipLaunchKernelGGL((longer ? k_lists_scatter<NL, 16> : k_lists_scatter<NL, 4>), dim3(a.blocks), dim3(threads), 0, s, a,
+                       mask_in, (const int32_t *)block_counts);
     return hipGetLastError();
 }
 

@@ -190,3 +190,41 @@ def test_pyramid_lists_around_the_one_launch_limits(n, h, w, first, packed):
         cnt = int(count.cpu().item())
         assert cnt == want_cnt
         np.testing.assert_array_equal(idx[:cnt].cpu().numpy(), want_idx)
+
+
+@pytest.mark.parametrize("n,h,w", [(1, 1280, 1280), (1, 1280, 1281), (3, 801, 701), (2, 1079, 1921)])
+@pytest.mark.parametrize("form", ["bytes", "bytes at an odd address", "bits out", "bits in and out", "strided"])
+def test_long_lists(n, h, w, form):
+    """Lists on both sides of 400 workgroups of 4096 positions (1 638 400), where a lane takes sixteen positions instead of
+    four: sizes off the sixteen and the 64-bit word, all input and output forms."""
+    torch = G.torch_mod()
+    mask = synth.mask_bernoulli(n, h, w, 0.5, 262, h, w) * np.uint8(3)
+    steps = [((3, 3), (2, 2), (1, 1), (1, 1)) if form == "strided" else ((3, 3), (1, 1), (1, 1), (1, 1)),
+             ((3, 3), (2, 1), (1, 1), (1, 1))]
+    md = G.mask_dev(mask)
+    if form == "bytes at an odd address":
+        room = torch.zeros((mask.size + 1,), dtype=torch.uint8, device=G.dev())
+        room[1:] = md.reshape(-1)
+        md = room[1:].view(n, h, w)
+    if form == "bits in and out":
+        pyr = B.PreparedPyramid(B.mask_pack(md), steps, packed=True, packed_in=True, shape=(n, h, w))
+    else:
+        pyr = B.PreparedPyramid(md, steps, packed=form == "bits out")
+    m = mask
+    for (m_out, idx, count), (k, s, p, d) in zip(pyr(), steps):
+        m = O.mask_downsample(m, k[0], k[1], s, p, d)
+        got = m_out.cpu().numpy()
+        if form.startswith("bits"):
+            got = got.view(np.uint8)
+            assert not np.unpackbits(got, bitorder="little")[m.size:(m.size + 63) // 64 * 64].any()
+            got = np.unpackbits(got, bitorder="little")[:m.size].reshape(m.shape)
+        np.testing.assert_array_equal(got, m)
+        want_idx, want_cnt = O.active_index_compact(m.reshape(-1))
+        cnt = int(count.cpu().item())
+        assert cnt == want_cnt
+        np.testing.assert_array_equal(idx[:cnt].cpu().numpy(), want_idx)
+    if form in ("bytes", "bits in and out"):     # one list by itself
+        want_idx, want_cnt = O.active_index_compact(mask.reshape(-1))
+        idx, count = B.active_index_compact(md) if form == "bytes" else B.active_index_compact_packed(B.mask_pack(md), mask.size)
+        assert int(count.cpu().item()) == want_cnt
+        np.testing.assert_array_equal(idx[:want_cnt].cpu().numpy(), want_idx)
