@@ -484,15 +484,15 @@ def pointwise_bench(torch, B, synth, workloads, args):
 def grouped_bench(torch, B, synth, workloads, args):
     """The 3x3 grouped layers of a ResNeXt-50 (32 groups of 4 to 32 channels), bf16, blob masks:
     per layer the focused call (list given) and the dense call, each as a HIP-graph replay of four
-    calls.  These layers run on the vector ALUs (fp32 multiply-adds), so the bound quoted is the
-    fp32 vector peak; their arithmetic intensity (a few dozen FLOP per byte) puts the memory
-    roofline far above what they reach."""
+    calls.  Their arithmetic intensity is a few dozen FLOP per byte and the matrix cores multiply nothing
+    but a group's own channels, so the bound quoted is memory traffic: algorithmic bytes = input mask, labels and
+    list + relevant input pixels once + weights and bias + every output row once."""
     irr = workloads.HEADLINE_IRRELEVANT if args.irrelevant is None else args.irrelevant
     n = 16 if args.batch is None else args.batch
     dev = torch.device("cuda:0")
     gen = synth.mask_bernoulli if args.mask == "bernoulli" else synth.mask_objects
     rows, t_f, t_d, fl_f, fl_d = [], 0.0, 0.0, 0.0, 0.0
-    t_mf = t_md = 0.0
+    t_mf = t_md = by_f = 0.0
     for li, (c, side) in enumerate(((128, 56), (256, 28), (512, 14), (1024, 7))):
         groups = 32
         x = synth.activations((n, side, side, c), synth.BF16, 8, li, 1)
@@ -529,13 +529,15 @@ def grouped_bench(torch, B, synth, workloads, args):
 
         tmf, tmd = timed_call(on_mfma_f), timed_call(on_mfma_d)
         per_pos = 2.0 * 9 * (c // groups) * c
-        ff, fd = float(np.count_nonzero(mask)) * per_pos, float(mask.size) * per_pos
-        rows.append({"layer": "c%d@%d/g%d" % (c, side, groups), "focused_us": round(tf * 1e6, 2),
+        kept = float(np.count_nonzero(mask))
+        ff, fd = kept * per_pos, float(mask.size) * per_pos
+        by = 2.0 * mask.size + 4.0 * kept + 2.0 * kept * c + 2.0 * w.size + 4.0 * c + 2.0 * mask.size * c
+        rows.append({"layer": "c%d@%d/g%d" % (c, side, groups), "focused_GBps": round(by / tf / 1e9, 1), "focused_us": round(tf * 1e6, 2),
                      "dense_us": round(td * 1e6, 2), "speedup": round(td / tf, 3),
                      "focused_TFLOPs": round(ff / tf / 1e12, 2), "dense_TFLOPs": round(fd / td / 1e12, 2),
                      "block_diagonal_on_matrix_cores_focused_us": round(tmf * 1e6, 2),
                      "block_diagonal_on_matrix_cores_dense_us": round(tmd * 1e6, 2)})
-        t_f, t_d, fl_f, fl_d = t_f + tf, t_d + td, fl_f + ff, fl_d + fd
+        t_f, t_d, fl_f, fl_d, by_f = t_f + tf, t_d + td, fl_f + ff, fl_d + fd, by_f + by
         t_mf, t_md = t_mf + tmf, t_md + tmd
         del xd, out, on_mfma_f, on_mfma_d
     print(json.dumps({
@@ -545,9 +547,9 @@ def grouped_bench(torch, B, synth, workloads, args):
         "speedup_vs_dense": round(t_d / t_f, 3),
         "block_diagonal_on_matrix_cores": {"focused_ms": round(t_mf * 1e3, 4), "dense_ms": round(t_md * 1e3, 4),
                                            "speedup_vs_dense": round(t_md / t_mf, 3)},
-        "roofline": {"bound": "alu", "achieved": round(fl_f / t_f / 1e12, 3), "peak": 157.3, "unit": "TFLOP/s",
-                     "frac": round(fl_f / t_f / 157.3e12, 4), "traffic": None},
-        "dense_TFLOPs": round(fl_d / t_d / 1e12, 2)}))
+        "roofline": {"bound": "hbm", "achieved": round(by_f / t_f / 1e9, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
+                     "frac": round(by_f / t_f / 1e9 / HBM_PEAK_GBPS, 4), "traffic": None},
+        "focused_TFLOPs": round(fl_f / t_f / 1e12, 2), "dense_TFLOPs": round(fl_d / t_d / 1e12, 2)}))
 
 
 def masks_bench(torch, B, synth, workloads, args):

@@ -324,7 +324,8 @@ int32_t fc_focused_gconv2d(const fc_conv_desc *desc, int32_t groups, const void 
  * w_grouped[c_out][kh][kw][c_in / groups], any storage type, both device.  With them
  * fc_focused_conv2d runs the grouped layer as a full one: the only way to run a grouped layer in
  * FC_FP8, and a fast one for channel counts per group that fc_focused_gconv2d leaves to the vector
- * ALUs (for the others, see there, fc_focused_gconv2d is the faster call).  Two things differ
+ * ALUs (for the others, see there, fc_focused_gconv2d is the faster call, but for layers of few
+ * channels with a kept list, where it is two launches).  Two things differ
  * from it: the terms outside the blocks are multiplied, so a value that is not finite reaches the
  * outputs of every group, and c_in and c_out count as those of a full layer.  Expand once when the
  * weights are loaded. */
