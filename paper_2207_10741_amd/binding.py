@@ -239,17 +239,28 @@ _WORKSPACE_STREAMS, _WORKSPACE_MOST = 4, 64 << 20
 _kept = threading.local()
 
 
-def _own_workspace(need: int, device, raw_stream: int):
+def _scratch(need: int, device, stream):
+    """Device scratch for a call on `stream` (None: the current one).  The allocator takes memory to belong to the
+    stream that is current when it is allocated: it is told where else it is used, or it would hand it out again
+    while the call still runs there."""
+    torch = _torch()
+    t = torch.empty((need,), dtype=torch.uint8, device=device)
+    if stream is not None:
+        t.record_stream(stream)
+    return t
+
+
+def _own_workspace(need: int, device, raw_stream: int, stream):
     torch = _torch()
     if need > _WORKSPACE_MOST or torch._C._cuda_isCurrentStreamCapturing():
-        return torch.empty((need,), dtype=torch.uint8, device=device)
+        return _scratch(need, device, stream)
     pool = _kept.__dict__
     key = (raw_stream, device)
     ws = pool.get(key)
     if ws is None or ws.numel() < need:
         if key not in pool and len(pool) >= _WORKSPACE_STREAMS:
             pool.clear()
-        ws = pool[key] = torch.empty((need,), dtype=torch.uint8, device=device)
+        ws = pool[key] = _scratch(need, device, stream)
     return ws
 
 
@@ -340,7 +351,7 @@ def active_index_compact_packed(bits, m: int, idx=None, count=None, workspace=No
     if count is None:
         count = torch.empty((1,), dtype=torch.int32, device=bits.device)
     if workspace is None:
-        workspace = torch.empty((compact_workspace_bytes(m),), dtype=torch.uint8, device=bits.device)
+        workspace = _scratch(compact_workspace_bytes(m), bits.device, stream)
     _check(lib().fc_active_index_compact_packed(_ptr(bits), m, _ptr(idx), _ptr(count), _ptr(workspace),
                                                 workspace.numel(), _stream(stream)), "fc_active_index_compact_packed")
     return idx, count
@@ -399,7 +410,7 @@ def active_index_compact(mask, idx=None, count=None, workspace=None, stream=None
     if count is None:
         count = torch.empty((1,), dtype=torch.int32, device=mask.device)
     if workspace is None:
-        workspace = torch.empty((compact_workspace_bytes(m),), dtype=torch.uint8, device=mask.device)
+        workspace = _scratch(compact_workspace_bytes(m), mask.device, stream)
     _check(lib().fc_active_index_compact(_ptr(mask), m, _ptr(idx), _ptr(count), _ptr(workspace),
                                          workspace.numel() * workspace.element_size(), _stream(stream)),
            "fc_active_index_compact")
@@ -418,7 +429,7 @@ def active_index_compact_tiled(mask, tile_h: int = 8, tile_w: int = 16, idx=None
     b = ctypes.c_size_t()
     _check(lib().fc_compact_tiled_workspace_bytes(n, ho, wo, tile_h, tile_w, ctypes.byref(b)),
            "fc_compact_tiled_workspace_bytes")
-    ws = torch.empty((max(int(b.value), 16),), dtype=torch.uint8, device=mask.device)
+    ws = _scratch(max(int(b.value), 16), mask.device, stream)
     _check(lib().fc_active_index_compact_tiled(_ptr(mask), n, ho, wo, tile_h, tile_w, _ptr(idx), _ptr(count),
                                                _ptr(ws), ws.numel(), _stream(stream)),
            "fc_active_index_compact_tiled")
@@ -434,7 +445,7 @@ def focused_conv2d(desc: ConvDesc, x, w, bias=None, mask_in=None, mask_out=None,
         out = x.new_empty(shape, dtype=dtype)
     raw = _stream(stream)
     if workspace is None and mask_in is not None and idx is None:
-        workspace = _own_workspace(need, x.device, raw)
+        workspace = _own_workspace(need, x.device, raw, stream)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     _check(lib().fc_focused_conv2d(ctypes.byref(desc), x.data_ptr(), _ptr(mask_in), w.data_ptr(), _ptr(bias),
                                    _ptr(mask_out), _ptr(idx), _ptr(count), out.data_ptr(), _ptr(workspace),
@@ -494,7 +505,7 @@ def focused_gconv2d(desc: ConvDesc, groups: int, x, w, bias=None, mask_in=None, 
         out = x.new_empty(shape, dtype=dtype)
     raw = _stream(stream)
     if workspace is None and mask_in is not None and idx is None:
-        workspace = _own_workspace(need, x.device, raw)
+        workspace = _own_workspace(need, x.device, raw, stream)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     _check(lib().fc_focused_gconv2d(ctypes.byref(desc), groups, x.data_ptr(), _ptr(mask_in), w.data_ptr(), _ptr(bias),
                                     _ptr(mask_out), _ptr(idx), _ptr(count), out.data_ptr(), _ptr(workspace),

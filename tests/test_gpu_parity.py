@@ -776,3 +776,33 @@ def test_list_that_ends_at_its_count(layer, dtype):
         trimmed = B.focused_conv2d(desc, x, wt, mask_in=md, mask_out=m_out, idx=idx[:kept].clone(), count=count,
                                    workspace=workspace)
         assert torch.equal(full, trimmed)
+
+
+def test_scratch_of_a_call_on_another_stream_is_not_handed_out_while_it_runs():
+    """Scratch that the binding allocates for a call on a given stream stays that call's until the stream gets there, also
+    when the kept workspace is dropped or replaced meanwhile."""
+    torch = G.torch_mod()
+    n, h, w, c = 2, 40, 48, 32
+    x = G.to_dev(synth.activations((n, h, w, c), synth.BF16, 242, 1), synth.BF16)
+    wt = G.to_dev(synth.he_weights(c, 1, 1, c, synth.BF16, 242, 2), synth.BF16)
+    md = G.mask_dev(synth.mask_objects(n, h, w, 0.5, 242, 4))
+    # (sizes of their own, so that the allocator has no other free block of the size)
+    desc = B.conv_desc(n, h, w, c, c, (1, 1), pad=(0, 0))
+    want = B.focused_conv2d(desc, x, wt, mask_in=md)
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    B._kept.__dict__.clear()
+    torch.cuda.empty_cache()
+    with torch.cuda.stream(side):
+        torch.cuda._sleep(200_000_000)      # (about a tenth of a second)
+    got = B.focused_conv2d(desc, x, wt, mask_in=md, stream=side)
+    (ws,) = B._kept.__dict__.values()
+    address, size = ws.data_ptr(), ws.numel()
+    del ws
+    B._kept.__dict__.clear()
+    other = torch.empty((size,), dtype=torch.uint8, device=G.dev())
+    assert not side.query()                 # the call has not run yet
+    assert other.data_ptr() != address
+    other.fill_(0xFF)
+    torch.cuda.synchronize()
+    assert torch.equal(got, want)
