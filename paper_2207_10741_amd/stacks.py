@@ -94,7 +94,8 @@ class _Plan:
         self.slots = ctypes.c_void_p * n_slots
         # A range is given out again some ops after its tensor's last reader while the arena stays inside the
         # chip's last cache level: writing over what the ops just before have read or written costs (MobileNetV2,
-        # batch 32: 425 us with ranges reused at once, 401 us six ops later).  A larger arena is packed tightly
+        # batch 32: 427 us with ranges reused at once, 403 us six ops later; after 512 MB of other data 458 and 437 us;
+        # the other networks within 1 % either way, warm and cold).  A larger arena is packed tightly
         # (ResNet-50 on 12 frames of 100 x 100: 711 us tight in 153 MB, 735 us in 322 MB).
         for rest in (12, 8, 6, 4, 2, 0):
             offsets, self.arena_bytes = _place(arena_ops, rest)
