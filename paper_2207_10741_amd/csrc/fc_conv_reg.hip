@@ -430,9 +430,9 @@ hipError_t launch_conv_f32(const Geom &g, const void *x, const uint8_t *mask_in,
 // from being the bound: 4 -> 4 channels on 16 x 56 x 56, half kept, is 0.4 us of them.  The halves of an
 // 8-channel piece are summed apart and added at the end (as one chain the error of 8 -> 8 f16 channels against 64-bit
 // sums is 7.4e-8 of the result, so 6.1e-8; products of 32 elements had 5.8e-8).  The four waves of a workgroup take the
-// quads of rows in turn.
+// quads of rows in turn.  (8 -> 8 in the window form below: two products of 16 channels instead.)
 // (With a mask / without one / with a list and no zero-fill, us: 128 channels in 32 groups on 16 x 56 x 56 12.6 / 12.8 /
-// 13.1, and at stride 2 9.2 / 8.4 / 8.8; 256 in 32 groups 22.4 / 25.2 / 23.1.  16-channel products with zero weights for the
+// 13.1, and at stride 2 9.2 / 8.4 / 8.8; 256 in 32 groups 21.8 / 24.4 / 23.0.  16-channel products with zero weights for the
 // foreign groups, which mixed groups as said above: 12.9 / 13.8 / 15.0, 10.0 / 9.6 / 9.9, 22.8 / 23.8 / 26.2.  On the vector
 // ALUs, with a compaction and a zero-fill launch, the first of these was 61 us.)
 // ---------------------------------------------------------------------------------------------
@@ -700,7 +700,9 @@ __global__ __launch_bounds__(kRegThreads, V * NL > 36 ? 1 : 2) void k_conv_group
 // Here the pixels under a span of 64 consecutive positions are, for every kernel row, one run of
 // 64 + (kw - 1) dil_w consecutive pixels: they are staged in LDS once (whole 128-byte pieces of 64 output
 // channels' groups), the workgroup's weights likewise, and all operands come from there; a gated tap
-// reads a piece of zeros.  V = 0: blocks of 16 channels, KS matrix steps.  V = 1, 2: quads of rows, 3x3 kernels and 4 V
+// reads a piece of zeros.  V = 0: blocks of 16 channels, KS matrix steps; NG = 2: a block of two groups of 8, a product for each
+// on the same weights, of which every lane keeps its own group's rows (256 channels in 32 groups on 16 x 56 x 56: 21.8 us with half
+// the pixels kept and 24.4 without a mask, as quads 22.4 and 25.2: those read a pixel's pieces twice).  V = 1, 2: quads of rows, 3x3 kernels and 4 V
 // input channels per group, so that a tap is one read; everything about the reads is fixed when the kernel is compiled
 // (a pixel's pieces 1 << LG, its kernel row's line), because what a quad costs is the instructions of its addresses: with
 // the line's length and the taps at run time the kernel took 17.8 us where it now takes 12.5 (4 -> 4 channels on 16 x 56 x 56, half kept).
@@ -713,7 +715,7 @@ struct WindowCut {
     FastDiv by_line, by_kw, by_ppt;
 };
 
-template <int DT, typename TO, int V, int KS, int LG>
+template <int DT, typename TO, int V, int KS, int LG, int NG = 1>
 __global__ __launch_bounds__(kRegThreads, 2) void k_conv_grouped_window(
     Geom g, WindowCut cut, int cig, int cog, const uint16_t *__restrict__ x, const uint8_t *__restrict__ mask_in,
     const uint8_t *__restrict__ mask_out, const uint16_t *__restrict__ w, const float *__restrict__ bias,
@@ -810,9 +812,9 @@ __global__ __launch_bounds__(kRegThreads, 2) void k_conv_grouped_window(
         if (co0 >= g.c_out) return;
         // ---- this wave's 16 channels: weights from LDS to registers, and where their pieces lie ----
         const int ppt = cig >> 3;
-        const int bw0 = (co0 / cog) * cig; // first input channel of the block's group
+        const int bw0 = (co0 / cog) * cig; // first input channel of the block's first group
         const int co = co0 + col;
-        u32x4_t wf[KS];
+        u32x4_t wf[KS];    // of the channel's own group
         int xq[KS];        // pixel slot of the piece from the position's own slot
         uint32_t xc[KS], xsel[KS];
 #pragma unroll
@@ -832,16 +834,28 @@ __global__ __launch_bounds__(kRegThreads, 2) void k_conv_grouped_window(
             const bool live = r0 + col < n;
             const int j = live ? order_s[r0 + col] : 0;
             const uint32_t bits = live ? bits_s[j] : 0u;
-            u32x4_t xv[KS];
+            // a product per group: rows of the other group come out as anything and are dropped
+            u32x4_t xv[NG][KS];
 #pragma unroll
             for (int s = 0; s < KS; ++s) {
                 const uint32_t q = (uint32_t)(j + xq[s]);
-                const uint32_t at = ((q << cut.lg_pieces) + ((xc[s] ^ (uint32_t)swizzle((int)q)) & pmask)) * 16u;
-                xv[s] = *reinterpret_cast<const u32x4_t *>(lds + ((bits & xsel[s]) ? at : zero_at));
-            }
-            f32x4_t acc = {bq.x, bq.y, bq.z, bq.w};
 #pragma unroll
-            for (int s = 0; s < KS; ++s) acc = mfma16<DT>(wf[s], xv[s], acc);
+                for (int k = 0; k < NG; ++k) {
+                    const uint32_t c = xc[s] + (uint32_t)(k * ppt);
+                    const uint32_t at = ((q << cut.lg_pieces) + ((c ^ (uint32_t)swizzle((int)q)) & pmask)) * 16u;
+                    xv[k][s] = *reinterpret_cast<const u32x4_t *>(lds + ((bits & xsel[s]) ? at : zero_at));
+                }
+            }
+            f32x4_t of[NG];
+#pragma unroll
+            for (int k = 0; k < NG; ++k) {
+                of[k] = f32x4_t{bq.x, bq.y, bq.z, bq.w};
+#pragma unroll
+                for (int s = 0; s < KS; ++s) of[k] = mfma16<DT>(wf[s], xv[k][s], of[k]);
+            }
+            f32x4_t acc;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[i] = NG == 1 || quarter < 2 ? of[0][i] : of[NG - 1][i];
             if (g.flags & FC_RELU) relu4(acc);
             if (live)
                 store4<DT, TO>(out + (int64_t)(first + j) * g.c_out + co0 + quarter * 4, acc[0], acc[1], acc[2], acc[3]);
@@ -938,14 +952,15 @@ static hipError_t launch_grouped(const Geom &g, int groups, const void *x, const
     const int cig = g.c_in / groups, cog = g.c_out / groups, taps = g.kh * g.kw, steps = grouped_steps(g, cig, cog);
     const bool quads = cog < 16;
     const int v = cig % 8 == 0 ? 2 : 1; // quads: 4-channel pieces of a load
+    const bool pairs = cog == 8 && v == 2; // windows: two groups of a 16-channel block
     // spans of positions as windows of pixels: unit stride, same size, no list, groups that do not straddle a
     // workgroup's 64 channels and whose channels make a power of two of 16-byte pieces, at most 64 KB of LDS; quads: what
     // their form is compiled for
     const int wch = cog <= 64 && 64 % cog == 0 ? 64 / cog * cig : 0;
     if (!idx && g.sh == 1 && g.sw == 1 && g.ho == g.h && g.wo == g.w && wch >= 32 && wch <= 128 && (wch & (wch - 1)) == 0 &&
-        (quads ? g.kh == 3 && g.kw == 3 && g.dw == 1 && cig == 4 * v : steps <= 9)) {
+        (pairs || !quads ? steps <= 9 : g.kh == 3 && g.kw == 3 && g.dw == 1 && cig == 4 * v)) {
         WindowCut cut;
-        cut.line = quads ? kQuadLine : kWindowSpan + (g.kw - 1) * g.dw;
+        cut.line = quads && !pairs ? kQuadLine : kWindowSpan + (g.kw - 1) * g.dw;
         cut.lg_pieces = wch == 32 ? 2 : (wch == 64 ? 3 : 4);
         cut.x_bytes = (g.kh * cut.line * wch * 2 + 1023) & ~1023;
         cut.w_bytes = (64 * taps * cig * 2 + 1023) & ~1023;
@@ -954,10 +969,11 @@ static hipError_t launch_grouped(const Geom &g, int groups, const void *x, const
         cut.by_ppt = make_fastdiv((uint32_t)(cig >= 8 ? cig / 8 : 1));
         const int bytes = cut.x_bytes + cut.w_bytes + 16 + kWindowSpan * 5;
         if (bytes <= 64 * 1024) {
-            // (quads: 4 -> 8, 4 -> 4, 8 -> 8, 8 -> 4 channels per group)
-            auto kern = !quads ? (steps <= 5 ? k_conv_grouped_window<DT, TO, 0, 5, 0> : k_conv_grouped_window<DT, TO, 0, 9, 0>)
+            // (quads: 4 -> 8, 4 -> 4, 8 -> 4 channels per group)
+            auto kern = pairs ? (taps * cig <= 96 ? k_conv_grouped_window<DT, TO, 0, 3, 0, 2> : k_conv_grouped_window<DT, TO, 0, 5, 0, 2>)
+                        : !quads ? (steps <= 5 ? k_conv_grouped_window<DT, TO, 0, 5, 0> : k_conv_grouped_window<DT, TO, 0, 9, 0>)
                         : v == 1 ? (cog == 8 ? k_conv_grouped_window<DT, TO, 1, 9, 2> : k_conv_grouped_window<DT, TO, 1, 9, 3>)
-                                 : (cog == 8 ? k_conv_grouped_window<DT, TO, 2, 9, 3> : k_conv_grouped_window<DT, TO, 2, 9, 4>);
+                                 : k_conv_grouped_window<DT, TO, 2, 9, 4>;
             hipLaunchKernelGGL(kern, dim3((g.m + kWindowSpan - 1) / kWindowSpan, (g.c_out + 63) / 64), dim3(kRegThreads), bytes, s,
                                g, cut, cig, cog, (const uint16_t *)x, mask_in, mask_out, (const uint16_t *)w, bias, (TO *)out);
             return hipGetLastError();
