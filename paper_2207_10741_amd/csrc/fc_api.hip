@@ -332,8 +332,10 @@ int32_t fc_focused_conv2d(const fc_conv_desc *desc, const void *x, const uint8_t
     }
     const bool room = tile_counters != nullptr;
     const bool small = mfma && conv_small_wanted(g, desc->in_dtype, room, mask_in && !idx);
-    // (a layer whose reduction is not split leaves the counters alone)
-    bool counters_cleared = small ? !conv_small_counts(g, room) : !split_k_reachable(g, desc->in_dtype);
+    // (a layer whose reduction is not split leaves the counters alone; without a mask the row count, and with it
+    // the number of splits, is known here)
+    bool counters_cleared = small ? !conv_small_counts(g, room)
+                                  : !split_k_reachable(g, desc->in_dtype) || (!mask_in && !dense_layer_splits(g, desc->in_dtype));
     const bool f32 = desc->in_dtype == FC_F32 && conv_f32_supported(g);
 
     if (mask_in && !idx) {
@@ -348,9 +350,12 @@ int32_t fc_focused_conv2d(const fc_conv_desc *desc, const void *x, const uint8_t
         // Labels the caller brings (mask_out without a list) are compacted as they are, so that
         // the rows computed and the rows cleared follow the same labels.
         // The fp32 kernel and the one for small layers label their rows themselves, whatever the labels' source.
-        const bool rank_in_kernel = f32 || small || (mfma && g.m <= kInlineRankPositions && !mask_out) ||
-                                    (mfma && tiles_label_rows(g, desc->in_dtype) &&
-                                     !conv_line_wanted(g, desc->in_dtype, desc->out_dtype, true));
+        const bool own_tiles = mfma && !small && tiles_label_rows(g, desc->in_dtype) &&
+                               !conv_line_wanted(g, desc->in_dtype, desc->out_dtype, true);
+        // (such tiles are never split: the launch that clears the counters was 1.4 us and the gap behind it 1.6 us of
+        // the 13.7 us a 72 -> 200 layer on 3 x 75 x 101 took)
+        if (own_tiles) counters_cleared = true;
+        const bool rank_in_kernel = f32 || small || (mfma && g.m <= kInlineRankPositions && !mask_out) || own_tiles;
         if (!rank_in_kernel) {
             CompactExtras ex;
             if (tile_counters && !counters_cleared) {

@@ -947,6 +947,22 @@ bool tiles_label_rows(const Geom &g, int in_dtype)
     return tiles <= kSplitGrid && tiles * 9 * chunks <= 20 * kSplitGrid;
 }
 
+// (the tile launch_tile takes for a layer that may split, and the split of all of the layer's rows)
+bool dense_layer_splits(const Geom &g, int in_dtype)
+{
+    const int64_t rows128 = (g.m + 127) / 128, tiles128 = rows128 * ((g.c_out + 127) / 128);
+    int64_t tiles = rows128 * ((g.c_out + 63) / 64);
+    if (tiles <= kSmallLayerTiles && g.kh * g.kw != 1 && !(g.kh == 3 && g.kw == 3)) {
+        // (any kernel size but 1x1 and 3x3 stays on 128 x 64 tiles)
+    } else if (tiles <= kSmallLayerTiles) {
+        tiles = (int64_t)((g.m + 63) / 64) * ((g.c_out + 63) / 64);
+    } else if (g.kh == 1 && g.kw == 1 && g.c_out > 64 && tiles128 >= 256) {
+        tiles = tiles128;
+    }
+    const int stages = g.kh * g.kw * ((g.c_in * (in_dtype == FC_FP8 ? 1 : 2) + 127) / 128);
+    return split_k_splits((int)tiles, kSplitGrid, stages, stages) > 1;
+}
+
 bool conv_mfma_supported(const Geom &g, int in_dtype, int out_dtype)
 {
     if (in_dtype != FC_BF16 && in_dtype != FC_F16 && in_dtype != FC_FP8) return false;

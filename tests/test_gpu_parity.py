@@ -596,6 +596,33 @@ def test_workspace_ready_flag_skips_the_clear_and_leaves_the_counters_zero():
         assert not ws[:B.WORKSPACE_COUNTER_BYTES].any()
 
 
+@pytest.mark.parametrize("layer,masked", [
+    # n, h, w, ci, co, k, s, p, d: split or not by the dense row count, on either side of the rule's lines
+    ((3, 75, 101, 72, 200, 3, 2, 1, 1), True),       # tiles that label their rows: never split
+    ((2, 40, 48, 128, 128, 3, 1, 1, 1), False),      # 60 tiles of 64 x 64 (30 of 128 x 64), 18 stages: split
+    ((4, 40, 48, 128, 128, 3, 1, 1, 1), False),      # 120 tiles of 128 x 64: eight stages each, split
+    ((5, 40, 48, 128, 128, 3, 1, 1, 1), False),      # 150 tiles: a busy chip, 18 stages stay whole
+    ((5, 40, 48, 512, 128, 3, 1, 1, 1), False),      # the same, 72 stages: split
+    ((9, 40, 48, 512, 128, 3, 1, 1, 1), False),      # 270 tiles: more than half the grid, whole
+    ((1, 30, 34, 64, 128, 5, 1, 2, 1), False),       # another kernel size
+    ((8, 32, 32, 2048, 512, 1, 1, 0, 1), False),     # 1x1, 256 tiles of 128 x 128: split in two
+    ((8, 32, 30, 2048, 512, 1, 1, 0, 1), False),     # 1x1, 240 of them: 480 tiles of 128 x 64, whole
+])
+def test_counters_with_garbage_are_cleared_where_a_reduction_is_split(layer, masked):
+    """A workspace that was never cleared: the same bits as with cleared counters, on every kind of call that may
+    leave the clearing launch out."""
+    torch = G.torch_mod()
+    n, h, w, ci, co, k, s, p, d = layer
+    x = G.to_dev(synth.activations((n, h, w, ci), synth.BF16, 252, 1), synth.BF16)
+    wt = G.to_dev(synth.he_weights(co, k, k, ci, synth.BF16, 252, 2), synth.BF16)
+    md = G.mask_dev(synth.mask_objects(n, h, w, 0.48, 252, 4)) if masked else None
+    desc = B.conv_desc(n, h, w, ci, co, (k, k), (s, s), (p, p), (d, d), synth.BF16, B.F32, B.RELU)
+    ws = torch.zeros((B.workspace_bytes(desc),), dtype=torch.uint8, device=G.dev())
+    want = B.focused_conv2d(desc, x, wt, mask_in=md, workspace=ws)
+    ws.fill_(0xAB)
+    assert torch.equal(B.focused_conv2d(desc, x, wt, mask_in=md, workspace=ws), want)
+
+
 def test_two_runs_are_bit_identical():
     torch = G.torch_mod()
     a, _, _ = _run_layer(2, 28, 28, 128, 128, 3, 1, 1, 1, synth.BF16, seed=208)
