@@ -81,24 +81,32 @@ bool conv_line_wanted(const Geom &g, int in_dtype, int out_dtype, bool focused)
     return (int64_t)(g.m + 31) / 32 <= 8 * 256;
 }
 
-// 3x3 layers of 128-byte pixels (64 16-bit channels) into at most 64 channels (the first stage of ResNet-18/34 and the 3x3
-// of a ResNet-50's first stage, VGG's conv1_2): the nine taps' weights (72 KB) stay in LDS and
-// every wave runs its own pipeline, against 128-row tiles that stage the weights again for every
-// tile.  Measured against the tiled kernel at 48 % irrelevant pixels on 50 000 .. 2.5 M
-// positions: without a mask 12 .. 25 % faster up to 0.6 M positions (6 % slower at 2.5 M);
-// chained (no zero-fill) equal at 50 000, 1 .. 17 % faster from 100 000 on; with zero-fill 4 .. 7 %
-// slower up to 0.4 M (the zero-fill comes after a wave's units instead of between tiles).  From 0.5 M on, 30 .. 70 %
-// irrelevant, on inputs that are not in the last cache level already, 3 .. 18 % faster at each of 14 sizes up to 16.6 M
-// (0.5 M 55 against 47 us, 1.0 M 105 / 92, 2.1 M 199 / 185, 2.8 M 256 / 242, 4.1 M 366 / 344, 16.6 M 1 354 / 1 307); called again
-// and again on one input, of which up to 256 MB are then in that level, the tiled kernel gets more out of it: 2 .. 7 % faster
-// from 2.1 to 2.8 M, even at 3.7 M.  Into 128 channels the tiled kernels win or draw.  128 8-bit
-// channels into 64 follow the same pattern (2.1 M positions: 198 / 176 us; 0.6 M: 25 .. 28 % faster in all three modes).
-static bool conv_pw_wanted_3x3(const Geom &g, bool masked)
+// 3x3 layers of 128-byte pixels (64 channels of a 16-bit type, 128 of the 8-bit one): the first stage of ResNets, VGG's
+// conv1_2 and conv2_1.  With a unit horizontal step they run on k_conv_res3 (fc_conv_res.hip) from 12 000 positions
+// on.  Measured against the tiled kernels (dense / zero-filled / chained, us, tiled -> here; 48 % irrelevant, list given):
+// 64 -> 64 on 32 x 28 x 28 9.5 / 9.7 / 9.5 -> 8.6 / 10.1 / 9.8 (30 % irrelevant, zero-filled: 9.9 -> 8.6), 32 x 56 x 56 15.3 / 12.1 /
+// 10.3 -> 15.5 / 10.1 / 10.0, 16 x 128 x 128 zero-filled 24.7 -> 21.3, 8 x 540 x 960 dense 470 -> 388; 64 -> 128 on 16 x 120 x 160
+// 64.1 / 40.3 / 36.1 -> 58.2 / 34.4 / 34.1, 8 x 540 x 960 736 / 487 / 407 -> 709 / 439 / 388; 64 -> 256 on 16 x 120 x 160 120 / 78 -> 115 /
+// 63; E4M3 128 -> 128 on 32 x 60 x 80 33.3 / 23.2 / 22.7 -> 31.5 / 22.0 / 21.7, 8 x 224 x 224 78.5 / 51.6 / 47.2 -> 72.5 / 43.3 / 43.5.
+// Where its 32-row blocks come to one and a half per wave (two slices at 100 000 positions) the tiled kernel is up to 5 %
+// faster on inputs already in the caches, and neither on others; below 12 000 positions the weights (72 KB a workgroup)
+// are too much to fetch for the rows: 8 x 28 x 28 8.1 -> 9.0.
+//
+// Other steps and dilations take the tap-by-tap form of the resident-weights kernel, into at most 64 channels, along the
+// lines measured on that form: without a mask 12 .. 25 % faster than the tiled kernel up to 0.6 M positions and 6 % slower at
+// 2.5 M; chained equal at 50 000, 1 .. 17 % faster from 100 000 on; with zero-fill 4 .. 7 % slower up to 0.4 M and
+// 3 .. 18 % faster from 0.5 M on.
+static bool conv_taps_wanted(const Geom &g, bool masked)
 {
     if (g.c_out > 64) return false;
     if (!masked) return g.m >= 40000 && g.m < 1500000;
     if (g.flags & (FC_SKIP_ZERO_FILL | FC_COMPACT_OUT)) return g.m >= 80000;
     return g.m >= 500000;
+}
+
+static bool conv_pw_wanted_3x3(const Geom &g, bool masked)
+{
+    return conv_res3_supported(g) ? g.m >= 12000 && g.c_out <= 256 : conv_taps_wanted(g, masked);
 }
 
 // Does the resident-weights kernel serve this layer?  1x1 layers without padding whose rows are whole
@@ -149,6 +157,11 @@ ConvWorkspace conv_ws_layout(const Geom &g)
 }
 
 } // namespace
+
+bool fc::conv_taps_bias_last(const Geom &g, bool masked)
+{
+    return (g.flags & FC_RESIDENT_WEIGHTS) || conv_taps_wanted(g, masked);
+}
 
 extern "C" {
 
@@ -395,8 +408,7 @@ int32_t fc_focused_conv2d(const fc_conv_desc *desc, const void *x, const uint8_t
         e = launch_conv_small(g, desc->in_dtype, desc->out_dtype, room, x, mask_in, mask_out, w, bias, idx, count, out,
                               partials, tile_counters, s);
         if (e != hipSuccess) return FC_ERR_HIP;
-    } else if (mfma && idx && !(pw && (g.flags & FC_RESIDENT_WEIGHTS)) &&
-        conv_line_wanted(g, desc->in_dtype, desc->out_dtype, mask_in != nullptr)) {
+    } else if (mfma && idx && !pw && conv_line_wanted(g, desc->in_dtype, desc->out_dtype, mask_in != nullptr)) {
         e = launch_conv_line(g, desc->in_dtype, desc->out_dtype, x, mask_in, mask_out, w, bias, idx, count, out, s);
         if (e != hipSuccess) return FC_ERR_HIP;
     } else if (pw) {

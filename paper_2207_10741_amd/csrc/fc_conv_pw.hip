@@ -27,7 +27,7 @@
 // chunk t the pixel under tap t, slices of 64 output channels (72 KB of weights).  A tap outside
 // the image or under an irrelevant pixel is not read (its chunk arrives as zeros): the mask bytes
 // under the nine taps of a unit's rows are fetched into LDS a unit ahead, and every gathered row
-// carries a nine-bit set of the taps it reads.  Any stride, padding and dilation.
+// carries a nine-bit set of the taps it reads.  (Layers with a unit horizontal step have a kernel of their own, k_conv_res3.)
 #include "fc_dma_util.hpp"
 #include <atomic>
 
@@ -43,57 +43,6 @@ constexpr uint32_t pw_wave_bytes_of(int ring, int taps) { return pw_wave_bytes(r
 struct PwDivs {
     FastDiv wo, ho, cpr; // output width, output height, 16-byte pieces per output row
 };
-
-__device__ __forceinline__ void pw_dma_load4(const u32x4_t &rsrc, uint32_t byte_offset, uint32_t lds_addr)
-{
-    __asm__ volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds"
-                     :
-                     : "s"(lds_addr), "v"(byte_offset), "s"(rsrc)
-                     : "memory");
-}
-
-// one byte per lane, zero-extended into the lane's dword of LDS (out of range: zero)
-__device__ __forceinline__ void pw_dma_load1(const u32x4_t &rsrc, uint32_t byte_offset, uint32_t lds_addr)
-{
-    __asm__ volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_ubyte %1, %2, 0 offen lds"
-                     :
-                     : "s"(lds_addr), "v"(byte_offset), "s"(rsrc)
-                     : "memory");
-}
-
-// s_waitcnt takes its count as an immediate, and n (wave-uniform) is known at run time only: a
-// jump into a table of 16 waits for the even counts 0 .. 30 (each followed by a branch to the
-// end), taking the largest even count that is not above n.
-#define FC_WJ(k) "s_waitcnt vmcnt(" #k ")\n\ts_branch 1f\n\t"
-__device__ __forceinline__ void pw_wait_vmcnt(int n)
-{
-    // the table starts 12 bytes after the address s_getpc_b64 returns; an entry is 8 bytes
-    // (n is wave-uniform; the scalar operand below must not be handed a vector register)
-    const uint32_t off = (uint32_t)(min(__builtin_amdgcn_readfirstlane(n), 30) >> 1) * 8u + 12u;
-    __asm__ volatile("s_getpc_b64 vcc\n\t"
-                     "s_add_u32 vcc_lo, vcc_lo, %0\n\t"
-                     "s_addc_u32 vcc_hi, vcc_hi, 0\n\t"
-                     "s_setpc_b64 vcc\n\t"
-                     FC_WJ(0) FC_WJ(2) FC_WJ(4) FC_WJ(6) FC_WJ(8) FC_WJ(10) FC_WJ(12) FC_WJ(14)
-                     FC_WJ(16) FC_WJ(18) FC_WJ(20) FC_WJ(22) FC_WJ(24) FC_WJ(26) FC_WJ(28) FC_WJ(30)
-                     "1:"
-                     :
-                     : "s"(off)
-                     : "vcc", "scc", "memory");
-}
-#undef FC_WJ
-
-// Before a load into LDS is issued: every LDS read this wave has issued has returned.  The reads
-// of the area the load overwrites come earlier in program order, but issued is not done: the
-// compiler places the matrix instructions that wait for them after the (asynchronous, to it
-// opaque) load, and the LDS queue of a workgroup whose waves all read weights can hold a read
-// back for longer than a load that hits in the cache takes to come back.  Measured before this
-// wait was there: in about one launch of ten of a 512 -> 2048 layer one unit's last k-step of a
-// chunk was multiplied with the data of the chunk two stages later, on a prefix of its rows.
-__device__ __forceinline__ void pw_lds_reads_done()
-{
-    __asm__ volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-}
 
 // DT: storage type (bf16 / f16 / E4M3); TO: float or the 16-bit / 8-bit carrier of the output;
 // NCB: 32-channel blocks of a workgroup's slice of the output channels; KCT: the number of
@@ -173,7 +122,7 @@ void k_conv_pw(Geom g, PwDivs dv, int kch_arg, const unsigned char *__restrict__
         // the bias (channels past the last one, and a layer without one: zeros)
         const u32x4_t rsrc_b = make_rsrc_words(bias, bias ? (uint32_t)g.c_out * 4u : 0u);
         for (int ii = wave; ii < COUT / 64; ii += nw)
-            pw_dma_load4(rsrc_b, (uint32_t)(co0 + ii * 64 + lane) * 4u, lds0 + wbytes + (uint32_t)ii * 256u);
+            dma_load4(rsrc_b, (uint32_t)(co0 + ii * 64 + lane) * 4u, lds0 + wbytes + (uint32_t)ii * 256u);
     }
     // (nobody waits for them here: they travel while the first units' rows are looked up and sent for)
 
@@ -207,8 +156,8 @@ void k_conv_pw(Geom g, PwDivs dv, int kch_arg, const unsigned char *__restrict__
     auto issue_idx = [&](int v) {
         if (!use_list) return;
         const uint32_t r = (uint32_t)(b0 + v) * 32u + (uint32_t)lane;
-        pw_lds_reads_done();
-        pw_dma_load4(rsrc_i, lane < 32 ? r * 4u : kOutOfRange, my0 + RING * kPwChunkBytes);
+        lds_reads_done();
+        dma_load4(rsrc_i, lane < 32 ? r * 4u : kOutOfRange, my0 + RING * kPwChunkBytes);
         issued += 1;
         mark_idx = issued;
     };
@@ -246,7 +195,7 @@ void k_conv_pw(Geom g, PwDivs dv, int kch_arg, const unsigned char *__restrict__
         const bool valid = r < rows;
         int p = r;
         if (use_list) {
-            pw_wait_vmcnt(issued - mark_idx);
+            wait_vmcnt_upto(issued - mark_idx);
             p = idx_w[l32];
         }
         st_pn = valid ? p : -1;
@@ -255,11 +204,11 @@ void k_conv_pw(Geom g, PwDivs dv, int kch_arg, const unsigned char *__restrict__
             const int ow = (valid ? p : 0) - q1 * g.wo;
             const int n = (int)fast_div((uint32_t)q1, dv.ho);
             const int oh = q1 - n * g.ho;
-            pw_lds_reads_done();
+            lds_reads_done();
 #pragma unroll
             for (int q = 0; q < 5; ++q) {
                 const int px = valid ? tap_pixel(n, oh, ow, 2 * q + half) : -1;
-                pw_dma_load1(rsrc_m, px < 0 ? kOutOfRange : (uint32_t)(packed_masks ? px >> 3 : px), mask0 + (uint32_t)q * 256u);
+                dma_load1(rsrc_m, px < 0 ? kOutOfRange : (uint32_t)(packed_masks ? px >> 3 : px), mask0 + (uint32_t)q * 256u);
             }
             issued += 5;
             mark_m = issued;
@@ -277,7 +226,7 @@ void k_conv_pw(Geom g, PwDivs dv, int kch_arg, const unsigned char *__restrict__
             // this lane's taps (2q + half): inside the image, and relevant
             uint32_t bits = 0;
             if (mask_in) {
-                pw_wait_vmcnt(issued - mark_m);
+                wait_vmcnt_upto(issued - mark_m);
             }
 #pragma unroll
             for (int q = 0; q < 5; ++q) {
@@ -307,7 +256,7 @@ void k_conv_pw(Geom g, PwDivs dv, int kch_arg, const unsigned char *__restrict__
         const bool valid = r < rows;
         int p = r;
         if (use_list) {
-            pw_wait_vmcnt(issued - mark_idx);
+            wait_vmcnt_upto(issued - mark_idx);
             p = idx_w[l32];
         }
         int pix = p;
@@ -332,7 +281,7 @@ void k_conv_pw(Geom g, PwDivs dv, int kch_arg, const unsigned char *__restrict__
     };
     // one stage: chunk c of the unit with state k, into ring buffer `buf`
     auto issue_x = [&](int k, int c, int buf) {
-        pw_lds_reads_done();
+        lds_reads_done();
         if constexpr (TAPS == 9) {
             // chunk c is the pixel under tap c: the row's origin + (kh dil_h W + kw dil_w) pixels
             const int kh = (c * 11) >> 5, kw = c - kh * 3;
@@ -483,7 +432,7 @@ void k_conv_pw(Geom g, PwDivs dv, int kch_arg, const unsigned char *__restrict__
     }
     // the workgroup's weights and bias have landed: this wave's were requested before everything counted in
     // `issued` (one round trip less in front of the first unit: 64 -> 384 channels on 32 x 14 x 14 8.2 us)
-    pw_wait_vmcnt(issued);
+    wait_vmcnt_upto(issued);
     __syncthreads();
     f32x16_t acc[GB];
     int buf = 0;
@@ -511,7 +460,7 @@ void k_conv_pw(Geom g, PwDivs dv, int kch_arg, const unsigned char *__restrict__
                 }
                 issue_x(1, 0, bufn);
             }
-            pw_wait_vmcnt(issued - (buf == 0 ? mark_x[0] : mark_x[1]));
+            wait_vmcnt_upto(issued - (buf == 0 ? mark_x[0] : mark_x[1]));
             const unsigned char *xs = my + (size_t)buf * kPwChunkBytes;
             Frag<DT> xf[KK];
 #pragma unroll
@@ -722,6 +671,8 @@ hipError_t launch_conv_pw(const Geom &g, int in_dtype, int out_dtype, const void
                           const uint8_t *mask_out, const void *w, const float *bias, const int32_t *idx,
                           const int32_t *count, void *out, hipStream_t s)
 {
+    if (conv_res3_supported(g))
+        return launch_conv_res3(g, in_dtype, out_dtype, pw_grid(), conv_taps_bias_last(g, mask_in != nullptr), x, mask_in, mask_out, w, bias, idx, count, out, s);
 #define FC_PW_CALL(DT, TO) launch_pw_shape<DT, TO>(g, x, mask_in, mask_out, w, bias, idx, count, out, s)
     if (in_dtype == FC_BF16) {
         if (out_dtype == FC_F32) return FC_PW_CALL(FC_BF16, float);

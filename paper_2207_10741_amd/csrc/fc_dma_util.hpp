@@ -58,4 +58,56 @@ __device__ __forceinline__ void wait_vmcnt()
     __asm__ volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
 }
 
+// one dword per lane
+__device__ __forceinline__ void dma_load4(const u32x4_t &rsrc, uint32_t byte_offset, uint32_t lds_addr)
+{
+    __asm__ volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds"
+                     :
+                     : "s"(lds_addr), "v"(byte_offset), "s"(rsrc)
+                     : "memory");
+}
+
+// one byte per lane, zero-extended into the lane's dword of LDS (out of range: zero)
+__device__ __forceinline__ void dma_load1(const u32x4_t &rsrc, uint32_t byte_offset, uint32_t lds_addr)
+{
+    __asm__ volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_ubyte %1, %2, 0 offen lds"
+                     :
+                     : "s"(lds_addr), "v"(byte_offset), "s"(rsrc)
+                     : "memory");
+}
+
+// s_waitcnt takes its count as an immediate, and n (wave-uniform) is known at run time only: a
+// jump into a table of 16 waits for the even counts 0 .. 30 (each followed by a branch to the
+// end), taking the largest even count that is not above n.
+#define FC_WJ(k) "s_waitcnt vmcnt(" #k ")\n\ts_branch 1f\n\t"
+__device__ __forceinline__ void wait_vmcnt_upto(int n)
+{
+    // the table starts 12 bytes after the address s_getpc_b64 returns; an entry is 8 bytes
+    // (n is wave-uniform; the scalar operand below must not be handed a vector register)
+    const uint32_t off = (uint32_t)(min(__builtin_amdgcn_readfirstlane(n), 30) >> 1) * 8u + 12u;
+    __asm__ volatile("s_getpc_b64 vcc\n\t"
+                     "s_add_u32 vcc_lo, vcc_lo, %0\n\t"
+                     "s_addc_u32 vcc_hi, vcc_hi, 0\n\t"
+                     "s_setpc_b64 vcc\n\t"
+                     FC_WJ(0) FC_WJ(2) FC_WJ(4) FC_WJ(6) FC_WJ(8) FC_WJ(10) FC_WJ(12) FC_WJ(14)
+                     FC_WJ(16) FC_WJ(18) FC_WJ(20) FC_WJ(22) FC_WJ(24) FC_WJ(26) FC_WJ(28) FC_WJ(30)
+                     "1:"
+                     :
+                     : "s"(off)
+                     : "vcc", "scc", "memory");
+}
+#undef FC_WJ
+
+// Before a load into LDS is issued: every LDS read this wave has issued has returned.  The reads
+// of the area the load overwrites come earlier in program order, but issued is not done: the
+// compiler places the matrix instructions that wait for them after the (asynchronous, to it
+// opaque) load, and the LDS queue of a workgroup whose waves all read weights can hold a read
+// back for longer than a load that hits in the cache takes to come back.  Measured before this
+// wait was there: in about one launch of ten of a 512 -> 2048 layer one unit's last k-step of a
+// chunk was multiplied with the data of the chunk two stages later, on a prefix of its rows.
+__device__ __forceinline__ void lds_reads_done()
+{
+    __asm__ volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+}
+
 } // namespace fc

@@ -392,6 +392,17 @@ hipError_t launch_conv_small(const Geom &g, int in_dtype, int out_dtype, bool ro
                              const uint8_t *mask_out, const void *w, const float *bias, const int32_t *idx,
                              const int32_t *count, void *out, float *partials, int32_t *tile_counters, hipStream_t s);
 
+// 3x3 layers of 128-byte pixels with unit horizontal stride and dilation, which launch_conv_pw sends on (see
+// fc_conv_res.hip); grid: one workgroup per CU; bias_last: the bias is added to the finished sum, else the sum starts from it.
+bool conv_res3_supported(const Geom &g);
+// Is the bias of such a layer added last, as on the tap-by-tap form of the resident-weights kernel, or first, as on the
+// tiled kernels?  By the sizes each of them serves, so that a layer's sums do not depend on the kernel: a changed last bit
+// of a few 16-bit values is 1 % of the outputs fifty layers on.
+bool conv_taps_bias_last(const Geom &g, bool masked);
+hipError_t launch_conv_res3(const Geom &g, int in_dtype, int out_dtype, int grid, bool bias_last, const void *x, const uint8_t *mask_in,
+                            const uint8_t *mask_out, const void *w, const float *bias, const int32_t *idx, const int32_t *count,
+                            void *out, hipStream_t s);
+
 // Calibration launches (see fc_calibrate.hip): `blocks` workgroups of four waves each run
 // `iters` rounds of eight matrix instructions; a streaming copy of `bytes` bytes.
 hipError_t launch_calibrate_mfma(int dtype, int iters, int blocks, float *sink, hipStream_t s);

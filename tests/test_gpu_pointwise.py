@@ -468,6 +468,33 @@ def test_3x3_layer_sent_to_the_resident_weights_kernel_by_the_size_rule_matches_
         assert float(np.abs(got - want).max()) / rms <= TOL_F32_OUT
 
 
+@pytest.mark.parametrize("w,mask_kind", [(5, "all"), (14, "all"), (33, "all"), (97, "all"), (97, "checker"), (97, "columns"),
+                                         (40, "one"), (31, "bernoulli")])
+@pytest.mark.parametrize("out_dtype", [synth.BF16, synth.FP8])
+def test_units_whose_pixel_line_is_short_of_slots(w, mask_kind, out_dtype):
+    """Where a unit of the resident-weights 3x3 kernel ends: rows of a few pixels, isolated positions (three slots
+    each: thirteen rows a unit), every other column, a single kept position, lists in tile order."""
+    torch = G.torch_mod()
+    n, h, ci, co = 2, 4800 // w, 64, 64
+    dtype = synth.BF16
+    yy, xx = np.mgrid[0:h, 0:w]
+    mask = {"all": np.ones((h, w)), "checker": (yy + xx) % 2, "columns": xx % 2, "one": (yy == h // 2) & (xx == w - 1),
+            "bernoulli": synth.mask_bernoulli(1, h, w, 0.5, 251, 1)[0]}[mask_kind]
+    mask = np.ascontiguousarray(np.broadcast_to(mask.astype(np.uint8), (n, h, w)))
+    x = synth.activations((n, h, w, ci), dtype, 251, 1)
+    wt = synth.he_weights(co, 3, 3, ci, dtype, 251, 2)
+    bias = synth.bias(co, 251, 3)
+    xd, wd, bd, md = G.to_dev(x, dtype), G.to_dev(wt, dtype), torch.from_numpy(bias).to(G.dev()), G.mask_dev(mask)
+    want = O.focused_conv2d(O.ConvShape(n, h, w, ci, co, relu=True), x, wt, bias=bias, mask_in=mask, dtype=dtype)
+    for idx, count in (B.active_index_compact(md), B.active_index_compact_tiled(md, 4, 8)):
+        desc = B.conv_desc(n, h, w, ci, co, in_dtype=dtype, out_dtype=B.F32, flags=B.RELU | RW)
+        f32 = B.focused_conv2d(desc, xd, wd, bd, mask_in=md, mask_out=md, idx=idx, count=count)
+        _check_f32(f32, want, mask != 0)
+        desc = B.conv_desc(n, h, w, ci, co, in_dtype=dtype, out_dtype=out_dtype, flags=B.RELU | RW)
+        got = B.focused_conv2d(desc, xd, wd, bd, mask_in=md, mask_out=md, idx=idx, count=count)
+        assert torch.equal(got.float(), f32.clamp(max=448.0).to(got.dtype).float() if out_dtype == synth.FP8 else f32.to(got.dtype).float())
+
+
 def test_many_launches_of_a_3x3_layer_on_the_resident_weights_kernel_are_bit_identical():
     """One unit per wave at most (2 906 units of 32 rows on 2 048 waves): every wave is in its
     start-up, where the loads of the list entries, of the tap masks and of the first chunks
