@@ -23,10 +23,8 @@ HIPCC_FLAGS = [
     "-Wall", "-Wno-unused-command-line-argument",
 ]
 
-# fc_conv_mfma.hip holds most of the kernel instances; it is compiled as this many units
-# (-DFC_MFMA_PART=p), side by side with the other sources
-MFMA_SOURCE = "fc_conv_mfma.hip"
-MFMA_PARTS = 6
+# sources that hold many kernel instances are compiled as several units (-D<macro>=p), side by side with the others
+PARTS = {"fc_conv_mfma.hip": ("FC_MFMA_PART", 6), "fc_conv_wide.hip": ("FC_WIDE_PART", 9)}
 
 
 def _run(cmd, verbose):
@@ -52,10 +50,11 @@ def build(verbose: bool = True) -> str:
         units = []      # (object file, compile command); the large units first
         for src in srcs:
             name = os.path.basename(src)
-            if name == MFMA_SOURCE:
-                for part in range(MFMA_PARTS):
+            if name in PARTS:
+                macro, parts = PARTS[name]
+                for part in range(parts):
                     obj = os.path.join(tmp, "%s.%d.o" % (name, part))
-                    units.insert(0, (obj, [hipcc, *HIPCC_FLAGS, *inc, "-DFC_MFMA_PART=%d" % part, "-c", src, "-o", obj]))
+                    units.insert(0, (obj, [hipcc, *HIPCC_FLAGS, *inc, "-D%s=%d" % (macro, part), "-c", src, "-o", obj]))
             else:
                 obj = os.path.join(tmp, name + ".o")
                 units.append((obj, [hipcc, *HIPCC_FLAGS, *inc, "-c", src, "-o", obj]))

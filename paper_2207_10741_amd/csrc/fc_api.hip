@@ -132,6 +132,22 @@ bool conv_pw_wanted(const Geom &g, int in_dtype, int out_dtype, bool masked)
     return true;
 }
 
+// Does the kernel of wide tiles serve this 3x3 layer?  From 1 000 granules of its tiles on (64 rows x 256 channels or 128 x 128,
+// counted over all positions; 600 without a mask), that is from about two tiles of kept rows a CU.  Measured against the tiled
+// kernels, us dense / zero-filled / chained at 48 % irrelevant, list given: 256 -> 256 bf16 on 16 x 60 x 80 (1 200 granules)
+// 95 / 59 / 59 -> 89 / 53 / 49, on 8 x 135 x 240 (4 050) 288 / 171 / 167 -> 257 / 167 / 153, E4M3 153 / 96 / 88 -> 142 / 88 / 77; 512 -> 512 on
+// 32 x 30 x 40 (1 200) 185 / 112 / 115 -> 170 / 96 / 91; 128 -> 128 on 32 x 60 x 80 (1 200) 53 / 34 / 34 -> 49 / 33 / 29.  Below: 256 ->
+// 256 on 32 x 30 x 40 (600) 56 / 35 / 35 -> 47 / 40 / 35, on 16 x 32 x 32 (256) 24 / 22 / 22 -> 28 / 28 / 25.  512 -> 512 on 8 x 67 x 120, half
+// kept by depth, is the one size above the line that loses (148 -> 152: two full rounds of the tiled kernel's slots).  Other
+// channel counts stay: 384 channels are three tiles of 128, each of which reads the rows again (256 -> 384 on 16 x 60 x 80
+// zero-filled 76 -> 102).
+bool conv_wide_wanted(const Geom &g, int in_dtype, int out_dtype, bool masked)
+{
+    if (!conv_wide_supported(g, in_dtype, out_dtype)) return false;
+    if (g.c_out != 128 && g.c_out % 256 != 0) return false;
+    return (int64_t)g.m * g.c_out >= (int64_t)64 * 256 * (masked ? 1000 : 600);
+}
+
 size_t compact_ws(int64_t m) { return align_up((size_t)compact_blocks(m) * sizeof(int32_t), 256); }
 
 static_assert(kSplitGrid * sizeof(int32_t) == FC_WORKSPACE_COUNTER_BYTES, "the header promises this size");
@@ -407,6 +423,9 @@ int32_t fc_focused_conv2d(const fc_conv_desc *desc, const void *x, const uint8_t
         }
         e = launch_conv_small(g, desc->in_dtype, desc->out_dtype, room, x, mask_in, mask_out, w, bias, idx, count, out,
                               partials, tile_counters, s);
+        if (e != hipSuccess) return FC_ERR_HIP;
+    } else if (mfma && (idx || !mask_in) && !pw && conv_wide_wanted(g, desc->in_dtype, desc->out_dtype, mask_in != nullptr)) {
+        e = launch_conv_wide(g, desc->in_dtype, desc->out_dtype, conv_grid_cus(), x, mask_in, mask_out, w, bias, idx, count, out, s);
         if (e != hipSuccess) return FC_ERR_HIP;
     } else if (mfma && idx && !pw && conv_line_wanted(g, desc->in_dtype, desc->out_dtype, mask_in != nullptr)) {
         e = launch_conv_line(g, desc->in_dtype, desc->out_dtype, x, mask_in, mask_out, w, bias, idx, count, out, s);

@@ -716,24 +716,6 @@ bool conv_line_supported(const Geom &g, int in_dtype, int out_dtype)
     return true;
 }
 
-static int line_grid()
-{
-    // one workgroup per CU (the count is read once per process; all devices of a node are alike)
-    static std::atomic<int> cus{0};
-    int v = cus.load(std::memory_order_relaxed);
-    if (v == 0) {
-        int dev = 0;
-        hipDeviceProp_t prop;
-        if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess)
-            v = prop.multiProcessorCount;
-        if (v <= 0) v = 256;
-        v &= ~7; // a multiple of the XCD count
-        if (v < 8) v = 8;
-        cus.store(v, std::memory_order_relaxed);
-    }
-    return v;
-}
-
 template <int DT, typename TO, int TN, int WM, int WN, int PBW, int NSUB, int NBW, int MINW>
 static hipError_t launch_line(const Geom &g, const void *x, const uint8_t *mask_in, const uint8_t *mask_out,
                               const void *w, const float *bias, const int32_t *idx, const int32_t *count, void *out,
@@ -747,7 +729,7 @@ static hipError_t launch_line(const Geom &g, const void *x, const uint8_t *mask_
     dv.wo = make_fastdiv((uint32_t)g.wo);
     dv.ho = make_fastdiv((uint32_t)g.ho);
     dv.n_nt = (g.c_out + TN - 1) / TN;
-    dv.n_rs_max = line_grid() / dv.n_nt < 1 ? 1 : line_grid() / dv.n_nt;
+    dv.n_rs_max = conv_grid_cus() / dv.n_nt < 1 ? 1 : conv_grid_cus() / dv.n_nt;
     dv.rs = make_fastdiv((uint32_t)dv.n_rs_max);
     // the dynamic LDS limit is raised once per function and device to the most any layer can ask for
     static std::atomic<uint64_t> attr_devices{0};
@@ -761,7 +743,7 @@ static hipError_t launch_line(const Geom &g, const void *x, const uint8_t *mask_
         if (e != hipSuccess) return e;
         attr_devices.fetch_or(dev_bit, std::memory_order_release);
     }
-    hipLaunchKernelGGL(kern, dim3(line_grid()), dim3(kLineThreads), lds, s, g, dv, (const uint16_t *)x, mask_in, mask_out,
+    hipLaunchKernelGGL(kern, dim3(conv_grid_cus()), dim3(kLineThreads), lds, s, g, dv, (const uint16_t *)x, mask_in, mask_out,
                        (const uint16_t *)w, bias, idx, count, (TO *)out);
     return hipGetLastError();
 }

@@ -566,9 +566,8 @@ static int pw_slice_blocks(const Geom &g, int es)
     return 0;
 }
 
-static int pw_grid()
+int conv_grid_cus()
 {
-    // one workgroup per CU (the count is read once per process; all devices of a node are alike)
     static std::atomic<int> cus{0};
     int v = cus.load(std::memory_order_relaxed);
     if (v == 0) {
@@ -597,7 +596,7 @@ bool conv_pw_supported(const Geom &g, int in_dtype, int out_dtype)
     const int ncb = pw_slice_blocks(g, es);
     if (ncb == 0) return false;
     // the slices of a group of workgroups sit on one XCD
-    const int n_slices = (g.c_out + ncb * 32 - 1) / (ncb * 32), per_xcd = pw_grid() >> 3;
+    const int n_slices = (g.c_out + ncb * 32 - 1) / (ncb * 32), per_xcd = conv_grid_cus() >> 3;
     if (n_slices > per_xcd) return false;
     if ((uint64_t)g.n * g.h * g.w * g.c_in * (uint64_t)es >= kBufferLimit) return false;
     if ((uint64_t)g.c_out * g.c_in * (uint64_t)es >= kBufferLimit) return false;
@@ -635,7 +634,7 @@ static hipError_t launch_pw(const Geom &g, const void *x, const uint8_t *mask_in
         if (e != hipSuccess) return e;
         attr_devices.fetch_or(dev_bit, std::memory_order_release);
     }
-    hipLaunchKernelGGL(kern, dim3(pw_grid()), dim3(nw * 64), lds, s, g, dv, kch, (const unsigned char *)x, mask_in, mask_out,
+    hipLaunchKernelGGL(kern, dim3(conv_grid_cus()), dim3(nw * 64), lds, s, g, dv, kch, (const unsigned char *)x, mask_in, mask_out,
                        (const unsigned char *)w, bias, idx, count, (TO *)out);
     return hipGetLastError();
 }
@@ -672,7 +671,7 @@ hipError_t launch_conv_pw(const Geom &g, int in_dtype, int out_dtype, const void
                           const int32_t *count, void *out, hipStream_t s)
 {
     if (conv_res3_supported(g))
-        return launch_conv_res3(g, in_dtype, out_dtype, pw_grid(), conv_taps_bias_last(g, mask_in != nullptr), x, mask_in, mask_out, w, bias, idx, count, out, s);
+        return launch_conv_res3(g, in_dtype, out_dtype, conv_grid_cus(), conv_taps_bias_last(g, mask_in != nullptr), x, mask_in, mask_out, w, bias, idx, count, out, s);
 #define FC_PW_CALL(DT, TO) launch_pw_shape<DT, TO>(g, x, mask_in, mask_out, w, bias, idx, count, out, s)
     if (in_dtype == FC_BF16) {
         if (out_dtype == FC_F32) return FC_PW_CALL(FC_BF16, float);

@@ -403,6 +403,15 @@ hipError_t launch_conv_res3(const Geom &g, int in_dtype, int out_dtype, int grid
                             const uint8_t *mask_out, const void *w, const float *bias, const int32_t *idx, const int32_t *count,
                             void *out, hipStream_t s);
 
+// 3x3 layers with several wide tiles per CU (see fc_conv_wide.hip; shapes conv_mfma_supported accepts): whole chunks of
+// input channels, whole 128-channel blocks of output channels, unit horizontal stride and dilation.  Needs the kept list (or
+// no mask at all); grid: one workgroup per CU.
+bool conv_wide_supported(const Geom &g, int in_dtype, int out_dtype);
+hipError_t launch_conv_wide(const Geom &g, int in_dtype, int out_dtype, int grid, const void *x, const uint8_t *mask_in,
+                            const uint8_t *mask_out, const void *w, const float *bias, const int32_t *idx, const int32_t *count,
+                            void *out, hipStream_t s);
+int conv_grid_cus(); // the CU count, a multiple of the XCD count (read once per process; all devices of a node are alike)
+
 // Calibration launches (see fc_calibrate.hip): `blocks` workgroups of four waves each run
 // `iters` rounds of eight matrix instructions; a streaming copy of `bytes` bytes.
 hipError_t launch_calibrate_mfma(int dtype, int iters, int blocks, float *sink, hipStream_t s);
