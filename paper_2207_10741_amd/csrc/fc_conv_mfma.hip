@@ -1060,6 +1060,18 @@ static hipError_t launch_tile(const Geom &g, const void *x, const uint8_t *mask_
     }
     // (1x1 layers keep the wide tiles down to 256 of them: 2048 -> 512 on 32 x 15 x 20 positions,
     // 300 tiles, 37 us dense / 29 us chained against 51 / 32 us with 128 x 64 tiles)
+    // Long reductions, tap by tap, whose kept rows come to at most one 128 x 128 tile per CU (up to 360 tiles of all rows: 252 at a kept
+    // share of 0.7): one workgroup per CU with three stages on their way.  1x1 layers ran two per CU with one stage each, whose round
+    // trip to memory was most of their time; strided 3x3 layers ran twice the 128 x 64 tiles, which fetch the weights twice
+    // as often.  us, zero-filled, bf16, irrelevant 0.3 / 0.48, before -> here: 2048 -> 512 on 32 x 15 x 20 32.6 / 28.6 -> 24.0 / 22.5, 1024 -> 512
+    // 19.0 / 17.3 -> 15.3 / 14.5; 3x3, stride 2, 512 -> 512 from 32 x 29 x 39 70.6 / 63.2 -> 46.9 / 45.0, 256 -> 256 from 9 x 73 x 119 40.1 / 34.0 -> 27.7 / 26.4.
+    // The count is known on the device only, so both ends of the range pay: 0.1 irrelevant is more than a tile per CU (1x1 35.8 -> 42.3,
+    // 20.3 -> 26.3; 3x3 105.8 -> 85.9 all the same), at 0.7 a 3x3 layer's 128 x 64 tiles still fit one round (36.1 -> 41.6; 1x1 25.7 -> 20.8).
+    if constexpr (TAPC != 32) {
+        const int stages = TAPC * ((g.c_in * (DT == FC_FP8 ? 1 : 2) + 127) / 128);
+        if (g.c_out > 64 && mask_in && !partials && tiles128 >= 256 && tiles128 <= 360 && stages >= 12)
+            return launch_dma<DT, TO, CMP, 128, 128, 2, 2, TAPC, 4, 2>(FC_ARGS);
+    }
     if (g.c_out > 64 && tiles128 >= (TAPC == 1 ? 256 : 512))
         return launch_dma<DT, TO, CMP, 128, 128, 2, 2, TAPC, (sizeof(TO) == 4 ? 3 : 2), 2>(FC_ARGS);
     // narrow layers with many tiles: two stage buffers, so that three workgroups fit a CU

@@ -623,6 +623,40 @@ def test_counters_with_garbage_are_cleared_where_a_reduction_is_split(layer, mas
     assert torch.equal(B.focused_conv2d(desc, x, wt, mask_in=md, workspace=ws), want)
 
 
+@pytest.mark.parametrize("layer,dtype", [
+    # n, h, w, ci, co, k, s, p, d: 256 .. 360 tiles of 128 x 128, twelve stages and more: one deep tile per CU; rows and channels off the tile
+    ((8, 32, 32, 768, 512, 1, 1, 0, 1), synth.BF16), ((9, 36, 35, 800, 400, 1, 1, 0, 1), synth.F16),
+    ((6, 61, 59, 136, 1000, 3, 2, 1, 1), synth.BF16), ((5, 57, 59, 256, 256, 3, 1, 2, 2), synth.F16), ((8, 32, 33, 1536, 512, 1, 1, 0, 1), synth.FP8)])
+@pytest.mark.parametrize("irr", [0.48, 0.02])
+def test_long_reductions_of_a_tile_per_cu(layer, dtype, irr):
+    """Against the oracle on sampled positions; zero rows to the byte, kept rows all written.  Nearly all rows kept: more tiles
+    than CUs."""
+    torch = G.torch_mod()
+    n, h, w, ci, co, k, s, p, d = layer
+    x = synth.activations((n, h, w, ci), dtype, 254, 1)
+    wt = synth.he_weights(co, k, k, ci, dtype, 254, 2)
+    bias = synth.bias(co, 254, 3)
+    mask = synth.mask_objects(n, h, w, irr, 254, 4)
+    geo = ((k, k), (s, s), (p, p), (d, d))
+    md = G.mask_dev(mask)
+    m_out = B.mask_downsample(md, *geo)
+    idx, count = B.active_index_compact(m_out)
+    desc = B.conv_desc(n, h, w, ci, co, *geo, dtype, B.F32, B.RELU)
+    out = torch.full((n, *B.out_dims(desc), co), 7.0, dtype=torch.float32, device=G.dev())
+    B.focused_conv2d(desc, G.to_dev(x, dtype), G.to_dev(wt, dtype), torch.from_numpy(bias).to(G.dev()), mask_in=md, mask_out=m_out,
+                     idx=idx, count=count, out=out)
+    keep = m_out.cpu().numpy() != 0
+    kd = torch.from_numpy(keep).to(G.dev())
+    assert not bool(out[~kd].view(torch.int32).any()) and not bool((out[kd] == 7.0).all(dim=-1).any())
+    pos = np.sort(np.random.default_rng(254).choice(np.flatnonzero(keep.reshape(-1)), size=400, replace=False))
+    shape = O.ConvShape(n, h, w, ci, co, k, k, (s, s), (p, p), (d, d), relu=True)
+    want = O.focused_conv2d_at(shape, x, wt, pos, bias=bias, mask_in=mask, dtype=dtype)
+    got = out.reshape(-1, co)[torch.from_numpy(pos).to(G.dev())].cpu().numpy().astype(np.float64)
+    from tests.test_gpu_fp8 import TOL_FP8
+    rms = float(np.sqrt(np.mean(np.square(want))))
+    assert float(np.abs(got - want).max()) / rms <= (TOL_FP8 if dtype == synth.FP8 else TOL_F32_OUT)
+
+
 def test_two_runs_are_bit_identical():
     torch = G.torch_mod()
     a, _, _ = _run_layer(2, 28, 28, 128, 128, 3, 1, 1, 1, synth.BF16, seed=208)
