@@ -91,6 +91,8 @@ bool conv_line_wanted(const Geom &g, int in_dtype, int out_dtype, bool focused)
 // Where its 32-row blocks come to one and a half per wave (two slices at 100 000 positions) the tiled kernel is up to 5 %
 // faster on inputs already in the caches, and neither on others; below 12 000 positions the weights (72 KB a workgroup)
 // are too much to fetch for the rows: 8 x 28 x 28 8.1 -> 9.0.
+// The shape of the mask is known on the device only: where positions are dropped one by one at random (no regions) the pixel line breaks at
+// every other row and 64 -> 64 on 16 x 128 x 128 takes 0 .. 28 % more at 0.3 .. 0.8 kept (22.6 -> 24.4 at half; regions 24.0 -> 20.4).
 //
 // Other steps and dilations take the tap-by-tap form of the resident-weights kernel, into at most 64 channels, along the
 // lines measured on that form: without a mask 12 .. 25 % faster than the tiled kernel up to 0.6 M positions and 6 % slower at
@@ -141,6 +143,10 @@ bool conv_pw_wanted(const Geom &g, int in_dtype, int out_dtype, bool masked)
 // kept by depth, is the one size above the line that loses (148 -> 152: two full rounds of the tiled kernel's slots).  Other
 // channel counts stay: 384 channels are three tiles of 128, each of which reads the rows again (256 -> 384 on 16 x 60 x 80
 // zero-filled 76 -> 102).
+// The masks meant here are few large regions.  The kept share and the shape of the mask are known on the device only, and both can turn
+// the rule round: at most a fifth kept loses 0 .. 20 % (128 -> 128 on 128 x 64 x 64, a tenth kept: 39 -> 43), and positions dropped one by one
+// at random break the pixel line at every other row, so that a tile takes half the rows: 512 -> 512 on 128 x 16 x 16 0 .. 9 % slower at half and more
+// kept and 58 -> 110 at 0.3, 128 -> 128 on 128 x 64 x 64 104 -> 134 at half (regions: 108 -> 89 and 100 -> 94).
 bool conv_wide_wanted(const Geom &g, int in_dtype, int out_dtype, bool masked)
 {
     if (!conv_wide_supported(g, in_dtype, out_dtype)) return false;
