@@ -181,12 +181,13 @@ __global__ __launch_bounds__(kLineThreads, MINW) void k_conv_line(Geom g, LineDi
         const bool kept = !((drop >> lane) & 1ull);
         const int nd = __popcll(drop);
         if (!kept) dropped[__popcll(drop & ((1ull << lane) - 1ull))] = pp; // in position order
-        // (same wave wrote and reads the list: program order suffices)
+        wave_lds_order();
         const int total = nd * cpr;
         for (int c = lane; c < total; c += 64) {
             const int rk = c / cpr, pc = c - rk * cpr;
             __builtin_nontemporal_store(zero4, o4 + (int64_t)dropped[rk] * cpr + pc);
         }
+        wave_lds_order();
     };
     bool zf_kept = true;
     const bool zf_pending = zero_fill && zf_first < g.m;

@@ -250,12 +250,13 @@ __global__ __launch_bounds__(WM *WN * 64, MINW) void k_conv_dma(Geom g, const ui
                 const uint64_t drop = __ballot(!kept);
                 const int nd = __popcll(drop);
                 if (!kept) dropped[__popcll(drop & ((1ull << lane) - 1ull))] = pp; // in position order
-                // (same wave wrote and reads the list: program order suffices)
+                wave_lds_order();
                 const int total = nd * cpr;
                 for (int c = lane; c < total; c += 64) {
                     const int rk = c / cpr, pc = c - rk * cpr;
                     __builtin_nontemporal_store(zero4, o4 + (int64_t)dropped[rk] * cpr + pc);
                 }
+                wave_lds_order();
             }
         }
     }

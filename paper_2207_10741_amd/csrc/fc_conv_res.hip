@@ -206,11 +206,13 @@ void k_conv_res3(Geom g, FastDiv div_cpr, bool bias_last, const unsigned char *_
 #pragma unroll
             for (int k = 0; k < 3; ++k) rows_in |= (uint32_t)((uint32_t)(ih0 + k * g.dh) < (uint32_t)g.h) << (28 + k);
             if (lane < LS) tab[lane] = 0;
+            wave_lds_order(); // (lanes write entries of one another)
             if (valid && half == 0) {
                 tab[cs] = (pix & kPixBits) | ((uint32_t)iwc < (uint32_t)g.w ? rows_in : 0u);
                 if (!ladj) tab[cs - 1] = ((pix - 1u) & kPixBits) | ((uint32_t)(iwc - 1) < (uint32_t)g.w ? rows_in : 0u);
                 if (!radj) tab[cs + 1] = ((pix + 1u) & kPixBits) | ((uint32_t)(iwc + 1) < (uint32_t)g.w ? rows_in : 0u);
             }
+            wave_lds_order(); // (lanes write entries of one another)
             w0 = tab[sl0];
             w1 = live1 ? tab[sl1] : 0u;
             if (mask_in) {

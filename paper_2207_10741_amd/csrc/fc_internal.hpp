@@ -180,6 +180,10 @@ __device__ __forceinline__ bool position_kept(const Geom &g, const uint8_t *__re
     return mask_at(mask_in, (int64_t)(b * g.h + ih) * g.w + iw, packed);
 }
 
+// Between LDS writes of some lanes of a wave and the reads of others (and the other way round): LDS serves a wave's accesses in
+// the order they were issued, and this keeps the compiler to the order they are written in.
+__device__ __forceinline__ void wave_lds_order() { __asm__ volatile("" ::: "memory"); }
+
 // Zero-fill of the irrelevant output rows (whole 16-byte pieces, `pieces` per row): wave `worker` of
 // `workers` looks at 64 positions at a time (one label each), lists the irrelevant ones in LDS in order
 // (`dropped`: 64 ints of its own), and then all its lanes store 16-byte pieces of those rows, so the stores
@@ -200,7 +204,7 @@ __device__ __forceinline__ void clear_irrelevant(const Geom &g, const uint8_t *_
         const uint64_t drop = __ballot(!kept);
         const int nd = __popcll(drop);
         if (!kept) dropped[__popcll(drop & ((1ull << lane) - 1ull))] = (int32_t)(p0 + lane); // in position order
-        // (same wave wrote and reads the list: program order suffices)
+        wave_lds_order();
         const int64_t pn = p0 + step + lane;
         kept = pn >= g.m || position_kept(g, mask_in, mask_out, pn);
         const int total = nd * pieces;
@@ -208,6 +212,7 @@ __device__ __forceinline__ void clear_irrelevant(const Geom &g, const uint8_t *_
             const int rk = c / pieces, pc = c - rk * pieces;
             __builtin_nontemporal_store(zero4, o4 + (int64_t)dropped[rk] * pieces + pc);
         }
+        wave_lds_order();
     }
 }
 
