@@ -927,6 +927,73 @@ __global__ __launch_bounds__(WM *WN * 64, MINW) void k_conv_dma(Geom g, const ui
 
 // ---------------------------------------------------------------------------
 
+// The instances a layer can take, by the tile of a workgroup (rows x channels).
+struct TileShape {
+    enum Kind {
+        own64,      // 64 x 64, rows labelled by the tile itself (tiles_label_rows)
+        small64,    // 64 x 64, four stage buffers
+        line128,    // 128 x 128 on the shared pixel line
+        line64,     // 128 x 64 on the shared pixel line
+        deep128,    // 128 x 128, one workgroup per CU with three stages on their way
+        wide128,    // 128 x 128, two workgroups per CU
+        narrow64,   // 128 x 64, three workgroups per CU
+        tall64,     // 128 x 64, two workgroups per CU
+    } kind;
+    int rows() const { return kind == own64 || kind == small64 ? 64 : 128; }
+    int cols() const { return kind == line128 || kind == deep128 || kind == wide128 ? 128 : 64; }
+};
+
+// splits: the call brings split-K scratch; labels_rows: a mask and no list
+static inline TileShape choose_tile(const Geom &g, int in_dtype, bool masked, bool labels_rows, bool splits)
+{
+    const bool k1 = g.kh == 1 && g.kw == 1, k3 = g.kh == 3 && g.kw == 3;
+    const int64_t rows128 = (g.m + 127) / 128;
+    const int64_t tiles128 = rows128 * ((g.c_out + 127) / 128), tiles64 = rows128 * ((g.c_out + 63) / 64);
+    if (k3 && labels_rows && g.m > kInlineRankPositions) return {TileShape::own64};
+    // Layers with only a handful of tiles (the late layers of a network at batch 1) are all
+    // latency: 64 x 64 tiles put them on more CUs and four stage buffers keep three gathers in
+    // flight (a ResNet-18 stack at batch 1: 0.243 -> 0.221 ms dense, 0.266 -> 0.245 ms focused)
+    if ((k1 || k3) && tiles64 <= kSmallLayerTiles) return {TileShape::small64};
+    // 128 x 128 tiles when there are enough of them to give every CU two workgroups;
+    // otherwise 128 x 64, which doubles the tile count (the kept count is not known here,
+    // so the dense row count decides)
+    //
+    // 3x3 kernels that step one pixel at a time horizontally share the gathered pixels
+    // between their three horizontal taps (worth it when image rows are long enough for runs
+    // of adjacent kept positions; narrow layers with many tiles do better with three
+    // workgroups per CU, see below)
+    if (k3 && g.sw == 1 && g.dw == 1 && g.wo >= 16) {
+        // (with many 128 x 128 tiles it pays down to 16-pixel rows: C512@16 at batch 128 is
+        // 13 % faster dense and 17 % faster focused than tap by tap)
+        if (g.c_out > 64 && tiles128 >= 512) return {TileShape::line128};
+        // narrow layers: only with very many tiles (C64@128: -7 % focused, -4..8 % dense from batch
+        // 128 on, 16 384 row tiles; at 4 800 row tiles, 64 -> 64 on 32 x 120 x 160 positions, three
+        // workgroups per CU, below, are 7 % faster, and at batch 16 as fast)
+        const bool many_narrow_tiles = rows128 >= 8192;
+        if (g.wo >= 32 && (g.c_out > 64 || splits || many_narrow_tiles)) return {TileShape::line64};
+        // shorter image rows, wide layers, a few hundred tiles (C512 on 32 x 15 x 20 positions:
+        // 66 us dense / 45 us chained against 102 / 49 us tap by tap; with 128 tiles, C512@16 at
+        // batch 16, tap by tap stays ahead)
+        if (g.c_out > 64 && tiles128 >= 256) return {TileShape::line64};
+    }
+    // (1x1 layers keep the wide tiles down to 256 of them: 2048 -> 512 on 32 x 15 x 20 positions,
+    // 300 tiles, 37 us dense / 29 us chained against 51 / 32 us with 128 x 64 tiles)
+    // Long reductions, tap by tap, whose kept rows come to at most one 128 x 128 tile per CU (up to 360 tiles of all rows: 252 at a kept
+    // share of 0.7): one workgroup per CU with three stages on their way.  1x1 layers ran two per CU with one stage each, whose round
+    // trip to memory was most of their time; strided 3x3 layers ran twice the 128 x 64 tiles, which fetch the weights twice
+    // as often.  us, zero-filled, bf16, irrelevant 0.3 / 0.48, before -> here: 2048 -> 512 on 32 x 15 x 20 32.6 / 28.6 -> 24.0 / 22.5, 1024 -> 512
+    // 19.0 / 17.3 -> 15.3 / 14.5; 3x3, stride 2, 512 -> 512 from 32 x 29 x 39 70.6 / 63.2 -> 46.9 / 45.0, 256 -> 256 from 9 x 73 x 119 40.1 / 34.0 -> 27.7 / 26.4.
+    // The count is known on the device only, so both ends of the range pay: 0.1 irrelevant is more than a tile per CU (1x1 35.8 -> 42.3,
+    // 20.3 -> 26.3; 3x3 105.8 -> 85.9 all the same), at 0.7 a 3x3 layer's 128 x 64 tiles still fit one round (36.1 -> 41.6; 1x1 25.7 -> 20.8).
+    const int stages = g.kh * g.kw * ((g.c_in * (in_dtype == FC_FP8 ? 1 : 2) + 127) / 128);
+    if ((k1 || k3) && g.c_out > 64 && masked && !splits && tiles128 >= 256 && tiles128 <= 360 && stages >= 12) return {TileShape::deep128};
+    if (g.c_out > 64 && tiles128 >= (k1 ? 256 : 512)) return {TileShape::wide128};
+    // narrow layers with many tiles: two stage buffers, so that three workgroups fit a CU
+    // and overlap each other's set-up and epilogue
+    if (g.c_out <= 64 && !splits) return {TileShape::narrow64};
+    return {TileShape::tall64};
+}
+
 #if !defined(FC_MFMA_PART) || FC_MFMA_PART == 0
 // Does a 3x3 layer with a mask and no list label its rows tile by tile (64 x 64 tiles of consecutive positions,
 // irrelevant ones stored as zeros) instead of compacting them in a launch of its own?  While all tiles of the
@@ -948,18 +1015,11 @@ bool tiles_label_rows(const Geom &g, int in_dtype)
     return tiles <= kSplitGrid && tiles * 9 * chunks <= 20 * kSplitGrid;
 }
 
-// (the tile launch_tile takes for a layer that may split, and the split of all of the layer's rows)
 bool dense_layer_splits(const Geom &g, int in_dtype)
 {
-    const int64_t rows128 = (g.m + 127) / 128, tiles128 = rows128 * ((g.c_out + 127) / 128);
-    int64_t tiles = rows128 * ((g.c_out + 63) / 64);
-    if (tiles <= kSmallLayerTiles && g.kh * g.kw != 1 && !(g.kh == 3 && g.kw == 3)) {
-        // (any kernel size but 1x1 and 3x3 stays on 128 x 64 tiles)
-    } else if (tiles <= kSmallLayerTiles) {
-        tiles = (int64_t)((g.m + 63) / 64) * ((g.c_out + 63) / 64);
-    } else if (g.kh == 1 && g.kw == 1 && g.c_out > 64 && tiles128 >= 256) {
-        tiles = tiles128;
-    }
+    // (asked for calls with split-K scratch only)
+    const TileShape t = choose_tile(g, in_dtype, false, false, true);
+    const int64_t tiles = (int64_t)((g.m + t.rows() - 1) / t.rows()) * ((g.c_out + t.cols() - 1) / t.cols());
     const int stages = g.kh * g.kw * ((g.c_in * (in_dtype == FC_FP8 ? 1 : 2) + 127) / 128);
     return split_k_splits((int)tiles, kSplitGrid, stages, stages) > 1;
 }
@@ -1021,64 +1081,30 @@ static hipError_t launch_tile(const Geom &g, const void *x, const uint8_t *mask_
                               const void *w, const float *bias, const int32_t *idx, const int32_t *count,
                               void *out, float *partials, int32_t *tile_counters, hipStream_t s)
 {
-    // 128 x 128 tiles when there are enough of them to give every CU two workgroups;
-    // otherwise 128 x 64, which doubles the tile count (the kept count is not known here,
-    // so the dense row count decides)
-    const int64_t tiles128 = (int64_t)((g.m + 127) / 128) * ((g.c_out + 127) / 128);
-    if constexpr (TAPC == 9 && !CMP) {
-        if (mask_in && !idx && g.m > kInlineRankPositions) // the layers of tiles_label_rows; others have a list
-            return launch_dma<DT, TO, CMP, 64, 64, 2, 2, TAPC, 4, 2, 0, 2, true>(FC_ARGS);
-    }
-    // Layers with only a handful of tiles (the late layers of a network at batch 1) are all
-    // latency: 64 x 64 tiles put them on more CUs and four stage buffers keep three gathers in
-    // flight (a ResNet-18 stack at batch 1: 0.243 -> 0.221 ms dense, 0.266 -> 0.245 ms focused)
-    if constexpr (TAPC != 32) {
-        const int64_t tiles64w = (int64_t)((g.m + 127) / 128) * ((g.c_out + 63) / 64);
-        if (tiles64w <= kSmallLayerTiles) return launch_dma<DT, TO, CMP, 64, 64, 2, 2, TAPC, 4, 2>(FC_ARGS);
-    }
-    // 3x3 kernels that step one pixel at a time horizontally share the gathered pixels
-    // between their three horizontal taps (worth it when image rows are long enough for runs
-    // of adjacent kept positions; narrow layers with many tiles do better with three
-    // workgroups per CU, see below)
-    if constexpr (TAPC == 9) {
-        if (g.sw == 1 && g.dw == 1 && g.wo >= 16) {
-            // (with many 128 x 128 tiles it pays down to 16-pixel rows: C512@16 at batch 128 is
-            // 13 % faster dense and 17 % faster focused than tap by tap)
-            if (g.c_out > 64 && tiles128 >= 512)
-                return launch_dma<DT, TO, CMP, 128, 128, 2, 2, TAPC, 2, 2, 160, 2>(FC_ARGS);
-            // narrow layers: only with very many tiles (C64@128: -7 % focused, -4..8 % dense from batch
-            // 128 on, 16 384 row tiles; at 4 800 row tiles, 64 -> 64 on 32 x 120 x 160 positions, three
-            // workgroups per CU, below, are 7 % faster, and at batch 16 as fast)
-            const bool many_narrow_tiles = (int64_t)((g.m + 127) / 128) >= 8192;
-            if (g.wo >= 32 && (g.c_out > 64 || partials || many_narrow_tiles))
-                return launch_dma<DT, TO, CMP, 128, 64, 2, 2, TAPC, 3, 2, 160, 3>(FC_ARGS);
-            // shorter image rows, wide layers, a few hundred tiles (C512 on 32 x 15 x 20 positions:
-            // 66 us dense / 45 us chained against 102 / 49 us tap by tap; with 128 tiles, C512@16 at
-            // batch 16, tap by tap stays ahead)
-            if (g.c_out > 64 && tiles128 >= 256)
-                return launch_dma<DT, TO, CMP, 128, 64, 2, 2, TAPC, 3, 2, 160, 3>(FC_ARGS);
-        }
-    }
-    // (1x1 layers keep the wide tiles down to 256 of them: 2048 -> 512 on 32 x 15 x 20 positions,
-    // 300 tiles, 37 us dense / 29 us chained against 51 / 32 us with 128 x 64 tiles)
-    // Long reductions, tap by tap, whose kept rows come to at most one 128 x 128 tile per CU (up to 360 tiles of all rows: 252 at a kept
-    // share of 0.7): one workgroup per CU with three stages on their way.  1x1 layers ran two per CU with one stage each, whose round
-    // trip to memory was most of their time; strided 3x3 layers ran twice the 128 x 64 tiles, which fetch the weights twice
-    // as often.  us, zero-filled, bf16, irrelevant 0.3 / 0.48, before -> here: 2048 -> 512 on 32 x 15 x 20 32.6 / 28.6 -> 24.0 / 22.5, 1024 -> 512
-    // 19.0 / 17.3 -> 15.3 / 14.5; 3x3, stride 2, 512 -> 512 from 32 x 29 x 39 70.6 / 63.2 -> 46.9 / 45.0, 256 -> 256 from 9 x 73 x 119 40.1 / 34.0 -> 27.7 / 26.4.
-    // The count is known on the device only, so both ends of the range pay: 0.1 irrelevant is more than a tile per CU (1x1 35.8 -> 42.3,
-    // 20.3 -> 26.3; 3x3 105.8 -> 85.9 all the same), at 0.7 a 3x3 layer's 128 x 64 tiles still fit one round (36.1 -> 41.6; 1x1 25.7 -> 20.8).
-    if constexpr (TAPC != 32) {
-        const int stages = TAPC * ((g.c_in * (DT == FC_FP8 ? 1 : 2) + 127) / 128);
-        if (g.c_out > 64 && mask_in && !partials && tiles128 >= 256 && tiles128 <= 360 && stages >= 12)
-            return launch_dma<DT, TO, CMP, 128, 128, 2, 2, TAPC, 4, 2>(FC_ARGS);
-    }
-    if (g.c_out > 64 && tiles128 >= (TAPC == 1 ? 256 : 512))
+    switch (choose_tile(g, DT, mask_in != nullptr, mask_in && !idx, partials != nullptr).kind) {
+    case TileShape::own64:
+        if constexpr (TAPC == 9 && !CMP) return launch_dma<DT, TO, CMP, 64, 64, 2, 2, TAPC, 4, 2, 0, 2, true>(FC_ARGS);
+        break;
+    case TileShape::small64:
+        if constexpr (TAPC != 32) return launch_dma<DT, TO, CMP, 64, 64, 2, 2, TAPC, 4, 2>(FC_ARGS);
+        break;
+    case TileShape::line128:
+        if constexpr (TAPC == 9) return launch_dma<DT, TO, CMP, 128, 128, 2, 2, TAPC, 2, 2, 160, 2>(FC_ARGS);
+        break;
+    case TileShape::line64:
+        if constexpr (TAPC == 9) return launch_dma<DT, TO, CMP, 128, 64, 2, 2, TAPC, 3, 2, 160, 3>(FC_ARGS);
+        break;
+    case TileShape::deep128:
+        if constexpr (TAPC != 32) return launch_dma<DT, TO, CMP, 128, 128, 2, 2, TAPC, 4, 2>(FC_ARGS);
+        break;
+    case TileShape::wide128:
         return launch_dma<DT, TO, CMP, 128, 128, 2, 2, TAPC, (sizeof(TO) == 4 ? 3 : 2), 2>(FC_ARGS);
-    // narrow layers with many tiles: two stage buffers, so that three workgroups fit a CU
-    // and overlap each other's set-up and epilogue
-    if (g.c_out <= 64 && !partials) return launch_dma<DT, TO, CMP, 128, 64, 2, 2, TAPC, 2, 3>(FC_ARGS);
-    return launch_dma<DT, TO, CMP, 128, 64, 2, 2, TAPC, 3, 2>(FC_ARGS);
+    case TileShape::narrow64:
+        return launch_dma<DT, TO, CMP, 128, 64, 2, 2, TAPC, 2, 3>(FC_ARGS);
+    case TileShape::tall64:
+        return launch_dma<DT, TO, CMP, 128, 64, 2, 2, TAPC, 3, 2>(FC_ARGS);
+    }
+    return hipErrorInvalidValue; // (a tile this kernel size has no instance of: choose_tile names none)
 }
 #undef FC_ARGS
 

@@ -379,7 +379,8 @@ hipError_t launch_zero_i32(int32_t *p, int n, hipStream_t s);
 // Matrix-core path (only for shapes conv_mfma_supported accepts).  It also clears
 // the irrelevant output rows unless FC_SKIP_ZERO_FILL is set; mask_out may be NULL.
 bool tiles_label_rows(const Geom &g, int in_dtype);
-// Is the reduction of a layer without a mask split (given split-K scratch)?  Only then are the counters used.
+// Is the reduction of a layer without a mask split (given split-K scratch)?  Only then are the counters used.  (By the tile that
+// launch_conv_mfma takes: both ask choose_tile.)
 bool dense_layer_splits(const Geom &g, int in_dtype);
 bool conv_mfma_supported(const Geom &g, int in_dtype, int out_dtype);
 hipError_t launch_conv_mfma(const Geom &g, int in_dtype, int out_dtype, const void *x,
