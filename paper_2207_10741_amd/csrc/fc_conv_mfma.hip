@@ -84,20 +84,17 @@ constexpr size_t dma_lds_bytes()
 // OWN: the 64 x 64 instance for layers with a mask and no list that label their rows themselves (tiles_label_rows).
 // The rows of a tile are consecutive positions, the irrelevant ones are stored as zeros, and no reduction is split.
 //
+// LIST: the list is given and its length (list_rows) known already.
+//
 // CMP: the instances that serve compacted activations (FC_COMPACT_IN / FC_COMPACT_OUT: rows
 // stored in list order).  Separate instances, so that the ordinary ones do not change by a
 // register: the 128 x 64 three-buffer instance loses 20 % with a handful more.
-template <int DT, typename TO, int TM, int TN, int WM, int WN, int TAPC, int NB, int MINW, int SL, int NBW, bool CMP, bool OWN>
-__global__ __launch_bounds__(WM *WN * 64, MINW) void k_conv_dma(Geom g, const uint16_t *__restrict__ x,
-                                                                 const uint8_t *__restrict__ mask_in,
-                                                                 const uint8_t *__restrict__ mask_out,
-                                                                 const uint16_t *__restrict__ w,
-                                                                 const float *__restrict__ bias,
-                                                                 const int32_t *__restrict__ idx,
-                                                                 const int32_t *__restrict__ count,
-                                                                 TO *__restrict__ out,
-                                                                 float *__restrict__ partials,
-                                                                 int32_t *__restrict__ tile_counters)
+template <int DT, typename TO, int TM, int TN, int WM, int WN, int TAPC, int NB, int SL, int NBW, bool CMP, bool OWN, bool LIST = false>
+__device__ __forceinline__ void conv_dma_tiles(const Geom &g, const uint16_t *__restrict__ x, const uint8_t *__restrict__ mask_in,
+                                               const uint8_t *__restrict__ mask_out, const uint16_t *__restrict__ w,
+                                               const float *__restrict__ bias, const int32_t *__restrict__ idx,
+                                               const int32_t *__restrict__ count, TO *__restrict__ out,
+                                               float *__restrict__ partials, int32_t *__restrict__ tile_counters, int list_rows = 0)
 {
     constexpr int NT = WM * WN * 64;
     constexpr int RPP = NT / 8;        // rows covered by one pass of wave loads
@@ -154,7 +151,7 @@ __global__ __launch_bounds__(WM *WN * 64, MINW) void k_conv_dma(Geom g, const ui
     // tile then has every thread drop its positions of that tile's rank range into row_p.  A
     // small layer so needs no compaction launch before this one.
     const bool packed_masks = (g.flags & FC_PACKED_MASKS) != 0; // masks are one bit per pixel
-    const bool inline_rank = !OWN && !idx && mask_in;
+    const bool inline_rank = !OWN && !LIST && !idx && mask_in;
     uint32_t rank_flags = 0;
     int rank_base = 0;
     int rows = g.m;
@@ -177,6 +174,8 @@ __global__ __launch_bounds__(WM *WN * 64, MINW) void k_conv_dma(Geom g, const ui
         rank_base = before + incl - cnt;
         rows = total;
         __syncthreads(); // row_p is free again
+    } else if (LIST) {
+        rows = list_rows;
     } else if (!OWN && idx) {
         rows = *count;
     }
@@ -299,7 +298,7 @@ __global__ __launch_bounds__(WM *WN * 64, MINW) void k_conv_dma(Geom g, const ui
             const int m = mt * TM + tid;
             int p = -1, base = 0, b = 0, hw = 0;
             if (m < rows) {
-                p = inline_rank ? row_p[tid] : (!OWN && idx ? idx[m] : m);
+                p = inline_rank ? row_p[tid] : (LIST || (!OWN && idx) ? idx[m] : m);
                 if constexpr (OWN) dropped_row = !position_kept(g, mask_in, mask_out, m);
                 const int q = (int)fast_div((uint32_t)p, g.div_wo), ow = p - q * g.wo;
                 b = (int)fast_div((uint32_t)q, g.div_ho);
@@ -925,6 +924,53 @@ __global__ __launch_bounds__(WM *WN * 64, MINW) void k_conv_dma(Geom g, const ui
 
 }
 
+template <int DT, typename TO, int TM, int TN, int WM, int WN, int TAPC, int NB, int MINW, int SL, int NBW, bool CMP, bool OWN>
+__global__ __launch_bounds__(WM *WN * 64, MINW) void k_conv_dma(Geom g, const uint16_t *__restrict__ x, const uint8_t *__restrict__ mask_in,
+                                                                 const uint8_t *__restrict__ mask_out, const uint16_t *__restrict__ w,
+                                                                 const float *__restrict__ bias, const int32_t *__restrict__ idx,
+                                                                 const int32_t *__restrict__ count, TO *__restrict__ out,
+                                                                 float *__restrict__ partials, int32_t *__restrict__ tile_counters)
+{
+    conv_dma_tiles<DT, TO, TM, TN, WM, WN, TAPC, NB, SL, NBW, CMP, OWN>(g, x, mask_in, mask_out, w, bias, idx, count, out, partials, tile_counters);
+}
+
+// Long reductions, tap by tap, of about a tile per CU: one workgroup per CU with two or three stages on their way (two workgroups with one
+// stage each wait a round trip a stage), its tile chosen by the kept count, which is known here only, so that one round of tiles
+// covers the rows (cus: workgroups that run at once): 128 x 128, in 1x1 layers 192 x 128 where that is more than one round, in 3x3
+// layers 128 x 64 where that is still one.  bf16, chained, us at a kept share of 0.1 / 0.3 / 0.5 / 0.7 / 0.9 / 1, two workgroups per CU -> here:
+// 1x1 2048 -> 512 on 32 x 15 x 20 21.8 / 25.2 / 28.0 / 32.3 / 35.0 / 35.4 -> 20.0 / 21.0 / 21.5 / 22.8 / 27.0 / 28.4, 1024 -> 512 11.2 / 14.0 / 16.1 / 18.4 /
+// 19.9 / 19.9 -> 12.0 / 12.8 / 13.5 / 14.8 / 17.0 / 18.0; 3x3, stride 2, 512 -> 512 from 32 x 29 x 39 33.1 / 33.8 / 62.2 / 69.4 / 105 / 105 -> 33.0 / 33.7 / 41.3 /
+// 44.6 / 82.5 / 86, 256 -> 256 from 9 x 73 x 119 19.2 / 20.4 / 33.0 / 39.0 / 57.9 / 58.4 -> 18.9 / 20.2 / 24.1 / 26.6 / 46.5 / 50.1.  With 128 x 128 tiles
+// alone the ends of the range lost: 25.4 at 0.9 kept (1024 -> 512), 38.5 and 22.3 at 0.1 (3x3).
+constexpr int kDeepBuffersNarrow = 4, kDeepBuffers = 4, kDeepBuffersTall = 3;
+template <int TAPC> constexpr size_t deep_lds_bytes()
+{
+    constexpr size_t a = dma_lds_bytes<128, 128, kDeepBuffers, 0, 2>();
+    constexpr size_t b = TAPC == 1 ? dma_lds_bytes<192, 128, kDeepBuffersTall, 0, 2>() : dma_lds_bytes<128, 64, kDeepBuffersNarrow, 0, 2>();
+    return a > b ? a : b;
+}
+
+template <int DT, typename TO, int TAPC, bool CMP>
+__global__ __launch_bounds__(256, 2) void k_conv_deep(Geom g, int cus, const uint16_t *__restrict__ x, const uint8_t *__restrict__ mask_in,
+                                                      const uint8_t *__restrict__ mask_out, const uint16_t *__restrict__ w,
+                                                      const float *__restrict__ bias, const int32_t *__restrict__ idx,
+                                                      const int32_t *__restrict__ count, TO *__restrict__ out)
+{
+    const int rows = __builtin_amdgcn_readfirstlane(*count), rows128 = (rows + 127) / 128;
+    if constexpr (TAPC == 1) {
+        if (rows128 * ((g.c_out + 127) / 128) > cus) {
+            conv_dma_tiles<DT, TO, 192, 128, 2, 2, TAPC, kDeepBuffersTall, 0, 2, CMP, false, true>(g, x, mask_in, mask_out, w, bias, idx, count, out, nullptr, nullptr, rows);
+            return;
+        }
+    } else {
+        if (rows128 * ((g.c_out + 63) / 64) <= cus) {
+            conv_dma_tiles<DT, TO, 128, 64, 2, 2, TAPC, kDeepBuffersNarrow, 0, 2, CMP, false, true>(g, x, mask_in, mask_out, w, bias, idx, count, out, nullptr, nullptr, rows);
+            return;
+        }
+    }
+    conv_dma_tiles<DT, TO, 128, 128, 2, 2, TAPC, kDeepBuffers, 0, 2, CMP, false, true>(g, x, mask_in, mask_out, w, bias, idx, count, out, nullptr, nullptr, rows);
+}
+
 // ---------------------------------------------------------------------------
 
 // The instances a layer can take, by the tile of a workgroup (rows x channels).
@@ -934,13 +980,13 @@ struct TileShape {
         small64,    // 64 x 64, four stage buffers
         line128,    // 128 x 128 on the shared pixel line
         line64,     // 128 x 64 on the shared pixel line
-        deep128,    // 128 x 128, one workgroup per CU with three stages on their way
+        deep,       // k_conv_deep: one workgroup per CU, the tile by the kept count
         wide128,    // 128 x 128, two workgroups per CU
         narrow64,   // 128 x 64, three workgroups per CU
         tall64,     // 128 x 64, two workgroups per CU
     } kind;
     int rows() const { return kind == own64 || kind == small64 ? 64 : 128; }
-    int cols() const { return kind == line128 || kind == deep128 || kind == wide128 ? 128 : 64; }
+    int cols() const { return kind == line128 || kind == deep || kind == wide128 ? 128 : 64; }
 };
 
 // splits: the call brings split-K scratch; labels_rows: a mask and no list
@@ -978,15 +1024,13 @@ static inline TileShape choose_tile(const Geom &g, int in_dtype, bool masked, bo
     }
     // (1x1 layers keep the wide tiles down to 256 of them: 2048 -> 512 on 32 x 15 x 20 positions,
     // 300 tiles, 37 us dense / 29 us chained against 51 / 32 us with 128 x 64 tiles)
-    // Long reductions, tap by tap, whose kept rows come to at most one 128 x 128 tile per CU (up to 360 tiles of all rows: 252 at a kept
-    // share of 0.7): one workgroup per CU with three stages on their way.  1x1 layers ran two per CU with one stage each, whose round
-    // trip to memory was most of their time; strided 3x3 layers ran twice the 128 x 64 tiles, which fetch the weights twice
-    // as often.  us, zero-filled, bf16, irrelevant 0.3 / 0.48, before -> here: 2048 -> 512 on 32 x 15 x 20 32.6 / 28.6 -> 24.0 / 22.5, 1024 -> 512
-    // 19.0 / 17.3 -> 15.3 / 14.5; 3x3, stride 2, 512 -> 512 from 32 x 29 x 39 70.6 / 63.2 -> 46.9 / 45.0, 256 -> 256 from 9 x 73 x 119 40.1 / 34.0 -> 27.7 / 26.4.
-    // The count is known on the device only, so both ends of the range pay: 0.1 irrelevant is more than a tile per CU (1x1 35.8 -> 42.3,
-    // 20.3 -> 26.3; 3x3 105.8 -> 85.9 all the same), at 0.7 a 3x3 layer's 128 x 64 tiles still fit one round (36.1 -> 41.6; 1x1 25.7 -> 20.8).
-    const int stages = g.kh * g.kw * ((g.c_in * (in_dtype == FC_FP8 ? 1 : 2) + 127) / 128);
-    if ((k1 || k3) && g.c_out > 64 && masked && !splits && tiles128 >= 256 && tiles128 <= 360 && stages >= 12) return {TileShape::deep128};
+    // Long reductions, tap by tap: from a 128 x 128 tile per CU on (fewer leave CUs without one) to as many rows as a 192 x 128 tile per CU
+    // covers, so that 1x1 layers are one round whatever the mask keeps (1024 -> 512 on 32 x 15 x 25, 376 tiles, 0.1 / 0.5 / 0.9 / 1 kept: 11.2 /
+    // 17.6 / 19.5 / 19.7 -> 12.1 / 14.2 / 19.0 / 20.4).  Below twelve stages there is little to keep on its way.
+    const int cus = conv_grid_cus(), stages = g.kh * g.kw * ((g.c_in * (in_dtype == FC_FP8 ? 1 : 2) + 127) / 128);
+    if ((k1 || k3) && g.c_out > 64 && masked && !labels_rows && !splits && stages >= 12 && tiles128 >= cus &&
+        (int64_t)((g.m + 191) / 192) * ((g.c_out + 127) / 128) <= cus)
+        return {TileShape::deep};
     if (g.c_out > 64 && tiles128 >= (k1 ? 256 : 512)) return {TileShape::wide128};
     // narrow layers with many tiles: two stage buffers, so that three workgroups fit a CU
     // and overlap each other's set-up and epilogue
@@ -1045,6 +1089,22 @@ bool conv_mfma_supported(const Geom &g, int in_dtype, int out_dtype)
 }
 #endif
 
+// more than 64 KB of dynamic LDS has to be allowed once per function and device; two
+// threads that both find the bit clear both set the attribute, which is harmless
+[[maybe_unused]] static hipError_t allow_lds(const void *kern, size_t lds, std::atomic<uint64_t> &devices)
+{
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    const uint64_t dev_bit = 1ull << (dev & 63);
+    if (!(devices.load(std::memory_order_acquire) & dev_bit)) {
+        e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+        devices.fetch_or(dev_bit, std::memory_order_release);
+    }
+    return hipSuccess;
+}
+
 template <int DT, typename TO, bool CMP, int TM, int TN, int WM, int WN, int TAPC, int NB, int MINW, int SL = 0, int NBW = 2, bool OWN = false>
 static hipError_t launch_dma(const Geom &g, const void *x, const uint8_t *mask_in, const uint8_t *mask_out,
                              const void *w, const float *bias, const int32_t *idx, const int32_t *count,
@@ -1052,25 +1112,30 @@ static hipError_t launch_dma(const Geom &g, const void *x, const uint8_t *mask_i
 {
     auto kern = k_conv_dma<DT, TO, TM, TN, WM, WN, TAPC, NB, MINW, SL, NBW, CMP, OWN>;
     constexpr size_t lds = dma_lds_bytes<TM, TN, NB, SL, NBW>();
-    // more than 64 KB of dynamic LDS has to be allowed once per function and device; two
-    // threads that both find the bit clear both set the attribute, which is harmless
     static std::atomic<uint64_t> attr_devices{0};
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
+    const hipError_t e = allow_lds(reinterpret_cast<const void *>(kern), lds, attr_devices);
     if (e != hipSuccess) return e;
-    const uint64_t dev_bit = 1ull << (dev & 63);
-    if (!(attr_devices.load(std::memory_order_acquire) & dev_bit)) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)lds);
-        if (e != hipSuccess) return e;
-        attr_devices.fetch_or(dev_bit, std::memory_order_release);
-    }
     const int64_t max_tiles = (int64_t)((g.m + TM - 1) / TM) * ((g.c_out + TN - 1) / TN);
     const int64_t cap = 256 * 8;
     int blocks = (int)((max_tiles < cap ? max_tiles : cap) + 7) & ~7; // a multiple of the XCD count
     if (partials && !OWN) blocks = kSplitGrid; // few tiles: enough workgroups for the K-split to fill the chip
     hipLaunchKernelGGL(kern, dim3(blocks), dim3(WM * WN * 64), lds, s, g, (const uint16_t *)x, mask_in, mask_out,
                        (const uint16_t *)w, bias, idx, count, (TO *)out, partials, tile_counters);
+    return hipGetLastError();
+}
+
+template <int DT, typename TO, int TAPC, bool CMP>
+static hipError_t launch_deep(const Geom &g, const void *x, const uint8_t *mask_in, const uint8_t *mask_out, const void *w,
+                              const float *bias, const int32_t *idx, const int32_t *count, void *out, float *, int32_t *, hipStream_t s)
+{
+    auto kern = k_conv_deep<DT, TO, TAPC, CMP>;
+    constexpr size_t lds = deep_lds_bytes<TAPC>();
+    static_assert(lds <= 160 * 1024, "LDS of a CU");
+    static std::atomic<uint64_t> attr_devices{0};
+    const hipError_t e = allow_lds(reinterpret_cast<const void *>(kern), lds, attr_devices);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3(conv_grid_cus()), dim3(256), lds, s, g, conv_grid_cus(), (const uint16_t *)x, mask_in, mask_out,
+                       (const uint16_t *)w, bias, idx, count, (TO *)out);
     return hipGetLastError();
 }
 
@@ -1094,8 +1159,8 @@ static hipError_t launch_tile(const Geom &g, const void *x, const uint8_t *mask_
     case TileShape::line64:
         if constexpr (TAPC == 9) return launch_dma<DT, TO, CMP, 128, 64, 2, 2, TAPC, 3, 2, 160, 3>(FC_ARGS);
         break;
-    case TileShape::deep128:
-        if constexpr (TAPC != 32) return launch_dma<DT, TO, CMP, 128, 128, 2, 2, TAPC, 4, 2>(FC_ARGS);
+    case TileShape::deep:
+        if constexpr (TAPC != 32) return launch_deep<DT, TO, TAPC, CMP>(FC_ARGS);
         break;
     case TileShape::wide128:
         return launch_dma<DT, TO, CMP, 128, 128, 2, 2, TAPC, (sizeof(TO) == 4 ? 3 : 2), 2>(FC_ARGS);

@@ -624,13 +624,15 @@ def test_counters_with_garbage_are_cleared_where_a_reduction_is_split(layer, mas
 
 
 @pytest.mark.parametrize("layer,dtype", [
-    # n, h, w, ci, co, k, s, p, d: 256 .. 360 tiles of 128 x 128, twelve stages and more: one deep tile per CU; rows and channels off the tile
+    # n, h, w, ci, co, k, s, p, d: from 256 tiles of 128 x 128 to 256 of 192 x 128, twelve stages and more: one deep tile per CU; rows and
+    # channels off the tile
     ((8, 32, 32, 768, 512, 1, 1, 0, 1), synth.BF16), ((9, 36, 35, 800, 400, 1, 1, 0, 1), synth.F16),
-    ((6, 61, 59, 136, 1000, 3, 2, 1, 1), synth.BF16), ((5, 57, 59, 256, 256, 3, 1, 2, 2), synth.F16), ((8, 32, 33, 1536, 512, 1, 1, 0, 1), synth.FP8)])
-@pytest.mark.parametrize("irr", [0.48, 0.02])
+    ((6, 61, 59, 136, 1000, 3, 2, 1, 1), synth.BF16), ((5, 57, 59, 256, 256, 3, 1, 2, 2), synth.F16), ((8, 32, 33, 1536, 512, 1, 1, 0, 1), synth.FP8),
+    ((32, 15, 25, 768, 512, 1, 1, 0, 1), synth.BF16), ((7, 62, 83, 208, 512, 3, 2, 1, 1), synth.FP8)])
+@pytest.mark.parametrize("irr", [0.48, 0.02, 0.8])
 def test_long_reductions_of_a_tile_per_cu(layer, dtype, irr):
-    """Against the oracle on sampled positions; zero rows to the byte, kept rows all written.  Nearly all rows kept: more tiles
-    than CUs."""
+    """Against the oracle on sampled positions; zero rows to the byte, kept rows all written; rows in list order the same bits.  Nearly all
+    rows kept: more 128 x 128 tiles than CUs (1x1: tiles of 192 rows); few kept: at most one 128 x 64 tile per CU (3x3)."""
     torch = G.torch_mod()
     n, h, w, ci, co, k, s, p, d = layer
     x = synth.activations((n, h, w, ci), dtype, 254, 1)
@@ -648,6 +650,10 @@ def test_long_reductions_of_a_tile_per_cu(layer, dtype, irr):
     keep = m_out.cpu().numpy() != 0
     kd = torch.from_numpy(keep).to(G.dev())
     assert not bool(out[~kd].view(torch.int32).any()) and not bool((out[kd] == 7.0).all(dim=-1).any())
+    desc = B.conv_desc(n, h, w, ci, co, *geo, dtype, B.F32, B.RELU | B.COMPACT_OUT)
+    rows = B.focused_conv2d(desc, G.to_dev(x, dtype), G.to_dev(wt, dtype), torch.from_numpy(bias).to(G.dev()), mask_in=md, mask_out=m_out,
+                            idx=idx, count=count)
+    assert torch.equal(rows.reshape(-1, co)[:int(count)], out[kd])
     pos = np.sort(np.random.default_rng(254).choice(np.flatnonzero(keep.reshape(-1)), size=400, replace=False))
     shape = O.ConvShape(n, h, w, ci, co, k, k, (s, s), (p, p), (d, d), relu=True)
     want = O.focused_conv2d_at(shape, x, wt, pos, bias=bias, mask_in=mask, dtype=dtype)
