@@ -94,27 +94,13 @@ void k_conv_res3(Geom g, FastDiv div_cpr, bool bias_last, const unsigned char *_
         }
     }
 
-    // ---- the waves that clear: 64 positions at a time, the next labels on their way.  The rows of 64
-    // positions are one piece of memory, so a lane's 16-byte pieces need no list of the dropped rows ----
+    // ---- the waves that clear ----
     if (wave >= kResWaves) {
         wait_vmcnt<0>();
         __syncthreads();
-        const int cpr = g.c_out * (int)sizeof(TO) / 16; // 16-byte pieces per row
-        const u32x4_t zero4 = {0u, 0u, 0u, 0u};
-        u32x4_t *o4 = reinterpret_cast<u32x4_t *>(out);
         const int per_wg = nwaves - kResWaves;
-        const int64_t step = (int64_t)gridDim.x * per_wg * 64;
-        int64_t p0 = ((int64_t)blockIdx.x * per_wg + (wave - kResWaves)) * 64;
-        bool kept = p0 + lane >= g.m || position_kept(g, mask_in, mask_out, p0 + lane);
-        for (; p0 < g.m; p0 += step) {
-            const uint64_t drop = __ballot(!kept);
-            const int64_t pn = p0 + step + lane;
-            kept = pn >= g.m || position_kept(g, mask_in, mask_out, pn);
-            if (drop == 0) continue;
-            u32x4_t *at = o4 + p0 * cpr;
-            for (int c = lane; c < 64 * cpr; c += 64)
-                if ((drop >> fast_div((uint32_t)c, div_cpr)) & 1ull) __builtin_nontemporal_store(zero4, at + c);
-        }
+        clear_irrelevant_runs(g, mask_in, mask_out, out, g.c_out * (int)sizeof(TO) / 16, div_cpr, 0, g.m,
+                              (int)blockIdx.x * per_wg + (wave - kResWaves), (int)gridDim.x * per_wg);
         return;
     }
 

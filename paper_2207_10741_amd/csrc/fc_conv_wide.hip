@@ -14,16 +14,21 @@
 // Nothing stands in the way of the products: fragments are read a k-step ahead, across the stage boundary as well (the barrier
 // stands inside the last k-step of a stage, whose remaining products cover the first reads of the next one), every read and
 // load goes out between two products (in bursts between the k-steps: 1 126 us with four waves, 964 so), a stage's slab is
-// sent for a stage ahead, a line two.
+// sent for a stage ahead, a line two.  A stage of one or two granules lasts less than a round trip, so tiles of at most two, whose
+// lines are short, keep a third slab in the room behind them and send for slabs two stages ahead.
 //
 // Tiles are made of granules of WM * 32 rows; XCD j takes the j-th eighth of the granules and deals them to its workgroups side by
 // side, every workgroup the same number but for one, in as few rounds as tiles of PBX granules allow and all rounds alike: 4.7 granules
 // a workgroup are two tiles of two or three, not one of four and one of one, whose stages would last no less than a round
-// trip (256 -> 256 on 16 x 60 x 80 without a mask 92 -> 88 .. 91 us).  A tile whose pixel line would not fit
-// (a fragmented mask) takes fewer granules; the smallest always fits (three slots a row).
+// trip (256 -> 256 on 16 x 60 x 80 without a mask 92 -> 88 .. 91 us).  A tile whose pixel line would not fit (a fragmented mask)
+// gathers its rows tap by tap instead, into the same buffers, a buffer of rows a stage; the order of the sums is the same.  (With
+// fewer granules per tile instead: 512 -> 512 on 128 x 16 x 16, 0.3 kept at random, 110 us, so 64; 256 -> 256 on 128 x 32 x 32 87, so 51.)
 //
 // Irrelevant rows are cleared inside the loop: every tile comes with a range of positions, whose labels it reads in its
-// set-up; a stage's stores go out right after its barrier, before its loads, and have a stage to complete.
+// set-up, and a stage's stores go out at its end.  Loads and stores count in one counter and come back in order, so the waits
+// for loads let the stores that went out after them be (as if they were not there, a store had one stage to complete).  Workgroups that
+// the longest quota leaves without a tile only clear.  Zero-filled layers that keep little, before -> so: 128 -> 128 on
+// 128 x 64 x 64, 0.1 / 0.2 kept 44.5 / 61 -> 33 / 52 us, 256 -> 256 on 128 x 32 x 32 36 / 48 -> 32 / 42.
 #include "fc_dma_util.hpp"
 #include <atomic>
 #include <type_traits>
@@ -33,10 +38,19 @@ namespace fc {
 constexpr int kWideWaves = 8, kWideThreads = kWideWaves * 64;
 constexpr int kWideWords = 3; // positions a tile clears: up to 64 * 3 per wave
 
-template <int WM, int TN, int PBX, int SL>
+// Tiles of at most two granules have three slabs instead of two: the third lies behind their lines, which are at most SLS
+// slots long (or three buffers of rows).
+template <int WM, int TN, int SL, int SLS>
+constexpr uint32_t wide_x_bytes()
+{
+    constexpr uint32_t two = 2u * SL * 128u, line3 = 2u * SLS * 128u + TN * 128u, rows3 = 3u * 2u * WM * 32u * 128u + TN * 128u;
+    return two > line3 ? (two > rows3 ? two : rows3) : (line3 > rows3 ? line3 : rows3);
+}
+
+template <int WM, int TN, int PBX, int SL, int SLS>
 constexpr size_t wide_lds_bytes()
 {
-    return (size_t)2 * SL * 128 + (size_t)2 * TN * 128 + (size_t)(2 * WM * PBX * 32 + 3 * SL + 32) * sizeof(int32_t) + (size_t)kWideWords * kWideWaves * 8;
+    return wide_x_bytes<WM, TN, SL, SLS>() + (size_t)2 * TN * 128 + (size_t)(2 * WM * PBX * 32 + 3 * SL + 32) * sizeof(int32_t) + (size_t)kWideWords * kWideWaves * 8;
 }
 
 // f(integral_constant 0) .. f(integral_constant N - 1)
@@ -55,7 +69,7 @@ struct WideArgs {
 
 // DT: storage type; TO: float or the 16-bit / 8-bit carrier of the output; WM x WN waves (eight); TN = WN * 64 output channels; PBX: most
 // 32-row blocks of a wave; SL: slots of a pixel line.
-template <int DT, typename TO, int WM, int PBX, int SL>
+template <int DT, typename TO, int WM, int PBX, int SL, int SLS>
 __global__ __launch_bounds__(kWideThreads, 2)
 void k_conv_wide(Geom g, WideArgs wa, const unsigned char *__restrict__ x, const uint8_t *__restrict__ mask_in,
                  const uint8_t *__restrict__ mask_out, const unsigned char *__restrict__ w, const float *__restrict__ bias,
@@ -67,21 +81,21 @@ void k_conv_wide(Geom g, WideArgs wa, const unsigned char *__restrict__ x, const
     constexpr uint32_t KSTEP = kStepBytes<DT>;
     constexpr int KK = kStageBytes / (int)KSTEP;
     constexpr int RPL = NT / 8;                         // LDS rows the eight waves' loads cover side by side
-    constexpr int XL = SL / RPL, WL = TN / RPL;        // wave loads per wave: a line, a slab
-    constexpr int RIT = (TM + NT - 1) / NT, SIT = (SL + NT - 1) / NT;
-    constexpr uint32_t XB = (uint32_t)SL * 128u, WB = (uint32_t)TN * 128u, HALF = KSTEP / 32u;
-    static_assert(SL % RPL == 0 && SL >= GR * 3 + 1, "whole wave loads; the smallest tile fits");
+    constexpr int WL = TN / RPL;                       // wave loads per wave: a slab
+    constexpr int SIT = (SL + NT - 1) / NT;
+    constexpr uint32_t WB = (uint32_t)TN * 128u, HALF = KSTEP / 32u;
+    constexpr uint32_t W0 = wide_x_bytes<WM, TN, SL, SLS>(); // slabs 0 and 1 lie from here on, slab 2 right below
+    static_assert(SL % RPL == 0 && SLS % RPL == 0 && SL >= TM && SLS >= 2 * GR && TM <= NT, "whole wave loads; rows fit where lines do; one row a thread");
 
     extern __shared__ __align__(16) unsigned char smem_raw[];
     const uint32_t lds0 = (uint32_t)reinterpret_cast<uintptr_t>(smem_raw);
-    int32_t *row_p = reinterpret_cast<int32_t *>(smem_raw + 2 * XB + 2 * WB);
+    int32_t *row_p = reinterpret_cast<int32_t *>(smem_raw + W0 + 2 * WB);
     int32_t *row_cs = row_p + TM;
     int32_t *slot_pix = row_cs + TM;
     int32_t *slot_hw = slot_pix + SL;
     uint32_t *slot_bits = reinterpret_cast<uint32_t *>(slot_hw + SL);
-    int32_t *scan_part = reinterpret_cast<int32_t *>(slot_bits + SL); // [RIT][8] wave totals
-    int32_t *edge = scan_part + 16;                                    // slots of the first 1 .. PBX granules
-    uint64_t *drop = reinterpret_cast<uint64_t *>(edge + 16);          // [kWideWords][8] irrelevant ones of the positions to clear
+    int32_t *scan_part = reinterpret_cast<int32_t *>(slot_bits + SL); // [8] wave totals
+    uint64_t *drop = reinterpret_cast<uint64_t *>(scan_part + 32);     // [kWideWords][8] irrelevant ones of the positions to clear
 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // (what follows from the thread number alone is computed per tile: kept for the whole kernel it takes the registers
@@ -109,24 +123,34 @@ void k_conv_wide(Geom g, WideArgs wa, const unsigned char *__restrict__ x, const
     const int nb = (rows + GR - 1) / GR, total = nb * wa.n_nt;
     const int xcd = (int)blockIdx.x & 7, slot_x = (int)blockIdx.x >> 3, per_xcd = (int)gridDim.x >> 3;
     const int x0 = (int)(((int64_t)total * xcd) >> 3), x1 = (int)(((int64_t)total * (xcd + 1)) >> 3);
-    // a workgroup's quota is q granules or q + 1 (extra: how many of the workgroups before it have one more), cut into rounds
-    const int n_x = x1 - x0, q = n_x / per_xcd, rem = n_x - q * per_xcd, rounds = (q + (rem > 0) + PBX - 1) / PBX;
-    const int extra = (slot_x * rem) / per_xcd, mine = q + ((slot_x + 1) * rem) / per_xcd - extra;
-
-    // ---- zero-fill: a granule clears zq positions (all channels); masks that keep little are cleared at the end ----
+    // (with rows to clear no more workgroups take tiles than the longest quota needs: 410 granules are two each for 205 of 256, and
+    // the others only clear)
     const bool zero_fill = mask_in && !(g.flags & FC_SKIP_ZERO_FILL);
-    const int zq = total > 0 ? (int)(((int64_t)g.m + total - 1) / total) : 0;
-    const bool clear_in_loop = zero_fill && total > 0 && zq <= kWideWords * NT / PBX;
-    const int cpr = g.c_out * (int)sizeof(TO) / 16;
+    const int n_x = x1 - x0, qm = (n_x + per_xcd - 1) / per_xcd;
+    const int takers = zero_fill ? (qm > 0 ? (n_x + qm - 1) / qm : 0) : per_xcd, clearers = per_xcd - takers;
+    // a workgroup's quota is q granules or q + 1 (extra: how many of the workgroups before it have one more), cut into rounds
+    const int q = takers > 0 ? n_x / takers : 0, rem = n_x - q * takers, rounds = (qm + PBX - 1) / PBX;
+    const int extra = takers > 0 ? (slot_x * rem) / takers : 0, mine = takers > 0 ? q + ((slot_x + 1) * rem) / takers - extra : 0;
 
-    for (int round = 0; round < rounds; ++round) {
+    // ---- zero-fill: an XCD clears the j-th eighth of the positions (all channels).  A workgroup without tiles clears what two with
+    // tiles do; a granule comes with zq positions, or where those are too many (masks that keep little) its share is cleared
+    // at the end ----
+    const int cpr = g.c_out * (int)sizeof(TO) / 16;
+    const int zx0 = (int)(((int64_t)g.m * xcd) >> 3), zx1 = (int)(((int64_t)g.m * (xcd + 1)) >> 3);
+    const int z_apart = n_x > 0 ? (int)((int64_t)(zx1 - zx0) * (2 * clearers) / (2 * clearers + takers)) : zx1 - zx0;
+    const int zt0 = zx0 + z_apart, zq = n_x > 0 ? (zx1 - zt0 + n_x - 1) / n_x : 0;
+    const bool clear_in_loop = zero_fill && n_x > 0 && (int64_t)zq * ((qm + rounds - 1) / max(rounds, 1)) <= kWideWords * NT;
+    if (zero_fill && slot_x >= takers)
+        clear_irrelevant_runs(g, mask_in, mask_out, out, cpr, wa.cpr, zx0, zt0, (slot_x - takers) * kWideWaves + wave, clearers * kWideWaves);
+
+    for (int round = slot_x < takers ? 0 : rounds; round < rounds; ++round) {
         const int qa = (q * round) / rounds, qb = ((q + 1) * round) / rounds; // granules of the rounds before, per workgroup of either kind
         const int ca = (q * (round + 1)) / rounds - qa, cb = ((q + 1) * (round + 1)) / rounds - qb;
-        int g0 = x0 + (per_xcd - rem) * qa + rem * qb + (slot_x - extra) * ca + extra * cb;
+        int g0 = x0 + (takers - rem) * qa + rem * qb + (slot_x - extra) * ca + extra * cb;
         const int g1 = g0 + (mine > q ? cb : ca);
         while (g0 < g1) {
             const int nt = g0 / nb, rg = g0 - nt * nb;
-            const int kmax = min(min(g1 - g0, nb - rg), PBX);
+            const int k = min(min(g1 - g0, nb - rg), PBX);
             const int co0 = nt * TN, m0 = rg * GR;
             const int tid = thread_number(), lane = tid & 63, slot8 = lane & 7;
             // fragment addressing as in the tiled kernel
@@ -150,7 +174,7 @@ void k_conv_wide(Geom g, WideArgs wa, const unsigned char *__restrict__ x, const
                 wkh += wc;
             };
             auto issue_w = [&](int j, uint32_t buf) __attribute__((always_inline)) {
-                dma_load16_s(rsrc_w, woff, ld_sw + (uint32_t)j * RPL * wrow, lds_wave + 2u * XB + buf * WB + (uint32_t)j * (RPL * 128u));
+                dma_load16_s(rsrc_w, woff, ld_sw + (uint32_t)j * RPL * wrow, lds_wave + W0 + (buf < 2 ? buf * WB : 0u - WB) + (uint32_t)j * (RPL * 128u));
             };
             __syncthreads(); // the previous tile is done with LDS
 #pragma unroll
@@ -161,35 +185,31 @@ void k_conv_wide(Geom g, WideArgs wa, const unsigned char *__restrict__ x, const
             }
 
             // ---- set-up: rows -> slots of the pixel line -> tap bits; the labels of the positions to clear ----
-            int sp[RIT], sb[RIT], sow[RIT], sih[RIT], incl[RIT];
-            bool ladj[RIT], radj[RIT];
-#pragma unroll
-            for (int i = 0; i < RIT; ++i) {
-                const int r = tid + i * NT, m = m0 + r;
-                const bool live = r < kmax * GR && m < rows;
-                sp[i] = live ? (idx ? idx[m] : m) : -1;
-                const int prev = (live && r > 0) ? (idx ? idx[m - 1] : m - 1) : -2;
-                const int next = (live && r + 1 < kmax * GR && m + 1 < rows) ? (idx ? idx[m + 1] : m + 1) : -2;
-                const int q = (int)fast_div((uint32_t)max(sp[i], 0), g.div_wo);
-                sow[i] = max(sp[i], 0) - q * g.wo;
-                sb[i] = (int)fast_div((uint32_t)q, g.div_ho);
-                sih[i] = (q - sb[i] * g.ho) * g.sh - g.ph;
-                ladj[i] = live && prev == sp[i] - 1 && sow[i] > 0;
-                radj[i] = live && next == sp[i] + 1 && sow[i] < g.wo - 1;
-                const int cnt = r < kmax * GR ? (live ? 1 + !ladj[i] + !radj[i] : 1) : 0;
-                incl[i] = wave_inclusive_scan(cnt);
-                if (lane == 63) scan_part[i * kWideWaves + wave] = incl[i];
-                if (r < TM) row_p[r] = sp[i];
-            }
-            const int z0 = clear_in_loop ? min(g0 * zq, g.m) : 0;
-            int zl = 0; // positions this tile clears (set when its granules are known)
+            // (one row a thread)
+            const bool live = tid < k * GR && m0 + tid < rows;
+            const int m = m0 + tid;
+            const int sp = live ? (idx ? idx[m] : m) : -1;
+            const int prev = (live && tid > 0) ? (idx ? idx[m - 1] : m - 1) : -2;
+            const int next = (live && tid + 1 < k * GR && m + 1 < rows) ? (idx ? idx[m + 1] : m + 1) : -2;
+            const int sq = (int)fast_div((uint32_t)max(sp, 0), g.div_wo);
+            const int sow = max(sp, 0) - sq * g.wo;
+            const int sb = (int)fast_div((uint32_t)sq, g.div_ho);
+            const int sih = (sq - sb * g.ho) * g.sh - g.ph;
+            const bool ladj = live && prev == sp - 1 && sow > 0;
+            const bool radj = live && next == sp + 1 && sow < g.wo - 1;
+            const int lead = live && !ladj, cnt = tid < k * GR ? 1 + lead + (live && !radj) : 0;
+            const int incl = wave_inclusive_scan(cnt);
+            if (lane == 63) scan_part[wave] = incl;
+            if (tid < TM) row_p[tid] = sp;
+            const int z0 = clear_in_loop ? min(zt0 + (g0 - x0) * zq, zx1) : 0;
+            const int zl = clear_in_loop ? min(k * zq, zx1 - z0) : 0; // positions this tile clears
             {
                 bool kept[kWideWords];
 #pragma unroll
                 for (int i = 0; i < kWideWords; ++i) {
                     const int p = z0 + i * NT + tid;
                     kept[i] = true;
-                    if (clear_in_loop && i * NT < kmax * zq && p < g.m && i * NT + tid < kmax * zq) kept[i] = position_kept(g, mask_in, mask_out, p);
+                    if (i * NT + tid < zl) kept[i] = position_kept(g, mask_in, mask_out, p);
                 }
 #pragma unroll
                 for (int i = 0; i < kWideWords; ++i) {
@@ -198,100 +218,105 @@ void k_conv_wide(Geom g, WideArgs wa, const unsigned char *__restrict__ x, const
                 }
             }
             __syncthreads();
-            {
-                int carry = 0;
+            int ns = 1, before = 0; // slots of the line (a row past the end reads the slot after its own as well)
 #pragma unroll
-                for (int i = 0; i < RIT; ++i) {
-                    int before = carry;
+            for (int v = 0; v < kWideWaves; ++v) {
+                const int t = scan_part[v];
+                before += v < wave ? t : 0;
+                ns += t;
+            }
+            ns = __builtin_amdgcn_readfirstlane(ns);
+            // A line that does not fit (a fragmented mask): the rows are gathered tap by tap, into the same buffers.
+            const bool by_tap = ns > (k <= 2 ? SLS : SL);
+            const int iwc = sow - g.pw + 1;
+            const int pixc = (sb * g.h + sih) * g.w + iwc;
+            if (by_tap) {
+                // (the nine bytes of a row are in flight together)
+                uint32_t bits = 0;
+                bool in[9], on[9];
 #pragma unroll
-                    for (int v = 0; v < kWideWaves; ++v) {
-                        const int t = scan_part[i * kWideWaves + v];
-                        before += v < wave ? t : 0;
-                        carry += t;
-                    }
-                    const int r = tid + i * NT;
-                    const bool live = sp[i] >= 0;
-                    const int lead = live ? !ladj[i] : 0, cnt = live ? 1 + lead + !radj[i] : 1;
-                    const int cs = before + incl[i] - cnt + lead;
-                    if (r < kmax * GR) {
-                        row_cs[r] = cs;
-                        if ((r & (GR - 1)) == GR - 1) edge[r / GR] = cs + 2;
-                        const int iwc = sow[i] - g.pw + 1;
-                        const int pixc = (sb[i] * g.h + sih[i]) * g.w + iwc;
-                        const int ih16 = (int)((uint32_t)sih[i] & 0xffffu);
-                        if (live) {
-                            if (cs < SL) {
-                                slot_pix[cs] = pixc;
-                                slot_hw[cs] = ih16 | (int)((uint32_t)iwc << 16);
-                            }
-                            if (!ladj[i] && cs - 1 < SL) {
-                                slot_pix[cs - 1] = pixc - 1;
-                                slot_hw[cs - 1] = ih16 | (int)((uint32_t)(iwc - 1) << 16);
-                            }
-                            if (!radj[i] && cs + 1 < SL) {
-                                slot_pix[cs + 1] = pixc + 1;
-                                slot_hw[cs + 1] = ih16 | (int)((uint32_t)(iwc + 1) << 16);
-                            }
-                        } else if (cs < SL) {
-                            slot_pix[cs] = 0;
-                            slot_hw[cs] = (int)((uint32_t)(-20000) << 16); // never inside an image
+                for (int t = 0; t < 9; ++t) {
+                    const int ih = sih + t / 3 * g.dh, iw = iwc - 1 + t % 3;
+                    in[t] = live && (uint32_t)ih < (uint32_t)g.h && (uint32_t)iw < (uint32_t)g.w;
+                    on[t] = true;
+                    if (mask_in) on[t] = mask_at(mask_in, in[t] ? pixc - 1 + t / 3 * g.dh * g.w + t % 3 : 0, packed_masks);
+                }
+#pragma unroll
+                for (int t = 0; t < 9; ++t) bits |= (uint32_t)(in[t] && on[t]) << t;
+                if (tid < TM) {
+                    slot_pix[tid] = live ? pixc - 1 : 0;
+                    slot_bits[tid] = bits;
+                }
+            } else {
+                const int cs = before + incl - cnt + lead;
+                const int ih16 = (int)((uint32_t)sih & 0xffffu);
+                if (tid < k * GR) {
+                    row_cs[tid] = cs;
+                    if (live) {
+                        slot_pix[cs] = pixc;
+                        slot_hw[cs] = ih16 | (int)((uint32_t)iwc << 16);
+                        if (!ladj) {
+                            slot_pix[cs - 1] = pixc - 1;
+                            slot_hw[cs - 1] = ih16 | (int)((uint32_t)(iwc - 1) << 16);
                         }
+                        if (!radj) {
+                            slot_pix[cs + 1] = pixc + 1;
+                            slot_hw[cs + 1] = ih16 | (int)((uint32_t)(iwc + 1) << 16);
+                        }
+                    } else {
+                        slot_pix[cs] = 0;
+                        slot_hw[cs] = (int)((uint32_t)(-20000) << 16); // never inside an image
                     }
                 }
-            }
-            __syncthreads();
-            // granules whose slots fit (one always does; a row past the end reads the slot after its own as well)
-            int k = 1, ns = edge[0];
+                __syncthreads();
 #pragma unroll
-            for (int j = 1; j < PBX; ++j) {
-                const int e = edge[j];
-                const bool fits = j < kmax && e <= SL && k == j;
-                ns = fits ? e : ns;
-                k = fits ? j + 1 : k;
-            }
-            k = __builtin_amdgcn_readfirstlane(k);
-            ns = __builtin_amdgcn_readfirstlane(min(ns, SL));
+                for (int i = 0; i < SIT; ++i) {
+                    const int sl = tid + i * NT;
+                    const bool used = sl < ns - 1;
+                    const int hw = used ? slot_hw[sl] : 0, pix = used ? slot_pix[sl] : 0;
+                    const int ih0 = (int)(int16_t)(hw & 0xffff), iw = hw >> 16;
+                    bool in[3];
+                    bool on[3];
 #pragma unroll
-            for (int i = 0; i < SIT; ++i) {
-                const int sl = tid + i * NT;
-                const bool live = sl < ns - 1 || (sl < ns && m0 + k * GR <= rows);
-                const int hw = sl < ns ? slot_hw[sl] : 0, pix = sl < ns ? slot_pix[sl] : 0;
-                const int ih0 = (int)(int16_t)(hw & 0xffff), iw = hw >> 16;
-                bool in[3];
-                bool on[3];
-#pragma unroll
-                for (int q = 0; q < 3; ++q) {
-                    const int ih = ih0 + q * g.dh;
-                    in[q] = live && ih >= 0 && ih < g.h && iw >= 0 && iw < g.w;
-                    on[q] = in[q] && (!mask_in || mask_at(mask_in, in[q] ? pix + q * g.dh * g.w : 0, packed_masks));
-                }
-                if (sl < SL) {
-                    slot_bits[sl] = (uint32_t)on[0] | (uint32_t)on[1] << 1 | (uint32_t)on[2] << 2;
-                    if (sl >= ns) slot_pix[sl] = 0;
+                    for (int q = 0; q < 3; ++q) {
+                        const int ih = ih0 + q * g.dh;
+                        in[q] = used && ih >= 0 && ih < g.h && iw >= 0 && iw < g.w;
+                        on[q] = in[q] && (!mask_in || mask_at(mask_in, in[q] ? pix + q * g.dh * g.w : 0, packed_masks));
+                    }
+                    if (sl < SL) {
+                        slot_bits[sl] = (uint32_t)on[0] | (uint32_t)on[1] << 1 | (uint32_t)on[2] << 2;
+                        if (!used) slot_pix[sl] = 0;
+                    }
                 }
             }
             __syncthreads();
             const int nxl = (ns + RPL - 1) / RPL; // loads of a line
-            zl = clear_in_loop ? max(min(z0 + k * zq, g.m) - z0, 0) : 0;
 
-            auto run = [&](auto pb_c) __attribute__((always_inline)) {
+            // PB: 32-row blocks of a wave (granules of the tile); TAP: gathered tap by tap
+            auto run = [&](auto pb_c, auto tap_c) __attribute__((always_inline)) {
                 constexpr int PB = decltype(pb_c)::value;
+                constexpr bool TAP = decltype(tap_c)::value;
+                constexpr int R = PB <= 2 ? 3 : 2;                                     // slabs, and buffers of rows
+                constexpr int XL = TAP ? PB * GR / RPL : (R == 3 ? SLS : SL) / RPL;    // wave loads per wave: rows, a line
+                constexpr uint32_t XB = (TAP ? PB * GR : (R == 3 ? SLS : SL)) * 128u;  // a buffer of theirs
+                constexpr int NG = TAP ? 9 : 3, PW = TAP ? 3 : 10;                     // gates per slot (row) this lane gathers; of them a word holds
+                static_assert((TAP ? R : 2) * XB + (R - 2) * WB <= W0, "buffers of rows and the third slab");
                 uint32_t hxoff[XL];
-                uint32_t hxbits[2] = {0, 0}; // three bits per slot this lane gathers
-                static_assert(XL <= 20, "ten slots a word");
+                uint32_t hxbits[2] = {0, 0};
+                static_assert(XL <= 2 * PW, "two words");
 #pragma unroll
                 for (int j = 0; j < XL; ++j) {
                     const int sl = j * RPL + wave * 8 + (lane >> 3);
                     hxoff[j] = (uint32_t)slot_pix[sl] * (uint32_t)(g.c_in * ES) + (uint32_t)(slot8 ^ FC_SWZ(sl)) * 16u + xbias;
-                    hxbits[j / 10] |= slot_bits[sl] << (3 * (j % 10));
+                    hxbits[j / PW] |= slot_bits[sl] << (NG * (j % PW));
                 }
-                uint32_t xfa[PB][3];
+                uint32_t xfa[PB][TAP ? 1 : 3];
 #pragma unroll
                 for (int a = 0; a < PB; ++a) {
-                    const int cs = row_cs[(wave_m * PB + a) * 32 + (lane & 31)];
+                    const int r = (wave_m * PB + a) * 32 + (lane & 31), cs = TAP ? r : row_cs[r] - 1;
 #pragma unroll
-                    for (int t = 0; t < 3; ++t) {
-                        const int sl = cs + t - 1;
+                    for (int t = 0; t < (TAP ? 1 : 3); ++t) {
+                        const int sl = cs + t;
                         xfa[a][t] = (uint32_t)sl * 128u + (uint32_t)(((lane >> 5) * HALF) ^ FC_SWZ(sl)) * 16u;
                     }
                 }
@@ -310,39 +335,53 @@ void k_conv_wide(Geom g, WideArgs wa, const unsigned char *__restrict__ x, const
                             acc[a][b][q * 4 + 3] = bq.w;
                         }
                     }
-                int xkh = 0, xcc = 0, xleft = groups;
+                int xkh = 0, xcc = 0, xkw = 0, xleft = TAP ? 3 * groups : groups;
                 uint32_t ld_sx = 0, ld_sel = 0;
                 auto next_x = [&]() __attribute__((always_inline)) {
-                    ld_sx = xleft > 0 ? (uint32_t)((xkh * g.dh) * g.w * g.c_in + xcc * TK) * (uint32_t)ES : 0u;
-                    ld_sel = xleft > 0 ? 1u << xkh : 0u;
+                    ld_sx = xleft > 0 ? (uint32_t)(((xkh * g.dh) * g.w + xkw) * g.c_in + xcc * TK) * (uint32_t)ES : 0u;
+                    ld_sel = xleft > 0 ? 1u << (TAP ? xkh * 3 + xkw : xkh) : 0u;
                     --xleft;
-                    const int wrap = (xcc + 1 == cchunks);
-                    xcc = wrap ? 0 : xcc + 1;
+                    const int w3 = !TAP || xkw == 2, wrap = w3 & (xcc + 1 == cchunks);
+                    if constexpr (TAP) xkw = w3 ? 0 : xkw + 1;
+                    xcc = w3 ? (wrap ? 0 : xcc + 1) : xcc;
                     xkh += wrap;
                 };
                 auto issue_x = [&](int j, uint32_t buf) __attribute__((always_inline)) {
-                    if (j < nxl)
-                        dma_load16_s(rsrc_x, (hxbits[j / 10] & (ld_sel << (3 * (j % 10)))) ? hxoff[j] : kOutOfRange, ld_sx, lds_wave + buf * XB + (uint32_t)j * (RPL * 128u));
+                    if (TAP || j < nxl)
+                        dma_load16_s(rsrc_x, (hxbits[j / PW] & (ld_sel << (NG * (j % PW)))) ? hxoff[j] : kOutOfRange, ld_sx, lds_wave + buf * XB + (uint32_t)j * (RPL * 128u));
                 };
-                // zero stores of a stage: wave v clears the positions of its own label words, in whole 64-piece runs
+                // Zero stores of a stage: wave v clears the positions of its own label words, in whole 64-piece runs.  A run is one store
+                // instruction (a lane with nothing to clear is out of range), so that the waits can count them: z1 and z2 are those of the
+                // last two stages.  Lane i holds label word i (an LDS read here would wait for all fragments on their way).
                 const int zruns = ((zl + NT - 1) / NT) * cpr, zstep = (zruns + 3 * groups - 1) / (3 * groups);
-                int zc = 0;
-                const u32x4_t zero4 = {0u, 0u, 0u, 0u};
+                const u32x4_t rsrc_z = make_rsrc_words(out + (int64_t)z0 * g.c_out, (uint32_t)zl * (uint32_t)cpr * 16u);
+                const uint64_t dropped = drop[min(lane, kWideWords - 1) * kWideWaves + wave];
+                int zc = 0, z1 = 0, z2 = 0;
                 auto clear_some = [&]() __attribute__((always_inline)) {
+                    z2 = z1;
+                    z1 = 0;
                     for (int e = 0; e < zstep && zc < zruns; ++e, ++zc) {
                         const int wd = (int)fast_div((uint32_t)zc, wa.cpr), run = zc - wd * cpr; // word, run of 64 pieces in it
-                        const uint64_t d = drop[wd * kWideWaves + wave];
+                        const uint64_t d = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)dropped, wd) |
+                                           (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(dropped >> 32), wd) << 32;
                         if (d == 0) continue;
                         const uint32_t pc = (uint32_t)(run * 64 + lane), ps = fast_div(pc, wa.cpr);
-                        const int zp = z0 + wd * NT + wave * 64;
-                        if (((d >> ps) & 1ull) && wd * NT + wave * 64 + (int)ps < zl)
-                            __builtin_nontemporal_store(zero4, reinterpret_cast<u32x4_t *>(out) + (int64_t)zp * cpr + pc);
+                        store16_zero_nt(rsrc_z, ((d >> ps) & 1ull) ? ((uint32_t)((wd * kWideWaves + wave) * 64 * cpr) + pc) * 16u : kOutOfRange);
+                        ++z1;
                     }
                 };
 
-                next_x();
+                if constexpr (R == 3) {
+                    next_w();
 #pragma unroll
-                for (int j = 0; j < XL; ++j) issue_x(j, 0);
+                    for (int j = 0; j < WL; ++j) issue_w(j, 2);
+                }
+#pragma unroll
+                for (int d = 0; d < (TAP ? R : 1); ++d) {
+                    next_x();
+#pragma unroll
+                    for (int j = 0; j < XL; ++j) issue_x(j, (uint32_t)d);
+                }
                 wait_vmcnt<0>();
                 __syncthreads();
 
@@ -351,11 +390,11 @@ void k_conv_wide(Geom g, WideArgs wa, const unsigned char *__restrict__ x, const
                 // fragment r of a k-step, in the order the products need them: w0, x0, w1, x1 ..
                 auto read_frag = [&](int r, int set, uint32_t xb, uint32_t wb, int t, int kk) __attribute__((always_inline)) {
                     const unsigned char *xs = smem_raw + xb * XB;
-                    const unsigned char *ws = smem_raw + 2u * XB + wb * WB + (uint32_t)(wave_n * (CB * 32)) * 128u + frag_row;
+                    const unsigned char *ws = smem_raw + W0 + (wb < 2 ? wb * WB : 0u - WB) + (uint32_t)(wave_n * (CB * 32)) * 128u + frag_row;
                     if (r == 1 || r > CB) {
                         const int a = r == 1 ? 0 : r - CB;
                         // (the exclusive or stays here: kept for all k-steps the addresses take the registers of the fragments)
-                        uint32_t o = xfa[a][t];
+                        uint32_t o = xfa[a][TAP ? 0 : t];
                         if (kk > 0) __asm__ volatile("v_xor_b32 %0, %1, %0" : "+v"(o) : "n"(kk * (int)KSTEP));
                         xf[set][a].load(xs, o);
                     } else {
@@ -376,17 +415,25 @@ void k_conv_wide(Geom g, WideArgs wa, const unsigned char *__restrict__ x, const
                         constexpr bool last = kk == KK - 1;
                         constexpr int BAR = NM / 4; // the barrier of a stage stands after this many products of its last k-step
                         constexpr int from = last ? BAR : 0, gaps = NM - from;
-                        // loads: after the barrier the slab of the stage after the next, which has a stage to arrive; on tap 1, in
-                        // front of which only a slab was sent for, the next group's line, which has two
-                        constexpr int nw = last ? WL : 0, nx = (t == 1 && kk == 0) ? XL : 0, nl = nw + nx;
-                        if constexpr (t == 1 && kk == 0) next_x();
+                        // loads: after the barrier the slab R stages ahead, and tap by tap the rows, into the buffers just read;
+                        // a line goes out a group ahead, when everyone has left the line before it: with two slabs
+                        // on tap 1, in front of which only a slab was sent for, with three on tap 0
+                        constexpr int nw = last ? WL : 0, nx = (TAP ? last : t == (R == 3 ? 0 : 1) && kk == 0) ? XL : 0, nl = nw + nx;
+                        if constexpr (!TAP && nx > 0) next_x();
                         steps<NM>([&](auto i_c) __attribute__((always_inline)) {
                             constexpr int i = decltype(i_c)::value;
                             if constexpr (last && i == BAR) {
-                                // the next stage's slab (and on tap 2 its line) has landed; everyone has read this stage
-                                if constexpr (t == 1) wait_vmcnt_upto(nxl); else wait_vmcnt<0>();
+                                // the next stage's slab and rows have landed (what was sent for after them may be on its way, zero
+                                // stores included); everyone has read this stage
+                                constexpr int younger = TAP ? (R - 2) * (WL + XL) : (R == 3 ? WL : 0);
+                                constexpr bool line_younger = !TAP && (R == 3 ? t < 2 : t == 1);
+                                if (line_younger || z1 + z2 > 0)
+                                    wait_vmcnt_upto16(younger + (line_younger ? nxl : 0) + z1 + (R == 3 ? z2 : 0));
+                                else
+                                    wait_vmcnt<younger>();
                                 __syncthreads();
                                 next_w();
+                                if constexpr (TAP) next_x();
                             }
                             acc[i / CB][i % CB] = mfma32<DT>(wf[kk & 1][i % CB], xf[kk & 1][i / CB], acc[i / CB][i % CB]);
                             __builtin_amdgcn_sched_barrier(0);
@@ -395,14 +442,14 @@ void k_conv_wide(Geom g, WideArgs wa, const unsigned char *__restrict__ x, const
                                 steps<((j + 1) * NR + gaps - 1) / gaps - (j * NR + gaps - 1) / gaps>([&](auto e_c) __attribute__((always_inline)) {
                                     constexpr int r = (j * NR + gaps - 1) / gaps + decltype(e_c)::value;
                                     if constexpr (r < NR) {
-                                        if constexpr (last) read_frag(r, 0, t == 2 ? CX ^ 1u : CX, CW ^ 1u, t == 2 ? 0 : t + 1, 0);
+                                        if constexpr (last) read_frag(r, 0, TAP ? (CW + 1u) % R : (t == 2 ? CX ^ 1u : CX), (CW + 1u) % R, (t + 1) % 3, 0);
                                         else read_frag(r, (kk + 1) & 1, CX, CW, t, kk + 1);
                                     }
                                 });
                                 steps<((j + 1) * nl) / gaps - (j * nl) / gaps>([&](auto e_c) __attribute__((always_inline)) {
                                     constexpr int ld = (j * nl) / gaps + decltype(e_c)::value;
                                     if constexpr (ld < nw) issue_w(ld, CW);
-                                    else issue_x(ld - nw, CX ^ 1u);
+                                    else issue_x(ld - nw, TAP ? CW : CX ^ 1u);
                                 });
                                 __builtin_amdgcn_sched_barrier(0);
                             }
@@ -412,17 +459,32 @@ void k_conv_wide(Geom g, WideArgs wa, const unsigned char *__restrict__ x, const
                 };
                 using I0 = std::integral_constant<uint32_t, 0>;
                 using I1 = std::integral_constant<uint32_t, 1>;
+                using I2 = std::integral_constant<uint32_t, 2>;
                 using T0 = std::integral_constant<int, 0>;
                 using T1 = std::integral_constant<int, 1>;
                 using T2 = std::integral_constant<int, 2>;
-                for (int gi = 0; gi < groups; gi += 2) {
-                    stage(I0{}, I0{}, T0{});
-                    stage(I0{}, I1{}, T1{});
-                    stage(I0{}, I0{}, T2{});
-                    if (gi + 1 < groups) {
-                        stage(I1{}, I1{}, T0{});
-                        stage(I1{}, I0{}, T1{});
-                        stage(I1{}, I1{}, T2{});
+                if constexpr (TAP && R == 3) {
+                    for (int gi = 0; gi < groups; ++gi) {
+                        stage(I0{}, I0{}, T0{});
+                        stage(I1{}, I1{}, T1{});
+                        stage(I2{}, I2{}, T2{});
+                    }
+                } else if constexpr (TAP) {
+                    for (int st = 0; st < 3 * groups; st += 2) {
+                        stage(I0{}, I0{}, T0{});
+                        if (st + 1 < 3 * groups) stage(I1{}, I1{}, T1{});
+                    }
+                } else {
+                    constexpr uint32_t A = R == 3 ? 0 : 1; // (two slabs: the second group starts with the other one)
+                    for (int gi = 0; gi < groups; gi += 2) {
+                        stage(I0{}, I0{}, T0{});
+                        stage(I0{}, I1{}, T1{});
+                        stage(I0{}, std::integral_constant<uint32_t, R == 3 ? 2 : 0>{}, T2{});
+                        if (gi + 1 < groups) {
+                            stage(I1{}, std::integral_constant<uint32_t, A>{}, T0{});
+                            stage(I1{}, std::integral_constant<uint32_t, 1 - A>{}, T1{});
+                            stage(I1{}, std::integral_constant<uint32_t, R == 3 ? 2 : 1>{}, T2{});
+                        }
                     }
                 }
 
@@ -481,20 +543,20 @@ void k_conv_wide(Geom g, WideArgs wa, const unsigned char *__restrict__ x, const
                     __asm__ volatile("" ::: "memory");
                 }
             };
-            switch (k) {
-            case 1: run(std::integral_constant<int, 1>{}); break;
-            case 2: run(std::integral_constant<int, 2>{}); break;
-            case 3: run(std::integral_constant<int, 3>{}); break;
-            default: if constexpr (PBX >= 4) run(std::integral_constant<int, 4>{}); break;
-            }
+            auto run_form = [&](auto tap_c) __attribute__((always_inline)) {
+                switch (k) {
+                case 1: run(std::integral_constant<int, 1>{}, tap_c); break;
+                case 2: run(std::integral_constant<int, 2>{}, tap_c); break;
+                case 3: run(std::integral_constant<int, 3>{}, tap_c); break;
+                default: if constexpr (PBX >= 4) run(std::integral_constant<int, 4>{}, tap_c); break;
+                }
+            };
+            if (by_tap) run_form(std::true_type{}); else run_form(std::false_type{});
             g0 += k;
         }
     }
-    if (zero_fill && !clear_in_loop) {
-        __syncthreads();
-        clear_irrelevant(g, mask_in, mask_out, out, cpr, (int)blockIdx.x * kWideWaves + wave, (int)gridDim.x * kWideWaves,
-                         reinterpret_cast<int32_t *>(smem_raw) + wave * 64);
-    }
+    if (zero_fill && !clear_in_loop)
+        clear_irrelevant_runs(g, mask_in, mask_out, out, cpr, wa.cpr, zt0, zx1, slot_x * kWideWaves + wave, per_xcd * kWideWaves);
 }
 
 // ---------------------------------------------------------------------------
@@ -511,13 +573,13 @@ bool conv_wide_supported(const Geom &g, int in_dtype, int out_dtype)
 }
 #endif
 
-template <int DT, typename TO, int WM, int PBX, int SL>
+template <int DT, typename TO, int WM, int PBX, int SL, int SLS>
 static hipError_t launch_wide(const Geom &g, int grid, const void *x, const uint8_t *mask_in, const uint8_t *mask_out, const void *w,
                               const float *bias, const int32_t *idx, const int32_t *count, void *out, hipStream_t s)
 {
     constexpr int TN = (kWideWaves / WM) * 64;
-    auto kern = k_conv_wide<DT, TO, WM, PBX, SL>;
-    constexpr size_t lds = wide_lds_bytes<WM, TN, PBX, SL>();
+    auto kern = k_conv_wide<DT, TO, WM, PBX, SL, SLS>;
+    constexpr size_t lds = wide_lds_bytes<WM, TN, PBX, SL, SLS>();
     static_assert(lds <= 160 * 1024, "LDS of a CU");
     // the dynamic LDS limit is raised once per function and device
     static std::atomic<uint64_t> attr_devices{0};
@@ -543,8 +605,8 @@ static hipError_t launch_wide_shape(const Geom &g, int grid, const void *x, cons
                                     const void *w, const float *bias, const int32_t *idx, const int32_t *count, void *out, hipStream_t s)
 {
     // (8-bit fragments are twice as large: three blocks a wave, or the loop spills)
-    if (g.c_out % 256 == 0) return launch_wide<DT, TO, 2, DT == FC_FP8 ? 3 : 4, DT == FC_FP8 ? 256 : 320>(g, grid, x, mask_in, mask_out, w, bias, idx, count, out, s);
-    return launch_wide<DT, TO, 4, 3, 448>(g, grid, x, mask_in, mask_out, w, bias, idx, count, out, s);
+    if (g.c_out % 256 == 0) return launch_wide<DT, TO, 2, DT == FC_FP8 ? 3 : 4, DT == FC_FP8 ? 256 : 320, 192>(g, grid, x, mask_in, mask_out, w, bias, idx, count, out, s);
+    return launch_wide<DT, TO, 4, 3, 448, 384>(g, grid, x, mask_in, mask_out, w, bias, idx, count, out, s);
 }
 
 // The instances are spread over nine translation units, one per pair of types (-DFC_WIDE_PART=p; without the macro this file

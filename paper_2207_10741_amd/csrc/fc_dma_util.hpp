@@ -96,7 +96,30 @@ __device__ __forceinline__ void wait_vmcnt_upto(int n)
                      : "s"(off)
                      : "vcc", "scc", "memory");
 }
+
+// the same for every count 0 .. 15
+__device__ __forceinline__ void wait_vmcnt_upto16(int n)
+{
+    const uint32_t off = (uint32_t)min(__builtin_amdgcn_readfirstlane(n), 15) * 8u + 12u;
+    __asm__ volatile("s_getpc_b64 vcc\n\t"
+                     "s_add_u32 vcc_lo, vcc_lo, %0\n\t"
+                     "s_addc_u32 vcc_hi, vcc_hi, 0\n\t"
+                     "s_setpc_b64 vcc\n\t"
+                     FC_WJ(0) FC_WJ(1) FC_WJ(2) FC_WJ(3) FC_WJ(4) FC_WJ(5) FC_WJ(6) FC_WJ(7)
+                     FC_WJ(8) FC_WJ(9) FC_WJ(10) FC_WJ(11) FC_WJ(12) FC_WJ(13) FC_WJ(14) FC_WJ(15)
+                     "1:"
+                     :
+                     : "s"(off)
+                     : "vcc", "scc", "memory");
+}
 #undef FC_WJ
+
+// 16 bytes of zeros per lane, past the caches (out of range: nothing)
+__device__ __forceinline__ void store16_zero_nt(const u32x4_t &rsrc, uint32_t byte_offset)
+{
+    const u32x4_t zero4 = {0u, 0u, 0u, 0u};
+    __asm__ volatile("buffer_store_dwordx4 %0, %1, %2, 0 offen nt" : : "v"(zero4), "v"(byte_offset), "s"(rsrc) : "memory");
+}
 
 // Before a load into LDS is issued: every LDS read this wave has issued has returned.  The reads
 // of the area the load overwrites come earlier in program order, but issued is not done: the

@@ -216,6 +216,30 @@ __device__ __forceinline__ void clear_irrelevant(const Geom &g, const uint8_t *_
     }
 }
 
+// The same for positions begin .. end - 1 without a list: the rows of 64 positions are one piece of memory, and a lane clears
+// those of its 16-byte pieces that lie in irrelevant rows (div_pieces: by the pieces of a row).
+__device__ __forceinline__ void clear_irrelevant_runs(const Geom &g, const uint8_t *__restrict__ mask_in, const uint8_t *__restrict__ mask_out,
+                                                      void *__restrict__ out, int pieces, const FastDiv &div_pieces, int64_t begin, int64_t end,
+                                                      int worker, int workers)
+{
+    const int lane = threadIdx.x & 63;
+    const int64_t step = (int64_t)workers * 64;
+    typedef uint32_t u32x4_nt __attribute__((ext_vector_type(4)));
+    const u32x4_nt zero4 = {0u, 0u, 0u, 0u};
+    u32x4_nt *o4 = reinterpret_cast<u32x4_nt *>(out);
+    int64_t p0 = begin + (int64_t)worker * 64;
+    bool kept = p0 + lane >= end || position_kept(g, mask_in, mask_out, p0 + lane);
+    for (; p0 < end; p0 += step) {
+        const uint64_t drop = __ballot(!kept);
+        const int64_t pn = p0 + step + lane;
+        kept = pn >= end || position_kept(g, mask_in, mask_out, pn);
+        if (drop == 0) continue;
+        u32x4_nt *at = o4 + p0 * pieces;
+        for (int c = lane; c < 64 * pieces; c += 64)
+            if ((drop >> fast_div((uint32_t)c, div_pieces)) & 1ull) __builtin_nontemporal_store(zero4, at + c);
+    }
+}
+
 // inclusive prefix sum over the 64 lanes of a wave, on the cross-lane data path of the
 // vector ALU (no LDS traffic): shifts by 1, 2, 4, 8 inside each row of 16 lanes, then the last
 // lane of row 0 / row 2 is broadcast into row 1 / row 3, then lane 31 into rows 2 and 3.
