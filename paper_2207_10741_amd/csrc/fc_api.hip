@@ -188,9 +188,13 @@ ConvWorkspace conv_ws_layout(const Geom &g)
 
 } // namespace
 
-bool fc::conv_taps_bias_last(const Geom &g, bool masked)
+// (sizes of its own, not those of a dispatch rule: a line that moves there must not move last bits here)
+bool fc::conv_res3_bias_last(const Geom &g, bool masked)
 {
-    return (g.flags & FC_RESIDENT_WEIGHTS) || conv_taps_wanted(g, masked);
+    if (g.flags & FC_RESIDENT_WEIGHTS) return true;
+    if (g.c_out > 64) return false;
+    if (!masked) return g.m >= 40000 && g.m < 1500000;
+    return g.m >= (g.flags & (FC_SKIP_ZERO_FILL | FC_COMPACT_OUT) ? 80000 : 500000);
 }
 
 extern "C" {

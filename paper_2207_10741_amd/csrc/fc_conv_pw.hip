@@ -671,7 +671,7 @@ hipError_t launch_conv_pw(const Geom &g, int in_dtype, int out_dtype, const void
                           const int32_t *count, void *out, hipStream_t s)
 {
     if (conv_res3_supported(g))
-        return launch_conv_res3(g, in_dtype, out_dtype, conv_grid_cus(), conv_taps_bias_last(g, mask_in != nullptr), x, mask_in, mask_out, w, bias, idx, count, out, s);
+        return launch_conv_res3(g, in_dtype, out_dtype, conv_grid_cus(), conv_res3_bias_last(g, mask_in != nullptr), x, mask_in, mask_out, w, bias, idx, count, out, s);
 #define FC_PW_CALL(DT, TO) launch_pw_shape<DT, TO>(g, x, mask_in, mask_out, w, bias, idx, count, out, s)
     if (in_dtype == FC_BF16) {
         if (out_dtype == FC_F32) return FC_PW_CALL(FC_BF16, float);

@@ -426,9 +426,9 @@ hipError_t launch_conv_small(const Geom &g, int in_dtype, int out_dtype, bool ro
 // fc_conv_res.hip); grid: one workgroup per CU; bias_last: the bias is added to the finished sum, else the sum starts from it.
 bool conv_res3_supported(const Geom &g);
 // Is the bias of such a layer added last, as on the tap-by-tap form of the resident-weights kernel, or first, as on the
-// tiled kernels?  By the sizes each of them serves, so that a layer's sums do not depend on the kernel: a changed last bit
-// of a few 16-bit values is 1 % of the outputs fifty layers on.
-bool conv_taps_bias_last(const Geom &g, bool masked);
+// tiled kernels?  By the sizes each of them served before this kernel, so that a layer keeps its sums: a changed last bit of a few
+// 16-bit values is 1 % of the outputs fifty layers on.
+bool conv_res3_bias_last(const Geom &g, bool masked);
 hipError_t launch_conv_res3(const Geom &g, int in_dtype, int out_dtype, int grid, bool bias_last, const void *x, const uint8_t *mask_in,
                             const uint8_t *mask_out, const void *w, const float *bias, const int32_t *idx, const int32_t *count,
                             void *out, hipStream_t s);
