@@ -434,11 +434,13 @@ def test_16bit_output_is_rne_of_fp32_output(layer, dtype):
 HALO_LAYERS = [
     # n, h, w, ci, co, k, s, p, d
     (2, 40, 56, 64, 128, 3, 1, 1, 1),               # 128 x 64 tiles
-    (8, 96, 96, 64, 128, 3, 1, 1, 1),               # 128 x 128 tiles (576 of them)
+    (8, 96, 96, 72, 136, 3, 1, 1, 1),               # 128 x 128 tiles (1152 of them), channel tails
+    (8, 96, 96, 64, 128, 3, 1, 1, 1),               # 128-byte pixels: resident weights, two slices
     (1, 36, 64, 64, 64, 3, 1, 1, 1),                # narrow layer, reduction split over workgroups
     (1, 33, 47, 72, 136, 3, (2, 1), (0, 2), (2, 1)),  # vertical stride and dilation, wide padding, channel tails
     (3, 17, 32, 128, 72, 3, (1, 1), (1, 0), (1, 1)),  # no horizontal padding: the output is narrower
-    (128, 16, 16, 64, 256, 3, 1, 1, 1),             # 16-pixel rows, 512 tiles of 128 x 128: short runs on the pixel line
+    (128, 16, 16, 72, 256, 3, 1, 1, 1),             # 16-pixel rows, 512 tiles of 128 x 128: short runs on the pixel line
+    (128, 16, 16, 64, 256, 3, 1, 1, 1),             # the same tiles with a mask; without one resident weights, four slices
     (2, 30, 70, 64, 128, 3, 1, (3, 2), (3, 1)),     # three padded rows and two padded pixels: first taps far outside
 ]
 
@@ -451,7 +453,7 @@ def test_shared_halo_layers_match_oracle(layer, mask_kind):
     assert not out.cpu().numpy()[~keep].view(np.uint32).any()
 
 
-@pytest.mark.parametrize("layer", [HALO_LAYERS[0], HALO_LAYERS[2], HALO_LAYERS[3]])
+@pytest.mark.parametrize("layer", [HALO_LAYERS[0], HALO_LAYERS[3], HALO_LAYERS[4]])
 def test_shared_halo_precomputed_list_and_16bit_output(layer):
     torch = G.torch_mod()
     a, want, keep = _run_layer(*layer, synth.F16, mask_kind="mixed", seed=208)
@@ -468,7 +470,8 @@ def test_shared_halo_precomputed_list_and_16bit_output(layer):
 CHAINED_LINE_LAYERS = [
     # n, h, w, ci, co, k, s, p, d
     (2, 40, 56, 64, 128, 3, 1, 1, 1),               # 4480 positions: a block or two per workgroup
-    (8, 96, 64, 64, 128, 3, 1, 1, 1),               # 49152 positions: several blocks per workgroup
+    (8, 96, 64, 72, 128, 3, 1, 1, 1),               # 49152 positions: several blocks per workgroup
+    (8, 96, 64, 64, 128, 3, 1, 1, 1),               # the same on 128-byte pixels: the resident-weights kernel
     (16, 64, 64, 128, 128, 3, 1, 1, 1),             # the bench shape: two channel chunks, eight blocks when dense
     (3, 47, 61, 72, 96, 3, 1, 1, 1),                # channel tails on both sides, ragged rows
     (2, 61, 47, 64, 128, 3, (2, 1), (0, 2), (2, 1)),  # vertical stride and dilation, wide padding

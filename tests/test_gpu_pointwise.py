@@ -472,8 +472,8 @@ def test_3x3_layer_sent_to_the_resident_weights_kernel_by_the_size_rule_matches_
                                          (40, "one"), (31, "bernoulli")])
 @pytest.mark.parametrize("out_dtype", [synth.BF16, synth.FP8])
 def test_units_whose_pixel_line_is_short_of_slots(w, mask_kind, out_dtype):
-    """Where a unit of the resident-weights 3x3 kernel ends: rows of a few pixels, isolated positions (three slots
-    each: thirteen rows a unit), every other column, a single kept position, lists in tile order."""
+    """Units of the resident-weights 3x3 kernel with few slots to spare or too few (three slots an isolated position: such units of 32 rows
+    go tap by tap): rows of a few pixels, isolated positions, every other column, a single kept position, lists in tile order."""
     torch = G.torch_mod()
     n, h, ci, co = 2, 4800 // w, 64, 64
     dtype = synth.BF16
