@@ -141,21 +141,22 @@ bool conv_pw_wanted(const Geom &g, int in_dtype, int out_dtype, bool masked)
 }
 
 // Does the kernel of wide tiles serve this 3x3 layer?  Without a mask from 600 granules of its tiles on (64 rows x 256 channels or
-// 128 x 128, counted over all positions).  The kept share is known on the device only, and a tile's set-up and the last round weigh more the
-// fewer stages a tile has, so with a mask the line lies where no kept share loses much: 1 000 granules of 72 stages or more (a stage
-// is a tap and 128 bytes of its channels), 1 600 of 36 (256 16-bit channels), 4 000 of fewer (chained: 1 600) and with 128-channel tiles.
+// 128 x 128, counted over all positions).  The kept share is known on the device only, and a tile's set-up, the last round and the rows to clear
+// weigh more the fewer stages a tile has (a stage is a tap and 128 bytes of its channels), so with a mask the line lies where the shares
+// from 0.3 to 0.9 gain on the whole: from 1 000 granules on, zero-filled 4 000 with 128-channel tiles and 3 000 with fewer than 36 stages.
 // us, tiled -> here, masks of regions, list given, at a kept share of 0.1 / 0.3 / 0.5 / 0.7 / 0.9, zero-filled and chained:
 // 512 -> 512 on 128 x 16 x 16 (1 024 granules, 72 stages): 47 / 67 / 107 / 117 / 141 -> 49 / 67 / 87 / 101 / 123, 46 / 63 / 105 / 111 / 131 -> 43 / 59 / 84 /
-// 93 / 112; 256 -> 256 on 128 x 32 x 32 (2 048, 36): 30 / 62 / 94 / 116 / 144 -> 33 / 53 / 90 / 109 / 129, 25 / 58 / 90 / 109 / 139 -> 26 / 48 / 83 / 98 / 120;
-// 128 -> 128 on 128 x 64 x 64 (4 096, 18): 38 / 66 / 103 / 132 / 155 -> 33 / 63 / 93 / 119 / 150, 22 / 52 / 86 / 113 / 143 -> 22 / 51 / 81 / 106 / 135; E4M3
-// 256 -> 256 on 32 x 60 x 80 (2 400, 18): zero-filled (not taken) 20 / 36 / 53 / 70 / 88 -> 25 / 35 / 53 / 73 / 82, chained 16 / 33 / 50 / 68 / 87 -> 17 / 29 / 46 /
-// 65 / 75; 128 -> 256 on 8 x 135 x 240 (4 050, 18): 36 / 65 / 96 / 128 / 155 -> 32 / 64 / 88 / 115 / 146, on 16 x 70 x 100 (1 750) zero-filled (not taken) 19 / 36 /
-// 44 / 56 / 72 -> 22 / 32 / 41 / 60 / 69, chained 15 / 33 / 42 / 55 / 72 -> 17 / 29 / 36 / 53 / 64.
-// Below the lines: 256 -> 256 on 16 x 60 x 80 (1 200, 36): 25 / 35 / 58 / 71 / 90 -> 29 / 39 / 51 / 65 / 89; 128 -> 128 on 32 x 60 x 80 (1 200, 18): 16 / 22 /
-// 33 / 41 / 52 -> 19 / 25 / 32 / 46 / 54, on 32 x 94 x 95 (2 231): 21 / 37 / 55 / 74 / 87 -> 23 / 36 / 56 / 78 / 88; without a mask 256 -> 256 on 32 x 30 x 40 (600) 53
-// -> 44, on 16 x 32 x 32 (256) 24 -> 28.  Masks without regions (positions dropped one by one at random, same shares, zero-filled):
-// 512 channels 47 / 55 / 112 / 122 / 144 -> 49 / 64 / 87 / 98 / 122, 256 31 / 62 / 79 / 111 / 145 -> 31 / 51 / 71 / 104 / 130, 128 35 / 61 / 102 / 130 / 149 -> 34 / 63 /
-// 93 / 129 / 165.
+// 93 / 112; 256 -> 256 on 16 x 60 x 80 (1 200, 36): 25 / 35 / 58 / 71 / 90 -> 29 / 39 / 51 / 65 / 89, 22 / 34 / 57 / 69 / 89 -> 25 / 35 / 48 / 60 / 84, on 128 x 32 x 32
+// (2 048): 30 / 62 / 94 / 116 / 144 -> 33 / 53 / 90 / 109 / 129, 25 / 58 / 90 / 109 / 139 -> 26 / 48 / 83 / 98 / 120; 128 -> 256 on 8 x 135 x 240 (4 050, 18): 36 / 65 / 96 /
+// 128 / 155 -> 32 / 64 / 88 / 115 / 146, 21 / 55 / 84 / 119 / 148 -> 23 / 53 / 75 / 105 / 135; 128 -> 128 on 128 x 64 x 64 (4 096, 18): 38 / 66 / 103 / 132 / 155 -> 33 / 63 / 93 /
+// 119 / 150, 22 / 52 / 86 / 113 / 143 -> 22 / 51 / 81 / 106 / 135.
+// Zero-filled below the lines: 128 -> 256 on 16 x 70 x 100 (1 750) 19 / 36 / 44 / 56 / 72 -> 22 / 32 / 41 / 60 / 69; E4M3 256 -> 256 on 32 x 60 x 80 (2 400, 18) 20 / 36 / 53 /
+// 70 / 88 -> 25 / 35 / 53 / 73 / 82; 64 -> 512 on 16 x 60 x 80 (2 400, 9) 22 / 29 / 39 / 52 / 62 -> 22 / 29 / 46 / 53 / 68; 128 -> 128 on 32 x 60 x 80 (1 200, 18) 16 / 22 / 33 / 41 / 52 ->
+// 19 / 25 / 32 / 46 / 54, on 32 x 94 x 95 (2 231) 21 / 37 / 55 / 74 / 87 -> 23 / 36 / 56 / 78 / 88.  Chained, the same five: 15 / 33 / 42 / 55 / 72 -> 17 / 29 / 36 / 53 / 64, 16 / 33 / 50 / 68 /
+// 87 -> 17 / 29 / 46 / 65 / 75, 11 / 23 / 35 / 48 / 60 -> 14 / 22 / 34 / 42 / 51, 15 / 20 / 31 / 39 / 50 -> 15 / 21 / 27 / 40 / 48, 15 / 33 / 53 / 71 / 85 -> 17 / 30 / 51 / 71 / 81.
+// Without a mask 256 -> 256 on 32 x 30 x 40 (600) 53 -> 44, on 16 x 32 x 32 (256) 24 -> 28.  Masks without regions (positions dropped one by one at
+// random, same shares, zero-filled): 512 channels 47 / 55 / 112 / 122 / 144 -> 49 / 64 / 87 / 98 / 122, 256 on 128 x 32 x 32 31 / 62 / 79 / 111 / 145 -> 31 / 51 / 71 / 104 / 130, on
+// 16 x 60 x 80 26 / 33 / 62 / 72 / 91 -> 30 / 38 / 51 / 64 / 82, 128 35 / 61 / 102 / 130 / 149 -> 34 / 63 / 93 / 129 / 165.
 // Other channel counts stay: 384 channels are three tiles of 128, each of which reads the rows again (256 -> 384 on 16 x 60 x 80
 // zero-filled 76 -> 102).
 bool conv_wide_wanted(const Geom &g, int in_dtype, int out_dtype, bool masked)
@@ -164,8 +165,8 @@ bool conv_wide_wanted(const Geom &g, int in_dtype, int out_dtype, bool masked)
     if (g.c_out != 128 && g.c_out % 256 != 0) return false;
     const int64_t granules = (int64_t)g.m * g.c_out / (64 * 256), stages = 9 * ((int64_t)g.c_in * (in_dtype == FC_FP8 ? 1 : 2) / 128);
     if (!masked) return granules >= 600;
-    if (g.c_out == 128) return granules >= 4000;
-    return granules >= (stages >= 72 ? 1000 : (stages >= 36 || (g.flags & FC_SKIP_ZERO_FILL) ? 1600 : 4000));
+    if (g.flags & FC_SKIP_ZERO_FILL) return granules >= 1000;
+    return granules >= (g.c_out == 128 ? 4000 : (stages >= 36 ? 1000 : 3000));
 }
 
 size_t compact_ws(int64_t m) { return align_up((size_t)compact_blocks(m) * sizeof(int32_t), 256); }

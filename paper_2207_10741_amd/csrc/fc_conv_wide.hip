@@ -136,10 +136,15 @@ void k_conv_wide(Geom g, WideArgs wa, const unsigned char *__restrict__ x, const
     // tiles do; a granule comes with zq positions, or where those are too many (masks that keep little) its share is cleared
     // at the end ----
     const int cpr = g.c_out * (int)sizeof(TO) / 16;
-    const int zx0 = (int)(((int64_t)g.m * xcd) >> 3), zx1 = (int)(((int64_t)g.m * (xcd + 1)) >> 3);
-    const int z_apart = n_x > 0 ? (int)((int64_t)(zx1 - zx0) * (2 * clearers) / (2 * clearers + takers)) : zx1 - zx0;
-    const int zt0 = zx0 + z_apart, zq = n_x > 0 ? (zx1 - zt0 + n_x - 1) / n_x : 0;
-    const bool clear_in_loop = zero_fill && n_x > 0 && (int64_t)zq * ((qm + rounds - 1) / max(rounds, 1)) <= kWideWords * NT;
+    int zx0 = 0, zx1 = 0, zt0 = 0, zq = 0;
+    bool clear_in_loop = false;
+    if (zero_fill) {
+        zx0 = (int)(((int64_t)g.m * xcd) >> 3);
+        zx1 = (int)(((int64_t)g.m * (xcd + 1)) >> 3);
+        zt0 = n_x > 0 ? zx0 + (zx1 - zx0) / (2 * clearers + takers) * (2 * clearers) : zx1;
+        zq = n_x > 0 ? (zx1 - zt0 + n_x - 1) / n_x : 0;
+        clear_in_loop = n_x > 0 && (int64_t)zq * ((qm + rounds - 1) / max(rounds, 1)) <= kWideWords * NT;
+    }
     if (zero_fill && slot_x >= takers)
         clear_irrelevant_runs(g, mask_in, mask_out, out, cpr, wa.cpr, zx0, zt0, (slot_x - takers) * kWideWaves + wave, clearers * kWideWaves);
 
@@ -301,6 +306,8 @@ void k_conv_wide(Geom g, WideArgs wa, const unsigned char *__restrict__ x, const
                 constexpr uint32_t XB = (TAP ? PB * GR : (R == 3 ? SLS : SL)) * 128u;  // a buffer of theirs
                 constexpr int NG = TAP ? 9 : 3, PW = TAP ? 3 : 10;                     // gates per slot (row) this lane gathers; of them a word holds
                 static_assert((TAP ? R : 2) * XB + (R - 2) * WB <= W0, "buffers of rows and the third slab");
+                // (a short line is sent for whole, whatever it holds: the waits then know its loads)
+                constexpr bool WHOLE = TAP || XL <= 3;
                 uint32_t hxoff[XL];
                 uint32_t hxbits[2] = {0, 0};
                 static_assert(XL <= 2 * PW, "two words");
@@ -347,7 +354,7 @@ void k_conv_wide(Geom g, WideArgs wa, const unsigned char *__restrict__ x, const
                     xkh += wrap;
                 };
                 auto issue_x = [&](int j, uint32_t buf) __attribute__((always_inline)) {
-                    if (TAP || j < nxl)
+                    if (WHOLE || j < nxl)
                         dma_load16_s(rsrc_x, (hxbits[j / PW] & (ld_sel << (NG * (j % PW)))) ? hxoff[j] : kOutOfRange, ld_sx, lds_wave + buf * XB + (uint32_t)j * (RPL * 128u));
                 };
                 // Zero stores of a stage: wave v clears the positions of its own label words, in whole 64-piece runs.  A run is one store
@@ -371,18 +378,18 @@ void k_conv_wide(Geom g, WideArgs wa, const unsigned char *__restrict__ x, const
                     }
                 };
 
-                if constexpr (R == 3) {
-                    next_w();
-#pragma unroll
-                    for (int j = 0; j < WL; ++j) issue_w(j, 2);
-                }
 #pragma unroll
                 for (int d = 0; d < (TAP ? R : 1); ++d) {
                     next_x();
 #pragma unroll
                     for (int j = 0; j < XL; ++j) issue_x(j, (uint32_t)d);
                 }
-                wait_vmcnt<0>();
+                if constexpr (R == 3) { // (nobody needs it before the second barrier)
+                    next_w();
+#pragma unroll
+                    for (int j = 0; j < WL; ++j) issue_w(j, 2);
+                }
+                wait_vmcnt<(R - 2) * WL>();
                 __syncthreads();
 
                 Frag<DT> wf[2][CB], xf[2][PB];
@@ -425,10 +432,10 @@ void k_conv_wide(Geom g, WideArgs wa, const unsigned char *__restrict__ x, const
                             if constexpr (last && i == BAR) {
                                 // the next stage's slab and rows have landed (what was sent for after them may be on its way, zero
                                 // stores included); everyone has read this stage
-                                constexpr int younger = TAP ? (R - 2) * (WL + XL) : (R == 3 ? WL : 0);
-                                constexpr bool line_younger = !TAP && (R == 3 ? t < 2 : t == 1);
-                                if (line_younger || z1 + z2 > 0)
-                                    wait_vmcnt_upto16(younger + (line_younger ? nxl : 0) + z1 + (R == 3 ? z2 : 0));
+                                constexpr bool line = !TAP && (R == 3 ? t < 2 : t == 1), counted = line && !WHOLE;
+                                constexpr int younger = TAP ? (R - 2) * (WL + XL) : (R == 3 ? WL : 0) + (line && WHOLE ? XL : 0);
+                                if (counted || z1 + z2 > 0)
+                                    wait_vmcnt_upto16(younger + (counted ? nxl : 0) + z1 + (R == 3 ? z2 : 0));
                                 else
                                     wait_vmcnt<younger>();
                                 __syncthreads();

@@ -12,11 +12,11 @@ from tests import gpu_util as G
 pytestmark = pytest.mark.gpu
 
 LAYERS = [
-    # n, h, w, ci, co, dtype, sh, (ph, pw), dh; granules of a tile: 64 rows x 256 channels, 128 x 128.  With a mask the kernel serves 1 000 of 72
-    # stages (a stage: a tap and 128 bytes of channels), 1 600 of 36, 4 000 of fewer and with 128-channel tiles.
+    # n, h, w, ci, co, dtype, sh, (ph, pw), dh; granules of a tile: 64 rows x 256 channels, 128 x 128.  With a mask the kernel serves 1 000 of
+    # them; zero-filled 3 000 of fewer than 36 stages (a stage: a tap and 128 bytes of channels) and 4 000 with 128-channel tiles.
     (13, 130, 161, 128, 256, synth.BF16, 1, (1, 1), 1),     # 256-channel tiles: 4 251 granules of 18 stages
     (31, 131, 127, 128, 128, synth.F16, 1, (1, 1), 1),      # 128-channel tiles: 4 029
-    (1, 1000, 130, 128, 512, synth.BF16, 1, (1, 1), 1),      # two channel tiles
+    (1, 1000, 130, 128, 512, synth.BF16, 1, (1, 1), 1),     # two channel tiles
     (184, 17, 33, 256, 256, synth.BF16, 1, (1, 1), 1),      # short image rows
     (10, 201, 99, 256, 256, synth.BF16, 2, (3, 2), 2),      # vertical stride and dilation, wide padding
     (1, 360, 361, 64, 512, synth.BF16, 1, (1, 1), 1),       # one chunk of channels: three groups of stages
