@@ -155,8 +155,8 @@ bool conv_pw_wanted(const Geom &g, int in_dtype, int out_dtype, bool masked)
 // 19 / 25 / 32 / 46 / 54, on 32 x 94 x 95 (2 231) 21 / 37 / 55 / 74 / 87 -> 23 / 36 / 56 / 78 / 88.  Chained, the same five: 15 / 33 / 42 / 55 / 72 -> 17 / 29 / 36 / 53 / 64, 16 / 33 / 50 / 68 /
 // 87 -> 17 / 29 / 46 / 65 / 75, 11 / 23 / 35 / 48 / 60 -> 14 / 22 / 34 / 42 / 51, 15 / 20 / 31 / 39 / 50 -> 15 / 21 / 27 / 40 / 48, 15 / 33 / 53 / 71 / 85 -> 17 / 30 / 51 / 71 / 81.
 // Without a mask 256 -> 256 on 32 x 30 x 40 (600) 53 -> 44, on 16 x 32 x 32 (256) 24 -> 28.  Masks without regions (positions dropped one by one at
-// random, same shares, zero-filled): 512 channels 47 / 55 / 112 / 122 / 144 -> 49 / 64 / 87 / 98 / 122, 256 on 128 x 32 x 32 31 / 62 / 79 / 111 / 145 -> 31 / 51 / 71 / 104 / 130, on
-// 16 x 60 x 80 26 / 33 / 62 / 72 / 91 -> 30 / 38 / 51 / 64 / 82, 128 35 / 61 / 102 / 130 / 149 -> 34 / 63 / 93 / 129 / 165.
+// random, same shares, zero-filled): 512 channels 47 / 55 / 112 / 122 / 144 -> 47 / 65 / 87 / 98 / 120, 256 on 128 x 32 x 32 31 / 62 / 79 / 111 / 145 -> 31 / 52 / 69 / 96 / 117, on
+// 16 x 60 x 80 26 / 33 / 62 / 72 / 91 -> 29 / 38 / 50 / 62 / 80, 128 35 / 61 / 102 / 130 / 149 -> 36 / 63 / 93 / 123 / 146.
 // Other channel counts stay: 384 channels are three tiles of 128, each of which reads the rows again (256 -> 384 on 16 x 60 x 80
 // zero-filled 76 -> 102).
 bool conv_wide_wanted(const Geom &g, int in_dtype, int out_dtype, bool masked)

@@ -202,7 +202,9 @@ void k_conv_wide(Geom g, WideArgs wa, const unsigned char *__restrict__ x, const
             const int sih = (sq - sb * g.ho) * g.sh - g.ph;
             const bool ladj = live && prev == sp - 1 && sow > 0;
             const bool radj = live && next == sp + 1 && sow < g.wo - 1;
-            const int lead = live && !ladj, cnt = tid < k * GR ? 1 + lead + (live && !radj) : 0;
+            // (the pixel between two kept positions with one dropped between them has one slot, the right of the one and the left of the
+            // other: 0.9 kept at random, 128 -> 128 on 128 x 64 x 64 155 -> 146 us, 256 -> 256 on 128 x 32 x 32 126 -> 117)
+            const int lead = live && !ladj && !(prev == sp - 2 && sow > 1), cnt = tid < k * GR ? 1 + lead + (live && !radj) : 0;
             const int incl = wave_inclusive_scan(cnt);
             if (lane == 63) scan_part[wave] = incl;
             if (tid < TM) row_p[tid] = sp;
