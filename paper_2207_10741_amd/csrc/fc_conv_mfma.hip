@@ -98,7 +98,7 @@ __global__ __launch_bounds__(WM *WN * 64, MINW) void k_conv_dma(Geom g, const ui
 {
     constexpr bool LIST = false;
     constexpr int list_rows = 0;
-#include "fc_conv_dma_body.inc"
+#include "fc_conv_dma_body.hpp"
 }
 
 // The tap-by-tap loop over the tiles of a list of list_rows rows.
@@ -112,7 +112,7 @@ __device__ __forceinline__ void conv_list_tiles(const Geom &g, const uint16_t *_
     constexpr bool OWN = false, LIST = true;
     float *const partials = nullptr;
     int32_t *const tile_counters = nullptr;
-#include "fc_conv_dma_body.inc"
+#include "fc_conv_dma_body.hpp"
 }
 
 // Long reductions, tap by tap, of about a tile per CU: one workgroup per CU with two or three stages on their way (two workgroups with one
