@@ -634,7 +634,7 @@ def test_counters_with_garbage_are_cleared_where_a_reduction_is_split(layer, mas
     ((32, 15, 25, 768, 512, 1, 1, 0, 1), synth.BF16), ((7, 62, 83, 208, 512, 3, 2, 1, 1), synth.FP8)])
 @pytest.mark.parametrize("irr", [0.48, 0.02, 0.8])
 def test_long_reductions_of_a_tile_per_cu(layer, dtype, irr):
-    """Against the oracle on sampled positions; zero rows to the byte, kept rows all written; rows in list order the same bits.  Nearly all
+    """Against the oracle on sampled positions; zero rows to the byte, kept rows all written; rows in list order (out, and for 1x1 in) the same bits.  Nearly all
     rows kept: more 128 x 128 tiles than CUs (1x1: tiles of 192 rows); few kept: at most one 128 x 64 tile per CU (3x3)."""
     torch = G.torch_mod()
     n, h, w, ci, co, k, s, p, d = layer
@@ -657,6 +657,14 @@ def test_long_reductions_of_a_tile_per_cu(layer, dtype, irr):
     rows = B.focused_conv2d(desc, G.to_dev(x, dtype), G.to_dev(wt, dtype), torch.from_numpy(bias).to(G.dev()), mask_in=md, mask_out=m_out,
                             idx=idx, count=count)
     assert torch.equal(rows.reshape(-1, co)[:int(count)], out[kd])
+    if k == 1:                                               # and from rows in list order
+        xd = G.to_dev(x, dtype)
+        xc = torch.zeros_like(xd).view(torch.uint8).reshape(-1, ci * xd.element_size())
+        xc[:int(count)] = xd.view(torch.uint8).reshape(-1, ci * xd.element_size())[idx[:int(count)].long()]
+        desc = B.conv_desc(n, h, w, ci, co, *geo, dtype, B.F32, B.RELU | B.COMPACT_OUT | B.COMPACT_IN)
+        again = B.focused_conv2d(desc, xc.reshape(-1).view(xd.dtype).reshape(xd.shape), G.to_dev(wt, dtype), torch.from_numpy(bias).to(G.dev()),
+                                 mask_in=md, mask_out=m_out, idx=idx, count=count)
+        assert torch.equal(again.reshape(-1, co)[:int(count)], out[kd])
     pos = np.sort(np.random.default_rng(254).choice(np.flatnonzero(keep.reshape(-1)), size=400, replace=False))
     shape = O.ConvShape(n, h, w, ci, co, k, k, (s, s), (p, p), (d, d), relu=True)
     want = O.focused_conv2d_at(shape, x, wt, pos, bias=bias, mask_in=mask, dtype=dtype)
