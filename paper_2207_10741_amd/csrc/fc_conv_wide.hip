@@ -14,8 +14,9 @@
 // Nothing stands in the way of the products: fragments are read a k-step ahead, across the stage boundary as well (the barrier
 // stands inside the last k-step of a stage, whose remaining products cover the first reads of the next one), every read and
 // load goes out between two products (in bursts between the k-steps: 1 126 us with four waves, 964 so), a stage's slab is
-// sent for a stage ahead, a line two.  A stage of one or two granules lasts less than a round trip, so tiles of at most two, whose
-// lines are short, keep a third slab in the room behind them and send for slabs two stages ahead.
+// sent for a stage ahead, a line two.  A stage of one or two granules lasts less than a round trip, so 256-channel tiles of at most
+// two, whose lines are short, keep a third slab in the room behind them and send for slabs two stages ahead (512 -> 512 on 128 x 16 x 16, chained,
+// 0.1 / 0.2 kept 49 / 57 -> 43 / 46 us; 128-channel tiles, whose slabs are half as large, +1 %).
 //
 // Tiles are made of granules of WM * 32 rows; XCD j takes the j-th eighth of the granules and deals them to its workgroups side by
 // side, every workgroup the same number but for one, in as few rounds as tiles of PBX granules allow and all rounds alike: 4.7 granules
@@ -38,13 +39,14 @@ namespace fc {
 constexpr int kWideWaves = 8, kWideThreads = kWideWaves * 64;
 constexpr int kWideWords = 3; // positions a tile clears: up to 64 * 3 per wave
 
-// Tiles of at most two granules have three slabs instead of two: the third lies behind their lines, which are at most SLS
-// slots long (or three buffers of rows).
+// SLS > 0: tiles of at most two granules have three slabs instead of two.  The third lies behind their lines, which are at most
+// SLS slots long (or three buffers of rows).
 template <int WM, int TN, int SL, int SLS>
 constexpr uint32_t wide_x_bytes()
 {
     constexpr uint32_t two = 2u * SL * 128u, line3 = 2u * SLS * 128u + TN * 128u, rows3 = 3u * 2u * WM * 32u * 128u + TN * 128u;
-    return two > line3 ? (two > rows3 ? two : rows3) : (line3 > rows3 ? line3 : rows3);
+    constexpr uint32_t three = line3 > rows3 ? line3 : rows3;
+    return SLS > 0 && three > two ? three : two;
 }
 
 template <int WM, int TN, int PBX, int SL, int SLS>
@@ -85,7 +87,7 @@ void k_conv_wide(Geom g, WideArgs wa, const unsigned char *__restrict__ x, const
     constexpr int SIT = (SL + NT - 1) / NT;
     constexpr uint32_t WB = (uint32_t)TN * 128u, HALF = KSTEP / 32u;
     constexpr uint32_t W0 = wide_x_bytes<WM, TN, SL, SLS>(); // slabs 0 and 1 lie from here on, slab 2 right below
-    static_assert(SL % RPL == 0 && SLS % RPL == 0 && SL >= TM && SLS >= 2 * GR && TM <= NT, "whole wave loads; rows fit where lines do; one row a thread");
+    static_assert(SL % RPL == 0 && SLS % RPL == 0 && SL >= TM && (SLS == 0 || SLS >= 2 * GR) && TM <= NT, "whole wave loads; rows fit where lines do; one row a thread");
 
     extern __shared__ __align__(16) unsigned char smem_raw[];
     const uint32_t lds0 = (uint32_t)reinterpret_cast<uintptr_t>(smem_raw);
@@ -234,7 +236,7 @@ void k_conv_wide(Geom g, WideArgs wa, const unsigned char *__restrict__ x, const
             }
             ns = __builtin_amdgcn_readfirstlane(ns);
             // A line that does not fit (a fragmented mask): the rows are gathered tap by tap, into the same buffers.
-            const bool by_tap = ns > (k <= 2 ? SLS : SL);
+            const bool by_tap = ns > (SLS > 0 && k <= 2 ? SLS : SL);
             const int iwc = sow - g.pw + 1;
             const int pixc = (sb * g.h + sih) * g.w + iwc;
             if (by_tap) {
@@ -303,7 +305,7 @@ void k_conv_wide(Geom g, WideArgs wa, const unsigned char *__restrict__ x, const
             auto run = [&](auto pb_c, auto tap_c) __attribute__((always_inline)) {
                 constexpr int PB = decltype(pb_c)::value;
                 constexpr bool TAP = decltype(tap_c)::value;
-                constexpr int R = PB <= 2 ? 3 : 2;                                     // slabs, and buffers of rows
+                constexpr int R = SLS > 0 && PB <= 2 ? 3 : 2;                          // slabs, and buffers of rows
                 constexpr int XL = TAP ? PB * GR / RPL : (R == 3 ? SLS : SL) / RPL;    // wave loads per wave: rows, a line
                 constexpr uint32_t XB = (TAP ? PB * GR : (R == 3 ? SLS : SL)) * 128u;  // a buffer of theirs
                 constexpr int NG = TAP ? 9 : 3, PW = TAP ? 3 : 10;                     // gates per slot (row) this lane gathers; of them a word holds
@@ -615,7 +617,7 @@ static hipError_t launch_wide_shape(const Geom &g, int grid, const void *x, cons
 {
     // (8-bit fragments are twice as large: three blocks a wave, or the loop spills)
     if (g.c_out % 256 == 0) return launch_wide<DT, TO, 2, DT == FC_FP8 ? 3 : 4, DT == FC_FP8 ? 256 : 320, 192>(g, grid, x, mask_in, mask_out, w, bias, idx, count, out, s);
-    return launch_wide<DT, TO, 4, 3, 448, 384>(g, grid, x, mask_in, mask_out, w, bias, idx, count, out, s);
+    return launch_wide<DT, TO, 4, 3, 448, 0>(g, grid, x, mask_in, mask_out, w, bias, idx, count, out, s);
 }
 
 // The instances are spread over nine translation units, one per pair of types (-DFC_WIDE_PART=p; without the macro this file
