@@ -82,8 +82,8 @@ bool conv_line_wanted(const Geom &g, int in_dtype, int out_dtype, bool focused)
 }
 
 // 3x3 layers of 128-byte pixels (64 channels of a 16-bit type, 128 of the 8-bit one): the first stage of ResNets, VGG's
-// conv1_2 and conv2_1.  With a unit horizontal step they run on k_conv_res3 (fc_conv_res.hip) from 12 000 positions on without a mask, with one
-// from 80 000 on, into more than 64 channels from 40 000.  Measured against the tiled kernels, us, tiled -> here:
+// conv1_2 and conv2_1.  With a unit horizontal step they run on k_conv_res3 (fc_conv_res.hip) from 12 000 positions on, into at most 256
+// channels.  Against the tiled kernels, us, tiled -> here:
 // Without a mask 64 -> 64 on 32 x 20 x 20 8.4 -> 7.7, 32 x 28 x 28 8.7 -> 7.9, 32 x 56 x 56 13.6 -> 13.5, 8 x 540 x 960 470 -> 388; 64 -> 128 on 32 x 28 x 28
 // 11.2 -> 8.5, 16 x 120 x 160 61 -> 58; E4M3 128 -> 64 on 32 x 28 x 28 8.9 -> 8.0; 8 x 28 x 28 8.1 -> 9.0: below 12 000 positions the weights (72 KB a workgroup)
 // are too much to fetch for the rows.
@@ -91,8 +91,12 @@ bool conv_line_wanted(const Geom &g, int in_dtype, int out_dtype, bool focused)
 // 9.3 / 9.8 / 14.8 -> 8.9 / 8.9 / 13.6, on 16 x 128 x 128 14.5 / 22.5 / 28.0 -> 14.8 / 17.8 / 22.1, 15.1 / 21.0 / 22.5 -> 13.8 / 17.0 / 20.6; 64 -> 128 on 32 x 56 x 56 12.3 /
 // 15.6 / 22.2 -> 10.4 / 15.7 / 20.6, 11.3 / 14.0 / 20.9 -> 9.6 / 14.6 / 19.3, on 16 x 120 x 160 30 / 41 / 53 -> 23 / 34 / 45, 22 / 32 / 46 -> 21 / 31 / 43; 64 -> 256 on 16 x 60 x 60
 // 14.1 / 17.6 / 22.2 -> 14.1 / 15.8 / 20.0, 13.4 / 14.1 / 21.0 -> 12.9 / 14.9 / 19.6, on 16 x 120 x 160 61 / 81 / 101 -> 41 / 63 / 87.
-// Below the masked lines: 64 -> 64 on 32 x 28 x 28 9.1 / 9.2 / 9.3 -> 9.9 / 9.7 / 9.6, 8.9 / 9.0 / 9.1 -> 9.7 / 9.6 / 9.5, on 32 x 40 x 40 9.5 / 8.6 / 10.4 -> 9.9 / 9.8 / 8.7; 64 ->
-// 128 on 32 x 28 x 28 9.4 / 9.6 / 11.8 -> 10.2 / 10.1 / 10.1; E4M3 128 -> 64 on 32 x 28 x 28 9.2 / 9.3 / 9.5 -> 9.7 / 9.6 / 9.5.
+// Masked layers of 12 000 .. 80 000 positions are a draw that the other layers around them decide.  Called again and again by themselves the tiled kernel is
+// ahead: 64 -> 64 on 32 x 28 x 28 9.1 / 9.2 / 9.3 -> 9.9 / 9.7 / 9.6, 8.9 / 9.0 / 9.1 -> 9.7 / 9.6 / 9.5, on 32 x 40 x 40 9.5 / 8.6 / 10.4 -> 9.9 / 9.8 / 8.7, 64 -> 128 on 32 x 28 x 28
+// 9.4 / 9.6 / 11.8 -> 10.2 / 10.1 / 10.1, E4M3 128 -> 64 there 9.2 / 9.3 / 9.5 -> 9.7 / 9.6 / 9.5.  Inside a network, after other kernels, this one is (64 -> 64 of a ResNet-18
+// on five images, 0.33 kept, 9.4 -> 9.0): whole passes with the masked line at 80 000, into more than 64 channels at 40 000, -> at 12 000: ResNet-18 on three, five and
+// eight images 195.7 / 220.1 / 265.3 -> 193.5 / 217.2 / 262.0, ResNet-50 on four of 80 x 90, zero-filled and chained, 621 -> 617, 531 -> 529, VGG-16 on 246 x 437
+// 218.1 -> 218.8, 217.8 -> 214.9.
 // Where the 32-row blocks come to one and a half per wave (two slices at 100 000 positions, half kept) the tiled kernel is up to 7 %
 // faster on inputs already in the caches, and neither on others.
 // The shape of the mask is known on the device only: where positions are dropped one by one at random (no regions) the pixel line breaks at
@@ -113,8 +117,7 @@ static bool conv_taps_wanted(const Geom &g, bool masked)
 
 static bool conv_pw_wanted_3x3(const Geom &g, bool masked)
 {
-    if (!conv_res3_supported(g)) return conv_taps_wanted(g, masked);
-    return g.c_out <= 256 && g.m >= (!masked ? 12000 : (g.c_out <= 64 ? 80000 : 40000));
+    return conv_res3_supported(g) ? g.m >= 12000 && g.c_out <= 256 : conv_taps_wanted(g, masked);
 }
 
 // Does the resident-weights kernel serve this layer?  1x1 layers without padding whose rows are whole

@@ -91,8 +91,8 @@ LAYERS = [
     # n, h, w, ci, co, k, s, p, d
     (2, 40, 56, 64, 128, 3, 1, 1, 1),       # tiled matrix-core kernel, shared pixel lines (4480 positions)
     (1, 19, 23, 64, 128, 3, 2, 1, 1),       # small layer: ranks its rows inside the kernel
-    (6, 64, 64, 64, 128, 3, 1, 1, 1),       # 128 x 64 tiles (24576 positions)
-    (6, 90, 80, 64, 128, 3, 1, 1, 1),       # resident weights (43200 positions)
+    (6, 64, 64, 64, 128, 3, 1, 1, 1),       # resident weights (24576 positions)
+    (6, 64, 64, 72, 128, 3, 1, 1, 1),       # 128 x 64 tiles (24576 positions)
     (2, 20, 24, 64, 256, 1, 1, 0, 1),       # 1x1
     (1, 17, 13, 24, 40, 3, 1, 1, 1),        # channel tails
     (1, 12, 12, 5, 7, 3, 1, 1, 1),          # direct kernel

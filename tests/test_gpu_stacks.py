@@ -116,7 +116,8 @@ def test_resnet50_layers_full_batch_sampled(layer):
     (8, 96, 96, 72, 136, 3, 1, 1),      # many 128 x 128 tiles, shared pixel line
     (8, 96, 96, 64, 128, 3, 1, 1),      # resident weights, two slices
     (4, 64, 64, 128, 128, 3, 1, 1),     # fewer tiles: 128 x 64, shared pixel line, reduction may be split
-    (6, 80, 80, 64, 64, 3, 1, 1),       # 64 output channels
+    (6, 80, 80, 72, 64, 3, 1, 1),       # 64 output channels
+    (6, 80, 80, 64, 64, 3, 1, 1),       # the same on 128-byte pixels: resident weights
     (4, 72, 72, 96, 192, 3, 2, 1),      # stride 2: tap by tap
     (4, 60, 64, 256, 320, 1, 1, 0),     # 1x1
     (2, 48, 160, 32, 64, 5, 1, 2),      # 25 taps
