@@ -101,11 +101,21 @@
     const uint32_t frag_row = (uint32_t)(lane & 31) * 128u;
     const uint32_t frag_t16 = (uint32_t)(((lane >> 5) * HALF) ^ FC_SWZ(lane & 31)) * 16u;
 
-    // Tile order: all row tiles of channel tile 0, then of channel tile 1, ...  Workgroups
-    // are dispatched round-robin over the 8 XCDs, each with its own L2, so XCD j takes the
-    // j-th contiguous eighth of that order: its tiles share one weight slab and
-    // neighbouring image rows (the halo of the 3x3 taps) in that L2.
+    // Tile order.  Workgroups are dispatched round-robin over the 8 XCDs, each with its own L2, so XCD j takes the
+    // j-th contiguous eighth of the order: its tiles share neighbouring image rows (the halo of the 3x3 taps) in
+    // that L2.  The order is by groups of `1 << nt_log` channel tiles, within a group row tile by row tile: the
+    // pixels of a row tile are read by one XCD per group, a group's weights by the XCDs that share it.  Against one
+    // channel tile after another (half kept, chained): 256 -> 256 stride 2 from 32 x 60 x 80 reads 174 -> 68 MB past the L2s, 48.8 -> 43.2 us;
+    // 1024 -> 512 on 32 x 30 x 40 167 -> 54 MB, 40.7 -> 36.8; 1024 -> 256 there 83 -> 46 MB, 25.2 -> 23.4; 512 -> 512 3x3 on 32 x 15 x 20
+    // 94 -> 30 MB, 45 -> 41.
     const int n_mt = (rows + TM - 1) / TM;
+    int nt_log = 0;
+    {
+        // doubling a group halves the readers of the pixels and doubles those of the weights (both in units of c_in)
+        const float px = (float)rows * (float)(taps == 1 ? 1 : g.sh * g.sw) * (float)(n_nt * n_nt);
+        const float wt = 16.f * (float)g.c_out * (float)taps;
+        while (!(n_nt & ((2 << nt_log) - 1)) && px > wt * (float)(1 << (2 * nt_log))) ++nt_log;
+    }
     // Split-K: when there are fewer tiles than workgroups (small layers, or few kept rows)
     // the reduction of every tile is cut into S equal runs of stages, one work unit each, so
     // that the serial K loop of a workgroup gets S times shorter and the chip fills up.
@@ -175,7 +185,8 @@
             s_end = (int)((uint32_t)((split + 1) * stages) / (uint32_t)S);
         }
         int nst = s_end - s_begin; // stages of this unit
-        const int nt = tile / n_mt, mt = tile - nt * n_mt;
+        const int grp = tile / (n_mt << nt_log), in_grp = tile - grp * (n_mt << nt_log);
+        const int mt = in_grp >> nt_log, nt = (grp << nt_log) + (in_grp & ((1 << nt_log) - 1));
         const int co0 = nt * TN;
 
         __syncthreads(); // the previous tile's epilogue is done with LDS
