@@ -100,7 +100,7 @@ hipError_t launch_mask_window(const uint8_t *mask_in, int n, int h, int w, int k
 // throughput of long ones, see launch_lists_n.  Bound: launch latency for the masks of one image, HBM for the
 // largest.  No workgroup ever waits on another, so every grid drains:
 //   - short lists: ONE launch; a workgroup counts the kept positions before its own by itself (16 bytes per
-//     lane and load at the mask's resolution, sixteen labels per lane in flight otherwise);
+//     lane and load, also through a stride);
 //   - longer lists: two launches, labels and per-workgroup counts first, then offsets and lists.
 // (Four levels of one 224 x 224 mask: 7.1 + 4.2 us in two launches with sixteen positions per lane and the
 // levels' maps applied one after another; the labels of 5 814 positions through a stride: 8.9 us.)
@@ -108,12 +108,12 @@ hipError_t launch_mask_window(const uint8_t *mask_in, int n, int h, int w, int k
 constexpr int kListThreads = 1024; // of a workgroup whose lanes take four positions
 constexpr int kListWaves = kListThreads / 64;
 template <int PER> constexpr int kThreadsOf = kCompactBlockElems / PER;
-// Most workgroups of a list in the one-launch form.  At the mask's resolution the last workgroup reads
-// 16 KB per 16 lanes-wide load, so 64 of them (256 KB) cost what one round trip and a half costs (one list of
-// 131 072 positions 4.6 us against 5.7 us in two launches, of 262 144 5.9 against 5.8).  Through a stride four workgroups
-// before it are one round trip, and every further four one more: four levels of one 224 x 224 mask 6.2 us against 6.5 us
-// in two launches, of two 8.8 against 6.6 us, of 16 x 128 x 128 17.0 against 7.6 us.
-constexpr int kOnceBlocksIdentity = 64, kOnceBlocks = 4;
+// 16-byte reads of a list's last workgroup up to which one launch serves all lists, and up to which its workgroups have 256 threads
+// (kOnceBlocks: where a list has to be labelled position by position).  One launch after another, bytes, us, two launches or one of 1024
+// threads that labels the positions before its own one by one -> here: four levels of 224 x 224 (3 136 reads) 5.8 -> 4.2, 251 x 333 (5 224) 6.3 -> 5.4, 2 x 224 x 224
+// (6 272) 6.5 -> 5.2, 8 x 131 x 127 6.4 -> 5.1, 4 x 224 x 224 (12 544) 6.7 -> 6.6, 16 x 128 x 128 (16 384) 7.3 -> 6.5.  With 256 threads the last three take 5.7, 6.0, 8.0 and
+// 9.5; 160 x 160 takes 3.4 with them and 4.1 with 1024.  Past 16 384 the counting alone is what the second launch costs.
+constexpr int kOncePieces = 16384, kBriefPieces = 4096, kOnceBlocks = 4;
 // Workgroups of a list at the mask's resolution from which on a lane takes sixteen positions: there the labels of
 // sixteen are one load as those of four are, and what such a list costs is instructions per lane.  Four -> sixteen, a list
 // alone / a pyramid of four levels: 1.6 M positions 10.1 -> 9.9 / 12.4 -> 12.4 us, 2.1 M 10.1 -> 10.0 / 13.9 -> 12.8, 5.2 M
@@ -266,50 +266,133 @@ __device__ __forceinline__ int store_list(const LabelMap &L, int p0, uint32_t f,
     return total;
 }
 
-// one launch: labels, lists and counts
-template <int NL>
-__global__ __launch_bounds__(kListThreads) void k_lists_once(ListArgs<NL> a, const uint8_t *__restrict__ mask_in)
-{
-    __shared__ int wave_sum[kListWaves], scratch[kListWaves];
-    const int tid = threadIdx.x;
-    const LabelMap &L = a.at[NL == 1 ? 0 : list_of_block(a, blockIdx.x)];
-    const int block = blockIdx.x - L.block0;
-    const int p0 = block * kCompactBlockElems + tid * 4;
-    const bool vec = a.vec_in != 0;
-    const uint32_t f = labels<4>(L, mask_in, p0, vec);
+// sum + nonzero bytes of v (the masked byte differences of v ^ 1 and v: one for every byte that is not zero)
+__device__ __forceinline__ uint32_t add_nonzero(uint32_t v, uint32_t sum) { return __builtin_amdgcn_msad_u8(v ^ 0x01010101u, v, sum); }
 
-    // kept positions of this list before this workgroup's
-    int part = 0;
-    if (L.identity && vec && !L.packed_in) {
+// Kept positions among the first `before` of a list, this lane's share of them (the workgroup's lanes share all): 16 bytes a load, B loads in
+// flight.  A row of a list that steps through the mask is read by pieces that start at its first position's byte.
+template <int THREADS, int B>
+__device__ __forceinline__ int kept_before(const LabelMap &L, const uint8_t *__restrict__ mask_in, int before)
+{
+    uint32_t part = 0;
+    if (L.identity) {
         const uint4 *m4 = reinterpret_cast<const uint4 *>(mask_in);
-        const int pieces = block * (kCompactBlockElems / 16);
-        for (int i0 = tid; i0 < pieces; i0 += 4 * kListThreads) {
-            uint4 v[4];
+        const int pieces = before >> 4; // (a multiple of 16)
+        for (int i0 = threadIdx.x; i0 < pieces; i0 += B * THREADS) {
+            uint4 v[B];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) v[k] = i0 + k * kListThreads < pieces ? m4[i0 + k * kListThreads] : make_uint4(0, 0, 0, 0);
+            for (int k = 0; k < B; ++k) v[k] = i0 + k * THREADS < pieces ? m4[i0 + k * THREADS] : make_uint4(0, 0, 0, 0);
 #pragma unroll
-            for (int k = 0; k < 4; ++k)
-                part += __popc(nonzero_bytes(v[k].x)) + __popc(nonzero_bytes(v[k].y)) + __popc(nonzero_bytes(v[k].z)) +
-                        __popc(nonzero_bytes(v[k].w));
+            for (int k = 0; k < B; ++k) part = add_nonzero(v[k].w, add_nonzero(v[k].z, add_nonzero(v[k].y, add_nonzero(v[k].x, part))));
         }
+        return part;
+    }
+    const int full = (int)fast_div((uint32_t)before, L.div_w), rest = before - full * L.wl; // whole rows, positions of the next
+    const int pieces = full * L.pieces + (rest ? L.pieces : 0), bytes = L.rows_in * L.w0;
+    for (int i0 = threadIdx.x; i0 < pieces; i0 += B * THREADS) {
+        uint4 v[B];
+        int n[B]; // positions of the piece that count
+#pragma unroll
+        for (int k = 0; k < B; ++k) {
+            const int i = i0 + k * THREADS;
+            const int r = (int)fast_div((uint32_t)i, L.div_pieces), q = i - r * L.pieces;
+            const int b = (int)fast_div((uint32_t)r, L.div_h), oh = r - b * L.hl;
+            n[k] = i < pieces ? min((r < full ? L.wl : rest) - q * L.per, L.per) : 0;
+            const int ih = min(max(oh * L.row.mul + L.row.add, L.row.lo), L.row.hi);
+            const int at = (b * L.h0 + ih) * L.w0 + L.col.add + q * 16;
+            v[k] = make_uint4(0, 0, 0, 0);
+            if (n[k] > 0) {
+                if (at + 16 <= bytes) {
+                    __builtin_memcpy(&v[k], mask_in + at, 16);
+                } else { // (the mask's last bytes)
+                    for (int j = 0; j < n[k]; ++j) part += mask_in[at + j * L.col.mul] != 0;
+                    n[k] = 0;
+                }
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < B; ++k) {
+            uint32_t f[4] = {v[k].x & L.sel, v[k].y & L.sel_odd, v[k].z & L.sel_rest, v[k].w & L.sel_odd};
+            const int end = n[k] * L.col.mul; // bytes of it
+            if (n[k] < L.per)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) f[j] &= end >= 4 * j + 4 ? ~0u : (end > 4 * j ? (1u << (8 * (end - 4 * j))) - 1u : 0u);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) part = add_nonzero(f[j], part);
+        }
+    }
+    return part;
+}
+
+// The labels of four positions of a list whose bytes are col.mul apart in a byte mask, at least four to a row.
+__device__ __forceinline__ uint32_t labels_stepped(const LabelMap &L, const uint8_t *__restrict__ mask_in, int p0)
+{
+    if (p0 >= L.m) return 0;
+    const int t = (int)fast_div((uint32_t)p0, L.div_w), ow = p0 - t * L.wl;
+    auto row_at = [&](int r) {
+        const int b = (int)fast_div((uint32_t)r, L.div_h), oh = r - b * L.hl;
+        return (b * L.h0 + min(max(oh * L.row.mul + L.row.add, L.row.lo), L.row.hi)) * L.w0 + L.col.add;
+    };
+    const int here = L.wl - ow, left = L.m - p0; // positions to the end of the row, of the list
+    const int at0 = row_at(t) + ow * L.col.mul, at1 = here < 4 && here < left ? row_at(t + 1) - here * L.col.mul : at0;
+    uint32_t got[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) got[j] = j < left ? mask_in[(j < here ? at0 : at1) + j * L.col.mul] : 0u;
+    return (got[0] ? 1u : 0u) | (got[1] ? 2u : 0u) | (got[2] ? 4u : 0u) | (got[3] ? 8u : 0u);
+}
+
+// One launch: labels, lists and counts.  A row of workgroups per list, four positions a lane; a workgroup counts the kept positions before
+// its own by itself.  What this kernel takes is instructions, one wave's after another, and the round trip of the labels: 256 threads for
+// the masks of an image, whose waves have a SIMD each, 1024 for longer ones, so that the last workgroups' counting
+// has enough loads on its way.
+template <int NL, int THREADS>
+__global__ __launch_bounds__(THREADS) void k_lists_once(ListArgs<NL> a, const uint8_t *__restrict__ mask_in)
+{
+    constexpr int W = THREADS / 64, ELEMS = THREADS * 4;
+    __shared__ int wave_sum[2 * W];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const LabelMap &L = a.at[NL == 1 ? 0 : blockIdx.y];
+    const int before = blockIdx.x * ELEMS, p0 = before + tid * 4;
+    if (before >= L.m) return;
+    const bool vec = a.vec_in != 0;
+    uint32_t f;
+    int part = 0;
+    if (L.identity ? vec && !L.packed_in : L.pieces > 0) {
+        f = L.identity ? labels<4>(L, mask_in, p0, vec) : labels_stepped(L, mask_in, p0);
+        part = kept_before<THREADS, 4>(L, mask_in, before);
     } else {
-        for (int b0 = 0; b0 < block; b0 += 4) {
+        f = labels<4>(L, mask_in, p0, vec);
+        for (int b0 = 0; b0 < (int)blockIdx.x; b0 += 4) {
             uint32_t g[4];
 #pragma unroll
-            for (int k = 0; k < 4; ++k)
-                g[k] = b0 + k < block ? labels<4>(L, mask_in, (b0 + k) * kCompactBlockElems + tid * 4, vec) : 0u;
+            for (int k = 0; k < 4; ++k) g[k] = b0 + k < (int)blockIdx.x ? labels<4>(L, mask_in, (b0 + k) * ELEMS + tid * 4, vec) : 0u;
 #pragma unroll
             for (int k = 0; k < 4; ++k) part += __popc(g[k]);
         }
     }
+    const int c = __popc(f), incl = wave_inclusive_scan(c), earlier = wave_inclusive_scan(part);
+    if (lane == 63) {
+        wave_sum[wave] = incl;
+        wave_sum[W + wave] = earlier;
+    }
     store_labels<4>(L, p0, f);
-    const int base = block ? block_sum<kListWaves>(part, scratch) : 0;
-    const int total = store_list<4>(L, p0, f, base, wave_sum);
-    if (tid == 0 && (int64_t)(block + 1) * kCompactBlockElems >= L.m) *L.count = base + total;
+    __syncthreads();
+    int at = incl - c, total = 0;
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+        const int t = wave_sum[i], e = wave_sum[W + i];
+        at += (i < wave ? t : 0) + e;
+        total += t + e;
+    }
+    int32_t *to = L.idx + at;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        if ((f >> j) & 1u) *to++ = p0 + j;
+    if (tid == 0 && before + ELEMS >= L.m) *L.count = total;
 
     // on the side, for the convolution that follows: clear its split-K tile counters
     if (NL == 1 && a.ex.zero && blockIdx.x == 0)
-        for (int i = tid; i < a.ex.zero_n; i += kListThreads) a.ex.zero[i] = 0;
+        for (int i = tid; i < a.ex.zero_n; i += THREADS) a.ex.zero[i] = 0;
 }
 
 // two launches: labels and per-workgroup counts ...
@@ -364,17 +447,50 @@ __global__ __launch_bounds__(kThreadsOf<PER>) void k_lists_scatter(ListArgs<NL> 
         for (int i = tid; i < a.ex.zero_n; i += kThreadsOf<PER>) a.ex.zero[i] = 0;
 }
 
+// Are the bytes of a list's positions col.mul apart along a row, so that 16-byte pieces hold 16 / col.mul of them each?
+static void set_pieces(LabelMap &L, bool vec)
+{
+    L.pieces = 0;
+    L.rows_in = 0;
+    const int mul = L.col.mul;
+    if (L.identity || L.packed_in || (mul != 1 && mul != 2 && mul != 4 && mul != 8 && mul != 16) || L.wl < 4 || L.col.add < 0) return;
+    if ((int64_t)(L.wl - 1) * mul + L.col.add > L.w0 - 1 || L.col.lo > 0 + L.col.add || L.col.hi < (L.wl - 1) * mul + L.col.add) return;
+    L.per = 16 / mul;
+    L.pieces = (L.wl + L.per - 1) / L.per;
+    L.div_pieces = make_fastdiv((uint32_t)L.pieces);
+    L.rows_in = (int32_t)((int64_t)L.m / ((int64_t)L.hl * L.wl) * L.h0);
+    L.sel = mul == 1 ? 0xffffffffu : (mul == 2 ? 0x00ff00ffu : 0x000000ffu);
+    L.sel_odd = mul <= 4 ? L.sel : 0u;
+    L.sel_rest = mul <= 8 ? L.sel : 0u;
+}
+
 template <int NL>
 static hipError_t launch_lists_n(const ListArgs<NL> &a, const uint8_t *mask_in, int32_t *block_counts, hipStream_t s)
 {
-    bool once = true, longer = false;
+    ListArgs<NL> b = a;
+    bool once = true, brief = true, longer = false;
+    int64_t most = 0;
     for (int l = 0; l < a.lists; ++l) {
-        const bool fast = a.at[l].identity && a.vec_in && !a.at[l].packed_in;
-        longer = longer || ((fast || (a.at[l].identity && a.at[l].packed_in)) && compact_blocks(a.at[l].m) > kLongBlocks);
-        once = once && compact_blocks(a.at[l].m) <= (fast ? kOnceBlocksIdentity : kOnceBlocks);
+        LabelMap &L = b.at[l];
+        set_pieces(L, a.vec_in != 0);
+        const bool fast = L.identity && a.vec_in && !L.packed_in;
+        longer = longer || ((fast || (L.identity && L.packed_in)) && compact_blocks(L.m) > kLongBlocks);
+        const int64_t rows = ((int64_t)L.m + L.wl - 1) / L.wl, reads = fast ? ((int64_t)L.m + 15) / 16 : rows * L.pieces;
+        if (fast || L.pieces > 0) {
+            once = once && reads <= kOncePieces;
+            brief = brief && reads <= kBriefPieces;
+        } else {
+            once = once && compact_blocks(L.m) <= kOnceBlocks;
+            brief = brief && L.m <= 1024;
+        }
+        most = L.m > most ? L.m : most;
+    }
+    if (once && brief) {
+        hipLaunchKernelGGL((k_lists_once<NL, 256>), dim3((unsigned)((most + 1023) / 1024), a.lists), dim3(256), 0, s, b, mask_in);
+        return hipGetLastError();
     }
     if (once) {
-        hipLaunchKernelGGL(k_lists_once<NL>, dim3(a.blocks), dim3(kListThreads), 0, s, a, mask_in);
+        hipLaunchKernelGGL((k_lists_once<NL, kListThreads>), dim3((unsigned)compact_blocks(most), a.lists), dim3(kListThreads), 0, s, b, mask_in);
         return hipGetLastError();
     }
     const int threads = longer ? kThreadsOf<16> : kThreadsOf<4>;
