@@ -18,6 +18,7 @@
 // entries, and the caller clears the irrelevant rows.
 #include "fc_dma_util.hpp"
 #include <type_traits>
+#include <atomic>
 
 namespace fc {
 
@@ -370,6 +371,257 @@ __global__ __launch_bounds__(kRegThreads, 2) void k_conv_f32(Geom g, const float
     }
 }
 
+// ---------------------------------------------------------------------------------------------
+// The same split (WK = 4) for 3x3 kernels of whole 32-channel chunks, horizontally undilated, with bytes for masks: what bounds k_conv_f32 there is not
+// the matrix cores (two workgroups of a CU: 9 200 cycles) but what its waves issue beside them: stamps of 64 -> 64 on 2 x 60 x 80, half
+// kept, 5 100 cycles to the rows' bits (three divisions by run-time numbers a look-up, five barriers), 13 500 in the stages, 3 500 from there to
+// the last store.  Here
+//   - a lane holds a row: consecutive positions (rows are 32 a tile, so compacting them saves no instruction), or list entries; every
+//     wave finds all 32 by itself, no barrier;
+//   - what the mask says about a row's taps selects the LDS address its operand is read from: the row's, or one of zeros;
+//   - lane q knows the offsets of stage q; a load is an addition and an instruction;
+//   - a round is three stages with one barrier, two rounds are on their way, LDS offsets are constants.
+// The products, their order and the order of the four waves' sums are those of k_conv_f32.  Mask given, one launch after
+// another, half kept, us: 64 -> 64 on 2 x 60 x 80 15.5 -> 10.4, 32 -> 32 on 14 x 20 7.3 -> 4.6, 64 -> 66 on 8 x 30 x 40 stride 2 9.7 -> 6.6, 96 -> 128 on 4 x 67 x 90
+// 60.5 -> 46.6.
+// ---------------------------------------------------------------------------------------------
+constexpr int kF32Round = 3;
+constexpr uint32_t kF32Stage = 64u * 128u;
+template <int RING> constexpr uint32_t kF32Zeros = RING * kF32Round * kF32Stage;
+template <int RING> constexpr uint32_t kF32Lds = kF32Zeros<RING> + 128u;
+constexpr int kF32MostStages = 63; // a lane each
+
+// RING: rounds in LDS
+template <int RING>
+__global__ __launch_bounds__(kRegThreads, RING == 2 ? 3 : 2) void k_conv_f32_rounds(Geom g, FastDiv by_cch, const float *__restrict__ x,
+                                                                    const uint8_t *__restrict__ mask_in,
+                                                                    const uint8_t *__restrict__ mask_out,
+                                                                    const float *__restrict__ w,
+                                                                    const float *__restrict__ bias,
+                                                                    const int32_t *__restrict__ idx,
+                                                                    const int32_t *__restrict__ count, float *__restrict__ out)
+{
+    extern __shared__ __align__(16) unsigned char lds[];
+    const int rows = idx ? __builtin_amdgcn_readfirstlane(*count) : g.m;
+    const int first = blockIdx.x * 32;
+    if (first >= rows) return;
+    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int co0 = blockIdx.y * 32;
+
+    // ---- request what decides about the rows, and the bias of the channels this lane stores ----
+    int p = first + l32;
+    bool live = p < rows;
+    // (values of loads that are waited for by hand are touched by nothing before the wait)
+    uint32_t entry, label;
+    if (idx) {
+        const u32x4_t rsrc_i = make_rsrc_words(idx, (uint32_t)rows * 4u);
+        __asm__ volatile("buffer_load_dword %0, %1, %2, 0 offen" : "=v"(entry) : "v"((uint32_t)p * 4u), "s"(rsrc_i) : "memory");
+    } else if (mask_in) {
+        int at = live ? p : 0;
+        if (!mask_out) { // under the centre tap
+            const int q = (int)fast_div((uint32_t)at, g.div_wo), ow = at - q * g.wo;
+            const int img = (int)fast_div((uint32_t)q, g.div_ho), oh = q - img * g.ho;
+            const int ih = min(max(oh * g.sh - g.ph + g.dh, 0), g.h - 1), iw = min(max(ow * g.sw - g.pw + 1, 0), g.w - 1);
+            at = (img * g.h + ih) * g.w + iw;
+        }
+        __asm__ volatile("global_load_ubyte %0, %1, %2" : "=v"(label) : "v"(at), "s"(mask_out ? mask_out : mask_in) : "memory");
+    }
+    const int co = co0 + wave * 8 + half * 4;
+    const u32x4_t rsrc_b = make_rsrc_words(bias, bias ? (uint32_t)g.c_out * 4u : 0u);
+    uint32_t bq[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        __asm__ volatile("buffer_load_dword %0, %1, %2, 0 offen" : "=v"(bq[i]) : "v"((uint32_t)(co + i) * 4u), "s"(rsrc_b) : "memory");
+
+    // ---- stages: wave v loads rows 8 v .. 8 v + 7 of the pixels and of the weights ----
+    const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)reinterpret_cast<uintptr_t>(lds) + (uint32_t)wave * 1024u);
+    const int prow = wave * 8 + (lane >> 3);
+    const uint32_t piece = (uint32_t)((lane & 7) ^ FC_SWZ(prow)) * 16u;
+    const uint32_t pixel = (uint32_t)g.c_in * 4u, wrow = 9u * pixel;
+    const int cch = g.c_in >> 5, stages = 9 * cch;
+    const u32x4_t rsrc_w = make_rsrc_words(w, (uint32_t)g.c_out * wrow);
+    uint32_t woff = (uint32_t)(co0 + prow) * wrow + piece;
+    __asm__("" : "+v"(woff));
+    woff = co0 + prow < g.c_out ? woff : kOutOfRange;
+    const int tap_q = (int)fast_div((uint32_t)lane, by_cch), kh_q = tap_q * 11 >> 5;
+    const int x_q = (kh_q * g.dh * g.w + (tap_q - 3 * kh_q)) * (int)pixel + (lane - tap_q * cch) * 128, bit_q = 1 << (tap_q & 31);
+    if (tid < 8) *reinterpret_cast<uint4 *>(lds + kF32Zeros<RING> + tid * 16) = make_uint4(0u, 0u, 0u, 0u);
+
+    // ---- the rows ----
+    wait_vmcnt<4>();
+    bool drop = false;
+    if (idx) {
+        __asm__ volatile("" : "+v"(entry)::"memory");
+        p = live ? (int)entry : 0;
+    } else if (mask_in) {
+        __asm__ volatile("" : "+v"(label)::"memory");
+        const bool kept = live && label != 0;
+        drop = live && !kept;
+        live = kept;
+    }
+    const bool fill = mask_in && !idx && !(g.flags & FC_SKIP_ZERO_FILL);
+    float *const to = out + (int64_t)(drop ? first + l32 : p) * g.c_out + co;
+    auto store = [&](float4 v) __attribute__((always_inline)) {
+        if (!(live || (drop && fill))) return;
+        const float e[4] = {drop ? 0.f : v.x, drop ? 0.f : v.y, drop ? 0.f : v.z, drop ? 0.f : v.w};
+        if ((g.c_out & 3) == 0) {
+            if (co < g.c_out) *reinterpret_cast<float4 *>(to) = make_float4(e[0], e[1], e[2], e[3]);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (co + i < g.c_out) to[i] = e[i];
+        }
+    };
+    if (__ballot(live) == 0) { // (the same in all waves)
+        store(make_float4(0.f, 0.f, 0.f, 0.f));
+        return;
+    }
+    const int pp = live ? p : 0;
+    const int q = (int)fast_div((uint32_t)pp, g.div_wo), ow = pp - q * g.wo;
+    const int img = (int)fast_div((uint32_t)q, g.div_ho), oh = q - img * g.ho;
+    const int ih0 = oh * g.sh - g.ph, iw0 = ow * g.sw - g.pw;
+    const int pix0 = (img * g.h + ih0) * g.w + iw0; // may lie outside the image
+
+    // the mask bytes under the taps of a kernel row with one (unaligned) 4-byte load each; one that would leave the
+    // mask is moved inside it and its bytes moved back (without a mask: three loads of something, not looked at)
+    const uint8_t *const from = mask_in ? mask_in : reinterpret_cast<const uint8_t *>(w);
+    const int most = mask_in ? g.n * g.h * g.w - 4 : 0;
+    uint32_t m[3];
+    int moved[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const int off = pix0 + k * g.dh * g.w, at = min(max(off, 0), most);
+        moved[k] = off - at;
+        __asm__ volatile("global_load_dword %0, %1, %2" : "=v"(m[k]) : "v"(at), "s"(from) : "memory");
+    }
+    const u32x4_t rsrc_x = make_rsrc_words(x, (uint32_t)g.n * g.h * g.w * pixel);
+    // (what lies outside the tensor is out of range, whichever side; what lies in it beside the image is not looked at)
+    const uint32_t xoff = (uint32_t)__shfl(pix0, prow) * pixel + piece;
+    auto load_round = [&](int s, int slot) __attribute__((always_inline)) {
+        uint32_t sx[kF32Round], sw[kF32Round];
+#pragma unroll
+        for (int d = 0; d < kF32Round; ++d) {
+            sx[d] = (uint32_t)__builtin_amdgcn_readlane(x_q, s + d);
+            sw[d] = (uint32_t)(s + d) * 128u;
+            __asm__ volatile("" : "+s"(sw[d]));
+        }
+#pragma unroll
+        for (int d = 0; d < kF32Round; ++d) {
+            dma_load16(rsrc_x, xoff + sx[d], lds0 + (uint32_t)(slot + d) * kF32Stage);
+            dma_load16_s(rsrc_w, woff, sw[d], lds0 + (uint32_t)(slot + d) * kF32Stage + 4096u);
+        }
+    };
+#pragma unroll
+    for (int r = 0; r < RING - 1; ++r) load_round(r * kF32Round, r * kF32Round);
+
+    // taps inside the image and relevant
+    uint32_t bits = 0, rel = 0, cols = 0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) cols |= (uint32_t)(iw0 + k) < (uint32_t)g.w ? 1u << k : 0u;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) bits |= (uint32_t)(ih0 + k * g.dh) < (uint32_t)g.h ? cols << (3 * k) : 0u;
+    wait_vmcnt<(RING - 1) * 2 * kF32Round>();
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        __asm__ volatile("" : "+v"(m[k])::"memory");
+        uint32_t v = moved[k] < 0 ? (moved[k] > -4 ? m[k] << (-8 * moved[k]) : 0u) : (moved[k] < 4 ? m[k] >> (8 * moved[k]) : 0u);
+        v = (((v & 0x7f7f7f7fu) + 0x7f7f7f7fu) | v) & 0x80808080u; // nonzero bytes
+        rel |= (((v >> 7) & 1u) | ((v >> 14) & 2u) | ((v >> 21) & 4u)) << (3 * k);
+    }
+    bits = live ? bits & (mask_in ? rel : ~0u) : 0u;
+
+    f32x16_t acc;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+    const uint32_t at = (uint32_t)l32 * 128u + (uint32_t)((2 * wave + half) ^ FC_SWZ(l32)) * 16u;
+    auto round = [&](int s, int r) __attribute__((always_inline)) {
+        if (RING == 2 || s + kF32Round == stages) wait_vmcnt<0>();
+        else wait_vmcnt<(RING - 2) * 2 * kF32Round>(); // this round's stages have landed
+        __syncthreads();                               // ... all waves' parts; the round before is read
+        float4 xv[kF32Round], wv[kF32Round];
+#pragma unroll
+        for (int d = 0; d < kF32Round; ++d) {
+            const uint32_t slot = (uint32_t)(r * kF32Round + d) * kF32Stage;
+            const bool on = bits & (uint32_t)__builtin_amdgcn_readlane(bit_q, s + d);
+            xv[d] = *reinterpret_cast<const float4 *>(lds + slot + (on ? at : kF32Zeros<RING> - slot));
+            wv[d] = *reinterpret_cast<const float4 *>(lds + slot + 4096u + at);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (s + (RING - 1) * kF32Round < stages) load_round(s + (RING - 1) * kF32Round, (r + RING - 1) % RING * kF32Round);
+#pragma unroll
+        for (int d = 0; d < kF32Round; ++d) {
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wv[d].x, xv[d].x, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wv[d].y, xv[d].y, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wv[d].z, xv[d].z, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wv[d].w, xv[d].w, acc, 0, 0, 0);
+        }
+    };
+    for (int s = 0; s < stages; s += RING * kF32Round) {
+#pragma unroll
+        for (int r = 0; r < RING; ++r)
+            if (RING == 3 || r == 0 || s + r * kF32Round < stages) round(s + r * kF32Round, r); // (the rounds are a multiple of three)
+    }
+    // wave v finishes quad v: channels co0 + 8 v + 4 half .. + 3 of the position of row l & 31
+    __syncthreads(); // every wave is done with the stages
+    float4 *part = reinterpret_cast<float4 *>(lds);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) part[(wave * 4 + k) * 64 + lane] = make_float4(acc[k * 4], acc[k * 4 + 1], acc[k * 4 + 2], acc[k * 4 + 3]);
+    __syncthreads();
+    float4 v = part[wave * 64 + lane];
+#pragma unroll
+    for (int k = 1; k < 4; ++k) {
+        const float4 t = part[(k * 4 + wave) * 64 + lane];
+        v.x += t.x; v.y += t.y; v.z += t.z; v.w += t.w;
+    }
+    float e[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        __asm__ volatile("" : "+v"(bq[i])::"memory");
+        if (bias) e[i] += __uint_as_float(bq[i]);
+        if (g.flags & FC_RELU) e[i] = !(e[i] > 0.f) ? (e[i] != e[i] ? e[i] : 0.f) : e[i];
+    }
+    store(make_float4(e[0], e[1], e[2], e[3]));
+}
+
+static bool f32_rounds(const Geom &g, bool masked)
+{
+    return g.kh == 3 && g.kw == 3 && g.dw == 1 && g.c_in % 32 == 0 && 9 * (g.c_in / 32) <= kF32MostStages &&
+           (!masked || (!(g.flags & FC_PACKED_MASKS) && (int64_t)g.n * g.h * g.w >= 4));
+}
+
+template <int RING>
+static hipError_t launch_f32_ring(const Geom &g, const void *x, const uint8_t *mask_in, const uint8_t *mask_out, const void *w,
+                                    const float *bias, const int32_t *idx, const int32_t *count, void *out, hipStream_t s)
+{
+    // (more than 64 KB of dynamic LDS: allowed once per device)
+    static std::atomic<uint64_t> attr_devices{0};
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    const uint64_t dev_bit = 1ull << (dev & 63);
+    if (!(attr_devices.load(std::memory_order_acquire) & dev_bit)) {
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_conv_f32_rounds<RING>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kF32Lds<RING>);
+        if (e != hipSuccess) return e;
+        attr_devices.fetch_or(dev_bit, std::memory_order_release);
+    }
+    hipLaunchKernelGGL(k_conv_f32_rounds<RING>, dim3((g.m + 31) / 32, (g.c_out + 31) / 32), dim3(kRegThreads), kF32Lds<RING>, s, g,
+                       make_fastdiv((uint32_t)(g.c_in / 32)), (const float *)x, mask_in, mask_out, (const float *)w, bias, idx, count, (float *)out);
+    return hipGetLastError();
+}
+
+static hipError_t launch_f32_rounds(const Geom &g, const void *x, const uint8_t *mask_in, const uint8_t *mask_out, const void *w,
+                                    const float *bias, const int32_t *idx, const int32_t *count, void *out, hipStream_t s)
+{
+    // Three workgroups of a CU with two rounds each, or two with three.  Three hide each other's waits better (128 -> 128 on 3 x 50 x 50, half kept, 25.8 ->
+    // 20.8 us), but where there is work for two a CU - about seven tenths of the tiles of a mask of regions hold a kept row - some CUs
+    // get three and others one (64 -> 64 on 2 x 60 x 80, 0.5 / 0.7 kept: 11.8 / 11.9 us, with two 10.4 / 10.4).
+    const int64_t tiles = (int64_t)((g.m + 31) / 32) * ((g.c_out + 31) / 32), busy = mask_in ? tiles * 7 / 10 : tiles;
+    const int cus = conv_grid_cus();
+    if (busy > cus && busy <= 2 * cus) return launch_f32_ring<3>(g, x, mask_in, mask_out, w, bias, idx, count, out, s);
+    return launch_f32_ring<2>(g, x, mask_in, mask_out, w, bias, idx, count, out, s);
+}
+
 // four channels: one piece; 64 taps: the tap-valid bits of a row; 32-bit byte offsets into x and w; row
 // origins in 16 bits
 bool conv_f32_supported(const Geom &g)
@@ -404,6 +656,9 @@ hipError_t launch_conv_f32(const Geom &g, const void *x, const uint8_t *mask_in,
     // (95 -> 116 on 4 x 67 x 90, half of it kept: 73 -> 67 us; without a mask 33 -> 65 on 4 x 90 x 90 loses,
     // 47 -> 53 us).  32 output channels then: 64 halve the workgroups (64 -> 64 on 2 x 60 x 80: 15.6 and 17.5 us).
     const int64_t waves = (int64_t)((g.m + 31) / 32) * (wide ? blocks32 / 2 : blocks32);
+    // (k_conv_f32_rounds without a mask too: 96 -> 128 on 4 x 67 x 90 70 -> 58 us, 128 -> 64 on 3 x 100 x 110 88 -> 56; 128 -> 128 on 8 x 120 x 120, 7 200
+    // waves, 322 -> 332, with a mask 233 / 244 / 251 -> 175 / 229 / 267 at 0.3 / 0.5 / 0.7 kept)
+    if (waves < 4096 && f32_rounds(g, mask_in != nullptr)) return launch_f32_rounds(g, x, mask_in, mask_out, w, bias, idx, count, out, s);
     if (waves < (mask_in ? 4096 : 1024)) return FC_F32(32, 4, 6);
     return wide ? FC_F32(64, 1, 2) : FC_F32(32, 1, 3);
 #undef FC_F32
