@@ -66,7 +66,10 @@ class _Plan:
                                 (1, 1), stack.dtype)
                 calls.append(B.Call(d, B.CALL_MAXPOOL, src, -1, -1, -1, m_out, -1, -1, out_slot[i]))
             else:
-                skip = chain and masked and stack._gated_readers_only(i, readers)
+                # (an output that nobody reads and the caller does not get: its irrelevant rows are nobody's either; the four
+                # projections of a ResNet-50 on 32 frames of 120 x 160 wrote 640 MB instead of 330)
+                unseen = not readers.get(i) and not keep_outputs and i < n - 1
+                skip = chain and masked and (unseen or stack._gated_readers_only(i, readers))
                 extra = B.SKIP_ZERO_FILL if skip else 0
                 if op.src in compacted:
                     extra |= B.COMPACT_IN
@@ -242,7 +245,7 @@ class ConvStack:
 
     def _compact_out(self, i: int, skip: bool, readers) -> bool:
         """May op i hand its output on as a list of kept rows?"""
-        return (skip and self.ops[i].kind == "conv" and self._matrix_core_shape(i)
+        return (skip and bool(readers.get(i)) and self.ops[i].kind == "conv" and self._matrix_core_shape(i)
                 and all(self._pointwise(j) and self._matrix_core_shape(j) for j in readers[i]))
 
     def _run_planned(self, x, mask, keep_outputs: bool, chain: bool, compact: bool):
@@ -303,7 +306,7 @@ class ConvStack:
         unwritten (FC_SKIP_ZERO_FILL): every reader gates its taps by the same mask, so those
         rows are never looked at (Sec. III-A: irrelevant pixels are excluded from the
         product; Sec. III-B: the mask is the same all the way).  Outputs that a pooling
-        layer or nobody reads are still zero-filled.
+        layer reads, and those nobody reads that the caller gets, are still zero-filled.
         compact (with chain): a conv read only by 1x1 convs of unit stride writes its kept rows
         compacted, in list order (FC_COMPACT_OUT), and those readers read them that way
         (FC_COMPACT_IN): they see the same mask through the same geometry, hence the same list.

@@ -5,7 +5,7 @@ import random
 
 import pytest
 
-from paper_2207_10741_amd import binding as B, stacks
+from paper_2207_10741_amd import binding as B, stacks, workloads
 
 
 def _tensors(rng, n):
@@ -40,6 +40,32 @@ def test_arena_of_a_chain_reuses_its_ranges():
     assert stacks._place(chain, 0)[1] == 2 * 1024       # the tensor being read and the one being written
     assert stacks._place(chain, 4)[1] == 6 * 1024
     assert stacks._place([], 0) == ([], 0)
+
+
+@pytest.mark.parametrize("keep", [False, True])
+@pytest.mark.parametrize("compact", [False, True])
+def test_rows_nobody_can_see_stay_unwritten(keep, compact):
+    """Chained: an op that only convs read leaves its irrelevant rows; of the ops nobody reads, only those whose output the caller gets are
+    zero-filled, and none of them is handed on as a list."""
+    stack = object.__new__(stacks.ConvStack)
+    stack.ops, stack.n, stack.h, stack.w, stack.dtype, stack.relu = workloads.resnet50_bottlenecks(), 2, 30, 40, B.BF16, True
+    stack.sizes = {-1: (30, 40)}
+    for i, op in enumerate(stack.ops):
+        hi, wi = stack.sizes[op.src]
+        stack.sizes[i] = B.out_dims(B.conv_desc(2, hi, wi, 1, 1, (op.k, op.k), (op.stride, op.stride), (op.pad, op.pad), (1, 1), B.F32))
+    stack.pyramid_steps = stack._pyramid_steps()
+    plan = stacks._Plan(stack, True, keep, True, compact)
+    calls = [c for _, part in plan.parts for c in part]
+    read = {op.src for op in stack.ops}
+    returned = {i for i, _, _ in plan.returned}
+    assert returned == (set(range(len(stack.ops))) if keep else {len(stack.ops) - 1})
+    alone = [i for i in range(len(stack.ops)) if i not in read]
+    assert len(alone) == 5                                   # the four projections and the last layer
+    for i, call in enumerate(calls):
+        skipped = bool(call.desc.flags & B.SKIP_ZERO_FILL)
+        assert skipped == (i in read or i not in returned)
+        if i not in read:
+            assert not call.desc.flags & B.COMPACT_OUT
 
 
 # ---- fc_run_calls ----
