@@ -77,7 +77,7 @@ bool conv_line_wanted(const Geom &g, int in_dtype, int out_dtype, bool focused)
 {
     if (!focused || !(g.flags & FC_SKIP_ZERO_FILL) || !conv_line_supported(g, in_dtype, out_dtype)) return false;
     if (g.m <= kInlineRankPositions) return false;
-    if (g.c_out <= 64 || g.c_out > 128) return false;
+    if (g.c_out <= 64 || g.c_out > 128 || taps_packed(g, in_dtype, focused)) return false;
     return (int64_t)(g.m + 31) / 32 <= 8 * 256;
 }
 
@@ -392,7 +392,7 @@ int32_t fc_focused_conv2d(const fc_conv_desc *desc, const void *x, const uint8_t
     // (a layer whose reduction is not split leaves the counters alone; without a mask the row count, and with it
     // the number of splits, is known here)
     bool counters_cleared = small ? !conv_small_counts(g, room)
-                                  : !split_k_reachable(g, desc->in_dtype) || (!mask_in && !dense_layer_splits(g, desc->in_dtype));
+                                  : !split_k_reachable(g, desc->in_dtype, mask_in != nullptr) || (!mask_in && !dense_layer_splits(g, desc->in_dtype));
     const bool f32 = desc->in_dtype == FC_F32 && conv_f32_supported(g);
 
     if (mask_in && !idx) {

@@ -88,7 +88,8 @@
     const int taps = TAPC == 32 ? g.kh * g.kw : TAPC;
     const int kwid = TAPC == 32 ? g.kw : (TAPC == 9 ? 3 : 1);
     const int cchunks = (g.c_in + TK - 1) / TK;
-    const int stages = taps * cchunks;
+    const int tap_pieces = g.c_in / EPP; // PACK: a tap's 16-byte pieces
+    const int stages = PACK ? (taps * tap_pieces + 7) >> 3 : taps * cchunks;
     const bool self_tap = TAPC == 1 && g.ph == 0 && g.pw == 0;
     const u32x4_t rsrc_x = make_rsrc_words(x, (uint32_t)g.n * g.h * g.w * g.c_in * (uint32_t)ES);
     const u32x4_t rsrc_w = make_rsrc_words(w, (uint32_t)g.c_out * taps * g.c_in * (uint32_t)ES);
@@ -371,7 +372,7 @@
             const int r = prow + j * RPP;
             const int co = co0 + r;
             wgp[j] = slot ^ FC_SWZ(r);
-            woff[j] = co < g.c_out ? ((uint32_t)co * (uint32_t)(taps * g.c_in) + (uint32_t)wgp[j] * EPP) * ES
+            woff[j] = co < g.c_out ? ((uint32_t)co * (uint32_t)(taps * g.c_in) + (PACK ? 0u : (uint32_t)wgp[j] * EPP)) * ES
                                    : kOutOfRange;
         }
 
@@ -584,7 +585,7 @@
         for (int j = 0; j < XR; ++j) {
             const int r = prow + j * RPP;
             xgp[j] = slot ^ FC_SWZ(r);
-            xoff[j] = ((uint32_t)row_base[r] * (uint32_t)g.c_in + (uint32_t)xgp[j] * EPP) * ES;
+            xoff[j] = ((uint32_t)row_base[r] * (uint32_t)g.c_in + (PACK ? 0u : (uint32_t)xgp[j] * EPP)) * ES;
             xbits[j] = OWN && row_p[r] < 0 ? 0u : row_bits[r];
         }
         if constexpr (OWN) {
@@ -596,6 +597,18 @@
         int kh = tap / kwid, kw = tap - kh * kwid;
         int to_issue = nst; // stages of this unit not yet issued
         int ibuf = 0;       // LDS buffer the next stage goes to
+        // PACK: the piece of the reduction that this lane fetches (the same column of every row), its tap and its place in the tap; a
+        // stage further on they are eight pieces on
+        static_assert(!PACK || RPP % 16 == 0, "one swizzle for all of a lane's rows");
+        int piece = 0, ptap = 0, pch = 0, step_taps = 0, step_rest = 0, kw_inv = 0;
+        if constexpr (PACK) {
+            piece = s_begin * 8 + (slot ^ FC_SWZ(prow));
+            ptap = piece / tap_pieces;
+            pch = piece - ptap * tap_pieces;
+            step_taps = 8 / tap_pieces;
+            step_rest = 8 - step_taps * tap_pieces;
+            kw_inv = 65536 / kwid + 1; // tap / kwid, exact for the taps there are
+        }
 
         // Offsets and LDS targets of the cursor's stage (L wave loads), then advance the cursor.
         uint32_t ld_off[L], ld_lds[L];
@@ -626,6 +639,31 @@
         kh += wrap_w;                                                                                     \
         ibuf = (ibuf + 1 == NB) ? 0 : ibuf + 1;                                                           \
     }
+        // the same, pieces packed: the offsets of a row's tap and of the piece in it are the lane's own
+        auto prepare_packed = [&]() __attribute__((always_inline)) {
+            const int pkh = (ptap * kw_inv) >> 16, pkw = ptap - pkh * kwid;
+            const uint32_t sx = (uint32_t)((pkh * g.dh * g.w + pkw * g.dw) * tap_pieces + pch) * 16u;
+            const uint32_t ldsx = lds0 + (uint32_t)ibuf * STAGE_BYTES + (uint32_t)wave * 1024u;
+            const bool in_k = to_issue > 0 && ptap < taps;
+            --to_issue;
+            const uint32_t bit = in_k ? 1u << (ptap & 31) : 0u;
+#pragma unroll
+            for (int j = 0; j < XR; ++j) {
+                ld_off[j] = (xbits[j] & bit) ? xoff[j] + sx : kOutOfRange;
+                ld_lds[j] = ldsx + (uint32_t)j * (RPP * 128);
+            }
+#pragma unroll
+            for (int j = 0; j < WR; ++j) {
+                ld_off[XR + j] = in_k ? woff[j] + (uint32_t)piece * 16u : kOutOfRange;
+                ld_lds[XR + j] = ldsx + (uint32_t)(TM * 128 + j * (RPP * 128));
+            }
+            piece += 8;
+            pch += step_rest;
+            const int over = pch >= tap_pieces;
+            ptap += step_taps + over;
+            pch -= over ? tap_pieces : 0;
+            ibuf = (ibuf + 1 == NB) ? 0 : ibuf + 1;
+        };
 #define FC_ISSUE_LOADS(first, last)                                                                       \
     _Pragma("unroll") for (int j = (first); j < (last); ++j)                                              \
         if (j < L) dma_load16(j < XR ? rsrc_x : rsrc_w, ld_off[j], __builtin_amdgcn_readfirstlane(ld_lds[j]));
@@ -633,14 +671,17 @@
         // prologue: NB-1 stages in flight (stages past the end are all out of range: free)
 #pragma unroll
         for (int d = 0; d < NB - 1; ++d) {
-            FC_PREPARE_STAGE()
+            if constexpr (PACK) prepare_packed();
+            else FC_PREPARE_STAGE()
             FC_ISSUE_LOADS(0, L)
         }
 
         constexpr int LPK = (L + KK - 1) / KK; // wave loads issued per 16-wide k-step
         int cbuf = 0;                          // buffer of the stage being multiplied
         for (int s = 0; s < nst; ++s) {
-            FC_PREPARE_STAGE()          // stage s + NB - 1: addresses only
+            // stage s + NB - 1: addresses only
+            if constexpr (PACK) prepare_packed();
+            else FC_PREPARE_STAGE()
             wait_vmcnt<(NB - 2) * L>(); // this thread's loads of stage s have landed
             __syncthreads();            // ... and everyone else's; buffer (s-1) % NB is free
             const unsigned char *xs = stage0 + cbuf * STAGE_BYTES + (wave_m * WTM) * 128 + frag_row;

@@ -84,12 +84,16 @@ constexpr size_t dma_lds_bytes()
 // OWN: the 64 x 64 instance for layers with a mask and no list that label their rows themselves (tiles_label_rows).
 // The rows of a tile are consecutive positions, the irrelevant ones are stored as zeros, and no reduction is split.
 //
+// PACK: the reduction is one run of 16-byte pieces, eight a stage (taps_packed): a row of weights is contiguous over taps and channels,
+// and a lane, which fetches the same column of every row of a stage, keeps the tap and the place in it of its own piece.  No stage is
+// filled up with channels that are not there: 72 -> 200 on 3 x 75 x 101, stride 2, f16, 11 stages instead of 18, 12.8 -> 10.1 us.
+//
 // LIST (conv_list_tiles): the list is given and its length, list_rows, known already.
 //
 // CMP: the instances that serve compacted activations (FC_COMPACT_IN / FC_COMPACT_OUT: rows
 // stored in list order).  Separate instances, so that the ordinary ones do not change by a
 // register: the 128 x 64 three-buffer instance loses 20 % with a handful more.
-template <int DT, typename TO, int TM, int TN, int WM, int WN, int TAPC, int NB, int MINW, int SL, int NBW, bool CMP, bool OWN>
+template <int DT, typename TO, int TM, int TN, int WM, int WN, int TAPC, int NB, int MINW, int SL, int NBW, bool CMP, bool OWN, bool PACK>
 __global__ __launch_bounds__(WM *WN * 64, MINW) void k_conv_dma(Geom g, const uint16_t *__restrict__ x, const uint8_t *__restrict__ mask_in,
                                                                  const uint8_t *__restrict__ mask_out, const uint16_t *__restrict__ w,
                                                                  const float *__restrict__ bias, const int32_t *__restrict__ idx,
@@ -109,7 +113,7 @@ __device__ __forceinline__ void conv_list_tiles(const Geom &g, const uint16_t *_
                                                 const int32_t *__restrict__ count, int list_rows, TO *__restrict__ out)
 {
     constexpr int SL = 0, NBW = 2;
-    constexpr bool OWN = false, LIST = true;
+    constexpr bool OWN = false, LIST = true, PACK = false;
     float *const partials = nullptr;
     int32_t *const tile_counters = nullptr;
 #include "fc_conv_dma_body.hpp"
@@ -166,21 +170,22 @@ struct TileShape {
         narrow64,   // 128 x 64, three workgroups per CU
         tall64,     // 128 x 64, two workgroups per CU
     } kind;
+    bool packed; // taps_packed, for tiles that go tap by tap
     int rows() const { return kind == own64 || kind == small64 ? 64 : 128; }
     int cols() const { return kind == line128 || kind == deep || kind == wide128 ? 128 : 64; }
 };
 
 // splits: the call brings split-K scratch; labels_rows: a mask and no list
-static inline TileShape choose_tile(const Geom &g, int in_dtype, bool masked, bool labels_rows, bool splits)
+static inline TileShape::Kind choose_kind(const Geom &g, int in_dtype, bool masked, bool labels_rows, bool splits, bool packed)
 {
     const bool k1 = g.kh == 1 && g.kw == 1, k3 = g.kh == 3 && g.kw == 3;
     const int64_t rows128 = (g.m + 127) / 128;
     const int64_t tiles128 = rows128 * ((g.c_out + 127) / 128), tiles64 = rows128 * ((g.c_out + 63) / 64);
-    if (k3 && labels_rows && g.m > kInlineRankPositions) return {TileShape::own64};
+    if (labels_rows && tiles_label_rows(g, in_dtype)) return TileShape::own64;
     // Layers with only a handful of tiles (the late layers of a network at batch 1) are all
     // latency: 64 x 64 tiles put them on more CUs and four stage buffers keep three gathers in
     // flight (a ResNet-18 stack at batch 1: 0.243 -> 0.221 ms dense, 0.266 -> 0.245 ms focused)
-    if ((k1 || k3) && tiles64 <= kSmallLayerTiles) return {TileShape::small64};
+    if (tiles64 <= kSmallLayerTiles) return TileShape::small64;
     // 128 x 128 tiles when there are enough of them to give every CU two workgroups;
     // otherwise 128 x 64, which doubles the tile count (the kept count is not known here,
     // so the dense row count decides)
@@ -189,19 +194,19 @@ static inline TileShape choose_tile(const Geom &g, int in_dtype, bool masked, bo
     // between their three horizontal taps (worth it when image rows are long enough for runs
     // of adjacent kept positions; narrow layers with many tiles do better with three
     // workgroups per CU, see below)
-    if (k3 && g.sw == 1 && g.dw == 1 && g.wo >= 16) {
+    if (k3 && g.sw == 1 && g.dw == 1 && g.wo >= 16 && !packed) {
         // (with many 128 x 128 tiles it pays down to 16-pixel rows: C512@16 at batch 128 is
         // 13 % faster dense and 17 % faster focused than tap by tap)
-        if (g.c_out > 64 && tiles128 >= 512) return {TileShape::line128};
+        if (g.c_out > 64 && tiles128 >= 512) return TileShape::line128;
         // narrow layers: only with very many tiles (C64@128: -7 % focused, -4..8 % dense from batch
         // 128 on, 16 384 row tiles; at 4 800 row tiles, 64 -> 64 on 32 x 120 x 160 positions, three
         // workgroups per CU, below, are 7 % faster, and at batch 16 as fast)
         const bool many_narrow_tiles = rows128 >= 8192;
-        if (g.wo >= 32 && (g.c_out > 64 || splits || many_narrow_tiles)) return {TileShape::line64};
+        if (g.wo >= 32 && (g.c_out > 64 || splits || many_narrow_tiles)) return TileShape::line64;
         // shorter image rows, wide layers, a few hundred tiles (C512 on 32 x 15 x 20 positions:
         // 66 us dense / 45 us chained against 102 / 49 us tap by tap; with 128 tiles, C512@16 at
         // batch 16, tap by tap stays ahead)
-        if (g.c_out > 64 && tiles128 >= 256) return {TileShape::line64};
+        if (g.c_out > 64 && tiles128 >= 256) return TileShape::line64;
     }
     // (1x1 layers keep the wide tiles down to 256 of them: 2048 -> 512 on 32 x 15 x 20 positions,
     // 300 tiles, 37 us dense / 29 us chained against 51 / 32 us with 128 x 64 tiles)
@@ -209,15 +214,22 @@ static inline TileShape choose_tile(const Geom &g, int in_dtype, bool masked, bo
     // covers, so that 1x1 layers are one round whatever the mask keeps (1024 -> 512 on 32 x 15 x 25, 376 tiles, 0.1 / 0.5 / 0.9 / 1 kept: 11.2 /
     // 17.5 / 19.4 / 19.5 -> 12.0 / 14.2 / 19.2 / 20.3).  Below twelve stages there is little to keep on its way (at twelve, 768 -> 128 on 28 x 30 x 41,
     // 0.3 / 0.5 / 0.7 / 0.9: 9.6 / 11.7 / 14.9 / 16.7 -> 10.4 / 11.3 / 12.1 / 13.5).
-    const int cus = conv_grid_cus(), stages = g.kh * g.kw * ((g.c_in * (in_dtype == FC_FP8 ? 1 : 2) + 127) / 128);
+    const int cus = conv_grid_cus(), stages = reduction_stages(g, in_dtype, false);
     if ((k1 || k3) && g.c_out > 64 && masked && !labels_rows && !splits && stages >= 12 && tiles128 >= cus &&
         (int64_t)((g.m + 191) / 192) * ((g.c_out + 127) / 128) <= cus)
-        return {TileShape::deep};
-    if (g.c_out > 64 && tiles128 >= (k1 ? 256 : 512)) return {TileShape::wide128};
+        return TileShape::deep;
+    if (g.c_out > 64 && tiles128 >= (k1 ? 256 : 512)) return TileShape::wide128;
     // narrow layers with many tiles: two stage buffers, so that three workgroups fit a CU
     // and overlap each other's set-up and epilogue
-    if (g.c_out <= 64 && !splits) return {TileShape::narrow64};
-    return {TileShape::tall64};
+    if (g.c_out <= 64 && !splits) return TileShape::narrow64;
+    return TileShape::tall64;
+}
+
+static inline TileShape choose_tile(const Geom &g, int in_dtype, bool masked, bool labels_rows, bool splits)
+{
+    const bool packed = taps_packed(g, in_dtype, masked);
+    const TileShape::Kind kind = choose_kind(g, in_dtype, masked, labels_rows, splits, packed);
+    return {kind, packed && kind != TileShape::deep};
 }
 
 #if !defined(FC_MFMA_PART) || FC_MFMA_PART == 0
@@ -233,12 +245,13 @@ static inline TileShape choose_tile(const Geom &g, int in_dtype, bool masked, bo
 // kept, so its last bits can be others there.)
 bool tiles_label_rows(const Geom &g, int in_dtype)
 {
-    if (g.kh != 3 || g.kw != 3 || g.m <= kInlineRankPositions || (g.flags & FC_RESIDENT_WEIGHTS)) return false;
-    const int chunks = (g.c_in * (in_dtype == FC_FP8 ? 1 : 2) + 127) / 128;
+    const bool packed = taps_packed(g, in_dtype, true), k3 = g.kh == 3 && g.kw == 3;
+    if (g.kh * g.kw == 1 || (g.flags & FC_RESIDENT_WEIGHTS) || (!packed && (!k3 || g.m <= kInlineRankPositions))) return false;
+    const int stages = reduction_stages(g, in_dtype, packed);
     // (with a list these take the shared-halo loop, whose order of stages is another one)
-    if (g.sw == 1 && g.dw == 1 && g.wo >= 32 && chunks > 1) return false;
+    if (!packed && g.sw == 1 && g.dw == 1 && g.wo >= 32 && stages > 9) return false;
     const int64_t tiles = (int64_t)((g.m + 63) / 64) * ((g.c_out + 63) / 64);
-    return tiles <= kSplitGrid && tiles * 9 * chunks <= 20 * kSplitGrid;
+    return tiles <= kSplitGrid && tiles * stages <= 20 * kSplitGrid;
 }
 
 bool dense_layer_splits(const Geom &g, int in_dtype)
@@ -246,7 +259,7 @@ bool dense_layer_splits(const Geom &g, int in_dtype)
     // (asked for calls with split-K scratch only)
     const TileShape t = choose_tile(g, in_dtype, false, false, true);
     const int64_t tiles = (int64_t)((g.m + t.rows() - 1) / t.rows()) * ((g.c_out + t.cols() - 1) / t.cols());
-    const int stages = g.kh * g.kw * ((g.c_in * (in_dtype == FC_FP8 ? 1 : 2) + 127) / 128);
+    const int stages = reduction_stages(g, in_dtype, t.packed);
     return split_k_splits((int)tiles, kSplitGrid, stages, stages) > 1;
 }
 
@@ -287,12 +300,12 @@ bool conv_mfma_supported(const Geom &g, int in_dtype, int out_dtype)
     return hipSuccess;
 }
 
-template <int DT, typename TO, bool CMP, int TM, int TN, int WM, int WN, int TAPC, int NB, int MINW, int SL = 0, int NBW = 2, bool OWN = false>
+template <int DT, typename TO, bool CMP, int TM, int TN, int WM, int WN, int TAPC, int NB, int MINW, int SL = 0, int NBW = 2, bool OWN = false, bool PACK = false>
 static hipError_t launch_dma(const Geom &g, const void *x, const uint8_t *mask_in, const uint8_t *mask_out,
                              const void *w, const float *bias, const int32_t *idx, const int32_t *count,
                              void *out, float *partials, int32_t *tile_counters, hipStream_t s)
 {
-    auto kern = k_conv_dma<DT, TO, TM, TN, WM, WN, TAPC, NB, MINW, SL, NBW, CMP, OWN>;
+    auto kern = k_conv_dma<DT, TO, TM, TN, WM, WN, TAPC, NB, MINW, SL, NBW, CMP, OWN, PACK>;
     constexpr size_t lds = dma_lds_bytes<TM, TN, NB, SL, NBW>();
     static std::atomic<uint64_t> attr_devices{0};
     const hipError_t e = allow_lds(reinterpret_cast<const void *>(kern), lds, attr_devices);
@@ -326,33 +339,33 @@ static hipError_t launch_deep(const Geom &g, const void *x, const uint8_t *mask_
 
 #define FC_ARGS g, x, mask_in, mask_out, w, bias, idx, count, out, partials, tile_counters, s
 
-template <int DT, typename TO, int TAPC, bool CMP>
+template <int DT, typename TO, int TAPC, bool CMP, bool PACK>
 static hipError_t launch_tile(const Geom &g, const void *x, const uint8_t *mask_in, const uint8_t *mask_out,
                               const void *w, const float *bias, const int32_t *idx, const int32_t *count,
-                              void *out, float *partials, int32_t *tile_counters, hipStream_t s)
+                              void *out, float *partials, int32_t *tile_counters, hipStream_t s, TileShape::Kind kind)
 {
-    switch (choose_tile(g, DT, mask_in != nullptr, mask_in && !idx, partials != nullptr).kind) {
+    switch (kind) {
     case TileShape::own64:
-        if constexpr (TAPC == 9 && !CMP) return launch_dma<DT, TO, CMP, 64, 64, 2, 2, TAPC, 4, 2, 0, 2, true>(FC_ARGS);
+        if constexpr (TAPC != 1 && !CMP) return launch_dma<DT, TO, CMP, 64, 64, 2, 2, TAPC, 4, 2, 0, 2, true, PACK>(FC_ARGS);
         break;
     case TileShape::small64:
-        if constexpr (TAPC != 32) return launch_dma<DT, TO, CMP, 64, 64, 2, 2, TAPC, 4, 2>(FC_ARGS);
+        return launch_dma<DT, TO, CMP, 64, 64, 2, 2, TAPC, 4, 2, 0, 2, false, PACK>(FC_ARGS);
         break;
     case TileShape::line128:
-        if constexpr (TAPC == 9) return launch_dma<DT, TO, CMP, 128, 128, 2, 2, TAPC, 2, 2, 160, 2>(FC_ARGS);
+        if constexpr (TAPC == 9 && !PACK) return launch_dma<DT, TO, CMP, 128, 128, 2, 2, TAPC, 2, 2, 160, 2>(FC_ARGS);
         break;
     case TileShape::line64:
-        if constexpr (TAPC == 9) return launch_dma<DT, TO, CMP, 128, 64, 2, 2, TAPC, 3, 2, 160, 3>(FC_ARGS);
+        if constexpr (TAPC == 9 && !PACK) return launch_dma<DT, TO, CMP, 128, 64, 2, 2, TAPC, 3, 2, 160, 3>(FC_ARGS);
         break;
     case TileShape::deep:
-        if constexpr (TAPC != 32) return launch_deep<DT, TO, TAPC, CMP>(FC_ARGS);
+        if constexpr (TAPC != 32 && !PACK) return launch_deep<DT, TO, TAPC, CMP>(FC_ARGS);
         break;
     case TileShape::wide128:
-        return launch_dma<DT, TO, CMP, 128, 128, 2, 2, TAPC, (sizeof(TO) == 4 ? 3 : 2), 2>(FC_ARGS);
+        return launch_dma<DT, TO, CMP, 128, 128, 2, 2, TAPC, (sizeof(TO) == 4 ? 3 : 2), 2, 0, 2, false, PACK>(FC_ARGS);
     case TileShape::narrow64:
-        return launch_dma<DT, TO, CMP, 128, 64, 2, 2, TAPC, 2, 3>(FC_ARGS);
+        return launch_dma<DT, TO, CMP, 128, 64, 2, 2, TAPC, 2, 3, 0, 2, false, PACK>(FC_ARGS);
     case TileShape::tall64:
-        return launch_dma<DT, TO, CMP, 128, 64, 2, 2, TAPC, 3, 2>(FC_ARGS);
+        return launch_dma<DT, TO, CMP, 128, 64, 2, 2, TAPC, 3, 2, 0, 2, false, PACK>(FC_ARGS);
     }
     return hipErrorInvalidValue; // (a tile this kernel size has no instance of: choose_tile names none)
 }
@@ -365,9 +378,11 @@ static hipError_t launch_cmp(const Geom &g, const void *x, const uint8_t *mask_i
                             const void *w, const float *bias, const int32_t *idx, const int32_t *count,
                             void *out, float *partials, int32_t *tile_counters, hipStream_t s)
 {
-    if (g.kh == 1 && g.kw == 1) return launch_tile<DT, TO, 1, CMP>(FC_ARGS2);
-    if (g.kh == 3 && g.kw == 3) return launch_tile<DT, TO, 9, CMP>(FC_ARGS2);
-    return launch_tile<DT, TO, 32, CMP>(FC_ARGS2);
+    const TileShape t = choose_tile(g, DT, mask_in != nullptr, mask_in && !idx, partials != nullptr);
+    if (g.kh == 1 && g.kw == 1) return launch_tile<DT, TO, 1, CMP, false>(FC_ARGS2, t.kind);
+    if (g.kh == 3 && g.kw == 3)
+        return t.packed ? launch_tile<DT, TO, 9, CMP, true>(FC_ARGS2, t.kind) : launch_tile<DT, TO, 9, CMP, false>(FC_ARGS2, t.kind);
+    return t.packed ? launch_tile<DT, TO, 32, CMP, true>(FC_ARGS2, t.kind) : launch_tile<DT, TO, 32, CMP, false>(FC_ARGS2, t.kind);
 }
 
 // The instances of one storage type, with or without compacted activations.

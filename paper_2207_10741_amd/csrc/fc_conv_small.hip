@@ -723,7 +723,14 @@ bool conv_small_wanted(const Geom &g, int in_dtype, bool room, bool needs_labels
     // 3x3: what the tiled kernel would run on 64 x 64 tiles, while a CU gets no more than about four waves
     // (512 -> 512 on 8 x 7 x 7, 1 872 waves, is 14.8 us there and 24.6 us here)
     if (taps == 9 && ((int64_t)((g.m + 127) / 128) * ((g.c_out + 63) / 64) > kSmallLayerTiles || tiles * splits > 1024)) return false;
-    if (taps != 9 && tiles > 1024) return false;
+    // Packed reductions without a list: tiles that label their own rows take fewer stages (3x3 where nothing is split here, so that the sums are the same: 16 ->
+    // 64 on 28 x 28 7.6 -> 5.2 us, 40 -> 96 7.6 -> 6.1; with splits there is little in it, 72 -> 200 8.3 -> 8.0, 136 -> 136 on 56 x 56 / 2 8.5 -> 8.6).  Other kernels label and gate more taps there: 24 ->
+    // 128, 5x5, on 56 x 56 (1 568 waves, 10 stages) 15.6 -> 10.3, 40 -> 96 (1 176, 16) 9.9 -> 11.8; 136 -> 136 (1 960, 54) 25.6 -> 22.1, 80 -> 80 (1 176, 32) 12.3 -> 16.4.
+    // Unpacked 64 -> 64, 5x5, on 4 x 48 x 60 (2 880) 21.5 -> 19.6, 192 -> 192 on 56 x 56 (2 352) 27.2 -> 27.9, 128 -> 32 on 4 x 48 x 60 (1 440) 20.3 -> 24.8.
+    const bool own_tiles = needs_labels && taps_packed(g, in_dtype, true) && tiles_label_rows(g, in_dtype);
+    const int own_stages = reduction_stages(g, in_dtype, true);
+    if (taps == 9 && own_tiles && splits == 1) return false;
+    if (taps != 9 && (tiles > 1024 || tiles * splits > (own_tiles ? (own_stages <= 16 ? 1200 : 1500) : 2560))) return false;
     return !needs_labels || splits == small_splits(g.m, g.c_out, total, taps, room);
 }
 

@@ -393,10 +393,30 @@ __host__ __device__ static inline int split_k_splits(int ntiles, int grid, int w
     return s;
 }
 constexpr int kSmallLayerTiles = 64;   // layers with at most this many 128 x 64 tiles use small tiles
-static inline bool split_k_reachable(const Geom &g, int in_dtype)
+// Does the tiled kernel take a reduction as one run of 16-byte pieces, eight a stage whatever tap they belong to, instead of tap by tap in whole
+// stages?  Where that leaves at most three quarters of the stages: 9 x 72 channels are 11 stages instead of 18, 9 x 16 are 3 instead of 9.
+static inline int reduction_stages(const Geom &g, int in_dtype, bool packed)
 {
-    const int64_t row = (int64_t)g.c_in * (in_dtype == FC_FP8 ? 1 : 2);
-    return split_k_possible(g) && (int64_t)g.kh * g.kw * ((row + 127) / 128) >= 2 * kMinSplitStages;
+    const int row = g.c_in * (in_dtype == FC_FP8 ? 1 : 2);
+    return packed ? (g.kh * g.kw * row + 127) / 128 : g.kh * g.kw * ((row + 127) / 128);
+}
+// us, tap by tap or on the shared line -> packed, half kept, list given unless said: 72 -> 200 3x3 / 2 on 3 x 75 x 101, mask only, 12.8 -> 10.1, on 4 x 48 x 60
+// 17.2 -> 8.2; 16 -> 64 on 16 x 60 x 80, mask only, 15.6 -> 12.4, 5x5 29.5 -> 20.7; 24 -> 128 on 32 x 60 x 80 23.3 -> 17.9, without a mask 32.9 -> 23.9; 72 -> 128 there
+// 35.4 -> 32.8, 52.3 -> 47.2; 72 -> 200, 5x5, on 16 x 60 x 80, mask only, 99 -> 70; E4M3 48 -> 80 on 8 x 60 x 80 11.6 -> 9.6.
+// On the shared line a stage costs less: where its half-kept tiles are more than one and fewer than two a CU it stays (72 -> 128 on 4 / 6 / 8 / 12 / 20 x 60 x 80 12.8 /
+// 13.4 / 14.9 / 17.3 / 23.2 -> 9.9 / 10.5 / 15.9 / 16.1 / 19.5, mask only 15.0 / 15.8 / 18.8 / 21.2 / 27.6 -> 12.9 / 13.6 / 19.2 / 19.7 / 23.0; 136 -> 128 15.7 / 17.0 / 20.6 / 22.7 / 31.5 -> 14.5 /
+// 16.3 / 20.8 / 24.1 / 29.7), and without a mask where more than two thirds of the stages are left (136 -> 128 on 8 / 12 x 60 x 80 30.1 / 37.5 -> 30.4 / 40.2).
+static inline bool taps_packed(const Geom &g, int in_dtype, bool masked)
+{
+    const int stages = reduction_stages(g, in_dtype, true), whole = reduction_stages(g, in_dtype, false);
+    if (g.kh * g.kw == 1 || 4 * stages > 3 * whole) return false;
+    const int64_t tiles64 = (int64_t)((g.m + 127) / 128) * ((g.c_out + 63) / 64);
+    const bool line = g.kh == 3 && g.kw == 3 && g.sw == 1 && g.dw == 1 && g.wo >= 32 && g.c_out > 64 && tiles64 >= kSplitGrid;
+    return !line || (masked ? tiles64 >= (stages > 16 ? 1000 : 768) : 3 * stages <= 2 * whole);
+}
+static inline bool split_k_reachable(const Geom &g, int in_dtype, bool masked)
+{
+    return split_k_possible(g) && reduction_stages(g, in_dtype, taps_packed(g, in_dtype, masked)) >= 2 * kMinSplitStages;
 }
 static inline size_t split_k_counter_bytes(const Geom &g) { return split_k_possible(g) ? align_up(kSplitGrid * sizeof(int32_t), 256) : 0; }
 static inline size_t split_k_partial_bytes(const Geom &g)
