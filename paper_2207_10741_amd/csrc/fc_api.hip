@@ -71,12 +71,15 @@ int32_t make_geom(const fc_conv_desc *d, Geom *g)
 // tiled kernel at a kept share of one half).  With the zero-fill in the launch the tiled kernel
 // stays: its idle workgroups clear rows beside the tiles, while a launch that keeps every CU
 // busy can only clear them after its tiles (measured: no gain at one half, slower elsewhere).
-// Layers small enough to rank their rows inside the tiled kernel stay there as well, whether
-// or not the caller brings a list (one kernel, one summation order per layer).
+// Smaller layers leave most workgroups here with a block or two a wave, and the tiled kernel's tiles are one round: chained, list given, us at
+// 0.1 / 0.3 / 0.5 / 0.7 / 0.9 kept, here -> tiled: 128 -> 128 on 8 x 28 x 28 13.2 / 13.3 / 13.4 / 13.4 / 13.5 -> 11.3 / 11.4 / 11.8 / 12.3 / 12.8, on 4 x 60 x 80 13.3 /
+// 13.5 / 14.0 / 14.6 / 15.4 -> 11.1 / 11.9 / 11.3 / 11.7 / 14.4, on 8 x 60 x 80 13.5 / 14.3 / 15.9 / 17.6 / 19.6 -> 11.5 / 11.4 / 15.0 / 15.7 / 23.1, 256 -> 128 on 4 x 60 x 80 19.7 / 20.1 /
+// 21.0 / 21.9 / 23.9 -> 12.2 / 16.9 / 16.9 / 17.7 / 22.4; 128 -> 128 on 12 x 60 x 80 13.8 / 15.8 / 17.9 / 20.6 / 23.4 -> 12.4 / 14.9 / 16.5 / 23.7 / 27.8, on 16 x 64 x 64 13.9 / 16.0 /
+// 19.6 / 22.4 / 25.7 -> 15.0 / 16.9 / 21.4 / 22.6 / 25.1; image rows too short for the tiled kernel's pixel line, 32 x 28 x 28 13.5 / 14.0 / 14.6 / 15.8 / 16.4 -> 11.7 / 13.6 / 13.9 / 17.3 / 17.8.
 bool conv_line_wanted(const Geom &g, int in_dtype, int out_dtype, bool focused)
 {
     if (!focused || !(g.flags & FC_SKIP_ZERO_FILL) || !conv_line_supported(g, in_dtype, out_dtype)) return false;
-    if (g.m <= kInlineRankPositions) return false;
+    if (g.m < (g.wo >= 32 ? 44000 : 20000)) return false;
     if (g.c_out <= 64 || g.c_out > 128 || taps_packed(g, in_dtype, focused)) return false;
     return (int64_t)(g.m + 31) / 32 <= 8 * 256;
 }
@@ -160,6 +163,8 @@ bool conv_pw_wanted(const Geom &g, int in_dtype, int out_dtype, bool masked)
 // Without a mask 256 -> 256 on 32 x 30 x 40 (600) 53 -> 44, on 16 x 32 x 32 (256) 24 -> 28.  Masks without regions (positions dropped one by one at
 // random, same shares, zero-filled): 512 channels 47 / 55 / 112 / 122 / 144 -> 47 / 65 / 87 / 98 / 120, 256 on 128 x 32 x 32 31 / 62 / 79 / 111 / 145 -> 31 / 52 / 69 / 96 / 117, on
 // 16 x 60 x 80 26 / 33 / 62 / 72 / 91 -> 29 / 38 / 50 / 62 / 80, 128 35 / 61 / 102 / 130 / 149 -> 36 / 63 / 93 / 123 / 146.
+// Rows in list order (FC_COMPACT_OUT): 128 -> 128 on 32 x 60 x 80 16.0 / 22.8 / 34.6 / 42.2 / 52.5 -> 16.4 / 23.0 / 30.2 / 41.8 / 49.6, 256 -> 256 there 28.7 / 60 / 92 / 122 / 150 ->
+// 30.2 / 52 / 86 / 109 / 137.
 // Other channel counts stay: 384 channels are three tiles of 128, each of which reads the rows again (256 -> 384 on 16 x 60 x 80
 // zero-filled 76 -> 102).
 bool conv_wide_wanted(const Geom &g, int in_dtype, int out_dtype, bool masked)

@@ -209,7 +209,7 @@ void k_conv_wide(Geom g, WideArgs wa, const unsigned char *__restrict__ x, const
             const int lead = live && !ladj && !(prev == sp - 2 && sow > 1), cnt = tid < k * GR ? 1 + lead + (live && !radj) : 0;
             const int incl = wave_inclusive_scan(cnt);
             if (lane == 63) scan_part[wave] = incl;
-            if (tid < TM) row_p[tid] = sp;
+            if (tid < TM) row_p[tid] = live && (g.flags & FC_COMPACT_OUT) ? m : sp; // where the row goes
             const int z0 = clear_in_loop ? min(zt0 + (g0 - x0) * zq, zx1) : 0;
             const int zl = clear_in_loop ? min(k * zq, zx1 - z0) : 0; // positions this tile clears
             {
@@ -580,7 +580,7 @@ bool conv_wide_supported(const Geom &g, int in_dtype, int out_dtype)
     const int es = in_dtype == FC_FP8 ? 1 : 2;
     if (!(g.kh == 3 && g.kw == 3 && g.sw == 1 && g.dw == 1) || g.c_out % 128 != 0) return false;
     if ((g.c_in * es) % 128 != 0) return false; // whole chunks
-    return !(g.flags & (FC_COMPACT_IN | FC_COMPACT_OUT));
+    return !(g.flags & FC_COMPACT_IN);
 }
 #endif
 
