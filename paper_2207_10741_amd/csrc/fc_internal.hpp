@@ -296,11 +296,6 @@ struct LabelMap {
     FastDiv div_w, div_h;
     uint8_t *mask_out;             // the labels, or NULL
     int32_t *idx, *count;
-    // set by launch_lists.  pieces: 16-byte pieces of a row that hold its positions' bytes, 0 where positions are not `col.mul` bytes
-    // apart in a byte mask (a divisor of 16), per: positions of a piece, sel: their bytes in words 0, 1 and 3, 2 of a piece
-    int32_t pieces, per, rows_in; // rows_in: rows of the whole input mask
-    uint32_t sel, sel_odd, sel_rest;
-    FastDiv div_pieces;
 };
 template <int NL> struct ListArgs {
     int32_t lists, blocks;

@@ -108,12 +108,14 @@ hipError_t launch_mask_window(const uint8_t *mask_in, int n, int h, int w, int k
 constexpr int kListThreads = 1024; // of a workgroup whose lanes take four positions
 constexpr int kListWaves = kListThreads / 64;
 template <int PER> constexpr int kThreadsOf = kCompactBlockElems / PER;
-// 16-byte reads of a list's last workgroup up to which one launch serves all lists, and up to which its workgroups have 256 threads
+// 16-byte reads of a list's last workgroup (off their alignment they count twice) up to which one launch serves all lists, and up to which its workgroups have 256 threads
 // (kOnceBlocks: where a list has to be labelled position by position).  One launch after another, bytes, us, two launches or one of 1024
 // threads that labels the positions before its own one by one -> here: four levels of 224 x 224 (3 136 reads) 5.8 -> 4.2, 251 x 333 (5 224) 6.3 -> 5.4, 2 x 224 x 224
 // (6 272) 6.5 -> 5.2, 8 x 131 x 127 6.4 -> 5.1, 4 x 224 x 224 (12 544) 6.7 -> 6.6, 16 x 128 x 128 (16 384) 7.3 -> 6.5.  With 256 threads the last three take 5.7, 6.0, 8.0 and
 // 9.5; 160 x 160 takes 3.4 with them and 4.1 with 1024.  Past 16 384 the counting alone is what the second launch costs.
-constexpr int kOncePieces = 16384, kBriefPieces = 4096, kOnceBlocks = 4;
+// Through a stride less: a list and the layer behind it, two launches -> one: 12 x 112 x 112 / 2 (4 704 reads) 11.7 -> 10.8, 10 x 130 x 130 / 2 (11 700)
+// 12.2 -> 13.6, 14 x 105 x 131 / 2 (13 356) 12.2 -> 14.0.
+constexpr int kOncePieces = 16384, kOncePiecesStepped = 10000, kBriefPieces = 4096, kOnceBlocks = 4;
 // Workgroups of a list at the mask's resolution from which on a lane takes sixteen positions: there the labels of
 // sixteen are one load as those of four are, and what such a list costs is instructions per lane.  Four -> sixteen, a list
 // alone / a pyramid of four levels: 1.6 M positions 10.1 -> 9.9 / 12.4 -> 12.4 us, 2.1 M 10.1 -> 10.0 / 13.9 -> 12.8, 5.2 M
@@ -269,10 +271,21 @@ __device__ __forceinline__ int store_list(const LabelMap &L, int p0, uint32_t f,
 // sum + nonzero bytes of v (the masked byte differences of v ^ 1 and v: one for every byte that is not zero)
 __device__ __forceinline__ uint32_t add_nonzero(uint32_t v, uint32_t sum) { return __builtin_amdgcn_msad_u8(v ^ 0x01010101u, v, sum); }
 
+// How a list steps through a byte mask, for the one-launch form.  pieces: 16-byte pieces of a row that hold its positions' bytes, 0 where positions
+// are not `col.mul` bytes apart (a divisor of 16), per: positions of a piece, sel: their bytes in words 0, 1 and 3, 2 of a piece
+struct RowPieces {
+    int32_t pieces, per, rows_in; // rows_in: rows of the whole input mask
+    uint32_t sel, sel_odd, sel_rest;
+    FastDiv div_pieces;
+};
+template <int NL> struct RowPiecesArgs {
+    RowPieces at[NL];
+};
+
 // Kept positions among the first `before` of a list, this lane's share of them (the workgroup's lanes share all): 16 bytes a load, B loads in
 // flight.  A row of a list that steps through the mask is read by pieces that start at its first position's byte.
 template <int THREADS, int B>
-__device__ __forceinline__ int kept_before(const LabelMap &L, const uint8_t *__restrict__ mask_in, int before)
+__device__ __forceinline__ int kept_before(const LabelMap &L, const RowPieces &P, const uint8_t *__restrict__ mask_in, int before)
 {
     uint32_t part = 0;
     if (L.identity) {
@@ -288,16 +301,16 @@ __device__ __forceinline__ int kept_before(const LabelMap &L, const uint8_t *__r
         return part;
     }
     const int full = (int)fast_div((uint32_t)before, L.div_w), rest = before - full * L.wl; // whole rows, positions of the next
-    const int pieces = full * L.pieces + (rest ? L.pieces : 0), bytes = L.rows_in * L.w0;
+    const int pieces = full * P.pieces + (rest ? P.pieces : 0), bytes = P.rows_in * L.w0;
     for (int i0 = threadIdx.x; i0 < pieces; i0 += B * THREADS) {
         uint4 v[B];
         int n[B]; // positions of the piece that count
 #pragma unroll
         for (int k = 0; k < B; ++k) {
             const int i = i0 + k * THREADS;
-            const int r = (int)fast_div((uint32_t)i, L.div_pieces), q = i - r * L.pieces;
+            const int r = (int)fast_div((uint32_t)i, P.div_pieces), q = i - r * P.pieces;
             const int b = (int)fast_div((uint32_t)r, L.div_h), oh = r - b * L.hl;
-            n[k] = i < pieces ? min((r < full ? L.wl : rest) - q * L.per, L.per) : 0;
+            n[k] = i < pieces ? min((r < full ? L.wl : rest) - q * P.per, P.per) : 0;
             const int ih = min(max(oh * L.row.mul + L.row.add, L.row.lo), L.row.hi);
             const int at = (b * L.h0 + ih) * L.w0 + L.col.add + q * 16;
             v[k] = make_uint4(0, 0, 0, 0);
@@ -312,9 +325,9 @@ __device__ __forceinline__ int kept_before(const LabelMap &L, const uint8_t *__r
         }
 #pragma unroll
         for (int k = 0; k < B; ++k) {
-            uint32_t f[4] = {v[k].x & L.sel, v[k].y & L.sel_odd, v[k].z & L.sel_rest, v[k].w & L.sel_odd};
+            uint32_t f[4] = {v[k].x & P.sel, v[k].y & P.sel_odd, v[k].z & P.sel_rest, v[k].w & P.sel_odd};
             const int end = n[k] * L.col.mul; // bytes of it
-            if (n[k] < L.per)
+            if (n[k] < P.per)
 #pragma unroll
                 for (int j = 0; j < 4; ++j) f[j] &= end >= 4 * j + 4 ? ~0u : (end > 4 * j ? (1u << (8 * (end - 4 * j))) - 1u : 0u);
 #pragma unroll
@@ -346,20 +359,21 @@ __device__ __forceinline__ uint32_t labels_stepped(const LabelMap &L, const uint
 // the masks of an image, whose waves have a SIMD each, 1024 for longer ones, so that the last workgroups' counting
 // has enough loads on its way.
 template <int NL, int THREADS>
-__global__ __launch_bounds__(THREADS) void k_lists_once(ListArgs<NL> a, const uint8_t *__restrict__ mask_in)
+__global__ __launch_bounds__(THREADS) void k_lists_once(ListArgs<NL> a, RowPiecesArgs<NL> by_row, const uint8_t *__restrict__ mask_in)
 {
     constexpr int W = THREADS / 64, ELEMS = THREADS * 4;
     __shared__ int wave_sum[2 * W];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const LabelMap &L = a.at[NL == 1 ? 0 : blockIdx.y];
+    const RowPieces &P = by_row.at[NL == 1 ? 0 : blockIdx.y];
     const int before = blockIdx.x * ELEMS, p0 = before + tid * 4;
     if (before >= L.m) return;
     const bool vec = a.vec_in != 0;
     uint32_t f;
     int part = 0;
-    if (L.identity ? vec && !L.packed_in : L.pieces > 0) {
+    if (L.identity ? vec && !L.packed_in : P.pieces > 0) {
         f = L.identity ? labels<4>(L, mask_in, p0, vec) : labels_stepped(L, mask_in, p0);
-        part = kept_before<THREADS, 4>(L, mask_in, before);
+        part = kept_before<THREADS, 4>(L, P, mask_in, before);
     } else {
         f = labels<4>(L, mask_in, p0, vec);
         for (int b0 = 0; b0 < (int)blockIdx.x; b0 += 4) {
@@ -448,49 +462,54 @@ __global__ __launch_bounds__(kThreadsOf<PER>) void k_lists_scatter(ListArgs<NL> 
 }
 
 // Are the bytes of a list's positions col.mul apart along a row, so that 16-byte pieces hold 16 / col.mul of them each?
-static void set_pieces(LabelMap &L, bool vec)
+static RowPieces row_pieces(const LabelMap &L)
 {
-    L.pieces = 0;
-    L.rows_in = 0;
+    RowPieces P = {};
     const int mul = L.col.mul;
-    if (L.identity || L.packed_in || (mul != 1 && mul != 2 && mul != 4 && mul != 8 && mul != 16) || L.wl < 4 || L.col.add < 0) return;
-    if ((int64_t)(L.wl - 1) * mul + L.col.add > L.w0 - 1 || L.col.lo > 0 + L.col.add || L.col.hi < (L.wl - 1) * mul + L.col.add) return;
-    L.per = 16 / mul;
-    L.pieces = (L.wl + L.per - 1) / L.per;
-    L.div_pieces = make_fastdiv((uint32_t)L.pieces);
-    L.rows_in = (int32_t)((int64_t)L.m / ((int64_t)L.hl * L.wl) * L.h0);
-    L.sel = mul == 1 ? 0xffffffffu : (mul == 2 ? 0x00ff00ffu : 0x000000ffu);
-    L.sel_odd = mul <= 4 ? L.sel : 0u;
-    L.sel_rest = mul <= 8 ? L.sel : 0u;
+    if (L.identity || L.packed_in || (mul != 1 && mul != 2 && mul != 4 && mul != 8 && mul != 16) || L.wl < 4 || L.col.add < 0) return P;
+    if ((int64_t)(L.wl - 1) * mul + L.col.add > L.w0 - 1 || L.col.lo > 0 + L.col.add || L.col.hi < (L.wl - 1) * mul + L.col.add) return P;
+    P.per = 16 / mul;
+    P.pieces = (L.wl + P.per - 1) / P.per;
+    P.div_pieces = make_fastdiv((uint32_t)P.pieces);
+    P.rows_in = (int32_t)((int64_t)L.m / ((int64_t)L.hl * L.wl) * L.h0);
+    P.sel = mul == 1 ? 0xffffffffu : (mul == 2 ? 0x00ff00ffu : 0x000000ffu);
+    P.sel_odd = mul <= 4 ? P.sel : 0u;
+    P.sel_rest = mul <= 8 ? P.sel : 0u;
+    return P;
 }
 
 template <int NL>
 static hipError_t launch_lists_n(const ListArgs<NL> &a, const uint8_t *mask_in, int32_t *block_counts, hipStream_t s)
 {
-    ListArgs<NL> b = a;
-    bool once = true, brief = true, longer = false;
+    bool longer = false;
     int64_t most = 0;
     for (int l = 0; l < a.lists; ++l) {
-        LabelMap &L = b.at[l];
-        set_pieces(L, a.vec_in != 0);
-        const bool fast = L.identity && a.vec_in && !L.packed_in;
-        longer = longer || ((fast || (L.identity && L.packed_in)) && compact_blocks(L.m) > kLongBlocks);
-        const int64_t rows = ((int64_t)L.m + L.wl - 1) / L.wl, reads = fast ? ((int64_t)L.m + 15) / 16 : rows * L.pieces;
-        if (fast || L.pieces > 0) {
-            once = once && reads <= kOncePieces;
-            brief = brief && reads <= kBriefPieces;
-        } else {
-            once = once && compact_blocks(L.m) <= kOnceBlocks;
-            brief = brief && L.m <= 1024;
-        }
+        const LabelMap &L = a.at[l];
+        longer = longer || (L.identity && (a.vec_in || L.packed_in) && compact_blocks(L.m) > kLongBlocks);
         most = L.m > most ? L.m : most;
     }
+    bool once = most <= 16 * (int64_t)kOncePieces, brief = true; // (a read holds sixteen positions at most)
+    RowPiecesArgs<NL> by_row;
+    for (int l = 0; once && l < a.lists; ++l) {
+        const LabelMap &L = a.at[l];
+        const RowPieces &P = by_row.at[l] = row_pieces(L);
+        const bool fast = L.identity && a.vec_in && !L.packed_in;
+        const int64_t rows = ((int64_t)L.m + L.wl - 1) / L.wl;
+        const int64_t reads = fast ? ((int64_t)L.m + 15) / 16 : rows * P.pieces * (L.w0 % 16 || L.col.add % 16 ? 2 : 1);
+        if (fast || P.pieces > 0) {
+            once = reads <= (fast ? kOncePieces : kOncePiecesStepped);
+            brief = brief && reads <= kBriefPieces;
+        } else {
+            once = compact_blocks(L.m) <= kOnceBlocks;
+            brief = brief && L.m <= 1024;
+        }
+    }
     if (once && brief) {
-        hipLaunchKernelGGL((k_lists_once<NL, 256>), dim3((unsigned)((most + 1023) / 1024), a.lists), dim3(256), 0, s, b, mask_in);
+        hipLaunchKernelGGL((k_lists_once<NL, 256>), dim3((unsigned)((most + 1023) / 1024), a.lists), dim3(256), 0, s, a, by_row, mask_in);
         return hipGetLastError();
     }
     if (once) {
-        hipLaunchKernelGGL((k_lists_once<NL, kListThreads>), dim3((unsigned)compact_blocks(most), a.lists), dim3(kListThreads), 0, s, b, mask_in);
+        hipLaunchKernelGGL((k_lists_once<NL, kListThreads>), dim3((unsigned)compact_blocks(most), a.lists), dim3(kListThreads), 0, s, a, by_row, mask_in);
         return hipGetLastError();
     }
     const int threads = longer ? kThreadsOf<16> : kThreadsOf<4>;
@@ -510,7 +529,16 @@ hipError_t launch_lists(const ListArgs<1> &a, const uint8_t *mask_in, int32_t *b
 
 hipError_t launch_lists(const ListArgs<kMaxPyramidLevels> &a, const uint8_t *mask_in, int32_t *block_counts, hipStream_t s)
 {
-    return launch_lists_n(a, mask_in, block_counts, s);
+    // (few pyramids have more: fewer arguments to hand over)
+    constexpr int kFew = 5;
+    if (a.lists > kFew) return launch_lists_n(a, mask_in, block_counts, s);
+    ListArgs<kFew> few;
+    few.lists = a.lists;
+    few.blocks = a.blocks;
+    few.vec_in = a.vec_in;
+    few.ex = a.ex;
+    for (int l = 0; l < a.lists; ++l) few.at[l] = a.at[l];
+    return launch_lists_n(few, mask_in, block_counts, s);
 }
 
 static int32_t to_int32(int64_t v)

@@ -21,8 +21,13 @@ PYRAMIDS = [
     (1, 150, 210, (((3, 3), (1, 3), (1, 1), (1, 1)), S2)),       # a step of 3: position by position
     (1, 90, 100, (((5, 5), (2, 2), (4, 4), (2, 2)), S2)),        # centre taps clamped at the border
     (5, 126, 130, (S1, S2, S2)),                                 # 1 024 threads
-    (7, 188, 199, (S1, S2, S2)),                                 # just inside one launch
+    (8, 130, 131, (S1, S2, S2)),                                 # just inside one launch (through the stride, rows off the pieces)
+    (9, 130, 131, (S1, S2, S2)),                                 # just outside
+    (5, 208, 244, (S1, ((1, 1), (16, 16), (0, 0), (1, 1)))),     # just inside at the mask's resolution
+    (7, 188, 199, (S1,)),
     (8, 181, 182, (S1, S2)),                                     # just outside
+    (2, 120, 180, (S1, S2, S2, S2, S2)),                         # five levels
+    (2, 120, 180, (S1, S2, S2, S2, S2, S2)),                     # six
 ]
 
 
