@@ -48,9 +48,12 @@ class _Plan:
         calls = []
         self.dtype = B.torch_dtype(stack.dtype)
         self.levels = [(i, stack._level_of[i] if masked else -1) for i in range(n)]
-        params = []         # (op, slot of its weights, slot of its bias)
-        self.returned, arena_ops = [], []
-        for i, op in enumerate(ops):
+        params = []         # (place in the order, op, slot of its weights, slot of its bias)
+        self.returned, arena_ops, arena_slots = [], [], []
+        self.order = _order(ops, readers)
+        place = {i: at for at, i in enumerate(self.order)}
+        for at, i in enumerate(self.order):
+            op = ops[i]
             ho, wo = stack.sizes[i]
             shape = (stack.n, ho, wo, op.c_out)
             m_in = m_out = idx = count = -1
@@ -78,7 +81,7 @@ class _Plan:
                     compacted.add(i)
                     shape = (stack.n * ho * wo, op.c_out)
                 w, b = slot(), slot()
-                params.append((i, w, b))
+                params.append((at, i, w, b))
                 if op.kind == "dwconv":
                     # labels come from the input mask inside the call: no list, no workspace
                     calls.append(B.Call(stack.desc(i, flags_extra=extra), B.CALL_DWCONV, src, m_in, w, b, -1, -1, -1,
@@ -89,11 +92,13 @@ class _Plan:
             if keep_outputs or i == n - 1:
                 self.returned.append((i, out_slot[i], shape))
             else:
-                arena_ops.append((i, max(readers.get(i, [i])), int(np.prod(shape)) * self.dtype.itemsize))
+                arena_ops.append((at, max(place[j] for j in readers.get(i, [i])), int(np.prod(shape)) * self.dtype.itemsize))
+                arena_slots.append(out_slot[i])
+        self.returned.sort()
         # the pass is enqueued in two parts: the device runs the first layers while the host fills in the others' slots
         # (MobileNetV2's 104 tensors take it tens of microseconds)
         cut = min(HEAD_CALLS, n)
-        self.parts = [([q for q in params if lo <= q[0] < hi], (B.Call * (hi - lo))(*calls[lo:hi]))
+        self.parts = [([q[1:] for q in params if lo <= q[0] < hi], (B.Call * (hi - lo))(*calls[lo:hi]))
                       for lo, hi in ((0, cut), (cut, n)) if hi > lo]
         self.slots = ctypes.c_void_p * n_slots
         # A range is given out again some ops after its tensor's last reader while the arena stays inside the
@@ -105,7 +110,20 @@ class _Plan:
             offsets, self.arena_bytes = _place(arena_ops, rest)
             if self.arena_bytes <= ARENA_CACHED:
                 break
-        self.in_arena = [(out_slot[i], at) for (i, _, _), at in zip(arena_ops, offsets)]
+        self.in_arena = list(zip(arena_slots, offsets))
+
+
+def _order(ops, readers):
+    """The order the ops are enqueued in: their own, but an op that nobody reads (a block's projection; not the last op) directly
+    after the op it reads.  Later it would stand between a block's last layer and its reader and put its own output between
+    them in the last cache level (ResNet-50, 32 frames of 120 x 160: the 256 -> 64 layer behind it 60 -> 49 us, a chained pass 1667 -> 1639, E4M3
+    1093 -> 1055)."""
+    n = len(ops)
+    early = [i for i in range(n - 1) if not readers.get(i)]
+    order = [i for i in range(n) if i not in early]
+    for i in reversed(early):
+        order.insert(order.index(ops[i].src) + 1 if ops[i].src >= 0 else 0, i)
+    return order
 
 
 def _place(tensors, rest: int):

@@ -42,6 +42,24 @@ def test_arena_of_a_chain_reuses_its_ranges():
     assert stacks._place([], 0) == ([], 0)
 
 
+@pytest.mark.parametrize("net", ["resnet18", "resnet50_bottlenecks", "vgg16", "mobilenetv2"])
+def test_ops_follow_what_they_read_and_unread_ones_follow_at_once(net):
+    ops = getattr(workloads, net)()
+    readers = {}
+    for j, op in enumerate(ops):
+        readers.setdefault(op.src, []).append(j)
+    order = stacks._order(ops, readers)
+    assert sorted(order) == list(range(len(ops))) and order[-1] == len(ops) - 1
+    at = {i: k for k, i in enumerate(order)}
+    at[-1] = -1
+    for i, op in enumerate(ops):
+        assert at[i] > at[op.src]
+        if not readers.get(i) and i < len(ops) - 1:
+            assert at[i] == at[op.src] + 1
+    kept = [i for i in range(len(ops)) if readers.get(i)]
+    assert [i for i in order if i in kept] == kept          # the others keep their order
+
+
 @pytest.mark.parametrize("keep", [False, True])
 @pytest.mark.parametrize("compact", [False, True])
 def test_rows_nobody_can_see_stay_unwritten(keep, compact):
@@ -61,7 +79,7 @@ def test_rows_nobody_can_see_stay_unwritten(keep, compact):
     assert returned == (set(range(len(stack.ops))) if keep else {len(stack.ops) - 1})
     alone = [i for i in range(len(stack.ops)) if i not in read]
     assert len(alone) == 5                                   # the four projections and the last layer
-    for i, call in enumerate(calls):
+    for i, call in zip(plan.order, calls):
         skipped = bool(call.desc.flags & B.SKIP_ZERO_FILL)
         assert skipped == (i in read or i not in returned)
         if i not in read:
