@@ -319,9 +319,14 @@
                     sin_[i] = inb;
                     spix_[i] = inb ? slot_pix[s2] + kh_i * g.dh * g.w : 0;
                 }
-                uint8_t smv[SIT];
+                uint32_t smv[SIT];
 #pragma unroll
-                for (int i = 0; i < SIT; ++i) smv[i] = mask_in ? (uint8_t)mask_at(mask_in, spix_[i], packed_masks) : (uint8_t)1;
+                for (int i = 0; i < SIT; ++i) smv[i] = 1u;
+                if (mask_in) {
+#pragma unroll
+                    for (int i = 0; i < SIT; ++i) smv[i] = mask_at(mask_in, spix_[i], packed_masks);
+                    loaded_together(smv);
+                }
 #pragma unroll
                 for (int i = 0; i < SIT; ++i)
                     if (sin_[i] && smv[i]) atomicOr(&slot_bits[ssl_[i]], 1u << skh_[i]);
@@ -353,9 +358,14 @@
                 pin_[i] = inb;
                 ppix_[i] = inb ? (row_img[rr] * g.h + ih) * g.w + iw : 0;
             }
-            uint8_t mv[PAIR_CH];
+            uint32_t mv[PAIR_CH];
 #pragma unroll
-            for (int i = 0; i < PAIR_CH; ++i) mv[i] = mask_in ? (uint8_t)mask_at(mask_in, ppix_[i], packed_masks) : (uint8_t)1;
+            for (int i = 0; i < PAIR_CH; ++i) mv[i] = 1u;
+            if (mask_in) {
+#pragma unroll
+                for (int i = 0; i < PAIR_CH; ++i) mv[i] = mask_at(mask_in, ppix_[i], packed_masks);
+                loaded_together(mv);
+            }
 #pragma unroll
             for (int i = 0; i < PAIR_CH; ++i)
                 if (pin_[i] && mv[i]) atomicOr(&row_bits[prow_[i]], 1u << ptap_[i]);

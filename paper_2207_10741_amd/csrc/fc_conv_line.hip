@@ -423,15 +423,20 @@ __global__ __launch_bounds__(kLineThreads, MINW) void k_conv_line(Geom g, LineDi
                     const int pix = slot_pix[sl];
                     const int ih0 = (int)(int16_t)(hw & 0xffff), iw0 = hw >> 16;
                     bool inb[NQ];
-                    uint8_t mv[NQ];
+                    uint32_t mv[NQ];
+                    int px[NQ];
 #pragma unroll
                     for (int q = 0; q < NQ; ++q) {
                         const int kh_i = NQ == 3 ? q : q / KW, kw_i = NQ == 3 ? 0 : q - (q / KW) * KW;
                         const int ih = ih0 + kh_i * g.dh, iw = iw0 + kw_i * g.dw;
                         inb[q] = ih >= 0 && ih < g.h && iw >= 0 && iw < g.w;
-                        mv[q] = mask_in
-                                    ? (uint8_t)mask_at(mask_in, inb[q] ? pix + kh_i * g.dh * g.w + kw_i * g.dw : 0, packed_masks)
-                                    : (uint8_t)1;
+                        px[q] = inb[q] ? pix + kh_i * g.dh * g.w + kw_i * g.dw : 0;
+                        mv[q] = 1u;
+                    }
+                    if (mask_in) {
+#pragma unroll
+                        for (int q = 0; q < NQ; ++q) mv[q] = mask_at(mask_in, px[q], packed_masks);
+                        loaded_together(mv);
                     }
                     uint32_t bits = 0;
 #pragma unroll

@@ -248,7 +248,10 @@ void k_conv_wide(Geom g, WideArgs wa, const unsigned char *__restrict__ x, const
                     const int ih = sih + t / 3 * g.dh, iw = iwc - 1 + t % 3;
                     in[t] = live && (uint32_t)ih < (uint32_t)g.h && (uint32_t)iw < (uint32_t)g.w;
                     on[t] = true;
-                    if (mask_in) on[t] = mask_at(mask_in, in[t] ? pixc - 1 + t / 3 * g.dh * g.w + t % 3 : 0, packed_masks);
+                }
+                if (mask_in) {
+#pragma unroll
+                    for (int t = 0; t < 9; ++t) on[t] = mask_at(mask_in, in[t] ? pixc - 1 + t / 3 * g.dh * g.w + t % 3 : 0, packed_masks);
                 }
 #pragma unroll
                 for (int t = 0; t < 9; ++t) bits |= (uint32_t)(in[t] && on[t]) << t;
@@ -290,7 +293,15 @@ void k_conv_wide(Geom g, WideArgs wa, const unsigned char *__restrict__ x, const
                     for (int q = 0; q < 3; ++q) {
                         const int ih = ih0 + q * g.dh;
                         in[q] = used && ih >= 0 && ih < g.h && iw >= 0 && iw < g.w;
-                        on[q] = in[q] && (!mask_in || mask_at(mask_in, in[q] ? pix + q * g.dh * g.w : 0, packed_masks));
+                        on[q] = in[q];
+                    }
+                    if (mask_in) {
+                        uint32_t rel[3];
+#pragma unroll
+                        for (int q = 0; q < 3; ++q) rel[q] = mask_at(mask_in, in[q] ? pix + q * g.dh * g.w : 0, packed_masks);
+                        loaded_together(rel);
+#pragma unroll
+                        for (int q = 0; q < 3; ++q) on[q] = on[q] && rel[q];
                     }
                     if (sl < SL) {
                         slot_bits[sl] = (uint32_t)on[0] | (uint32_t)on[1] << 1 | (uint32_t)on[2] << 2;

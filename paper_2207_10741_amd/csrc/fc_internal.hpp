@@ -85,13 +85,22 @@ struct MaskGeom {
     int64_t m;        // n*ho*wo
 };
 
+// Values loaded together: without this the compiler moves each load to the branch that uses it, with a wait of its own there.
+template <typename T, int N> __device__ __forceinline__ void loaded_together(T (&v)[N])
+{
+#pragma unroll
+    for (int i = 0; i < N; ++i) __asm__ volatile("" : "+v"(v[i]));
+}
+
 // A mask is one byte per pixel (nonzero = relevant) or, packed, one bit per pixel: bit p & 31
 // of the 32-bit word p >> 5 (little-endian, so the same bits as bit p & 63 of the 64-bit word
 // p >> 6, one wave ballot); bits past the last pixel are zero.
+// One load of a byte for both, without a branch: a branch per form ends in a wait for its load, so look-ups that a kernel
+// makes together came back one after another.
 __device__ __forceinline__ bool mask_at(const uint8_t *__restrict__ m, int64_t p, bool packed)
 {
-    if (packed) return (reinterpret_cast<const uint32_t *>(m)[p >> 5] >> (uint32_t)(p & 31)) & 1u;
-    return m[p] != 0;
+    const uint32_t byte = m[packed ? p >> 3 : p];
+    return (byte >> (packed ? (uint32_t)p & 7u : 0u)) & (packed ? 1u : 0xffu);
 }
 
 __host__ __device__ static inline MaskGeom mask_geom(int n, int h, int w, int kh, int kw, int sh, int sw, int ph, int pw, int dh,
@@ -152,16 +161,18 @@ __device__ __forceinline__ uint32_t kept_flags16(const MaskGeom &g, const uint8_
     if (g.packed_in) {
         uint32_t got[16];
 #pragma unroll
-        for (int j = 0; j < 16; ++j) got[j] = at[j] >= 0 ? reinterpret_cast<const uint32_t *>(mask_in)[at[j] >> 5] : 0u;
+        for (int j = 0; j < 16; ++j) got[j] = reinterpret_cast<const uint32_t *>(mask_in)[max(at[j], 0) >> 5];
+        loaded_together(got);
 #pragma unroll
-        for (int j = 0; j < 16; ++j) flags |= ((got[j] >> (at[j] & 31)) & 1u) << j;
+        for (int j = 0; j < 16; ++j) flags |= (at[j] >= 0 ? (got[j] >> (at[j] & 31)) & 1u : 0u) << j;
         return flags;
     }
-    uint8_t got[16];
+    uint32_t got[16];
 #pragma unroll
-    for (int j = 0; j < 16; ++j) got[j] = at[j] >= 0 ? mask_in[at[j]] : (uint8_t)0;
+    for (int j = 0; j < 16; ++j) got[j] = mask_in[max(at[j], 0)];
+    loaded_together(got);
 #pragma unroll
-    for (int j = 0; j < 16; ++j) flags |= got[j] ? (1u << j) : 0u;
+    for (int j = 0; j < 16; ++j) flags |= at[j] >= 0 && got[j] ? (1u << j) : 0u;
     return flags;
 }
 
