@@ -98,7 +98,7 @@ __device__ __forceinline__ void span_rows(const Geom &g, const uint8_t *__restri
     constexpr int U = 3; // look-ups of a thread in flight together
     for (int i0 = tid; i0 < n * taps; i0 += U * kRegThreads) {
         int row[U], tp[U], pix[U];
-        uint8_t rel[U];
+        uint32_t rel[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int i = i0 + u * kRegThreads;
@@ -112,7 +112,12 @@ __device__ __forceinline__ void span_rows(const Geom &g, const uint8_t *__restri
             pix[u] = ok ? (s.img[r] * g.h + ih) * g.w + iw : -1;
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u) rel[u] = mask_in ? (uint8_t)mask_at(mask_in, max(pix[u], 0), packed) : (uint8_t)1;
+        for (int u = 0; u < U; ++u) rel[u] = 1u;
+        if (mask_in) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) rel[u] = mask_at(mask_in, max(pix[u], 0), packed);
+            loaded_together(rel);
+        }
 #pragma unroll
         for (int u = 0; u < U; ++u)
             if (pix[u] >= 0 && rel[u]) atomicOr(&s.bits[tp[u] >> 5][row[u]], 1u << (tp[u] & 31));
@@ -321,7 +326,20 @@ __global__ __launch_bounds__(kRegThreads, 2) void k_conv_f32(Geom g, const float
     }
     wait_vmcnt<0>();
 
-    // a lane's quad (b, q) = channels co0 + 32 b + 8 q + 4 half .. + 3 of the position of row r
+    // a lane's quad (b, q) = channels co0 + 32 b + 8 q + 4 half .. + 3 of the position of row r; the bias of all its quads comes in one
+    // round trip (where it was used, each value had one of its own: 128 -> 128 without a mask on 8 x 120 x 120 323 -> 315 us, half kept 246 -> 239)
+    constexpr int NQ = WK == 4 ? 1 : 4; // quads of a block that a lane finishes
+    float bq[CB * NQ * 4];
+    if (bias) {
+#pragma unroll
+        for (int b = 0; b < CB; ++b)
+#pragma unroll
+            for (int q = 0; q < NQ; ++q)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    bq[(b * NQ + q) * 4 + i] = bias[min(co0 + b * 32 + (WK == 4 ? wave : q) * 8 + half * 4 + i, g.c_out - 1)];
+        loaded_together(bq);
+    }
     const int r = wm * 32 + l32;
     const int64_t at = r < n ? (int64_t)rows_s.p[r] * g.c_out : -1;
     auto finish = [&](int b, int q, float4 v) __attribute__((always_inline)) {
@@ -329,7 +347,7 @@ __global__ __launch_bounds__(kRegThreads, 2) void k_conv_f32(Geom g, const float
         float e[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            if (bias && co + i < g.c_out) e[i] += bias[co + i];
+            if (bias) e[i] += bq[(b * NQ + (WK == 4 ? 0 : q)) * 4 + i];
             if (g.flags & FC_RELU) e[i] = !(e[i] > 0.f) ? (e[i] != e[i] ? e[i] : 0.f) : e[i];
         }
         if (at < 0) return;
@@ -999,12 +1017,73 @@ __global__ __launch_bounds__(kRegThreads, 2) void k_conv_grouped_window(
         for (uint32_t o = (uint32_t)wave * 1024u; o < (uint32_t)cut.w_bytes; o += 4096u)
             dma_load16(rsrc_w, at + o + (uint32_t)lane * 16u, __builtin_amdgcn_readfirstlane(lds0 + cut.x_bytes + o));
     }
-    // ---- labels: lane l of every wave holds position first + l ----
+    // ---- pixels: LDS piece c of pixel slot q holds the window's piece c ^ swizzle(q).  (A pixel before or past its image may be another image's or,
+    // checked by the descriptor, none: no tap reads it.) ----
+    const u32x4_t rsrc_x = make_rsrc_words(x, (uint32_t)g.n * g.h * g.w * g.c_in * 2u);
+    const int pieces = 1 << lg_pieces, slots = g.kh * line;
+    auto pixel_at = [&](int o) __attribute__((always_inline)) {
+        const int i = o + lane, q = i >> lg_pieces, c = (i ^ swizzle(q)) & (pieces - 1);
+        const int k = V ? (int)((uint32_t)q / (uint32_t)kQuadLine) : (int)fast_div((uint32_t)q, cut.by_line);
+        const int t = q - k * line - (V ? 1 : 0), ch = win0 + c * 8;
+        const int pix = first + (k * g.dh - g.ph) * g.w - g.pw + t;
+        return (V == 0 || t >= 0) && q < slots && ch < g.c_in ? ((uint32_t)pix * (uint32_t)g.c_in + (uint32_t)ch) * 2u : kOutOfRange;
+    };
+    auto request_pixels = [&]() __attribute__((always_inline)) {
+        for (int o = wave * 64; o < (slots << lg_pieces); o += kRegThreads)
+            dma_load16(rsrc_x, pixel_at(o), __builtin_amdgcn_readfirstlane(lds0 + (uint32_t)o * 16u));
+    };
+    if (!mask_in) request_pixels();
+    // ---- labels: lane l of every wave holds position first + l; they and the mask under this wave's share of the taps are requested together
+    // (one after another they were four round trips), and while they are on their way a quad kernel finds its pixels' addresses.  4 -> 4
+    // channels on 16 x 56 x 56, half kept, 13.4 -> 11.8 us, 8 -> 8 there 21.6 -> 19.8, 16 -> 16 on 32 x 60 x 60 48.9 -> 45.3. ----
     const int p = first + lane;
-    const bool inside = p < g.m;
-    const bool kept = inside && (!mask_in || position_kept(g, mask_in, mask_out, p));
+    const bool inside = p < g.m, packed = (g.flags & FC_PACKED_MASKS) != 0;
+    const int pp = inside ? p : 0;
+    const int r = (int)fast_div((uint32_t)pp, g.div_wo), ow = pp - r * g.wo;
+    const int img = (int)fast_div((uint32_t)r, g.div_ho), oh = r - img * g.ho;
+    constexpr int U = 3; // look-ups in flight
+    bool in[U];
+    int tap_pix[U];
+    uint32_t m[U + 1]; // and the label
+    auto tap_places = [&](int t0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int t = t0 + 4 * u, kh = (int)fast_div((uint32_t)t, cut.by_kw), kw = t - kh * g.kw;
+            const int ih = oh - g.ph + kh * g.dh, iw = ow - g.pw + kw * g.dw;
+            in[u] = inside && t < taps && (uint32_t)ih < (uint32_t)g.h && (uint32_t)iw < (uint32_t)g.w;
+            tap_pix[u] = in[u] ? (img * g.h + ih) * g.w + iw : 0;
+            m[u] = 1u;
+        }
+    };
+    tap_places(wave);
+    constexpr int PL = V ? ((3 * kQuadLine << LG) + kRegThreads - 1) / kRegThreads : 1; // quads: a lane's pieces
+    uint32_t from[PL];
+    m[U] = 1u;
+    if (mask_in) {
+        const int ihc = min(max(oh - g.ph + g.dh * ((g.kh - 1) / 2), 0), g.h - 1), iwc = min(max(ow - g.pw + g.dw * ((g.kw - 1) / 2), 0), g.w - 1);
+        m[U] = mask_at(mask_out ? mask_out : mask_in, mask_out ? pp : (img * g.h + ihc) * g.w + iwc, packed);
+#pragma unroll
+        for (int u = 0; u < U; ++u) m[u] = mask_at(mask_in, tap_pix[u], packed);
+        if constexpr (V != 0) {
+#pragma unroll
+            for (int i = 0; i < PL; ++i) from[i] = pixel_at(wave * 64 + i * kRegThreads);
+        }
+        loaded_together(m);
+    }
+    const bool kept = inside && m[U];
     const uint64_t kept_set = __ballot(kept), drop_set = __ballot(inside && !kept);
     const int n = __popcll(kept_set), nd = __popcll(drop_set);
+    if (mask_in && n > 0) {
+        if constexpr (V != 0) {
+#pragma unroll
+            for (int i = 0; i < PL; ++i) {
+                const int o = wave * 64 + i * kRegThreads;
+                if (o < (slots << LG)) dma_load16(rsrc_x, from[i], __builtin_amdgcn_readfirstlane(lds0 + (uint32_t)o * 16u));
+            }
+        } else {
+            request_pixels();
+        }
+    }
     if (wave == 0) {
         const uint64_t below = (1ull << lane) - 1ull;
         if (kept) order_s[__popcll(kept_set & below)] = (uint8_t)lane;
@@ -1013,39 +1092,20 @@ __global__ __launch_bounds__(kRegThreads, 2) void k_conv_grouped_window(
         if (lane < 4) reinterpret_cast<uint32_t *>(zero_s)[lane] = 0u;
     }
     if (n > 0) {
-        // ---- pixels: LDS piece c of pixel slot q holds the window's piece c ^ swizzle(q) ----
-        const int pieces = 1 << lg_pieces;
-        const u32x4_t rsrc_x = make_rsrc_words(x, (uint32_t)g.n * g.h * g.w * g.c_in * 2u);
-        const int npix = g.n * g.h * g.w, slots = g.kh * line;
-        for (int o = wave * 64; o < (slots << lg_pieces); o += kRegThreads) {
-            const int i = o + lane, q = i >> lg_pieces, c = (i ^ swizzle(q)) & (pieces - 1);
-            const int k = V ? (int)((uint32_t)q / (uint32_t)kQuadLine) : (int)fast_div((uint32_t)q, cut.by_line);
-            const int t = q - k * line - (V ? 1 : 0);
-            const int pix = first + (k * g.dh - g.ph) * g.w - g.pw + t, ch = win0 + c * 8;
-            const bool ok = q < slots && t >= 0 && pix >= 0 && pix < npix && ch < g.c_in;
-            dma_load16(rsrc_x, ok ? (uint32_t)(pix * g.c_in + ch) * 2u : kOutOfRange,
-                       __builtin_amdgcn_readfirstlane(lds0 + (uint32_t)o * 16u));
-        }
         // ---- taps in use: this wave's share of them, for all positions ----
-        const bool packed = (g.flags & FC_PACKED_MASKS) != 0;
-        const int pp = kept ? p : 0;
-        const int r = (int)fast_div((uint32_t)pp, g.div_wo), ow = pp - r * g.wo;
-        const int img = (int)fast_div((uint32_t)r, g.div_ho), oh = r - img * g.ho;
         __syncthreads(); // bits_s cleared
         uint32_t mine = 0;
-        constexpr int U = 3; // look-ups in flight
         for (int t0 = wave; t0 < taps; t0 += 4 * U) {
-            bool in[U];
-            uint8_t m[U];
+            if (t0 != wave) {
+                tap_places(t0);
+                if (mask_in) {
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int t = t0 + 4 * u, kh = (int)fast_div((uint32_t)t, cut.by_kw), kw = t - kh * g.kw;
-                const int ih = oh - g.ph + kh * g.dh, iw = ow - g.pw + kw * g.dw;
-                in[u] = kept && t < taps && (uint32_t)ih < (uint32_t)g.h && (uint32_t)iw < (uint32_t)g.w;
-                m[u] = mask_in ? (uint8_t)mask_at(mask_in, in[u] ? (img * g.h + ih) * g.w + iw : 0, packed) : (uint8_t)1;
+                    for (int u = 0; u < U; ++u) m[u] = mask_at(mask_in, tap_pix[u], packed);
+                    loaded_together(m);
+                }
             }
 #pragma unroll
-            for (int u = 0; u < U; ++u) mine |= in[u] && m[u] ? 1u << (t0 + 4 * u) : 0u;
+            for (int u = 0; u < U; ++u) mine |= kept && in[u] && m[u] ? 1u << (t0 + 4 * u) : 0u;
         }
         if (mine) atomicOr(&bits_s[lane], mine);
     }
