@@ -704,7 +704,7 @@ hipError_t launch_conv_f32(const Geom &g, const void *x, const uint8_t *mask_in,
 // 8-channel piece are summed apart and added at the end (as one chain the error of 8 -> 8 f16 channels against 64-bit
 // sums is 7.4e-8 of the result, so 6.1e-8; products of 32 elements had 5.8e-8).  The four waves of a workgroup take the
 // quads of rows in turn.  (8 -> 8 in the window form below: two products of 16 channels instead.)
-// (With a mask / without one / with a list and no zero-fill, us: 128 channels in 32 groups on 16 x 56 x 56 12.6 / 12.8 /
+// (With a mask / without one / with a list and no zero-fill, us, when this form was chosen: 128 channels in 32 groups on 16 x 56 x 56 12.6 / 12.8 /
 // 13.1, and at stride 2 9.2 / 8.4 / 8.8; 256 in 32 groups 21.8 / 24.4 / 23.0.  16-channel products with zero weights for the
 // foreign groups, which mixed groups as said above: 12.9 / 13.8 / 15.0, 10.0 / 9.6 / 9.9, 22.8 / 23.8 / 26.2.  On the vector
 // ALUs, with a compaction and a zero-fill launch, the first of these was 61 us.)
@@ -975,10 +975,10 @@ __global__ __launch_bounds__(kRegThreads, V * NL > 36 ? 1 : 2) void k_conv_group
 // channels' groups), the workgroup's weights likewise, and all operands come from there; a gated tap
 // reads a piece of zeros.  V = 0: blocks of 16 channels, KS matrix steps; NG = 2: a block of two groups of 8, a product for each
 // on the same weights, of which every lane keeps its own group's rows (256 channels in 32 groups on 16 x 56 x 56: 21.8 us with half
-// the pixels kept and 24.4 without a mask, as quads 22.4 and 25.2: those read a pixel's pieces twice).  V = 1, 2: quads of rows, 3x3 kernels and 4 V
+// the pixels kept and 24.4 without a mask, now 19.8 and 23.7, as quads 22.4 and 25.2: those read a pixel's pieces twice).  V = 1, 2: quads of rows, 3x3 kernels and 4 V
 // input channels per group, so that a tap is one read; everything about the reads is fixed when the kernel is compiled
 // (a pixel's pieces 1 << LG, its kernel row's line), because what a quad costs is the instructions of its addresses: with
-// the line's length and the taps at run time the kernel took 17.8 us where it now takes 12.5 (4 -> 4 channels on 16 x 56 x 56, half kept).
+// the line's length and the taps at run time the kernel took 17.8 us where it then took 12.5 and now takes 11.8 (4 -> 4 channels on 16 x 56 x 56, half kept).
 constexpr int kWindowSpan = 64;
 constexpr int kQuadLine = kWindowSpan + 4; // pixel slots of a line: one of zeros, 66 pixels, one to make four divide it
 struct WindowCut {
