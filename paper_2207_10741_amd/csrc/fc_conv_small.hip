@@ -179,15 +179,17 @@ __device__ __forceinline__ void small_clear_tile(const Geom &g, const SmallUnit 
         *reinterpret_cast<u32x4_t *>(out + (int64_t)(u.r0 + l32) * g.c_out + u.co0 + i * (16 / (int)sizeof(TO))) = zero;
 }
 
-// With a list: the irrelevant rows, by the workgroups whose tile does not exist when there are enough.
+// With a list: the irrelevant rows, by the workgroups whose tile does not exist when there are enough.  Every wave has waited for its own
+// loads; the waves' lists lie in the first wave's slots, where its weights and pixels (in k_conv_small_once the weights of idle tiles too) and the sums of
+// a tile come to lie, so all waves meet before the first entry is written.
 template <typename TO>
-__device__ __forceinline__ void small_clear_rest(const Geom &g, const SmallUnit &u, int tiles, int nts, bool any, const uint8_t *__restrict__ mask_in,
+__device__ __forceinline__ void small_clear_rest(const Geom &g, const SmallUnit &u, int tiles, int nts, const uint8_t *__restrict__ mask_in,
                                                  const uint8_t *__restrict__ mask_out, TO *__restrict__ out, unsigned char *lds)
 {
     const int unit = blockIdx.x, grid = gridDim.x, idle = grid - tiles * nts;
     const bool idle_only = idle * 16 >= grid;
     if (!idle_only || u.mt >= tiles) {
-        if (any) __syncthreads(); // LDS is free again
+        __syncthreads(); // (the condition is the workgroup's)
         clear_irrelevant(g, mask_in, mask_out, out, g.c_out * (int)sizeof(TO) / 16,
                          (idle_only ? unit - tiles * nts : unit) * u.waves + u.wave, (idle_only ? idle : grid) * u.waves,
                          reinterpret_cast<int32_t *>(lds) + u.wave * 64);
@@ -467,7 +469,7 @@ __global__ __launch_bounds__(64 * kSmallWaves, 1) void k_conv_small(Geom g, Smal
     }
     if (idx && fill) {
         const SmallUnit u = {waves, wave, mt, nt, group, splits, split, co0, r0, p, live, drop};
-        small_clear_rest(g, u, tiles, nts, any, mask_in, mask_out, out, lds);
+        small_clear_rest(g, u, tiles, nts, mask_in, mask_out, out, lds);
     }
 }
 
@@ -704,7 +706,7 @@ __global__ __launch_bounds__(64 * kSmallWaves, 1) void k_conv_small_once(Geom g,
     }
     if (any) small_meet_and_store<DT, TO>(g, u, cut.n_nt, fill, acc, lds, out, partials, tile_counters);
     else if (fill && drop && group == 0) small_clear_tile(g, u, out);
-    if (idx && fill) small_clear_rest(g, u, (rows + kSmallRows - 1) / kSmallRows, nts, any, mask_in, mask_out, out, lds);
+    if (idx && fill) small_clear_rest(g, u, (rows + kSmallRows - 1) / kSmallRows, nts, mask_in, mask_out, out, lds);
 }
 
 // ---------------------------------------------------------------------------------------------
