@@ -427,7 +427,7 @@ __global__ __launch_bounds__(kRegThreads, RING == 2 ? 3 : 2) void k_conv_f32_rou
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int co0 = blockIdx.y * 32;
 
-    // ---- request what decides about the rows, and the bias of the channels this lane stores ----
+    // ---- request what decides about the rows ----
     int p = first + l32;
     bool live = p < rows;
     // (values of loads that are waited for by hand are touched by nothing before the wait)
@@ -446,11 +446,6 @@ __global__ __launch_bounds__(kRegThreads, RING == 2 ? 3 : 2) void k_conv_f32_rou
         __asm__ volatile("global_load_ubyte %0, %1, %2" : "=v"(label) : "v"(at), "s"(mask_out ? mask_out : mask_in) : "memory");
     }
     const int co = co0 + wave * 8 + half * 4;
-    const u32x4_t rsrc_b = make_rsrc_words(bias, bias ? (uint32_t)g.c_out * 4u : 0u);
-    uint32_t bq[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-        __asm__ volatile("buffer_load_dword %0, %1, %2, 0 offen" : "=v"(bq[i]) : "v"((uint32_t)(co + i) * 4u), "s"(rsrc_b) : "memory");
 
     // ---- stages: wave v loads rows 8 v .. 8 v + 7 of the pixels and of the weights ----
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)reinterpret_cast<uintptr_t>(lds) + (uint32_t)wave * 1024u);
@@ -467,7 +462,7 @@ __global__ __launch_bounds__(kRegThreads, RING == 2 ? 3 : 2) void k_conv_f32_rou
     if (tid < 8) *reinterpret_cast<uint4 *>(lds + kF32Zeros<RING> + tid * 16) = make_uint4(0u, 0u, 0u, 0u);
 
     // ---- the rows ----
-    wait_vmcnt<4>();
+    wait_vmcnt<0>();
     bool drop = false;
     if (idx) {
         __asm__ volatile("" : "+v"(entry)::"memory");
@@ -491,7 +486,7 @@ __global__ __launch_bounds__(kRegThreads, RING == 2 ? 3 : 2) void k_conv_f32_rou
                 if (co + i < g.c_out) to[i] = e[i];
         }
     };
-    if (__ballot(live) == 0) { // (the same in all waves)
+    if (__ballot(live) == 0) { // (the same in all waves; nothing is on its way to a register here)
         store(make_float4(0.f, 0.f, 0.f, 0.f));
         return;
     }
@@ -501,6 +496,12 @@ __global__ __launch_bounds__(kRegThreads, RING == 2 ? 3 : 2) void k_conv_f32_rou
     const int ih0 = oh * g.sh - g.ph, iw0 = ow * g.sw - g.pw;
     const int pix0 = (img * g.h + ih0) * g.w + iw0; // may lie outside the image
 
+    // the bias of the channels this lane stores, added at the end
+    const u32x4_t rsrc_b = make_rsrc_words(bias, bias ? (uint32_t)g.c_out * 4u : 0u);
+    uint32_t bq[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        __asm__ volatile("buffer_load_dword %0, %1, %2, 0 offen" : "=v"(bq[i]) : "v"((uint32_t)(co + i) * 4u), "s"(rsrc_b) : "memory");
     // the mask bytes under the taps of a kernel row with one (unaligned) 4-byte load each; one that would leave the
     // mask is moved inside it and its bytes moved back (without a mask: three loads of something, not looked at)
     const uint8_t *const from = mask_in ? mask_in : reinterpret_cast<const uint8_t *>(w);

@@ -90,3 +90,50 @@ def test_lists_in_lds_lie_behind_a_barrier(kernels):
             seen.add(at)
             assert not k.code[at].startswith("ds_write_b32"), "%s: `%s` while another wave's load may be on its way" % (name, k.code[at])
             todo += k.after(at)
+
+
+def _registers(text):
+    """Vector registers that an instruction names."""
+    named = set()
+    for first, last, one in re.findall(r"\bv\[(\d+):(\d+)\]|\bv(\d+)\b", text):
+        named |= {int(one)} if one else set(range(int(first), int(last) + 1))
+    return named
+
+
+def _is_memory(text):
+    return text.startswith(("buffer_load", "buffer_store", "buffer_atomic", "global_", "flat_", "scratch_"))
+
+
+def _unwaited(k, at):
+    """A place where the registers of the load at `at` are named, or the kernel ends, before a wait that covers the load; None if there is none."""
+    written = _registers(k.code[at].split(",", 1)[0])
+    seen, todo = set(), [(n, 0) for n in k.after(at)]       # (place, requests after the load)
+    while todo:
+        here = todo.pop()
+        if here in seen:
+            continue
+        seen.add(here)
+        place, later = here
+        text = k.code[place]
+        wait = re.search(r"vmcnt\((\d+)\)", text) if text.startswith("s_waitcnt") else None
+        if wait and int(wait.group(1)) <= later:
+            continue
+        # (a multiply-add of 32 bits names a pair as its addend, whose high half is whatever lies there)
+        spare = re.match(r"(v_mad_u64_u32 .*)v\[(\d+):\d+\]$", text)
+        if text.startswith("s_endpgm") or _registers(spare.expand(r"\1v\2") if spare else text) & written:
+            return text
+        later = min(later + _is_memory(text), 63)
+        todo += [(n, later) for n in k.after(place)]
+    return None
+
+
+@pytest.mark.parametrize("source,part,loads", [("fc_conv_small.hip", "k_conv_small_once", 9), ("fc_conv_reg.hip", "k_conv_f32_rounds", 9)])
+def test_loads_written_by_hand_are_waited_for(kernels, source, part, loads):
+    """The compiler does not know that the registers of such a load are still to be written: until a wait that covers it nothing may name
+    them, on any path, and no path may end without one (there the compiler is free to use them for something else)."""
+    for name, k in _named(kernels[source], part).items():
+        by_hand = [at for at, text in enumerate(k.code) if k.by_hand[at] and _is_memory(text) and not _is_lds_load(text)]
+        assert len(by_hand) == loads, name                  # entry, label, four of the bias, three of the mask
+        for at in by_hand:
+            found = _unwaited(k, at)
+            assert found is None, "%s: `%s` after `%s`" % (name, found, k.code[at])
