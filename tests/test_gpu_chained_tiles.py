@@ -11,11 +11,15 @@ pytestmark = pytest.mark.gpu
 
 LAYERS = [
     # n, h, w, ci, co, dtype, stride
-    (13, 59, 57, 128, 128, synth.BF16, 1),      # 43 719 positions: the tiled kernel
-    (13, 59, 58, 128, 128, synth.BF16, 1),      # 44 486: a workgroup per CU
+    (7, 60, 78, 128, 128, synth.BF16, 1),       # 512 tiles of 128 x 64: the tiled kernel
+    (13, 59, 43, 128, 128, synth.BF16, 1),      # 516: a workgroup per CU
+    (20, 28, 29, 128, 104, synth.F16, 1),       # short rows, 254: the tiled kernel
+    (17, 33, 30, 128, 104, synth.F16, 1),       # 264: a workgroup per CU
+    (13, 59, 57, 128, 128, synth.BF16, 1),
+    (13, 59, 58, 128, 128, synth.BF16, 1),
     (16, 61, 67, 192, 96, synth.F16, 1),
     (60, 61, 63, 64, 104, synth.BF16, 2),       # 59 520: no pixel line
-    (90, 31, 29, 64, 128, synth.BF16, 2),       # 21 600 with short rows
+    (90, 31, 29, 64, 128, synth.BF16, 2),       # short rows, stride 2, 338 tiles: the tiled kernel
     (13, 100, 101, 128, 128, synth.BF16, 1),    # 1 025 granules of 128 x 128: wide tiles
     (7, 100, 101, 256, 256, synth.F16, 1),      # 1 104 of 64 x 256
     (7, 100, 101, 256, 256, synth.FP8, 1),
