@@ -62,3 +62,28 @@ def test_f32_rounds(layer, kind, how):
     # sums' size; the largest of thousands lies within five times that
     assert np.abs(got[pos] - want).max() / np.sqrt(np.mean(np.square(want))) <= 1e-5
     assert not np.any(got[keep] == 7.0)
+
+
+@pytest.mark.parametrize("how", ["mask", "labels", "list"])
+@pytest.mark.parametrize("layer", LAYERS)
+def test_same_sums_as_the_kernel_for_any_layer(layer, how):
+    """Masks of bits send these layers to the kernel that serves every fp32 layer: the same products in the same order, so the same bits."""
+    torch = G.torch_mod()
+    n, h, w, ci, co, s, p, dh = layer
+    geo = ((3, 3), s, p, (dh, 1))
+    xd = G.to_dev(synth.activations((n, h, w, ci), synth.F32, 47, 1), synth.F32)
+    wd, bd = G.to_dev(synth.he_weights(co, 3, 3, ci, synth.F32, 47, 2), synth.F32), torch.from_numpy(synth.bias(co, 47, 3)).to(G.dev())
+    md = G.mask_dev(synth.mask_objects(n, h, w, 0.48, 47, 4))
+    m_out = B.mask_downsample(md, *geo)
+    idx, count = B.active_index_compact(m_out)
+    outs = []
+    for flag, form in ((0, lambda m: m), (B.PACKED_MASKS, B.mask_pack)):
+        kw = dict(mask_in=form(md))
+        if how != "mask":
+            kw["mask_out"] = form(m_out)
+        if how == "list":
+            kw.update(idx=idx, count=count)
+        desc = B.conv_desc(n, h, w, ci, co, *geo, B.F32, B.F32, B.RELU | flag)
+        outs.append(B.focused_conv2d(desc, xd, wd, bd, **kw))
+    assert float(outs[0].abs().max()) > 0 or int(count) == 0
+    assert torch.equal(outs[0], outs[1])

@@ -78,3 +78,28 @@ def test_small_layers(layer, kind, how):
     out16 = torch.full(out.shape, 7.0, device=G.dev()).to(B.torch_dtype(dtype))
     B.focused_conv2d(B.conv_desc(n, h, w, ci, co, *geo, dtype, None, flags), xd, wd, bd, out=out16, **kw)
     assert torch.equal(out16, out.to(out16.dtype))
+
+
+@pytest.mark.parametrize("how", ["mask", "labels", "list"])
+@pytest.mark.parametrize("layer", LAYERS)
+def test_same_sums_as_the_looping_kernel(layer, how):
+    """Masks of bits send these layers to the kernel that loops over its stages: the same products in the same order, so the same bits."""
+    torch = G.torch_mod()
+    n, h, w, ci, co, dtype, s, p, dh = layer
+    geo = ((3, 3), s, p, (dh, 1))
+    xd = G.to_dev(synth.activations((n, h, w, ci), dtype, 43, 1), dtype)
+    wd, bd = G.to_dev(synth.he_weights(co, 3, 3, ci, dtype, 43, 2), dtype), torch.from_numpy(synth.bias(co, 43, 3)).to(G.dev())
+    md = G.mask_dev(synth.mask_objects(n, h, w, 0.48, 43, 4))
+    m_out = B.mask_downsample(md, *geo)
+    idx, count = B.active_index_compact(m_out)
+    outs = []
+    for flag, form in ((0, lambda m: m), (B.PACKED_MASKS, B.mask_pack)):
+        kw = dict(mask_in=form(md))
+        if how != "mask":
+            kw["mask_out"] = form(m_out)
+        if how == "list":
+            kw.update(idx=idx, count=count)
+        desc = B.conv_desc(n, h, w, ci, co, *geo, dtype, B.F32, B.RELU | flag)
+        outs.append(B.focused_conv2d(desc, xd, wd, bd, **kw))
+    assert float(outs[0].abs().max()) > 0 or int(count) == 0
+    assert torch.equal(outs[0], outs[1])
