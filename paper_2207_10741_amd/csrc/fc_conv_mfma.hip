@@ -346,11 +346,11 @@ static hipError_t launch_tile(const Geom &g, const void *x, const uint8_t *mask_
 {
     switch (kind) {
     case TileShape::own64:
-        if constexpr (TAPC != 1 && !CMP) return launch_dma<DT, TO, CMP, 64, 64, 2, 2, TAPC, 4, 2, 0, 2, true, PACK>(FC_ARGS);
+        // (kernels other than 3x3 label their own rows only with packed taps)
+        if constexpr ((TAPC == 9 || (TAPC == 32 && PACK)) && !CMP) return launch_dma<DT, TO, CMP, 64, 64, 2, 2, TAPC, 4, 2, 0, 2, true, PACK>(FC_ARGS);
         break;
     case TileShape::small64:
         return launch_dma<DT, TO, CMP, 64, 64, 2, 2, TAPC, 4, 2, 0, 2, false, PACK>(FC_ARGS);
-        break;
     case TileShape::line128:
         if constexpr (TAPC == 9 && !PACK) return launch_dma<DT, TO, CMP, 128, 128, 2, 2, TAPC, 2, 2, 160, 2>(FC_ARGS);
         break;

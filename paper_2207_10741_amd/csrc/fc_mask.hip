@@ -109,10 +109,11 @@ constexpr int kListThreads = 1024; // of a workgroup whose lanes take four posit
 constexpr int kListWaves = kListThreads / 64;
 template <int PER> constexpr int kThreadsOf = kCompactBlockElems / PER;
 // 16-byte reads of a list's last workgroup (off their alignment they count twice) up to which one launch serves all lists, and up to which its workgroups have 256 threads
-// (kOnceBlocks: where a list has to be labelled position by position).  One launch after another, bytes, us, two launches or one of 1024
-// threads that labels the positions before its own one by one -> here: four levels of 224 x 224 (3 136 reads) 5.8 -> 4.2, 251 x 333 (5 224) 6.3 -> 5.4, 2 x 224 x 224
-// (6 272) 6.5 -> 5.2, 8 x 131 x 127 6.4 -> 5.1, 4 x 224 x 224 (12 544) 6.7 -> 6.6, 16 x 128 x 128 (16 384) 7.3 -> 6.5.  With 256 threads the last three take 5.7, 6.0, 8.0 and
-// 9.5; 160 x 160 takes 3.4 with them and 4.1 with 1024.  Past 16 384 the counting alone is what the second launch costs.
+// (kOnceBlocks: where a list has to be labelled position by position).  One launch after another, bytes, us, two launches -> here: four levels of 160 x 160
+// (1 600 reads) 6.1 -> 3.6, 224 x 224 (3 136) 6.2 -> 4.4, 251 x 333 (5 224) 6.4 -> 5.5, 2 x 224 x 224 (6 272) 6.4 -> 5.4, 8 x 131 x 127 (8 320) 6.4 -> 5.3, 12 x 128 x 128
+// (12 288) 6.8 -> 6.7, 4 x 224 x 224 (12 544) 6.6 -> 7.0, 16 x 128 x 128 (16 384) 7.3 -> 6.8; one list of the last two 5.9 -> 4.8 and 5.9 -> 5.3.  With 256 threads 2 x 224 x 224, 8 x 131
+// x 127, 4 x 224 x 224 and 16 x 128 x 128 take 5.7, 6.0, 8.1 and 9.2; with 1024 160 x 160 and 224 x 224 take 4.4 and 5.2.  Past 16 384 the counting alone is what the
+// second launch costs.
 // Through a stride less: a list and the layer behind it, two launches -> one: 12 x 112 x 112 / 2 (4 704 reads) 11.7 -> 10.8, 10 x 130 x 130 / 2 (11 700)
 // 12.2 -> 13.6, 14 x 105 x 131 / 2 (13 356) 12.2 -> 14.0.
 constexpr int kOncePieces = 16384, kOncePiecesStepped = 10000, kBriefPieces = 4096, kOnceBlocks = 4;
@@ -467,7 +468,7 @@ static RowPieces row_pieces(const LabelMap &L)
     RowPieces P = {};
     const int mul = L.col.mul;
     if (L.identity || L.packed_in || (mul != 1 && mul != 2 && mul != 4 && mul != 8 && mul != 16) || L.wl < 4 || L.col.add < 0) return P;
-    if ((int64_t)(L.wl - 1) * mul + L.col.add > L.w0 - 1 || L.col.lo > 0 + L.col.add || L.col.hi < (L.wl - 1) * mul + L.col.add) return P;
+    if ((int64_t)(L.wl - 1) * mul + L.col.add > L.w0 - 1 || L.col.lo > L.col.add || L.col.hi < (L.wl - 1) * mul + L.col.add) return P;
     P.per = 16 / mul;
     P.pieces = (L.wl + P.per - 1) / P.per;
     P.div_pieces = make_fastdiv((uint32_t)P.pieces);
