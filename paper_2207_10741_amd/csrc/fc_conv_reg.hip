@@ -632,10 +632,14 @@ static hipError_t launch_f32_ring(const Geom &g, const void *x, const uint8_t *m
 static hipError_t launch_f32_rounds(const Geom &g, const void *x, const uint8_t *mask_in, const uint8_t *mask_out, const void *w,
                                     const float *bias, const int32_t *idx, const int32_t *count, void *out, hipStream_t s)
 {
-    // Three workgroups of a CU with two rounds each, or two with three.  Three hide each other's waits better (128 -> 128 on 3 x 50 x 50, half kept, 25.8 ->
-    // 20.8 us), but where there is work for two a CU - about seven tenths of the tiles of a mask of regions hold a kept row - some CUs
-    // get three and others one (64 -> 64 on 2 x 60 x 80, 0.5 / 0.7 kept: 11.8 / 11.9 us, with two 10.4 / 10.4).
-    const int64_t tiles = (int64_t)((g.m + 31) / 32) * ((g.c_out + 31) / 32), busy = mask_in ? tiles * 7 / 10 : tiles;
+    // Three workgroups of a CU with two rounds each, or two with three.  Three hide each other's waits better (128 -> 128 without a mask on 3 x 50 x 50
+    // 29.2 -> 28.6 us), but where there is work for two a CU some CUs get three and others one.  Of the tiles of a mask of regions about 17 in 20
+    // hold a kept row; a list's rows fill no more than they have to.  Mask alone, 0.3 / 0.5 / 0.7 kept, two rounds -> three: 64 -> 64 on
+    // 2 x 60 x 80 (600 tiles) 11.7 / 12.9 / 13.3 -> 10.8 / 11.2 / 11.6, 192 -> 128 on 56 x 80 (560) 25.5 / 25.8 / 28.3 -> 21.8 / 22.3 / 22.6, 64 -> 64 on 2 x 55 x 88 (606) 11.7 / 13.0 /
+    // 13.3 -> 10.8 / 11.5 / 15.0, on 100 x 98 (614) 11.5 / 11.9 / 12.9 -> 10.7 / 12.2 / 14.9, 96 -> 128 on 2 x 50 x 50 (628) 16.9 / 17.4 / 17.7 -> 15.8 / 19.8 / 20.4; few tiles, 64 -> 64 on 60 x 80
+    // (300) 9.5 / 9.6 / 9.7 -> 9.3 / 9.4 / 9.4.  With a list 2 x 60 x 80 12.9 / 13.6 / 14.3 -> 12.7 / 13.4 / 14.3, 128 -> 128 on 72 x 75 (676) 20.6 / 21.5 / 26.4 -> 20.8 / 21.5 /
+    // 21.8, on 3 x 50 x 50 (940) 26.3 / 27.0 / 28.0 -> 21.6 / 22.7 / 33.3.  Masks that keep nine tenths fill more tiles than that: 2 x 60 x 80 13.6 -> 16.8, with a list 17.1 -> 19.6.
+    const int64_t tiles = (int64_t)((g.m + 31) / 32) * ((g.c_out + 31) / 32), busy = idx ? tiles * 7 / 10 : mask_in ? tiles * 17 / 20 : tiles;
     const int cus = conv_grid_cus();
     if (busy > cus && busy <= 2 * cus) return launch_f32_ring<3>(g, x, mask_in, mask_out, w, bias, idx, count, out, s);
     return launch_f32_ring<2>(g, x, mask_in, mask_out, w, bias, idx, count, out, s);
