@@ -43,11 +43,15 @@ __device__ __forceinline__ void dma_load16(const u32x4_t &rsrc, uint32_t byte_of
 // the part of an address that is the same for every lane costs no vector arithmetic.  An
 // out-of-range `byte_offset` stays out of range whatever the scalar offset is (it is checked
 // against the descriptor's size less the scalar offset).
+// A memory instruction may read a scalar register no sooner than five wait states after the vector unit wrote it, and the
+// compiler, which brings spilled scalars back with v_readlane, keeps to that only for instructions of its own: the offset is
+// copied by the scalar unit, which does wait (and stands where M0 wants a wait state anyway).
 __device__ __forceinline__ void dma_load16_s(const u32x4_t &rsrc, uint32_t byte_offset, uint32_t scalar_offset,
                                              uint32_t lds_addr)
 {
-    __asm__ volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                     :
+    uint32_t scalar;
+    __asm__ volatile("s_mov_b32 m0, %1\n\ts_mov_b32 %0, %4\n\tbuffer_load_dwordx4 %2, %3, %0 offen lds"
+                     : "=&s"(scalar)
                      : "s"(lds_addr), "v"(byte_offset), "s"(rsrc), "s"(scalar_offset)
                      : "memory");
 }
@@ -58,10 +62,10 @@ __device__ __forceinline__ void wait_vmcnt()
     __asm__ volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
 }
 
-// one dword per lane
+// one dword per lane (these few loads wait out a descriptor that v_readlane has just brought back)
 __device__ __forceinline__ void dma_load4(const u32x4_t &rsrc, uint32_t byte_offset, uint32_t lds_addr)
 {
-    __asm__ volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds"
+    __asm__ volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_dword %1, %2, 0 offen lds"
                      :
                      : "s"(lds_addr), "v"(byte_offset), "s"(rsrc)
                      : "memory");
@@ -70,7 +74,7 @@ __device__ __forceinline__ void dma_load4(const u32x4_t &rsrc, uint32_t byte_off
 // one byte per lane, zero-extended into the lane's dword of LDS (out of range: zero)
 __device__ __forceinline__ void dma_load1(const u32x4_t &rsrc, uint32_t byte_offset, uint32_t lds_addr)
 {
-    __asm__ volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_ubyte %1, %2, 0 offen lds"
+    __asm__ volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_ubyte %1, %2, 0 offen lds"
                      :
                      : "s"(lds_addr), "v"(byte_offset), "s"(rsrc)
                      : "memory");
