@@ -316,7 +316,7 @@ __device__ __forceinline__ int kept_before(const LabelMap &L, const RowPieces &P
             const int at = (b * L.h0 + ih) * L.w0 + L.col.add + q * 16;
             v[k] = make_uint4(0, 0, 0, 0);
             if (n[k] > 0) {
-                if (at + 16 <= bytes) {
+                if (at <= bytes - 16) { // (the sum could pass 31 bits)
                     __builtin_memcpy(&v[k], mask_in + at, 16);
                 } else { // (the mask's last bytes)
                     for (int j = 0; j < n[k]; ++j) part += mask_in[at + j * L.col.mul] != 0;
