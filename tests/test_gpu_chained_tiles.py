@@ -64,3 +64,48 @@ def test_rows_in_place_and_in_list_order(layer, kind):
         assert np.abs(rows[torch.from_numpy(at).to(G.dev())].cpu().numpy().astype(np.float64) - want).max() / rms <= bar
     # rows nobody sampled: the two forms differ in the order of their sums only
     assert float((got[B.SKIP_ZERO_FILL] - got[B.COMPACT_OUT]).abs().max()) / rms <= 2 * bar
+
+
+WORKGROUP_PER_CU = [
+    # n, h, w, ci, co, dtype, stride, pad, dilation: past 512 tiles of 128 x 64, at most eight 32-row blocks a CU
+    (8, 96, 64, 120, 128, synth.BF16, (1, 1), (1, 1), (1, 1)),     # a partial channel chunk
+    (13, 51, 61, 56, 96, synth.F16, (1, 1), (1, 1), (1, 1)),       # channel tails on both sides, ragged rows
+    (16, 64, 64, 64 * 3, 104, synth.BF16, (1, 1), (1, 1), (1, 1)),  # the most positions, three chunks
+    (20, 61, 60, 128, 128, synth.BF16, (2, 1), (0, 2), (2, 1)),    # vertical stride and dilation, wide padding
+    (17, 127, 65, 128, 72, synth.BF16, (2, 2), (1, 1), (1, 1)),    # stride 2: no shared line, tap by tap
+    (8, 70, 70, 104, 128, synth.F16, (1, 1), (1, 1), (2, 2)),      # dilation 2: tap by tap
+]
+
+
+@pytest.mark.parametrize("kind,irr", [("objects", 0.48), ("bernoulli", 0.5), ("objects", 0.95), ("objects", 0.0), ("objects", 1.0)])
+@pytest.mark.parametrize("layer", WORKGROUP_PER_CU)
+def test_a_workgroup_per_cu(layer, kind, irr):
+    torch = G.torch_mod()
+    n, h, w, ci, co, dtype, s, p, d = layer
+    geo = ((3, 3), s, p, d)
+    x, wt, bias = synth.activations_large((n, h, w, ci), dtype, 53, 1), synth.he_weights(co, 3, 3, ci, dtype, 53, 2), synth.bias(co, 53, 3)
+    mask = np.ones((n, h, w), np.uint8) if irr == 0 else np.zeros((n, h, w), np.uint8) if irr == 1 else \
+        (synth.mask_bernoulli if kind == "bernoulli" else synth.mask_objects)(n, h, w, irr, 53, 4)
+    xd, wd, bd = G.to_dev(x, dtype).clone(), G.to_dev(wt, dtype), torch.from_numpy(bias).to(G.dev())
+    xd[torch.from_numpy(mask == 0).to(G.dev())] = float("nan")
+    md = G.mask_dev(mask)
+    m_out = B.mask_downsample(md, *geo)
+    idx, count = B.active_index_compact(m_out)
+    keep = (O.mask_downsample(mask, 3, 3, s, p, d) != 0).reshape(-1)
+    positions = keep.size
+    assert -(-positions // 128) * 2 > 512 and positions <= 65536
+    outs = []
+    for out_dtype in (B.F32, None):
+        desc = B.conv_desc(n, h, w, ci, co, *geo, dtype, out_dtype, B.RELU | B.SKIP_ZERO_FILL)
+        out = torch.full((positions, co), 7.0, device=G.dev(), dtype=B.torch_dtype(B.F32 if out_dtype is not None else dtype))
+        B.focused_conv2d(desc, xd, wd, bd, mask_in=md, mask_out=m_out, idx=idx, count=count, out=out)
+        outs.append(out)
+    kd = torch.from_numpy(keep).to(G.dev())
+    assert bool((outs[0][~kd] == 7.0).all()) and torch.equal(outs[1], outs[0].to(outs[1].dtype))
+    if not keep.any():
+        return
+    assert bool(torch.isfinite(outs[0]).all())
+    at = np.sort(np.random.default_rng(53).choice(np.flatnonzero(keep), size=min(400, int(keep.sum())), replace=False))
+    want = O.focused_conv2d_at(O.ConvShape(n, h, w, ci, co, 3, 3, s, p, d, relu=True), x, wt, at, bias=bias, mask_in=mask, dtype=dtype)
+    got = outs[0][torch.from_numpy(at).to(G.dev())].cpu().numpy().astype(np.float64)
+    assert np.abs(got - want).max() / float(np.sqrt(np.mean(np.square(want)))) <= 1e-4     # the parity tests' bound

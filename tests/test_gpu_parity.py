@@ -465,18 +465,19 @@ def test_shared_halo_precomputed_list_and_16bit_output(layer):
 
 
 # Chained 3x3 layers (irrelevant rows left unwritten) of 65 .. 128 output channels and up to 65536
-# positions run on the one-workgroup-per-CU kernel: kept rows dealt out in 32-row blocks, one
-# pixel line per tile, tap by tap where a tile's line would not fit or the geometry has none
+# positions.  Those of more than 512 tiles of 128 x 64 run on the one-workgroup-per-CU kernel (kept rows dealt out in
+# 32-row blocks, one pixel line per tile, tap by tap where a tile's line would not fit or the geometry has none), the
+# others on the tiled ones; test_gpu_chained_tiles.py has more of the former.
 CHAINED_LINE_LAYERS = [
     # n, h, w, ci, co, k, s, p, d
-    (2, 40, 56, 64, 128, 3, 1, 1, 1),               # 4480 positions: a block or two per workgroup
-    (8, 96, 64, 72, 128, 3, 1, 1, 1),               # 49152 positions: several blocks per workgroup
+    (2, 40, 56, 64, 128, 3, 1, 1, 1),               # 4480 positions
+    (8, 96, 64, 72, 128, 3, 1, 1, 1),               # 49152 positions, packed taps
     (8, 96, 64, 64, 128, 3, 1, 1, 1),               # the same on 128-byte pixels: the resident-weights kernel
-    (16, 64, 64, 128, 128, 3, 1, 1, 1),             # the bench shape: two channel chunks, eight blocks when dense
+    (16, 64, 64, 128, 128, 3, 1, 1, 1),             # the bench shape: a workgroup per CU, two channel chunks, eight blocks when dense
     (3, 47, 61, 72, 96, 3, 1, 1, 1),                # channel tails on both sides, ragged rows
     (2, 61, 47, 64, 128, 3, (2, 1), (0, 2), (2, 1)),  # vertical stride and dilation, wide padding
-    (2, 63, 65, 64, 128, 3, 2, 1, 1),               # stride 2: no shared line, tap by tap
-    (1, 70, 70, 64, 104, 3, 1, 1, 2),               # dilation 2: tap by tap
+    (2, 63, 65, 64, 128, 3, 2, 1, 1),               # stride 2
+    (1, 70, 70, 64, 104, 3, 1, 1, 2),               # dilation 2
 ]
 
 
