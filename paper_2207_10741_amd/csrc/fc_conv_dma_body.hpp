@@ -362,9 +362,19 @@
 #pragma unroll
             for (int i = 0; i < PAIR_CH; ++i) mv[i] = 1u;
             if (mask_in) {
+                // (Instances with a pixel line use a branch per form of mask: without one their loop over the taps comes out with too few registers to hold
+                // a stage's fragment addresses ahead of its barrier, and the look-ups are a small part of their long reductions: 512 -> 512 on 32 x 15 x 20, 0.1 /
+                // 0.3 / 0.5 kept, 32.2 / 33.8 / 42.4 -> 30.2 / 32.0 / 41.2 us, E4M3 20.3 / 21.8 / 25.6 -> 18.6 / 20.0 / 24.4.  The tiles that label their own rows lose
+                // 0.2 us with it, 512 -> 512 stride 2 from 32 x 30 x 40 1.8.)
 #pragma unroll
-                for (int i = 0; i < PAIR_CH; ++i) mv[i] = mask_at(mask_in, ppix_[i], packed_masks);
-                loaded_together(mv);
+                for (int i = 0; i < PAIR_CH; ++i) {
+                    if constexpr (HALO)
+                        mv[i] = packed_masks ? (reinterpret_cast<const uint32_t *>(mask_in)[ppix_[i] >> 5] >> (uint32_t)(ppix_[i] & 31)) & 1u
+                                             : (uint32_t)mask_in[ppix_[i]];
+                    else
+                        mv[i] = mask_at(mask_in, ppix_[i], packed_masks);
+                }
+                if constexpr (!HALO) loaded_together(mv);
             }
 #pragma unroll
             for (int i = 0; i < PAIR_CH; ++i)
