@@ -494,9 +494,8 @@ static_assert(kSmallRows == kSmallChannels, "pixels take the place of the weight
 // A 1 KB load into LDS at base + at (a constant once inlined).
 __device__ __forceinline__ void once_load(const u32x4_t &rsrc, uint32_t byte_offset, uint32_t scalar_offset, uint32_t base, uint32_t at)
 {
-    uint32_t scalar; // (as in dma_load16_s)
-    __asm__ volatile("s_add_u32 m0, %1, %5\n\ts_mov_b32 %0, %4\n\tbuffer_load_dwordx4 %2, %3, %0 offen lds"
-                     : "=&s"(scalar)
+    __asm__ volatile("s_add_u32 m0, %0, %4\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                     :
                      : "s"(base), "v"(byte_offset), "s"(rsrc), "s"(scalar_offset), "n"(at)
                      : "memory", "scc");
 }
@@ -576,12 +575,13 @@ __global__ __launch_bounds__(64 * kSmallWaves, 1) void k_conv_small_once(Geom g,
     const int q_e = q0 + min(max(lane - (skip ? 1 : 0), 0), ST - 1);
     const int tap_e = (int)fast_div((uint32_t)q_e, cut.by_cch), kh_e = tap_e * 11 >> 5;
     const int w_e = q_e * 128, x_e = (kh_e * g.dh * g.w + (tap_e - 3 * kh_e)) * (int)pixel + (q_e - tap_e * cch) * 128, bit_e = 1 << tap_e;
-    uint32_t sw[ST];
+    uint32_t sw[ST]; // (all before the first load: a scalar register that the vector unit wrote may not be read by a load right after)
 #pragma unroll
     for (int e = 0; e < ST; ++e) {
         sw[e] = (uint32_t)__builtin_amdgcn_readlane(w_e, e);
         __asm__ volatile("" : "+s"(sw[e]));
     }
+    __asm__ volatile("s_nop 4");
 #pragma unroll
     for (int e = 0; e < ST; ++e)
 #pragma unroll

@@ -181,7 +181,7 @@ void k_conv_wide(Geom g, WideArgs wa, const unsigned char *__restrict__ x, const
                 wkh += wc;
             };
             auto issue_w = [&](int j, uint32_t buf) __attribute__((always_inline)) {
-                dma_load16_s(rsrc_w, woff, ld_sw + (uint32_t)j * RPL * wrow, lds_wave + W0 + (buf < 2 ? buf * WB : 0u - WB) + (uint32_t)j * (RPL * 128u));
+                dma_load16_any(rsrc_w, woff, ld_sw + (uint32_t)j * RPL * wrow, lds_wave + W0 + (buf < 2 ? buf * WB : 0u - WB) + (uint32_t)j * (RPL * 128u));
             };
             __syncthreads(); // the previous tile is done with LDS
 #pragma unroll
@@ -370,7 +370,7 @@ void k_conv_wide(Geom g, WideArgs wa, const unsigned char *__restrict__ x, const
                 };
                 auto issue_x = [&](int j, uint32_t buf) __attribute__((always_inline)) {
                     if (WHOLE || j < nxl)
-                        dma_load16_s(rsrc_x, (hxbits[j / PW] & (ld_sel << (NG * (j % PW)))) ? hxoff[j] : kOutOfRange, ld_sx, lds_wave + buf * XB + (uint32_t)j * (RPL * 128u));
+                        dma_load16_any(rsrc_x, (hxbits[j / PW] & (ld_sel << (NG * (j % PW)))) ? hxoff[j] : kOutOfRange, ld_sx, lds_wave + buf * XB + (uint32_t)j * (RPL * 128u));
                 };
                 // Zero stores of a stage: wave v clears the positions of its own label words, in whole 64-piece runs.  A run is one store
                 // instruction (a lane with nothing to clear is out of range), so that the waits can count them: z1 and z2 are those of the

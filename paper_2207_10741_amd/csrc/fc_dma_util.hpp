@@ -43,11 +43,21 @@ __device__ __forceinline__ void dma_load16(const u32x4_t &rsrc, uint32_t byte_of
 // the part of an address that is the same for every lane costs no vector arithmetic.  An
 // out-of-range `byte_offset` stays out of range whatever the scalar offset is (it is checked
 // against the descriptor's size less the scalar offset).
-// A memory instruction may read a scalar register no sooner than five wait states after the vector unit wrote it, and the
-// compiler, which brings spilled scalars back with v_readlane, keeps to that only for instructions of its own: the offset is
-// copied by the scalar unit, which does wait (and stands where M0 wants a wait state anyway).
+// A memory instruction may read a scalar register no sooner than five wait states after the vector unit wrote it, and the compiler, which brings
+// spilled scalars back with v_readlane, keeps to that only for instructions of its own: here the offset has to be the scalar unit's or old enough.
 __device__ __forceinline__ void dma_load16_s(const u32x4_t &rsrc, uint32_t byte_offset, uint32_t scalar_offset,
                                              uint32_t lds_addr)
+{
+    __asm__ volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                     :
+                     : "s"(lds_addr), "v"(byte_offset), "s"(rsrc), "s"(scalar_offset)
+                     : "memory");
+}
+
+// The same whatever wrote the offset: the scalar unit, which waits for the vector unit's write, copies it, where M0 wants a wait state anyway.  (In the
+// kernel of wide tiles, which spills its offsets, it costs nothing; a lone wave of k_conv_small pays 7 cycles a load for it, 0.2 us of 7.8.)
+__device__ __forceinline__ void dma_load16_any(const u32x4_t &rsrc, uint32_t byte_offset, uint32_t scalar_offset,
+                                               uint32_t lds_addr)
 {
     uint32_t scalar;
     __asm__ volatile("s_mov_b32 m0, %1\n\ts_mov_b32 %0, %4\n\tbuffer_load_dwordx4 %2, %3, %0 offen lds"
