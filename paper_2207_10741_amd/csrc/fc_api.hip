@@ -71,20 +71,22 @@ int32_t make_geom(const fc_conv_desc *d, Geom *g)
 // tiled kernel at a kept share of one half).  With the zero-fill in the launch the tiled kernel
 // stays: its idle workgroups clear rows beside the tiles, while a launch that keeps every CU
 // busy can only clear them after its tiles (measured: no gain at one half, slower elsewhere).
-// Smaller layers leave most workgroups here with a block or two a wave.  They stay on the tiled kernel while its 128 x 64 tiles are one round
-// however much the mask keeps: two a CU, one where image rows of a unit stride are too short for its pixel line.  Chained, list given, us at
-// 0.1 / 0.3 / 0.5 / 0.7 / 0.9 / 0.97 kept, here -> tiled: 128 -> 128 on 4 x 60 x 80 13.1 / 13.0 / 13.4 / 14.0 / 15.1 / 15.1 -> 11.1 / 11.8 / 10.8 / 11.1 / 14.0 / 14.1, on
-// 7 x 60 x 78 (512 tiles) 13.1 / 13.6 / 14.9 / 15.9 / 17.4 / 17.8 -> 11.2 / 10.8 / 14.0 / 14.7 / 15.6 / 16.0; 256 -> 128 there 19.5 / 20.6 / 23.0 / 24.7 / 26.7 / 27.2 -> 16.7 /
-// 16.4 / 21.8 / 22.9 / 24.2 / 24.8; short rows, 128 -> 128 on 20 x 28 x 29 (254) 13.3 / 13.5 / 13.7 / 13.7 / 14.3 / 14.4 -> 11.1 / 11.9 / 12.5 / 12.9 / 13.3 / 13.4; stride 2 onto 41 x
-// 28 x 28 (504) 16.5 / 20.4 / 21.1 / 21.9 / 22.6 / 22.8 -> 11.8 / 13.5 / 14.3 / 18.0 / 18.8 / 19.1.  Past that little kept still gains and much kept loses: on 8 x 60 x 80 13.3 / 14.0 / 15.5 / 17.1 /
-// 18.9 / 19.2 -> 11.9 / 11.0 / 14.4 / 15.4 / 23.2 / 23.3, stride 2 onto 8 x 60 x 80 16.7 / 20.5 / 21.4 / 22.3 / 23.9 / 24.2 -> 11.4 / 13.2 / 16.7 / 17.5 / 31.0 / 30.9, short rows
-// 24 x 28 x 28 13.3 / 13.5 / 13.8 / 14.0 / 15.2 / 15.4 -> 11.0 / 12.1 / 12.7 / 13.2 / 16.6 / 16.6.  With a mask and no list, where the compaction (or tiles that label their own rows) comes on
-// top, the two sides lie as far apart: 7 x 60 x 78 16.2 / 16.6 / 18.0 / 19.4 / 21.3 / 21.5 -> 14.2 / 13.9 / 17.3 / 18.2 / 19.3 / 19.9, 20 x 28 x 29 16.2 / 16.2 / 16.4 / 16.6 / 17.1 /
-// 17.5 -> 11.7 / 12.1 / 12.4 / 12.7 / 13.0 / 12.9, 8 x 60 x 80 16.5 / 17.0 / 19.1 / 21.3 / 22.9 / 23.3 -> 15.1 / 14.4 / 18.1 / 19.6 / 26.9 / 26.9.
+// Smaller layers leave most workgroups here with a block or two a wave, and the tiled kernel's 128 x 64 tiles of the kept rows are one round (two a CU) while
+// the mask keeps up to about three quarters of 44 000 positions.  Chained, list given, us at 0.1 / 0.3 / 0.5 / 0.7 / 0.9 / 0.97 kept, here -> tiled: 128 -> 128 on
+// 4 x 60 x 80 13.1 / 13.0 / 13.4 / 14.0 / 15.1 / 15.1 -> 11.1 / 11.8 / 10.8 / 11.1 / 14.0 / 14.1, on 7 x 60 x 78 13.1 / 13.6 / 14.9 / 15.9 / 17.4 / 17.8 -> 11.2 / 10.8 / 14.0 /
+// 14.7 / 15.6 / 16.0, on 8 x 60 x 80 13.3 / 14.0 / 15.5 / 17.1 / 18.9 / 19.2 -> 11.9 / 11.0 / 14.4 / 15.4 / 23.2 / 23.3; 256 -> 128 on 7 x 60 x 78 19.5 / 20.6 / 23.0 / 24.7 / 26.7 /
+// 27.2 -> 16.7 / 16.4 / 21.8 / 22.9 / 24.2 / 24.8; stride 2 onto 8 x 60 x 80 16.7 / 20.5 / 21.4 / 22.3 / 23.9 / 24.2 -> 11.4 / 13.2 / 16.7 / 17.5 / 31.0 / 30.9; past the line, 0.1 ... 0.9,
+// 12 x 60 x 80 13.8 / 15.8 / 17.9 / 20.6 / 23.4 -> 12.4 / 14.9 / 16.5 / 23.7 / 27.8, 16 x 64 x 64 13.9 / 16.0 / 19.6 / 22.4 / 25.7 -> 15.0 / 16.9 / 21.4 / 22.6 / 25.1.  Image rows too short for
+// the tiled kernel's pixel line: 20 x 28 x 29 13.3 / 13.5 / 13.7 / 13.7 / 14.3 / 14.4 -> 11.1 / 11.9 / 12.5 / 12.9 / 13.3 / 13.4, 24 x 28 x 28 13.3 / 13.5 / 13.8 / 14.0 / 15.2 / 15.4 -> 11.0 /
+// 12.1 / 12.7 / 13.2 / 16.6 / 16.6; past the line 32 x 28 x 28 13.5 / 14.0 / 14.6 / 15.8 / 16.4 -> 11.7 / 13.6 / 13.9 / 17.3 / 17.8.  The line lies where masks that keep 0.3 to
+// 0.7 have it; the count is the device's, and one that keeps nine tenths of 33 000 to 44 000 positions (short rows: 17 000 to 20 000) pays a second round, 9 to 30 %.  (A line at
+// one round of all positions' tiles takes nothing there and gave away 6 to 55 % at 0.3 to 0.7: a network of 627 us took 643.)  With a mask and no list, where the
+// compaction comes on top, the two lie as far apart: 7 x 60 x 78 16.2 / 16.6 / 18.0 / 19.4 / 21.3 / 21.5 -> 14.2 / 13.9 / 17.3 / 18.2 / 19.3 / 19.9, 20 x 28 x 29 16.2 / 16.2 / 16.4 / 16.6 /
+// 17.1 / 17.5 -> 11.7 / 12.1 / 12.4 / 12.7 / 13.0 / 12.9, 8 x 60 x 80 16.5 / 17.0 / 19.1 / 21.3 / 22.9 / 23.3 -> 15.1 / 14.4 / 18.1 / 19.6 / 26.9 / 26.9.
 bool conv_line_wanted(const Geom &g, int in_dtype, int out_dtype, bool focused)
 {
     if (!focused || !(g.flags & FC_SKIP_ZERO_FILL) || !conv_line_supported(g, in_dtype, out_dtype)) return false;
-    if ((int64_t)((g.m + 127) / 128) * ((g.c_out + 63) / 64) <= (g.wo >= 32 || g.sw > 1 ? 2 : 1) * conv_grid_cus()) return false;
+    if (g.m < (g.wo >= 32 ? 44000 : 20000)) return false;
     if (g.c_out <= 64 || g.c_out > 128 || taps_packed(g, in_dtype, focused)) return false;
     return (int64_t)(g.m + 31) / 32 <= 8 * 256;
 }

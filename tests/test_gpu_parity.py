@@ -465,7 +465,7 @@ def test_shared_halo_precomputed_list_and_16bit_output(layer):
 
 
 # Chained 3x3 layers (irrelevant rows left unwritten) of 65 .. 128 output channels and up to 65536
-# positions.  Those of more than 512 tiles of 128 x 64 run on the one-workgroup-per-CU kernel (kept rows dealt out in
+# positions.  Those from 44 000 positions on (short rows: 20 000) run on the one-workgroup-per-CU kernel (kept rows dealt out in
 # 32-row blocks, one pixel line per tile, tap by tap where a tile's line would not fit or the geometry has none), the
 # others on the tiled ones; test_gpu_chained_tiles.py has more of the former.
 CHAINED_LINE_LAYERS = [
