@@ -108,7 +108,9 @@
     // pixels of a row tile are read by one XCD per group, a group's weights by the XCDs that share it.  Against one
     // channel tile after another (half kept, chained): 256 -> 256 stride 2 from 32 x 60 x 80 reads 174 -> 68 MB past the L2s, 48.8 -> 43.2 us;
     // 1024 -> 512 on 32 x 30 x 40 167 -> 54 MB, 40.7 -> 36.8; 1024 -> 256 there 83 -> 46 MB, 25.2 -> 23.4; 512 -> 512 3x3 on 32 x 15 x 20
-    // 94 -> 30 MB, 45 -> 41.
+    // 94 -> 30 MB, over six masks each that keep 0.3 / 0.5 / 0.7 34.2 / 43.3 / 43.6 -> 33.7 / 42.3 / 42.8 (one mask by itself 39 to 46 either way: it decides which CUs
+    // get two tiles that go tap by tap).  What it costs shows where pixels and weights fit an L2 anyhow: 256 -> 256 on 8 x 30 x 40 16.8 -> 17.0, 128 -> 128 on
+    // 8 x 60 x 80 14.7 -> 15.0.
     const int n_mt = (rows + TM - 1) / TM;
     int nt_log = 0;
     {
