@@ -555,7 +555,7 @@ def grouped_bench(torch, B, synth, workloads, args):
 def masks_bench(torch, B, synth, workloads, args):
     """Mask propagation + ordered compaction at the mask sizes of the workloads, with byte masks and
     with packed masks (one bit per pixel): the mask pyramid (every level's mask and kept list from the
-    one input mask, two launches) and the single-level compaction of the first level.  Each figure is
+    one input mask, one or two launches) and the single-level compaction of the first level.  Each figure is
     a HIP-graph replay of four calls; GB/s = algorithmic bytes / time, where the algorithmic bytes are
     the input mask once, every level's mask written once and read once (the list pass), and four
     bytes per kept position."""
@@ -711,7 +711,7 @@ def main():
         L["host"] = L["host"][:3] + (mh,)
         L["kept"] = int(np.count_nonzero(mh))
         L["flops_kept"] = 2.0 * L["kept"] * L["k"] * L["c"]
-    # ... which the library builds, with all kept lists, from the first mask in two launches:
+    # ... which the library builds, with all kept lists, from the first mask in one or two launches:
     # the layer's own window, then three stride-2 3x3 windows
     pyramid = B.PreparedPyramid(layers[0]["mask"], [((3, 3), (1, 1), (1, 1), (1, 1))] +
                                 [((3, 3), (2, 2), (1, 1), (1, 1))] * (len(layers) - 1))
@@ -878,7 +878,7 @@ def main():
             "workload": ("" if in_dtype == B.BF16 else "E4M3 storage, %s outputs: " % ("E4M3" if out_dtype == B.FP8 else "bf16")) +
                         "ResNet-50 3x3 layer shapes (C64@128, C128@64, C256@32, C512@16), batch %d, "
                         "one %s mask per image with %.0f %% irrelevant, rescaled to the four resolutions; step = "
-                        "mask pyramid (propagation + compaction for all four layers, two launches) + focused "
+                        "mask pyramid (propagation + compaction for all four layers, one or two launches) + focused "
                         "conv + zero-fill per layer" % (batch, args.mask, 100 * irr),
             "batch": batch, "irrelevant": irr, "mask": args.mask,
             "kept_fraction": round(sum(L["kept"] for L in layers) / sum(L["m"] for L in layers), 4),
