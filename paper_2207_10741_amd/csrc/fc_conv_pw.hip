@@ -30,6 +30,7 @@
 // carries a nine-bit set of the taps it reads.  (Layers with a unit horizontal step have a kernel of their own, k_conv_res3.)
 #include "fc_dma_util.hpp"
 #include <atomic>
+#include <type_traits>
 
 namespace fc {
 
@@ -392,20 +393,21 @@ void k_conv_pw(Geom g, PwDivs dv, int kch_arg, const unsigned char *__restrict__
     auto store_bytes = [&](const f32x16_t *a, int cb, unsigned char *stg) {
         if constexpr (sizeof(TO) == 1) {
             if (cb * 32 >= co_left) return; // (a group wholly past the last channel)
+            auto pack = [&](auto relu) {
 #pragma unroll
-            for (int bl = 0; bl < GB; ++bl) {
+                for (int bl = 0; bl < GB; ++bl) {
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const float4 bq = *reinterpret_cast<const float4 *>(bias_s + (cb + bl) * 32 + q * 8 + half * 4);
-                    uint32_t pk;
-                    store4<ODT, TO>(reinterpret_cast<TO *>(&pk), a[bl][q * 4] + bq.x, a[bl][q * 4 + 1] + bq.y,
-                                    a[bl][q * 4 + 2] + bq.z, a[bl][q * 4 + 3] + bq.w);
-                    if (g.flags & FC_RELU) pk = relu_packed8(pk);
-                    const uint32_t at = (uint32_t)l32 * 128u + (uint32_t)((bl * 2 + (q >> 1)) ^ FC_SWZ(l32)) * 16u +
-                                        (uint32_t)((q & 1) * 8 + half * 4);
-                    *reinterpret_cast<uint32_t *>(stg + at) = pk;
+                    for (int q = 0; q < 4; ++q) {
+                        const float4 bq = *reinterpret_cast<const float4 *>(bias_s + (cb + bl) * 32 + q * 8 + half * 4);
+                        const uint32_t at = (uint32_t)l32 * 128u + (uint32_t)((bl * 2 + (q >> 1)) ^ FC_SWZ(l32)) * 16u +
+                                            (uint32_t)((q & 1) * 8 + half * 4);
+                        *reinterpret_cast<uint32_t *>(stg + at) = pack4_e4m3<relu>(a[bl][q * 4] + bq.x, a[bl][q * 4 + 1] + bq.y,
+                                                                                   a[bl][q * 4 + 2] + bq.z, a[bl][q * 4 + 3] + bq.w);
+                    }
                 }
-            }
+            };
+            if (g.flags & FC_RELU) pack(std::true_type());
+            else pack(std::false_type());
             __asm__ volatile("" ::: "memory");
             const bool inside = (lane & 7) < GB * 2 && cb * 32 + (lane & 7) * 16 < co_left; // this lane's 16 channels exist
 #pragma unroll
@@ -476,6 +478,7 @@ void k_conv_pw(Geom g, PwDivs dv, int kch_arg, const unsigned char *__restrict__
                 const unsigned char *ws = smem_raw + (size_t)(c * COUT + gb * 32) * 128u;
 #pragma unroll
                 for (int kk = 0; kk < KK; ++kk) {
+                    if (DT == FC_FP8 && KCT == 1 && (uint32_t)kk * KSTEP >= row_bytes) break;      // (half a chunk: 64 channels)
                     Frag<DT> wf[GB];
 #pragma unroll
                     for (int b = 0; b < GB; ++b) wf[b].load(ws + b * 4096, frag ^ ((uint32_t)kk * KSTEP));
