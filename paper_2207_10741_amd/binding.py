@@ -29,7 +29,7 @@ FUNCTIONS = ("fc_status_string", "fc_out_dims", "fc_workspace_bytes", "fc_compac
              "fc_mask_pyramid_packed",
              "fc_expand_group_weights",
              "fc_focused_dwconv2d",
-             "fc_maxpool2d", "fc_maxpool2d_masked", "fc_run_calls")
+             "fc_maxpool2d", "fc_maxpool2d_masked", "fc_run_calls", "fc_run_calls_unseen")
 MAX_PYRAMID_LEVELS = 8
 
 
@@ -145,6 +145,8 @@ def lib():
         L.fc_maxpool2d_masked.argtypes = [vp] + [i32] * 8 + [vp, vp, vp]
         L.fc_run_calls.restype = i32
         L.fc_run_calls.argtypes = [ctypes.POINTER(Call), i32, ctypes.POINTER(vp), i32, vp, ctypes.c_size_t, vp]
+        L.fc_run_calls_unseen.restype = i32
+        L.fc_run_calls_unseen.argtypes = [ctypes.POINTER(Call), i32, ctypes.c_char_p, ctypes.POINTER(vp), i32, vp, ctypes.c_size_t, vp]
         _lib = L
     return _lib
 
@@ -614,9 +616,12 @@ def maxpool2d(x, k: int, stride: int, pad: int, dtype: int, out=None, stream=Non
     return out
 
 
-def run_calls(calls, slots, workspace, stream=None):
+def run_calls(calls, slots, workspace, stream=None, unseen=None):
     """fc_run_calls: `calls` a ctypes array of Call, `slots` a ctypes array of device addresses (c_void_p).
-    The caller keeps the tensors behind the addresses alive."""
+    The caller keeps the tensors behind the addresses alive.  unseen: a byte per call, nonzero where only the next call
+    reads the output (fc_run_calls_unseen)."""
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(lib().fc_run_calls(calls, len(calls), slots, len(slots), _ptr(workspace), ws_bytes, _stream(stream)),
+    if unseen is not None and len(unseen) != len(calls):
+        raise ValueError("one byte per call")
+    _check(lib().fc_run_calls_unseen(calls, len(calls), unseen, slots, len(slots), _ptr(workspace), ws_bytes, _stream(stream)),
            "fc_run_calls")

@@ -210,6 +210,37 @@ ConvWorkspace conv_ws_layout(const Geom &g)
 
 } // namespace
 
+// Two layers of a sequence as one launch, where the first one's output is read by the second alone and seen by nobody: false
+// if they are to be enqueued one by one (and any error of theirs to be found there).
+static bool try_pair(const fc_conv_desc *d1, const fc_conv_desc *d2, const void *x, const void *mask1, const void *w1, const float *bias1,
+                     const void *w2, const float *bias2, const int32_t *idx, const int32_t *count, const void *mask2, const void *mid, void *out,
+                     hipStream_t s, hipError_t *e)
+{
+    Geom g1, g2;
+    if (make_geom(d1, &g1) != FC_OK || make_geom(d2, &g2) != FC_OK) return false;
+    const int dtype = d1->in_dtype;
+    if (d1->out_dtype != dtype || d2->in_dtype != dtype || d2->out_dtype != dtype || !conv_pair_supported(g1, g2, dtype)) return false;
+    // what each call asks for by itself
+    for (const void *p : {x, w1, w2, mid, (const void *)out})
+        if (!p || !aligned16(p)) return false;
+    if (!aligned16(idx) || !aligned16(bias1) || !aligned16(bias2) || (idx == nullptr) != (count == nullptr)) return false;
+    // the same rows: a list with the masks that gate the taps, or all of them
+    if (idx ? !mask1 || !mask2 : mask1 || mask2) return false;
+    if (!idx && ((g1.flags | g2.flags) & (FC_COMPACT_IN | FC_COMPACT_OUT))) return false;
+    // the first layer's rows lie as the second one takes them; irrelevant rows of the output stay as they are
+    if (((g1.flags & FC_COMPACT_OUT) != 0) != ((g2.flags & FC_COMPACT_IN) != 0)) return false;
+    if (idx && !(g2.flags & (FC_SKIP_ZERO_FILL | FC_COMPACT_OUT))) return false;
+    // neither call would have been refused, and one launch reads x while it writes out
+    if (conv_tensors_overlap(g1, d1, x, mid) || conv_tensors_overlap(g2, d2, mid, out) ||
+        ranges_overlap(x, (size_t)g1.n * g1.h * g1.w * g1.c_in * dtype_bytes(dtype), out, (size_t)g2.m * g2.c_out * dtype_bytes(dtype)))
+        return false;
+    const bool pw1 = conv_pw_wanted(g1, dtype, dtype, idx != nullptr), pw2 = conv_pw_wanted(g2, dtype, dtype, idx != nullptr);
+    // (a reduction that is split is summed in another order)
+    if ((!pw1 && split_k_reachable(g1, dtype, idx != nullptr)) || (!pw2 && split_k_reachable(g2, dtype, idx != nullptr))) return false;
+    *e = launch_conv_pair(g1, g2, dtype, !pw1, !pw2, x, w1, bias1, w2, bias2, idx, count, out, s);
+    return true;
+}
+
 // (sizes of its own, not those of a dispatch rule: a line that moves there must not move last bits here)
 bool fc::conv_res3_bias_last(const Geom &g, bool masked)
 {
@@ -851,6 +882,12 @@ int32_t fc_calibrate_issue(int32_t mode, int32_t waves_per_simd, int32_t steps, 
 int32_t fc_run_calls(const fc_call *calls, int32_t n_calls, void *const *slots, int32_t n_slots, void *workspace,
                      size_t workspace_bytes, void *stream)
 {
+    return fc_run_calls_unseen(calls, n_calls, nullptr, slots, n_slots, workspace, workspace_bytes, stream);
+}
+
+int32_t fc_run_calls_unseen(const fc_call *calls, int32_t n_calls, const uint8_t *unseen, void *const *slots, int32_t n_slots,
+                            void *workspace, size_t workspace_bytes, void *stream)
+{
     if (!calls || !slots) return FC_ERR_NULL;
     if (n_calls < 0 || n_slots < 0) return FC_ERR_SHAPE;
     for (int32_t i = 0; i < n_calls; ++i) {
@@ -865,6 +902,18 @@ int32_t fc_run_calls(const fc_call *calls, int32_t n_calls, void *const *slots, 
         const fc_call &c = calls[i];
         const fc_conv_desc &d = c.desc;
         int32_t rc;
+        if (unseen && unseen[i] && i + 1 < n_calls) {
+            const fc_call &r = calls[i + 1];
+            hipError_t e;
+            if (c.kind == FC_CALL_CONV && r.kind == FC_CALL_CONV && r.x == c.out && c.idx == r.idx && c.count == r.count &&
+                try_pair(&d, &r.desc, at(c.x), at(c.mask_in), at(c.w), (const float *)at(c.bias),
+                at(r.w), (const float *)at(r.bias), (const int32_t *)at(c.idx), (const int32_t *)at(c.count), at(r.mask_in), at(c.out), at(r.out),
+                (hipStream_t)stream, &e)) {
+                if (e != hipSuccess) return FC_ERR_HIP;
+                ++i;
+                continue;
+            }
+        }
         if (c.kind == FC_CALL_CONV)
             rc = fc_focused_conv2d(&d, at(c.x), (const uint8_t *)at(c.mask_in), at(c.w), (const float *)at(c.bias),
                                    (const uint8_t *)at(c.mask_out), (const int32_t *)at(c.idx),

@@ -1,0 +1,527 @@
+// Two focused 1x1 layers one after the other on the gfx950 matrix cores, the second the only reader of the first: the
+// feature map between them stays in registers.
+//
+// A chained network is full of such pairs: a bottleneck's expansion and the next one's reduction (64 -> 256 -> 64), an
+// inverted residual's projection and the next one's expansion (192 -> 32 -> 192).  As two launches the wide map goes
+// through memory twice, or the launch and its chain of round trips (count, list, rows) is paid twice for a few
+// microseconds of work.  Both layers see the same kept rows (1x1, unit stride), so a wave that owns 32 rows needs
+// nothing but the weights: those of both layers stay in LDS for the whole launch, and each wave is a pipeline of its own
+// over units of 32 rows as in k_conv_pw (rows gathered by loads into LDS ahead of their use, no barrier after the prologue).
+//
+// The first layer's accumulators become the second one's operand without leaving the wave.  A lane of a product holds four
+// runs of four channels of its row, the runs of the two lane halves interleaved; rounded and packed, one exchange between the halves
+// (v_permlane32_swap) per packed register gives every lane the channels that the next product takes from it.  Operands, the order of the
+// steps and the place where the bias is added are those of the kernel that serves each layer by itself, so the sums are the same
+// bit for bit.
+//
+// What bounds it: the matrix and vector work of a unit (a block of the middle is 8 products and 40 vector instructions; 64 -> 256 -> 64
+// on 32 x 120 x 160, half kept, moves 82 MB in 35 us) on large layers, round trips and the fetch of the weights on small ones.
+// us, two launches -> one, half kept, inside a network: 64 -> 256 -> 64 there 35 + 43 -> 35, E4M3 32 + 20 -> 31; 32 -> 16 -> 96 on
+// 32 x 112 x 112 9.2 + 14.7 -> 17.3; 144 -> 24 -> 144 on 32 x 56 x 56 8.4 + 9.4 -> 12.0; 192 -> 32 -> 192 on 32 x 28 x 28 5.0 + 7.4 -> 7.7;
+// 384 -> 64 -> 384 on 32 x 14 x 14 6.2 + 7.0 -> 9.9.
+//
+// WIDE: the middle is wider than the output (at most NB * 32 channels): the output's accumulators stay, the middle is made
+// two blocks of 32 channels at a time.  Else the middle is at most NB * 32 channels: it is made whole, the output two blocks at
+// a time.
+#include "fc_dma_util.hpp"
+#include <algorithm>
+#include <atomic>
+#include <type_traits>
+
+namespace fc {
+
+constexpr uint32_t kPairChunkBytes = 32u * 128u;    // a chunk buffer: 32 rows of 128 bytes
+constexpr uint32_t kPairLdsBytes = 160u * 1024u;
+constexpr uint32_t pair_wave_bytes(int ring) { return (uint32_t)ring * kPairChunkBytes + 256u; }   // + a unit's list entries
+
+constexpr uint32_t kPairRelu1 = 1, kPairRelu2 = 2, kPairCompactIn = 4, kPairCompactOut = 8, kPairBiasFirst1 = 16, kPairBiasFirst2 = 32;
+
+struct PairArgs {
+    int32_t x_rows, m;                  // rows of x, output positions
+    int32_t c_in, c_mid, c_out;
+    int32_t kch, ring;                  // 128-byte chunks of an input row, chunk buffers of a wave
+    int32_t active, team;               // waves that own rows (the others load weights); log2 of those that share a unit's output channels
+    int32_t mid_rows, out_rows;         // rows of the two weight matrices in LDS
+    uint32_t flags;
+};
+
+// the lower halves of b <-> the upper halves of a
+__device__ __forceinline__ void swap_halves(uint32_t &a, uint32_t &b)
+{
+    typedef uint32_t u32x2_sw __attribute__((ext_vector_type(2)));
+    const u32x2_sw r = __builtin_bit_cast(u32x2_sw, __builtin_amdgcn_permlane32_swap(a, b, false, false));
+    a = r.x;
+    b = r.y;
+}
+
+template <int DT, typename TO, int NB, bool WIDE>
+__global__ __launch_bounds__(sizeof(TO) == 1 ? 512 : 768, 1)
+void k_conv_pair(PairArgs a, const int32_t *__restrict__ count, const int32_t *__restrict__ idx, const unsigned char *__restrict__ x,
+                 const unsigned char *__restrict__ w1, const float *__restrict__ bias1, const unsigned char *__restrict__ w2,
+                 const float *__restrict__ bias2, TO *__restrict__ out)
+{
+    static_assert(sizeof(TO) == (DT == FC_FP8 ? 1 : 2), "both layers store what they read");
+    static_assert(WIDE || DT != FC_FP8, "a narrow middle: 16-bit storage");
+    constexpr int ES = DT == FC_FP8 ? 1 : 2;
+    constexpr uint32_t KSTEP = kStepBytes<DT>;
+    constexpr int KK = 128 / (int)KSTEP;                // products of a chunk
+    constexpr int MB = WIDE ? 2 : NB;                   // middle blocks made at a time
+    constexpr int OB = WIDE ? NB : 2;                   // output blocks made at a time
+
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    const uint32_t lds0 = (uint32_t)reinterpret_cast<uintptr_t>(smem_raw);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = (int)blockDim.x >> 6;
+    const int l32 = lane & 31, half = lane >> 5;
+    const int mid_chunks = (a.c_mid * ES + 127) >> 7;
+    const uint32_t w1_bytes = (uint32_t)a.kch * (uint32_t)a.mid_rows * 128u, w2_bytes = (uint32_t)mid_chunks * (uint32_t)a.out_rows * 128u;
+    const uint32_t bias_at = w1_bytes + w2_bytes;
+    const int b1_room = (a.mid_rows + 63) & ~63;    // (a wave load brings 64 values; out_rows is a multiple of 64)
+    const uint32_t waves_at = bias_at + (uint32_t)(b1_room + a.out_rows) * 4u;
+    const unsigned char *const w1s = smem_raw, *const w2s = smem_raw + w1_bytes;
+    const float *const b1s = reinterpret_cast<const float *>(smem_raw + bias_at), *const b2s = b1s + b1_room;
+    const uint32_t my_at = waves_at + (uint32_t)wave * pair_wave_bytes(a.ring);
+    unsigned char *const my = smem_raw + my_at;
+    const uint32_t my0 = lds0 + my_at, idx0 = my0 + (uint32_t)a.ring * kPairChunkBytes;
+    const int32_t *const idx_w = reinterpret_cast<const int32_t *>(my + (uint32_t)a.ring * kPairChunkBytes);
+
+    const bool compact_in = (a.flags & kPairCompactIn) != 0, compact_out = (a.flags & kPairCompactOut) != 0;
+    const bool first1 = (a.flags & kPairBiasFirst1) != 0, first2 = (a.flags & kPairBiasFirst2) != 0;
+    const int rows = __builtin_amdgcn_readfirstlane(idx ? *count : a.m);
+    const bool use_list = idx && !(compact_in && compact_out);      // (row j in, row j out: the list is not read)
+    const bool stream_out = (int64_t)rows * a.c_out * (int)sizeof(TO) > (256ll << 20);     // (see k_conv_pw)
+
+    // ---- the weights: rows of 128 bytes by chunk, their 16-byte pieces swizzled by the row; what lies past the last
+    // channel on either side arrives as zeros.  Nobody waits for them before the first rows are on their way. ----
+    const bool all_load = a.active == nw;
+    const int loader = all_load ? wave : wave - a.active, loaders = all_load ? nw : nw - a.active;
+    auto load_weights = [&](const unsigned char *w, int c_from, int c_to, int chunks, int rows_w, uint32_t at) {
+        const u32x4_t rsrc = make_rsrc_words(w, (uint32_t)c_to * (uint32_t)c_from * (uint32_t)ES);
+        const int pieces = (c_from * ES) >> 4;
+        for (int ch = 0; ch < chunks; ++ch)
+            for (int r0 = loader * 8; r0 < rows_w; r0 += loaders * 8) {
+                const int row = r0 + (lane >> 3), piece = ch * 8 + ((lane & 7) ^ (int)FC_SWZ(row));
+                const bool ok = row < c_to && piece < pieces;
+                dma_load16(rsrc, ok ? (uint32_t)row * (uint32_t)c_from * (uint32_t)ES + (uint32_t)piece * 16u : kOutOfRange,
+                           lds0 + at + ((uint32_t)ch * (uint32_t)rows_w + (uint32_t)r0) * 128u);
+            }
+    };
+    if (loader >= 0) {
+        load_weights(w1, a.c_in, a.c_mid, a.kch, a.mid_rows, 0u);
+        load_weights(w2, a.c_mid, a.c_out, mid_chunks, a.out_rows, w1_bytes);
+        const u32x4_t rsrc_1 = make_rsrc_words(bias1, bias1 ? (uint32_t)a.c_mid * 4u : 0u);
+        const u32x4_t rsrc_2 = make_rsrc_words(bias2, bias2 ? (uint32_t)a.c_out * 4u : 0u);
+        for (int i = loader * 64; i < b1_room; i += loaders * 64) dma_load4(rsrc_1, (uint32_t)(i + lane) * 4u, lds0 + bias_at + (uint32_t)i * 4u);
+        for (int i = loader * 64; i < a.out_rows; i += loaders * 64)
+            dma_load4(rsrc_2, (uint32_t)(i + lane) * 4u, lds0 + bias_at + (uint32_t)(b1_room + i) * 4u);
+    }
+
+    // ---- my share of the kept rows: units of 32, XCD j (workgroups b = j mod 8) takes the j-th contiguous eighth ----
+    const int teams = a.active >> a.team, team = wave >> a.team, member = wave - (team << a.team);
+    const int nwv = (int)gridDim.x * teams;
+    const int wv = ((int)(blockIdx.x & 7) * ((int)gridDim.x >> 3) + (int)(blockIdx.x >> 3)) * teams + team;
+    const int nb = (rows + 31) >> 5;
+    const int share_q = nb / nwv, share_r = nb - share_q * nwv;
+    const int b0 = wv * share_q + (wv * share_r) / nwv;
+    const int nu = wave < a.active ? (wv + 1) * share_q + ((wv + 1) * share_r) / nwv - b0 : 0;
+
+    const uint32_t row_bytes = (uint32_t)a.c_in * (uint32_t)ES;
+    const u32x4_t rsrc_x = make_rsrc_words(x, (uint32_t)a.x_rows * row_bytes);
+    const u32x4_t rsrc_i = make_rsrc_words(idx, (uint32_t)rows * 4u);
+    // the last chunk of a row may be short: bit j says whether the piece this lane gathers in wave load j lies inside the row there
+    const int tail8 = (int)(row_bytes >> 4) - (a.kch - 1) * 8;
+    uint32_t tail_ok = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) tail_ok |= (uint32_t)(((lane & 7) ^ (int)FC_SWZ(j * 8 + (lane >> 3))) < tail8) << j;
+
+    int issued = 0, mark_idx = 0;
+    auto issue_idx = [&](int v) {
+        if (!use_list) return;
+        const uint32_t r = (uint32_t)(b0 + v) * 32u + (uint32_t)lane;
+        lds_reads_done();
+        dma_load4(rsrc_i, lane < 32 ? r * 4u : kOutOfRange, idx0);
+        issued += 1;
+        mark_idx = issued;
+    };
+    // a unit's rows: where row 8j + lane / 8 is stored (-1: no row) and the byte offset of the piece of it that this lane gathers
+    int st_pr[2][4];
+    uint32_t st_off[2][4];
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) st_off[k][j] = kOutOfRange, st_pr[k][j] = -1;
+    auto setup = [&](int v, int k) {
+        const int r = (b0 + v) * 32 + l32;
+        const bool valid = r < rows;
+        int p = r;
+        if (use_list) {
+            wait_vmcnt_upto(issued - mark_idx);
+            p = idx_w[l32];
+        }
+        const uint32_t off = valid ? (uint32_t)(compact_in ? r : p) * row_bytes : kOutOfRange;
+        const int to = valid ? (compact_out ? r : p) : -1;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int row = j * 8 + (lane >> 3);
+            const uint32_t o = (uint32_t)__shfl((int)off, row, 64);
+            st_off[k][j] = o == kOutOfRange ? o : o + (uint32_t)((lane & 7) ^ FC_SWZ(row)) * 16u;
+            st_pr[k][j] = __shfl(to, row, 64);
+        }
+    };
+    // (all of this is the same for the whole wave; the compiler loses sight of that where the loops over chunks meet)
+    // chunks sent for and not yet used up, the next one to send for (of unit u + ahead_unit) and its buffer
+    int u = 0, ahead = 0, ahead_unit = 0, ahead_chunk = 0, ahead_buf = 0;
+    auto send = [&]() {
+        while (__builtin_amdgcn_readfirstlane(ahead) < a.ring) {
+            ahead_chunk = __builtin_amdgcn_readfirstlane(ahead_chunk);
+            ahead_unit = __builtin_amdgcn_readfirstlane(ahead_unit);
+            ahead_buf = __builtin_amdgcn_readfirstlane(ahead_buf);
+            if (ahead_chunk == a.kch) {
+                if (ahead_unit == 1 || u + 1 >= nu) return;     // (two units' rows are held)
+                setup(u + 1, 1);
+                if (u + 2 < nu) issue_idx(u + 2);
+                ahead_unit = 1;
+                ahead_chunk = 0;
+            }
+            lds_reads_done();
+            const bool last = ahead_chunk == a.kch - 1;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t o = ahead_unit ? st_off[1][j] : st_off[0][j];
+                dma_load16_s(rsrc_x, last && !((tail_ok >> j) & 1u) ? kOutOfRange : o, (uint32_t)ahead_chunk * 128u,
+                             my0 + (uint32_t)ahead_buf * kPairChunkBytes + (uint32_t)j * 1024u);
+            }
+            issued += 4;
+            ++ahead;
+            ++ahead_chunk;
+            ahead_buf = ahead_buf + 1 == a.ring ? 0 : ahead_buf + 1;
+        }
+    };
+
+    // lane reads row (lane & 31), in step kk the 16-byte piece 2 kk + half (8-bit storage: 4 kk + 2 half and the next)
+    const uint32_t frag = (uint32_t)l32 * 128u + (uint32_t)((half * (int)(KSTEP / 32u)) ^ FC_SWZ(l32)) * 16u;
+
+    auto start = [&](f32x16_t &v, const float *bias, int block, bool first) {
+        if (first) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float4 b = *reinterpret_cast<const float4 *>(bias + block * 32 + q * 8 + half * 4);
+                v[q * 4] = b.x, v[q * 4 + 1] = b.y, v[q * 4 + 2] = b.z, v[q * 4 + 3] = b.w;
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) v[i] = 0.f;
+        }
+    };
+    auto finish = [&](f32x16_t &v, const float *bias, int block, bool first) {
+        if (first) return;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float4 b = *reinterpret_cast<const float4 *>(bias + block * 32 + q * 8 + half * 4);
+            v[q * 4] += b.x, v[q * 4 + 1] += b.y, v[q * 4 + 2] += b.z, v[q * 4 + 3] += b.w;
+        }
+    };
+    // one or (8-bit storage) two middle blocks -> the second layer's operands: rounded as the first layer's output is
+    auto middle = [&](f32x16_t *acc, int block0, Frag<DT> *h) {
+#pragma unroll
+        for (int b = 0; b < MB; ++b) finish(acc[b], b1s, block0 + b, first1);
+        if constexpr (sizeof(TO) == 2) {
+#pragma unroll
+            for (int b = 0; b < MB; ++b) {
+                uint2 run[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    store4<DT, TO>(reinterpret_cast<TO *>(&run[q]), acc[b][q * 4], acc[b][q * 4 + 1], acc[b][q * 4 + 2], acc[b][q * 4 + 3]);
+                    if (a.flags & kPairRelu1) run[q].x = relu_packed16(run[q].x), run[q].y = relu_packed16(run[q].y);
+                }
+#pragma unroll
+                for (int q = 0; q < 4; q += 2) {
+                    swap_halves(run[q].x, run[q + 1].x);
+                    swap_halves(run[q].y, run[q + 1].y);
+                    h[b * 2 + (q >> 1)].v = make_uint4(run[q].x, run[q].y, run[q + 1].x, run[q + 1].y);
+                }
+            }
+        } else {
+            uint32_t run[2][4];
+            auto pack = [&](auto relu) {
+#pragma unroll
+                for (int b = 0; b < 2; ++b)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        run[b][q] = pack4_e4m3<relu>(acc[b][q * 4], acc[b][q * 4 + 1], acc[b][q * 4 + 2], acc[b][q * 4 + 3]);
+            };
+            if (a.flags & kPairRelu1) pack(std::true_type());
+            else pack(std::false_type());
+#pragma unroll
+            for (int q = 0; q < 4; ++q) swap_halves(run[0][q], run[1][q]);
+            h[0].v = make_uint4(run[0][0], run[1][0], run[0][1], run[1][1]);
+            h[0].v2 = make_uint4(run[0][2], run[1][2], run[0][3], run[1][3]);
+        }
+    };
+
+    // output blocks leave through LDS (the buffer of the chunk just used up) as whole lines: two blocks of a 16-bit type, or
+    // NB blocks of bytes
+    constexpr int SB = sizeof(TO) == 2 ? 2 : OB;
+    auto store = [&](f32x16_t *acc, int block0, unsigned char *stg) {
+        if (block0 * 32 >= a.c_out) return;
+        if constexpr (sizeof(TO) == 2) {
+#pragma unroll
+            for (int b = 0; b < SB; ++b) {
+                finish(acc[b], b2s, block0 + b, first2);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    uint2 pk;
+                    store4<DT, TO>(reinterpret_cast<TO *>(&pk), acc[b][q * 4], acc[b][q * 4 + 1], acc[b][q * 4 + 2], acc[b][q * 4 + 3]);
+                    if (a.flags & kPairRelu2) pk.x = relu_packed16(pk.x), pk.y = relu_packed16(pk.y);
+                    *reinterpret_cast<uint2 *>(stg + (uint32_t)l32 * 128u + (uint32_t)((b * 4 + q) ^ FC_SWZ(l32)) * 16u + (uint32_t)half * 8u) = pk;
+                }
+            }
+        } else {
+            auto pack = [&](auto relu) {
+#pragma unroll
+                for (int b = 0; b < SB; ++b) {
+                    finish(acc[b], b2s, block0 + b, first2);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        *reinterpret_cast<uint32_t *>(stg + (uint32_t)l32 * 128u + (uint32_t)((b * 2 + (q >> 1)) ^ FC_SWZ(l32)) * 16u +
+                                                      (uint32_t)((q & 1) * 8 + half * 4)) =
+                            pack4_e4m3<relu>(acc[b][q * 4], acc[b][q * 4 + 1], acc[b][q * 4 + 2], acc[b][q * 4 + 3]);
+                }
+            };
+            if (a.flags & kPairRelu2) pack(std::true_type());
+            else pack(std::false_type());
+        }
+        wave_lds_order();
+        const int per_row = SB * 2 * (int)sizeof(TO);           // 16-byte pieces of a row
+        const bool inside = (lane & 7) < per_row && block0 * 32 + (lane & 7) * (16 / (int)sizeof(TO)) < a.c_out;
+        u32x4_t piece[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int row = j * 8 + (lane >> 3);
+            piece[j] = *reinterpret_cast<const u32x4_t *>(stg + (uint32_t)row * 128u + (uint32_t)((lane & 7) ^ FC_SWZ(row)) * 16u);
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int pr = st_pr[0][j];
+            u32x4_t *to = reinterpret_cast<u32x4_t *>(out + (int64_t)(pr < 0 ? 0 : pr) * a.c_out + block0 * 32 + (lane & 7) * (16 / (int)sizeof(TO)));
+            if (pr >= 0 && inside) {
+                if (stream_out)
+                    __asm__ volatile("global_store_dwordx4 %0, %1, off nt" : : "v"(to), "v"(piece[j]) : "memory");
+                else
+                    *to = piece[j];
+            }
+        }
+        wave_lds_order();
+    };
+
+    if (nu > 0) {
+        issue_idx(0);
+        setup(0, 0);
+        if (nu > 1) issue_idx(1);
+        send();
+    }
+    // (this wave's share of the weights was requested before everything counted in `issued`)
+    wait_vmcnt_upto(issued);
+    __syncthreads();
+
+    // (narrow) the output blocks of this member of the team
+    [[maybe_unused]] const int out_from = ((a.out_rows >> 6) * member >> a.team) * 2, out_to = ((a.out_rows >> 6) * (member + 1) >> a.team) * 2;
+    int buf = 0;
+    for (; u < nu; ++u) {
+        const unsigned char *xs = my;
+        Frag<DT> h[sizeof(TO) == 2 ? MB * 2 : 1];
+        f32x16_t acc1[MB], acc2[OB];
+        if constexpr (WIDE) {
+            send();
+            wait_vmcnt_upto(4 * (ahead - 1));
+            xs = my + (uint32_t)buf * kPairChunkBytes;
+            Frag<DT> xf[KK];
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk) xf[kk].load(xs, frag ^ ((uint32_t)kk * KSTEP));
+            --ahead;
+#pragma unroll
+            for (int b = 0; b < OB; ++b) start(acc2[b], b2s, b, first2);
+#pragma unroll 1
+            for (int block = 0; block * 32 < a.c_mid; block += 2) {
+#pragma unroll
+                for (int b = 0; b < 2; ++b) start(acc1[b], b1s, block + b, first1);
+#pragma unroll
+                for (int kk = 0; kk < KK; ++kk) {
+                    if (DT == FC_FP8 && (uint32_t)kk * KSTEP >= row_bytes) break;      // (half a chunk: 64 channels)
+                    Frag<DT> wf[2];
+#pragma unroll
+                    for (int b = 0; b < 2; ++b) wf[b].load(w1s + (block + b) * 4096, frag ^ ((uint32_t)kk * KSTEP));
+#pragma unroll
+                    for (int b = 0; b < 2; ++b) acc1[b] = mfma32<DT>(wf[b], xf[kk], acc1[b]);
+                }
+                middle(acc1, block, h);
+                // (the middle's chunk of these blocks, and the first step of it they are: bytes lie four blocks to a chunk)
+                const unsigned char *ws = w2s + (uint32_t)(sizeof(TO) == 2 ? block >> 1 : block >> 2) * (uint32_t)a.out_rows * 128u;
+                const int kk0 = sizeof(TO) == 2 ? 0 : (block >> 1) & 1;
+#pragma unroll
+                for (int kk = 0; kk < (sizeof(TO) == 2 ? KK : 1); ++kk) {
+                    Frag<DT> wf[OB];
+#pragma unroll
+                    for (int b = 0; b < OB; ++b) wf[b].load(ws + b * 4096, frag ^ ((uint32_t)(kk0 + kk) * KSTEP));
+#pragma unroll
+                    for (int b = 0; b < OB; ++b) acc2[b] = mfma32<DT>(wf[b], h[kk], acc2[b]);
+                }
+            }
+#pragma unroll
+            for (int b = 0; b < OB; b += SB) store(acc2 + b, b, my + (uint32_t)buf * kPairChunkBytes);
+            buf = buf + 1 == a.ring ? 0 : buf + 1;
+        } else {
+#pragma unroll
+            for (int b = 0; b < MB; ++b) start(acc1[b], b1s, b, first1);
+            for (int c = 0; c < a.kch; ++c) {
+                send();
+                wait_vmcnt_upto(4 * (ahead - 1));
+                xs = my + (uint32_t)buf * kPairChunkBytes;
+                const unsigned char *ws = w1s + (uint32_t)c * (uint32_t)a.mid_rows * 128u;
+#pragma unroll
+                for (int kk = 0; kk < KK; ++kk) {
+                    Frag<DT> xf, wf[MB];
+                    xf.load(xs, frag ^ ((uint32_t)kk * KSTEP));
+#pragma unroll
+                    for (int b = 0; b < MB; ++b) wf[b].load(ws + b * 4096, frag ^ ((uint32_t)kk * KSTEP));
+#pragma unroll
+                    for (int b = 0; b < MB; ++b) acc1[b] = mfma32<DT>(wf[b], xf, acc1[b]);
+                }
+                --ahead;
+                buf = buf + 1 == a.ring ? 0 : buf + 1;
+            }
+            middle(acc1, 0, h);
+            unsigned char *const stg = const_cast<unsigned char *>(xs);
+#pragma unroll 1
+            for (int block = out_from; block < out_to; block += 2) {
+#pragma unroll
+                for (int b = 0; b < 2; ++b) start(acc2[b], b2s, block + b, first2);
+#pragma unroll
+                for (int kk = 0; kk < 2 * MB; ++kk) {
+                    Frag<DT> wf[2];
+#pragma unroll
+                    for (int b = 0; b < 2; ++b) wf[b].load(w2s + (uint32_t)(block + b) * 4096u, frag ^ ((uint32_t)kk * KSTEP));
+#pragma unroll
+                    for (int b = 0; b < 2; ++b) acc2[b] = mfma32<DT>(wf[b], h[kk], acc2[b]);
+                }
+                store(acc2, block, stg);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) st_off[0][j] = st_off[1][j], st_pr[0][j] = st_pr[1][j];
+        ahead_unit = 0;     // (with two buffers and more the last chunk of a unit has sent for the next unit's first)
+    }
+}
+
+// ---------------------------------------------------------------------------
+
+namespace {
+
+struct PairCut {
+    bool wide;
+    int blocks;             // NB
+    int waves, ring;
+    PairArgs a;
+    uint32_t lds;
+};
+
+// How the pair is cut, false if it does not fit: both layers' weights and at least four waves of two chunk buffers in LDS.
+bool pair_cut(const Geom &g1, const Geom &g2, int dtype, PairCut *cut)
+{
+    const int es = dtype == FC_FP8 ? 1 : 2;
+    PairCut c;
+    PairArgs &a = c.a;
+    a.m = g1.m;
+    a.x_rows = (g1.flags & FC_COMPACT_IN) ? g1.m : g1.n * g1.h * g1.w;
+    a.c_in = g1.c_in, a.c_mid = g1.c_out, a.c_out = g2.c_out;
+    a.kch = (a.c_in * es + 127) / 128;
+    a.flags = (g1.flags & FC_RELU ? kPairRelu1 : 0) | (g2.flags & FC_RELU ? kPairRelu2 : 0) |
+              (g1.flags & FC_COMPACT_IN ? kPairCompactIn : 0) | (g2.flags & FC_COMPACT_OUT ? kPairCompactOut : 0);
+    c.wide = a.kch == 1 && a.c_out <= (dtype == FC_FP8 ? 128 : 64) && a.c_mid > 64;
+    if (c.wide) {
+        c.blocks = a.c_out <= 64 ? 2 : 4;
+        a.mid_rows = (a.c_mid + 63) & ~63;
+        a.out_rows = c.blocks * 32;
+    } else {
+        if (dtype == FC_FP8 || a.c_mid > 64) return false;
+        c.blocks = a.c_mid <= 32 ? 1 : 2;
+        a.mid_rows = c.blocks * 32;
+        a.out_rows = (a.c_out + 63) & ~63;
+    }
+    const int mid_chunks = (a.c_mid * es + 127) / 128;
+    const uint32_t fixed = ((uint32_t)a.kch * a.mid_rows + (uint32_t)mid_chunks * a.out_rows) * 128u +
+                           (uint32_t)(((a.mid_rows + 63) & ~63) + a.out_rows) * 4u;
+    if (fixed >= kPairLdsBytes) return false;
+    const uint32_t room = kPairLdsBytes - fixed;
+    // A wave with rows for every unit of a CU, the rest of LDS for the chunks on their way; where that leaves waves idle, several share a
+    // unit's output channels (each makes the whole middle).  Eight waves at least fetch the weights.
+    const int units = (g1.m + 31) / 32, per_cu = (units + conv_grid_cus() - 1) / conv_grid_cus();
+    const int fit = (int)(room / pair_wave_bytes(2)), most = dtype == FC_FP8 ? 8 : 12;
+    if (fit < (c.wide ? 8 : 4)) return false;
+    a.team = 0;
+    if (!c.wide)
+        while (a.team < 2 && per_cu << (a.team + 1) <= std::min(fit, 8) && 64 << (a.team + 1) <= a.out_rows) ++a.team;
+    a.active = std::min({per_cu, fit >> a.team, most >> a.team}) << a.team;
+    c.waves = std::max(8, a.active);
+    c.ring = std::min(std::max(2, a.kch + 1), (int)((room / (uint32_t)a.active - 256u) / kPairChunkBytes));
+    a.ring = c.ring;
+    c.lds = fixed + (uint32_t)a.active * pair_wave_bytes(c.ring);
+    *cut = c;
+    return true;
+}
+
+template <int DT, typename TO, int NB, bool WIDE>
+hipError_t launch_pair(const PairCut &c, const void *x, const void *w1, const float *bias1, const void *w2, const float *bias2,
+                       const int32_t *idx, const int32_t *count, void *out, hipStream_t s)
+{
+    auto kern = k_conv_pair<DT, TO, NB, WIDE>;
+    // the dynamic LDS limit is raised once per function and device
+    static std::atomic<uint64_t> attr_devices{0};
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    const uint64_t dev_bit = 1ull << (dev & 63);
+    if (!(attr_devices.load(std::memory_order_acquire) & dev_bit)) {
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kPairLdsBytes);
+        if (e != hipSuccess) return e;
+        attr_devices.fetch_or(dev_bit, std::memory_order_release);
+    }
+    hipLaunchKernelGGL(kern, dim3(conv_grid_cus()), dim3(c.waves * 64), c.lds, s, c.a, count, idx, (const unsigned char *)x,
+                       (const unsigned char *)w1, bias1, (const unsigned char *)w2, bias2, (TO *)out);
+    return hipGetLastError();
+}
+
+} // namespace
+
+bool conv_pair_supported(const Geom &g1, const Geom &g2, int dtype)
+{
+    if (dtype != FC_BF16 && dtype != FC_F16 && dtype != FC_FP8) return false;
+    const int unit = dtype == FC_FP8 ? 16 : 8;
+    for (const Geom *g : {&g1, &g2}) {
+        if (!(g->kh == 1 && g->kw == 1 && g->sh == 1 && g->sw == 1 && g->ph == 0 && g->pw == 0)) return false;
+        if (g->c_in % unit != 0 || g->c_out % unit != 0) return false;
+        if ((uint64_t)g->n * g->h * g->w * g->c_in * (dtype == FC_FP8 ? 1u : 2u) >= kBufferLimit) return false;
+    }
+    if (g1.n != g2.n || g1.h != g2.h || g1.w != g2.w || g1.c_out != g2.c_in || (uint64_t)g1.m * 4u >= kBufferLimit) return false;
+    PairCut c;
+    return pair_cut(g1, g2, dtype, &c);
+}
+
+hipError_t launch_conv_pair(const Geom &g1, const Geom &g2, int dtype, bool bias_first1, bool bias_first2, const void *x, const void *w1,
+                            const float *bias1, const void *w2, const float *bias2, const int32_t *idx, const int32_t *count, void *out,
+                            hipStream_t s)
+{
+    PairCut c;
+    if (!pair_cut(g1, g2, dtype, &c)) return hipErrorInvalidValue;
+    c.a.flags |= (bias_first1 ? kPairBiasFirst1 : 0) | (bias_first2 ? kPairBiasFirst2 : 0);
+#define FC_PAIR_CALL(DT, TO, NB, WIDE) launch_pair<DT, TO, NB, WIDE>(c, x, w1, bias1, w2, bias2, idx, count, out, s)
+    if (dtype == FC_FP8) return c.blocks == 2 ? FC_PAIR_CALL(FC_FP8, uint8_t, 2, true) : FC_PAIR_CALL(FC_FP8, uint8_t, 4, true);
+    if (dtype == FC_BF16)
+        return c.wide ? FC_PAIR_CALL(FC_BF16, uint16_t, 2, true)
+                      : (c.blocks == 1 ? FC_PAIR_CALL(FC_BF16, uint16_t, 1, false) : FC_PAIR_CALL(FC_BF16, uint16_t, 2, false));
+    return c.wide ? FC_PAIR_CALL(FC_F16, uint16_t, 2, true)
+                  : (c.blocks == 1 ? FC_PAIR_CALL(FC_F16, uint16_t, 1, false) : FC_PAIR_CALL(FC_F16, uint16_t, 2, false));
+#undef FC_PAIR_CALL
+}
+
+} // namespace fc

@@ -498,4 +498,12 @@ hipError_t launch_conv_pw(const Geom &g, int in_dtype, int out_dtype, const void
                           const uint8_t *mask_out, const void *w, const float *bias, const int32_t *idx,
                           const int32_t *count, void *out, hipStream_t s);
 
+// Two 1x1 layers, the second the only reader of the first, in one launch (see fc_conv_pair.hip): unit stride, the same kept
+// rows, storage of one type throughout, irrelevant rows of the output left alone.  bias_first: the layer's sum starts from its
+// bias, as on the tiled kernels, else the bias is added to the finished sum, as on the resident-weights kernel.
+bool conv_pair_supported(const Geom &g1, const Geom &g2, int dtype);
+hipError_t launch_conv_pair(const Geom &g1, const Geom &g2, int dtype, bool bias_first1, bool bias_first2, const void *x, const void *w1,
+                            const float *bias1, const void *w2, const float *bias2, const int32_t *idx, const int32_t *count, void *out,
+                            hipStream_t s);
+
 } // namespace fc

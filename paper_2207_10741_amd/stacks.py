@@ -52,6 +52,9 @@ class _Plan:
         self.returned, arena_ops, arena_slots = [], [], []
         self.order = _order(ops, readers)
         place = {i: at for at, i in enumerate(self.order)}
+        # outputs that only the op behind reads, both of them 1x1 convs of unit stride: the library may run the two as one
+        next_only = [not keep_outputs and at + 1 < n and readers.get(i) == [self.order[at + 1]] and stack._pointwise(i) and
+                     stack._pointwise(self.order[at + 1]) for at, i in enumerate(self.order)]
         for at, i in enumerate(self.order):
             op = ops[i]
             ho, wo = stack.sizes[i]
@@ -92,14 +95,18 @@ class _Plan:
             if keep_outputs or i == n - 1:
                 self.returned.append((i, out_slot[i], shape))
             else:
-                arena_ops.append((at, max(place[j] for j in readers.get(i, [i])), int(np.prod(shape)) * self.dtype.itemsize))
+                # (a reader that may run as one with the op behind it reads this output for as long as that op runs)
+                last = max(place[j] for j in readers.get(i, [i]))
+                arena_ops.append((at, last + next_only[last], int(np.prod(shape)) * self.dtype.itemsize))
                 arena_slots.append(out_slot[i])
         self.returned.sort()
         # the pass is enqueued in two parts: the device runs the first layers while the host fills in the others' slots
         # (MobileNetV2's 104 tensors take it tens of microseconds)
         cut = min(HEAD_CALLS, n)
-        self.parts = [([q[1:] for q in params if lo <= q[0] < hi], (B.Call * (hi - lo))(*calls[lo:hi]))
-                      for lo, hi in ((0, cut), (cut, n)) if hi > lo]
+        cut += next_only[cut - 1]       # (not between two ops that may run as one)
+        spans = [(lo, hi) for lo, hi in ((0, cut), (cut, n)) if hi > lo]
+        self.parts = [([q[1:] for q in params if lo <= q[0] < hi], (B.Call * (hi - lo))(*calls[lo:hi])) for lo, hi in spans]
+        self.unseen = [bytes(next_only[lo:hi]) for lo, hi in spans]
         self.slots = ctypes.c_void_p * n_slots
         # A range is given out again some ops after its tensor's last reader while the arena stays inside the
         # chip's last cache level: writing over what the ops just before have read or written costs (MobileNetV2,
@@ -304,7 +311,7 @@ class ConvStack:
             out = outs[i] = x.new_empty(shape) if like_x else x.new_empty(shape, dtype=plan.dtype)
             slots[slot] = out.data_ptr()
         weights, biases = self.weights, self.biases
-        for params, calls in plan.parts:
+        for (params, calls), unseen in zip(plan.parts, plan.unseen):
             for i, w_slot, b_slot in params:        # whatever tensors the dicts hold now
                 w, b = weights[i], biases[i]
                 if not (w.is_cuda and w.is_contiguous() and (b is None or (b.is_cuda and b.is_contiguous()))):
@@ -312,7 +319,7 @@ class ConvStack:
                 slots[w_slot] = w.data_ptr()
                 if b is not None:
                     slots[b_slot] = b.data_ptr()
-            B.run_calls(calls, slots, self.workspace)
+            B.run_calls(calls, slots, self.workspace, unseen=unseen)
         return outs, masks
 
     def run(self, x, mask=None, keep_outputs: bool = True, chain: bool = False, canary=None, compact: bool = False):
