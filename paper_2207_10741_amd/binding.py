@@ -13,6 +13,7 @@ from dataclasses import dataclass
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libfocused_conv.so")
+NATIVE_PATH = os.path.join(_HERE, "_native.so")
 
 F32, BF16, F16, FP8 = 0, 1, 2, 3
 RELU, SKIP_ZERO_FILL, WORKSPACE_READY, COMPACT_OUT, COMPACT_IN, PACKED_MASKS, RESIDENT_WEIGHTS = 1, 2, 4, 8, 16, 32, 64
@@ -189,9 +190,38 @@ def _ptr(t):
     return None if t is None else t.data_ptr()      # (the argument types convert plain integers)
 
 
-# A call of a small layer costs a few microseconds on the device, so the host side of one is kept as
-# short: the stream's handle comes from torch's C function (torch.cuda.current_stream() builds a Python
-# object around it, 2.8 us against 0.1 us), sizes that only depend on the descriptor are looked up.
+# A call of a small layer costs a few microseconds on the device, so the host side of one is kept as short.  Plain calls go
+# through csrc/fc_python.cpp whole (tensors checked, output made, stream and workspace looked up in C++: a call of a 64 -> 64
+# layer on 1 x 56 x 56 takes the host 4.6 us so, 8.4 in Python); it answers None to any other, which is then made here.  Here the
+# stream's handle comes from torch's C function (torch.cuda.current_stream() builds a Python object around it, 2.8 us against
+# 0.1 us), and sizes that only depend on the descriptor are looked up.
+
+_native_module = None
+
+
+def _native():
+    """The extension, bound to the C library; raises if it has not been built."""
+    global _native_module
+    if _native_module is None:
+        L = lib()
+        if not os.path.exists(NATIVE_PATH):
+            raise ImportError("%s is missing: build it with `python -m paper_2207_10741_amd.build`" % NATIVE_PATH)
+        from . import _native as module
+        address = lambda f: ctypes.cast(f, ctypes.c_void_p).value
+        module.bind(tuple(address(f) for f in (L.fc_focused_conv2d, L.fc_focused_gconv2d, L.fc_focused_dwconv2d, L.fc_mask_pyramid,
+                                               L.fc_mask_pyramid_packed, L.fc_out_dims, L.fc_workspace_bytes)), _kept, _WORKSPACE_MOST)
+        _native_module = module
+    return _native_module
+
+
+def _first_call(*args):
+    global _call
+    _call = _native().call
+    return _call(*args)
+
+
+_call = _first_call     # the extension's function once it is loaded
+_CONV, _DWCONV, _PYRAMID, _PYRAMID_PACKED = range(4)    # kinds of Prepared
 
 def _current_raw_stream():
     c = _torch()._C
@@ -257,7 +287,7 @@ def _own_workspace(need: int, device, raw_stream: int, stream):
     if need > _WORKSPACE_MOST or torch._C._cuda_isCurrentStreamCapturing():
         return _scratch(need, device, stream)
     pool = _kept.__dict__
-    key = (raw_stream, device)
+    key = (raw_stream, device.index)
     ws = pool.get(key)
     if ws is None or ws.numel() < need:
         if key not in pool and len(pool) >= _WORKSPACE_STREAMS:
@@ -385,18 +415,19 @@ class PreparedPyramid:
         nl = len(steps)
         self._ptrs = tuple((vp * nl)(*[_ptr(lv[i]) for lv in self.levels]) for i in range(3))
         if packed:
-            self._args = (_ptr(mask_in), 1 if packed_in else 0, n, h, w, nl, self._steps, *self._ptrs,
-                          _ptr(self._ws), self._ws.numel())
-            self._fn = lib().fc_mask_pyramid_packed
+            self._run = _native().Prepared(_PYRAMID_PACKED, (_ptr(mask_in), 1 if packed_in else 0, n, h, w, nl, *self._tables(),
+                                                             _ptr(self._ws), self._ws.numel()))
         else:
             if packed_in:
                 raise ValueError("a packed input mask gives packed levels: pass packed=True")
-            self._args = (_ptr(mask_in), n, h, w, nl, self._steps, *self._ptrs, _ptr(self._ws), self._ws.numel())
-            self._fn = lib().fc_mask_pyramid
+            self._run = _native().Prepared(_PYRAMID, (_ptr(mask_in), n, h, w, nl, *self._tables(), _ptr(self._ws), self._ws.numel()))
         self.mask_in = mask_in   # (kept alive: the call reads it)
 
+    def _tables(self):
+        return [ctypes.addressof(t) for t in (self._steps, *self._ptrs)]
+
     def __call__(self, stream=None):
-        rc = self._fn(*self._args, _stream(stream))
+        rc = self._run(None if stream is None else stream.cuda_stream)
         if rc != 0:
             raise FcError(rc, "fc_mask_pyramid")
         return self.levels
@@ -441,6 +472,10 @@ def active_index_compact_tiled(mask, tile_h: int = 8, tile_w: int = 16, idx=None
 def focused_conv2d(desc: ConvDesc, x, w, bias=None, mask_in=None, mask_out=None, idx=None, count=None,
                    out=None, workspace=None, stream=None):
     """fc_focused_conv2d.  x NHWC, w [C_out,KH,KW,C_in]; returns out NHWC."""
+    if stream is None:
+        got = _call(desc, 0, x, w, bias, mask_in, mask_out, idx, count, out, workspace)
+        if got is not None:
+            return got if got.__class__ is not int else _check(got, "fc_focused_conv2d")
     _require_cuda(x, w, bias, mask_in, mask_out, idx, count, out, workspace)
     shape, dtype, need = _conv_sizes(desc)
     if out is None:
@@ -487,12 +522,11 @@ class PreparedConv:
         self.out = out
         self._keep = (desc, x, w, bias, mask_in, mask_out, idx, count, out, workspace)
         ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-        self._args = (ctypes.byref(desc), _ptr(x), _ptr(mask_in), _ptr(w), _ptr(bias), _ptr(mask_out), _ptr(idx),
-                      _ptr(count), _ptr(out), _ptr(workspace), ws_bytes)
-        self._fn = lib().fc_focused_conv2d
+        self._run = _native().Prepared(_CONV, (ctypes.addressof(desc), _ptr(x), _ptr(mask_in), _ptr(w), _ptr(bias), _ptr(mask_out), _ptr(idx),
+                                               _ptr(count), _ptr(out), _ptr(workspace), ws_bytes))
 
     def __call__(self, stream=None):
-        rc = self._fn(*self._args, _stream(stream))
+        rc = self._run(None if stream is None else stream.cuda_stream)
         if rc != 0:
             raise FcError(rc, "fc_focused_conv2d")
         return self.out
@@ -501,6 +535,10 @@ class PreparedConv:
 def focused_gconv2d(desc: ConvDesc, groups: int, x, w, bias=None, mask_in=None, mask_out=None, idx=None,
                     count=None, out=None, workspace=None, stream=None):
     """fc_focused_gconv2d.  x NHWC, w [C_out,KH,KW,C_in/groups]; returns out NHWC."""
+    if stream is None and groups > 0:
+        got = _call(desc, groups, x, w, bias, mask_in, mask_out, idx, count, out, workspace)
+        if got is not None:
+            return got if got.__class__ is not int else _check(got, "fc_focused_gconv2d")
     _require_cuda(x, w, bias, mask_in, mask_out, idx, count, out, workspace)
     shape, dtype, need = _conv_sizes(desc)
     if out is None:
@@ -528,6 +566,10 @@ def expand_group_weights(w, groups: int, dtype: int, stream=None):
 
 def focused_dwconv2d(desc: ConvDesc, x, w, bias=None, mask_in=None, out=None, stream=None):
     """fc_focused_dwconv2d.  x NHWC, w [C,KH,KW] (one filter per channel); returns out NHWC."""
+    if stream is None:
+        got = _call(desc, -1, x, w, bias, mask_in, None, None, None, out, None)
+        if got is not None:
+            return got if got.__class__ is not int else _check(got, "fc_focused_dwconv2d")
     torch = _torch()
     _require_cuda(x, w, bias, mask_in, out)
     shape, dtype, _ = _conv_sizes(desc)
@@ -549,11 +591,10 @@ class PreparedDwConv:
             out = torch.empty((desc.n, ho, wo, desc.c_out), dtype=torch_dtype(desc.out_dtype), device=x.device)
         self.out = out
         self._keep = (desc, x, w, bias, mask_in, out)
-        self._args = (ctypes.byref(desc), _ptr(x), _ptr(mask_in), _ptr(w), _ptr(bias), _ptr(out))
-        self._fn = lib().fc_focused_dwconv2d
+        self._run = _native().Prepared(_DWCONV, (ctypes.addressof(desc), _ptr(x), _ptr(mask_in), _ptr(w), _ptr(bias), _ptr(out)))
 
     def __call__(self, stream=None):
-        rc = self._fn(*self._args, _stream(stream))
+        rc = self._run(None if stream is None else stream.cuda_stream)
         if rc != 0:
             raise FcError(rc, "fc_focused_dwconv2d")
         return self.out

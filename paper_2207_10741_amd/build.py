@@ -1,4 +1,4 @@
-"""Build libfocused_conv.so in-tree with hipcc for gfx950.
+"""Build libfocused_conv.so in-tree with hipcc for gfx950, and the Python extension _native.so beside it.
 
     python -m paper_2207_10741_amd.build
 """
@@ -15,6 +15,7 @@ import tempfile
 _HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(_HERE)
 OUT = os.path.join(_HERE, "libfocused_conv.so")
+NATIVE = os.path.join(_HERE, "_native.so")          # the Python extension (host code, against PyTorch's C++ interface)
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -40,6 +41,17 @@ def _run(cmd, verbose):
         raise RuntimeError("hipcc failed (%d): %s\n%s" % (res.returncode, " ".join(cmd), res.stdout))
 
 
+def _native_command(out):
+    import sysconfig
+    import torch
+    home = os.path.dirname(torch.__file__)
+    return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+            "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-I", os.path.join(ROOT, "include"),
+            "-I", os.path.join(home, "include"), "-I", os.path.join(home, "include", "torch", "csrc", "api", "include"),
+            "-I", sysconfig.get_paths()["include"], "-I", "/opt/rocm/include", os.path.join(_HERE, "csrc", "fc_python.cpp"), "-o", out,
+            "-L", os.path.join(home, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", "-lamdhip64"]
+
+
 def build(verbose: bool = True) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     srcs = sorted(glob.glob(os.path.join(_HERE, "csrc", "*.hip")))
@@ -59,12 +71,13 @@ def build(verbose: bool = True) -> str:
                 obj = os.path.join(tmp, name + ".o")
                 units.append((obj, [hipcc, *HIPCC_FLAGS, *inc, "-c", src, "-o", obj]))
         with concurrent.futures.ThreadPoolExecutor(max_workers=jobs) as pool:
-            for f in [pool.submit(_run, cmd, verbose) for _, cmd in units]:
+            for f in [pool.submit(_run, cmd, verbose) for cmd in [cmd for _, cmd in units] + [_native_command(NATIVE + ".tmp")]]:
                 f.result()
         _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *[o for o, _ in units], "-o", OUT + ".tmp"], verbose)
     finally:
         shutil.rmtree(tmp, ignore_errors=True)
     os.replace(OUT + ".tmp", OUT)
+    os.replace(NATIVE + ".tmp", NATIVE)
     return OUT
 
 
