@@ -12,8 +12,9 @@
 // row, each padded to whole pieces of 8 elements, and a lane fetches a piece with one (unaligned)
 // 16-byte load; elements of taps outside the image or on an irrelevant input pixel, and
 // the padding, are then replaced by zeros.  (7x7 on one 224 x 224 image: eight 2-byte loads a step
-// and a weight loop with one load in flight took 32 us.)  A wave whose pieces would reach
-// past either end of x, a dilated kernel, and kernels whose rows are far from whole pieces load element by element -
+// and a weight loop with one load in flight took 32 us.)  Pieces that would reach past either end of x are loaded inside it and shifted: the
+// first and the last image rows have such waves, and while these loaded element by element the launch lasted as long as they did (one
+// 224 x 224 image 10.6 -> 9.1 us, 160 x 160 without a mask 12.5 -> 8.6).  A dilated kernel, and kernels whose rows are far from whole pieces load element by element -
 // but for those of up to 4 x 4 taps with rows of at least 7 elements (3x3 RGB): their pieces, in plain order, lie in one
 // kernel row or two and are put together from two 16-byte loads (TWO: two loads instead of eight, masks by four
 // bytes, 10 registers fewer; 64 channels at 8 x 1080 x 1920, half kept: 507 -> 438 us, 32 at 32 x 224 x 224 / 2 without
@@ -22,6 +23,7 @@
 // With a mask the kernel also clears the irrelevant rows: workgroups without a tile do it when
 // there are enough of them, else all after their tiles.
 #include "fc_mfma_util.hpp"
+#include <algorithm>
 
 namespace fc {
 
@@ -49,6 +51,29 @@ bool conv_stem_supported(const Geom &g, int in_dtype, int out_dtype)
     if ((int64_t)(g.kh - 1) * g.dh >= 65536 || (int64_t)(g.kw - 1) * g.dw >= 65536) return false; // 16-bit tap offsets
     if ((int64_t)g.n * g.h * g.w * g.c_in >= INT32_MAX) return false; // 32-bit element indices
     return true;
+}
+
+// Eight elements from element `off` on, where some lie before or past the tensor: loaded inside it and moved to their places (what takes
+// the places of the others is never used).
+__device__ __forceinline__ uint4 load8_moved(const uint16_t *__restrict__ x, int off, int elems)
+{
+    const int at = min(max(off, 0), elems - 8), up = at - off;
+    uint64_t v[2];
+    __builtin_memcpy(v, x + at, 16);
+    const uint32_t n = (uint32_t)(up < 0 ? -up : up) * 16u;
+    if (n != 0 && n < 128u) {
+        const uint32_t r = n & 63u;
+        if (up > 0) {
+            v[1] = n < 64u ? (v[1] << r) | (v[0] >> (64u - r)) : v[0] << r;
+            v[0] = n < 64u ? v[0] << r : 0u;
+        } else {
+            v[0] = n < 64u ? (v[0] >> r) | (v[1] << (64u - r)) : v[1] >> r;
+            v[1] = n < 64u ? v[1] >> r : 0u;
+        }
+    }
+    uint4 out;
+    __builtin_memcpy(&out, v, 16);
+    return out;
 }
 
 // divisors and the layout of the reduction, prepared on the host
@@ -319,15 +344,21 @@ __global__ __launch_bounds__(kStemThreads, TWO ? 4 : 3) void k_conv_stem(
                 acc[cb] = mfma32<DT>(wf, xf, acc[cb]);
             }
         };
-        if (!TWO && dv.pitch && __all(base >= 0 && base <= x_elems - dv.reach)) {
+        const bool inside = __all(base >= 0 && base <= x_elems - dv.reach);
+        if (!TWO && dv.pitch && x_elems >= 8) {
             constexpr int U = 4; // pieces in flight
             for (int j0 = 0; j0 < ksteps; j0 += U) {
                 uint4 v[U];
+                if (inside) {
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int j = min(j0 + u, ksteps - 1);
-                    const uint32_t e = lut[j * 16 + half * 8];
-                    __builtin_memcpy(&v[u], x + base + (int)(e & 0xffffffu), 16);
+                    for (int u = 0; u < U; ++u) {
+                        const uint32_t e = lut[min(j0 + u, ksteps - 1) * 16 + half * 8];
+                        __builtin_memcpy(&v[u], x + base + (int)(e & 0xffffffu), 16);
+                    }
+                } else {
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+                        v[u] = load8_moved(x, base + (int)(lut[min(j0 + u, ksteps - 1) * 16 + half * 8] & 0xffffffu), x_elems);
                 }
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
@@ -342,7 +373,7 @@ __global__ __launch_bounds__(kStemThreads, TWO ? 4 : 3) void k_conv_stem(
                     multiply(j0 + u, xf);
                 }
             }
-        } else if (TWO && __all(base >= 0 && base <= x_elems - dv.reach)) {
+        } else if (TWO && inside) {
             constexpr int U = 2; // steps in flight
             for (int j0 = 0; j0 < ksteps; j0 += U) {
                 uint4 a[U], b[U];
@@ -451,10 +482,8 @@ static hipError_t launch_stem_t(const Geom &g, const void *x, const uint8_t *mas
                                 const float *bias, const int32_t *idx, const int32_t *count, void *out,
                                 hipStream_t s)
 {
-    // grid sized for the dense row count (the kept count is only known on the device),
-    // capped at a few workgroups per CU: they stride over the tiles
+    // (the grid is sized below)
     const int64_t tiles = ((int64_t)g.m + kStemRows - 1) / kStemRows;
-    const int gx = (int)(tiles > 2048 ? 2048 : tiles);
     const int gy = (g.c_out + kStemCo - 1) / kStemCo;
     StemDivs dv;
     dv.wo = make_fastdiv((uint32_t)g.wo);
@@ -477,6 +506,16 @@ static hipError_t launch_stem_t(const Geom &g, const void *x, const uint8_t *mas
     const size_t lds = (size_t)kStemRows * (kStemCo * sizeof(TO) + 16) + (size_t)kStemCo * stem_weight_pitch(ksteps) +
                        (size_t)ksteps * 16 * sizeof(uint32_t) + (size_t)kStemRows * sizeof(int32_t) + (size_t)kStemCo * sizeof(float) +
                        (size_t)kStemMaxTaps * sizeof(uint32_t) + (two_rows ? (size_t)ksteps * 2 * 3 * sizeof(uint4) : 0);
+    // Sized for the dense row count (the kept count is only known on the device), capped at the workgroups that are resident together:
+    // they stride over the tiles, the next one's rows looked up beside the current one, and lay out the weights once.  At 2048 a
+    // workgroup had one tile and its own weights, or a second round of workgroups was started for the rest.  us, 2048 -> resident: 3x3, 3 -> 32
+    // on 32 x 224 x 224 / 2 chained 14.8 -> 12.4, without a mask 16.7 -> 14.9; 3 -> 64 on 2 x 700 x 1244 chained 37.9 -> 35.3, on
+    // 8 x 1080 x 1920 616 -> 603; 7x7 / 2 on 32 x 224 x 224 32.5 -> 29.3, on 8 x 280 x 290 17.7 -> 15.2 (half kept).  512 or 1536 for the 3x3
+    // layers 11 .. 34 % and 7 .. 19 % slower, 512 for the 7x7 ones 3 .. 32 %.
+    // Zero-filled full-HD frames (16.6 M positions, half kept, a depth threshold as mask) inside a network 581 us so, 563 at 2048, where workgroups that are
+    // done clear rows beside others' tiles; a network on 0.75 to 4.3 M positions 238 .. 1877 us so, 248 .. 1883 at 2048.
+    const int resident = tiles >= 65536 ? 2048 : conv_grid_cus() * (two_rows ? 4 : 3) / gy;
+    const int gx = (int)std::min<int64_t>(tiles, std::max(resident, 1));
     auto kern = two_rows ? k_conv_stem<DT, TO, true> : k_conv_stem<DT, TO, false>;
     hipLaunchKernelGGL(kern, dim3(gx, gy), dim3(kStemThreads), lds, s, g, dv, (const uint16_t *)x,
                        mask_in, mask_out, (const uint16_t *)w, bias, idx, count, (TO *)out);
