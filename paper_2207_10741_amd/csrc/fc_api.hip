@@ -214,7 +214,7 @@ ConvWorkspace conv_ws_layout(const Geom &g)
 // if they are to be enqueued one by one (and any error of theirs to be found there).
 static bool try_pair(const fc_conv_desc *d1, const fc_conv_desc *d2, const void *x, const void *mask1, const void *w1, const float *bias1,
                      const void *w2, const float *bias2, const int32_t *idx, const int32_t *count, const void *mask2, const void *mid, void *out,
-                     hipStream_t s, hipError_t *e)
+                     const void *workspace, size_t workspace_bytes, hipStream_t s, hipError_t *e)
 {
     Geom g1, g2;
     if (make_geom(d1, &g1) != FC_OK || make_geom(d2, &g2) != FC_OK) return false;
@@ -236,7 +236,10 @@ static bool try_pair(const fc_conv_desc *d1, const fc_conv_desc *d2, const void 
         return false;
     const bool pw1 = conv_pw_wanted(g1, dtype, dtype, idx != nullptr), pw2 = conv_pw_wanted(g2, dtype, dtype, idx != nullptr);
     // (a reduction that is split is summed in another order)
-    if ((!pw1 && split_k_reachable(g1, dtype, idx != nullptr)) || (!pw2 && split_k_reachable(g2, dtype, idx != nullptr))) return false;
+    const auto splits = [&](const Geom &g) {
+        return split_k_reachable(g, dtype, idx != nullptr) && workspace && workspace_bytes >= conv_ws_layout(g).split_only && aligned16(workspace);
+    };
+    if ((!pw1 && splits(g1)) || (!pw2 && splits(g2))) return false;
     *e = launch_conv_pair(g1, g2, dtype, !pw1, !pw2, x, w1, bias1, w2, bias2, idx, count, out, s);
     return true;
 }
@@ -908,7 +911,7 @@ int32_t fc_run_calls_unseen(const fc_call *calls, int32_t n_calls, const uint8_t
             if (c.kind == FC_CALL_CONV && r.kind == FC_CALL_CONV && r.x == c.out && c.idx == r.idx && c.count == r.count &&
                 try_pair(&d, &r.desc, at(c.x), at(c.mask_in), at(c.w), (const float *)at(c.bias),
                 at(r.w), (const float *)at(r.bias), (const int32_t *)at(c.idx), (const int32_t *)at(c.count), at(r.mask_in), at(c.out), at(r.out),
-                (hipStream_t)stream, &e)) {
+                workspace, workspace_bytes, (hipStream_t)stream, &e)) {
                 if (e != hipSuccess) return FC_ERR_HIP;
                 ++i;
                 continue;

@@ -2,6 +2,7 @@
 a middle that is never written."""
 import ctypes
 
+import numpy as np
 import pytest
 
 from paper_2207_10741_amd import binding as B, synth
@@ -53,6 +54,7 @@ def _run(shape, channels, dtype, mask, relu=(True, True), compact_in=False, comp
 PAIRS = [((64, 256, 64), B.BF16), ((64, 192, 40), B.F16), ((8, 72, 8), B.BF16), ((64, 256, 64), B.FP8), ((128, 256, 128), B.FP8),
          ((48, 80, 112), B.FP8), ((32, 16, 96), B.BF16), ((96, 24, 144), B.F16), ((192, 32, 192), B.BF16), ((192, 64, 384), B.BF16),
          ((384, 64, 384), B.F16), ((200, 40, 72), B.BF16)]
+STREAMED = [((128, 512, 128), B.BF16), ((128, 512, 128), B.FP8), ((128, 320, 72), B.F16), ((128, 1152, 112), B.FP8)]      # (more weights than LDS holds)
 
 
 @pytest.mark.parametrize("shape", [(1, 1, 1), (1, 5, 13), (2, 61, 83), (6, 130, 131)])
@@ -87,10 +89,24 @@ def test_pairs_without_relu_or_bias_and_masks_that_keep_nothing(channels, dtype)
     assert left and (one == CANARY).all() and (both == CANARY).all()
 
 
+@pytest.mark.parametrize("channels,dtype", STREAMED)
+def test_pairs_whose_weights_pass_through_lds(channels, dtype):
+    """No rows, one, a unit and one more, fewer units than workgroups and more, some in a second pass; rows in list order on either side."""
+    n, h, w = shape = (1, 150, 161)
+    for kept in (0, 1, 32, 33, 1000, 20000, n * h * w):
+        mask = np.zeros(n * h * w, np.uint8)
+        mask[np.random.default_rng(kept).permutation(n * h * w)[:kept]] = 1
+        one, both, left = _run(shape, channels, dtype, mask.reshape(shape), compact_in=kept == 33, compact_out=kept in (33, 1000))
+        assert left and (one == both).all(), kept
+    for relu in ((False, True), (True, False)):
+        one, both, left = _run((7, 120, 121), channels, dtype, None, relu=relu, bias=relu)
+        assert left and (one == both).all(), relu
+
+
 def test_layers_that_cannot_run_as_one_run_one_by_one():
     shape = (1, 30, 40)
     mask = synth.mask_objects(*shape, 0.5, 4, 2)
-    # the second clears irrelevant rows; weights that do not fit; an output over the input
-    for channels, over in (((64, 256, 64), dict(skip=False)), ((256, 1024, 256), {}), ((64, 256, 64), dict(x_over_out=True))):
+    # the second clears irrelevant rows; weights that do not fit, or are too many for the rows; an output over the input
+    for channels, over in (((64, 256, 64), dict(skip=False)), ((256, 1024, 256), {}), ((128, 512, 128), {}), ((64, 256, 64), dict(x_over_out=True))):
         one, both, left = _run(shape, channels, B.BF16, mask, **over)
         assert not left and (one == both).all(), (channels, over)
