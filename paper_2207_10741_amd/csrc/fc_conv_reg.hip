@@ -991,6 +991,8 @@ struct WindowCut {
     int32_t lg_pieces; // log2 of the 16-byte pieces of a pixel's window
     int32_t x_bytes, w_bytes;
     FastDiv by_line, by_kw, by_ppt;
+    FastDiv by_blocks; // 64-channel blocks of the output
+    int32_t blocks;
 };
 
 template <int DT, typename TO, int V, int KS, int LG, int NG = 1>
@@ -1007,7 +1009,10 @@ __global__ __launch_bounds__(kRegThreads, 2) void k_conv_grouped_window(
     const uint32_t lds0 = (uint32_t)reinterpret_cast<uintptr_t>(lds);
     const int tid = threadIdx.x, lane = tid & 63, col = lane & 15, quarter = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int first = blockIdx.x * kWindowSpan, blk0 = blockIdx.y * 64, co0 = blk0 + wave * 16;
+    // XCD j (workgroups b = j mod 8) takes the j-th contiguous eighth of the windows
+    const int xcd = (int)blockIdx.x & 7, whole = (int)gridDim.x >> 3, over = (int)gridDim.x & 7;
+    const int unit = xcd * whole + min(xcd, over) + (int)(blockIdx.x >> 3), span = (int)fast_div((uint32_t)unit, cut.by_blocks);
+    const int first = span * kWindowSpan, blk0 = (unit - span * cut.blocks) * 64, co0 = blk0 + wave * 16;
     const int taps = g.kh * g.kw;
     const int win0 = (blk0 / cog) * cig; // first input channel of the workgroup's groups
     const int lg_pieces = V ? LG : cut.lg_pieces, line = V ? kQuadLine : cut.line;
@@ -1294,7 +1299,9 @@ static hipError_t launch_grouped(const Geom &g, int groups, const void *x, const
                         : !quads ? (steps <= 5 ? k_conv_grouped_window<DT, TO, 0, 5, 0> : k_conv_grouped_window<DT, TO, 0, 9, 0>)
                         : v == 1 ? (cog == 8 ? k_conv_grouped_window<DT, TO, 1, 9, 2> : k_conv_grouped_window<DT, TO, 1, 9, 3>)
                                  : k_conv_grouped_window<DT, TO, 2, 9, 4>;
-            hipLaunchKernelGGL(kern, dim3((g.m + kWindowSpan - 1) / kWindowSpan, (g.c_out + 63) / 64), dim3(kRegThreads), bytes, s,
+            cut.blocks = (g.c_out + 63) / 64;
+            cut.by_blocks = make_fastdiv((uint32_t)cut.blocks);
+            hipLaunchKernelGGL(kern, dim3((g.m + kWindowSpan - 1) / kWindowSpan * cut.blocks), dim3(kRegThreads), bytes, s,
                                g, cut, cig, cog, (const uint16_t *)x, mask_in, mask_out, (const uint16_t *)w, bias, (TO *)out);
             return hipGetLastError();
         }
