@@ -415,7 +415,8 @@ struct DwTileArgs {
     int32_t per_block; // tiles of a workgroup
     int32_t chunks;    // channel chunks in all: C / 8
     int32_t tiles_x, tiles;
-    FastDiv div_lanes, div_tx;
+    int32_t blocks;    // workgroups of an image and channel chunk
+    FastDiv div_lanes, div_tx, div_blocks, div_n;
 };
 
 template <typename TI, typename TO, int S, int PY, int PX>
@@ -425,9 +426,14 @@ __global__ __launch_bounds__(kDwThreads, 3) void k_dwconv_tile(DwTileArgs a, con
 {
     constexpr int VEC = 8, TAPS = 9, R = (PY - 1) * S + 3, Q = (PX - 1) * S + 3, N = PY * PX;
     const Geom &g = a.g;
-    const int b = blockIdx.y, C = g.c_in, CT = a.lanes * VEC;
+    // (workgroups in the order of tiles, images, channel chunks, an eighth of them on an XCD: neighbouring tiles read the same pixels.  Batch 32, as numbered ->
+    // here: 32 channels at 112 x 112 12.7 -> 12.4 us, without a mask 16.4 -> 14.4, 96 at 112 / 2 13.6 -> 12.9, 192 at 28 7.6 -> 7.3; 144 at 56, batch 64, without
+    // a mask 32.3 -> 32.8)
+    const int unit = xcd_eighth((int)blockIdx.x, (int)gridDim.x), of_image = (int)fast_div((uint32_t)unit, a.div_blocks);
+    const int block = unit - of_image * a.blocks, z = (int)fast_div((uint32_t)of_image, a.div_n);
+    const int b = of_image - z * g.n, C = g.c_in, CT = a.lanes * VEC;
     const int tt = (int)fast_div(threadIdx.x, a.div_lanes), j = (int)threadIdx.x - tt * a.lanes;
-    const int chunk = blockIdx.z * a.lanes + j, c0 = chunk * VEC;
+    const int chunk = z * a.lanes + j, c0 = chunk * VEC;
     const bool mine = tt < a.per_block && chunk < a.chunks;
     extern __shared__ __align__(16) float dw_w[]; // [kDwPairRows + 1][CT]: packed pairs of taps, then the bias
 
@@ -438,7 +444,7 @@ __global__ __launch_bounds__(kDwThreads, 3) void k_dwconv_tile(DwTileArgs a, con
         0x00020000);
 
     // taps inside the image, and what the mask says about them
-    const int tile = blockIdx.x * a.per_block + tt;
+    const int tile = block * a.per_block + tt;
     const bool live = mine && tile < a.tiles;
     const int tile_y = (int)fast_div((uint32_t)tile, a.div_tx), oh0 = tile_y * PY, ow0 = (tile - tile_y * a.tiles_x) * PX;
     const int ih0 = oh0 * S - g.ph, iw0 = ow0 * S - g.pw;
@@ -568,7 +574,12 @@ hipError_t launch_tile(const Geom &g, const void *x, const uint8_t *mask_in, con
     a.div_lanes = make_fastdiv((uint32_t)a.lanes);
     a.div_tx = make_fastdiv((uint32_t)a.tiles_x);
     const size_t lds = (size_t)(kDwPairRows + 1) * a.lanes * 8 * sizeof(float);
-    hipLaunchKernelGGL((k_dwconv_tile<TI, TO, S, PY, PX>), dim3((a.tiles + a.per_block - 1) / a.per_block, g.n, ctiles),
+    a.blocks = (a.tiles + a.per_block - 1) / a.per_block;
+    const int64_t grid = (int64_t)a.blocks * g.n * ctiles;
+    if (grid > INT32_MAX) return hipErrorInvalidValue;
+    a.div_blocks = make_fastdiv((uint32_t)a.blocks);
+    a.div_n = make_fastdiv((uint32_t)g.n);
+    hipLaunchKernelGGL((k_dwconv_tile<TI, TO, S, PY, PX>), dim3((uint32_t)grid),
                        dim3(kDwThreads), lds, s, a, (const TI *)x, mask_in, (const TI *)w, bias, (TO *)out);
     return hipGetLastError();
 }

@@ -267,6 +267,14 @@ __device__ __forceinline__ int wave_inclusive_scan(int v)
     return v;
 }
 
+// Neighbouring workgroups on one XCD: workgroup b runs on XCD b mod 8, so with work dealt in the order of the numbers the pixels that
+// neighbours share are fetched by every XCD's L2.  Here XCD j takes the j-th contiguous eighth of the work.
+__device__ __forceinline__ int xcd_eighth(int block, int grid)
+{
+    const int xcd = block & 7;
+    return xcd * (grid >> 3) + min(xcd, grid & 7) + (block >> 3);
+}
+
 // ---- launchers (each enqueues on `s`, returns a hipError_t) ----------------
 hipError_t launch_mask_downsample(const uint8_t *mask_in, int n, int h, int w, int kh, int kw,
                                   int sh, int sw, int ph, int pw, int dh, int dw, int ho, int wo,
