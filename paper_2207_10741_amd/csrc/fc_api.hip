@@ -495,7 +495,9 @@ int32_t fc_focused_conv2d(const fc_conv_desc *desc, const void *x, const uint8_t
             e = launch_zero_i32(tile_counters, kSplitGrid, s);
             if (e != hipSuccess) return FC_ERR_HIP;
         }
-        e = launch_conv_small(g, desc->in_dtype, desc->out_dtype, room, x, mask_in, mask_out, w, bias, idx, count, out,
+        // (a 1x1 layer whose lists go to the resident-weights kernel has the same sums without one)
+        const bool as_pw = g.kh * g.kw == 1 && conv_pw_wanted(g, desc->in_dtype, desc->out_dtype, true);
+        e = launch_conv_small(g, desc->in_dtype, desc->out_dtype, as_pw, room, x, mask_in, mask_out, w, bias, idx, count, out,
                               partials, tile_counters, s);
         if (e != hipSuccess) return FC_ERR_HIP;
     } else if (mfma && (idx || !mask_in) && !pw && conv_wide_wanted(g, desc->in_dtype, desc->out_dtype, mask_in != nullptr)) {

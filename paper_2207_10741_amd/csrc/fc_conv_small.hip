@@ -1,5 +1,5 @@
 // Focused convolution on the matrix cores for layers of a few hundred row blocks (the layers of a
-// network at batch 1 to 4; 16-bit storage, more than one tap).
+// network at batch 1 to 4; 16-bit storage; 1x1 kernels where no list is given).
 //
 // Such a layer is a chain of memory round trips: its matrix work takes a tenth of its time.  This
 // kernel is cut for the chain, not for the throughput:
@@ -42,12 +42,12 @@ struct SmallCut {
     FastDiv by_splits;
 };
 
-// Splits of every tile's reduction when `rows` rows are kept: for 3x3 kernels the tiled kernel's rule for its
+// Splits of every tile's reduction when `rows` rows are kept: for 3x3 and 1x1 kernels the tiled kernel's rule for its
 // 64 x 64 tiles (which splits nothing without a workspace: 384 -> 48 on 4 x 26 x 14, 54 stages in one wave, 22.0 us, in
 // four 9.8 us); the others never ran there on such tiles and are cut for the waves of one workgroup.
 __host__ __device__ static inline int small_splits(int rows, int c_out, int stages, int taps, bool room)
 {
-    if (taps != 9) return stages >= 4 * kSmallWaves ? kSmallWaves : 1;
+    if ((taps | 8) != 9) return stages >= 4 * kSmallWaves ? kSmallWaves : 1;
     const int ntiles = ((rows + 63) / 64) * ((c_out + 63) / 64);
     if (!room) { // no workspace to meet in: the waves of a workgroup
         const int cap = stages / kMinSplitStages;
@@ -196,7 +196,9 @@ __device__ __forceinline__ void small_clear_rest(const Geom &g, const SmallUnit 
     }
 }
 
-template <int DT, typename TO>
+// BIAS_LAST (1x1 kernels): the bias is added to the finished sums instead of starting them.  (An instance of its own: chosen at run time, by a
+// select an accumulator, it cost 0.2 to 0.4 us of the 4.8 of a 1x1 layer, 0.7 of the 7.9 of a 3x3 one.)
+template <int DT, typename TO, bool BIAS_LAST>
 __global__ __launch_bounds__(64 * kSmallWaves, 1) void k_conv_small(Geom g, SmallCut cut, const uint16_t *__restrict__ x,
                                                                  const uint8_t *__restrict__ mask_in,
                                                                  const uint8_t *__restrict__ mask_out,
@@ -406,6 +408,12 @@ __global__ __launch_bounds__(64 * kSmallWaves, 1) void k_conv_small(Geom g, Smal
             if (bias && split == 0 && co < g.c_out) bq = *reinterpret_cast<const float4 *>(bias + co);
             acc[4 * q] = bq.x; acc[4 * q + 1] = bq.y; acc[4 * q + 2] = bq.z; acc[4 * q + 3] = bq.w;
         }
+        f32x16_t last;
+        if constexpr (BIAS_LAST) {
+            last = acc;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+        }
         const uint32_t frag = (uint32_t)l32 * 128u, swz = FC_SWZ(l32);
         // A step multiplies the operands it finds in registers, after requesting the next stage's from LDS;
         // the slot they came from is then free and takes the stage NS - 1 further on.
@@ -457,6 +465,9 @@ __global__ __launch_bounds__(64 * kSmallWaves, 1) void k_conv_small(Geom g, Smal
             step(ob, oa);
         }
         wait_vmcnt<0>();
+        if constexpr (BIAS_LAST)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[i] += last[i];
 
         const SmallUnit u = {waves, wave, mt, nt, group, splits, split, co0, r0, p, live, drop};
         small_meet_and_store<DT, TO>(g, u, cut.n_nt, fill, acc, lds, out, partials, tile_counters);
@@ -718,13 +729,27 @@ static int small_total(const Geom &g) { return g.kh * g.kw * ((g.c_in + 63) / 64
 bool conv_small_wanted(const Geom &g, int in_dtype, bool room, bool needs_labels)
 {
     if (in_dtype != FC_BF16 && in_dtype != FC_F16) return false;
-    if (g.kh * g.kw == 1 || (g.flags & (FC_COMPACT_IN | FC_RESIDENT_WEIGHTS))) return false;
+    if (g.flags & (FC_COMPACT_IN | FC_RESIDENT_WEIGHTS)) return false;
     const int taps = g.kh * g.kw, total = small_total(g);
     const int64_t tiles = (int64_t)((g.m + 31) / 32) * ((g.c_out + 31) / 32);
     const int splits = small_splits(1, g.c_out, total, taps, room);
+    const int64_t tiles64 = (int64_t)((g.m + 127) / 128) * ((g.c_out + 63) / 64);
+    if (taps == 1) {
+        // With a list 1x1 kernels are faster elsewhere (576 -> 96 on 16 x 14 x 14 6.3 us, 7.4 here).  Without one, what labels them here is
+        // a launch less, or one that ranks all positions in every workgroup, while the tiles are there at once (64 -> 64 on 53 x 33
+        // 7.3 -> 4.8 us, 256 -> 1024 on 28 x 28 16.3 -> 6.4, 64 -> 64 on 130 x 130 8.1 -> 6.0; past that, 256 -> 256 on 90 x 90, 2 032 tiles,
+        // 10.4 and 13.1), in two rounds where one stage is all they have (64 -> 256 on 90 x 90, 2 032 tiles, 10.6 -> 9.7; 16 ->
+        // 224 on 130 x 130, 3 703, 11.3 and 14.8).  Stages count: 256 -> 256 on 64 x 64, 1 024 tiles of four, with 30 % irrelevant 7.6
+        // and 7.8, 128 -> 128 on 90 x 90, 1 016 of two, 9.4 -> 6.0.
+        // Sums are the same as with a list, so they are cut where the tiled kernel cuts its 64 x 64 tiles, or not at all; past eight
+        // stages in one wave there is nothing left to win (768 -> 64 on 28 x 28 8.5 and 8.9; 512 -> 512 9.5 -> 7.4).
+        if (!needs_labels || tiles > (total == 1 ? 2048 : (total == 2 ? 1152 : 960))) return false;
+        if (total < 2 * kMinSplitStages) return total <= 8;
+        return room && tiles64 <= kSmallLayerTiles && tiles * splits <= 1152 && splits == small_splits(g.m, g.c_out, total, taps, room);
+    }
     // 3x3: what the tiled kernel would run on 64 x 64 tiles, while a CU gets no more than about four waves
     // (512 -> 512 on 8 x 7 x 7, 1 872 waves, is 14.8 us there and 24.6 us here)
-    if (taps == 9 && ((int64_t)((g.m + 127) / 128) * ((g.c_out + 63) / 64) > kSmallLayerTiles || tiles * splits > 1024)) return false;
+    if (taps == 9 && (tiles64 > kSmallLayerTiles || tiles * splits > 1024)) return false;
     // Packed reductions without a list: tiles that label their own rows take fewer stages (3x3 where nothing is split here, so that the sums are the same: 16 ->
     // 64 on 28 x 28 7.6 -> 5.2 us, 40 -> 96 7.6 -> 6.1; with splits there is little in it, 72 -> 200 8.3 -> 8.0, 136 -> 136 on 56 x 56 / 2 8.5 -> 8.6).  Other kernels label and gate more taps there: 24 ->
     // 128, 5x5, on 56 x 56 (1 568 waves, 10 stages) 15.6 -> 10.3, 40 -> 96 (1 176, 16) 9.9 -> 11.8; 136 -> 136 (1 960, 54) 25.6 -> 22.1, 80 -> 80 (1 176, 32) 12.3 -> 16.4.
@@ -750,26 +775,27 @@ static bool small_at_once(const Geom &g, bool room, bool masked)
 }
 
 template <int DT, typename TO>
-static hipError_t launch_small_t(const Geom &g, bool room, const void *x, const uint8_t *mask_in, const uint8_t *mask_out,
+static hipError_t launch_small_t(const Geom &g, bool as_pw, bool room, const void *x, const uint8_t *mask_in, const uint8_t *mask_out,
                                  const void *w, const float *bias, const int32_t *idx, const int32_t *count, void *out,
                                  float *partials, int32_t *tile_counters, hipStream_t s)
 {
     const bool once = small_at_once(g, room, mask_in != nullptr);
-    auto kern = once ? k_conv_small_once<DT, TO> : k_conv_small<DT, TO>;
+    const int which = once ? 0 : (as_pw ? 1 : 2);
+    auto kern = once ? k_conv_small_once<DT, TO> : (as_pw ? k_conv_small<DT, TO, true> : k_conv_small<DT, TO, false>);
     const uint32_t wave_bytes = once ? kOnceWaveBytes : kSmallWaveBytes;
     const int splits = small_splits(1, g.c_out, small_total(g), g.kh * g.kw, room); // the most any kept count gives
     const int waves = splits < kSmallWaves ? splits : kSmallWaves;
     // (more than 64 KB of dynamic LDS: allowed once per function and device)
-    static std::atomic<uint64_t> attr_devices[2] = {};
+    static std::atomic<uint64_t> attr_devices[3] = {};
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     const uint64_t dev_bit = 1ull << (dev & 63);
-    if (!(attr_devices[once].load(std::memory_order_acquire) & dev_bit)) {
+    if (!(attr_devices[which].load(std::memory_order_acquire) & dev_bit)) {
         e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)(kSmallWaves * wave_bytes));
         if (e != hipSuccess) return e;
-        attr_devices[once].fetch_or(dev_bit, std::memory_order_release);
+        attr_devices[which].fetch_or(dev_bit, std::memory_order_release);
     }
     SmallCut cut;
     cut.n_nt = (g.c_out + kSmallChannels - 1) / kSmallChannels;
@@ -787,11 +813,11 @@ static hipError_t launch_small_t(const Geom &g, bool room, const void *x, const 
     return hipGetLastError();
 }
 
-hipError_t launch_conv_small(const Geom &g, int in_dtype, int out_dtype, bool room, const void *x, const uint8_t *mask_in,
+hipError_t launch_conv_small(const Geom &g, int in_dtype, int out_dtype, bool as_pw, bool room, const void *x, const uint8_t *mask_in,
                              const uint8_t *mask_out, const void *w, const float *bias, const int32_t *idx,
                              const int32_t *count, void *out, float *partials, int32_t *tile_counters, hipStream_t s)
 {
-#define FC_SMALL(DT, TO) launch_small_t<DT, TO>(g, room, x, mask_in, mask_out, w, bias, idx, count, out, partials, tile_counters, s)
+#define FC_SMALL(DT, TO) launch_small_t<DT, TO>(g, as_pw, room, x, mask_in, mask_out, w, bias, idx, count, out, partials, tile_counters, s)
     if (in_dtype == FC_BF16)
         return out_dtype == FC_F32 ? FC_SMALL(FC_BF16, float) : (out_dtype == FC_FP8 ? FC_SMALL(FC_BF16, uint8_t) : FC_SMALL(FC_BF16, uint16_t));
     return out_dtype == FC_F32 ? FC_SMALL(FC_F16, float) : (out_dtype == FC_FP8 ? FC_SMALL(FC_F16, uint8_t) : FC_SMALL(FC_F16, uint16_t));

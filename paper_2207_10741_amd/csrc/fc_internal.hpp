@@ -451,13 +451,13 @@ hipError_t launch_conv_mfma(const Geom &g, int in_dtype, int out_dtype, const vo
                             const float *bias, const int32_t *idx, const int32_t *count, void *out,
                             float *partials, int32_t *tile_counters, hipStream_t s);
 
-// Layers of a few hundred tiles, 16-bit storage, more than one tap (see fc_conv_small.hip; shapes
+// Layers of a few hundred tiles, 16-bit storage; 1x1 kernels without a list only (see fc_conv_small.hip; shapes
 // conv_mfma_supported accepts).  Without a list the kernel labels the positions itself, from mask_out or the
 // centre tap of mask_in (needs_labels).  room: partials and tile_counters are there; conv_small_counts: the
-// counters are used and must be clear.
+// counters are used and must be clear.  as_pw (1x1 kernels): make the sums of launch_conv_pw, in one wave with the bias last.
 bool conv_small_wanted(const Geom &g, int in_dtype, bool room, bool needs_labels);
 bool conv_small_counts(const Geom &g, bool room);
-hipError_t launch_conv_small(const Geom &g, int in_dtype, int out_dtype, bool room, const void *x, const uint8_t *mask_in,
+hipError_t launch_conv_small(const Geom &g, int in_dtype, int out_dtype, bool as_pw, bool room, const void *x, const uint8_t *mask_in,
                              const uint8_t *mask_out, const void *w, const float *bias, const int32_t *idx,
                              const int32_t *count, void *out, float *partials, int32_t *tile_counters, hipStream_t s);
 
