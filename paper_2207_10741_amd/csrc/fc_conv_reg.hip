@@ -204,10 +204,13 @@ __global__ __launch_bounds__(kRegThreads, 2) void k_conv_f32(Geom g, const float
     // a row's offset is that of its first tap, which may lie in front of the tensor: x is read through a
     // descriptor that starts a padding's worth earlier (those taps are switched off, nothing in front
     // of the tensor is read), so that the per-lane part of an offset is never negative
-    const uint32_t xbias = (uint32_t)(g.ph * g.w + g.pw) * (uint32_t)g.c_in * 4u;
+    // (TAIL: x and w through descriptors that start one piece earlier still, since a row's last piece may begin before the lane's own offset, 33
+    // channels at three of the first chunk's, and the range is checked before a stage's scalar offset is added)
+    constexpr uint32_t lead = TAIL ? 16u : 0u;
+    const uint32_t xbias = (uint32_t)(g.ph * g.w + g.pw) * (uint32_t)g.c_in * 4u + lead;
     const u32x4_t rsrc_x = make_rsrc_words(reinterpret_cast<const unsigned char *>(x) - xbias,
                                            (uint32_t)g.n * g.h * g.w * g.c_in * 4u + xbias);
-    const u32x4_t rsrc_w = make_rsrc_words(w, (uint32_t)g.c_out * taps * g.c_in * 4u);
+    const u32x4_t rsrc_w = make_rsrc_words(reinterpret_cast<const unsigned char *>(w) - lead, (uint32_t)g.c_out * taps * g.c_in * 4u + lead);
     // A row whose length is no multiple of four ends in a piece of its last four channels, of which the
     // first `again` were already in the piece before it: they are cleared in both operands.  `edge` = first
     // channel of that piece.
@@ -229,7 +232,7 @@ __global__ __launch_bounds__(kRegThreads, 2) void k_conv_f32(Geom g, const float
 #pragma unroll
     for (int j = 0; j < WR; ++j) {
         const int co = co0 + prow + j * 32;
-        woff[j] = co < g.c_out ? (uint32_t)(co * taps * g.c_in + piece * 4) * 4u : kOutOfRange;
+        woff[j] = co < g.c_out ? (uint32_t)(co * taps * g.c_in + piece * 4) * 4u + lead : kOutOfRange;
     }
     const uint32_t lds0 =
         __builtin_amdgcn_readfirstlane((uint32_t)reinterpret_cast<uintptr_t>(stage) + (uint32_t)wave * 1024u);
@@ -650,8 +653,8 @@ static hipError_t launch_f32_rounds(const Geom &g, const void *x, const uint8_t 
 bool conv_f32_supported(const Geom &g)
 {
     return g.c_in >= 4 && g.kh * g.kw <= 64 && g.h <= 16384 && g.w <= 16384 && g.ph <= 8192 && g.pw <= 8192 &&
-           ((uint64_t)g.n * g.h * g.w + (uint64_t)g.ph * g.w + g.pw) * g.c_in * 4u < kBufferLimit &&
-           (uint64_t)g.c_out * g.kh * g.kw * g.c_in * 4u < kBufferLimit;
+           ((uint64_t)g.n * g.h * g.w + (uint64_t)g.ph * g.w + g.pw) * g.c_in * 4u + 16u < kBufferLimit &&
+           (uint64_t)g.c_out * g.kh * g.kw * g.c_in * 4u + 16u < kBufferLimit; // (16: the piece a descriptor may start earlier)
 }
 
 template <int TN, int WK, int NB, bool TAIL>
