@@ -393,7 +393,7 @@ __global__ __launch_bounds__(kRegThreads, 2) void k_conv_f32(Geom g, const float
 }
 
 // ---------------------------------------------------------------------------------------------
-// The same split (WK = 4) for 3x3 kernels of whole 32-channel chunks, horizontally undilated, with bytes for masks: what bounds k_conv_f32 there is not
+// The same split (WK = 4) for 3x3 kernels, horizontally undilated, with bytes for masks: what bounds k_conv_f32 there is not
 // the matrix cores (two workgroups of a CU: 9 200 cycles) but what its waves issue beside them: stamps of 64 -> 64 on 2 x 60 x 80, half
 // kept, 5 100 cycles to the rows' bits (three divisions by run-time numbers a look-up, five barriers), 13 500 in the stages, 3 500 from there to
 // the last store.  Here
@@ -412,8 +412,8 @@ template <int RING> constexpr uint32_t kF32Zeros = RING * kF32Round * kF32Stage;
 template <int RING> constexpr uint32_t kF32Lds = kF32Zeros<RING> + 128u;
 constexpr int kF32MostStages = 63; // a lane each
 
-// RING: rounds in LDS
-template <int RING>
+// RING: rounds in LDS; TAIL: the input channels are not whole 32-channel stages
+template <int RING, bool TAIL>
 __global__ __launch_bounds__(kRegThreads, RING == 2 ? 3 : 2) void k_conv_f32_rounds(Geom g, FastDiv by_cch, const float *__restrict__ x,
                                                                     const uint8_t *__restrict__ mask_in,
                                                                     const uint8_t *__restrict__ mask_out,
@@ -455,13 +455,23 @@ __global__ __launch_bounds__(kRegThreads, RING == 2 ? 3 : 2) void k_conv_f32_rou
     const int prow = wave * 8 + (lane >> 3);
     const uint32_t piece = (uint32_t)((lane & 7) ^ FC_SWZ(prow)) * 16u;
     const uint32_t pixel = (uint32_t)g.c_in * 4u, wrow = 9u * pixel;
-    const int cch = g.c_in >> 5, stages = 9 * cch;
+    const int cch = (g.c_in + 31) >> 5, stages = 9 * cch;
     const u32x4_t rsrc_w = make_rsrc_words(w, (uint32_t)g.c_out * wrow);
     uint32_t woff = (uint32_t)(co0 + prow) * wrow + piece;
     __asm__("" : "+v"(woff));
     woff = co0 + prow < g.c_out ? woff : kOutOfRange;
-    const int tap_q = (int)fast_div((uint32_t)lane, by_cch), kh_q = tap_q * 11 >> 5;
-    const int x_q = (kh_q * g.dh * g.w + (tap_q - 3 * kh_q)) * (int)pixel + (lane - tap_q * cch) * 128, bit_q = 1 << (tap_q & 31);
+    const int tap_q = (int)fast_div((uint32_t)lane, by_cch), kh_q = tap_q * 11 >> 5, cc_q = lane - tap_q * cch;
+    // (TAIL: bit 31 marks the last stage of a tap)
+    const int bit_q = 1 << (tap_q & 15) | (TAIL && cc_q + 1 == cch ? 1 << 31 : 0);
+    const int x_q = (kh_q * g.dh * g.w + (tap_q - 3 * kh_q)) * (int)pixel + cc_q * 128, w_q = tap_q * (int)pixel + cc_q * 128;
+    // TAIL: what a tap's last stage loads: nothing past the last channel, and a row whose length is no multiple of four ends in a piece of
+    // its last four channels, of which the first `again` were already in the piece before it: they are cleared in both operands.
+    const uint32_t left = (uint32_t)(g.c_in - (cch - 1) * 32) * 4u; // bytes of that stage
+    const int again = TAIL ? (4 - (g.c_in & 3)) & 3 : 0;
+    const uint32_t back = again && piece == (left & ~15u) ? (uint32_t)again * 4u : 0u;
+    const bool past = piece >= left;
+    const uint32_t woff_last = past || woff == kOutOfRange ? kOutOfRange : woff - back;
+    const int cleared = 2 * wave + half == (int)(left >> 4) ? again : 0; // of the piece that this lane multiplies
     if (tid < 8) *reinterpret_cast<uint4 *>(lds + kF32Zeros<RING> + tid * 16) = make_uint4(0u, 0u, 0u, 0u);
 
     // ---- the rows ----
@@ -520,6 +530,7 @@ __global__ __launch_bounds__(kRegThreads, RING == 2 ? 3 : 2) void k_conv_f32_rou
     const u32x4_t rsrc_x = make_rsrc_words(x, (uint32_t)g.n * g.h * g.w * pixel);
     // (what lies outside the tensor is out of range, whichever side; what lies in it beside the image is not looked at)
     const uint32_t xoff = (uint32_t)__shfl(pix0, prow) * pixel + piece;
+    const uint32_t xoff_last = past ? kOutOfRange : xoff - back; // (out of range with a tap's offset added, see f32_rounds)
     auto load_round = [&](int s, int slot) __attribute__((always_inline)) {
         uint32_t sx[kF32Round], sw[kF32Round];
 #pragma unroll
@@ -527,6 +538,22 @@ __global__ __launch_bounds__(kRegThreads, RING == 2 ? 3 : 2) void k_conv_f32_rou
             sx[d] = (uint32_t)__builtin_amdgcn_readlane(x_q, s + d);
             sw[d] = (uint32_t)(s + d) * 128u;
             __asm__ volatile("" : "+s"(sw[d]));
+        }
+        if constexpr (TAIL) {
+            uint32_t ox[kF32Round], ow[kF32Round];
+#pragma unroll
+            for (int d = 0; d < kF32Round; ++d) {
+                const bool last = __builtin_amdgcn_readlane(bit_q, s + d) < 0;
+                ox[d] = (last ? xoff_last : xoff) + sx[d];
+                // (by the vector unit: what it wrote into a scalar register may not be a load's scalar offset right after)
+                ow[d] = (last ? woff_last : woff) + (uint32_t)__builtin_amdgcn_readlane(w_q, s + d);
+            }
+#pragma unroll
+            for (int d = 0; d < kF32Round; ++d) {
+                dma_load16(rsrc_x, ox[d], lds0 + (uint32_t)(slot + d) * kF32Stage);
+                dma_load16(rsrc_w, ow[d], lds0 + (uint32_t)(slot + d) * kF32Stage + 4096u);
+            }
+            return;
         }
 #pragma unroll
         for (int d = 0; d < kF32Round; ++d) {
@@ -570,6 +597,14 @@ __global__ __launch_bounds__(kRegThreads, RING == 2 ? 3 : 2) void k_conv_f32_rou
             wv[d] = *reinterpret_cast<const float4 *>(lds + slot + 4096u + at);
         }
         __builtin_amdgcn_sched_barrier(0);
+        if (TAIL && again) // uniform
+#pragma unroll
+            for (int d = 0; d < kF32Round; ++d) {
+                const int drop = __builtin_amdgcn_readlane(bit_q, s + d) < 0 ? cleared : 0;
+                xv[d].x = drop > 0 ? 0.f : xv[d].x; wv[d].x = drop > 0 ? 0.f : wv[d].x;
+                xv[d].y = drop > 1 ? 0.f : xv[d].y; wv[d].y = drop > 1 ? 0.f : wv[d].y;
+                xv[d].z = drop > 2 ? 0.f : xv[d].z; wv[d].z = drop > 2 ? 0.f : wv[d].z;
+            }
         if (s + (RING - 1) * kF32Round < stages) load_round(s + (RING - 1) * kF32Round, (r + RING - 1) % RING * kF32Round);
 #pragma unroll
         for (int d = 0; d < kF32Round; ++d) {
@@ -608,11 +643,12 @@ __global__ __launch_bounds__(kRegThreads, RING == 2 ? 3 : 2) void k_conv_f32_rou
 
 static bool f32_rounds(const Geom &g, bool masked)
 {
-    return g.kh == 3 && g.kw == 3 && g.dw == 1 && g.c_in % 32 == 0 && 9 * (g.c_in / 32) <= kF32MostStages &&
+    return g.kh == 3 && g.kw == 3 && g.dw == 1 && 9 * ((g.c_in + 31) / 32) <= kF32MostStages &&
+           (g.c_in % 32 == 0 || ((int64_t)g.dh * g.w + 1) * 2 * g.c_in * 4 < (int64_t)(0xffffffffu - kOutOfRange)) &&
            (!masked || (!(g.flags & FC_PACKED_MASKS) && (int64_t)g.n * g.h * g.w >= 4));
 }
 
-template <int RING>
+template <int RING, bool TAIL>
 static hipError_t launch_f32_ring(const Geom &g, const void *x, const uint8_t *mask_in, const uint8_t *mask_out, const void *w,
                                     const float *bias, const int32_t *idx, const int32_t *count, void *out, hipStream_t s)
 {
@@ -623,12 +659,12 @@ static hipError_t launch_f32_ring(const Geom &g, const void *x, const uint8_t *m
     if (e != hipSuccess) return e;
     const uint64_t dev_bit = 1ull << (dev & 63);
     if (!(attr_devices.load(std::memory_order_acquire) & dev_bit)) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_conv_f32_rounds<RING>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kF32Lds<RING>);
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_conv_f32_rounds<RING, TAIL>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kF32Lds<RING>);
         if (e != hipSuccess) return e;
         attr_devices.fetch_or(dev_bit, std::memory_order_release);
     }
-    hipLaunchKernelGGL(k_conv_f32_rounds<RING>, dim3((g.m + 31) / 32, (g.c_out + 31) / 32), dim3(kRegThreads), kF32Lds<RING>, s, g,
-                       make_fastdiv((uint32_t)(g.c_in / 32)), (const float *)x, mask_in, mask_out, (const float *)w, bias, idx, count, (float *)out);
+    hipLaunchKernelGGL((k_conv_f32_rounds<RING, TAIL>), dim3((g.m + 31) / 32, (g.c_out + 31) / 32), dim3(kRegThreads), kF32Lds<RING>, s, g,
+                       make_fastdiv((uint32_t)((g.c_in + 31) / 32)), (const float *)x, mask_in, mask_out, (const float *)w, bias, idx, count, (float *)out);
     return hipGetLastError();
 }
 
@@ -644,8 +680,11 @@ static hipError_t launch_f32_rounds(const Geom &g, const void *x, const uint8_t 
     // 21.8, on 3 x 50 x 50 (940) 26.3 / 27.0 / 28.0 -> 21.6 / 22.7 / 33.3.  Masks that keep nine tenths fill more tiles than that: 2 x 60 x 80 13.6 -> 16.8, with a list 17.1 -> 19.6.
     const int64_t tiles = (int64_t)((g.m + 31) / 32) * ((g.c_out + 31) / 32), busy = idx ? tiles * 7 / 10 : mask_in ? tiles * 17 / 20 : tiles;
     const int cus = conv_grid_cus();
-    if (busy > cus && busy <= 2 * cus) return launch_f32_ring<3>(g, x, mask_in, mask_out, w, bias, idx, count, out, s);
-    return launch_f32_ring<2>(g, x, mask_in, mask_out, w, bias, idx, count, out, s);
+#define FC_RING(RING)                                                                                                        \
+    (g.c_in % 32 ? launch_f32_ring<RING, true>(g, x, mask_in, mask_out, w, bias, idx, count, out, s)                         \
+                 : launch_f32_ring<RING, false>(g, x, mask_in, mask_out, w, bias, idx, count, out, s))
+    return busy > cus && busy <= 2 * cus ? FC_RING(3) : FC_RING(2);
+#undef FC_RING
 }
 
 // four channels: one piece; 64 taps: the tap-valid bits of a row; 32-bit byte offsets into x and w; row
@@ -684,7 +723,14 @@ hipError_t launch_conv_f32(const Geom &g, const void *x, const uint8_t *mask_in,
     const int64_t waves = (int64_t)((g.m + 31) / 32) * (wide ? blocks32 / 2 : blocks32);
     // (k_conv_f32_rounds without a mask too: 96 -> 128 on 4 x 67 x 90 70 -> 58 us, 128 -> 64 on 3 x 100 x 110 88 -> 56; 128 -> 128 on 8 x 120 x 120, 7 200
     // waves, 322 -> 332, with a mask 233 / 244 / 251 -> 175 / 229 / 267 at 0.3 / 0.5 / 0.7 kept)
-    if (waves < 4096 && f32_rounds(g, mask_in != nullptr)) return launch_f32_rounds(g, x, mask_in, mask_out, w, bias, idx, count, out, s);
+    // Channels past whole chunks are a quarter to three quarters of a stage that its four waves wait for together.  Mask given, us, general
+    // kernel -> rounds: 76 -> 40 on 4 x 91 x 51 30.2 -> 22.7, 16 -> 56 on 7 x 32 x 89 19.7 -> 13.9, 21 -> 44 on 2 x 17 x 38 8.6 -> 5.7, 100 -> 110 on
+    // 5 x 54 x 102 91.6 -> 75.7, 20 -> 128 on 8 x 120 x 120 66.8 -> 67.0.  Without a mask as much while a wave a block of rows is too few (52 -> 73 on 2 x
+    // 57 x 26 12.7 -> 10.1); then that wave, which multiplies no padding, is better unless there is next to none: 100 -> 110 on 5 x 54 x 102 (13 of 16
+    // steps) 81 -> 91, 33 -> 65 on 4 x 90 x 90 (5 of 8) 42 -> 49, but 95 -> 116 on 4 x 67 x 90 (12 of 12) 71 -> 67, 120 -> 60 on 3 x 100 x 110
+    // (15 of 16) 85 -> 59.
+    const bool padded = (g.c_in + 7) / 8 * 16 < (g.c_in + 31) / 32 * 4 * 15;
+    if (waves < (mask_in || !padded ? 4096 : 1024) && f32_rounds(g, mask_in != nullptr)) return launch_f32_rounds(g, x, mask_in, mask_out, w, bias, idx, count, out, s);
     if (waves < (mask_in ? 4096 : 1024)) return FC_F32(32, 4, 6);
     return wide ? FC_F32(64, 1, 2) : FC_F32(32, 1, 3);
 #undef FC_F32
