@@ -125,7 +125,7 @@
     // Units of one tile are adjacent in the order, so they share an XCD.  S is the same in
     // every workgroup (it depends on the kept count and the grid only).
     int S = 1;
-    if (!OWN && partials && ntiles > 0) S = split_k_splits(ntiles, (int)gridDim.x, HALO ? g.kh * cchunks : stages, stages);
+    if (!OWN && partials && ntiles > 0) S = split_k_splits(ntiles, (int)gridDim.x, HALO ? g.kh * cchunks : stages, stages, (g.flags & kOneUnitPerCu) != 0);
     const int nunits = ntiles * S;
     const int per_xcd = (nunits + 7) >> 3;
     const int xcd = blockIdx.x & 7;

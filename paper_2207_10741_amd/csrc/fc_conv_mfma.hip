@@ -313,8 +313,12 @@ static hipError_t launch_dma(const Geom &g, const void *x, const uint8_t *mask_i
     const int64_t max_tiles = (int64_t)((g.m + TM - 1) / TM) * ((g.c_out + TN - 1) / TN);
     const int64_t cap = 256 * 8;
     int blocks = (int)((max_tiles < cap ? max_tiles : cap) + 7) & ~7; // a multiple of the XCD count
-    if (partials && !OWN) blocks = kSplitGrid; // few tiles: enough workgroups for the K-split to fill the chip
-    hipLaunchKernelGGL(kern, dim3(blocks), dim3(WM * WN * 64), lds, s, g, (const uint16_t *)x, mask_in, mask_out,
+    Geom gl = g;
+    if (partials && !OWN) {
+        blocks = kSplitGrid; // few tiles: enough workgroups for the K-split to fill the chip
+        if (splits_of_its_own(g, DT, TM)) gl.flags |= kOneUnitPerCu;
+    }
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(WM * WN * 64), lds, s, gl, (const uint16_t *)x, mask_in, mask_out,
                        (const uint16_t *)w, bias, idx, count, (TO *)out, partials, tile_counters);
     return hipGetLastError();
 }

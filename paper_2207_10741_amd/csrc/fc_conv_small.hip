@@ -749,7 +749,7 @@ bool conv_small_wanted(const Geom &g, int in_dtype, bool room, bool needs_labels
     }
     // 3x3: what the tiled kernel would run on 64 x 64 tiles, while a CU gets no more than about four waves
     // (512 -> 512 on 8 x 7 x 7, 1 872 waves, is 14.8 us there and 24.6 us here)
-    if (taps == 9 && (tiles64 > kSmallLayerTiles || tiles * splits > 1024)) return false;
+    if (taps == 9 && (tiles64 > kSmallLayerTiles || tiles * splits > kSmallSplitWaves)) return false;
     // Packed reductions without a list: tiles that label their own rows take fewer stages (3x3 where nothing is split here, so that the sums are the same: 16 ->
     // 64 on 28 x 28 7.6 -> 5.2 us, 40 -> 96 7.6 -> 6.1; with splits there is little in it, 72 -> 200 8.3 -> 8.0, 136 -> 136 on 56 x 56 / 2 8.5 -> 8.6).  Other kernels label and gate more taps there: 24 ->
     // 128, 5x5, on 56 x 56 (1 568 waves, 10 stages) 15.6 -> 10.3, 40 -> 96 (1 176, 16) 9.9 -> 11.8; 136 -> 136 (1 960, 54) 25.6 -> 22.1, 80 -> 80 (1 176, 32) 12.3 -> 16.4.

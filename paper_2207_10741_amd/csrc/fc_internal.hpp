@@ -389,10 +389,18 @@ static inline bool split_k_possible(const Geom &g)
 constexpr int kMinSplitStages = 8;
 constexpr int kMaxSplits = 16;         // most K-splits of one tile
 constexpr int kBusySplitStages = 64;   // shortest reduction that is split on a busy chip
-// Splits of a reduction of `stages` stages (dealt out in `work` pieces) of each of ntiles tiles on `grid` workgroups.
-__host__ __device__ static inline int split_k_splits(int ntiles, int grid, int work, int stages)
+// Splits of a reduction of `stages` stages (dealt out in `work` pieces) of each of ntiles tiles on `grid` workgroups, two a CU.
+// one_a_cu: no more units than a workgroup a CU, as long as that leaves them few stages: two of a CU slow each other, and every split is
+// a tile more to park and to read back.  us, two a CU -> one: 488 -> 248, 3x3, on 8 x 15 x 19 (32 tiles in 9 -> 8 splits) 20.0 -> 16.8, E4M3
+// 208 -> 64, 5x5 / 2, on 17 x 32 x 87 (52 in 6 -> 4) 22.5 -> 19.3, 384 -> 128, 3x3, on 3 x 60 x 60 15.7 -> 13.8, 512 -> 512 on 32 x 7 x 7 (56 in 9 -> 4)
+// 20.6 -> 17.7; without a mask (104 tiles of 72 stages in 4 -> 2) 21.2 -> 21.8, 1024 -> 64 on 5 x 31 x 40 (50 of 144 in 10 -> 5) 18.5 -> 21.6.
+__host__ __device__ static inline int split_k_splits(int ntiles, int grid, int work, int stages, bool one_a_cu = false)
 {
     int s = grid / ntiles;
+    if (one_a_cu && s > 1) {
+        const int half = s >> 1; // = grid / (2 * ntiles)
+        if (stages <= 24 * half) s = half;
+    }
     s = s < 1 ? 1 : (s > work ? work : s);
     if (s > kMaxSplits) s = kMaxSplits;
     // the exchange of partial tiles costs about as much as twenty stages, so a unit keeps at
@@ -405,6 +413,17 @@ __host__ __device__ static inline int split_k_splits(int ntiles, int grid, int w
     // 16 x 16, batch 16: 72 stages split three ways 31 -> 26 us, 36 stages 20 -> 28 us)
     if (ntiles * 4 > grid && stages < kBusySplitStages) s = 1;
     return s;
+}
+constexpr int kSmallSplitWaves = 1024; // a 3x3 layer goes to conv_small with at most this many waves
+constexpr uint32_t kOneUnitPerCu = 1u << 31; // flag of a launch: split_k_splits' one_a_cu (decided on the host: as device code it cost 0.2 us)
+// May the tiled kernel keep its splits to one unit a CU?  Not where another kernel makes the same sums for the same layer, with the list or
+// without it: small 16-bit layers (the rules of conv_small_wanted), and all 1x1 kernels on 64 x 64 tiles.
+static inline bool splits_of_its_own(const Geom &g, int in_dtype, int tile_rows)
+{
+    if (tile_rows > 64 || in_dtype == FC_FP8) return true;
+    if (g.kh * g.kw != 9) return g.kh * g.kw != 1;
+    const int total = 9 * ((g.c_in + 63) / 64);
+    return ((g.m + 31) / 32) * ((g.c_out + 31) / 32) * split_k_splits((g.c_out + 63) / 64, kSplitGrid, total, total) > kSmallSplitWaves;
 }
 constexpr int kSmallLayerTiles = 64;   // layers with at most this many 128 x 64 tiles use small tiles
 // Does the tiled kernel take a reduction as one run of 16-byte pieces, eight a stage whatever tap they belong to, instead of tap by tap in whole
