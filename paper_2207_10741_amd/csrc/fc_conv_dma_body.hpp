@@ -149,8 +149,14 @@
             u32x4_t *o4 = reinterpret_cast<u32x4_t *>(out);
             const u32x4_t zero4 = {0u, 0u, 0u, 0u};
             const int ch0 = -g.ph + g.dh * ((g.kh - 1) / 2), cw0 = -g.pw + g.dw * ((g.kw - 1) / 2);
-            for (int p0 = worker * 64; p0 < g.m; p0 += nworkers * 64) {
-                const int pp = p0 + lane;
+            // Where there are more waves than blocks of 64 positions, as many as have a row's sixteen pieces each share a block: one wave alone
+            // stores 1 KB at a time, and 512 -> 2048 on 2 x 7 x 7 has two blocks of 128 KB to clear (15.2 -> 6.2 us, chained 6.1; 320 -> 1280 on 32 x 7 x 7
+            // 12.3 -> 6.7, 256 -> 1024 on 2 x 14 x 14 11.7 -> 5.2).  Narrow rows leave one wave little, and more of them disturb the tiles (960 -> 160 on
+            // 32 x 14 x 14 shared by all 10.3 -> 10.6).
+            const int nblocks = (g.m + 63) >> 6, parts = max(min(nworkers / nblocks, cpr / 16), 1);
+            for (int item = worker; item < nblocks * parts; item += nworkers) {
+                const int blk = item / parts, part = item - blk * parts;
+                const int pp = blk * 64 + lane;
                 bool kept = true;
                 if (pp < g.m) {
                     if (mask_out) {
@@ -168,7 +174,7 @@
                 if (!kept) dropped[__popcll(drop & ((1ull << lane) - 1ull))] = pp; // in position order
                 wave_lds_order();
                 const int total = nd * cpr;
-                for (int c = lane; c < total; c += 64) {
+                for (int c = part * 64 + lane; c < total; c += parts * 64) {
                     const int rk = c / cpr, pc = c - rk * cpr;
                     __builtin_nontemporal_store(zero4, o4 + (int64_t)dropped[rk] * cpr + pc);
                 }
