@@ -433,9 +433,10 @@ __global__ __launch_bounds__(kRegThreads, RING == 2 ? 3 : 2) void k_conv_f32_rou
     // ---- request what decides about the rows ----
     int p = first + l32;
     bool live = p < rows;
-    // (values of loads that are waited for by hand are touched by nothing before the wait)
+    // (values of loads that are waited for by hand are touched by nothing before the wait; by a scalar, so that no path leads from one load to the other)
+    const int by_list = TAIL ? __builtin_amdgcn_readfirstlane(idx != nullptr ? 1 : 0) : idx != nullptr;
     uint32_t entry, label;
-    if (idx) {
+    if (by_list) {
         const u32x4_t rsrc_i = make_rsrc_words(idx, (uint32_t)rows * 4u);
         __asm__ volatile("buffer_load_dword %0, %1, %2, 0 offen" : "=v"(entry) : "v"((uint32_t)p * 4u), "s"(rsrc_i) : "memory");
     } else if (mask_in) {
@@ -455,14 +456,14 @@ __global__ __launch_bounds__(kRegThreads, RING == 2 ? 3 : 2) void k_conv_f32_rou
     const int prow = wave * 8 + (lane >> 3);
     const uint32_t piece = (uint32_t)((lane & 7) ^ FC_SWZ(prow)) * 16u;
     const uint32_t pixel = (uint32_t)g.c_in * 4u, wrow = 9u * pixel;
-    const int cch = (g.c_in + 31) >> 5, stages = 9 * cch;
+    const int cch = TAIL ? (g.c_in + 31) >> 5 : g.c_in >> 5, stages = 9 * cch;
     const u32x4_t rsrc_w = make_rsrc_words(w, (uint32_t)g.c_out * wrow);
     uint32_t woff = (uint32_t)(co0 + prow) * wrow + piece;
     __asm__("" : "+v"(woff));
     woff = co0 + prow < g.c_out ? woff : kOutOfRange;
     const int tap_q = (int)fast_div((uint32_t)lane, by_cch), kh_q = tap_q * 11 >> 5, cc_q = lane - tap_q * cch;
     // (TAIL: bit 31 marks the last stage of a tap)
-    const int bit_q = 1 << (tap_q & 15) | (TAIL && cc_q + 1 == cch ? 1 << 31 : 0);
+    const int bit_q = TAIL ? 1 << (tap_q & 15) | (cc_q + 1 == cch ? 1 << 31 : 0) : 1 << (tap_q & 31);
     const int x_q = (kh_q * g.dh * g.w + (tap_q - 3 * kh_q)) * (int)pixel + cc_q * 128, w_q = tap_q * (int)pixel + cc_q * 128;
     // TAIL: what a tap's last stage loads: nothing past the last channel, and a row whose length is no multiple of four ends in a piece of
     // its last four channels, of which the first `again` were already in the piece before it: they are cleared in both operands.
@@ -477,7 +478,7 @@ __global__ __launch_bounds__(kRegThreads, RING == 2 ? 3 : 2) void k_conv_f32_rou
     // ---- the rows ----
     wait_vmcnt<0>();
     bool drop = false;
-    if (idx) {
+    if (by_list) {
         __asm__ volatile("" : "+v"(entry)::"memory");
         p = live ? (int)entry : 0;
     } else if (mask_in) {
