@@ -83,10 +83,13 @@ __device__ __forceinline__ void pair_finish(f32x16_t &v, const float *bias, int 
 }
 
 // N middle blocks -> the second layer's operands, rounded as the first layer's output is: two steps a block of a 16-bit type, one step of
-// two blocks of bytes
+// two blocks of bytes.  Channels past the last one become zeros: their weights are zeros, but zero times an infinite pixel is NaN, and NaN
+// times the second layer's zeros would be every output channel's.  (c_mid is a multiple of 8: whole runs of both halves.  A branch that
+// the whole wave takes, in the last blocks only.)
 template <int DT, typename TO, int N>
-__device__ __forceinline__ void pair_middle(f32x16_t *acc, const float *bias, int block0, int half, bool first, bool relu1, Frag<DT> *h)
+__device__ __forceinline__ void pair_middle(f32x16_t *acc, const float *bias, int block0, int c_mid, int half, bool first, bool relu1, Frag<DT> *h)
 {
+    const bool past = (block0 + N) * 32 > c_mid;
 #pragma unroll
     for (int b = 0; b < N; ++b) pair_finish(acc[b], bias, block0 + b, half, first);
     if constexpr (sizeof(TO) == 2) {
@@ -97,6 +100,11 @@ __device__ __forceinline__ void pair_middle(f32x16_t *acc, const float *bias, in
             for (int q = 0; q < 4; ++q) {
                 store4<DT, TO>(reinterpret_cast<TO *>(&run[q]), acc[b][q * 4], acc[b][q * 4 + 1], acc[b][q * 4 + 2], acc[b][q * 4 + 3]);
                 if (relu1) run[q].x = relu_packed16(run[q].x), run[q].y = relu_packed16(run[q].y);
+            }
+            if (past) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if ((block0 + b) * 32 + q * 8 >= c_mid) run[q] = make_uint2(0u, 0u);
             }
 #pragma unroll
             for (int q = 0; q < 4; q += 2) {
@@ -117,6 +125,13 @@ __device__ __forceinline__ void pair_middle(f32x16_t *acc, const float *bias, in
         };
         if (relu1) pack(std::true_type());
         else pack(std::false_type());
+        if (past) {
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if ((block0 + b) * 32 + q * 8 >= c_mid) run[b][q] = 0u;
+        }
 #pragma unroll
         for (int q = 0; q < 4; ++q) swap_halves(run[0][q], run[1][q]);
         h[0].v = make_uint4(run[0][0], run[1][0], run[0][1], run[1][1]);
@@ -377,7 +392,7 @@ void k_conv_pair(PairArgs a, const int32_t *__restrict__ count, const int32_t *_
 #pragma unroll
                     for (int b = 0; b < 2; ++b) acc1[b] = mfma32<DT>(wf[b], xf[kk], acc1[b]);
                 }
-                pair_middle<DT, TO, 2>(acc1, b1s, block, half, first1, relu1, h);
+                pair_middle<DT, TO, 2>(acc1, b1s, block, a.c_mid, half, first1, relu1, h);
                 // (the middle's chunk of these blocks, and the first step of it they are: bytes lie four blocks to a chunk)
                 const unsigned char *ws = w2s + (uint32_t)(sizeof(TO) == 2 ? block >> 1 : block >> 2) * (uint32_t)a.out_rows * 128u;
                 const int kk0 = sizeof(TO) == 2 ? 0 : (block >> 1) & 1;
@@ -413,7 +428,7 @@ void k_conv_pair(PairArgs a, const int32_t *__restrict__ count, const int32_t *_
                 --ahead;
                 buf = buf + 1 == a.ring ? 0 : buf + 1;
             }
-            pair_middle<DT, TO, MB>(acc1, b1s, 0, half, first1, relu1, h);
+            pair_middle<DT, TO, MB>(acc1, b1s, 0, a.c_mid, half, first1, relu1, h);
             unsigned char *const stg = const_cast<unsigned char *>(xs);
 #pragma unroll 1
             for (int block = out_from; block < out_to; block += 2) {
@@ -548,7 +563,7 @@ void k_conv_pair_stream(PairArgs a, const int32_t *__restrict__ count, const int
 #pragma unroll
                         for (int b = 0; b < MB; ++b) acc1[b] = mfma32<DT>(wf[b], xf[c * KK + kk], acc1[b]);
                     }
-                pair_middle<DT, TO, MB>(acc1, b1s, stage * (MID / 32) + mb, half, first1, (a.flags & kPairRelu1) != 0, h);
+                pair_middle<DT, TO, MB>(acc1, b1s, stage * (MID / 32) + mb, INT32_MAX, half, first1, (a.flags & kPairRelu1) != 0, h);
 #pragma unroll
                 for (int kk = 0; kk < STEPS; ++kk) {
                     const int step = DT == FC_FP8 ? mb / 2 : mb * 2 + kk;
