@@ -13,8 +13,10 @@
 #include <c10/core/impl/TorchDispatchModeTLS.h>
 #include <c10/hip/HIPStream.h>
 #include <hip/hip_runtime_api.h>
+#include <pybind11/gil.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/csrc/utils/object_ptr.h>
 
 #include "focused_conv.h"
 
@@ -94,39 +96,41 @@ PyObject *call(PyObject *, PyObject *const *args, Py_ssize_t n)
 
     const at::Tensor &x = THPVariable_Unpack(args[2]);
     void *const stream = c10::hip::getCurrentHIPStream().stream();
-    PyObject *ws = args[10];
-    if (ws == Py_None && args[5] != Py_None && args[7] == Py_None && groups >= 0) {
-        ws = kept_workspace(need, x, stream);
-        if (!ws) Py_RETURN_NONE;        // (binding.py makes it, and keeps it where it may)
+    PyObject *scratch_in = args[10];
+    if (scratch_in == Py_None && args[5] != Py_None && args[7] == Py_None && groups >= 0) {
+        scratch_in = kept_workspace(need, x, stream);
+        if (!scratch_in) Py_RETURN_NONE;    // (binding.py makes it, and keeps it where it may)
     }
-    Py_INCREF(ws);                      // (another thread may replace what is kept while the lock is not held)
-    PyObject *out = args[9];
-    if (out == Py_None) {
+    // (both are given back whatever the allocation throws; another thread may replace what is kept while the lock is not held)
+    THPObjectPtr ws = THPObjectPtr::dup(scratch_in);
+    THPObjectPtr out;
+    if (args[9] == Py_None) {
         static constexpr c10::ScalarType types[] = {c10::kFloat, c10::kBFloat16, c10::kHalf, c10::ScalarType::Float8_e4m3fn};
         const int64_t shape[] = {desc.n, ho, wo, desc.c_out};
-        out = THPVariable_Wrap(at::empty(shape, x.options().dtype(types[desc.out_dtype]).requires_grad(false)));
-        if (!out) {
-            Py_DECREF(ws);
-            return nullptr;
+        const auto options = x.options().dtype(types[desc.out_dtype]).requires_grad(false);
+        at::Tensor made;
+        {
+            const pybind11::gil_scoped_release unlocked;    // (an allocation may wait for the device)
+            made = at::empty(shape, options);
         }
+        out = THPVariable_Wrap(std::move(made));
+        if (!out) return nullptr;
     } else {
-        Py_INCREF(out);
+        out = THPObjectPtr::dup(args[9]);
     }
-    const size_t ws_bytes = ws == Py_None ? 0 : THPVariable_Unpack(ws).nbytes();
+    const size_t ws_bytes = ws.get() == Py_None ? 0 : THPVariable_Unpack(ws.get()).nbytes();
     const void *const xp = address(args[2]), *const w = address(args[3]);
     const float *const bias = static_cast<float *>(address(args[4]));
     const uint8_t *const mask_in = static_cast<uint8_t *>(address(args[5])), *const mask_out = static_cast<uint8_t *>(address(args[6]));
     const int32_t *const idx = static_cast<int32_t *>(address(args[7])), *const count = static_cast<int32_t *>(address(args[8]));
-    void *const to = address(out), *const scratch = address(ws);
+    void *const to = address(out.get()), *const scratch = address(ws.get());
     int32_t status;
     Py_BEGIN_ALLOW_THREADS
     status = groups < 0    ? fn.dwconv2d(&desc, xp, mask_in, w, bias, to, stream)
              : groups == 0 ? fn.conv2d(&desc, xp, mask_in, w, bias, mask_out, idx, count, to, scratch, ws_bytes, stream)
                            : fn.gconv2d(&desc, static_cast<int32_t>(groups), xp, mask_in, w, bias, mask_out, idx, count, to, scratch, ws_bytes, stream);
     Py_END_ALLOW_THREADS
-    Py_DECREF(ws);
-    if (status == FC_OK) return out;
-    Py_DECREF(out);
+    if (status == FC_OK) return out.release();
     return PyLong_FromLong(status);
     END_HANDLE_TH_ERRORS
 }
