@@ -192,20 +192,18 @@ def _ptr(t):
 
 # A call of a small layer costs a few microseconds on the device, so the host side of one is kept as short.  Plain calls go
 # through csrc/fc_python.cpp whole (tensors checked, output made, stream and workspace looked up in C++: a call of a 64 -> 64
-# layer on 1 x 56 x 56 takes the host 4.6 us so, 8.4 in Python); it answers None to any other, which is then made here.  Here the
-# stream's handle comes from torch's C function (torch.cuda.current_stream() builds a Python object around it, 2.8 us against
-# 0.1 us), and sizes that only depend on the descriptor are looked up.
+# layer on 1 x 56 x 56 takes the host 4.6 us so, 8.4 in Python); it answers None to any other, which is then made here, as all are
+# where only the C library has been built.  Here the stream's handle comes from torch's C function (torch.cuda.current_stream()
+# builds a Python object around it, 2.8 us against 0.1 us), and sizes that only depend on the descriptor are looked up.
 
 _native_module = None
 
 
 def _native():
-    """The extension, bound to the C library; raises if it has not been built."""
+    """The extension, bound to the C library; None if it has not been built."""
     global _native_module
-    if _native_module is None:
+    if _native_module is None and os.path.exists(NATIVE_PATH):
         L = lib()
-        if not os.path.exists(NATIVE_PATH):
-            raise ImportError("%s is missing: build it with `python -m paper_2207_10741_amd.build`" % NATIVE_PATH)
         from . import _native as module
         address = lambda f: ctypes.cast(f, ctypes.c_void_p).value
         module.bind(tuple(address(f) for f in (L.fc_focused_conv2d, L.fc_focused_gconv2d, L.fc_focused_dwconv2d, L.fc_mask_pyramid,
@@ -214,14 +212,39 @@ def _native():
     return _native_module
 
 
+def _no_call(*args):
+    return None
+
+
 def _first_call(*args):
     global _call
-    _call = _native().call
+    module = _native()
+    _call = _no_call if module is None else module.call
     return _call(*args)
 
 
 _call = _first_call     # the extension's function once it is loaded
 _CONV, _DWCONV, _PYRAMID, _PYRAMID_PACKED = range(4)    # kinds of Prepared
+
+
+class _PreparedCall:
+    """The extension's Prepared in Python: a call whose arguments are numbers already."""
+
+    def __init__(self, kind, args):
+        L = lib()
+        self._fn = (L.fc_focused_conv2d, L.fc_focused_dwconv2d, L.fc_mask_pyramid, L.fc_mask_pyramid_packed)[kind]
+        if len(args) != len(self._fn.argtypes) - 1:
+            raise ValueError("not a prepared call")
+        self._args = [a if t in (ctypes.c_void_p, ctypes.c_int32, ctypes.c_size_t) else ctypes.cast(a, t) for a, t in zip(args, self._fn.argtypes)]
+
+    def __call__(self, raw_stream):
+        return self._fn(*self._args, _current_raw_stream() if raw_stream is None else raw_stream)
+
+
+def _prepared(kind, args):
+    module = _native()
+    return (_PreparedCall if module is None else module.Prepared)(kind, args)
+
 
 def _current_raw_stream():
     c = _torch()._C
@@ -415,12 +438,12 @@ class PreparedPyramid:
         nl = len(steps)
         self._ptrs = tuple((vp * nl)(*[_ptr(lv[i]) for lv in self.levels]) for i in range(3))
         if packed:
-            self._run = _native().Prepared(_PYRAMID_PACKED, (_ptr(mask_in), 1 if packed_in else 0, n, h, w, nl, *self._tables(),
-                                                             _ptr(self._ws), self._ws.numel()))
+            self._run = _prepared(_PYRAMID_PACKED, (_ptr(mask_in), 1 if packed_in else 0, n, h, w, nl, *self._tables(),
+                                                     _ptr(self._ws), self._ws.numel()))
         else:
             if packed_in:
                 raise ValueError("a packed input mask gives packed levels: pass packed=True")
-            self._run = _native().Prepared(_PYRAMID, (_ptr(mask_in), n, h, w, nl, *self._tables(), _ptr(self._ws), self._ws.numel()))
+            self._run = _prepared(_PYRAMID, (_ptr(mask_in), n, h, w, nl, *self._tables(), _ptr(self._ws), self._ws.numel()))
         self.mask_in = mask_in   # (kept alive: the call reads it)
 
     def _tables(self):
@@ -522,8 +545,8 @@ class PreparedConv:
         self.out = out
         self._keep = (desc, x, w, bias, mask_in, mask_out, idx, count, out, workspace)
         ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-        self._run = _native().Prepared(_CONV, (ctypes.addressof(desc), _ptr(x), _ptr(mask_in), _ptr(w), _ptr(bias), _ptr(mask_out), _ptr(idx),
-                                               _ptr(count), _ptr(out), _ptr(workspace), ws_bytes))
+        self._run = _prepared(_CONV, (ctypes.addressof(desc), _ptr(x), _ptr(mask_in), _ptr(w), _ptr(bias), _ptr(mask_out), _ptr(idx),
+                                       _ptr(count), _ptr(out), _ptr(workspace), ws_bytes))
 
     def __call__(self, stream=None):
         rc = self._run(None if stream is None else stream.cuda_stream)
@@ -591,7 +614,7 @@ class PreparedDwConv:
             out = torch.empty((desc.n, ho, wo, desc.c_out), dtype=torch_dtype(desc.out_dtype), device=x.device)
         self.out = out
         self._keep = (desc, x, w, bias, mask_in, out)
-        self._run = _native().Prepared(_DWCONV, (ctypes.addressof(desc), _ptr(x), _ptr(mask_in), _ptr(w), _ptr(bias), _ptr(out)))
+        self._run = _prepared(_DWCONV, (ctypes.addressof(desc), _ptr(x), _ptr(mask_in), _ptr(w), _ptr(bias), _ptr(out)))
 
     def __call__(self, stream=None):
         rc = self._run(None if stream is None else stream.cuda_stream)

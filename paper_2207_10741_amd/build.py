@@ -1,4 +1,4 @@
-"""Build libfocused_conv.so in-tree with hipcc for gfx950, and the Python extension _native.so beside it.
+"""Build libfocused_conv.so in-tree with hipcc for gfx950, and, where PyTorch is installed, the Python extension _native.so beside it.
 
     python -m paper_2207_10741_amd.build
 """
@@ -42,8 +42,12 @@ def _run(cmd, verbose):
 
 
 def _native_command(out):
+    """The compile command of the extension, None without PyTorch (the C library needs only ROCm; binding.py makes all calls by itself then)."""
     import sysconfig
-    import torch
+    try:
+        import torch
+    except ImportError:
+        return None
     home = os.path.dirname(torch.__file__)
     return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
             "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-I", os.path.join(ROOT, "include"),
@@ -71,13 +75,15 @@ def build(verbose: bool = True) -> str:
                 obj = os.path.join(tmp, name + ".o")
                 units.append((obj, [hipcc, *HIPCC_FLAGS, *inc, "-c", src, "-o", obj]))
         with concurrent.futures.ThreadPoolExecutor(max_workers=jobs) as pool:
-            for f in [pool.submit(_run, cmd, verbose) for cmd in [cmd for _, cmd in units] + [_native_command(NATIVE + ".tmp")]]:
+            native = _native_command(NATIVE + ".tmp")
+            for f in [pool.submit(_run, cmd, verbose) for cmd in [cmd for _, cmd in units] + ([native] if native else [])]:
                 f.result()
         _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *[o for o, _ in units], "-o", OUT + ".tmp"], verbose)
     finally:
         shutil.rmtree(tmp, ignore_errors=True)
     os.replace(OUT + ".tmp", OUT)
-    os.replace(NATIVE + ".tmp", NATIVE)
+    if native:
+        os.replace(NATIVE + ".tmp", NATIVE)
     return OUT
 
 
