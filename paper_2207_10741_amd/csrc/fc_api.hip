@@ -220,6 +220,8 @@ static bool try_pair(const fc_conv_desc *d1, const fc_conv_desc *d2, const void 
     if (make_geom(d1, &g1) != FC_OK || make_geom(d2, &g2) != FC_OK) return false;
     const int dtype = d1->in_dtype;
     if (d1->out_dtype != dtype || d2->in_dtype != dtype || d2->out_dtype != dtype || !conv_pair_supported(g1, g2, dtype)) return false;
+    // (what the matrix cores do not take by itself, images of more than 16 384 rows or columns, is refused or summed in another order there)
+    if (!conv_mfma_supported(g1, dtype, dtype) || !conv_mfma_supported(g2, dtype, dtype)) return false;
     // what each call asks for by itself
     for (const void *p : {x, w1, w2, mid, (const void *)out})
         if (!p || !aligned16(p)) return false;
