@@ -912,7 +912,9 @@ int32_t fc_run_calls_unseen(const fc_call *calls, int32_t n_calls, const uint8_t
         if (unseen && unseen[i] && i + 1 < n_calls) {
             const fc_call &r = calls[i + 1];
             hipError_t e;
-            if (c.kind == FC_CALL_CONV && r.kind == FC_CALL_CONV && r.x == c.out && c.idx == r.idx && c.count == r.count &&
+            // (labels without a mask are refused below)
+            const bool labels = (at(c.mask_out) && !at(c.mask_in)) || (at(r.mask_out) && !at(r.mask_in));
+            if (c.kind == FC_CALL_CONV && r.kind == FC_CALL_CONV && r.x == c.out && c.idx == r.idx && c.count == r.count && !labels &&
                 try_pair(&d, &r.desc, at(c.x), at(c.mask_in), at(c.w), (const float *)at(c.bias),
                 at(r.w), (const float *)at(r.bias), (const int32_t *)at(c.idx), (const int32_t *)at(c.count), at(r.mask_in), at(c.out), at(r.out),
                 workspace, workspace_bytes, (hipStream_t)stream, &e)) {
