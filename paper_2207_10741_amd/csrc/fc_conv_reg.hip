@@ -644,8 +644,10 @@ __global__ __launch_bounds__(kRegThreads, RING == 2 ? 3 : 2) void k_conv_f32_rou
 
 static bool f32_rounds(const Geom &g, bool masked)
 {
+    // (channels past whole chunks: a piece past the last one stays out of range with the offset of any stage added, two rows and two pixels
+    // and less than a pixel more)
     return g.kh == 3 && g.kw == 3 && g.dw == 1 && 9 * ((g.c_in + 31) / 32) <= kF32MostStages &&
-           (g.c_in % 32 == 0 || ((int64_t)g.dh * g.w + 1) * 2 * g.c_in * 4 < (int64_t)(0xffffffffu - kOutOfRange)) &&
+           (g.c_in % 32 == 0 || ((int64_t)g.dh * g.w * 2 + 3) * g.c_in * 4 < (int64_t)(0xffffffffu - kOutOfRange)) &&
            (!masked || (!(g.flags & FC_PACKED_MASKS) && (int64_t)g.n * g.h * g.w >= 4));
 }
 
