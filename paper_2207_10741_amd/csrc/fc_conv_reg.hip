@@ -1043,8 +1043,9 @@ struct WindowCut {
     int32_t lg_pieces; // log2 of the 16-byte pieces of a pixel's window
     int32_t x_bytes, w_bytes;
     FastDiv by_line, by_kw, by_ppt;
-    FastDiv by_blocks; // 64-channel blocks of the output
-    int32_t blocks;
+    // of the workgroups: the 64-channel blocks of a span in a row or, block_major, the spans of a block; see xcd_eighth_of
+    FastDiv by_inner;
+    uint32_t inner : 26, lg_order : 5, block_major : 1;
 };
 
 template <int DT, typename TO, int V, int KS, int LG, int NG = 1>
@@ -1061,12 +1062,15 @@ __global__ __launch_bounds__(kRegThreads, 2) void k_conv_grouped_window(
     const uint32_t lds0 = (uint32_t)reinterpret_cast<uintptr_t>(lds);
     const int tid = threadIdx.x, lane = tid & 63, col = lane & 15, quarter = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // (neighbouring windows share rows of pixels: by eighths, runs of 4 .. 32 windows gain half as much.  us, as numbered -> here, half kept, m, and
-    // without a mask, d: 128 channels in 32 groups on 16 x 56 x 56 12.2 -> 11.5 m, 13.0 -> 12.4 d, 256 there 19.4 -> 18.6 m, 23.7 -> 20.4 d, 128 on
-    // 8 x 56 x 56 7.8 -> 7.4 m; masks that drop half of every image in one piece, where the eighths of few images have unlike work: 512 on 32 x 60 x 60
-    // 95.5 -> 95.9, on 2 x 60 x 60 10.9 -> 11.2, 128 on 8 x 56 x 56 7.7 -> 7.3)
-    const int unit = xcd_eighth((int)blockIdx.x, (int)gridDim.x), span = (int)fast_div((uint32_t)unit, cut.by_blocks);
-    const int first = span * kWindowSpan, blk0 = (unit - span * cut.blocks) * 64, co0 = blk0 + wave * 16;
+    int span, blk;
+    if (cut.block_major == 0) {
+        const int unit = xcd_eighth((int)blockIdx.x, (int)gridDim.x);
+        span = (int)fast_div((uint32_t)unit, cut.by_inner), blk = unit - span * (int)cut.inner;
+    } else {
+        const int unit = xcd_eighth_of((int)blockIdx.x, (int)gridDim.x, (int)cut.lg_order);
+        blk = (int)fast_div((uint32_t)unit, cut.by_inner), span = unit - blk * (int)cut.inner;
+    }
+    const int first = span * kWindowSpan, blk0 = blk * 64, co0 = blk0 + wave * 16;
     const int taps = g.kh * g.kw;
     const int win0 = (blk0 / cog) * cig; // first input channel of the workgroup's groups
     const int lg_pieces = V ? LG : cut.lg_pieces, line = V ? kQuadLine : cut.line;
@@ -1353,9 +1357,21 @@ static hipError_t launch_grouped(const Geom &g, int groups, const void *x, const
                         : !quads ? (steps <= 5 ? k_conv_grouped_window<DT, TO, 0, 5, 0> : k_conv_grouped_window<DT, TO, 0, 9, 0>)
                         : v == 1 ? (cog == 8 ? k_conv_grouped_window<DT, TO, 1, 9, 2> : k_conv_grouped_window<DT, TO, 1, 9, 3>)
                                  : k_conv_grouped_window<DT, TO, 2, 9, 4>;
-            cut.blocks = (g.c_out + 63) / 64;
-            cut.by_blocks = make_fastdiv((uint32_t)cut.blocks);
-            hipLaunchKernelGGL(kern, dim3((g.m + kWindowSpan - 1) / kWindowSpan * cut.blocks), dim3(kRegThreads), bytes, s,
+            // Neighbouring windows share rows of pixels: an XCD takes an eighth of the work in one piece, spans with all their blocks.  With a mask and fewer images
+            // than XCDs that piece may be all kept or all irrelevant.  Where the blocks are a multiple of eight an XCD then takes whole blocks; else eight spans at a
+            // time.  us, as numbered -> eighths (-> by this rule, where it is another), masks of regions, other buffers each time: 128 channels in 32 groups on
+            // 16 x 56 x 56 11.8 -> 11.1, without a mask 13.4 -> 12.8, 256 on 16 x 28 x 28 8.5 -> 7.9; 512 on 2 x 60 x 60 9.9 -> 11.0 -> 9.0, with the lower half of
+            // both images irrelevant 9.1 -> 11.2 -> 7.7; 128 on 1 x 200 x 200 9.6 -> 10.9 -> 9.8, lower half 8.4 -> 10.9 -> 8.2, on 5 x 56 x 56 6.5 -> 6.2 -> 6.3; 64 in
+            // 16 groups on 7 x 100 x 100, lower half, 7.9 -> 8.9 -> 8.2.  What loses: lower halves of as many images as XCDs (512 on 8 x 30 x 30 9.0 -> 9.4), 32 images
+            // of a map no cache holds (512 on 60 x 60, without a mask, 102.5 -> 106; 94.6 -> 92.3 where it is read again).
+            const int spans = (g.m + kWindowSpan - 1) / kWindowSpan, blocks = (g.c_out + 63) / 64;
+            const bool few = mask_in && g.n < 8;
+            if ((int64_t)spans * blocks >= 1 << 24) return hipErrorInvalidValue; // (2^32 threads; x would be past 16 GB)
+            cut.block_major = few;
+            cut.inner = few ? spans : blocks;
+            cut.by_inner = make_fastdiv(cut.inner);
+            cut.lg_order = few && blocks % 8 != 0 ? 6 : kOneSegment;
+            hipLaunchKernelGGL(kern, dim3(spans * blocks), dim3(kRegThreads), bytes, s,
                                g, cut, cig, cog, (const uint16_t *)x, mask_in, mask_out, (const uint16_t *)w, bias, (TO *)out);
             return hipGetLastError();
         }

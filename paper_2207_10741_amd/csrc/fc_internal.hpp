@@ -267,12 +267,19 @@ __device__ __forceinline__ int wave_inclusive_scan(int v)
     return v;
 }
 
-// Neighbouring workgroups on one XCD: workgroup b runs on XCD b mod 8, so with work dealt in the order of the numbers the pixels that
-// neighbours share are fetched by every XCD's L2.  Here XCD j takes the j-th contiguous eighth of the work.
+// Neighbouring units of work on one XCD: workgroup b runs on XCD b mod 8, so with units dealt in the order of the numbers the pixels that
+// neighbours share are fetched by every XCD's L2.  Here XCD j takes the j-th contiguous eighth of the units, or of every 2^lg of them.
+// (By shifts: two more arguments, for runs of any length, came to 0.4 us of a launch whose arguments no cache holds.)
 __device__ __forceinline__ int xcd_eighth(int block, int grid)
 {
     const int xcd = block & 7;
     return xcd * (grid >> 3) + min(xcd, grid & 7) + (block >> 3);
+}
+constexpr int kOneSegment = 30; // (launches have fewer workgroups)
+__device__ __forceinline__ int xcd_eighth_of(int block, int grid, int lg)
+{
+    const int base = block >> lg << lg;
+    return base + xcd_eighth(block - base, min(grid - base, 1 << lg));
 }
 
 // ---- launchers (each enqueues on `s`, returns a hipError_t) ----------------
