@@ -416,6 +416,7 @@ struct DwTileArgs {
     int32_t chunks;    // channel chunks in all: C / 8
     int32_t tiles_x, tiles;
     int32_t blocks;    // workgroups of an image and channel chunk
+    int32_t lg_order;  // order of the workgroups (tiles, images, channel chunks): see xcd_eighth_of
     FastDiv div_lanes, div_tx, div_blocks, div_n;
 };
 
@@ -426,10 +427,8 @@ __global__ __launch_bounds__(kDwThreads, 3) void k_dwconv_tile(DwTileArgs a, con
 {
     constexpr int VEC = 8, TAPS = 9, R = (PY - 1) * S + 3, Q = (PX - 1) * S + 3, N = PY * PX;
     const Geom &g = a.g;
-    // (workgroups in the order of tiles, images, channel chunks, an eighth of them on an XCD: neighbouring tiles read the same pixels.  Batch 32, as numbered ->
-    // here: 32 channels at 112 x 112 12.7 -> 12.4 us, without a mask 16.4 -> 14.4, 96 at 112 / 2 13.6 -> 12.9, 192 at 28 7.6 -> 7.3; 144 at 56, batch 64, without
-    // a mask 32.3 -> 32.8)
-    const int unit = xcd_eighth((int)blockIdx.x, (int)gridDim.x), of_image = (int)fast_div((uint32_t)unit, a.div_blocks);
+    const int unit = a.lg_order == kOneSegment ? xcd_eighth((int)blockIdx.x, (int)gridDim.x) : xcd_eighth_of((int)blockIdx.x, (int)gridDim.x, a.lg_order);
+    const int of_image = (int)fast_div((uint32_t)unit, a.div_blocks);
     const int block = unit - of_image * a.blocks, z = (int)fast_div((uint32_t)of_image, a.div_n);
     const int b = of_image - z * g.n, C = g.c_in, CT = a.lanes * VEC;
     const int tt = (int)fast_div(threadIdx.x, a.div_lanes), j = (int)threadIdx.x - tt * a.lanes;
@@ -577,6 +576,16 @@ hipError_t launch_tile(const Geom &g, const void *x, const uint8_t *mask_in, con
     a.blocks = (a.tiles + a.per_block - 1) / a.per_block;
     const int64_t grid = (int64_t)a.blocks * g.n * ctiles;
     if (grid > INT32_MAX) return hipErrorInvalidValue;
+    // Neighbouring tiles read the same pixels, so an XCD takes an eighth of the work in one piece, in the order of tiles, images, channel chunks; of maps of
+    // 64 MB and more an eighth of about eight images at a time, so that the XCDs stream through neighbouring memory.  us, as numbered -> eighths (-> by
+    // this rule, where it is another): where the maps are read again, batch 32, without a mask, 32 channels at 112 x 112 16.3 -> 14.2, 96 at 112 / 2 19.0 ->
+    // 16.2 -> 16.4, 144 at 56 17.1 -> 14.8; other buffers each time, 96 at 112 / 2 21.5 -> 22.5 -> 21.2, batch 64 38.2 -> 41.2 -> 37.4, masked and chained 28.5 ->
+    // 29.5 -> 29.0, 144 at 56 there 32.6 -> 33.5 -> 31.6, 27.9 -> 28.7 -> 28.4.  MobileNetV2 on 64 images of 224 x 224, chained, 491 -> 469, all of it in layers of 16
+    // to 64 MB (a layer's eighth is what the XCD wrote of the map in the pointwise layer before); on 64 of 256 x 256 without a mask 706 -> 672 -> 661.
+    const int64_t bytes = ((int64_t)g.n * g.h * g.w * (int64_t)sizeof(TI) + (int64_t)g.m * (int64_t)sizeof(TO)) * g.c_in;
+    a.lg_order = kOneSegment;
+    if (bytes >= 64000000)
+        for (a.lg_order = 3; (3ll << a.lg_order) < 16ll * a.blocks && a.lg_order < kOneSegment;) ++a.lg_order; // two thirds of eight images to four thirds
     a.div_blocks = make_fastdiv((uint32_t)a.blocks);
     a.div_n = make_fastdiv((uint32_t)g.n);
     hipLaunchKernelGGL((k_dwconv_tile<TI, TO, S, PY, PX>), dim3((uint32_t)grid),

@@ -18,3 +18,30 @@ def test_grouped_windows(layer, mask_kind, irr):
     out, want, keep = GR._run(layer, synth.BF16, B.F32, mask_kind=mask_kind, irr=irr)
     assert G.rel_err(G.to_f64(out), want, keep) <= GR.TOL_F32_OUT
     assert not out.cpu().numpy()[~keep].any()
+
+
+@pytest.mark.parametrize("layer", [
+    # n, h, w, c, stride; 64 MB and more: segments of 2^k workgroups, the last one short; images of one workgroup, and more than a segment has
+    (67, 57, 61, 144, 1), (9, 121, 113, 272, 2), (4001, 9, 9, 104, 1), (2, 500, 499, 72, 1), (1, 601, 700, 96, 2), (11, 60, 60, 1040, 1)])
+@pytest.mark.parametrize("masked", [True, False])
+def test_depthwise_tiles(layer, masked):
+    """The images of a batch give the bits that each gives alone."""
+    torch = G.torch_mod()
+    n, h, w, c, s = layer
+    gen = torch.Generator(device=G.dev()).manual_seed(7)
+    x = torch.randn((n, h, w, c), generator=gen, device=G.dev()).to(torch.bfloat16)
+    wt = G.to_dev(synth.he_weights(c, 3, 3, 1, B.BF16, 53, 2)[..., 0], B.BF16)
+    mask = (torch.rand((n, h, w), generator=gen, device=G.dev()) < 0.5).to(torch.uint8) if masked else None
+    desc = lambda images: B.conv_desc(images, h, w, c, c, stride=(s, s), in_dtype=B.BF16, flags=B.RELU)
+    ho, wo = B.out_dims(desc(n))
+    assert n * (h * w + ho * wo) * c * 2 >= 64000000
+    out = torch.full((n, ho, wo, c), 7.0, dtype=torch.bfloat16, device=G.dev())
+    B.focused_dwconv2d(desc(n), x, wt, mask_in=mask, out=out)
+    few = max(1, 30000000 // ((h * w + ho * wo) * c * 2))       # (as many images as stay below)
+    for i in range(0, n, few):
+        part = x[i:i + few]
+        alone = B.focused_dwconv2d(desc(part.shape[0]), part, wt, mask_in=None if mask is None else mask[i:i + few])
+        assert torch.equal(out[i:i + few], alone), i
+    if masked:
+        kept = mask[:, ::s, ::s].bool()
+        assert not out[~kept].any() and out[kept].any()
