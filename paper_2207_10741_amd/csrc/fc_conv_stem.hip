@@ -508,13 +508,18 @@ static hipError_t launch_stem_t(const Geom &g, const void *x, const uint8_t *mas
                        (size_t)kStemMaxTaps * sizeof(uint32_t) + (two_rows ? (size_t)ksteps * 2 * 3 * sizeof(uint4) : 0);
     // Sized for the dense row count (the kept count is only known on the device), capped at the workgroups that are resident together:
     // they stride over the tiles, the next one's rows looked up beside the current one, and lay out the weights once.  At 2048 a
-    // workgroup had one tile and its own weights, or a second round of workgroups was started for the rest.  us, 2048 -> resident: 3x3, 3 -> 32
-    // on 32 x 224 x 224 / 2 chained 14.8 -> 12.4, without a mask 16.7 -> 14.9; 3 -> 64 on 2 x 700 x 1244 chained 37.9 -> 35.3, on
-    // 8 x 1080 x 1920 616 -> 603; 7x7 / 2 on 32 x 224 x 224 32.5 -> 29.3, on 8 x 280 x 290 17.7 -> 15.2 (half kept).  512 or 1536 for the 3x3
-    // layers 11 .. 34 % and 7 .. 19 % slower, 512 for the 7x7 ones 3 .. 32 %.
-    // Zero-filled full-HD frames (16.6 M positions, half kept, a depth threshold as mask) inside a network 581 us so, 563 at 2048, where workgroups that are
-    // done clear rows beside others' tiles; a network on 0.75 to 4.3 M positions 238 .. 1877 us so, 248 .. 1883 at 2048.
-    const int resident = tiles >= 65536 ? 2048 : conv_grid_cus() * (two_rows ? 4 : 3) / gy;
+    // workgroup had one tile and its own weights, or a second round of workgroups was started for the rest.  us, half kept, lists given, other buffers each time,
+    // 2048 -> resident: 3x3, 3 -> 64 on 2 x 360 x 640 without a mask 19.0 -> 17.3, zero-filled 23.4 -> 18.5, chained 16.2 -> 14.0, on 8 x 1080 x 1920 without a mask 426 ->
+    // 423, chained 265 -> 266; 3 -> 32 on 32 x 224 x 224 / 2 16.7 -> 14.9, 15.7 -> 13.8, 14.4 -> 11.8; 7x7 / 2, 3 -> 64, on 32 x 224 x 224 37.3 -> 32.1, 31.6 -> 28.4,
+    // 31.1 -> 25.0, on 16 x 1080 x 1920 518 -> 512, 419 -> 405, 360 -> 349.  512 or 1536 for the 3x3 layers 11 .. 34 % and 7 .. 19 % slower, 512 for the 7x7 ones 3 .. 32 %.
+    // Workgroups that are done clear rows beside others' tiles only where more are started than are resident: kernels of few taps into more memory than the
+    // last cache level, where clearing is much of the launch.  Zero-filled, 2048 -> resident: 3x3, 3 -> 64 on 3 x 600 x 800 (184 MB) 45.3 -> 44.7, on 2 x 720 x 1280
+    // (236 MB) 55.9 -> 56.4, on 4 x 720 x 1280 107 -> 108.5, on 4 x 1080 x 1920 229 -> 239, on 8 of them 444 -> 463; 3 -> 128 on 2 x 360 x 640 (118 MB) 37.5 -> 31.5, on 2 x 600
+    // x 800 (246 MB) 57.3 -> 60.3; 3 -> 32 on 1 x 1080 x 1920 (133 MB) 48.0 -> 46.4, on 2 (265 MB) 88.4 -> 89.3; / 2 on 16 x 720 x 1280 107 -> 109; 5x5, 3 -> 64 on 1 x 1080 x
+    // 1920 (265 MB) 90.6 -> 86.1, on 4 (1 062 MB) 324 -> 332; 7x7 there 402 -> 397.
+    const int64_t out_bytes = (int64_t)g.m * g.c_out * (int64_t)sizeof(TO);
+    const bool beside = mask_in && !(g.flags & FC_SKIP_ZERO_FILL) && g.kh * g.kw <= 25 && out_bytes >= (int64_t)std::max(g.kh * g.kw, 9) * 22000000;
+    const int resident = beside ? 2048 : conv_grid_cus() * (two_rows ? 4 : 3) / gy;
     const int gx = (int)std::min<int64_t>(tiles, std::max(resident, 1));
     auto kern = two_rows ? k_conv_stem<DT, TO, true> : k_conv_stem<DT, TO, false>;
     hipLaunchKernelGGL(kern, dim3(gx, gy), dim3(kStemThreads), lds, s, g, dv, (const uint16_t *)x,

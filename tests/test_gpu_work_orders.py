@@ -45,3 +45,27 @@ def test_depthwise_tiles(layer, masked):
     if masked:
         kept = mask[:, ::s, ::s].bool()
         assert not out[~kept].any() and out[kept].any()
+
+
+@pytest.mark.parametrize("layer", [
+    # n, h, w, co, k, s: about 198 MB of output (22 MB a tap), where more workgroups are started than are resident, and below
+    (2, 601, 800, 128, 3, 1), (2, 380, 1001, 128, 3, 1), (1, 1081, 1920, 136, 5, 1), (4, 1080, 1919, 96, 3, 2)])
+def test_rgb_rows_cleared_beside_tiles(layer):
+    torch = G.torch_mod()
+    n, h, w, co, k, s = layer
+    gen = torch.Generator(device=G.dev()).manual_seed(9)
+    x = torch.randn((n, h, w, 3), generator=gen, device=G.dev()).to(torch.bfloat16)
+    wt = G.to_dev(synth.he_weights(co, k, k, 3, B.BF16, 57, 2), B.BF16)
+    mask = G.mask_dev(synth.mask_objects(n, h, w, 0.48, 57, 4))
+    outs = []
+    for flag in (0, B.SKIP_ZERO_FILL):
+        desc = B.conv_desc(n, h, w, 3, co, (k, k), (s, s), (k // 2, k // 2), in_dtype=B.BF16, flags=B.RELU | flag)
+        ho, wo = B.out_dims(desc)
+        raw = torch.full((n * ho * wo + 1, co), 7.0, dtype=torch.bfloat16, device=G.dev())
+        B.focused_conv2d(desc, x, wt, mask_in=mask, out=raw[:-1].view(n, ho, wo, co))
+        outs.append(raw)
+    keep = torch.cat([B.mask_downsample(mask, (k, k), (s, s), (k // 2, k // 2)).reshape(-1).bool(), torch.zeros(1, dtype=torch.bool, device=G.dev())])
+    filled, chained = outs
+    assert torch.equal(filled[keep], chained[keep]) and filled[keep].any()
+    assert bool((chained[~keep] == 7.0).all()) and bool((filled[-1] == 7.0).all())
+    assert not filled[:-1][~keep[:-1]].any()
