@@ -581,7 +581,7 @@ hipError_t launch_tile(const Geom &g, const void *x, const uint8_t *mask_in, con
     // this rule, where it is another): where the maps are read again, batch 32, without a mask, 32 channels at 112 x 112 16.3 -> 14.2, 96 at 112 / 2 19.0 ->
     // 16.2 -> 16.4, 144 at 56 17.1 -> 14.8; other buffers each time, 96 at 112 / 2 21.5 -> 22.5 -> 21.2, batch 64 38.2 -> 41.2 -> 37.4, masked and chained 28.5 ->
     // 29.5 -> 29.0, 144 at 56 there 32.6 -> 33.5 -> 31.6, 27.9 -> 28.7 -> 28.4.  MobileNetV2 on 64 images of 224 x 224, chained, 491 -> 469, all of it in layers of 16
-    // to 64 MB (a layer's eighth is what the XCD wrote of the map in the pointwise layer before); on 64 of 256 x 256 without a mask 706 -> 672 -> 661.
+    // to 64 MB (a layer's eighth is what the XCD wrote of the map in the pointwise layer before); on 64 of 256 x 256 without a mask, eighths -> this rule, 672 -> 661.
     const int64_t bytes = ((int64_t)g.n * g.h * g.w * (int64_t)sizeof(TI) + (int64_t)g.m * (int64_t)sizeof(TO)) * g.c_in;
     a.lg_order = kOneSegment;
     if (bytes >= 64000000)
