@@ -415,8 +415,8 @@ int32_t fc_run_calls(const fc_call *calls, int32_t n_calls, void *const *slots, 
 
 /* The same, where the caller does not look at every output.  unseen (host, n_calls bytes, or NULL): a nonzero byte
  * says that only the next call of the sequence reads this call's output and that what `out` holds afterwards is
- * undefined.  `out` has to be there all the same.  Such an output may never be written: two 1x1 layers of unit stride are one launch where
- * their weights fit on the chip.  Every other output is bit for bit what fc_run_calls writes. */
+ * undefined.  `out` has to be there all the same.  Such an output may never be written: two 1x1 layers of unit stride
+ * may be one launch.  Every other output is bit for bit what fc_run_calls writes, values that are not finite included. */
 int32_t fc_run_calls_unseen(const fc_call *calls, int32_t n_calls, const uint8_t *unseen, void *const *slots,
                             int32_t n_slots, void *workspace, size_t workspace_bytes, void *stream);
 
